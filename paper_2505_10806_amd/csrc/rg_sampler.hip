@@ -1,16 +1,39 @@
 // Epoch schedule and multi-hop neighbour sampling (Alg. 1 line 1; SAMPLE(eta(v), k) of Section II-B).
 //
 // Data layout in HBM: CSR (row_ptr int32/int64, col_idx int32) is read-only; the batch's cumulative
-// frontier `nodes` grows tier by tier; membership lives in two N-bit bitmaps (`visited` = members of
-// the cumulative frontier, `marked` = those plus the ids the current hop has sampled) and `pos[v]` maps a member to
-// its position.  All sizes that depend on the data (frontier and edge counts) stay on the device:
-// launches are sized by static upper bounds and kernels read the actual counts.
+// frontier `nodes` grows tier by tier; `visited` is the N-bit bitmap of its members.  A hop's new tier is found in one of
+// three ways (TierMode below); a member's position comes from the tier's rank words or from `pos[v]`.  All sizes that
+// depend on the data (frontier and edge counts) stay on the device: launches are sized by static upper bounds and
+// kernels read the actual counts.
 #include "rg_internal.h"
 
 namespace {
 
-constexpr int kChunk = 256;          // frontier nodes per workgroup in the count / sample kernels
-constexpr int kWordsPerBlock = 1024; // bitmap words per workgroup in the tier kernels (256 threads x 4)
+constexpr int kChunk = 1024;         // frontier nodes per workgroup in the count kernel: the unit of chunk_sum
+constexpr int kWordsPerBlock = 1024; // bitmap words per workgroup in the tier kernels of kTierAtomic (256 threads x 4)
+
+// How the ids a hop has sampled become its new tier.
+//  kTierSliced    (ascending order) no marking during the draw.  A workgroup owns an id range of slice_words * 32 ids as a bitmap
+//                 in LDS and reads the hop's whole edge list (or one split of it) for the ids of its range.  Measured on hop 2
+//                 of 8 batches of 4096 seeds at N = 10 M (15.9 M edges): reading col_idx and writing nbr takes 207 us, with
+//                 one global atomicOr per edge behind a probe 717 us (37 G atomics/s, the same for every scope), with a
+//                 byte store per edge 341 us; the LDS pass adds 44 us.
+//  kTierAtomic    (ascending order) one probe and at most one atomicOr per edge on the bitmap `marked`.
+//  kTierFirstSeen the first edge of the hop that names a node is kept per node (atomicMax).
+// The sliced way moves about N bytes per hop whatever the edges, and every slice reads every edge; the atomic way costs 27 ps
+// per edge.  Whole call, sliced against atomic: 8 batches of 4096 seeds (15,10,5) at N = 10 M 715 / 1700 us, at 40 M 733 / 1026,
+// at 100 M (80 slices) 1312 / 841; 8 batches of 64 seeds (10,5) at N = 10 M 102 / 92 us, at 40 M 239 / 160; on smaller graphs
+// both are bound by their launches, of which the sliced way has fewer.
+inline bool rg_use_slices(int slices, int64_t num_nodes, int64_t edges_bound) {
+    return slices > 0 && (num_nodes <= (4ll << 20) || edges_bound >= num_nodes / 16);
+}
+enum TierMode { kTierSliced = 0, kTierAtomic = 1, kTierFirstSeen = 2 };
+constexpr int kSliceWords = 40000;   // bitmap words of a slice: 160,000 of the 163,840 bytes of LDS a compute unit has
+constexpr int kMaxSlices = 32;
+constexpr int kSliceGroups = 256;    // workgroups the marking pass is split into at most (slices x splits x batches): one per
+                                     // compute unit, which is what a full slice's LDS admits
+constexpr int kSplitEdges = 8192;    // edges per split at least, and two per bitmap word (a split writes its slice out once)
+constexpr int kTierWords = 512;      // bitmap words per workgroup in the tier kernels of kTierSliced
 
 template <typename RP>
 __device__ __forceinline__ void rg_row_extent(const RP* __restrict__ row_ptr, int v, int64_t& start, int64_t& deg) {
@@ -113,20 +136,23 @@ struct SampleGroup {
     int32_t* tier_off[kMaxGroup];
     int32_t* indptr[kMaxGroup];       // of the current hop
     int32_t* nbr[kMaxGroup];
-    int32_t* nbr_local[kMaxGroup];    // may be NULL
     int32_t* edges_out[kMaxGroup];    // may be NULL
 };
 
 struct SampleScratch {
     uint32_t* visited;                // [group][words]
-    uint32_t* marked;                 // [group][words]
-    int32_t* pos;                     // [group][num_nodes]
+    uint32_t* marked;                 // kTierAtomic: [group][words], every id met; kTierSliced: [group][splits][words], ids of a hop
+    uint2* rank;                      // kTierSliced: [group][hops][words], tier t + 1: {its members among the 32 ids, position of the first}
+    int32_t* pos;                     // [group][num_nodes] (kTierSliced: of the seeds only)
     int32_t* chunk_sum;               // [group][chunk_stride]
     int64_t* row_start;               // [group][frontier_stride]
     int32_t* row_deg;                 // [group][frontier_stride]
     int32_t* first_key;               // [group][num_nodes], first-seen order only: 0x7FFFFFFF - (index of the first edge of
                                       // the current hop that names the node), 0 = not named (kept all-zero between hops)
     int64_t words, num_nodes, chunk_stride, frontier_stride;
+    int hops;
+    int slices, splits;               // of the marking pass: id ranges of slice_words bitmap words, parts of the edge list
+    int slice_words;
     int group;                        // batches in this call
     int xcd_map;                      // 1: consecutive workgroups belong to consecutive batches (see rg_batch)
 };
@@ -164,9 +190,40 @@ __global__ void __launch_bounds__(256) k_mark_seeds(const SampleGroup G, const S
     atomicOr(&S.marked[g * S.words + ((uint32_t)v >> 5)], 1u << (v & 31));
 }
 
+// The same in one launch for graphs of up to kMaxSlices slices: a workgroup owns one slice of a batch's ids, collects the
+// seeds of its range in LDS and writes its part of `visited`.
+// copy: `marked` starts as `visited` (kTierAtomic).
+__global__ void __launch_bounds__(1024) k_sample_init(const SampleGroup G, const SampleScratch S, int copy) {
+    extern __shared__ uint32_t slice_bits[];
+    const int g = rg_batch(S);
+    const unsigned slice = rg_block(S);
+    const int64_t w0 = (int64_t)slice * S.slice_words;
+    const int n_words = (int)(S.words - w0 < S.slice_words ? S.words - w0 : S.slice_words);
+    for (int w = threadIdx.x; w < n_words; w += 1024) slice_bits[w] = 0u;
+    const int num_seeds = G.num_seeds[g];
+    if (slice == 0 && threadIdx.x == 0) { G.tier_off[g][0] = 0; G.tier_off[g][1] = num_seeds; }
+    __syncthreads();
+    const uint32_t id0 = (uint32_t)(w0 << 5), n_ids = (uint32_t)n_words << 5;
+    for (int i = threadIdx.x; i < num_seeds; i += 1024) {
+        const int32_t v = G.seeds[g][i];
+        const uint32_t d = (uint32_t)v - id0;
+        if (d >= n_ids) continue;
+        G.nodes[g][i] = v;
+        S.pos[g * S.num_nodes + v] = i;
+        atomicOr(&slice_bits[d >> 5], 1u << (d & 31u));
+    }
+    __syncthreads();
+    uint32_t* __restrict__ visited = S.visited + g * S.words + w0;
+    uint32_t* __restrict__ marked = S.marked + g * S.words + w0;
+    for (int w = threadIdx.x; w < n_words; w += 1024) {
+        visited[w] = slice_bits[w];
+        if (copy) marked[w] = slice_bits[w];
+    }
+}
+
 // ---------------------------------------------------------------------------- per hop: sizes
-// indptr[i] = exclusive prefix of m within the node's 256-node chunk; chunk_sum[b] = chunk total;
-// row_start[i], row_deg[i] = the node's adjacency row.
+// indptr[i] = exclusive prefix of m within the node's kChunk-node chunk; chunk_sum[b] = chunk total;
+// row_start[i], row_deg[i] = the node's adjacency row.  Bound by the random row_ptr lines: 3.2 M nodes in 61 us.
 template <typename RP>
 __global__ void __launch_bounds__(kChunk) k_hop_count(const RP* __restrict__ row_ptr, const SampleGroup G, const SampleScratch S,
                                                       int hop, int fanout) {
@@ -211,7 +268,8 @@ __device__ __forceinline__ int rg_scan_in_place(int32_t* __restrict__ data, int6
     return carry_s;
 }
 
-// Chunk totals of a hop -> exclusive offsets; the hop's edge total goes behind the last indptr entry.
+// Chunk totals of a hop -> exclusive offsets; the hop's edge total goes behind the last indptr entry.  Only in front of the
+// wavefront-per-node draw: the thread-per-node draw adds up the totals in front of its own chunk itself.
 __global__ void __launch_bounds__(1024) k_scan_hop(const SampleGroup G, const SampleScratch S, int hop) {
     const int g = rg_batch(S);
     const int n_h = G.tier_off[g][hop + 1];
@@ -250,7 +308,7 @@ __device__ __forceinline__ void rg_note_first_edge(int32_t u, int64_t e, const u
 
 // General sampler: one wavefront (= one 64-thread workgroup) per frontier node, any fan-out up to
 // RG_MAX_FANOUT.  The Floyd set lives in LDS; step i tests membership of t with all lanes.
-template <bool FIRST_SEEN>
+template <int MODE>
 __global__ void __launch_bounds__(RG_WAVE) k_hop_sample_wave(const int32_t* __restrict__ col_idx, const SampleGroup G,
                                                             const SampleScratch S, int fanout, uint32_t hop, uint32_t k0,
                                                             uint32_t k1, uint32_t epoch) {
@@ -267,7 +325,7 @@ __global__ void __launch_bounds__(RG_WAVE) k_hop_sample_wave(const int32_t* __re
     const int32_t* __restrict__ row_deg = S.row_deg + g * S.frontier_stride;
     const uint32_t* __restrict__ visited = S.visited + g * S.words;
     uint32_t* __restrict__ marked = S.marked + g * S.words;
-    int32_t* __restrict__ first_key = FIRST_SEEN ? S.first_key + g * S.num_nodes : nullptr;
+    int32_t* __restrict__ first_key = MODE == kTierFirstSeen ? S.first_key + g * S.num_nodes : nullptr;
     const int lane = threadIdx.x;
     for (int64_t i = blk; i < n_h; i += rg_blocks_per_batch(S)) {
         const int32_t v = nodes[i];
@@ -279,7 +337,8 @@ __global__ void __launch_bounds__(RG_WAVE) k_hop_sample_wave(const int32_t* __re
             for (int64_t t = lane; t < deg; t += RG_WAVE) {
                 const int32_t u = col_idx[start + t];
                 nbr[base + t] = u;
-                if (FIRST_SEEN) rg_note_first_edge(u, base + t, visited, first_key); else rg_mark(u, marked);
+                if (MODE == kTierFirstSeen) rg_note_first_edge(u, base + t, visited, first_key);
+                if (MODE == kTierAtomic) rg_mark(u, marked);
             }
             continue;
         }
@@ -305,43 +364,60 @@ __global__ void __launch_bounds__(RG_WAVE) k_hop_sample_wave(const int32_t* __re
         for (int t = lane; t < k; t += RG_WAVE) {
             const int32_t u = col_idx[start + (int64_t)chosen[t]];
             nbr[base + t] = u;
-            if (FIRST_SEEN) rg_note_first_edge(u, base + t, visited, first_key); else rg_mark(u, marked);
+            if (MODE == kTierFirstSeen) rg_note_first_edge(u, base + t, visited, first_key);
+            if (MODE == kTierAtomic) rg_mark(u, marked);
         }
     }
 }
 
-// Fast sampler for fan-outs up to 32 on graphs with fewer than 2^32 edges: one thread per frontier node
-// draws (Philox + Floyd entirely in registers), the 256 nodes of a workgroup stage the col_idx offsets
-// of their picks in LDS in output order, then the whole workgroup reads col_idx and writes nbr with
-// consecutive lanes on consecutive output slots.
-template <int KMAX, bool FIRST_SEEN>
-__global__ void __launch_bounds__(kChunk) k_hop_sample_thread(const int32_t* __restrict__ col_idx, const SampleGroup G,
-                                                              const SampleScratch S, int fanout, uint32_t hop, uint32_t k0,
-                                                              uint32_t k1, uint32_t epoch) {
-    extern __shared__ uint32_t staged[];                 // kChunk * fanout col_idx offsets
+// Fast sampler for fan-outs up to 32 on graphs with fewer than 2^32 edges: NODES frontier nodes per workgroup of 256
+// threads, one thread per node draws (Philox + Floyd entirely in registers) and stages the col_idx offsets of its picks in
+// LDS in output order, then the whole workgroup reads col_idx and writes nbr with consecutive lanes on consecutive output
+// slots.  Bound by the random col_idx lines, so every thread keeps kDrawLoads of them in flight (one at a time: hop 0 of
+// 8 batches of 4096 seeds 35 us, hop 1 235 us with its marking atomics; now 15 and 66).
+// NODES = 64 spreads the reads of a frontier that fills less than two workgroups of 256 nodes per compute unit.
+constexpr int kDrawLoads = 8;
+
+template <int KMAX, int NODES, int MODE>
+__global__ void __launch_bounds__(256) k_hop_sample_thread(const int32_t* __restrict__ col_idx, const SampleGroup G,
+                                                           const SampleScratch S, int fanout, uint32_t hop, uint32_t k0,
+                                                           uint32_t k1, uint32_t epoch) {
+    extern __shared__ uint32_t staged[];                 // NODES * fanout col_idx offsets
+    __shared__ int part[4];
+    __shared__ int end_s;
     const int g = rg_batch(S);
     const unsigned blk = rg_block(S);
     const int n_h = G.tier_off[g][hop + 1];
-    const int64_t first = (int64_t)blk * kChunk;
-    if (first >= n_h) return;                            // uniform per workgroup
     int32_t* __restrict__ indptr = G.indptr[g];
+    const int64_t first = (int64_t)blk * NODES;
+    if (first >= n_h) {                                  // uniform per workgroup
+        if (n_h == 0 && blk == 0 && threadIdx.x == 0) {
+            indptr[0] = 0;
+            if (G.edges_out[g]) *G.edges_out[g] = 0;
+        }
+        return;
+    }
     int32_t* __restrict__ nbr = G.nbr[g];
     const int32_t* __restrict__ chunk_sum = S.chunk_sum + g * S.chunk_stride;
     const uint32_t* __restrict__ visited = S.visited + g * S.words;
     uint32_t* __restrict__ marked = S.marked + g * S.words;
-    int32_t* __restrict__ first_key = FIRST_SEEN ? S.first_key + g * S.num_nodes : nullptr;
+    int32_t* __restrict__ first_key = MODE == kTierFirstSeen ? S.first_key + g * S.num_nodes : nullptr;
     const int64_t i = first + threadIdx.x;
     const int k = fanout;
-    // chunk_sum[b] is the exclusive offset of chunk b; the chunk's edge count follows from its successor
-    // (or from the hop total behind the last indptr entry for the last chunk)
-    const int base = chunk_sum[blk];
-    const bool last_chunk = first + kChunk >= n_h;
-    const int chunk_edges = (last_chunk ? indptr[n_h] : chunk_sum[blk + 1]) - base;
-    if (i < n_h) {
+    // edges in front of this count chunk
+    const int chunk = (int)(first / kChunk);
+    int before = 0;
+    for (int c = threadIdx.x; c < chunk; c += 256) before += chunk_sum[c];
+    before = rg_wave_sum(before);
+    if (rg_lane() == 0) part[threadIdx.x >> 6] = before;
+    const int off0 = indptr[first];                      // of this workgroup's first node within the count chunk
+    const int n_here = (int)(n_h - first < NODES ? n_h - first : NODES);
+    int off = 0;
+    if ((int)threadIdx.x < n_here) {
         const int32_t v = G.nodes[g][i];
         const int64_t start = S.row_start[g * S.frontier_stride + i], deg = S.row_deg[g * S.frontier_stride + i];
-        const int off = indptr[i];                       // chunk-local exclusive prefix from k_hop_count
-        indptr[i] = base + off;
+        off = indptr[i] - off0;
+        if ((int)threadIdx.x == n_here - 1) end_s = off + (int)(deg <= k ? deg : k);
         if (deg <= k) {                                  // whole row, CSR order
             for (int t = 0; t < (int)deg; ++t) staged[off + t] = (uint32_t)(start + t);
         } else {
@@ -371,14 +447,147 @@ __global__ void __launch_bounds__(kChunk) k_hop_sample_thread(const int32_t* __r
         }
     }
     __syncthreads();
-    for (int e = threadIdx.x; e < chunk_edges; e += kChunk) {
-        const int32_t u = col_idx[staged[e]];
-        nbr[base + e] = u;
-        if (FIRST_SEEN) rg_note_first_edge(u, base + e, visited, first_key); else rg_mark(u, marked);
+    const int base = part[0] + part[1] + part[2] + part[3] + off0;
+    const int n_edges = end_s;
+    if ((int)threadIdx.x < n_here) indptr[i] = base + off;
+    if (threadIdx.x == 0 && first + NODES >= n_h) {
+        indptr[n_h] = base + n_edges;
+        if (G.edges_out[g]) *G.edges_out[g] = base + n_edges;
+    }
+    for (int e0 = threadIdx.x; e0 < n_edges; e0 += 256 * kDrawLoads) {
+        int32_t u[kDrawLoads];
+#pragma unroll
+        for (int q = 0; q < kDrawLoads; ++q)
+            if (e0 + 256 * q < n_edges) u[q] = col_idx[staged[e0 + 256 * q]];
+#pragma unroll
+        for (int q = 0; q < kDrawLoads; ++q) {
+            const int e = e0 + 256 * q;
+            if (e >= n_edges) break;
+            nbr[base + e] = u[q];
+            if (MODE == kTierFirstSeen) rg_note_first_edge(u[q], base + e, visited, first_key);
+            if (MODE == kTierAtomic) rg_mark(u[q], marked);
+        }
     }
 }
 
-// ---------------------------------------------------------------------------- per hop: new tier
+// ---------------------------------------------------------------------------- per hop: new tier, sliced
+// marked[split][w] = the ids of the hop's edges of that split, one workgroup per (batch, slice of ids, split of the edges).
+// The workgroups of a batch read the same list side by side, so all but the first read of a line hits L2.
+__device__ __forceinline__ void rg_slice_or(uint32_t* bits, int32_t u, uint32_t id0, uint32_t n_ids) {
+    const uint32_t d = (uint32_t)u - id0;
+    if (d < n_ids) atomicOr(&bits[d >> 5], 1u << (d & 31u));
+}
+
+__global__ void __launch_bounds__(1024) k_slice_mark(const SampleGroup G, const SampleScratch S, int hop) {
+    extern __shared__ uint32_t slice_bits[];
+    constexpr int U = 4;                                 // 16-byte loads in flight per thread
+    const int g = rg_batch(S);
+    const unsigned blk = rg_block(S);
+    const int slice = (int)(blk % (unsigned)S.slices), split = (int)(blk / (unsigned)S.slices);
+    const int64_t w0 = (int64_t)slice * S.slice_words;
+    const int n_words = (int)(S.words - w0 < S.slice_words ? S.words - w0 : S.slice_words);
+    for (int w = threadIdx.x; w < n_words; w += 1024) slice_bits[w] = 0u;
+    const int64_t n_edges = G.indptr[g][G.tier_off[g][hop + 1]];
+    const int64_t e0 = n_edges * split / S.splits;
+    const int n = (int)(n_edges * (split + 1) / S.splits - e0);
+    const int32_t* __restrict__ nbr = G.nbr[g] + e0;
+    const uint32_t id0 = (uint32_t)(w0 << 5), n_ids = (uint32_t)n_words << 5;
+    __syncthreads();
+    // the list may start at any 4-byte address: single ids up to the first 16-byte boundary and behind the last one
+    const int to_line = (int)((16u - ((uint32_t)(uintptr_t)nbr & 15u)) & 15u) / 4;
+    const int head = to_line < n ? to_line : n;
+    const int n4 = (n - head) / 4;
+    const int4* __restrict__ body = (const int4*)(nbr + head);
+    int i = threadIdx.x;
+    for (; i + (U - 1) * 1024 < n4; i += U * 1024) {
+        int4 x[U];
+#pragma unroll
+        for (int q = 0; q < U; ++q) x[q] = body[i + q * 1024];
+#pragma unroll
+        for (int q = 0; q < U; ++q) {
+            rg_slice_or(slice_bits, x[q].x, id0, n_ids);
+            rg_slice_or(slice_bits, x[q].y, id0, n_ids);
+            rg_slice_or(slice_bits, x[q].z, id0, n_ids);
+            rg_slice_or(slice_bits, x[q].w, id0, n_ids);
+        }
+    }
+    for (; i < n4; i += 1024) {
+        const int4 x = body[i];
+        rg_slice_or(slice_bits, x.x, id0, n_ids);
+        rg_slice_or(slice_bits, x.y, id0, n_ids);
+        rg_slice_or(slice_bits, x.z, id0, n_ids);
+        rg_slice_or(slice_bits, x.w, id0, n_ids);
+    }
+    if ((int)threadIdx.x < head) rg_slice_or(slice_bits, nbr[threadIdx.x], id0, n_ids);
+    const int tail = head + 4 * n4;
+    if ((int)threadIdx.x < n - tail) rg_slice_or(slice_bits, nbr[tail + threadIdx.x], id0, n_ids);
+    __syncthreads();
+    uint32_t* __restrict__ out = S.marked + ((int64_t)g * S.splits + split) * S.words + w0;
+    for (int w = threadIdx.x; w < n_words; w += 1024) out[w] = slice_bits[w];
+}
+
+// The splits' bitmaps -> the new tier's bits (into split 0) and the number of them per kTierWords words.
+__global__ void __launch_bounds__(kTierWords) k_slice_count(const SampleScratch S) {
+    constexpr int NW = kTierWords / RG_WAVE;
+    __shared__ int part[NW];
+    const int g = rg_batch(S);
+    const unsigned blk = rg_block(S);
+    const int64_t w = (int64_t)blk * kTierWords + threadIdx.x;
+    uint32_t* __restrict__ marked = S.marked + (int64_t)g * S.splits * S.words;
+    uint32_t bits = 0u;
+    if (w < S.words) {
+#pragma unroll 8
+        for (int s = 0; s < S.splits; ++s) bits |= marked[s * S.words + w];
+        bits &= ~S.visited[g * S.words + w];
+        marked[w] = bits;
+    }
+    const int c = rg_wave_sum(__popc(bits));
+    if (rg_lane() == 0) part[threadIdx.x >> 6] = c;
+    __syncthreads();
+    if (threadIdx.x < RG_WAVE) {
+        const int total = rg_wave_sum(threadIdx.x < NW ? part[threadIdx.x] : 0);
+        if (threadIdx.x == 0) S.chunk_sum[g * S.chunk_stride + blk] = total;
+    }
+}
+
+// Emits the new tier behind the current frontier, ascending, with its rank words, and makes its ids frontier members.  The
+// ids go through LDS so that they are stored by consecutive lanes (thread by thread: 135 us at hop 2 of 8 batches, 7.5 M ids;
+// now 30); a workgroup with more new ids than fit there (over half of its range) stores them directly.
+constexpr int kEmitIds = 8192;
+
+__global__ void __launch_bounds__(kTierWords) k_slice_emit(const SampleGroup G, const SampleScratch S, int hop) {
+    constexpr int NW = kTierWords / RG_WAVE;
+    __shared__ int smem[NW + 1];
+    __shared__ int part[NW];
+    __shared__ int32_t ids[kEmitIds];
+    const int g = rg_batch(S);
+    const unsigned blk = rg_block(S);
+    const int64_t w = (int64_t)blk * kTierWords + threadIdx.x;
+    const int32_t* __restrict__ chunk_sum = S.chunk_sum + g * S.chunk_stride;
+    int before = 0;                                      // new ids in front of this workgroup's words
+    for (unsigned c = threadIdx.x; c < blk; c += kTierWords) before += chunk_sum[c];
+    before = rg_wave_sum(before);
+    if (rg_lane() == 0) part[threadIdx.x >> 6] = before;
+    const uint32_t bits = w < S.words ? S.marked[(int64_t)g * S.splits * S.words + w] : 0u;
+    int total;
+    int j = rg_block_excl_scan<NW>(__popc(bits), smem, &total);                // its barriers publish part[]
+    int out = G.tier_off[g][hop + 1];
+#pragma unroll
+    for (int q = 0; q < NW; ++q) out += part[q];
+    if (threadIdx.x == 0 && blk + 1 == rg_blocks_per_batch(S)) G.tier_off[g][hop + 2] = out + total;
+    int32_t* __restrict__ nodes = G.nodes[g] + out;
+    int32_t* dst = total <= kEmitIds ? ids : nodes;
+    if (w < S.words) {
+        S.rank[((int64_t)g * S.hops + hop) * S.words + w] = make_uint2(bits, (uint32_t)(out + j));
+        if (bits) S.visited[g * S.words + w] |= bits;
+        for (uint32_t b = bits; b; b &= b - 1u) dst[j++] = (int32_t)(w << 5) + __ffs(b) - 1;
+    }
+    if (total > kEmitIds) return;                        // uniform
+    __syncthreads();
+    for (int i = threadIdx.x; i < total; i += kTierWords) nodes[i] = ids[i];
+}
+
+// ---------------------------------------------------------------------------- per hop: new tier, from `marked`
 __global__ void __launch_bounds__(256) k_tier_count(const SampleScratch S) {
     const int g = rg_batch(S);
     const unsigned blk = rg_block(S);
@@ -503,17 +712,56 @@ __global__ void __launch_bounds__(256) k_first_seen_emit(const SampleGroup G, co
         }
 }
 
+// ---------------------------------------------------------------------------- relabelling, all hops in one launch
+// A member's position never changes, so nbr_local of every hop is written after the last one.
+struct RelabelGroup {
+    const int32_t* indptr[RG_MAX_HOPS][kMaxGroup];
+    const int32_t* nbr[RG_MAX_HOPS][kMaxGroup];
+    int32_t* nbr_local[RG_MAX_HOPS][kMaxGroup];   // may be NULL
+    const int32_t* tier_off[kMaxGroup];
+};
+
 // nbr_local[e] = position of nbr[e] in the extended frontier; the hop's edge count is indptr[n_h].
-__global__ void __launch_bounds__(256) k_relabel(const SampleGroup G, const SampleScratch S, int hop) {
+// RANKED: the rank words of the tiers, latest first (a hop's edges mostly name its new tier), pos[] for the seeds.  The words
+// of one tier are N / 4 bytes (2.5 MB at N = 10 M, within one XCD's L2) where pos[] is 4 N: 142 us against 251 us for
+// 15.9 M edges; rank words alone, without the edges that name earlier tiers, would take 74 us.
+template <bool RANKED>
+__global__ void __launch_bounds__(256) k_relabel(const RelabelGroup R, const SampleScratch S) {
+    constexpr int U = 4;                                 // edges in flight per thread
     const int g = rg_batch(S);
-    const unsigned blk = rg_block(S);
-    int32_t* __restrict__ nbr_local = G.nbr_local[g];
-    if (!nbr_local) return;
-    const int32_t* __restrict__ nbr = G.nbr[g];
+    const int64_t stride = (int64_t)rg_blocks_per_batch(S) * 256;
     const int32_t* __restrict__ pos = S.pos + g * S.num_nodes;
-    const int n = G.indptr[g][G.tier_off[g][hop + 1]];
-    for (int64_t e = (int64_t)blk * blockDim.x + threadIdx.x; e < n; e += (int64_t)rg_blocks_per_batch(S) * blockDim.x)
-        nbr_local[e] = pos[nbr[e]];
+    for (int hop = S.hops - 1; hop >= 0; --hop) {
+        int32_t* __restrict__ nbr_local = R.nbr_local[hop][g];
+        if (!nbr_local) continue;
+        const int32_t* __restrict__ nbr = R.nbr[hop][g];
+        const uint2* __restrict__ rank = RANKED ? S.rank + ((int64_t)g * S.hops + hop) * S.words : nullptr;
+        const int64_t n = R.indptr[hop][g][R.tier_off[g][hop + 1]];
+        for (int64_t e0 = (int64_t)rg_block(S) * 256 + threadIdx.x; e0 < n; e0 += stride * U) {
+            int32_t u[U], r[U];
+#pragma unroll
+            for (int q = 0; q < U; ++q) u[q] = e0 + stride * q < n ? nbr[e0 + stride * q] : -1;
+            if (RANKED) {
+                uint2 x[U];
+#pragma unroll
+                for (int q = 0; q < U; ++q) x[q] = u[q] >= 0 ? rank[(uint32_t)u[q] >> 5] : make_uint2(0u, 0u);
+#pragma unroll
+                for (int q = 0; q < U; ++q) {
+                    if (u[q] < 0) continue;
+                    const uint32_t bit = 1u << (u[q] & 31);
+                    int t = hop;
+                    while (!(x[q].x & bit) && --t >= 0) x[q] = rank[((uint32_t)u[q] >> 5) - (int64_t)(hop - t) * S.words];
+                    r[q] = t >= 0 ? (int32_t)x[q].y + __popc(x[q].x & (bit - 1u)) : pos[u[q]];
+                }
+            } else {
+#pragma unroll
+                for (int q = 0; q < U; ++q) r[q] = u[q] >= 0 ? pos[u[q]] : 0;
+            }
+#pragma unroll
+            for (int q = 0; q < U; ++q)
+                if (u[q] >= 0) __builtin_nontemporal_store(r[q], &nbr_local[e0 + stride * q]);
+        }
+    }
 }
 
 // Per-batch strides of the scratch slices for a graph of N nodes and frontiers of up to `frontier` nodes.
@@ -523,7 +771,13 @@ void sampler_scratch_shape(int64_t N, int64_t frontier, int64_t max_edges, Sampl
     S.num_nodes = N;
     S.frontier_stride = rg_max64(frontier, 1);
     S.chunk_stride = rg_max64(rg_max64(rg_div_up(S.frontier_stride, kChunk), rg_div_up(max_edges, kEdgesPerBlock)),
-                              rg_max64(1, rg_div_up(S.words, kWordsPerBlock))) + 2;
+                              rg_max64(1, rg_div_up(S.words, kTierWords))) + 2;
+    const int64_t slices = rg_max64(1, rg_div_up(S.words, kSliceWords));
+    S.slices = slices <= kMaxSlices ? (int)slices : 0;       // 0: too large for the sliced marking
+    S.slice_words = S.slices ? (int)rg_max64(1, rg_div_up(S.words, slices)) : 0;
+    S.splits = 1;
+    S.hops = 1;
+    S.rank = nullptr;
     S.first_key = nullptr;
     S.group = 1;
     S.xcd_map = 1;
@@ -574,19 +828,29 @@ int grid_for(int64_t work_items, int per_block, int64_t cap) {
 
 }  // namespace
 
-rg_status rg_sampler_reserve(rg_ctx* ctx, int64_t num_nodes, int64_t max_frontier, int group, int64_t max_edges, bool first_seen) {
+rg_status rg_sampler_reserve(rg_ctx* ctx, int64_t num_nodes, int64_t max_frontier, int group, int hops, int64_t max_edges, bool first_seen) {
     SampleScratch S;
     sampler_scratch_shape(num_nodes, max_frontier, max_edges, S);
     const size_t g = (size_t)group;
     rg_status st;
     if ((st = rg_ensure(ctx, ctx->visited, g * S.words * 4)) != RG_OK) return st;
-    if ((st = rg_ensure(ctx, ctx->marked, g * S.words * 4)) != RG_OK) return st;
+    // marked: one bitmap per batch, or one per batch and split of the sliced marking (which is bounded for all batches together)
+    const size_t bitmaps = S.slices ? (size_t)rg_max64((int64_t)g, kSliceGroups / S.slices) : g;
+    if ((st = rg_ensure(ctx, ctx->marked, bitmaps * S.words * 4)) != RG_OK) return st;
+    if (S.slices && !first_seen && (st = rg_ensure(ctx, ctx->rank, g * (size_t)hops * S.words * 8)) != RG_OK) return st;
     if ((st = rg_ensure(ctx, ctx->pos, g * (size_t)num_nodes * 4)) != RG_OK) return st;
     if ((st = rg_ensure(ctx, ctx->chunk_sum, g * S.chunk_stride * 4)) != RG_OK) return st;
     if ((st = rg_ensure(ctx, ctx->row_start, g * S.frontier_stride * 8)) != RG_OK) return st;
     if ((st = rg_ensure(ctx, ctx->row_deg, g * S.frontier_stride * 4)) != RG_OK) return st;
     // first-seen order: the first-edge keys must be all-zero between hops (every hop leaves them zeroed)
     if (first_seen && (st = rg_ensure(ctx, ctx->first_key, g * (size_t)num_nodes * 4, true)) != RG_OK) return st;
+    return RG_OK;
+}
+
+// Slices use more LDS than a kernel may by default.
+rg_status rg_sampler_init(rg_ctx* ctx) {
+    RG_HIP(ctx, hipFuncSetAttribute((const void*)k_sample_init, hipFuncAttributeMaxDynamicSharedMemorySize, kSliceWords * 4));
+    RG_HIP(ctx, hipFuncSetAttribute((const void*)k_slice_mark, hipFuncAttributeMaxDynamicSharedMemorySize, kSliceWords * 4));
     return RG_OK;
 }
 
@@ -690,10 +954,11 @@ rg_status rg_sample_blocks_group(rg_ctx* ctx, const rg_csr* csr, int32_t group, 
     SampleScratch S;
     sampler_scratch_shape(N, fub_max[num_hops], max_edges, S);
     const int64_t words = S.words;
-    const int tier_blocks = (int)rg_max64(1, rg_div_up(words, kWordsPerBlock));
     ctx->last_sample_group = 0;                       // no membership bitmaps to add until this call has been queued
-    rg_status st = rg_sampler_reserve(ctx, N, fub_max[num_hops], group, max_edges, first_seen);
+    rg_status st = rg_sampler_reserve(ctx, N, fub_max[num_hops], group, num_hops, max_edges, first_seen);
     if (st != RG_OK) return st;
+    S.hops = num_hops;
+    S.rank = (uint2*)ctx->rank.p;
     S.first_key = first_seen ? (int32_t*)ctx->first_key.p : nullptr;
     S.group = group;
     S.xcd_map = ctx->knobs.xcd_map;
@@ -713,10 +978,13 @@ rg_status rg_sample_blocks_group(rg_ctx* ctx, const rg_csr* csr, int32_t group, 
         G.num_seeds[g] = live ? num_seeds[g] : 0;
         G.nodes[g] = live ? out[g].nodes : nullptr;
         G.tier_off[g] = live ? out[g].tier_off : nullptr;
-        G.indptr[g] = G.nbr[g] = G.nbr_local[g] = G.edges_out[g] = nullptr;
+        G.indptr[g] = G.nbr[g] = G.edges_out[g] = nullptr;
     }
     const unsigned ug = (unsigned)group;
 
+    int64_t edges_bound = 0;
+    for (int h = 0; h < num_hops; ++h) edges_bound += eub_max[h];
+    const TierMode mode = first_seen ? kTierFirstSeen : (rg_use_slices(S.slices, N, edges_bound) ? kTierSliced : kTierAtomic);
     if (words > 0) {
         if (ctx->sampler_dirty && ctx->first_key.bytes) {   // an earlier first-seen call stopped between a draw kernel and its emit
             const int64_t key_words = (int64_t)(ctx->first_key.bytes / 4);
@@ -724,25 +992,34 @@ rg_status rg_sample_blocks_group(rg_ctx* ctx, const rg_csr* csr, int32_t group, 
             RG_LAUNCH_CHECK(ctx, "k_clear_words");
         }
         ctx->sampler_dirty = true;       // cleared again when every launch of this call has been queued
+    }
+    if (S.slices) {
+        k_sample_init<<<(unsigned)S.slices * ug, 1024, (size_t)S.slice_words * 4, s>>>(G, S, mode == kTierAtomic ? 1 : 0);
+        RG_LAUNCH_CHECK(ctx, "k_sample_init");
+    } else {
         const int64_t group_words = (int64_t)group * words;
         k_clear_words<<<(int)rg_div_up(group_words, 256), 256, 0, s>>>(S.visited, group_words);
         RG_LAUNCH_CHECK(ctx, "k_clear_words");
-        if (!first_seen) {
+        if (mode == kTierAtomic) {
             k_clear_words<<<(int)rg_div_up(group_words, 256), 256, 0, s>>>(S.marked, group_words);
             RG_LAUNCH_CHECK(ctx, "k_clear_words");
         }
+        k_mark_seeds<<<(unsigned)(grid_for(seeds_max, 256, 1 << 30)) * ug, 256, 0, s>>>(G, S);
+        RG_LAUNCH_CHECK(ctx, "k_mark_seeds");
     }
-    k_mark_seeds<<<(unsigned)(grid_for(seeds_max, 256, 1 << 30)) * ug, 256, 0, s>>>(G, S);
-    RG_LAUNCH_CHECK(ctx, "k_mark_seeds");
 
+    RelabelGroup R = {};
+    int64_t relabel_edges = 0;
+    for (int g = 0; g < group; ++g) R.tier_off[g] = out[g].tier_off;
     for (int h = 0; h < num_hops; ++h) {
-        bool any_local = false;
         for (int g = 0; g < group; ++g) {
             G.indptr[g] = out[g].indptr[h];
             G.nbr[g] = out[g].nbr[h];
-            G.nbr_local[g] = out[g].nbr_local ? out[g].nbr_local[h] : nullptr;
             G.edges_out[g] = out[g].num_edges ? out[g].num_edges + h : nullptr;
-            any_local = any_local || G.nbr_local[g];
+            R.indptr[h][g] = out[g].indptr[h];
+            R.nbr[h][g] = out[g].nbr[h];
+            R.nbr_local[h][g] = out[g].nbr_local && eub_max[h] > 0 ? out[g].nbr_local[h] : nullptr;
+            if (R.nbr_local[h][g]) relabel_edges = rg_max64(relabel_edges, eub_max[h]);
         }
         const unsigned count_blocks = (unsigned)grid_for(fub_max[h], kChunk, 1ll << 30);
         if (rp64)
@@ -750,31 +1027,54 @@ rg_status rg_sample_blocks_group(rg_ctx* ctx, const rg_csr* csr, int32_t group, 
         else
             k_hop_count<int32_t><<<count_blocks * ug, kChunk, 0, s>>>((const int32_t*)csr->row_ptr, G, S, h, fanouts[h]);
         RG_LAUNCH_CHECK(ctx, "k_hop_count");
-        // chunk sums -> exclusive offsets; total edge count -> indptr[n_h]
-        k_scan_hop<<<ug, 1024, 0, s>>>(G, S, h);
-        RG_LAUNCH_CHECK(ctx, "k_scan_hop");
 
-        const int tok = rg_prof_begin(ctx, RG_K_SAMPLE, s);
         const int F = fanouts[h];
         if (F >= 1 && F <= 32 && csr->num_edges < (1ll << 32)) {
-            const int kmax = F <= 8 ? 8 : (F <= 16 ? 16 : 32);
-            const size_t lds = (size_t)kChunk * F * sizeof(uint32_t);
-#define RG_LAUNCH_FAST(KM, FS)                                                                                        \
-    k_hop_sample_thread<KM, FS><<<count_blocks * ug, kChunk, lds, s>>>(csr->col_idx, G, S, F, (uint32_t)h, k0, k1, epoch)
-            if (first_seen) { if (kmax == 8) RG_LAUNCH_FAST(8, true); else if (kmax == 16) RG_LAUNCH_FAST(16, true); else RG_LAUNCH_FAST(32, true); }
-            else { if (kmax == 8) RG_LAUNCH_FAST(8, false); else if (kmax == 16) RG_LAUNCH_FAST(16, false); else RG_LAUNCH_FAST(32, false); }
-#undef RG_LAUNCH_FAST
+            const int tok = rg_prof_begin(ctx, RG_K_SAMPLE, s);
+            // 64 nodes per workgroup while 256 would leave compute units without two workgroups (see the kernel)
+            const bool few = rg_div_up(fub_max[h], 256) * group < 2ll * ctx->num_cus;
+            const int nodes_per = few ? 64 : 256;
+            const unsigned draw_blocks = (unsigned)grid_for(fub_max[h], nodes_per, 1ll << 30);
+            const size_t lds = (size_t)nodes_per * F * sizeof(uint32_t);
+#define RG_LAUNCH_DRAW(KM, NP, MODE)                                                                                  \
+    k_hop_sample_thread<KM, NP, MODE><<<draw_blocks * ug, 256, lds, s>>>(csr->col_idx, G, S, F, (uint32_t)h, k0, k1, epoch)
+#define RG_LAUNCH_DRAW_K(NP, MODE)                                                                                    \
+    do { if (F <= 8) RG_LAUNCH_DRAW(8, NP, MODE); else if (F <= 16) RG_LAUNCH_DRAW(16, NP, MODE); else RG_LAUNCH_DRAW(32, NP, MODE); } while (0)
+#define RG_LAUNCH_DRAW_N(MODE) do { if (few) RG_LAUNCH_DRAW_K(64, MODE); else RG_LAUNCH_DRAW_K(256, MODE); } while (0)
+            if (mode == kTierSliced) RG_LAUNCH_DRAW_N(kTierSliced);
+            else if (mode == kTierAtomic) RG_LAUNCH_DRAW_N(kTierAtomic);
+            else RG_LAUNCH_DRAW_N(kTierFirstSeen);
+#undef RG_LAUNCH_DRAW_N
+#undef RG_LAUNCH_DRAW_K
+#undef RG_LAUNCH_DRAW
+            rg_prof_end(ctx, tok, s);
         } else {
+            // chunk sums -> exclusive offsets; total edge count -> indptr[n_h]
+            k_scan_hop<<<ug, 1024, 0, s>>>(G, S, h);
+            RG_LAUNCH_CHECK(ctx, "k_scan_hop");
+            const int tok = rg_prof_begin(ctx, RG_K_SAMPLE, s);
             const unsigned sample_blocks = (unsigned)grid_for(fub_max[h], 1, (int64_t)ctx->num_cus * 64);
-            if (first_seen)
-                k_hop_sample_wave<true><<<sample_blocks * ug, RG_WAVE, 0, s>>>(csr->col_idx, G, S, F, (uint32_t)h, k0, k1, epoch);
-            else
-                k_hop_sample_wave<false><<<sample_blocks * ug, RG_WAVE, 0, s>>>(csr->col_idx, G, S, F, (uint32_t)h, k0, k1, epoch);
+#define RG_LAUNCH_WAVE(MODE)                                                                                          \
+    k_hop_sample_wave<MODE><<<sample_blocks * ug, RG_WAVE, 0, s>>>(csr->col_idx, G, S, F, (uint32_t)h, k0, k1, epoch)
+            if (mode == kTierSliced) RG_LAUNCH_WAVE(kTierSliced);
+            else if (mode == kTierAtomic) RG_LAUNCH_WAVE(kTierAtomic);
+            else RG_LAUNCH_WAVE(kTierFirstSeen);
+#undef RG_LAUNCH_WAVE
+            rg_prof_end(ctx, tok, s);
         }
-        rg_prof_end(ctx, tok, s);
         RG_LAUNCH_CHECK(ctx, "k_hop_sample");
 
-        if (first_seen) {
+        if (mode == kTierSliced) {
+            const int64_t split_edges = rg_max64(kSplitEdges, 2 * (int64_t)S.slice_words);
+            S.splits = (int)rg_max64(1, rg_min64(eub_max[h] / split_edges, kSliceGroups / (S.slices * group)));
+            k_slice_mark<<<(unsigned)(S.slices * S.splits) * ug, 1024, (size_t)S.slice_words * 4, s>>>(G, S, h);
+            RG_LAUNCH_CHECK(ctx, "k_slice_mark");
+            const unsigned tier_blocks = (unsigned)rg_max64(1, rg_div_up(words, kTierWords));
+            k_slice_count<<<tier_blocks * ug, kTierWords, 0, s>>>(S);
+            RG_LAUNCH_CHECK(ctx, "k_slice_count");
+            k_slice_emit<<<tier_blocks * ug, kTierWords, 0, s>>>(G, S, h);
+            RG_LAUNCH_CHECK(ctx, "k_slice_emit");
+        } else if (mode == kTierFirstSeen) {
             // new tier: edges that open a node, counted per block of the edge list, scanned, emitted in edge order
             const int fs_blocks = (int)rg_max64(1, rg_div_up(eub_max[h], kEdgesPerBlock));
             k_first_seen_count<<<(unsigned)(fs_blocks) * ug, 256, 0, s>>>(G, S, h);
@@ -785,6 +1085,7 @@ rg_status rg_sample_blocks_group(rg_ctx* ctx, const rg_csr* csr, int32_t group, 
             RG_LAUNCH_CHECK(ctx, "k_first_seen_emit");
         } else {
             // new tier: count fresh bits per block, scan, emit ascending
+            const int tier_blocks = (int)rg_max64(1, rg_div_up(words, kWordsPerBlock));
             k_tier_count<<<(unsigned)(tier_blocks) * ug, 256, 0, s>>>(S);
             RG_LAUNCH_CHECK(ctx, "k_tier_count");
             k_scan_tier<<<ug, 1024, 0, s>>>(G, S, h, tier_blocks);
@@ -792,11 +1093,12 @@ rg_status rg_sample_blocks_group(rg_ctx* ctx, const rg_csr* csr, int32_t group, 
             k_tier_emit<<<(unsigned)(tier_blocks) * ug, 256, 0, s>>>(G, S, h);
             RG_LAUNCH_CHECK(ctx, "k_tier_emit");
         }
-
-        if (any_local && eub_max[h] > 0) {
-            k_relabel<<<(unsigned)(grid_for(eub_max[h], 256, (int64_t)ctx->num_cus * 16)) * ug, 256, 0, s>>>(G, S, h);
-            RG_LAUNCH_CHECK(ctx, "k_relabel");
-        }
+    }
+    if (relabel_edges > 0) {
+        const unsigned blocks = (unsigned)grid_for(relabel_edges, 1024, (int64_t)ctx->num_cus * 16);
+        if (mode == kTierSliced) k_relabel<true><<<blocks * ug, 256, 0, s>>>(R, S);
+        else k_relabel<false><<<blocks * ug, 256, 0, s>>>(R, S);
+        RG_LAUNCH_CHECK(ctx, "k_relabel");
     }
     ctx->sampler_dirty = false;
     ctx->last_sample_group = group;

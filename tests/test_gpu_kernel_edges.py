@@ -1,0 +1,79 @@
+"""GPU parity at the sizes where a kernel's tiling or a dispatch rule changes: edges of slices and blocks, remainders, the
+smallest and largest of a range.  Everything compared here is integer or copied data: exact equality with the CPU oracle."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from gpu_common import HipBatch, assert_batch_equal, log
+
+pytestmark = pytest.mark.gpu
+
+DEV = "cuda:0"
+
+
+@pytest.fixture(scope="module")
+def B():
+    from paper_2505_10806_amd import binding
+    return binding
+
+
+@pytest.fixture(scope="module")
+def ctx(B):
+    c = B.Context(0)
+    yield c
+    c.close()
+
+
+def _i32(a):
+    return torch.as_tensor(np.ascontiguousarray(a, dtype=np.int32), device=DEV)
+
+
+def _sparse_graph(n, active, degree, rng):
+    """A graph of n nodes of which `active`, spread over the whole id range (both ends among them), have about `degree`
+    neighbours, all active."""
+    ids = np.unique(np.concatenate([[0, n - 1], rng.integers(0, n, active)]))
+    deg = np.zeros(n, dtype=np.int64)
+    deg[ids] = rng.integers(0, 2 * degree + 1, ids.size)
+    rp = np.zeros(n + 1, dtype=np.int64)
+    np.cumsum(deg, out=rp[1:])
+    return rp, ids[rng.integers(0, ids.size, rp[-1])].astype(np.int32), ids
+
+
+# nodes, active nodes, mean degree, seeds per batch, fan-outs.  A slice of the marking pass covers at most 1,280,000 ids;
+# above 4 Mi nodes few edges take the atomic marking; above 40,960,000 nodes there are no slices at all.
+@pytest.mark.parametrize("n,active,degree,seeds,fanouts", [
+    (31, 31, 3, [4], (3, 2)),
+    (1_279_999, 3000, 8, [40, 7], (5, 3)),              # one slice, last word partial
+    (1_280_001, 3000, 8, [40, 7, 0], (5, 3)),           # a second slice of few words
+    (20_000, 20_000, 40, [700, 900], (32, 31)),         # over 8192 new ids within 512 words
+    (200_001, 150_000, 30, [1000, 1, 999], (25, 10)),   # the edge list split between workgroups
+    (3_000_017, 400_000, 12, [900] * 8, (40, 3)),       # wavefront-per-node draw in front of the slices
+    (4_194_337, 200_000, 12, [60, 50], (5, 3)),         # atomic marking on a graph that has slices
+    (4_194_337, 200_000, 12, [3000, 2000], (15, 10)),   # slices again: the edges outweigh the bitmaps
+    (41_000_033, 200_000, 12, [300, 200], (5, 3)),      # no slices
+])
+@pytest.mark.parametrize("first_seen", [False, True])
+def test_blocks_across_the_ways_to_build_a_tier(B, ctx, n, active, degree, seeds, fanouts, first_seen):
+    log(f"[tiers] N={n} active={active} seeds={seeds} fanouts={fanouts} first_seen={first_seen}")
+    rng = np.random.default_rng(n % 1000 + len(seeds))
+    rp, ci, ids = _sparse_graph(n, active, degree, rng)
+    csr = B.CsrGraph(torch.as_tensor(rp, device=DEV).to(torch.int32), _i32(ci))
+    order = oracle.ORDER_FIRST_SEEN if first_seen else oracle.ORDER_ASCENDING
+    lists = [rng.permutation(ids)[:k].astype(np.int32) for k in seeds]
+    outs = [B.BlockBuffers(n, ci.size, max(k, 1), fanouts, DEV) for k in seeds]
+    for j, o in enumerate(outs):                        # edge lists that start at any 4-byte address
+        for h in range(len(fanouts)):
+            shift = lambda t: torch.full((t.numel() + 3,), -7, dtype=torch.int32, device=DEV)[(j + h) % 4:][:t.numel()]  # noqa: E731
+            o.set_hop(h, shift(o.indptr[h]), shift(o.nbr[h]), shift(o.nbr_local[h]))
+    for epoch in range(2):                              # the second call finds the first one's scratch
+        ctx.sample_blocks_group(csr, [_i32(x) for x in lists], fanouts, 77, epoch, outs,
+                                node_order=B.RG_ORDER_FIRST_SEEN if first_seen else B.RG_ORDER_ASCENDING)
+        counts = torch.zeros(n, dtype=torch.int32, device=DEV)
+        ctx.access_histogram_sampled(len(seeds), counts)    # the bitmaps hold the batches' input nodes
+        want = np.zeros(n, dtype=np.uint32)
+        for j, o in enumerate(outs):
+            orc = oracle.sample_blocks(rp, ci, lists[j], fanouts, 77, epoch, order)
+            assert_batch_equal(HipBatch(o, len(fanouts)), orc, len(fanouts), f"batch {j} epoch {epoch}")
+            oracle.access_histogram(orc.input_nodes, want)
+        assert np.array_equal(counts.cpu().numpy().view(np.uint32), want)
