@@ -155,7 +155,7 @@ class EpochPipeline:
         self.consumer_stream = torch.cuda.Stream(device=device) if consumer else None
         self.ready = [torch.cuda.Event() for _ in range(self.queue_depth)]
         self.consumed = [torch.cuda.Event() for _ in range(self.queue_depth)]
-        self.rows_done = [torch.cuda.Event() for _ in range(self.queue_depth)]   # HBM-served half of the slot's batch copied
+        self.slot_free = [torch.cuda.Event() for _ in range(self.queue_depth)]   # the slot's batch copied and read on the gather stream
         self.miss_done = [torch.cuda.Event() for _ in range(self.queue_depth)]   # miss half copied
         self.prep_done = [torch.cuda.Event(), torch.cuda.Event()]                # lookups of a group made (one per half of the tickets)
         self._fork_due = {}                                                      # first ticket of a prepared group -> its half
@@ -385,6 +385,9 @@ class EpochPipeline:
         n = st.sizes[b]
         main = torch.cuda.current_stream()
         q = self._gathered % self.queue_depth
+        if self.decoupled and self._gathered:
+            # whatever the caller queued on this stream after the previous gather (on_batch) belongs to that batch's slot
+            self.slot_free[(self._gathered - 1) % self.queue_depth].record(main)
         self._gathered += 1
         self.out = self.out_ring[q]
         if self.consumer:
@@ -402,13 +405,12 @@ class EpochPipeline:
             half = self._fork_due.pop(ticket, None)
             if half is not None:
                 side.wait_event(self.prep_done[half])   # the one fork of the group: the miss stream reads the lookups' lists
-            side.wait_event(self.rows_done[q])          # the buffer's earlier batch: its HBM half (its miss half ran on this stream)
+            side.wait_event(self.slot_free[q])          # the buffer's earlier batch: its HBM half and whoever reads it on the gather stream
             if self.consumer:
                 side.wait_event(self.consumed[q])
             self.ctx.gather_run_part(ticket, B.RG_GATHER_PART_MISS, *args, stream=side)
             self.miss_done[q].record(side)
             self.ctx.gather_run_part(ticket, B.RG_GATHER_PART_HBM, *args, stream=main)
-            self.rows_done[q].record(main)
             main.wait_event(self.miss_done[q])          # the batch is whole on this stream
         else:
             self.ctx.gather_run(ticket, n, st.cache, self.wl.local_store, self.wl.remote_store, self.cfg.feat_dim, self.out,

@@ -77,3 +77,27 @@ def test_blocks_across_the_ways_to_build_a_tier(B, ctx, n, active, degree, seeds
             assert_batch_equal(HipBatch(o, len(fanouts)), orc, len(fanouts), f"batch {j} epoch {epoch}")
             oracle.access_histogram(orc.input_nodes, want)
         assert np.array_equal(counts.cpu().numpy().view(np.uint32), want)
+
+
+def test_decoupled_misses_wait_for_the_reader_of_their_buffer(B):
+    """The miss rows of batch b + 2 go into batch b's output buffer: they wait for what on_batch queued on the gather stream,
+    however late it runs (here behind a long spin)."""
+    import synth
+    from paper_2505_10806_amd.pipeline import EpochPipeline
+    wl = synth.build_workload("tiny", seed=4, device=DEV)
+    pipe = EpochPipeline(wl, device=DEV)
+    assert pipe.decoupled and pipe.queue_depth == 2
+    nb, dim = pipe.batches_per_epoch, wl.cfg.feat_dim
+    taken = []
+
+    def on_batch(p, b):
+        torch.cuda._sleep(10_000_000)                   # some milliseconds
+        taken.append(p.out[:p.sizes[b], :dim].clone())
+
+    with torch.cuda.stream(torch.cuda.Stream()):
+        pipe.run_epochs(0, 2, nb, on_batch=on_batch)
+        torch.cuda.synchronize()
+        for b in range(nb):
+            nodes = pipe.arena[b, :pipe.sizes[b]].long()
+            assert torch.equal(taken[nb + b], wl.features[nodes]), f"batch {b}"
+    pipe.close()
