@@ -51,8 +51,9 @@ struct rg_ctx {
     int64_t last_sample_nodes = 0; // input-node sets (rg_access_histogram_sampled), on graphs of this many nodes
     bool sampler_dirty = false;   // a sampling call was cut short by an error: the first-edge keys may hold stale entries
     // schedule scratch
-    RgBuf sched_keys;   // uint64[npad]
-    RgBuf sched_ids;    // int32[npad]
+    RgBuf sched_keys;   // uint64[n]
+    RgBuf sched_ids;    // int32[n]
+    RgBuf sched_buckets; // int32: pairs per bucket, scatter cursors, bucket starts
     // top-K scratch
     RgBuf topk_ctl;     // TopkCtl
     RgBuf topk_blk;     // int32[2 * nblocks]

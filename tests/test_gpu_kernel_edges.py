@@ -101,3 +101,25 @@ def test_decoupled_misses_wait_for_the_reader_of_their_buffer(B):
             nodes = pipe.arena[b, :pipe.sizes[b]].long()
             assert torch.equal(taken[nb + b], wl.features[nodes]), f"batch {b}"
     pipe.close()
+
+
+# One workgroup up to 4096 ids; buckets with LDS counters up to 8 Mi ids, with counters in HBM above.
+@pytest.mark.parametrize("n", [3, 4095, 4096, 4097, 262_145, 1_000_003, 8_388_609])
+def test_schedule_bucket_edges(ctx, n):
+    log(f"[schedule edges] n={n}")
+    ids = np.random.default_rng(n).permutation(2 * n)[:n].astype(np.int32)
+    dev = _i32(ids)
+    out = ctx.epoch_schedule(dev, (3 << 32) + 1, 9, dev)          # in place
+    assert np.array_equal(out.cpu().numpy(), oracle.epoch_schedule(ids, (3 << 32) + 1, 9))
+
+
+def test_schedule_of_ids_picked_for_one_bucket(ctx):
+    """Every id's key starts with the same two bits: one of the four buckets of 6000 ids holds them all, more than a workgroup
+    sorts in LDS; the others are empty."""
+    seed, epoch = 2025, 4
+    cand = np.arange(26_000, dtype=np.uint32)
+    top = np.array([oracle.philox4x32_10(np.array([v, 0xFFFFFFFF, 0, epoch]), np.array([seed, 0]))[0] >> 30 for v in cand])
+    ids = cand[top == 1][:6000].astype(np.int32)
+    assert ids.size == 6000
+    got = ctx.epoch_schedule(_i32(ids), seed, epoch)
+    assert np.array_equal(got.cpu().numpy(), oracle.epoch_schedule(ids, seed, epoch))
