@@ -645,7 +645,8 @@ __global__ void __launch_bounds__(256) k_plan_scatter(const int32_t* __restrict_
 // Ordered plan (num_batches + 1 <= 1024): a stable counting sort of the slots by first batch, so that every segment
 // lists its slots in ascending order, i.e. ascending remote rows: the link serves ascending host addresses
 // measurably faster than scattered ones (52 against 46 GB/s on 1 KiB rows).
-constexpr int kPlanChunk = 2048;     // slots per workgroup
+constexpr int kPlanChunk = 1024;     // slots per workgroup, one per thread
+constexpr int kPlanKeyBits = 10;
 
 __device__ __forceinline__ int rg_plan_key(const uint32_t* __restrict__ first_batch, int32_t v, int num_batches) {
     const uint32_t f = first_batch[v];
@@ -660,65 +661,77 @@ __global__ void __launch_bounds__(1024) k_plan_block_hist(const int32_t* __restr
     const int n_seg = num_batches + 1;
     if ((int)threadIdx.x < n_seg) h[threadIdx.x] = 0;
     __syncthreads();
-    const int64_t k = *num_cached;
-    const int64_t s0 = (int64_t)blockIdx.x * kPlanChunk;
-    for (int i = threadIdx.x; i < kPlanChunk; i += blockDim.x) {
-        const int64_t s = s0 + i;
-        if (s < k) atomicAdd(&h[rg_plan_key(first_batch, cache_ids[s], num_batches)], 1);
-    }
+    const int64_t s = (int64_t)blockIdx.x * kPlanChunk + threadIdx.x;
+    if (s < *num_cached) atomicAdd(&h[rg_plan_key(first_batch, cache_ids[s], num_batches)], 1);
     __syncthreads();
     if ((int)threadIdx.x < n_seg) hist[(int64_t)threadIdx.x * nblocks + blockIdx.x] = h[threadIdx.x];
 }
 
-// One workgroup: in-place exclusive scan of hist (key-major), segment starts to offsets[0..n_seg], total to offsets[n_seg].
-__global__ void __launch_bounds__(1024) k_plan_hist_scan(int32_t* __restrict__ hist, int64_t n, int nblocks, int n_seg,
-                                                         int32_t* __restrict__ offsets) {
-    __shared__ int smem[1024 / RG_WAVE + 1];
-    __shared__ int carry_s;
-    if (threadIdx.x == 0) carry_s = 0;
-    __syncthreads();
-    for (int64_t base = 0; base < n; base += 1024) {
-        const int64_t i = base + threadIdx.x;
-        const int x = i < n ? hist[i] : 0;
-        int total;
-        const int excl = rg_block_excl_scan<1024 / RG_WAVE>(x, smem, &total);
-        const int carry = carry_s;
-        if (i < n) {
-            hist[i] = carry + excl;
-            if (i % nblocks == 0) offsets[i / nblocks] = carry + excl;
-        }
-        __syncthreads();
-        if (threadIdx.x == 0) carry_s = carry + total;
-        __syncthreads();
+// One workgroup per key: in-place exclusive scan of the key's chunks, its total to total[key].  (One workgroup for all keys
+// took 39 us for 193 keys x 180 chunks.)
+__global__ void __launch_bounds__(256) k_plan_row_scan(int32_t* __restrict__ hist, int nblocks, int32_t* __restrict__ total) {
+    __shared__ int smem[256 / RG_WAVE + 1];
+    int32_t* __restrict__ row = hist + (int64_t)blockIdx.x * nblocks;
+    int carry = 0;
+    for (int base = 0; base < nblocks; base += 256) {
+        const int i = base + threadIdx.x;
+        const int x = i < nblocks ? row[i] : 0;
+        int sum;
+        const int excl = rg_block_excl_scan<256 / RG_WAVE>(x, smem, &sum);
+        if (i < nblocks) row[i] = carry + excl;
+        carry += sum;
     }
-    if (threadIdx.x == 0) offsets[n_seg] = carry_s;
+    if (threadIdx.x == 0) total[blockIdx.x] = carry;
 }
 
-// Thread `key` of a workgroup walks the chunk's keys in slot order and emits the chunk's slots of that key.
-__global__ void __launch_bounds__(1024) k_plan_block_scatter(const int32_t* __restrict__ cache_ids, const int64_t* __restrict__ num_cached,
-                                                             const uint32_t* __restrict__ first_batch, const int32_t* __restrict__ home,
-                                                             int num_batches, int nblocks, const int32_t* __restrict__ hist,
-                                                             int32_t* __restrict__ list) {
-    __shared__ uint16_t keys[kPlanChunk];
-    __shared__ int32_t rrow[kPlanChunk];
+// Every slot to its place: the keys in front of its own, its key's slots in earlier chunks, in earlier wavefronts of this
+// chunk, in lower lanes.  Lanes of the same key find each other with one ballot per key bit; the wavefronts' counts per key
+// meet in LDS.  (One thread per key walking the chunk's keys took 169 us for 367 k slots, 193 keys; now 13.)
+__global__ void __launch_bounds__(kPlanChunk) k_plan_block_scatter(const int32_t* __restrict__ cache_ids, const int64_t* __restrict__ num_cached,
+                                                                   const uint32_t* __restrict__ first_batch, const int32_t* __restrict__ home,
+                                                                   int num_batches, int nblocks, const int32_t* __restrict__ hist,
+                                                                   const int32_t* __restrict__ total, int32_t* __restrict__ offsets,
+                                                                   int32_t* __restrict__ list) {
+    constexpr int NW = kPlanChunk / RG_WAVE;
+    __shared__ uint16_t cnt[NW][1024];   // slots of a key in the wavefront, then in the earlier wavefronts
+    __shared__ int key_base[1024];
+    __shared__ int smem[NW + 1];
+    const int n_seg = num_batches + 1;
+    const int wave = threadIdx.x >> 6, lane = rg_lane();
+    for (int i = threadIdx.x; i < NW * 1024 / 2; i += kPlanChunk) ((uint32_t*)cnt)[i] = 0u;
     const int64_t k = *num_cached;
-    const int64_t s0 = (int64_t)blockIdx.x * kPlanChunk;
-    const int cnt = (int)(k - s0 < kPlanChunk ? (k - s0 > 0 ? k - s0 : 0) : kPlanChunk);
-    for (int i = threadIdx.x; i < cnt; i += blockDim.x) {
-        const int32_t v = cache_ids[s0 + i];
-        keys[i] = (uint16_t)rg_plan_key(first_batch, v, num_batches);
-        rrow[i] = (int32_t)((uint32_t)home[v] & RG_ROW_MASK);
+    const int64_t s = (int64_t)blockIdx.x * kPlanChunk + threadIdx.x;
+    const int32_t v = s < k ? cache_ids[s] : 0;
+    const int key = s < k ? rg_plan_key(first_batch, v, num_batches) : 1 << kPlanKeyBits;   // no key: matches only its like
+    const int32_t row = s < k ? (int32_t)((uint32_t)home[v] & RG_ROW_MASK) : 0;
+    int sum;
+    const int mine = (int)threadIdx.x < n_seg ? total[threadIdx.x] : 0;
+    const int before = rg_block_excl_scan<NW>(mine, smem, &sum);      // its barriers also end the clearing of cnt
+    if ((int)threadIdx.x < n_seg) {
+        key_base[threadIdx.x] = before + hist[(int64_t)threadIdx.x * nblocks + blockIdx.x];
+        if (blockIdx.x == 0) offsets[threadIdx.x] = before;
+    }
+    if (blockIdx.x == 0 && threadIdx.x == 0) offsets[n_seg] = sum;
+    unsigned long long same = ~0ull;
+#pragma unroll
+    for (int q = 0; q <= kPlanKeyBits; ++q) {
+        const unsigned long long ones = __ballot((key >> q) & 1);
+        same &= (key >> q) & 1 ? ones : ~ones;
+    }
+    const int rank = __popcll(same & ((1ull << lane) - 1ull));
+    if (s < k && rank == 0) cnt[wave][key] = (uint16_t)__popcll(same);
+    __syncthreads();
+    if ((int)threadIdx.x < n_seg) {
+        int run = 0;
+#pragma unroll
+        for (int w = 0; w < NW; ++w) { const int c = cnt[w][threadIdx.x]; cnt[w][threadIdx.x] = (uint16_t)run; run += c; }
     }
     __syncthreads();
-    const int key = threadIdx.x;
-    if (key > num_batches) return;
-    int64_t pos = hist[(int64_t)key * nblocks + blockIdx.x];
-    for (int i = 0; i < cnt; ++i)
-        if (keys[i] == key) {
-            list[2 * pos] = (int32_t)(s0 + i);
-            list[2 * pos + 1] = rrow[i];
-            ++pos;
-        }
+    if (s < k) {
+        const int64_t j = (int64_t)key_base[key] + cnt[wave][key] + rank;
+        list[2 * j] = (int32_t)s;
+        list[2 * j + 1] = row;
+    }
 }
 
 // ---------------------------------------------------------------------------- plan segments straight from the sampler's bitmaps
@@ -1083,8 +1096,9 @@ rg_status rg_plan_prefetch(rg_ctx* ctx, const rg_cache* cache, const int32_t* ho
         // ordered plan: stable counting sort by first batch
         const int nblocks = (int)rg_max64(1, rg_div_up(rows_ub, kPlanChunk));
         const int64_t n_hist = (int64_t)n_seg * nblocks;
-        if ((st = rg_ensure(ctx, ctx->plan_cursor, (size_t)n_hist * 4)) != RG_OK) return st;
+        if ((st = rg_ensure(ctx, ctx->plan_cursor, (size_t)(n_hist + n_seg) * 4)) != RG_OK) return st;
         int32_t* hist = (int32_t*)ctx->plan_cursor.p;
+        int32_t* total = hist + n_hist;
         if (rows_ub == 0) {
             k_zero_i32<<<(n_seg + 1 + 255) / 256, 256, 0, s>>>(plan->offsets, n_seg + 1);
             RG_LAUNCH_CHECK(ctx, "k_zero_i32");
@@ -1092,10 +1106,10 @@ rg_status rg_plan_prefetch(rg_ctx* ctx, const rg_cache* cache, const int32_t* ho
         }
         k_plan_block_hist<<<nblocks, 1024, 0, s>>>(cache->cache_ids, cache->num_cached, first_batch, plan->num_batches, nblocks, hist);
         RG_LAUNCH_CHECK(ctx, "k_plan_block_hist");
-        k_plan_hist_scan<<<1, 1024, 0, s>>>(hist, n_hist, nblocks, n_seg, plan->offsets);
-        RG_LAUNCH_CHECK(ctx, "k_plan_hist_scan");
-        k_plan_block_scatter<<<nblocks, 1024, 0, s>>>(cache->cache_ids, cache->num_cached, first_batch, home, plan->num_batches,
-                                                      nblocks, hist, plan->list);
+        k_plan_row_scan<<<n_seg, 256, 0, s>>>(hist, nblocks, total);
+        RG_LAUNCH_CHECK(ctx, "k_plan_row_scan");
+        k_plan_block_scatter<<<nblocks, kPlanChunk, 0, s>>>(cache->cache_ids, cache->num_cached, first_batch, home, plan->num_batches,
+                                                            nblocks, hist, total, plan->offsets, plan->list);
         RG_LAUNCH_CHECK(ctx, "k_plan_block_scatter");
         return RG_OK;
     }

@@ -123,3 +123,23 @@ def test_schedule_of_ids_picked_for_one_bucket(ctx):
     assert ids.size == 6000
     got = ctx.epoch_schedule(_i32(ids), seed, epoch)
     assert np.array_equal(got.cpu().numpy(), oracle.epoch_schedule(ids, seed, epoch))
+
+
+# Chunks of 1024 slots, wavefronts of 64; one key for all slots, a key per slot, keys in descending order.
+@pytest.mark.parametrize("slots", [1, 63, 65, 1024, 1025, 70_001])
+@pytest.mark.parametrize("pattern", ["one", "cycle", "descending", "random"])
+def test_ordered_plan_chunk_edges(B, ctx, slots, pattern):
+    log(f"[plan] slots={slots} pattern={pattern}")
+    nb = 1023 if pattern != "random" else 192
+    first = {"one": np.full(slots, 5), "cycle": np.arange(slots) % (nb + 1), "descending": nb - np.arange(slots) * (nb + 1) // slots,
+             "random": np.random.default_rng(slots).integers(0, nb + 2, slots)}[pattern].astype(np.int32)
+    home = _i32((2 << 30) + np.arange(slots)[::-1].astype(np.int64) - (1 << 32))       # every node remote, rows descending
+    cache = B.FeatureCache(slots, slots, 4, DEV)
+    ctx.build_cache(torch.ones(slots, dtype=torch.int32, device=DEV), home, None, 4, cache)
+    plan = B.PrefetchPlan(slots, nb, DEV)
+    ctx.plan_prefetch(cache, home, _i32(first), plan)
+    key = np.minimum(first, nb)
+    order = np.argsort(key, kind="stable")
+    pairs = plan.list.cpu().numpy().reshape(-1, 2)
+    assert np.array_equal(pairs[:, 0], order) and np.array_equal(pairs[:, 1], slots - 1 - order)
+    assert np.array_equal(plan.offsets.cpu().numpy(), np.searchsorted(key[order], np.arange(nb + 2)))
