@@ -112,10 +112,13 @@ rg_status rg_create(int device, rg_ctx** out) {
         delete ctx;
         return rg_set_error(nullptr, RG_ERR_HIP, "rg_create: hipEventCreate failed");
     }
-    if (rg_gather_static_init(ctx) != RG_OK || rg_sampler_init(ctx) != RG_OK) {
+    rg_status st = rg_gather_static_init(ctx);
+    if (st == RG_OK) st = rg_sampler_init(ctx);
+    if (st == RG_OK) st = rg_ensure(ctx, ctx->hist_bounds, (size_t)RG_HIST_BOUNDS * 4);   // the epoch histogram allocates nothing
+    if (st != RG_OK) {
         memcpy(g_create_error, ctx->err, sizeof(g_create_error));
         rg_destroy(ctx);
-        return RG_ERR_HIP;
+        return st;
     }
     // launch-shape knobs: read here once, never on the call paths
     RgKnobs& k = ctx->knobs;
@@ -139,7 +142,7 @@ void rg_destroy(rg_ctx* ctx) {
     (void)hipSetDevice(ctx->device);
     (void)hipDeviceSynchronize();
     RgBuf* bufs[] = {&ctx->visited, &ctx->marked, &ctx->rank, &ctx->pos, &ctx->chunk_sum, &ctx->row_start, &ctx->row_deg, &ctx->first_key, &ctx->sched_keys, &ctx->sched_ids, &ctx->sched_buckets,
-                     &ctx->topk_ctl, &ctx->topk_blk, &ctx->topk_caps, &ctx->pf_list, &ctx->pf_ctl, &ctx->plan_cursor, &ctx->claim_bits, &ctx->claim_blk, &ctx->gather_src, &ctx->miss_list,
+                     &ctx->hist_bounds, &ctx->topk_ctl, &ctx->topk_blk, &ctx->topk_caps, &ctx->pf_list, &ctx->pf_ctl, &ctx->plan_cursor, &ctx->claim_bits, &ctx->claim_blk, &ctx->gather_src, &ctx->miss_list,
                      &ctx->gather_ctl};
     for (RgBuf* b : bufs)
         if (b->p) (void)hipFree(b->p);

@@ -9,6 +9,8 @@
 
 #include "rapidgnn.h"
 
+#define RG_HIST_BOUNDS (2ll << 20)   // entries of the epoch histogram's bounds per launch (one batch of 2^30 nodes and 8 hops fits)
+
 // A growable device allocation owned by the context.
 struct RgBuf {
     void* p = nullptr;
@@ -54,6 +56,7 @@ struct rg_ctx {
     RgBuf sched_keys;   // uint64[n]
     RgBuf sched_ids;    // int32[n]
     RgBuf sched_buckets; // int32: pairs per bucket, scatter cursors, bucket starts
+    RgBuf hist_bounds;  // int32[RG_HIST_BOUNDS], made by rg_create: where the id ranges of the epoch histogram begin in every run
     // top-K scratch
     RgBuf topk_ctl;     // TopkCtl
     RgBuf topk_blk;     // int32[2 * nblocks]

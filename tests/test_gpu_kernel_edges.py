@@ -143,3 +143,32 @@ def test_ordered_plan_chunk_edges(B, ctx, slots, pattern):
     pairs = plan.list.cpu().numpy().reshape(-1, 2)
     assert np.array_equal(pairs[:, 0], order) and np.array_equal(pairs[:, 1], slots - 1 - order)
     assert np.array_equal(plan.offsets.cpu().numpy(), np.searchsorted(key[order], np.arange(nb + 2)))
+
+
+# Ranges of 512 ids at least, two workgroups per compute unit, 2 Mi bounds per launch; runs whose ids are far from proportional.
+@pytest.mark.parametrize("n,batches,hops", [(511, 3, 1), (513, 3, 2), (262_145, 9, 2), (300_000, 5000, 1), (5_000_011, 2, 3)])
+@pytest.mark.parametrize("skew", [1, 4])
+def test_epoch_histogram_range_edges(B, ctx, n, batches, hops, skew):
+    log(f"[histogram ranges] N={n} batches={batches} hops={hops} skew={skew}")
+    rng = np.random.default_rng(n + skew)
+    per = min(n // (hops + 1), 40_000 if batches < 10 else 60)
+    arena = np.zeros((batches, per * hops + 2), dtype=np.int32)
+    tier_offs = np.zeros((batches, hops + 2), dtype=np.int32)
+    want, first = np.zeros(n, dtype=np.uint32), np.full(n, 0xFFFFFFFF, dtype=np.uint32)
+    for b in range(batches):
+        ids = np.unique((n * rng.random(per * hops) ** skew).astype(np.int32))       # distinct; skew 4 crowds the low ids
+        ids = np.union1d(ids, [0, n - 1])[:arena.shape[1]].astype(np.int32)
+        tier = rng.integers(0, hops + 1, ids.size) if b % 3 else np.full(ids.size, hops)   # every third batch: one full tier
+        parts = [ids[tier == t] for t in range(hops + 1)]
+        arena[b, :ids.size] = np.concatenate([rng.permutation(parts[0])] + parts[1:])
+        tier_offs[b, 1:] = np.cumsum([p.size for p in parts])
+        oracle.access_histogram(ids, want)
+        first[ids] = np.minimum(first[ids], b)
+    counts = torch.zeros(n, dtype=torch.int32, device=DEV)
+    got_first = torch.full((n,), -1, dtype=torch.int32, device=DEV)
+    most = int(tier_offs[:, 1].max())
+    ctx.access_histogram_epoch(_i32(arena), _i32(tier_offs), batches, hops, most, counts, first_batch=got_first)
+    assert np.array_equal(counts.cpu().numpy().view(np.uint32), want)
+    assert np.array_equal(got_first.cpu().numpy().view(np.uint32), first)
+    ctx.access_histogram_epoch(_i32(arena), _i32(tier_offs), batches, hops, most, counts)
+    assert np.array_equal(counts.cpu().numpy().view(np.uint32), 2 * want)
