@@ -145,75 +145,87 @@ __global__ void __launch_bounds__(256) k_histogram_seeds(const int32_t* __restri
 // the period (a few hundred), so one streaming pass with a histogram of the counts clamped to kLowBins - 1 resolves T
 // whenever T < kLowBins - 1.  Only when the K_eff-th best candidate sits in the clamped last bin do the four byte passes
 // of a most-significant-byte-first radix select run; otherwise their kernels return at once.
+// The histograms stay in TopkCtl and the kernels up to the count read the threshold off them themselves (rg_topk_state, 8 KB
+// from L2 per workgroup): a launch of one workgroup between two passes costs 4.5 us, and there were five of them.
 constexpr int kLowBins = 2048;
 constexpr int kBallotBins = 4;       // counts 1..kBallotBins are tallied with wave ballots instead of LDS atomics
 
-struct TopkCtl {
-    uint32_t prefix;     // the threshold T (radix passes: its resolved high bytes)
+struct TopkState {
+    uint32_t T;          // the threshold (while radix passes are open: its resolved high bytes)
     uint32_t need;       // how many of the candidates tied with T are to be taken
     uint32_t k_eff;
-    uint32_t resolved;   // 1: T and need are final, the radix passes are skipped
+    uint32_t resolved;   // 1: T and need are final without radix passes
+};
+
+struct TopkCtl {
     uint32_t hist[4][256];
     uint32_t low[kLowBins];          // candidates per clamped count
     unsigned long long ovf_sum;      // sum of the counts of the candidates in the last (clamped) bin
+    TopkState state;                 // as k_topk_count found it
 };
 
 __device__ __forceinline__ bool rg_is_candidate(uint32_t home_word, uint32_t count) {
     return (home_word >> RG_TAG_SHIFT) == RG_TAG_REMOTE && count >= 1u;
 }
 
-// force_radix = the address of a flag that, when set, sends this selection through the radix passes.
-__global__ void __launch_bounds__(256) k_topk_init(TopkCtl* __restrict__ ctl, const uint32_t* __restrict__ skip_flag) {
-    if (skip_flag) {                 // a later selection of the hit curve: keep the low histogram, redo only the radix state
-        for (int i = threadIdx.x; i < 4 * 256; i += 256) (&ctl->hist[0][0])[i] = 0u;
-        if (threadIdx.x == 0) { ctl->prefix = 0u; ctl->need = 0u; ctl->k_eff = 0u; ctl->resolved = *skip_flag; }
-        return;
-    }
+__global__ void __launch_bounds__(256) k_topk_init(TopkCtl* __restrict__ ctl, int hist_only) {
     uint32_t* w = (uint32_t*)ctl;
-    for (int i = threadIdx.x; i < (int)(sizeof(TopkCtl) / 4); i += 256) w[i] = 0u;
+    const int n = (int)((hist_only ? sizeof(ctl->hist) : sizeof(TopkCtl)) / 4);      // hist_only: a later selection of the hit curve
+    for (int i = blockIdx.x * 256 + threadIdx.x; i < n; i += gridDim.x * 256) w[i] = 0u;
 }
 
-// low[min(count, kLowBins - 1)] += 1 for every candidate; ovf_sum += count for those in the last bin.
-__global__ void __launch_bounds__(256) k_topk_hist_low(const uint32_t* __restrict__ counts, const int32_t* __restrict__ home, int64_t n,
-                                                       TopkCtl* __restrict__ ctl) {
+// low[min(count, kLowBins - 1)] += 1 for every candidate; ovf_sum += count for those in the last bin.  One workgroup per
+// compute unit: with more of them their additions to the same few bins queue up (1196 workgroups 38 us at 2.4 M nodes).
+__global__ void __launch_bounds__(1024) k_topk_hist_low(const uint32_t* __restrict__ counts, const int32_t* __restrict__ home, int64_t n,
+                                                        TopkCtl* __restrict__ ctl) {
+    constexpr int U = 4;
     __shared__ uint32_t h[kLowBins];
     __shared__ unsigned long long ovf_s;
-    for (int i = threadIdx.x; i < kLowBins; i += 256) h[i] = 0u;
+    for (int i = threadIdx.x; i < kLowBins; i += 1024) h[i] = 0u;
     if (threadIdx.x == 0) ovf_s = 0ull;
     __syncthreads();
     unsigned long long ovf = 0ull;
     const int lane = rg_lane();
-    for (int64_t v0 = (int64_t)blockIdx.x * 256; v0 < n; v0 += (int64_t)gridDim.x * 256) {     // uniform per workgroup
-        const int64_t v = v0 + threadIdx.x;
-        uint32_t bin = 0u;                                   // bin 0: not a candidate
-        if (v < n) {
-            const uint32_t c = counts[v];
-            if (rg_is_candidate((uint32_t)home[v], c)) {
-                bin = c < (uint32_t)(kLowBins - 1) ? c : (uint32_t)(kLowBins - 1);
-                if (c >= (uint32_t)(kLowBins - 1)) ovf += c;
-            }
-        }
-        // most candidates of a long-tailed distribution have a count of 1..4: one LDS atomic per wavefront for each
+    for (int64_t v0 = (int64_t)blockIdx.x * (1024 * U); v0 < n; v0 += (int64_t)gridDim.x * (1024 * U)) {   // uniform per workgroup
+        uint32_t c[U], hw[U];
 #pragma unroll
-        for (uint32_t q = 1; q <= (uint32_t)kBallotBins; ++q) {
-            const unsigned long long m = __ballot(bin == q);
-            if (lane == 0 && m) atomicAdd(&h[q], (uint32_t)__popcll(m));
+        for (int u = 0; u < U; ++u) {
+            const int64_t v = v0 + u * 1024 + threadIdx.x;
+            c[u] = v < n ? counts[v] : 0u;
+            hw[u] = v < n ? (uint32_t)home[v] : 0u;
         }
-        if (bin > (uint32_t)kBallotBins) atomicAdd(&h[bin], 1u);
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            uint32_t bin = 0u;                               // bin 0: not a candidate
+            if (rg_is_candidate(hw[u], c[u])) {
+                bin = c[u] < (uint32_t)(kLowBins - 1) ? c[u] : (uint32_t)(kLowBins - 1);
+                if (c[u] >= (uint32_t)(kLowBins - 1)) ovf += c[u];
+            }
+            // most candidates of a long-tailed distribution have a count of 1..4: one LDS atomic per wavefront for each
+#pragma unroll
+            for (uint32_t q = 1; q <= (uint32_t)kBallotBins; ++q) {
+                const unsigned long long m = __ballot(bin == q);
+                if (lane == 0 && m) atomicAdd(&h[q], (uint32_t)__popcll(m));
+            }
+            if (bin > (uint32_t)kBallotBins) atomicAdd(&h[bin], 1u);
+        }
     }
     if (ovf) atomicAdd(&ovf_s, ovf);
     __syncthreads();
-    for (int i = threadIdx.x; i < kLowBins; i += 256) {
+    for (int i = threadIdx.x; i < kLowBins; i += 1024) {
         const uint32_t mine = h[i];
         if (mine) atomicAdd(&ctl->low[i], mine);
     }
     if (threadIdx.x == 0 && ovf_s) atomicAdd(&ctl->ovf_sum, ovf_s);
 }
 
-// One workgroup: K_eff = min(capacity, #candidates); T = the bin holding the K_eff-th best candidate.
-__global__ void __launch_bounds__(256) k_topk_pick_low(TopkCtl* __restrict__ ctl, int64_t capacity, int64_t* __restrict__ num_cached) {
-    __shared__ int smem[256 / RG_WAVE + 1];
-    constexpr int PER = kLowBins / 256;                      // thread t owns bins kLowBins-1-PER*t downwards
+// K_eff = min(capacity, #candidates) and its threshold, from the low histogram and, where that leaves it open, the first
+// `passes` byte histograms.  Every thread of a workgroup of NT threads calls it.
+template <int NT>
+__device__ __forceinline__ TopkState rg_topk_state(const TopkCtl* __restrict__ ctl, int64_t capacity, int passes) {
+    __shared__ int smem[NT / RG_WAVE + 1];
+    __shared__ TopkState st;
+    constexpr int PER = kLowBins / NT;                       // thread t owns bins kLowBins-1-PER*t downwards
     uint32_t h[PER];
     int mine = 0;
 #pragma unroll
@@ -222,78 +234,52 @@ __global__ void __launch_bounds__(256) k_topk_pick_low(TopkCtl* __restrict__ ctl
         mine += (int)h[j];
     }
     int total;
-    int above = rg_block_excl_scan<256 / RG_WAVE>(mine, smem, &total);     // candidates in strictly larger bins
+    int above = rg_block_excl_scan<NT / RG_WAVE>(mine, smem, &total);     // candidates in strictly larger bins
     const uint64_t k = (uint64_t)capacity < (uint64_t)total ? (uint64_t)capacity : (uint64_t)total;
-    if (threadIdx.x == 0) {
-        ctl->k_eff = (uint32_t)k;
-        if (num_cached) *num_cached = (int64_t)k;
-        if (k == 0) { ctl->prefix = 0xFFFFFFFFu; ctl->need = 0u; ctl->resolved = 1u; }   // a threshold no count reaches
-    }
-    if (k == 0) return;
+    if (k == 0) return TopkState{0xFFFFFFFFu, 0u, 0u, 1u};                // uniform; a threshold no count reaches
 #pragma unroll
     for (int j = 0; j < PER; ++j) {
         const int bin = kLowBins - 1 - (PER * (int)threadIdx.x + j);
-        if ((uint64_t)above < k && k <= (uint64_t)above + h[j]) {         // exactly one bin satisfies this
-            if (bin < kLowBins - 1) { ctl->prefix = (uint32_t)bin; ctl->need = (uint32_t)(k - above); ctl->resolved = 1u; }
-            else ctl->resolved = 0u;                                       // inside the clamped bin: radix passes decide
-        }
+        if ((uint64_t)above < k && k <= (uint64_t)above + h[j])           // exactly one bin satisfies this
+            st = bin < kLowBins - 1 ? TopkState{(uint32_t)bin, (uint32_t)(k - above), (uint32_t)k, 1u}
+                                    : TopkState{0u, (uint32_t)k, (uint32_t)k, 0u};   // the clamped bin: radix passes decide
         above += (int)h[j];
     }
+    __syncthreads();
+    if (st.resolved) return st;                                           // uniform
+    for (int pass = 0; pass < passes; ++pass) {                           // the byte value holding the need-th largest remaining candidate
+        const int d = 255 - (int)threadIdx.x;
+        const int n = d >= 0 ? (int)ctl->hist[pass][d] : 0;
+        const int larger = rg_block_excl_scan<NT / RG_WAVE>(n, smem, &total);
+        const uint32_t need = st.need;
+        __syncthreads();
+        if ((uint32_t)larger < need && need <= (uint32_t)larger + (uint32_t)n) {      // exactly one byte value satisfies this
+            st.T |= (uint32_t)d << (24 - 8 * pass);
+            st.need = need - (uint32_t)larger;
+        }
+        __syncthreads();
+    }
+    return st;
 }
 
 // Histogram of byte `pass` (0 = most significant) of the counts of candidates that match the prefix.
 __global__ void __launch_bounds__(256) k_topk_hist(const uint32_t* __restrict__ counts, const int32_t* __restrict__ home, int64_t n,
-                                                   int pass, TopkCtl* __restrict__ ctl) {
+                                                   int pass, int64_t capacity, TopkCtl* __restrict__ ctl) {
     __shared__ uint32_t h[256];
-    if (ctl->resolved) return;                               // uniform
+    const TopkState st = rg_topk_state<256>(ctl, capacity, pass);
+    if (st.resolved) return;                                 // uniform
     h[threadIdx.x] = 0u;
     __syncthreads();
     const int shift = 24 - 8 * pass;
-    const uint32_t prefix = ctl->prefix;
     for (int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; v < n; v += (int64_t)gridDim.x * blockDim.x) {
         const uint32_t c = counts[v];
         if (!rg_is_candidate((uint32_t)home[v], c)) continue;
-        if (pass > 0 && (c >> (shift + 8)) != (prefix >> (shift + 8))) continue;
+        if (pass > 0 && (c >> (shift + 8)) != (st.T >> (shift + 8))) continue;
         atomicAdd(&h[(c >> shift) & 255u], 1u);
     }
     __syncthreads();
     const uint32_t mine = h[threadIdx.x];
     if (mine) atomicAdd(&ctl->hist[pass][threadIdx.x], mine);
-}
-
-// One workgroup: pick the byte value holding the need-th largest remaining candidate.
-__global__ void __launch_bounds__(256) k_topk_pick(TopkCtl* __restrict__ ctl, int pass, int64_t capacity) {
-    __shared__ uint32_t h[256];
-    __shared__ uint32_t above[256];      // candidates in strictly larger byte values
-    __shared__ uint32_t need_s;
-    if (ctl->resolved) return;           // uniform
-    h[threadIdx.x] = ctl->hist[pass][threadIdx.x];
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        uint32_t run = 0;
-        for (int d = 255; d >= 0; --d) { above[d] = run; run += h[d]; }
-        uint32_t need0 = ctl->need;
-        if (pass == 0) {                 // run = number of candidates
-            const uint64_t k = (uint64_t)capacity < (uint64_t)run ? (uint64_t)capacity : (uint64_t)run;
-            ctl->k_eff = (uint32_t)k;
-            ctl->need = (uint32_t)k;
-            need0 = (uint32_t)k;
-        }
-        need_s = need0;
-    }
-    __syncthreads();
-    const uint32_t need = need_s;
-    const int shift = 24 - 8 * pass;
-    if (need == 0u) {
-        // nothing to select: a threshold no count can exceed or tie with a positive quota
-        if (threadIdx.x == 0 && pass == 3) ctl->prefix = 0xFFFFFFFFu;
-        return;
-    }
-    const int d = threadIdx.x;
-    if (above[d] < need && need <= above[d] + h[d]) {     // exactly one byte value satisfies this
-        ctl->prefix |= (uint32_t)d << shift;
-        ctl->need = need - above[d];
-    }
 }
 
 constexpr int kCapChunk = 64;
@@ -347,39 +333,43 @@ __global__ void __launch_bounds__(256) k_hit_curve_low(const TopkCtl* __restrict
     }
 }
 
-constexpr int kNodesPerBlock = 1024;   // 256 threads x 4 consecutive nodes
+constexpr int kNodesPerBlock = 4096;   // 1024 threads x 4 consecutive nodes
+constexpr int kTopkSelfScan = 4096;    // blocks up to which the emit kernel adds up the totals in front of it itself (N <= 16 Mi)
 
-// Per block: number of candidates above the threshold and number tied with it.
-__global__ void __launch_bounds__(256) k_topk_count(const uint32_t* __restrict__ counts, const int32_t* __restrict__ home, int64_t n,
-                                                    const TopkCtl* __restrict__ ctl, int32_t* __restrict__ blk_gt, int32_t* __restrict__ blk_eq) {
-    const uint32_t T = ctl->prefix;
+// Per block: number of candidates above the threshold and number tied with it; the number of rows selected.
+__global__ void __launch_bounds__(1024) k_topk_count(const uint32_t* __restrict__ counts, const int32_t* __restrict__ home, int64_t n,
+                                                     TopkCtl* __restrict__ ctl, int64_t capacity, int32_t* __restrict__ blk_gt,
+                                                     int32_t* __restrict__ blk_eq, int64_t* __restrict__ num_cached) {
+    __shared__ int part[1024 / RG_WAVE];
     const int64_t v0 = (int64_t)blockIdx.x * kNodesPerBlock + threadIdx.x * 4;
-    int gt = 0, eq = 0;
+    uint32_t c[4];
+    bool cand[4];
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
-        const int64_t v = v0 + q;
-        if (v < n) {
-            const uint32_t c = counts[v];
-            if (rg_is_candidate((uint32_t)home[v], c)) { gt += c > T; eq += c == T; }
-        }
+        c[q] = v0 + q < n ? counts[v0 + q] : 0u;
+        cand[q] = v0 + q < n && rg_is_candidate((uint32_t)home[v0 + q], c[q]);
     }
-    gt = rg_wave_sum(gt);
-    eq = rg_wave_sum(eq);
-    __shared__ int pg[4], pe[4];
-    if (rg_lane() == 0) { pg[threadIdx.x >> 6] = gt; pe[threadIdx.x >> 6] = eq; }
+    const TopkState st = rg_topk_state<1024>(ctl, capacity, 4);
+    int both = 0;                                            // above the threshold << 16 | tied with it: at most 4096 of either
+#pragma unroll
+    for (int q = 0; q < 4; ++q) both += cand[q] ? (c[q] > st.T ? 1 << 16 : c[q] == st.T) : 0;
+    both = rg_wave_sum(both);
+    if (rg_lane() == 0) part[threadIdx.x >> 6] = both;
     __syncthreads();
     if (threadIdx.x == 0) {
-        blk_gt[blockIdx.x] = pg[0] + pg[1] + pg[2] + pg[3];
-        blk_eq[blockIdx.x] = pe[0] + pe[1] + pe[2] + pe[3];
+        both = 0;
+#pragma unroll
+        for (int w = 0; w < 1024 / RG_WAVE; ++w) both += part[w];
+        blk_gt[blockIdx.x] = both >> 16;
+        blk_eq[blockIdx.x] = both & 0xFFFF;
+        if (blockIdx.x == 0) { *num_cached = (int64_t)st.k_eff; ctl->state = st; }
     }
 }
 
 // One workgroup: exclusive scans of both per-block arrays, in place.
 __global__ void __launch_bounds__(1024) k_topk_scan(int32_t* __restrict__ blk_gt, int32_t* __restrict__ blk_eq, int64_t nblocks) {
     __shared__ int smem[1024 / RG_WAVE + 1];
-    __shared__ int carry_g, carry_e;
-    if (threadIdx.x == 0) { carry_g = 0; carry_e = 0; }
-    __syncthreads();
+    int carry_g = 0, carry_e = 0;
     for (int64_t base = 0; base < nblocks; base += 1024) {
         const int64_t i = base + threadIdx.x;
         const int g = i < nblocks ? blk_gt[i] : 0;
@@ -387,52 +377,73 @@ __global__ void __launch_bounds__(1024) k_topk_scan(int32_t* __restrict__ blk_gt
         int tg, te;
         const int xg = rg_block_excl_scan<1024 / RG_WAVE>(g, smem, &tg);
         const int xe = rg_block_excl_scan<1024 / RG_WAVE>(e, smem, &te);
-        const int cg = carry_g, ce = carry_e;
-        if (i < nblocks) { blk_gt[i] = cg + xg; blk_eq[i] = ce + xe; }
-        __syncthreads();
-        if (threadIdx.x == 0) { carry_g = cg + tg; carry_e = ce + te; }
-        __syncthreads();
+        if (i < nblocks) { blk_gt[i] = carry_g + xg; blk_eq[i] = carry_e + xe; }
+        carry_g += tg;
+        carry_e += te;
     }
 }
 
 // Selected = above the threshold, or tied with it and among the first `need` ties in id order.
-// Slots are handed out in ascending id, so cache_ids comes out sorted.
-__global__ void __launch_bounds__(256) k_topk_emit(const uint32_t* __restrict__ counts, const int32_t* __restrict__ home, int64_t n,
-                                                   const TopkCtl* __restrict__ ctl, const int32_t* __restrict__ blk_gt,
-                                                   const int32_t* __restrict__ blk_eq, int32_t* __restrict__ cache_ids,
-                                                   int32_t* __restrict__ loc) {
-    __shared__ int smem[256 / RG_WAVE + 1];
-    const uint32_t T = ctl->prefix;
-    const int need = (int)ctl->need;
-    const int gt_before = blk_gt[blockIdx.x];
-    const int eq_before = blk_eq[blockIdx.x];
+// Slots are handed out in ascending id, so cache_ids comes out sorted.  scanned: the per-block counts are exclusive prefixes
+// already.  filled (NULL: left alone): bit s = `resident` for every selected slot, 0 behind them.
+__global__ void __launch_bounds__(1024) k_topk_emit(const uint32_t* __restrict__ counts, const int32_t* __restrict__ home, int64_t n,
+                                                    const TopkCtl* __restrict__ ctl, const int32_t* __restrict__ blk_gt,
+                                                    const int32_t* __restrict__ blk_eq, int scanned, int32_t* __restrict__ cache_ids,
+                                                    int32_t* __restrict__ loc, uint32_t* __restrict__ filled, int64_t filled_words,
+                                                    int resident) {
+    constexpr int NW = 1024 / RG_WAVE;
+    __shared__ int smem[NW + 1];
+    __shared__ int pg[NW], pe[NW];
     const int64_t v0 = (int64_t)blockIdx.x * kNodesPerBlock + threadIdx.x * 4;
-    uint32_t hw[4];
-    bool is_gt[4], is_eq[4];
-    int eq_cnt = 0;
+    uint32_t hw[4], c[4];
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
-        const int64_t v = v0 + q;
-        is_gt[q] = is_eq[q] = false;
-        hw[q] = 0u;
-        if (v < n) {
-            const uint32_t c = counts[v];
-            hw[q] = (uint32_t)home[v];
-            if (rg_is_candidate(hw[q], c)) { is_gt[q] = c > T; is_eq[q] = c == T; }
+        c[q] = v0 + q < n ? counts[v0 + q] : 0u;
+        hw[q] = v0 + q < n ? (uint32_t)home[v0 + q] : 0u;
+    }
+    int gt_before = 0, eq_before = 0;
+    if (scanned) {
+        gt_before = blk_gt[blockIdx.x];
+        eq_before = blk_eq[blockIdx.x];
+    } else {
+        for (unsigned b = threadIdx.x; b < blockIdx.x; b += 1024) { gt_before += blk_gt[b]; eq_before += blk_eq[b]; }
+        gt_before = rg_wave_sum(gt_before);
+        eq_before = rg_wave_sum(eq_before);
+        if (rg_lane() == 0) { pg[threadIdx.x >> 6] = gt_before; pe[threadIdx.x >> 6] = eq_before; }
+        __syncthreads();
+        gt_before = eq_before = 0;
+#pragma unroll
+        for (int w = 0; w < NW; ++w) { gt_before += pg[w]; eq_before += pe[w]; }
+    }
+    const TopkState st = ctl->state;
+    const int need = (int)st.need;
+    if (filled) {
+        for (int64_t w = (int64_t)blockIdx.x * 1024 + threadIdx.x; w < filled_words; w += (int64_t)gridDim.x * 1024) {
+            uint32_t bits = 0u;
+            const int64_t lo = w * 32, k = st.k_eff;
+            if (resident) bits = k >= lo + 32 ? 0xFFFFFFFFu : (k > lo ? (1u << (uint32_t)(k - lo)) - 1u : 0u);
+            filled[w] = bits;
         }
-        eq_cnt += is_eq[q];
+    }
+    bool is_gt[4], is_eq[4];
+    int both = 0;                                            // above the threshold << 16 | tied with it: at most 4096 of either
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        const bool cand = v0 + q < n && rg_is_candidate(hw[q], c[q]);
+        is_gt[q] = cand && c[q] > st.T;
+        is_eq[q] = cand && c[q] == st.T;
+        both += is_gt[q] ? 1 << 16 : is_eq[q];
     }
     int tot;
-    int eq_rank = eq_before + rg_block_excl_scan<256 / RG_WAVE>(eq_cnt, smem, &tot);
+    both = rg_block_excl_scan<NW>(both, smem, &tot);
+    int eq_rank = eq_before + (both & 0xFFFF);
+    int slot = gt_before + (both >> 16) + (eq_rank < need ? eq_rank : need);       // every tie in front of this node that was taken
     bool sel[4];
-    int sel_cnt = 0;
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
         sel[q] = is_gt[q] || (is_eq[q] && eq_rank < need);
         eq_rank += is_eq[q];
-        sel_cnt += sel[q];
     }
-    int slot = gt_before + (eq_before < need ? eq_before : need) + rg_block_excl_scan<256 / RG_WAVE>(sel_cnt, smem, &tot);
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
         const int64_t v = v0 + q;
@@ -450,10 +461,11 @@ __global__ void __launch_bounds__(256) k_topk_emit(const uint32_t* __restrict__ 
 // Radix path of the hit curve: hits += sum of the counts above the threshold plus (ties taken) x threshold.
 // `resolved` = 1 when the histogram pass already produced this capacity's value.
 __global__ void __launch_bounds__(256) k_hit_sum(const uint32_t* __restrict__ counts, const int32_t* __restrict__ home, int64_t n,
-                                                 const TopkCtl* __restrict__ ctl, const uint32_t* __restrict__ resolved,
+                                                 const TopkCtl* __restrict__ ctl, int64_t capacity, const uint32_t* __restrict__ resolved,
                                                  unsigned long long* __restrict__ hits) {
     if (*resolved) return;                                   // uniform
-    const uint32_t T = ctl->prefix;
+    const TopkState st = rg_topk_state<256>(ctl, capacity, 4);
+    const uint32_t T = st.T;
     unsigned long long above = 0ull;
     for (int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; v < n; v += (int64_t)gridDim.x * blockDim.x) {
         const uint32_t c = counts[v];
@@ -466,7 +478,7 @@ __global__ void __launch_bounds__(256) k_hit_sum(const uint32_t* __restrict__ co
     __syncthreads();
     if (threadIdx.x == 0) {
         unsigned long long a = pa[0] + pa[1] + pa[2] + pa[3];
-        if (blockIdx.x == 0) a += (unsigned long long)ctl->need * (unsigned long long)T;   // need == 0 when nothing is selected
+        if (blockIdx.x == 0) a += (unsigned long long)st.need * (unsigned long long)T;   // need == 0 when nothing is selected
         if (a) atomicAdd(hits, a);
     }
 }
@@ -516,21 +528,6 @@ __global__ void __launch_bounds__(256) k_cache_fill(const int32_t* __restrict__ 
                 }
         }
     }
-}
-
-// filled[w] = all-ones for slots below *num_cached (value = 1) or all-zero (value = 0).
-__global__ void __launch_bounds__(256) k_set_filled(uint32_t* __restrict__ filled, int64_t words, const int64_t* __restrict__ num_cached,
-                                                    int value) {
-    const int64_t w = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (w >= words) return;
-    uint32_t bits = 0u;
-    if (value) {
-        const int64_t k = *num_cached;
-        const int64_t lo = w * 32;
-        if (k >= lo + 32) bits = 0xFFFFFFFFu;
-        else if (k > lo) bits = (1u << (uint32_t)(k - lo)) - 1u;
-    }
-    filled[w] = bits;
 }
 
 __global__ void k_prefetch_reset(uint32_t* __restrict__ pctl) {
@@ -1004,27 +1001,28 @@ rg_status rg_build_cache(rg_ctx* ctx, const uint32_t* counts, const int32_t* hom
     int32_t* blk_gt = (int32_t*)ctx->topk_blk.p;
     int32_t* blk_eq = blk_gt + nblocks;
 
-    k_topk_init<<<1, 256, 0, s>>>(ctl, nullptr);
+    k_topk_init<<<4, 256, 0, s>>>(ctl, 0);
     RG_LAUNCH_CHECK(ctx, "k_topk_init");
-    const int hist_grid = (int)rg_max64(1, rg_min64(rg_div_up(num_nodes, 256 * 8), (int64_t)ctx->num_cus * 8));
-    k_topk_hist_low<<<hist_grid, 256, 0, s>>>(counts, home, num_nodes, ctl);
+    const int low_grid = (int)rg_max64(1, rg_min64(rg_div_up(num_nodes, 4096), ctx->num_cus));
+    k_topk_hist_low<<<low_grid, 1024, 0, s>>>(counts, home, num_nodes, ctl);
     RG_LAUNCH_CHECK(ctx, "k_topk_hist_low");
-    k_topk_pick_low<<<1, 256, 0, s>>>(ctl, cache->capacity_rows, cache->num_cached);
-    RG_LAUNCH_CHECK(ctx, "k_topk_pick_low");
+    const int hist_grid = (int)rg_max64(1, rg_min64(rg_div_up(num_nodes, 256 * 8), (int64_t)ctx->num_cus * 8));
     for (int pass = 0; pass < 4; ++pass) {                   // return at once unless the threshold is in the clamped bin
-        k_topk_hist<<<hist_grid, 256, 0, s>>>(counts, home, num_nodes, pass, ctl);
+        k_topk_hist<<<hist_grid, 256, 0, s>>>(counts, home, num_nodes, pass, cache->capacity_rows, ctl);
         RG_LAUNCH_CHECK(ctx, "k_topk_hist");
-        k_topk_pick<<<1, 256, 0, s>>>(ctl, pass, cache->capacity_rows);
-        RG_LAUNCH_CHECK(ctx, "k_topk_pick");
     }
-    k_topk_count<<<(int)nblocks, 256, 0, s>>>(counts, home, num_nodes, ctl, blk_gt, blk_eq);
+    k_topk_count<<<(int)nblocks, 1024, 0, s>>>(counts, home, num_nodes, ctl, cache->capacity_rows, blk_gt, blk_eq, cache->num_cached);
     RG_LAUNCH_CHECK(ctx, "k_topk_count");
-    k_topk_scan<<<1, 1024, 0, s>>>(blk_gt, blk_eq, nblocks);
-    RG_LAUNCH_CHECK(ctx, "k_topk_scan");
-    k_topk_emit<<<(int)nblocks, 256, 0, s>>>(counts, home, num_nodes, ctl, blk_gt, blk_eq, cache->cache_ids, cache->loc);
+    const int scanned = nblocks > kTopkSelfScan;
+    if (scanned) {
+        k_topk_scan<<<1, 1024, 0, s>>>(blk_gt, blk_eq, nblocks);
+        RG_LAUNCH_CHECK(ctx, "k_topk_scan");
+    }
+    const int64_t filled_words = cache->mirror_rows == 0 ? rg_div_up(rg_min64(cache->capacity_rows, num_nodes), 32) : 0;
+    k_topk_emit<<<(int)nblocks, 1024, 0, s>>>(counts, home, num_nodes, ctl, blk_gt, blk_eq, scanned, cache->cache_ids,
+                                              cache->loc, filled_words > 0 ? cache->filled : nullptr, filled_words, remote_store ? 1 : 0);
     RG_LAUNCH_CHECK(ctx, "k_topk_emit");
 
-    const int64_t filled_words = rg_div_up(rg_min64(cache->capacity_rows, num_nodes), 32);
     if (may_select && remote_store) {
         const void* ptrs[2] = {remote_store, cache->cache_rows};
         const int64_t strides[2] = {remote_stride, cache->row_stride};
@@ -1042,10 +1040,6 @@ rg_status rg_build_cache(rg_ctx* ctx, const uint32_t* counts, const int32_t* hom
             k_cache_fill<1><<<grid, 256, 0, s>>>(cache->cache_ids, home, cache->num_cached, remote_store, remote_stride, cache->cache_rows, cache->row_stride, shp.cpr, shp.log2L, shp.tail);
         rg_prof_end(ctx, tok, s);
         RG_LAUNCH_CHECK(ctx, "k_cache_fill");
-    }
-    if (cache->filled && filled_words > 0 && cache->mirror_rows == 0) {
-        k_set_filled<<<(int)rg_div_up(filled_words, 256), 256, 0, s>>>(cache->filled, filled_words, cache->num_cached, remote_store ? 1 : 0);
-        RG_LAUNCH_CHECK(ctx, "k_set_filled");
     }
     return RG_OK;
 }
@@ -1078,25 +1072,26 @@ rg_status rg_cache_hit_curve(rg_ctx* ctx, const uint32_t* counts, const int32_t*
         RG_LAUNCH_CHECK(ctx, "k_store_caps");
     }
     const int grid = (int)rg_max64(1, rg_min64(rg_div_up(num_nodes, 256 * 8), (int64_t)ctx->num_cus * 8));
+    const int low_grid = (int)rg_max64(1, rg_min64(rg_div_up(num_nodes, 4096), ctx->num_cus));
     // one pass over the nodes gives the histogram of the counts; every capacity is read off it
-    k_topk_init<<<1, 256, 0, s>>>(ctl, nullptr);
+    k_topk_init<<<4, 256, 0, s>>>(ctl, 0);
     RG_LAUNCH_CHECK(ctx, "k_topk_init");
-    k_topk_hist_low<<<grid, 256, 0, s>>>(counts, home, num_nodes, ctl);
+    k_topk_hist_low<<<low_grid, 1024, 0, s>>>(counts, home, num_nodes, ctl);
     RG_LAUNCH_CHECK(ctx, "k_topk_hist_low");
     k_hit_curve_low<<<1, 256, 0, s>>>(ctl, caps_dev, num_capacities, (unsigned long long*)hits, (unsigned long long*)remote_total, resolved);
     RG_LAUNCH_CHECK(ctx, "k_hit_curve_low");
     // capacities whose threshold lies among counts >= kLowBins - 1 (never the case when the counts are bounded by a few
     // hundred batches) go through the radix select one by one; for all others these kernels return at once
     for (int j = 0; j < num_capacities; ++j) {
-        k_topk_init<<<1, 256, 0, s>>>(ctl, resolved + j);
-        RG_LAUNCH_CHECK(ctx, "k_topk_init");
-        for (int pass = 0; pass < 4; ++pass) {
-            k_topk_hist<<<grid, 256, 0, s>>>(counts, home, num_nodes, pass, ctl);
-            RG_LAUNCH_CHECK(ctx, "k_topk_hist");
-            k_topk_pick<<<1, 256, 0, s>>>(ctl, pass, capacities[j]);
-            RG_LAUNCH_CHECK(ctx, "k_topk_pick");
+        if (j > 0) {
+            k_topk_init<<<4, 256, 0, s>>>(ctl, 1);
+            RG_LAUNCH_CHECK(ctx, "k_topk_init");
         }
-        k_hit_sum<<<grid, 256, 0, s>>>(counts, home, num_nodes, ctl, resolved + j, (unsigned long long*)hits + j);
+        for (int pass = 0; pass < 4; ++pass) {
+            k_topk_hist<<<grid, 256, 0, s>>>(counts, home, num_nodes, pass, capacities[j], ctl);
+            RG_LAUNCH_CHECK(ctx, "k_topk_hist");
+        }
+        k_hit_sum<<<grid, 256, 0, s>>>(counts, home, num_nodes, ctl, capacities[j], resolved + j, (unsigned long long*)hits + j);
         RG_LAUNCH_CHECK(ctx, "k_hit_sum");
     }
     return RG_OK;

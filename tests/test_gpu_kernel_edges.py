@@ -172,3 +172,25 @@ def test_epoch_histogram_range_edges(B, ctx, n, batches, hops, skew):
     assert np.array_equal(got_first.cpu().numpy().view(np.uint32), first)
     ctx.access_histogram_epoch(_i32(arena), _i32(tier_offs), batches, hops, most, counts)
     assert np.array_equal(counts.cpu().numpy().view(np.uint32), 2 * want)
+
+
+# Blocks of 4096 nodes; above 16 Mi nodes the blocks' totals are scanned by a launch of their own.  Capacities that cut a tie.
+@pytest.mark.parametrize("n", [1, 4095, 4096, 4097, 1_300_003, 16_777_217])
+@pytest.mark.parametrize("large", [False, True])
+def test_select_block_edges(B, ctx, n, large):
+    log(f"[select] N={n} large={large}")
+    rng = np.random.default_rng(n)
+    counts = rng.integers(0, 4, n).astype(np.uint32)
+    if large:                                           # the threshold behind the clamped bin
+        counts[rng.integers(0, n, n // 3 + 1)] = rng.choice(np.array([2046, 2047, 2048, 70_000, 2 ** 32 - 1], dtype=np.uint32))
+    remote = rng.random(n) < 0.7
+    home_np = np.where(remote, (2 << 30) + np.cumsum(remote) - 1, np.cumsum(~remote) - 1).astype(np.uint32).view(np.int32)
+    dev_counts, home = torch.from_numpy(counts.view(np.int32)).to(DEV), _i32(home_np)
+    for cap in {0, 1, n // 5, n}:
+        cache = B.FeatureCache(n, cap, 4, DEV)
+        cache.filled.fill_(-1)
+        ctx.build_cache(dev_counts, home, None, 4, cache)
+        ids, loc = oracle.build_cache(counts, home_np, cap)
+        assert int(cache.num_cached.item()) == ids.size, cap
+        assert np.array_equal(cache.cache_ids[:ids.size].cpu().numpy(), ids) and np.array_equal(cache.loc.cpu().numpy(), loc), cap
+        assert cap == 0 or not cache.filled.any()
