@@ -7,6 +7,9 @@ namespace {
 // agg[i] = (1/m_i) * sum over the block's edges e of row i, in edge order, of feat[nbr_local[e]].
 // A wavefront is split into groups of L lanes per destination row; each lane owns chunk c0 (+ L, + 2L, ...) of the
 // row and accumulates it in registers, E edges at a time so that E independent row loads are in flight.
+// Bound by the source rows' traffic behind L2 (27 % of the reads hit it on a power-law block; 270 k destinations of 5 edges,
+// 256 floats: 1.3 GB of rows in 196 us; 380 k distinct rows would be 0.4 GB).  E = 8 takes fan-outs of 5 in one step (E = 4: 206).
+// Cutting the columns into one part per XCD, so that every L2 holds its part of more rows, was slower (8 parts 228, 4 parts 205).
 template <int VEC, int E>
 __global__ void __launch_bounds__(256) k_mean_aggregate(const int32_t* __restrict__ indptr, const int32_t* __restrict__ nbr_local,
                                                         int64_t n_dst, const int32_t* __restrict__ n_dst_dev,
@@ -72,16 +75,26 @@ rg_status rg_mean_aggregate(rg_ctx* ctx, const int32_t* indptr, const int32_t* n
     const void* ptrs[2] = {feat, agg};
     const int64_t strides[2] = {feat_stride, agg_stride};
     const int vec = rg_pick_vec(dim, ptrs, 2, strides, 2);
-    const RgRowShape shp = rg_row_shape(dim, vec);
+    RgRowShape shp = rg_row_shape(dim, vec);
+    // Rows longer than a wavefront whose last step would idle most lanes: a group of 32 or 16 lanes instead if that takes a
+    // quarter fewer lane steps (80 chunks, 25 edges: 64 lanes 119 us, 32 lanes 94, 16 lanes 77; 151 chunks, 160 / 192 steps: all 74;
+    // 301 chunks of 8 bytes, 304 / 320: 97 with 16 lanes, 84 with 64).
+    if (shp.cpr > RG_WAVE) {
+        int64_t best = rg_div_up(shp.cpr, RG_WAVE) * RG_WAVE * 4 / 5 + 1;
+        for (int l = 5; l >= 4; --l) {
+            const int64_t steps = rg_div_up(shp.cpr, 1 << l) << l;
+            if (steps < best) { best = steps; shp.log2L = l; }
+        }
+    }
     const int rows_per_block = 4 * (RG_WAVE >> shp.log2L);
-    const int grid = (int)rg_max64(1, rg_min64(rg_div_up(n_dst, rows_per_block), (int64_t)ctx->num_cus * 64));
+    const int grid = (int)rg_max64(1, rg_min64(rg_div_up(n_dst, rows_per_block), (int64_t)ctx->num_cus * 16));
     const int tok = rg_prof_begin(ctx, RG_K_AGGREGATE, s);
     if (vec == 4)
-        k_mean_aggregate<4, 4><<<grid, 256, 0, s>>>(indptr, nbr_local, n_dst, n_dst_dev, feat, feat_stride, agg, agg_stride, shp.cpr, shp.log2L, shp.tail);
+        k_mean_aggregate<4, 8><<<grid, 256, 0, s>>>(indptr, nbr_local, n_dst, n_dst_dev, feat, feat_stride, agg, agg_stride, shp.cpr, shp.log2L, shp.tail);
     else if (vec == 2)
-        k_mean_aggregate<2, 4><<<grid, 256, 0, s>>>(indptr, nbr_local, n_dst, n_dst_dev, feat, feat_stride, agg, agg_stride, shp.cpr, shp.log2L, shp.tail);
+        k_mean_aggregate<2, 8><<<grid, 256, 0, s>>>(indptr, nbr_local, n_dst, n_dst_dev, feat, feat_stride, agg, agg_stride, shp.cpr, shp.log2L, shp.tail);
     else
-        k_mean_aggregate<1, 4><<<grid, 256, 0, s>>>(indptr, nbr_local, n_dst, n_dst_dev, feat, feat_stride, agg, agg_stride, shp.cpr, shp.log2L, shp.tail);
+        k_mean_aggregate<1, 8><<<grid, 256, 0, s>>>(indptr, nbr_local, n_dst, n_dst_dev, feat, feat_stride, agg, agg_stride, shp.cpr, shp.log2L, shp.tail);
     rg_prof_end(ctx, tok, s);
     RG_LAUNCH_CHECK(ctx, "k_mean_aggregate");
     return RG_OK;

@@ -194,3 +194,25 @@ def test_select_block_edges(B, ctx, n, large):
         assert int(cache.num_cached.item()) == ids.size, cap
         assert np.array_equal(cache.cache_ids[:ids.size].cpu().numpy(), ids) and np.array_equal(cache.loc.cpu().numpy(), loc), cap
         assert cap == 0 or not cache.filled.any()
+
+
+# Lane groups of 64, 32 and 16 (65, 68, 80, 151 chunks of 16 bytes; 301 of 8), eight edges per step.
+@pytest.mark.parametrize("dim,stride", [(260, 260), (269, 272), (317, 320), (602, 604), (602, 602)])
+def test_mean_aggregate_lane_groups(B, ctx, dim, stride):
+    rng = np.random.default_rng(dim)
+    m = np.concatenate([[0, 1, 7, 8, 9, 16, 17, 25], rng.integers(0, 12, 400)])
+    indptr = np.concatenate([[0], np.cumsum(m)]).astype(np.int32)
+    nbr = rng.integers(0, 900, indptr[-1]).astype(np.int32)
+    feat = torch.zeros(900, stride, device=DEV)
+    feat[:, :dim] = torch.from_numpy(rng.standard_normal((900, dim)).astype(np.float32)).to(DEV)
+    agg = torch.full((m.size, stride), float("nan"), device=DEV)
+    ctx.mean_aggregate(_i32(indptr), _i32(nbr), m.size, feat, dim, agg)
+    x = feat[:, :dim].cpu().numpy()
+    want = np.zeros((m.size, dim), dtype=np.float32)
+    for i in range(m.size):                             # the same fp32 sums in edge order, then one division
+        for e in range(indptr[i], indptr[i + 1]):
+            want[i] += x[nbr[e]]
+        if m[i]:
+            want[i] /= np.float32(m[i])
+    assert np.array_equal(agg[:, :dim].cpu().numpy(), want)
+    assert torch.isnan(agg[:, dim:]).all()
