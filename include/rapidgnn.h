@@ -356,7 +356,8 @@ RG_API rg_status rg_gather_features(rg_ctx* ctx, const int32_t* input_nodes, int
  * first_ticket + count - 1; rg_gather_run copies the rows of one prepared ticket (HBM rows on
  * hit_stream, miss rows on miss_stream, joined as in rg_gather_features).  Preparing several batches
  * at once pays the lookup launch once per group and leaves one copy kernel per batch on the stream.
- * rg_gather_features = prepare (ticket 0, one batch) + run.  A ticket is busy from its prepare until
+ * rg_gather_features = prepare (ticket 0, one batch) + run (batches of up to 32 MiB of rows in one launch, unless kernels are
+ * being timed).  A ticket is busy from its prepare until
  * the work of its run has finished; prepare and run of a ticket are given the same n, n_dev and
  * cache and are ordered on their streams by the caller (trivially so on one stream).
  * rg_gather_run returns RG_ERR_STATE if the ticket was not prepared for n rows.

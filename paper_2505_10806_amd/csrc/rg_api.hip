@@ -66,7 +66,7 @@ rg_status rg_check_device_readable(rg_ctx* ctx, const void* p, const char* what)
 
 rg_status rg_gather_reserve(rg_ctx* ctx, int64_t rows) {
     rg_status st;
-    if ((st = rg_ensure(ctx, ctx->gather_ctl, (size_t)RG_GATHER_TICKETS * 64)) != RG_OK) return st;
+    if ((st = rg_ensure(ctx, ctx->gather_ctl, (size_t)RG_GATHER_TICKETS * 64, true)) != RG_OK) return st;
     if (rows <= ctx->gather_cap) return RG_OK;
     // a larger per-ticket stride moves every ticket's slice: nothing prepared earlier stays valid
     for (int t = 0; t < RG_GATHER_TICKETS; ++t) ctx->gather_rows[t] = -1;

@@ -7,6 +7,8 @@
 // host-link transfers overlap the HBM copies.
 #include "rg_rowcopy.h"
 
+// For small batches rg_gather_features and rg_gather_features_static do all of that in one launch (k_gather_fused).
+
 // Scratch of rg_gather_features_static: one control block, the resolved location word of every output row and
 // the (output row, remote row) pairs of the miss rows, for up to RG_STATIC_GATHER_MAX_ROWS rows.  Every GPU the
 // library runs on holds its own copy of this array until the process ends.  Host code must not use the array's
@@ -30,7 +32,7 @@ namespace {
 struct GatherScratch {
     uint32_t* src;        // [rows] resolved location word per output row
     int32_t* miss_list;   // [2 * rows] (output row, remote row) pairs
-    uint32_t* gctl;       // [0] = number of misses
+    uint32_t* gctl;       // [0] = number of misses; [2], [3] = the batch's running counts, zero between launches (rg_add_counts)
 };
 
 GatherScratch ticket_scratch(rg_ctx* ctx, int t) {
@@ -74,16 +76,38 @@ __global__ void k_gather_reset(const ClassifyGroup C) {
     if (threadIdx.x < 3) C.stats[k][threadIdx.x] = 0ull;
 }
 
+// A batch's statistics without a launch that clears them first: every workgroup adds its misses, its hits and itself to one
+// 64-bit counter.  What it gets back is its place in the miss list, and the workgroup that completes the batch has the totals,
+// writes them out and leaves the counter zero.  (Additions to one address queue up at 12.5 ns each: few workgroups, one each.)
+constexpr int kCountBits = 23;           // rows < 2^23; workgroups < 2^18
+__device__ __forceinline__ uint32_t rg_add_counts(uint32_t* gctl, unsigned long long* stats, int misses, int hits, int64_t rows,
+                                                  unsigned workgroups) {
+    const unsigned long long mask = (1ull << kCountBits) - 1ull;
+    const unsigned long long add = (unsigned long long)misses | ((unsigned long long)hits << kCountBits) | (1ull << (2 * kCountBits));
+    const unsigned long long before = atomicAdd((unsigned long long*)(gctl + 2), add), all = before + add;
+    if ((all >> (2 * kCountBits)) == workgroups) {
+        const unsigned long long n_miss = all & mask, n_hit = (all >> kCountBits) & mask;
+        stats[0] = (unsigned long long)rows - n_miss - n_hit;
+        stats[1] = n_hit;
+        stats[2] = n_miss;
+        gctl[0] = (uint32_t)n_miss;
+        *(unsigned long long*)(gctl + 2) = 0ull;
+    }
+    return (uint32_t)(before & mask);
+}
+
 // Four rows per thread (row i0 + k*256 + threadIdx.x, k = 0..3) so that each thread has four independent
 // loc[] lookups in flight; the miss pairs of a workgroup are appended in that visiting order (any order is valid).
 constexpr int kClassifyRows = 4;
 
 // mirror_home != NULL: the cache is laid out as a mirror of the remote store, so a cached node's row is found at its
 // remote-store row (from its home word) instead of at its slot.
+// WIDE: batches of 2^23 rows or more, with separate counters that k_gather_reset has cleared.
+template <bool WIDE>
 __global__ void __launch_bounds__(256) k_classify(const ClassifyGroup C, const int32_t* __restrict__ loc,
                                                   const int32_t* __restrict__ mirror_home) {
     __shared__ int smem[256 / RG_WAVE + 1];
-    __shared__ int cls[3][4];
+    __shared__ int cls[2][4];
     __shared__ uint32_t miss_base;
     const int b = blockIdx.y;
     const int32_t* __restrict__ nodes = C.nodes[b];
@@ -93,7 +117,13 @@ __global__ void __launch_bounds__(256) k_classify(const ClassifyGroup C, const i
     unsigned long long* __restrict__ stats = C.stats[b];
     const int64_t n_act = rg_actual_n(C.n[b], C.n_dev[b]);
     const int64_t i0 = (int64_t)blockIdx.x * (256 * kClassifyRows);
-    if (i0 >= n_act) return;                                       // uniform per workgroup
+    if (i0 >= n_act) {                                             // uniform per workgroup
+        if (!WIDE && blockIdx.x == 0) {                            // an empty batch
+            if (threadIdx.x < 3) stats[threadIdx.x] = 0ull;
+            if (threadIdx.x == 0) gctl[0] = 0u;
+        }
+        return;
+    }
     uint32_t w[kClassifyRows];
     int32_t v[kClassifyRows];
 #pragma unroll
@@ -120,18 +150,26 @@ __global__ void __launch_bounds__(256) k_classify(const ClassifyGroup C, const i
         n_miss += tag == RG_TAG_REMOTE;
     }
     const int wave = threadIdx.x >> 6;
-    c_local = rg_wave_sum(c_local);
+    if (WIDE) c_local = rg_wave_sum(c_local);
     c_hit = rg_wave_sum(c_hit);
-    const int c_miss = rg_wave_sum(n_miss);
-    if (rg_lane() == 0) { cls[0][wave] = c_local; cls[1][wave] = c_hit; cls[2][wave] = c_miss; }
+    if (rg_lane() == 0) { cls[0][wave] = c_local; cls[1][wave] = c_hit; }
     int total_miss;
     int excl = rg_block_excl_scan<256 / RG_WAVE>(n_miss, smem, &total_miss);          // barriers inside publish cls[]
-    if (threadIdx.x < 3) {
-        const int t = cls[threadIdx.x][0] + cls[threadIdx.x][1] + cls[threadIdx.x][2] + cls[threadIdx.x][3];
-        if (t) atomicAdd(&stats[threadIdx.x], (unsigned long long)t);
+    if (threadIdx.x == 0) {
+        const int hits = cls[1][0] + cls[1][1] + cls[1][2] + cls[1][3];
+        if (WIDE) {
+            const int locals = cls[0][0] + cls[0][1] + cls[0][2] + cls[0][3];
+            if (locals) atomicAdd(&stats[0], (unsigned long long)locals);
+            if (hits) atomicAdd(&stats[1], (unsigned long long)hits);
+            if (total_miss) {
+                atomicAdd(&stats[2], (unsigned long long)total_miss);
+                miss_base = atomicAdd(&gctl[0], (uint32_t)total_miss);
+            }
+        } else {
+            miss_base = rg_add_counts(gctl, stats, total_miss, hits, n_act, (unsigned)((n_act + 256 * kClassifyRows - 1) / (256 * kClassifyRows)));
+        }
     }
     if (total_miss == 0) return;                                   // uniform
-    if (threadIdx.x == 0) miss_base = atomicAdd(&gctl[0], (uint32_t)total_miss);
     __syncthreads();
 #pragma unroll
     for (int k = 0; k < kClassifyRows; ++k)
@@ -245,6 +283,83 @@ __global__ void __launch_bounds__(1024) k_gather_miss(const int32_t* __restrict_
     }
 }
 
+// A small batch in one launch: a workgroup's first wavefront looks up `rpb` rows and publishes the location words and miss
+// pairs as k_classify does (a later rg_gather_run of the ticket finds them), then the workgroup copies its rows from whichever
+// store holds them, T chunks in flight per lane.  Saves the launches of lookup and miss copy and everything between two streams
+// but their order.  4 k rows of 64 floats, 1.5 k of them misses: 24 -> 13 us on one stream, 58 -> 35 on two; 60 k rows of 100 floats
+// in HBM 57 -> 40 on two.  The copies of a workgroup wait for its lookups and a tail of workgroups is left at the end, so large
+// batches are slower than with a lookup pass of their own: 70 k rows of 211 floats (59 MB) 46 / 46 us on one stream, of 602 floats
+// (168 MB) 76 / 65, 794 k rows of 256 floats 362 / 313.  The line is kFusedBytes of rows.
+constexpr int64_t kFusedBytes = 32ll << 20;
+template <int VEC, int T>
+__global__ void __launch_bounds__(256) k_gather_fused(const int32_t* __restrict__ nodes, int64_t n, const int32_t* __restrict__ n_dev,
+                                                      const int32_t* __restrict__ loc, const int32_t* __restrict__ mirror_home,
+                                                      const float* __restrict__ local_store, int64_t local_stride,
+                                                      const float* __restrict__ cache_rows, int64_t cache_stride,
+                                                      const float* __restrict__ remote_store, int64_t remote_stride,
+                                                      float* __restrict__ out, int64_t out_stride, int cpr, int tail, int rpb,
+                                                      uint32_t* __restrict__ src, int32_t* __restrict__ miss_list,
+                                                      uint32_t* __restrict__ gctl, unsigned long long* __restrict__ stats) {
+    typedef typename RgVec<VEC>::type V;
+    __shared__ const V* from[RG_WAVE];
+    const int64_t n_act = rg_actual_n(n, n_dev);
+    const int64_t row0 = (int64_t)blockIdx.x * rpb;
+    const int rows = row0 >= n_act ? 0 : (int)(n_act - row0 < rpb ? n_act - row0 : rpb);
+    uint32_t w = 0xFFFFFFFFu;                                          // tag 3 = no row
+    if ((int)threadIdx.x < rows) {
+        const int32_t v = nodes[row0 + threadIdx.x];
+        w = (uint32_t)loc[v];
+        if (mirror_home && (w >> RG_TAG_SHIFT) == RG_TAG_CACHE)
+            w = (RG_TAG_CACHE << RG_TAG_SHIFT) | ((uint32_t)mirror_home[v] & RG_ROW_MASK);
+        const uint32_t tag = w >> RG_TAG_SHIFT;
+        const int64_t row = (int64_t)(w & RG_ROW_MASK);
+        from[threadIdx.x] = (const V*)(tag == RG_TAG_LOCAL ? local_store + row * local_stride
+                                       : tag == RG_TAG_CACHE ? cache_rows + row * cache_stride : remote_store + row * remote_stride);
+        src[row0 + threadIdx.x] = w;
+    }
+    __syncthreads();
+    unsigned long long misses = 0ull;
+    uint32_t miss_base = 0u;
+    if (threadIdx.x < RG_WAVE) {                                       // the answer is used behind the copies
+        misses = __ballot((w >> RG_TAG_SHIFT) == RG_TAG_REMOTE);
+        const unsigned long long hits = __ballot((w >> RG_TAG_SHIFT) == RG_TAG_CACHE);
+        if (threadIdx.x == 0) miss_base = rg_add_counts(gctl, stats, __popcll(misses), __popcll(hits), n_act, gridDim.x);
+    }
+    int r = (int)threadIdx.x / cpr, c = (int)threadIdx.x % cpr;
+    const int dr = 256 / cpr, dc = 256 % cpr;
+    while (r < rows) {
+        V val[T];
+        V* to[T];
+        bool last[T];
+#pragma unroll
+        for (int t = 0; t < T; ++t) {
+            to[t] = nullptr;
+            if (r < rows) {
+                val[t] = from[r][c];
+                to[t] = (V*)(out + (row0 + r) * out_stride) + c;
+                last[t] = tail < VEC && c == cpr - 1;
+            }
+            r += dr;
+            c += dc;
+            if (c >= cpr) { c -= cpr; ++r; }
+        }
+#pragma unroll
+        for (int t = 0; t < T; ++t)
+            if (to[t]) {
+                if (last[t]) rg_store_head(to[t], val[t], tail);
+                else __builtin_nontemporal_store(val[t], to[t]);
+            }
+    }
+    if (threadIdx.x < RG_WAVE && misses) {
+        miss_base = (uint32_t)__shfl((int)miss_base, 0, RG_WAVE);
+        if ((misses >> threadIdx.x) & 1ull) {
+            const int64_t j = (int64_t)miss_base + __popcll(misses & ((1ull << threadIdx.x) - 1ull));
+            miss_list[2 * j] = (int32_t)(row0 + threadIdx.x);
+            miss_list[2 * j + 1] = (int32_t)(w & RG_ROW_MASK);
+        }
+    }
+}
+
 // Lookups of `count` batches in one launch; scr[k] receives batch k's results.
 rg_status launch_classify(rg_ctx* ctx, int count, const int32_t* const* input_nodes, const int64_t* n, const int32_t* const* n_dev,
                           const rg_cache* cache, rg_gather_stats* const* stats, const GatherScratch* scr, hipStream_t s) {
@@ -262,13 +377,16 @@ rg_status launch_classify(rg_ctx* ctx, int count, const int32_t* const* input_no
         C.stats[k] = live ? (unsigned long long*)stats[k] : nullptr;
         if (live) n_max = rg_max64(n_max, n[k]);
     }
-    k_gather_reset<<<count, 64, 0, s>>>(C);
-    RG_LAUNCH_CHECK(ctx, "k_gather_reset");
-    if (n_max > 0) {
-        k_classify<<<dim3((unsigned)rg_div_up(n_max, 256 * kClassifyRows), (unsigned)count), 256, 0, s>>>(
-            C, cache->loc, cache->mirror_rows > 0 ? cache->home : nullptr);
-        RG_LAUNCH_CHECK(ctx, "k_classify");
+    const bool wide = n_max >= (1ll << kCountBits);
+    if (wide) {
+        k_gather_reset<<<count, 64, 0, s>>>(C);
+        RG_LAUNCH_CHECK(ctx, "k_gather_reset");
     }
+    const dim3 grid((unsigned)rg_max64(1, rg_div_up(n_max, 256 * kClassifyRows)), (unsigned)count);
+    const int32_t* home = cache->mirror_rows > 0 ? cache->home : nullptr;
+    if (wide) k_classify<true><<<grid, 256, 0, s>>>(C, cache->loc, home);
+    else k_classify<false><<<grid, 256, 0, s>>>(C, cache->loc, home);
+    RG_LAUNCH_CHECK(ctx, "k_classify");
     return RG_OK;
 }
 
@@ -329,6 +447,40 @@ rg_status launch_copies(rg_ctx* ctx, const GatherScratch& scr, int64_t n, const 
     if (two_streams) {
         RG_HIP(ctx, hipEventRecord(ctx->ev_miss_done, sm));
         RG_HIP(ctx, hipStreamWaitEvent(sh, ctx->ev_miss_done, 0));
+    }
+    return RG_OK;
+}
+
+// Batches that k_gather_fused takes (see there).
+bool rg_fits_fused(int64_t n, int32_t dim) { return n > 0 && n * (int64_t)dim * 4 <= kFusedBytes && n < (1ll << kCountBits); }
+
+// The one-launch gather.  The miss rows keep their place in both streams' order: behind what miss_stream was given before, in
+// front of what either stream is given next.
+rg_status launch_fused(rg_ctx* ctx, const GatherScratch& scr, const int32_t* nodes, int64_t n, const int32_t* n_dev, const rg_cache* cache,
+                       const float* local_store, int64_t local_stride, const float* remote_store, int64_t remote_stride, int32_t dim,
+                       float* out, int64_t out_stride, rg_gather_stats* stats, hipStream_t sh, hipStream_t sm) {
+    if (sm != sh) {
+        RG_HIP(ctx, hipEventRecord(ctx->ev_classified, sm));
+        RG_HIP(ctx, hipStreamWaitEvent(sh, ctx->ev_classified, 0));
+    }
+    const void* ptrs[4] = {local_store, remote_store, cache->cache_rows, out};
+    const int64_t strides[4] = {local_stride, remote_stride, cache->cache_rows ? cache->row_stride : 0, out_stride};
+    const int vec = rg_pick_vec(dim, ptrs, 4, strides, 4);
+    const RgRowShape shp = rg_row_shape(dim, vec);
+    const int rpb = (int)rg_max64(8, rg_min64(RG_WAVE, n / (2 * ctx->num_cus)));   // two workgroups per compute unit, 8-64 rows each
+    const unsigned grid = (unsigned)rg_div_up(n, rpb);
+    const float* cache_rows = cache->cache_rows ? cache->cache_rows : local_store;   // never dereferenced without cache words
+    const int32_t* home = cache->mirror_rows > 0 ? cache->home : nullptr;
+#define RG_LAUNCH_FUSED(V, T)                                                                                           \
+    k_gather_fused<V, T><<<grid, 256, 0, sh>>>(nodes, n, n_dev, cache->loc, home, local_store, local_stride, cache_rows, cache->row_stride, \
+                                               remote_store, remote_stride, out, out_stride, shp.cpr, shp.tail, rpb, scr.src, scr.miss_list, \
+                                               scr.gctl, (unsigned long long*)stats)
+    if (vec == 4) RG_LAUNCH_FUSED(4, 4); else if (vec == 2) RG_LAUNCH_FUSED(2, 4); else RG_LAUNCH_FUSED(1, 4);
+#undef RG_LAUNCH_FUSED
+    RG_LAUNCH_CHECK(ctx, "k_gather_fused");
+    if (sm != sh) {
+        RG_HIP(ctx, hipEventRecord(ctx->ev_miss_done, sh));
+        RG_HIP(ctx, hipStreamWaitEvent(sm, ctx->ev_miss_done, 0));
     }
     return RG_OK;
 }
@@ -422,6 +574,15 @@ rg_status rg_gather_features(rg_ctx* ctx, const int32_t* input_nodes, int64_t n,
         RG_HIP(ctx, hipSetDevice(ctx->device));
         if ((st = rg_check_device_readable(ctx, remote_store, "rg_gather_features: remote_store")) != RG_OK) return st;
     }
+    if (rg_fits_fused(n, dim) && !ctx->profiling) {            // while kernels are timed, HBM and miss rows have one each
+        if ((st = rg_gather_reserve(ctx, n)) != RG_OK) return st;
+        ctx->gather_rows[0] = -1;
+        hipStream_t sh = (hipStream_t)hit_stream;
+        st = launch_fused(ctx, ticket_scratch(ctx, 0), input_nodes, n, n_dev, cache, local_store, local_stride, remote_store, remote_stride,
+                          dim, out, out_stride, stats, sh, miss_stream ? (hipStream_t)miss_stream : sh);
+        if (st == RG_OK) ctx->gather_rows[0] = n;              // the ticket's lookups are there, as after rg_gather_prepare
+        return st;
+    }
     st = rg_gather_prepare(ctx, 0, 1, &input_nodes, &n, &n_dev, cache, &stats, hit_stream);
     if (st != RG_OK) return st;
     return rg_gather_run(ctx, 0, n, n_dev, cache, local_store, local_stride, remote_store, remote_stride, dim, out, out_stride,
@@ -466,8 +627,10 @@ rg_status rg_gather_features_static(rg_ctx* ctx, const int32_t* input_nodes, int
     if (n > 0 && (st = rg_check_device_readable(ctx, remote_store, "rg_gather_features_static: remote_store")) != RG_OK) return st;
     hipStream_t sh = (hipStream_t)hit_stream;
     hipStream_t sm = miss_stream ? (hipStream_t)miss_stream : sh;
-    // the reset kernel zeroes the miss counter and the statistics the previous call left behind
     const GatherScratch scr = static_scratch(ctx);
+    if (rg_fits_fused(n, dim))
+        return launch_fused(ctx, scr, input_nodes, n, n_dev, cache, local_store, local_stride, remote_store, remote_stride, dim, out,
+                            out_stride, stats, sh, sm);
     if ((st = launch_classify(ctx, 1, &input_nodes, &n, &n_dev, cache, &stats, &scr, sh)) != RG_OK) return st;
     if (n == 0) return RG_OK;
     return launch_copies(ctx, scr, n, n_dev, cache, local_store, local_stride, remote_store, remote_stride, dim, out, out_stride,

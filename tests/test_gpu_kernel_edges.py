@@ -216,3 +216,51 @@ def test_mean_aggregate_lane_groups(B, ctx, dim, stride):
             want[i] /= np.float32(m[i])
     assert np.array_equal(agg[:, :dim].cpu().numpy(), want)
     assert torch.isnan(agg[:, dim:]).all()
+
+
+# One launch up to 32 MiB of rows (8-64 rows per workgroup), lookups of 1024 rows per workgroup; counters that have to be zero
+# again for the next call, whichever kernel makes it.
+@pytest.mark.parametrize("rows,dim,stride", [(1, 64, 64), (7, 602, 604), (513, 3, 3), (4097, 37, 40), (16_384, 512, 512), (16_385, 512, 512),
+                                             (131_000, 64, 64), (140_000, 64, 64)])
+@pytest.mark.parametrize("mirror", [False, True])
+def test_gather_one_launch_edges(B, ctx, rows, dim, stride, mirror):
+    log(f"[gather] rows={rows} dim={dim} mirror={mirror}")
+    rng = np.random.default_rng(rows + dim)
+    n = rows + 1000
+    x = rng.standard_normal((n, dim), dtype=np.float32)
+    is_local = rng.random(n) < 0.4
+    row = np.where(is_local, np.cumsum(is_local), np.cumsum(~is_local)) - 1
+    home_np = np.where(is_local, row, row + (2 << 30)).astype(np.uint32).view(np.int32)
+    n_remote = max(int((~is_local).sum()), 1)
+
+    def store(a, **kw):
+        t = torch.zeros(max(a.shape[0], 1), stride, **kw)
+        t[:a.shape[0], :dim] = torch.from_numpy(a)
+        return t
+    local, remote = store(x[is_local], device=DEV), store(x[~is_local], pin_memory=True)
+    counts_np = (rng.random(n) < (1.0 if mirror else 0.5)).astype(np.uint32)
+    home, counts = _i32(home_np), torch.from_numpy(counts_np.view(np.int32)).to(DEV)
+    cache = B.FeatureCache(n, n_remote, stride, DEV, mirror_rows=n_remote if mirror else 0, home=home if mirror else None)
+    ctx.build_cache(counts, home, None if mirror else remote, dim, cache)
+    if mirror:
+        cache.cache_rows.copy_(remote)
+    _, loc = oracle.build_cache(counts_np, home_np, n_remote)
+    side = torch.cuda.Stream()
+    for call in range(4):
+        nodes = rng.integers(0, n, rows).astype(np.int32)
+        want, st = oracle.gather_features(x, nodes, loc)
+        out = torch.full((rows, stride), float("nan"), device=DEV)
+        stats = torch.full((3,), -1, dtype=torch.int64, device=DEV)
+        n_dev = torch.tensor([rows // 2], dtype=torch.int32, device=DEV) if call == 3 else None
+        k = rows // 2 if call == 3 else rows
+        if call == 3:
+            want, st = oracle.gather_features(x, nodes[:k], loc)
+        gather = ctx.gather_features_static if call == 1 else ctx.gather_features
+        gather(_i32(nodes), rows, cache, local, remote, dim, out, stats, n_dev=n_dev, miss_stream=side if call else None)
+        assert tuple(stats.cpu().tolist()) == st, call
+        assert np.array_equal(out[:k, :dim].cpu().numpy(), want), call
+        assert torch.isnan(out[k:]).all() and torch.isnan(out[:, dim:]).all(), call
+        if call == 2:                                   # the ticket's lookups can be run again
+            out.fill_(float("nan"))
+            ctx.gather_run(0, rows, cache, local, remote, dim, out, miss_stream=side)
+            assert np.array_equal(out[:k, :dim].cpu().numpy(), want)
