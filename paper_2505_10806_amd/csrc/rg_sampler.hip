@@ -880,6 +880,150 @@ __global__ void __launch_bounds__(256) k_relabel(const RelabelGroup R, const Sam
     }
 }
 
+// ---------------------------------------------------------------------------- small batches, one launch
+// All hops of a small batch by one workgroup: the membership bits and the hop's marks are in LDS, the phases are separated by
+// barriers instead of launches (12 launches for two hops, each bound by its own latency).  A thread draws for one frontier
+// node and has all its picks' col_idx reads in flight.  One launch against one per phase, by nodes and the bound on a batch's
+// edges: 10 k nodes 16.6 k edges 27 / 53 us, 36 k 45 / 52, 72 k 60 / 52; 100 k nodes 4.2 k 21 / 53, 16.6 k 44 / 51, 18 k 54 / 54;
+// 500 k nodes 4.2 k 27 / 51, 16.6 k 65 / 55 (eight batches: the same, on as many compute units).
+constexpr int64_t kSmallNodes = 512 * 1024;     // two bitmaps of 64 KB
+inline bool rg_is_small(int64_t num_nodes, int64_t edges_bound) {
+    return num_nodes > 0 && num_nodes <= kSmallNodes && edges_bound <= (num_nodes <= 128 * 1024 ? 20 * 1024 : 8 * 1024);
+}
+
+struct SmallGroup {
+    RelabelGroup r;
+    const int32_t* seeds[kMaxGroup];
+    int32_t* nodes[kMaxGroup];
+    int32_t* tier_off[kMaxGroup];
+    int32_t* edges_out[kMaxGroup];    // [hops]; may be NULL
+    int32_t num_seeds[kMaxGroup];
+    int32_t fanout[RG_MAX_HOPS];
+};
+
+template <typename RP, int KMAX>
+__global__ void __launch_bounds__(1024) k_sample_small(const RP* __restrict__ row_ptr, const int32_t* __restrict__ col_idx, const SmallGroup G,
+                                                       uint32_t* __restrict__ visited_out, int64_t words64, int32_t* pos_all, int64_t num_nodes,
+                                                       int hops, uint32_t k0, uint32_t k1, uint32_t epoch) {
+    extern __shared__ uint32_t small_bits[];
+    __shared__ int smem[1024 / RG_WAVE + 1];
+    const int g = blockIdx.x, words = (int)words64;
+    uint32_t* visited = small_bits;
+    uint32_t* marked = small_bits + words;                             // members and the ids the hop has sampled
+    int32_t* nodes = G.nodes[g];
+    int32_t* tier_off = G.tier_off[g];
+    int32_t* pos = pos_all + g * num_nodes;
+    for (int w = threadIdx.x; w < 2 * words; w += 1024) small_bits[w] = 0u;
+    int n_h = G.num_seeds[g];
+    __syncthreads();
+    for (int i = threadIdx.x; i < n_h; i += 1024) {
+        const int32_t v = G.seeds[g][i];
+        nodes[i] = v;
+        pos[v] = i;
+        atomicOr(&visited[(uint32_t)v >> 5], 1u << (v & 31));
+        atomicOr(&marked[(uint32_t)v >> 5], 1u << (v & 31));
+    }
+    if (threadIdx.x == 0) { tier_off[0] = 0; tier_off[1] = n_h; }
+    const int per = (words + 1023) / 1024 | 1;                         // consecutive bitmap words per thread, odd: no two lanes on a bank
+    const int w0 = (int)threadIdx.x * per, w1 = w0 + per < words ? w0 + per : words;
+    for (int hop = 0; hop < hops; ++hop) {
+        const int k = G.fanout[hop];
+        int32_t* indptr = (int32_t*)G.r.indptr[hop][g];
+        int32_t* nbr = (int32_t*)G.r.nbr[hop][g];
+        int edges = 0;
+        __syncthreads();                                               // nodes[] and the bits are complete
+        for (int i0 = 0; i0 < n_h; i0 += 1024) {
+            const int i = i0 + (int)threadIdx.x;
+            int32_t v = 0;
+            int64_t start = 0, deg = 0;
+            int m = 0;
+            if (i < n_h) {
+                v = nodes[i];
+                rg_row_extent(row_ptr, v, start, deg);
+                m = deg <= k ? (int)deg : k;
+            }
+            int total;
+            const int at = edges + rg_block_excl_scan<1024 / RG_WAVE>(m, smem, &total);
+            edges += total;
+            if (i >= n_h) continue;
+            indptr[i] = at;
+            uint32_t c[KMAX];
+            if (deg <= k) {
+#pragma unroll
+                for (int s = 0; s < KMAX; ++s) c[s] = (uint32_t)s;     // whole row, CSR order
+            } else {
+#pragma unroll
+                for (int blk = 0; blk < KMAX / 4; ++blk) {
+                    if (blk * 4 < k) {
+                        uint32_t w[4];
+                        rg_philox4x32_10((uint32_t)v, (uint32_t)hop, (uint32_t)blk, epoch, k0, k1, w);
+#pragma unroll
+                        for (int q = 0; q < 4; ++q) {
+                            const int s = blk * 4 + q;
+                            if (s < k) {                               // Floyd: j = d-k+s, t uniform in [0, j]
+                                const uint32_t j = (uint32_t)(deg - k + s);
+                                const uint32_t t = __umulhi(w[q], j + 1u);
+                                bool found = false;
+#pragma unroll
+                                for (int l = 0; l < s; ++l) found |= (c[l] == t);
+                                c[s] = found ? j : t;
+                            }
+                        }
+                    }
+                }
+            }
+            int32_t u[KMAX];
+#pragma unroll
+            for (int s = 0; s < KMAX; ++s)
+                if (s < m) u[s] = col_idx[start + (int64_t)c[s]];
+#pragma unroll
+            for (int s = 0; s < KMAX; ++s)
+                if (s < m) {
+                    nbr[at + s] = u[s];
+                    atomicOr(&marked[(uint32_t)u[s] >> 5], 1u << (u[s] & 31));
+                }
+        }
+        if (threadIdx.x == 0) {
+            indptr[n_h] = edges;
+            if (G.edges_out[g]) G.edges_out[g][hop] = edges;
+        }
+        __syncthreads();                                               // the marks and nbr[] are complete
+        int fresh = 0;
+        for (int w = w0; w < w1; ++w) fresh += __popc(marked[w] & ~visited[w]);
+        int total;
+        int out = n_h + rg_block_excl_scan<1024 / RG_WAVE>(fresh, smem, &total);
+        for (int w = w0; w < w1; ++w) {
+            uint32_t b = marked[w] & ~visited[w];
+            if (b == 0u) continue;
+            visited[w] |= b;
+            for (; b; b &= b - 1u) {
+                const int32_t id = (w << 5) + __ffs(b) - 1;
+                nodes[out] = id;
+                pos[id] = out++;
+            }
+        }
+        n_h += total;
+        if (threadIdx.x == 0) tier_off[hop + 2] = n_h;
+        int32_t* nbr_local = G.r.nbr_local[hop][g];
+        if (nbr_local) {                                               // uniform
+            __syncthreads();                                           // pos[] is complete
+            for (int e0 = threadIdx.x; e0 < edges; e0 += 4096) {
+                int32_t u[4];
+#pragma unroll
+                for (int q = 0; q < 4; ++q) u[q] = e0 + 1024 * q < edges ? nbr[e0 + 1024 * q] : -1;
+#pragma unroll
+                for (int q = 0; q < 4; ++q)
+                    if (u[q] >= 0) u[q] = pos[u[q]];
+#pragma unroll
+                for (int q = 0; q < 4; ++q)
+                    if (e0 + 1024 * q < edges) nbr_local[e0 + 1024 * q] = u[q];
+            }
+        }
+    }
+    __syncthreads();
+    for (int w = threadIdx.x; w < words; w += 1024) visited_out[g * words64 + w] = visited[w];
+}
+
 // Per-batch strides of the scratch slices for a graph of N nodes and frontiers of up to `frontier` nodes.
 // max_edges: the largest per-hop edge bound when tiers are built from the edge list (first-seen order), else 0.
 void sampler_scratch_shape(int64_t N, int64_t frontier, int64_t max_edges, SampleScratch& S) {
@@ -967,6 +1111,9 @@ rg_status rg_sampler_reserve(rg_ctx* ctx, int64_t num_nodes, int64_t max_frontie
 rg_status rg_sampler_init(rg_ctx* ctx) {
     RG_HIP(ctx, hipFuncSetAttribute((const void*)k_sample_init, hipFuncAttributeMaxDynamicSharedMemorySize, kSliceWords * 4));
     RG_HIP(ctx, hipFuncSetAttribute((const void*)k_slice_mark, hipFuncAttributeMaxDynamicSharedMemorySize, kSliceWords * 4));
+    const void* small[] = {(const void*)k_sample_small<int32_t, 8>, (const void*)k_sample_small<int32_t, 16>, (const void*)k_sample_small<int32_t, 32>,
+                           (const void*)k_sample_small<int64_t, 8>, (const void*)k_sample_small<int64_t, 16>, (const void*)k_sample_small<int64_t, 32>};
+    for (const void* f : small) RG_HIP(ctx, hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)(kSmallNodes / 4)));
     return RG_OK;
 }
 
@@ -1109,6 +1256,36 @@ rg_status rg_sample_blocks_group(rg_ctx* ctx, const rg_csr* csr, int32_t group, 
     int64_t edges_bound = 0;
     for (int h = 0; h < num_hops; ++h) edges_bound += eub_max[h];
     const TierMode mode = first_seen ? kTierFirstSeen : (rg_use_slices(S.slices, N, edges_bound) ? kTierSliced : kTierAtomic);
+    int max_fanout = 0;
+    for (int h = 0; h < num_hops; ++h) max_fanout = fanouts[h] < 0 ? RG_MAX_FANOUT : (fanouts[h] > max_fanout ? fanouts[h] : max_fanout);
+    if (!first_seen && rg_is_small(N, edges_bound) && max_fanout <= 32 && csr->num_edges < (1ll << 32)) {
+        SmallGroup M = {};
+        for (int g = 0; g < group; ++g) {
+            M.seeds[g] = seeds[g];
+            M.nodes[g] = out[g].nodes;
+            M.tier_off[g] = out[g].tier_off;
+            M.edges_out[g] = out[g].num_edges;
+            M.num_seeds[g] = num_seeds[g];
+            for (int h = 0; h < num_hops; ++h) {
+                M.r.indptr[h][g] = out[g].indptr[h];
+                M.r.nbr[h][g] = out[g].nbr[h];
+                M.r.nbr_local[h][g] = out[g].nbr_local && eub_max[h] > 0 ? out[g].nbr_local[h] : nullptr;
+            }
+        }
+        for (int h = 0; h < num_hops; ++h) M.fanout[h] = fanouts[h];
+        const int tok = rg_prof_begin(ctx, RG_K_SAMPLE, s);
+#define RG_LAUNCH_SMALL(RP, KM)                                                                                       \
+    k_sample_small<RP, KM><<<ug, 1024, (size_t)words * 8, s>>>((const RP*)csr->row_ptr, csr->col_idx, M, S.visited, words, S.pos, N, num_hops, \
+                                                               k0, k1, epoch)
+        if (rp64) { if (max_fanout <= 8) RG_LAUNCH_SMALL(int64_t, 8); else if (max_fanout <= 16) RG_LAUNCH_SMALL(int64_t, 16); else RG_LAUNCH_SMALL(int64_t, 32); }
+        else { if (max_fanout <= 8) RG_LAUNCH_SMALL(int32_t, 8); else if (max_fanout <= 16) RG_LAUNCH_SMALL(int32_t, 16); else RG_LAUNCH_SMALL(int32_t, 32); }
+#undef RG_LAUNCH_SMALL
+        rg_prof_end(ctx, tok, s);
+        RG_LAUNCH_CHECK(ctx, "k_sample_small");
+        ctx->last_sample_group = group;
+        ctx->last_sample_nodes = N;
+        return RG_OK;
+    }
     if (words > 0) {
         if (ctx->sampler_dirty && ctx->first_key.bytes) {   // an earlier first-seen call stopped between a draw kernel and its emit
             const int64_t key_words = (int64_t)(ctx->first_key.bytes / 4);

@@ -43,7 +43,12 @@ def _sparse_graph(n, active, degree, rng):
 # nodes, active nodes, mean degree, seeds per batch, fan-outs.  A slice of the marking pass covers at most 1,280,000 ids;
 # above 4 Mi nodes few edges take the atomic marking; above 40,960,000 nodes there are no slices at all.
 @pytest.mark.parametrize("n,active,degree,seeds,fanouts", [
-    (31, 31, 3, [4], (3, 2)),
+    (31, 31, 3, [4], (3, 2)),                           # one launch for all hops: up to 20,480 edges (8192 above 131,072 nodes)
+    (131_072, 60_000, 30, [310, 0, 1], (10, 5)),
+    (131_072, 60_000, 30, [400, 300], (10, 5)),         # just too many edges for that
+    (131_041, 90_000, 9, [15, 16], (16, 0, 32)),
+    (524_288, 80_000, 30, [120, 64], (10, 5)),
+    (524_289, 80_000, 30, [120, 64], (10, 5)),
     (1_279_999, 3000, 8, [40, 7], (5, 3)),              # one slice, last word partial
     (1_280_001, 3000, 8, [40, 7, 0], (5, 3)),           # a second slice of few words
     (20_000, 20_000, 40, [700, 900], (32, 31)),         # over 8192 new ids within 512 words
