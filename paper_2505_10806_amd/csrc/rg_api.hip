@@ -114,7 +114,6 @@ rg_status rg_create(int device, rg_ctx** out) {
     }
     rg_status st = rg_gather_static_init(ctx);
     if (st == RG_OK) st = rg_sampler_init(ctx);
-    if (st == RG_OK) st = rg_ensure(ctx, ctx->hist_bounds, (size_t)RG_HIST_BOUNDS * 4);   // the epoch histogram allocates nothing
     if (st != RG_OK) {
         memcpy(g_create_error, ctx->err, sizeof(g_create_error));
         rg_destroy(ctx);
@@ -165,6 +164,7 @@ rg_status rg_reserve(rg_ctx* ctx, int64_t num_nodes, int64_t max_frontier, int64
     rg_status st;
     if ((st = rg_sampler_reserve(ctx, num_nodes, max_frontier, sample_group)) != RG_OK) return st;
     if ((st = rg_ensure(ctx, ctx->topk_blk, ((size_t)rg_div_up(num_nodes, 1024) + 2) * 8)) != RG_OK) return st;
+    if ((st = rg_histogram_reserve(ctx, num_nodes)) != RG_OK) return st;
     if ((st = rg_gather_reserve(ctx, max_rows)) != RG_OK) return st;
     if ((st = rg_ensure(ctx, ctx->pf_list, (size_t)max_rows * 8)) != RG_OK) return st;
     if ((st = rg_ensure(ctx, ctx->pf_ctl, 64)) != RG_OK) return st;

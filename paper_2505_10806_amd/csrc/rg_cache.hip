@@ -904,7 +904,25 @@ rg_status launch_list_copy(rg_ctx* ctx, const int32_t* list, const uint32_t* pct
     return RG_OK;
 }
 
+// Id ranges of the epoch histogram: whole rounds of two workgroups per compute unit.
+int hist_range(const rg_ctx* ctx, int64_t num_nodes) {
+    const int64_t places = 2ll * ctx->num_cus;
+    const int64_t rounds = rg_max64(1, rg_div_up(num_nodes, places * kHistRangeMax));
+    return (int)rg_max64(kHistRangeMin, rg_div_up(num_nodes, places * rounds));
+}
+
+// A call takes several launches rather than more scratch from kHistBoundsBatches batches per launch on; rg_reserve makes room for
+// twice as many of 8 hops.
+constexpr int64_t kHistBoundsBatches = 64;
+constexpr int64_t kHistBoundsMax = 2ll << 20;      // entries, or one batch
+
 }  // namespace
+
+rg_status rg_histogram_reserve(rg_ctx* ctx, int64_t num_nodes) {
+    if (num_nodes <= 0) return RG_OK;
+    const int64_t per_batch = RG_MAX_HOPS * (rg_div_up(num_nodes, hist_range(ctx, num_nodes)) + 1);
+    return rg_ensure(ctx, ctx->hist_bounds, (size_t)(per_batch * rg_max64(1, rg_min64(2 * kHistBoundsBatches, kHistBoundsMax / per_batch))) * 4);
+}
 
 extern "C" {
 
@@ -937,20 +955,21 @@ rg_status rg_access_histogram_epoch(rg_ctx* ctx, const int32_t* nodes, int64_t b
     RG_REQUIRE(ctx, nodes && tier_off && counts, "rg_access_histogram_epoch: null pointer");
     RG_HIP(ctx, hipSetDevice(ctx->device));
     hipStream_t s = (hipStream_t)stream;
+    const int range = hist_range(ctx, num_nodes);
+    const int ranges = (int)rg_div_up(num_nodes, range);
+    // batches per launch: the bounds of their runs fit the scratch, and a grid's second dimension
+    const int64_t per_batch = (int64_t)num_hops * (ranges + 1);
+    const int64_t most = rg_min64(num_batches, rg_max64(1, kHistBoundsMax / per_batch));
+    rg_status st;
+    if ((int64_t)(ctx->hist_bounds.bytes / 4) < per_batch * rg_min64(most, kHistBoundsBatches) &&
+        (st = rg_ensure(ctx, ctx->hist_bounds, (size_t)(per_batch * most) * 4)) != RG_OK) return st;
+    const int step = (int)rg_min64((int64_t)(ctx->hist_bounds.bytes / 4) / per_batch, 65535 / num_hops);
+    int32_t* bounds = (int32_t*)ctx->hist_bounds.p;
     const int tok = rg_prof_begin(ctx, RG_K_HISTOGRAM, s);
     if (max_seeds > 0) {
         dim3 seed_grid((unsigned)rg_min64(rg_div_up(max_seeds, 256), 64), (unsigned)num_batches);
         k_histogram_seeds<<<seed_grid, 256, 0, s>>>(nodes, batch_stride, tier_off, num_hops, counts, first_batch);
     }
-    // whole rounds of two workgroups per compute unit
-    const int64_t places = 2ll * ctx->num_cus;
-    const int64_t rounds = rg_max64(1, rg_div_up(num_nodes, places * kHistRangeMax));
-    const int range = (int)rg_max64(kHistRangeMin, rg_div_up(num_nodes, places * rounds));
-    const int ranges = (int)rg_div_up(num_nodes, range);
-    // batches per launch: the bounds of their runs fit the scratch, and a grid's second dimension
-    const int64_t per_batch = (int64_t)num_hops * (ranges + 1);
-    const int step = (int)rg_max64(1, rg_min64(RG_HIST_BOUNDS / per_batch, 65535 / num_hops));
-    int32_t* bounds = (int32_t*)ctx->hist_bounds.p;
     for (int b0 = 0; b0 < num_batches; b0 += step) {
         const int nb = num_batches - b0 < step ? num_batches - b0 : step;
         const int32_t* list = nodes + (int64_t)b0 * batch_stride;

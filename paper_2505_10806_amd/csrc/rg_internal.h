@@ -9,8 +9,6 @@
 
 #include "rapidgnn.h"
 
-#define RG_HIST_BOUNDS (2ll << 20)   // entries of the epoch histogram's bounds per launch (one batch of 2^30 nodes and 8 hops fits)
-
 // A growable device allocation owned by the context.
 struct RgBuf {
     void* p = nullptr;
@@ -56,7 +54,7 @@ struct rg_ctx {
     RgBuf sched_keys;   // uint64[n]
     RgBuf sched_ids;    // int32[n]
     RgBuf sched_buckets; // int32: pairs per bucket, scatter cursors, bucket starts
-    RgBuf hist_bounds;  // int32[RG_HIST_BOUNDS], made by rg_create: where the id ranges of the epoch histogram begin in every run
+    RgBuf hist_bounds;  // int32: where the id ranges of the epoch histogram begin in the runs of some batches
     // top-K scratch
     RgBuf topk_ctl;     // TopkCtl
     RgBuf topk_blk;     // int32[2 * nblocks]
@@ -90,6 +88,8 @@ rg_status rg_set_error(rg_ctx* ctx, rg_status code, const char* fmt, ...);
 rg_status rg_ensure(rg_ctx* ctx, RgBuf& buf, size_t bytes, bool zero_new = false);
 // RG_OK if kernels on the ctx's device may dereference p (device, managed or pinned/registered host memory).
 rg_status rg_check_device_readable(rg_ctx* ctx, const void* p, const char* what);
+// Scratch with which an epoch histogram of any number of batches on num_nodes nodes allocates nothing.
+rg_status rg_histogram_reserve(rg_ctx* ctx, int64_t num_nodes);
 // Makes every gather ticket hold at least `rows` rows (a reallocation invalidates prepared tickets).
 rg_status rg_gather_reserve(rg_ctx* ctx, int64_t rows);
 // Sizes the sampler scratch for `group` batches side by side on a graph of num_nodes nodes with cumulative
