@@ -42,7 +42,7 @@
  *    lane of the HBM gather), RG_GATHER_BLOCKS_PER_CU (grid cap of the HBM gather, default
  *    none), RG_PULL_BLOCKS / RG_PULL_THREADS (grid of the host-link pull kernels, default
  *    16 x 1024), RG_PULL_ROWS (rows in flight per lane group of the pull kernel, 4 or 8), RG_MISS_BLOCKS /
- *    RG_MISS_THREADS (grid of the miss-row kernel, default 192 x 256), RG_XCD_MAP=0 (sampler workgroups in
+ *    RG_MISS_THREADS (grid of the miss-row kernel, default 64 x 1024 or 192 x 256 by the batch), RG_XCD_MAP=0 (sampler workgroups in
  *    batch-major order instead of one batch of a group per XCD).
  */
 #ifndef RAPIDGNN_H

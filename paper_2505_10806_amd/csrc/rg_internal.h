@@ -27,8 +27,8 @@ struct RgKnobs {
     int pull_blocks = 16;             // RG_PULL_BLOCKS / RG_PULL_THREADS: grid of the host-link pull kernels
     int pull_threads = 1024;
     int pull_rows = 4;                // RG_PULL_ROWS: rows in flight per lane group of the pull kernel (4 or 8)
-    int miss_blocks = 192;            // RG_MISS_BLOCKS / RG_MISS_THREADS: grid of the miss-row kernel
-    int miss_threads = 256;
+    int miss_blocks = 0;              // RG_MISS_BLOCKS / RG_MISS_THREADS: grid of the miss-row kernel (0 = by the batch, see launch_copies)
+    int miss_threads = 0;
     int xcd_map = 1;                  // RG_XCD_MAP=0: batch-major workgroup order in the sampler instead of one batch per XCD
 };
 

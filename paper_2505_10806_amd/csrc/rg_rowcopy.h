@@ -64,5 +64,5 @@ static inline RgRowShape rg_row_shape(int32_t dim, int vec) {
 //    8 x 1024, 8 rows in flight per lane group   51.1 GB/s   0.675   1338 batches/s
 // against 56.9 GB/s for the pull kernel alone, 57.3 GB/s for a plain runtime copy from pinned memory and 0.69 for
 // the gather alone.  Miss rows go through one more dependent lookup per step than the pulls and need more wavefronts
-// to fill the link (swept on the 602-dim workload: 48 workgroups of 256 threads 46 GB/s, 192 -> 51, 384 -> 53).
-// The grids are RgKnobs::pull_blocks x pull_threads and RgKnobs::miss_blocks x miss_threads.
+// to fill the link (swept on the 602-dim workload: 48 workgroups of 256 threads 46 GB/s, 192 -> 51, 384 -> 53); their grid
+// follows the batch (launch_copies).  The grid of the pulls is RgKnobs::pull_blocks x pull_threads.
