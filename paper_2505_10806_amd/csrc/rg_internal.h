@@ -47,6 +47,7 @@ struct rg_ctx {
     RgBuf row_start;    // int64[max_frontier] adjacency row start of every frontier node (current hop)
     RgBuf row_deg;      // int32[max_frontier] its degree
     RgBuf first_key;    // int32[N] per batch, first-seen node order only (see SampleScratch)
+    RgBuf seen;         // int32[2 * max_frontier] per batch, the same
     int last_sample_group = 0;     // batches of the last completed sampling call: their `visited` bitmaps are the batches'
     int64_t last_sample_nodes = 0; // input-node sets (rg_access_histogram_sampled), on graphs of this many nodes
     bool sampler_dirty = false;   // a sampling call was cut short by an error: the first-edge keys may hold stale entries
@@ -95,7 +96,7 @@ rg_status rg_gather_reserve(rg_ctx* ctx, int64_t rows);
 // Sizes the sampler scratch for `group` batches side by side on a graph of num_nodes nodes with cumulative
 // frontiers of up to max_frontier nodes (what rg_sample_blocks_group would otherwise grow on demand).
 rg_status rg_sampler_reserve(rg_ctx* ctx, int64_t num_nodes, int64_t max_frontier, int group, int hops = RG_MAX_HOPS,
-                             int64_t max_edges = 0, bool first_seen = false);
+                             int64_t max_edges = 0, bool first_seen = false, bool ranked_seen = false);
 // Allows the sampler's kernels the LDS they use on ctx->device (the device must be current).
 rg_status rg_sampler_init(rg_ctx* ctx);
 // Resolves the device address of the file-scope gather scratch for ctx->device (the device must be current).

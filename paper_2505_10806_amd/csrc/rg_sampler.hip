@@ -19,7 +19,11 @@ constexpr int kWordsPerBlock = 1024; // bitmap words per workgroup in the tier k
 //                 one global atomicOr per edge behind a probe 717 us (37 G atomics/s, the same for every scope), with a
 //                 byte store per edge 341 us; the LDS pass adds 44 us.
 //  kTierAtomic    (ascending order) one probe and at most one atomicOr per edge on the bitmap `marked`.
-//  kTierFirstSeen the first edge of the hop that names a node is kept per node (atomicMax).
+//  kTierFirstSeen (first-seen order) the first edge of the hop that names a node is kept per node (atomicMax).
+//  kTierRankedSeen (first-seen order) the tier is found as in kTierSliced, which gives its nodes their ascending positions; the
+//                 first edges are kept by those (N / 4 bytes of rank words and 4 bytes per new node instead of 4 N scattered
+//                 bytes), edges that open a node are counted and emitted in edge order, and `place` maps one position to the
+//                 other.  See rg_use_ranked_seen for the line between the two.
 // The sliced way moves about N bytes per hop whatever the edges, and every slice reads every edge; the atomic way costs 27 ps
 // per edge.  Whole call, sliced against atomic: 8 batches of 4096 seeds (15,10,5) at N = 10 M 715 / 1700 us, at 40 M 733 / 1026,
 // at 100 M (80 slices) 1312 / 841; 8 batches of 64 seeds (10,5) at N = 10 M 102 / 92 us, at 40 M 239 / 160; on smaller graphs
@@ -27,7 +31,16 @@ constexpr int kWordsPerBlock = 1024; // bitmap words per workgroup in the tier k
 inline bool rg_use_slices(int slices, int64_t num_nodes, int64_t edges_bound) {
     return slices > 0 && (num_nodes <= (4ll << 20) || edges_bound >= num_nodes / 16);
 }
-enum TierMode { kTierSliced = 0, kTierAtomic = 1, kTierFirstSeen = 2 };
+enum TierMode { kTierSliced = 0, kTierAtomic = 1, kTierFirstSeen = 2, kTierRankedSeen = 3 };
+// First-seen order through rank words: four more launches per hop, cheaper edges.  Whole call against kTierFirstSeen by the bound
+// on the edges of all batches: 8 batches of 4096 seeds (15,10,5) at N = 10 M 1395 / 2530 us; 8 of 1024, N = 2.4 M (8.6 M edges)
+// 409 / 650; 8 of 512, N = 1 M (4.3 M) 261 / 310; 8 of 1024 (25,10), N = 200 k (2.3 M) 146 / 165; one batch of 1024, N = 2.4 M
+// (1.1 M) 233 / 180; 8 of 512 (10,5), N = 1 M (0.3 M) 121 / 100.
+constexpr int64_t kRankedSeenMin = 2ll << 20;
+inline bool rg_use_ranked_seen(int slices, int64_t num_nodes, int64_t edges_bound, int group) {
+    return rg_use_slices(slices, num_nodes, edges_bound) && edges_bound * group >= kRankedSeenMin;
+}
+constexpr int64_t kRankedSeenEdges = 16ll << 20;     // per hop and batch: the emit kernel's workgroups add up the totals in front of them
 constexpr int kSliceWords = 40000;   // bitmap words of a slice: 160,000 of the 163,840 bytes of LDS a compute unit has
 constexpr int kMaxSlices = 32;
 constexpr int kSliceGroups = 256;    // workgroups the marking pass is split into at most (slices x splits x batches): one per
@@ -252,6 +265,7 @@ struct SampleGroup {
     int32_t* tier_off[kMaxGroup];
     int32_t* indptr[kMaxGroup];       // of the current hop
     int32_t* nbr[kMaxGroup];
+    int32_t* nbr_local[kMaxGroup];    // kTierRankedSeen only
     int32_t* edges_out[kMaxGroup];    // may be NULL
 };
 
@@ -263,7 +277,9 @@ struct SampleScratch {
     int32_t* chunk_sum;               // [group][chunk_stride]
     int64_t* row_start;               // [group][frontier_stride]
     int32_t* row_deg;                 // [group][frontier_stride]
-    int32_t* first_key;               // [group][num_nodes], first-seen order only: 0x7FFFFFFF - (index of the first edge of
+    int32_t* first_edge;              // kTierRankedSeen: [group][frontier_stride], by ascending position (see there)
+    int32_t* place;                   // the same: ascending position -> position
+    int32_t* first_key;               // [group][num_nodes], kTierFirstSeen only: 0x7FFFFFFF - (index of the first edge of
                                       // the current hop that names the node), 0 = not named (kept all-zero between hops)
     int64_t words, num_nodes, chunk_stride, frontier_stride;
     int hops;
@@ -671,11 +687,13 @@ __global__ void __launch_bounds__(kTierWords) k_slice_count(const SampleScratch 
 // now 30); a workgroup with more new ids than fit there (over half of its range) stores them directly.
 constexpr int kEmitIds = 8192;
 
+// RANKED_SEEN: the positions are ascending ones only, the nodes come later.
+template <bool RANKED_SEEN>
 __global__ void __launch_bounds__(kTierWords) k_slice_emit(const SampleGroup G, const SampleScratch S, int hop) {
     constexpr int NW = kTierWords / RG_WAVE;
     __shared__ int smem[NW + 1];
     __shared__ int part[NW];
-    __shared__ int32_t ids[kEmitIds];
+    __shared__ int32_t ids[RANKED_SEEN ? 1 : kEmitIds];
     const int g = rg_batch(S);
     const unsigned blk = rg_block(S);
     const int64_t w = (int64_t)blk * kTierWords + threadIdx.x;
@@ -696,9 +714,10 @@ __global__ void __launch_bounds__(kTierWords) k_slice_emit(const SampleGroup G, 
     if (w < S.words) {
         S.rank[((int64_t)g * S.hops + hop) * S.words + w] = make_uint2(bits, (uint32_t)(out + j));
         if (bits) S.visited[g * S.words + w] |= bits;
-        for (uint32_t b = bits; b; b &= b - 1u) dst[j++] = (int32_t)(w << 5) + __ffs(b) - 1;
+        if (!RANKED_SEEN)
+            for (uint32_t b = bits; b; b &= b - 1u) dst[j++] = (int32_t)(w << 5) + __ffs(b) - 1;
     }
-    if (total > kEmitIds) return;                        // uniform
+    if (RANKED_SEEN || total > kEmitIds) return;         // uniform
     __syncthreads();
     for (int i = threadIdx.x; i < total; i += kTierWords) nodes[i] = ids[i];
 }
@@ -828,6 +847,170 @@ __global__ void __launch_bounds__(256) k_first_seen_emit(const SampleGroup G, co
         }
 }
 
+// ---------------------------------------------------------------------------- per hop: first-seen order by rank words
+// Positions of U ids (-1: none) from the rank words of the hops' tiers, latest first (`rank` = those of hop's new tier), and from
+// pos[] for the seeds; the U reads of a tier are in flight together.
+template <int U>
+__device__ __forceinline__ void rg_ranked_positions(const int32_t (&u)[U], const uint2* __restrict__ rank, int hop, int64_t words,
+                                                    const int32_t* __restrict__ pos, int32_t (&r)[U]) {
+#pragma unroll
+    for (int q = 0; q < U; ++q) r[q] = u[q] >= 0 ? -1 : 0;
+    for (int t = hop; t >= 0; --t, rank -= words) {
+        uint2 x[U];
+#pragma unroll
+        for (int q = 0; q < U; ++q) x[q] = r[q] < 0 ? rank[(uint32_t)u[q] >> 5] : make_uint2(0u, 0u);
+        bool open = false;
+#pragma unroll
+        for (int q = 0; q < U; ++q) {
+            const uint32_t bit = 1u << (u[q] & 31);
+            if (x[q].x & bit) r[q] = (int32_t)x[q].y + __popc(x[q].x & (bit - 1u));
+            open = open || r[q] < 0;
+        }
+        if (!__any(open)) return;
+    }
+#pragma unroll
+    for (int q = 0; q < U; ++q)
+        if (r[q] < 0) r[q] = pos[u[q]];
+}
+
+// nbr_local[e] = ascending position of nbr[e].
+__global__ void __launch_bounds__(256) k_seen_rank(const SampleGroup G, const SampleScratch S, int hop) {
+    constexpr int U = 4;
+    const int g = rg_batch(S);
+    const int64_t stride = (int64_t)rg_blocks_per_batch(S) * 256;
+    const int64_t n = G.indptr[g][G.tier_off[g][hop + 1]];
+    const int32_t* __restrict__ nbr = G.nbr[g];
+    const int32_t* __restrict__ pos = S.pos + g * S.num_nodes;
+    const uint2* __restrict__ rank = S.rank + ((int64_t)g * S.hops + hop) * S.words;
+    int32_t* __restrict__ nbr_local = G.nbr_local[g];
+    for (int64_t e0 = (int64_t)rg_block(S) * 256 + threadIdx.x; e0 < n; e0 += stride * U) {
+        int32_t u[U], r[U];
+#pragma unroll
+        for (int q = 0; q < U; ++q) u[q] = e0 + stride * q < n ? nbr[e0 + stride * q] : -1;
+        rg_ranked_positions<U>(u, rank, hop, S.words, pos, r);
+#pragma unroll
+        for (int q = 0; q < U; ++q)
+            if (u[q] >= 0) nbr_local[e0 + stride * q] = r[q];
+    }
+}
+
+// first_edge[position] = the first edge of the hop that names the new node.  A workgroup owns kSeenSlice of the new positions in
+// LDS and reads every edge's position.  With one global atomicMin per edge behind a read (the positions in 1.1 MB per batch) hop 2
+// of 8 batches of 1024 seeds, 4.6 M edges, took 180 us.
+constexpr int kSeenSlice = 40000;
+__device__ __forceinline__ void rg_seen_min(int32_t* first, int32_t a, int64_t e, uint32_t a0, uint32_t n) {
+    const uint32_t d = (uint32_t)a - a0;
+    if (d < n) atomicMin(&first[d], (int32_t)e);
+}
+
+__global__ void __launch_bounds__(1024) k_seen_min(const SampleGroup G, const SampleScratch S, int hop) {
+    extern __shared__ int32_t slice_first[];
+    constexpr int U = 4;                                 // 16-byte loads in flight per thread
+    const int g = rg_batch(S);
+    const int n_h = G.tier_off[g][hop + 1];
+    const int64_t a0 = n_h + (int64_t)rg_block(S) * kSeenSlice, left = G.tier_off[g][hop + 2] - a0;
+    if (left <= 0) return;                               // uniform per workgroup
+    const int n_here = (int)(left < kSeenSlice ? left : kSeenSlice);
+    for (int i = threadIdx.x; i < n_here; i += 1024) slice_first[i] = 0x7FFFFFFF;
+    const int n = G.indptr[g][n_h];
+    const int32_t* __restrict__ at = G.nbr_local[g];
+    __syncthreads();
+    const int to_line = (int)((16u - ((uint32_t)(uintptr_t)at & 15u)) & 15u) / 4;      // at[] may start at any 4-byte address
+    const int head = to_line < n ? to_line : n;
+    const int n4 = (n - head) / 4;
+    const int4* __restrict__ body = (const int4*)(at + head);
+    for (int i = threadIdx.x; i < n4; i += U * 1024) {
+        int4 x[U];
+#pragma unroll
+        for (int q = 0; q < U; ++q) x[q] = body[i + q * 1024 < n4 ? i + q * 1024 : i];
+#pragma unroll
+        for (int q = 0; q < U; ++q) {
+            if (i + q * 1024 >= n4) break;
+            const int e = head + 4 * (i + q * 1024);
+            rg_seen_min(slice_first, x[q].x, e, (uint32_t)a0, (uint32_t)n_here);
+            rg_seen_min(slice_first, x[q].y, e + 1, (uint32_t)a0, (uint32_t)n_here);
+            rg_seen_min(slice_first, x[q].z, e + 2, (uint32_t)a0, (uint32_t)n_here);
+            rg_seen_min(slice_first, x[q].w, e + 3, (uint32_t)a0, (uint32_t)n_here);
+        }
+    }
+    const int tail = head + 4 * n4;
+    if ((int)threadIdx.x < head) rg_seen_min(slice_first, at[threadIdx.x], threadIdx.x, (uint32_t)a0, (uint32_t)n_here);
+    if ((int)threadIdx.x < n - tail) rg_seen_min(slice_first, at[tail + threadIdx.x], tail + threadIdx.x, (uint32_t)a0, (uint32_t)n_here);
+    __syncthreads();
+    int32_t* __restrict__ out = S.first_edge + g * S.frontier_stride + a0;
+    for (int i = threadIdx.x; i < n_here; i += 1024) out[i] = slice_first[i];
+}
+
+constexpr int kSeenEdges = 4096;       // edges per workgroup: 1024 threads x 4
+
+__global__ void __launch_bounds__(1024) k_seen_count(const SampleGroup G, const SampleScratch S, int hop) {
+    __shared__ int part[1024 / RG_WAVE];
+    const int g = rg_batch(S);
+    const unsigned blk = rg_block(S);
+    const int n_h = G.tier_off[g][hop + 1];
+    const int64_t n = G.indptr[g][n_h], first = (int64_t)blk * kSeenEdges;
+    if (first >= n) return;                              // uniform per workgroup
+    const int32_t* __restrict__ at = G.nbr_local[g];
+    const int32_t* __restrict__ first_edge = S.first_edge + g * S.frontier_stride;
+    int c = 0;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        const int64_t e = first + q * 1024 + threadIdx.x;
+        const int32_t a = e < n ? at[e] : -1;
+        c += a >= n_h && first_edge[a] == (int32_t)e;
+    }
+    c = rg_wave_sum(c);
+    if (rg_lane() == 0) part[threadIdx.x >> 6] = c;
+    __syncthreads();
+    if (threadIdx.x < RG_WAVE) {
+        c = rg_wave_sum(threadIdx.x < 1024 / RG_WAVE ? part[threadIdx.x] : 0);
+        if (threadIdx.x == 0) S.chunk_sum[g * S.chunk_stride + blk] = c;
+    }
+}
+
+// The nodes that edges open, in edge order, and where each ascending position ended up.
+__global__ void __launch_bounds__(1024) k_seen_emit(const SampleGroup G, const SampleScratch S, int hop) {
+    constexpr int NW = 1024 / RG_WAVE;
+    __shared__ int smem[NW + 1];
+    __shared__ int part[NW];
+    const int g = rg_batch(S);
+    const unsigned blk = rg_block(S);
+    const int n_h = G.tier_off[g][hop + 1];
+    const int64_t n = G.indptr[g][n_h], first = (int64_t)blk * kSeenEdges;
+    if (first >= n) return;                              // uniform per workgroup
+    const int32_t* __restrict__ at = G.nbr_local[g];
+    const int32_t* __restrict__ nbr = G.nbr[g];
+    const int32_t* __restrict__ first_edge = S.first_edge + g * S.frontier_stride;
+    const int32_t* __restrict__ chunk_sum = S.chunk_sum + g * S.chunk_stride;
+    int before = 0;                                      // nodes opened by the edges in front of this workgroup's
+    for (unsigned c = threadIdx.x; c < blk; c += 1024) before += chunk_sum[c];
+    before = rg_wave_sum(before);
+    if (rg_lane() == 0) part[threadIdx.x >> 6] = before;
+    const int64_t e0 = first + threadIdx.x * 4;
+    int32_t a[4];
+    bool opens[4];
+    int c = 0;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) a[q] = e0 + q < n ? at[e0 + q] : -1;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        opens[q] = a[q] >= n_h && first_edge[a[q]] == (int32_t)(e0 + q);
+        c += opens[q];
+    }
+    int total;
+    int out = n_h + rg_block_excl_scan<NW>(c, smem, &total);               // its barriers publish part[]
+#pragma unroll
+    for (int q = 0; q < NW; ++q) out += part[q];
+    int32_t* __restrict__ nodes = G.nodes[g];
+    int32_t* __restrict__ place = S.place + g * S.frontier_stride;
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+        if (opens[q]) {
+            nodes[out] = nbr[e0 + q];
+            place[a[q]] = out++;
+        }
+}
+
 // ---------------------------------------------------------------------------- relabelling, all hops in one launch
 // A member's position never changes, so nbr_local of every hop is written after the last one.
 struct RelabelGroup {
@@ -858,17 +1041,7 @@ __global__ void __launch_bounds__(256) k_relabel(const RelabelGroup R, const Sam
 #pragma unroll
             for (int q = 0; q < U; ++q) u[q] = e0 + stride * q < n ? nbr[e0 + stride * q] : -1;
             if (RANKED) {
-                uint2 x[U];
-#pragma unroll
-                for (int q = 0; q < U; ++q) x[q] = u[q] >= 0 ? rank[(uint32_t)u[q] >> 5] : make_uint2(0u, 0u);
-#pragma unroll
-                for (int q = 0; q < U; ++q) {
-                    if (u[q] < 0) continue;
-                    const uint32_t bit = 1u << (u[q] & 31);
-                    int t = hop;
-                    while (!(x[q].x & bit) && --t >= 0) x[q] = rank[((uint32_t)u[q] >> 5) - (int64_t)(hop - t) * S.words];
-                    r[q] = t >= 0 ? (int32_t)x[q].y + __popc(x[q].x & (bit - 1u)) : pos[u[q]];
-                }
+                rg_ranked_positions<U>(u, rank, hop, S.words, pos, r);
             } else {
 #pragma unroll
                 for (int q = 0; q < U; ++q) r[q] = u[q] >= 0 ? pos[u[q]] : 0;
@@ -1024,6 +1197,31 @@ __global__ void __launch_bounds__(1024) k_sample_small(const RP* __restrict__ ro
     for (int w = threadIdx.x; w < words; w += 1024) visited_out[g * words64 + w] = visited[w];
 }
 
+// kTierRankedSeen: nbr_local holds ascending positions; the seeds' are their own.
+__global__ void __launch_bounds__(256) k_seen_relabel(const RelabelGroup R, const SampleScratch S) {
+    constexpr int U = 4;
+    const int g = rg_batch(S);
+    const int64_t stride = (int64_t)rg_blocks_per_batch(S) * 256;
+    const int32_t* __restrict__ place = S.place + g * S.frontier_stride;
+    const int seeds = R.tier_off[g][1];
+    for (int hop = S.hops - 1; hop >= 0; --hop) {
+        int32_t* __restrict__ nbr_local = R.nbr_local[hop][g];
+        if (!nbr_local) continue;
+        const int64_t n = R.indptr[hop][g][R.tier_off[g][hop + 1]];
+        for (int64_t e0 = (int64_t)rg_block(S) * 256 + threadIdx.x; e0 < n; e0 += stride * U) {
+            int32_t a[U];
+#pragma unroll
+            for (int q = 0; q < U; ++q) a[q] = e0 + stride * q < n ? nbr_local[e0 + stride * q] : -1;
+#pragma unroll
+            for (int q = 0; q < U; ++q)
+                if (a[q] >= seeds) a[q] = place[a[q]];
+#pragma unroll
+            for (int q = 0; q < U; ++q)
+                if (e0 + stride * q < n) nbr_local[e0 + stride * q] = a[q];
+        }
+    }
+}
+
 // Per-batch strides of the scratch slices for a graph of N nodes and frontiers of up to `frontier` nodes.
 // max_edges: the largest per-hop edge bound when tiers are built from the edge list (first-seen order), else 0.
 void sampler_scratch_shape(int64_t N, int64_t frontier, int64_t max_edges, SampleScratch& S) {
@@ -1038,7 +1236,7 @@ void sampler_scratch_shape(int64_t N, int64_t frontier, int64_t max_edges, Sampl
     S.splits = 1;
     S.hops = 1;
     S.rank = nullptr;
-    S.first_key = nullptr;
+    S.first_edge = S.place = S.first_key = nullptr;
     S.group = 1;
     S.xcd_map = 1;
 }
@@ -1088,7 +1286,7 @@ int grid_for(int64_t work_items, int per_block, int64_t cap) {
 
 }  // namespace
 
-rg_status rg_sampler_reserve(rg_ctx* ctx, int64_t num_nodes, int64_t max_frontier, int group, int hops, int64_t max_edges, bool first_seen) {
+rg_status rg_sampler_reserve(rg_ctx* ctx, int64_t num_nodes, int64_t max_frontier, int group, int hops, int64_t max_edges, bool first_seen, bool ranked_seen) {
     SampleScratch S;
     sampler_scratch_shape(num_nodes, max_frontier, max_edges, S);
     const size_t g = (size_t)group;
@@ -1097,13 +1295,14 @@ rg_status rg_sampler_reserve(rg_ctx* ctx, int64_t num_nodes, int64_t max_frontie
     // marked: one bitmap per batch, or one per batch and split of the sliced marking (which is bounded for all batches together)
     const size_t bitmaps = S.slices ? (size_t)rg_max64((int64_t)g, kSliceGroups / S.slices) : g;
     if ((st = rg_ensure(ctx, ctx->marked, bitmaps * S.words * 4)) != RG_OK) return st;
-    if (S.slices && !first_seen && (st = rg_ensure(ctx, ctx->rank, g * (size_t)hops * S.words * 8)) != RG_OK) return st;
+    if (S.slices && (!first_seen || ranked_seen) && (st = rg_ensure(ctx, ctx->rank, g * (size_t)hops * S.words * 8)) != RG_OK) return st;
     if ((st = rg_ensure(ctx, ctx->pos, g * (size_t)num_nodes * 4)) != RG_OK) return st;
     if ((st = rg_ensure(ctx, ctx->chunk_sum, g * S.chunk_stride * 4)) != RG_OK) return st;
     if ((st = rg_ensure(ctx, ctx->row_start, g * S.frontier_stride * 8)) != RG_OK) return st;
     if ((st = rg_ensure(ctx, ctx->row_deg, g * S.frontier_stride * 4)) != RG_OK) return st;
     // first-seen order: the first-edge keys must be all-zero between hops (every hop leaves them zeroed)
-    if (first_seen && (st = rg_ensure(ctx, ctx->first_key, g * (size_t)num_nodes * 4, true)) != RG_OK) return st;
+    if (first_seen && !ranked_seen && (st = rg_ensure(ctx, ctx->first_key, g * (size_t)num_nodes * 4, true)) != RG_OK) return st;
+    if (ranked_seen && (st = rg_ensure(ctx, ctx->seen, g * S.frontier_stride * 8)) != RG_OK) return st;
     return RG_OK;
 }
 
@@ -1111,6 +1310,7 @@ rg_status rg_sampler_reserve(rg_ctx* ctx, int64_t num_nodes, int64_t max_frontie
 rg_status rg_sampler_init(rg_ctx* ctx) {
     RG_HIP(ctx, hipFuncSetAttribute((const void*)k_sample_init, hipFuncAttributeMaxDynamicSharedMemorySize, kSliceWords * 4));
     RG_HIP(ctx, hipFuncSetAttribute((const void*)k_slice_mark, hipFuncAttributeMaxDynamicSharedMemorySize, kSliceWords * 4));
+    RG_HIP(ctx, hipFuncSetAttribute((const void*)k_seen_min, hipFuncAttributeMaxDynamicSharedMemorySize, kSeenSlice * 4));
     const void* small[] = {(const void*)k_sample_small<int32_t, 8>, (const void*)k_sample_small<int32_t, 16>, (const void*)k_sample_small<int32_t, 32>,
                            (const void*)k_sample_small<int64_t, 8>, (const void*)k_sample_small<int64_t, 16>, (const void*)k_sample_small<int64_t, 32>};
     for (const void* f : small) RG_HIP(ctx, hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)(kSmallNodes / 4)));
@@ -1226,11 +1426,21 @@ rg_status rg_sample_blocks_group(rg_ctx* ctx, const rg_csr* csr, int32_t group, 
     sampler_scratch_shape(N, fub_max[num_hops], max_edges, S);
     const int64_t words = S.words;
     ctx->last_sample_group = 0;                       // no membership bitmaps to add until this call has been queued
-    rg_status st = rg_sampler_reserve(ctx, N, fub_max[num_hops], group, num_hops, max_edges, first_seen);
+    int64_t edges_bound = 0;
+    for (int h = 0; h < num_hops; ++h) edges_bound += eub_max[h];
+    // in first-seen order the edges' ascending positions are kept where their final ones go
+    bool ranked_seen = first_seen && rg_use_ranked_seen(S.slices, N, edges_bound, group);
+    for (int g = 0; g < group && ranked_seen; ++g)
+        for (int h = 0; h < num_hops; ++h)
+            ranked_seen = ranked_seen && eub_max[h] <= kRankedSeenEdges && out[g].nbr_local && out[g].nbr_local[h] && out[g].nbr_local[h] != out[g].nbr[h];
+    const TierMode mode = ranked_seen ? kTierRankedSeen : first_seen ? kTierFirstSeen : (rg_use_slices(S.slices, N, edges_bound) ? kTierSliced : kTierAtomic);
+    rg_status st = rg_sampler_reserve(ctx, N, fub_max[num_hops], group, num_hops, max_edges, first_seen, ranked_seen);
     if (st != RG_OK) return st;
     S.hops = num_hops;
     S.rank = (uint2*)ctx->rank.p;
-    S.first_key = first_seen ? (int32_t*)ctx->first_key.p : nullptr;
+    S.first_key = mode == kTierFirstSeen ? (int32_t*)ctx->first_key.p : nullptr;
+    S.first_edge = (int32_t*)ctx->seen.p;
+    S.place = S.first_edge + group * S.frontier_stride;
     S.group = group;
     S.xcd_map = ctx->knobs.xcd_map;
     S.visited = (uint32_t*)ctx->visited.p;
@@ -1249,13 +1459,10 @@ rg_status rg_sample_blocks_group(rg_ctx* ctx, const rg_csr* csr, int32_t group, 
         G.num_seeds[g] = live ? num_seeds[g] : 0;
         G.nodes[g] = live ? out[g].nodes : nullptr;
         G.tier_off[g] = live ? out[g].tier_off : nullptr;
-        G.indptr[g] = G.nbr[g] = G.edges_out[g] = nullptr;
+        G.indptr[g] = G.nbr[g] = G.nbr_local[g] = G.edges_out[g] = nullptr;
     }
     const unsigned ug = (unsigned)group;
 
-    int64_t edges_bound = 0;
-    for (int h = 0; h < num_hops; ++h) edges_bound += eub_max[h];
-    const TierMode mode = first_seen ? kTierFirstSeen : (rg_use_slices(S.slices, N, edges_bound) ? kTierSliced : kTierAtomic);
     int max_fanout = 0;
     for (int h = 0; h < num_hops; ++h) max_fanout = fanouts[h] < 0 ? RG_MAX_FANOUT : (fanouts[h] > max_fanout ? fanouts[h] : max_fanout);
     if (!first_seen && rg_is_small(N, edges_bound) && max_fanout <= 32 && csr->num_edges < (1ll << 32)) {
@@ -1316,6 +1523,7 @@ rg_status rg_sample_blocks_group(rg_ctx* ctx, const rg_csr* csr, int32_t group, 
         for (int g = 0; g < group; ++g) {
             G.indptr[g] = out[g].indptr[h];
             G.nbr[g] = out[g].nbr[h];
+            G.nbr_local[g] = out[g].nbr_local ? out[g].nbr_local[h] : nullptr;
             G.edges_out[g] = out[g].num_edges ? out[g].num_edges + h : nullptr;
             R.indptr[h][g] = out[g].indptr[h];
             R.nbr[h][g] = out[g].nbr[h];
@@ -1342,7 +1550,7 @@ rg_status rg_sample_blocks_group(rg_ctx* ctx, const rg_csr* csr, int32_t group, 
 #define RG_LAUNCH_DRAW_K(NP, MODE)                                                                                    \
     do { if (F <= 8) RG_LAUNCH_DRAW(8, NP, MODE); else if (F <= 16) RG_LAUNCH_DRAW(16, NP, MODE); else RG_LAUNCH_DRAW(32, NP, MODE); } while (0)
 #define RG_LAUNCH_DRAW_N(MODE) do { if (few) RG_LAUNCH_DRAW_K(64, MODE); else RG_LAUNCH_DRAW_K(256, MODE); } while (0)
-            if (mode == kTierSliced) RG_LAUNCH_DRAW_N(kTierSliced);
+            if (mode == kTierSliced || mode == kTierRankedSeen) RG_LAUNCH_DRAW_N(kTierSliced);
             else if (mode == kTierAtomic) RG_LAUNCH_DRAW_N(kTierAtomic);
             else RG_LAUNCH_DRAW_N(kTierFirstSeen);
 #undef RG_LAUNCH_DRAW_N
@@ -1357,7 +1565,7 @@ rg_status rg_sample_blocks_group(rg_ctx* ctx, const rg_csr* csr, int32_t group, 
             const unsigned sample_blocks = (unsigned)grid_for(fub_max[h], 1, (int64_t)ctx->num_cus * 64);
 #define RG_LAUNCH_WAVE(MODE)                                                                                          \
     k_hop_sample_wave<MODE><<<sample_blocks * ug, RG_WAVE, 0, s>>>(csr->col_idx, G, S, F, (uint32_t)h, k0, k1, epoch)
-            if (mode == kTierSliced) RG_LAUNCH_WAVE(kTierSliced);
+            if (mode == kTierSliced || mode == kTierRankedSeen) RG_LAUNCH_WAVE(kTierSliced);
             else if (mode == kTierAtomic) RG_LAUNCH_WAVE(kTierAtomic);
             else RG_LAUNCH_WAVE(kTierFirstSeen);
 #undef RG_LAUNCH_WAVE
@@ -1365,7 +1573,7 @@ rg_status rg_sample_blocks_group(rg_ctx* ctx, const rg_csr* csr, int32_t group, 
         }
         RG_LAUNCH_CHECK(ctx, "k_hop_sample");
 
-        if (mode == kTierSliced) {
+        if (mode == kTierSliced || mode == kTierRankedSeen) {
             const int64_t split_edges = rg_max64(kSplitEdges, 2 * (int64_t)S.slice_words);
             S.splits = (int)rg_max64(1, rg_min64(eub_max[h] / split_edges, kSliceGroups / (S.slices * group)));
             k_slice_mark<<<(unsigned)(S.slices * S.splits) * ug, 1024, (size_t)S.slice_words * 4, s>>>(G, S, h);
@@ -1373,8 +1581,22 @@ rg_status rg_sample_blocks_group(rg_ctx* ctx, const rg_csr* csr, int32_t group, 
             const unsigned tier_blocks = (unsigned)rg_max64(1, rg_div_up(words, kTierWords));
             k_slice_count<<<tier_blocks * ug, kTierWords, 0, s>>>(S);
             RG_LAUNCH_CHECK(ctx, "k_slice_count");
-            k_slice_emit<<<tier_blocks * ug, kTierWords, 0, s>>>(G, S, h);
+            if (mode == kTierSliced) k_slice_emit<false><<<tier_blocks * ug, kTierWords, 0, s>>>(G, S, h);
+            else k_slice_emit<true><<<tier_blocks * ug, kTierWords, 0, s>>>(G, S, h);
             RG_LAUNCH_CHECK(ctx, "k_slice_emit");
+            if (mode == kTierRankedSeen) {
+                // the edges that open a node, counted per block of the edge list, emitted in edge order
+                k_seen_rank<<<(unsigned)grid_for(eub_max[h], 1024, (int64_t)ctx->num_cus * 16) * ug, 256, 0, s>>>(G, S, h);
+                RG_LAUNCH_CHECK(ctx, "k_seen_rank");
+                const int64_t most_new = rg_min64(N, eub_max[h]);
+                k_seen_min<<<(unsigned)grid_for(most_new, kSeenSlice, 1 << 30) * ug, 1024, (size_t)rg_min64(most_new, kSeenSlice) * 4, s>>>(G, S, h);
+                RG_LAUNCH_CHECK(ctx, "k_seen_min");
+                const unsigned seen_blocks = (unsigned)grid_for(eub_max[h], kSeenEdges, 1 << 30);
+                k_seen_count<<<seen_blocks * ug, 1024, 0, s>>>(G, S, h);
+                RG_LAUNCH_CHECK(ctx, "k_seen_count");
+                k_seen_emit<<<seen_blocks * ug, 1024, 0, s>>>(G, S, h);
+                RG_LAUNCH_CHECK(ctx, "k_seen_emit");
+            }
         } else if (mode == kTierFirstSeen) {
             // new tier: edges that open a node, counted per block of the edge list, scanned, emitted in edge order
             const int fs_blocks = (int)rg_max64(1, rg_div_up(eub_max[h], kEdgesPerBlock));
@@ -1398,6 +1620,7 @@ rg_status rg_sample_blocks_group(rg_ctx* ctx, const rg_csr* csr, int32_t group, 
     if (relabel_edges > 0) {
         const unsigned blocks = (unsigned)grid_for(relabel_edges, 1024, (int64_t)ctx->num_cus * 16);
         if (mode == kTierSliced) k_relabel<true><<<blocks * ug, 256, 0, s>>>(R, S);
+        else if (mode == kTierRankedSeen) k_seen_relabel<<<blocks * ug, 256, 0, s>>>(R, S);
         else k_relabel<false><<<blocks * ug, 256, 0, s>>>(R, S);
         RG_LAUNCH_CHECK(ctx, "k_relabel");
     }

@@ -54,6 +54,9 @@ def _sparse_graph(n, active, degree, rng):
     (20_000, 20_000, 40, [700, 900], (32, 31)),         # over 8192 new ids within 512 words
     (200_001, 150_000, 30, [1000, 1, 999], (25, 10)),   # the edge list split between workgroups
     (3_000_017, 400_000, 12, [900] * 8, (40, 3)),       # wavefront-per-node draw in front of the slices
+    (300_007, 250_000, 30, [1500, 0, 1200, 1, 900, 1500, 1500, 1500], (25, 10)),    # over 2 Mi edges: first-seen order by rank words
+    (300_007, 250_000, 30, [1500] * 4, (40, 10)),
+    (2_600_021, 900_000, 12, [2000] * 4, (15, 10, 5)),
     (4_194_337, 200_000, 12, [60, 50], (5, 3)),         # atomic marking on a graph that has slices
     (4_194_337, 200_000, 12, [3000, 2000], (15, 10)),   # slices again: the edges outweigh the bitmaps
     (41_000_033, 200_000, 12, [300, 200], (5, 3)),      # no slices
@@ -82,6 +85,12 @@ def test_blocks_across_the_ways_to_build_a_tier(B, ctx, n, active, degree, seeds
             assert_batch_equal(HipBatch(o, len(fanouts)), orc, len(fanouts), f"batch {j} epoch {epoch}")
             oracle.access_histogram(orc.input_nodes, want)
         assert np.array_equal(counts.cpu().numpy().view(np.uint32), want)
+    if first_seen and n == 300_007:                     # without relabelling there is no room for the ranks: the same nodes
+        again = [B.BlockBuffers(n, ci.size, max(k, 1), fanouts, DEV, with_local=False) for k in seeds]
+        ctx.sample_blocks_group(csr, [_i32(x) for x in lists], fanouts, 77, 1, again, node_order=B.RG_ORDER_FIRST_SEEN)
+        for o, w in zip(again, outs):
+            k = int(o.tier_off[-1])
+            assert torch.equal(o.tier_off, w.tier_off) and torch.equal(o.nodes[:k], w.nodes[:k])
 
 
 def test_decoupled_misses_wait_for_the_reader_of_their_buffer(B):
