@@ -136,6 +136,11 @@ class EpochPipeline:
         if mirror_pulls not in ("group", "batch"):
             raise ValueError("mirror_pulls must be 'group' or 'batch'")
         self.group_pulls = self.mirror and mirror_pulls == "group"
+        # Short sampler calls in front cost the host about 0.1 ms each, so they have to save link time: they do from about
+        # 512 MB that one batch may name.  Whole epochs with and without them, by that bound: 14 batches 33 MB 2.0 / 1.5 ms, 19
+        # batches 9 MB 2.1 / 1.6; 40 batches 300 MB 7.13 / 7.16 and 6.93 / 6.87; 20 batches 300 MB 6.18 / 6.09 and 6.88 / 7.02,
+        # 768 MB 15.3 / 16.6, 1.1 GB 19.1 / 19.4.
+        self.ramp = self.group_pulls and min(wl.n_remote, self.slot) * wl.stride * 4 >= 512_000_000
         self.states = [_EpochState(wl, self.H, self.slot, self.max_batches, device, keep, mirror=self.mirror)
                        for _ in range(2 if double_buffer else 1)]
         if self.keep_rows and len(self.states) > 1:
@@ -286,7 +291,8 @@ class EpochPipeline:
             calls = []
             for k in range(self.period_epochs):
                 i0 = k * len(batch_ids)
-                for size in self._call_sizes(len(batch_ids), gsz, first=k == 0, last=k == self.period_epochs - 1):
+                for size in self._call_sizes(len(batch_ids), gsz, first=k == 0, last=k == self.period_epochs - 1,
+                                             ramp=self.ramp):
                     calls.append((k, i0, i0 + size))
                     i0 += size
             for call, (k, i0, i1) in enumerate(calls):
@@ -343,13 +349,13 @@ class EpochPipeline:
         st.sizes = None
         st.pulls_queued = self.mirror
 
-    def _call_sizes(self, n, gsz, first, last):
+    def _call_sizes(self, n, gsz, first, last, ramp=False):
         """Batches per sampler call for the n batches of one epoch of a period.  Groups of gsz, except that with one pull
-        per call the period opens with single batches and calls that grow by a third of what has gone before (the gathers of
-        a call's batches wait for its pull, and the first batches name most of the rows: a full group among them holds its
-        gathers back until they have to follow the last pull) and closes with calls of 2, 1 and 1 (a short last pull leaves a
-        short tail behind the link's last byte).  20 batches of 4096 seeds on 1 M nodes of 256 floats, pulls done after 13.3 ms:
-        one batch in front of the groups 16.7 ms, calls of 1, 1, 2, 4, 8 15.7, these 15.3."""
+        per call the period opens with a single batch (its rows start crossing the link while the next calls sample) and
+        closes with calls of 2, 1 and 1 batches (the gathers of a call's batches wait for its pull, so a short last pull
+        leaves a short tail behind the link's last byte).  Where a batch's pull can take milliseconds (ramp), the calls in
+        between grow from single batches by a third of what has gone before: the first batches name most of the rows, and
+        a full group among them holds its gathers back until they have to follow the last pull."""
         if not self.group_pulls or gsz == 1:
             return [min(gsz, n - i) for i in range(0, n, gsz)]
         tail = []
@@ -360,7 +366,7 @@ class EpochPipeline:
         head = []
         if first and n > 1:
             size = 1
-            while size < gsz and sum(head) + size + sum(tail) <= n:
+            while size < gsz and sum(head) + size + sum(tail) <= n and (ramp or not head):
                 head.append(size)
                 size = max(1, sum(head) // 3)
         body = n - sum(head) - sum(tail)

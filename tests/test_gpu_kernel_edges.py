@@ -278,3 +278,31 @@ def test_gather_one_launch_edges(B, ctx, rows, dim, stride, mirror):
             out.fill_(float("nan"))
             ctx.gather_run(0, rows, cache, local, remote, dim, out, miss_stream=side)
             assert np.array_equal(out[:k, :dim].cpu().numpy(), want)
+
+
+def test_mirrored_pulls_of_growing_calls(B):
+    """Calls that grow from single batches: every size adds up, and the gathers of an epoch sampled that way are right."""
+    import dataclasses
+
+    import synth
+    from paper_2505_10806_amd.pipeline import EpochPipeline
+    cfg = dataclasses.replace(synth.get_config("tiny"), cache_frac=1.0, max_batches=None)
+    wl = synth.build_workload(cfg, seed=6, device=DEV)
+    pipe = EpochPipeline(wl, device=DEV)
+    assert pipe.mirror and not pipe.ramp                # a small remote partition
+    pipe.ramp = True
+    for n in (1, 2, 3, 7, 20, 61):
+        for g in (2, 8, 16):
+            for first in (False, True):
+                for last in (False, True):
+                    sizes = pipe._call_sizes(n, g, first, last, ramp=True)
+                    assert sum(sizes) == n and all(0 < s <= g for s in sizes), (n, g, first, last, sizes)
+    assert pipe._call_sizes(20, 8, True, True, ramp=True) == [1, 1, 1, 1, 1, 1, 2, 2, 3, 3, 2, 1, 1]
+    taken = []
+    with torch.cuda.stream(torch.cuda.Stream()):
+        pipe.run_epoch(1, pipe.batches_per_epoch, lambda p, b: taken.append(p.out[:p.sizes[b], :cfg.feat_dim].clone()))
+        torch.cuda.synchronize()
+        for b, rows in enumerate(taken):
+            assert torch.equal(rows, wl.features[pipe.arena[b, :pipe.sizes[b]].long()]), f"batch {b}"
+        assert int(pipe.stats[:, 2].sum()) == 0
+    pipe.close()
