@@ -71,10 +71,11 @@ __global__ void __launch_bounds__(256) k_hist_bounds(const int32_t* __restrict__
 }
 
 // FIRST: also record, per id, the smallest batch index whose list contains it (first_batch[v] = min(old, b)); b0 = index of the
-// first of these batches.
+// first of these batches.  bounds == NULL (no scratch to be had): the workgroup bisects every run for its range itself.
 template <bool FIRST>
 __global__ void __launch_bounds__(1024) k_histogram_runs(const int32_t* __restrict__ nodes, int64_t batch_stride,
-                                                         const int32_t* __restrict__ bounds, int num_batches, int num_hops, int b0,
+                                                         const int32_t* __restrict__ tier_off, const int32_t* __restrict__ bounds,
+                                                         int num_batches, int num_hops, int b0,
                                                          uint32_t* __restrict__ counts, uint32_t* __restrict__ first_batch,
                                                          int64_t num_nodes, int range) {
     constexpr int U = 4;                                  // entries in flight per lane
@@ -93,7 +94,21 @@ __global__ void __launch_bounds__(1024) k_histogram_runs(const int32_t* __restri
     for (int tile = 0; tile < num_runs; tile += kHistRunTile) {
         __syncthreads();                                  // priv zeroed / previous tile's segments consumed
         const int r = tile + threadIdx.x;
-        if (threadIdx.x < kHistRunTile && r < num_runs) {
+        if (!bounds && threadIdx.x < kHistRunTile && r < num_runs) {
+            const int b = r / num_hops, t = r % num_hops + 1;
+            const int32_t* to = tier_off + (int64_t)b * (num_hops + 2);
+            const int32_t* list = nodes + (int64_t)b * batch_stride;
+            for (int side = 0; side < 2; ++side) {
+                const int64_t key = v0 + (int64_t)side * range;
+                int lo = to[t], hi = to[t + 1];
+                while (lo < hi) {
+                    const int mid = lo + (hi - lo) / 2;
+                    if (list[mid] < key) lo = mid + 1; else hi = mid;
+                }
+                (side ? seg_hi : seg_lo)[threadIdx.x] = lo;
+            }
+        }
+        if (bounds && threadIdx.x < kHistRunTile && r < num_runs) {
             const int32_t* at = bounds + (int64_t)r * (gridDim.x + 1) + blockIdx.x;
             seg_lo[threadIdx.x] = at[0];
             seg_hi[threadIdx.x] = at[1];
@@ -960,11 +975,12 @@ rg_status rg_access_histogram_epoch(rg_ctx* ctx, const int32_t* nodes, int64_t b
     // batches per launch: the bounds of their runs fit the scratch, and a grid's second dimension
     const int64_t per_batch = (int64_t)num_hops * (ranges + 1);
     const int64_t most = rg_min64(num_batches, rg_max64(1, kHistBoundsMax / per_batch));
-    rg_status st;
-    if ((int64_t)(ctx->hist_bounds.bytes / 4) < per_batch * rg_min64(most, kHistBoundsBatches) &&
-        (st = rg_ensure(ctx, ctx->hist_bounds, (size_t)(per_batch * most) * 4)) != RG_OK) return st;
-    const int step = (int)rg_min64((int64_t)(ctx->hist_bounds.bytes / 4) / per_batch, 65535 / num_hops);
-    int32_t* bounds = (int32_t*)ctx->hist_bounds.p;
+    // without scratch for one batch's bounds, in a captured call or for want of memory, the counting kernel searches for itself
+    if ((int64_t)(ctx->hist_bounds.bytes / 4) < per_batch * rg_min64(most, kHistBoundsBatches) && !rg_capturing(s))
+        (void)rg_ensure(ctx, ctx->hist_bounds, (size_t)(per_batch * most) * 4);
+    const int fit = (int)rg_min64((int64_t)(ctx->hist_bounds.bytes / 4) / per_batch, 65535 / num_hops);
+    const int step = fit > 0 ? fit : num_batches;
+    int32_t* bounds = fit > 0 ? (int32_t*)ctx->hist_bounds.p : nullptr;
     const int tok = rg_prof_begin(ctx, RG_K_HISTOGRAM, s);
     if (max_seeds > 0) {
         dim3 seed_grid((unsigned)rg_min64(rg_div_up(max_seeds, 256), 64), (unsigned)num_batches);
@@ -973,12 +989,14 @@ rg_status rg_access_histogram_epoch(rg_ctx* ctx, const int32_t* nodes, int64_t b
     for (int b0 = 0; b0 < num_batches; b0 += step) {
         const int nb = num_batches - b0 < step ? num_batches - b0 : step;
         const int32_t* list = nodes + (int64_t)b0 * batch_stride;
-        k_hist_bounds<<<dim3((unsigned)rg_div_up(ranges + 1, 256), (unsigned)(nb * num_hops)), 256, 0, s>>>(
-            list, batch_stride, tier_off + (int64_t)b0 * (num_hops + 2), num_hops, num_nodes, range, ranges, bounds);
+        const int32_t* tiers = tier_off + (int64_t)b0 * (num_hops + 2);
+        if (bounds)
+            k_hist_bounds<<<dim3((unsigned)rg_div_up(ranges + 1, 256), (unsigned)(nb * num_hops)), 256, 0, s>>>(
+                list, batch_stride, tiers, num_hops, num_nodes, range, ranges, bounds);
         if (first_batch)
-            k_histogram_runs<true><<<ranges, 1024, 0, s>>>(list, batch_stride, bounds, nb, num_hops, b0, counts, first_batch, num_nodes, range);
+            k_histogram_runs<true><<<ranges, 1024, 0, s>>>(list, batch_stride, tiers, bounds, nb, num_hops, b0, counts, first_batch, num_nodes, range);
         else
-            k_histogram_runs<false><<<ranges, 1024, 0, s>>>(list, batch_stride, bounds, nb, num_hops, b0, counts, nullptr, num_nodes, range);
+            k_histogram_runs<false><<<ranges, 1024, 0, s>>>(list, batch_stride, tiers, bounds, nb, num_hops, b0, counts, nullptr, num_nodes, range);
     }
     rg_prof_end(ctx, tok, s);
     RG_LAUNCH_CHECK(ctx, "k_histogram_runs");

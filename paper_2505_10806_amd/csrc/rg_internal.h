@@ -89,6 +89,12 @@ rg_status rg_set_error(rg_ctx* ctx, rg_status code, const char* fmt, ...);
 rg_status rg_ensure(rg_ctx* ctx, RgBuf& buf, size_t bytes, bool zero_new = false);
 // RG_OK if kernels on the ctx's device may dereference p (device, managed or pinned/registered host memory).
 rg_status rg_check_device_readable(rg_ctx* ctx, const void* p, const char* what);
+// True while s records a graph: nothing may be allocated then.
+static inline bool rg_capturing(hipStream_t s) {
+    hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(s, &status) != hipSuccess) { (void)hipGetLastError(); return false; }
+    return status == hipStreamCaptureStatusActive;
+}
 // Scratch with which an epoch histogram of any number of batches on num_nodes nodes allocates nothing.
 rg_status rg_histogram_reserve(rg_ctx* ctx, int64_t num_nodes);
 // Makes every gather ticket hold at least `rows` rows (a reallocation invalidates prepared tickets).

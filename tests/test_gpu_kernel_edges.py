@@ -188,6 +188,53 @@ def test_epoch_histogram_range_edges(B, ctx, n, batches, hops, skew):
     assert np.array_equal(counts.cpu().numpy().view(np.uint32), 2 * want)
 
 
+def _captured(call):
+    """The call recorded into a graph on a side stream."""
+    graph, side = torch.cuda.CUDAGraph(), torch.cuda.Stream()
+    torch.cuda.synchronize()
+    with torch.cuda.stream(side):
+        graph.capture_begin(capture_error_mode="global")
+        call()
+        graph.capture_end()
+    torch.cuda.synchronize()
+    return graph
+
+
+# The first histogram of a context inside a captured graph, where no scratch can be allocated: runs searched by the counting kernel.
+@pytest.mark.parametrize("n,batches,hops", [(700, 3, 1), (300_007, 200, 3), (4_300_001, 5, 8)])
+def test_epoch_histogram_without_scratch(B, n, batches, hops):
+    log(f"[captured histogram] N={n} batches={batches} hops={hops}")
+    rng = np.random.default_rng(n)
+    per = min(n // 2, 300 * hops)
+    arena, tier_offs = np.zeros((batches, per + 2), dtype=np.int32), np.zeros((batches, hops + 2), dtype=np.int32)
+    want, first = np.zeros(n, dtype=np.uint32), np.full(n, 0xFFFFFFFF, dtype=np.uint32)
+    for b in range(batches):
+        ids = np.union1d(rng.integers(0, n, per), [0, n - 1])[:per + 2].astype(np.int32)
+        tier = rng.integers(0, hops + 1, ids.size)
+        parts = [ids[tier == t] for t in range(hops + 1)]
+        arena[b, :ids.size] = np.concatenate(parts)
+        tier_offs[b, 1:] = np.cumsum([p.size for p in parts])
+        oracle.access_histogram(ids, want)
+        first[ids] = np.minimum(first[ids], b)
+    arena_d, tiers_d, most = _i32(arena), _i32(tier_offs), int(tier_offs[:, 1].max())
+    counts, got_first = torch.zeros(n, dtype=torch.int32, device=DEV), torch.full((n,), -1, dtype=torch.int32, device=DEV)
+    ctx = B.Context(0)
+    graph = _captured(lambda: ctx.access_histogram_epoch(arena_d, tiers_d, batches, hops, most, counts, first_batch=got_first))
+    plain = _captured(lambda: ctx.access_histogram_epoch(arena_d, tiers_d, batches, hops, most, counts))
+    for replay in range(3):
+        counts.zero_()
+        got_first.fill_(-1)
+        graph.replay()
+        torch.cuda.synchronize()
+        assert np.array_equal(counts.cpu().numpy().view(np.uint32), want)
+        assert np.array_equal(got_first.cpu().numpy().view(np.uint32), first)
+        plain.replay()
+        torch.cuda.synchronize()
+        assert np.array_equal(counts.cpu().numpy().view(np.uint32), 2 * want)
+    del graph, plain
+    ctx.close()
+
+
 # Blocks of 4096 nodes; above 16 Mi nodes the blocks' totals are scanned by a launch of their own.  Capacities that cut a tie.
 @pytest.mark.parametrize("n", [1, 4095, 4096, 4097, 1_300_003, 16_777_217])
 @pytest.mark.parametrize("large", [False, True])
