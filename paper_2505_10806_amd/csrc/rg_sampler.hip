@@ -1338,8 +1338,9 @@ rg_status rg_epoch_schedule(rg_ctx* ctx, const int32_t* train_ids, int64_t n, ui
     while (((int64_t)kSchedAvg << lb) < n) ++lb;
     const int64_t buckets = 1ll << lb;
     rg_status st;
-    if ((st = rg_ensure(ctx, ctx->sched_keys, (size_t)n * 8)) != RG_OK) return st;
-    if ((st = rg_ensure(ctx, ctx->sched_ids, (size_t)n * 4)) != RG_OK) return st;
+    // sized for the largest n of as many buckets, so that a call of another such n, captured perhaps, allocates nothing
+    if ((st = rg_ensure(ctx, ctx->sched_keys, (size_t)(kSchedAvg * buckets) * 8)) != RG_OK) return st;
+    if ((st = rg_ensure(ctx, ctx->sched_ids, (size_t)(kSchedAvg * buckets) * 4)) != RG_OK) return st;
     if ((st = rg_ensure(ctx, ctx->sched_buckets, (size_t)(3 * buckets + 1) * 4)) != RG_OK) return st;
     uint64_t* keys = (uint64_t*)ctx->sched_keys.p;
     int32_t* ids = (int32_t*)ctx->sched_ids.p;

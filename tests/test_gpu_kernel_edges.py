@@ -235,6 +235,23 @@ def test_epoch_histogram_without_scratch(B, n, batches, hops):
     ctx.close()
 
 
+def test_schedule_captured_after_a_smaller_one(B):
+    """A schedule of no more than twice as many ids, up to the next power of two, finds the scratch of an earlier call."""
+    few, many = 4097, 8192
+    ids = np.random.default_rng(3).permutation(50_000)[:many].astype(np.int32)
+    ids_d, order = _i32(ids), torch.zeros(many, dtype=torch.int32, device=DEV)
+    ctx = B.Context(0)
+    ctx.epoch_schedule(ids_d[:few], 5, 1)
+    graph = _captured(lambda: ctx.epoch_schedule(ids_d, 5, 2, order))
+    for replay in range(3):
+        order.zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert np.array_equal(order.cpu().numpy(), oracle.epoch_schedule(ids, 5, 2))
+    del graph
+    ctx.close()
+
+
 # Blocks of 4096 nodes; above 16 Mi nodes the blocks' totals are scanned by a launch of their own.  Capacities that cut a tie.
 @pytest.mark.parametrize("n", [1, 4095, 4096, 4097, 1_300_003, 16_777_217])
 @pytest.mark.parametrize("large", [False, True])
