@@ -102,7 +102,7 @@ rg_status rg_gather_reserve(rg_ctx* ctx, int64_t rows);
 // Sizes the sampler scratch for `group` batches side by side on a graph of num_nodes nodes with cumulative
 // frontiers of up to max_frontier nodes (what rg_sample_blocks_group would otherwise grow on demand).
 rg_status rg_sampler_reserve(rg_ctx* ctx, int64_t num_nodes, int64_t max_frontier, int group, int hops = RG_MAX_HOPS,
-                             int64_t max_edges = 0, bool first_seen = false, bool ranked_seen = false);
+                             int64_t max_edges = 0, bool first_seen = false, bool sliced = true);
 // Allows the sampler's kernels the LDS they use on ctx->device (the device must be current).
 rg_status rg_sampler_init(rg_ctx* ctx);
 // Resolves the device address of the file-scope gather scratch for ctx->device (the device must be current).

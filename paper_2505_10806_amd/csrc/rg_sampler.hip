@@ -1286,23 +1286,31 @@ int grid_for(int64_t work_items, int per_block, int64_t cap) {
 
 }  // namespace
 
-rg_status rg_sampler_reserve(rg_ctx* ctx, int64_t num_nodes, int64_t max_frontier, int group, int hops, int64_t max_edges, bool first_seen, bool ranked_seen) {
+// Scratch of the tier kernels that mark in slices, more than the others use.
+struct SlicedBytes { size_t marked, rank, seen; };
+static SlicedBytes sliced_bytes(const SampleScratch& S, int group, int hops, bool first_seen) {
+    const size_t g = (size_t)group, bitmaps = (size_t)rg_max64(group, kSliceGroups / S.slices);
+    return {bitmaps * S.words * 4, g * (size_t)hops * S.words * 8, first_seen ? g * S.frontier_stride * 8 : 0};
+}
+
+rg_status rg_sampler_reserve(rg_ctx* ctx, int64_t num_nodes, int64_t max_frontier, int group, int hops, int64_t max_edges, bool first_seen, bool sliced) {
     SampleScratch S;
     sampler_scratch_shape(num_nodes, max_frontier, max_edges, S);
     const size_t g = (size_t)group;
     rg_status st;
     if ((st = rg_ensure(ctx, ctx->visited, g * S.words * 4)) != RG_OK) return st;
     // marked: one bitmap per batch, or one per batch and split of the sliced marking (which is bounded for all batches together)
-    const size_t bitmaps = S.slices ? (size_t)rg_max64((int64_t)g, kSliceGroups / S.slices) : g;
-    if ((st = rg_ensure(ctx, ctx->marked, bitmaps * S.words * 4)) != RG_OK) return st;
-    if (S.slices && (!first_seen || ranked_seen) && (st = rg_ensure(ctx, ctx->rank, g * (size_t)hops * S.words * 8)) != RG_OK) return st;
+    sliced = sliced && S.slices;
+    const SlicedBytes extra = sliced ? sliced_bytes(S, group, hops, first_seen) : SlicedBytes{g * S.words * 4, 0, 0};
+    if ((st = rg_ensure(ctx, ctx->marked, extra.marked)) != RG_OK) return st;
+    if ((st = rg_ensure(ctx, ctx->rank, extra.rank)) != RG_OK) return st;
+    if ((st = rg_ensure(ctx, ctx->seen, extra.seen)) != RG_OK) return st;
     if ((st = rg_ensure(ctx, ctx->pos, g * (size_t)num_nodes * 4)) != RG_OK) return st;
     if ((st = rg_ensure(ctx, ctx->chunk_sum, g * S.chunk_stride * 4)) != RG_OK) return st;
     if ((st = rg_ensure(ctx, ctx->row_start, g * S.frontier_stride * 8)) != RG_OK) return st;
     if ((st = rg_ensure(ctx, ctx->row_deg, g * S.frontier_stride * 4)) != RG_OK) return st;
     // first-seen order: the first-edge keys must be all-zero between hops (every hop leaves them zeroed)
-    if (first_seen && !ranked_seen && (st = rg_ensure(ctx, ctx->first_key, g * (size_t)num_nodes * 4, true)) != RG_OK) return st;
-    if (ranked_seen && (st = rg_ensure(ctx, ctx->seen, g * S.frontier_stride * 8)) != RG_OK) return st;
+    if (first_seen && (st = rg_ensure(ctx, ctx->first_key, g * (size_t)num_nodes * 4, true)) != RG_OK) return st;
     return RG_OK;
 }
 
@@ -1434,8 +1442,22 @@ rg_status rg_sample_blocks_group(rg_ctx* ctx, const rg_csr* csr, int32_t group, 
     for (int g = 0; g < group && ranked_seen; ++g)
         for (int h = 0; h < num_hops; ++h)
             ranked_seen = ranked_seen && eub_max[h] <= kRankedSeenEdges && out[g].nbr_local && out[g].nbr_local[h] && out[g].nbr_local[h] != out[g].nbr[h];
-    const TierMode mode = ranked_seen ? kTierRankedSeen : first_seen ? kTierFirstSeen : (rg_use_slices(S.slices, N, edges_bound) ? kTierSliced : kTierAtomic);
-    rg_status st = rg_sampler_reserve(ctx, N, fub_max[num_hops], group, num_hops, max_edges, first_seen, ranked_seen);
+    TierMode mode = ranked_seen ? kTierRankedSeen : first_seen ? kTierFirstSeen : (rg_use_slices(S.slices, N, edges_bound) ? kTierSliced : kTierAtomic);
+    // Slices whose scratch is not there and cannot be allocated (a captured call, no memory): the atomic kernels, same results.
+    bool sliced = mode == kTierSliced || mode == kTierRankedSeen;
+    const TierMode unsliced = first_seen ? kTierFirstSeen : kTierAtomic;
+    if (sliced) {
+        const SlicedBytes need = sliced_bytes(S, group, num_hops, first_seen);
+        if ((ctx->marked.bytes < need.marked || ctx->rank.bytes < need.rank || ctx->seen.bytes < need.seen) && rg_capturing(s)) {
+            sliced = false;
+            mode = unsliced;
+        }
+    }
+    rg_status st = rg_sampler_reserve(ctx, N, fub_max[num_hops], group, num_hops, max_edges, first_seen, sliced);
+    if (st == RG_ERR_OOM && sliced) {
+        mode = unsliced;
+        st = rg_sampler_reserve(ctx, N, fub_max[num_hops], group, num_hops, max_edges, first_seen, false);
+    }
     if (st != RG_OK) return st;
     S.hops = num_hops;
     S.rank = (uint2*)ctx->rank.p;

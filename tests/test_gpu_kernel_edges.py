@@ -235,6 +235,42 @@ def test_epoch_histogram_without_scratch(B, n, batches, hops):
     ctx.close()
 
 
+# Calls whose tier kernels want scratch that the context's earlier calls had no use for, captured: ascending order after first-seen
+# order, small first-seen calls after calls of over 2 Mi edges, more hops, and the other ways round.
+@pytest.mark.parametrize("warm_seeds,warm_fanouts,warm_seen,seeds,fanouts,seen", [
+    ([600, 500], (25, 10), True, [600, 500], (25, 10), False),
+    ([600, 500], (25, 10), False, [600, 500], (24, 2, 2), False),
+    ([1500] * 8, (25, 10), True, [40] * 8, (5, 3), True),
+    ([1500] * 8, (25, 10), True, [1500] * 8, (25, 10), True),
+])
+def test_captured_call_after_another_kind(B, warm_seeds, warm_fanouts, warm_seen, seeds, fanouts, seen):
+    log(f"[captured sampler] {warm_seeds} {warm_fanouts} {warm_seen} -> {seeds} {fanouts} {seen}")
+    n = 300_007
+    rng = np.random.default_rng(len(seeds) + sum(fanouts))
+    rp, ci, ids = _sparse_graph(n, 250_000, 30, rng)
+    csr = B.CsrGraph(torch.as_tensor(rp, device=DEV).to(torch.int32), _i32(ci))
+    kind = lambda first: B.RG_ORDER_FIRST_SEEN if first else B.RG_ORDER_ASCENDING  # noqa: E731
+    warm = [rng.permutation(ids)[:k].astype(np.int32) for k in warm_seeds]
+    lists = [rng.permutation(ids)[:k].astype(np.int32) for k in seeds]
+    lists_d = [_i32(x) for x in lists]
+    outs = [B.BlockBuffers(n, ci.size, k, fanouts, DEV) for k in seeds]
+    ctx = B.Context(0)
+    ctx.sample_blocks_group(csr, [_i32(x) for x in warm], warm_fanouts, 77, 0,
+                            [B.BlockBuffers(n, ci.size, k, warm_fanouts, DEV) for k in warm_seeds], node_order=kind(warm_seen))
+    graph = _captured(lambda: ctx.sample_blocks_group(csr, lists_d, fanouts, 77, 1, outs, node_order=kind(seen)))
+    order = oracle.ORDER_FIRST_SEEN if seen else oracle.ORDER_ASCENDING
+    want = [oracle.sample_blocks(rp, ci, x, fanouts, 77, 1, order) for x in lists]
+    for replay in range(3):
+        for o in outs:
+            o.nodes.fill_(-7)
+            o.tier_off.fill_(0)
+        graph.replay()
+        for j, o in enumerate(outs):
+            assert_batch_equal(HipBatch(o, len(fanouts)), want[j], len(fanouts), f"batch {j} replay {replay}")
+    del graph
+    ctx.close()
+
+
 def test_schedule_captured_after_a_smaller_one(B):
     """A schedule of no more than twice as many ids, up to the next power of two, finds the scratch of an earlier call."""
     few, many = 4097, 8192
