@@ -1012,7 +1012,8 @@ __global__ void __launch_bounds__(1024) k_seen_emit(const SampleGroup G, const S
 }
 
 // ---------------------------------------------------------------------------- relabelling, all hops in one launch
-// A member's position never changes, so nbr_local of every hop is written after the last one.
+// A member's position never changes, so nbr_local of every hop can be written after the last one, if every hop's lists are still
+// there by then (rg_hops_share_buffers).
 struct RelabelGroup {
     const int32_t* indptr[RG_MAX_HOPS][kMaxGroup];
     const int32_t* nbr[RG_MAX_HOPS][kMaxGroup];
@@ -1277,6 +1278,23 @@ __global__ void __launch_bounds__(256) k_histogram_bitmaps(const uint32_t* __res
     }
 }
 
+// True if a later hop writes into a list of an earlier one (a caller that keeps nothing but nbr_local may pass one nbr or indptr
+// buffer for all hops): every hop has to be relabelled before the next one is drawn.
+bool rg_hops_share_buffers(const rg_blocks& o, int num_hops, const int64_t* fub, const int64_t* eub) {
+    if (!o.nbr_local) return false;
+    struct Range { uintptr_t lo, hi; } r[RG_MAX_HOPS][3];
+    for (int h = 0; h < num_hops; ++h) {
+        const int32_t* p[3] = {o.indptr[h], o.nbr[h], o.nbr_local[h]};
+        const int64_t n[3] = {fub[h] + 1, eub[h], eub[h]};
+        for (int j = 0; j < 3; ++j) r[h][j] = {(uintptr_t)p[j], (uintptr_t)p[j] + (uintptr_t)(p[j] ? 4 * n[j] : 0)};
+        for (int e = 0; e < h; ++e)
+            for (int j = 0; j < 3; ++j)
+                for (int q = 0; q < 3; ++q)
+                    if (r[e][j].lo < r[h][q].hi && r[h][q].lo < r[e][j].hi) return true;
+    }
+    return false;
+}
+
 int grid_for(int64_t work_items, int per_block, int64_t cap) {
     int64_t g = rg_div_up(work_items, per_block);
     if (g < 1) g = 1;
@@ -1393,7 +1411,7 @@ rg_status rg_sample_blocks_group(rg_ctx* ctx, const rg_csr* csr, int32_t group, 
     // static bounds: per batch for the capacity checks, their maximum for the launch shapes
     int64_t fub_max[RG_MAX_HOPS + 1] = {0}, eub_max[RG_MAX_HOPS] = {0};
     int32_t seeds_max = 0;
-    bool capacity_error = false;
+    bool capacity_error = false, shared = false;
     for (int g = 0; g < group; ++g) {
         rg_blocks* o = out + g;
         RG_REQUIRE(ctx, num_seeds[g] >= 0, "rg_sample_blocks: num_seeds is negative (batch %d)", g);
@@ -1420,6 +1438,7 @@ rg_status rg_sample_blocks_group(rg_ctx* ctx, const rg_csr* csr, int32_t group, 
             for (int h = 0; h < num_hops; ++h) { o->indptr_cap[h] = fub[h] + 1; o->nbr_cap[h] = eub[h]; }
             capacity_error = true;
         }
+        shared = shared || rg_hops_share_buffers(*o, num_hops, fub, eub);
         for (int h = 0; h <= num_hops; ++h) fub_max[h] = rg_max64(fub_max[h], fub[h]);
         seeds_max = num_seeds[g] > seeds_max ? num_seeds[g] : seeds_max;
     }
@@ -1542,6 +1561,15 @@ rg_status rg_sample_blocks_group(rg_ctx* ctx, const rg_csr* csr, int32_t group, 
     RelabelGroup R = {};
     int64_t relabel_edges = 0;
     for (int g = 0; g < group; ++g) R.tier_off[g] = out[g].tier_off;
+    const auto relabel = [&]() -> rg_status {              // every hop that R names
+        if (relabel_edges == 0) return RG_OK;
+        const unsigned blocks = (unsigned)grid_for(relabel_edges, 1024, (int64_t)ctx->num_cus * 16);
+        if (mode == kTierSliced) k_relabel<true><<<blocks * ug, 256, 0, s>>>(R, S);
+        else if (mode == kTierRankedSeen) k_seen_relabel<<<blocks * ug, 256, 0, s>>>(R, S);
+        else k_relabel<false><<<blocks * ug, 256, 0, s>>>(R, S);
+        RG_LAUNCH_CHECK(ctx, "k_relabel");
+        return RG_OK;
+    };
     for (int h = 0; h < num_hops; ++h) {
         for (int g = 0; g < group; ++g) {
             G.indptr[g] = out[g].indptr[h];
@@ -1639,14 +1667,13 @@ rg_status rg_sample_blocks_group(rg_ctx* ctx, const rg_csr* csr, int32_t group, 
             k_tier_emit<<<(unsigned)(tier_blocks) * ug, 256, 0, s>>>(G, S, h);
             RG_LAUNCH_CHECK(ctx, "k_tier_emit");
         }
+        if (shared) {
+            if ((st = relabel()) != RG_OK) return st;
+            for (int g = 0; g < group; ++g) R.nbr_local[h][g] = nullptr;
+            relabel_edges = 0;
+        }
     }
-    if (relabel_edges > 0) {
-        const unsigned blocks = (unsigned)grid_for(relabel_edges, 1024, (int64_t)ctx->num_cus * 16);
-        if (mode == kTierSliced) k_relabel<true><<<blocks * ug, 256, 0, s>>>(R, S);
-        else if (mode == kTierRankedSeen) k_seen_relabel<<<blocks * ug, 256, 0, s>>>(R, S);
-        else k_relabel<false><<<blocks * ug, 256, 0, s>>>(R, S);
-        RG_LAUNCH_CHECK(ctx, "k_relabel");
-    }
+    if ((st = relabel()) != RG_OK) return st;
     ctx->sampler_dirty = false;
     ctx->last_sample_group = group;
     ctx->last_sample_nodes = N;

@@ -93,6 +93,50 @@ def test_blocks_across_the_ways_to_build_a_tier(B, ctx, n, active, degree, seeds
             assert torch.equal(o.tier_off, w.tier_off) and torch.equal(o.nodes[:k], w.nodes[:k])
 
 
+# One launch for all hops, slices, atomic marking; first-seen order by first edges and by rank words.
+@pytest.mark.parametrize("n,active,degree,seeds,fanouts,first_seen", [
+    (131_072, 60_000, 30, [300, 40], (10, 5), False),
+    (300_007, 250_000, 30, [1500, 0, 900], (25, 10, 3), False),
+    (4_194_337, 200_000, 12, [60, 50], (5, 3), False),
+    (131_072, 60_000, 30, [300, 40], (10, 5), True),
+    (300_007, 250_000, 30, [1500] * 8, (25, 10), True),
+])
+@pytest.mark.parametrize("what", ["nbr", "indptr", "all"])
+def test_blocks_with_one_list_buffer_for_all_hops(B, ctx, n, active, degree, seeds, fanouts, first_seen, what):
+    """A caller that keeps only the positions passes the same nbr (and indptr) buffer for every hop: each hop's positions are
+    those of its own edges; what is left in the shared lists is the last hop's."""
+    log(f"[shared lists] N={n} seeds={seeds} fanouts={fanouts} first_seen={first_seen} what={what}")
+    rng = np.random.default_rng(n % 1000 + len(seeds))
+    rp, ci, ids = _sparse_graph(n, active, degree, rng)
+    csr = B.CsrGraph(torch.as_tensor(rp, device=DEV).to(torch.int32), _i32(ci))
+    lists = [rng.permutation(ids)[:k].astype(np.int32) for k in seeds]
+    outs, H = [B.BlockBuffers(n, ci.size, max(k, 1), fanouts, DEV) for k in seeds], len(fanouts)
+    for o in outs:
+        for t in o.nbr_local:
+            t.fill_(-7)
+        room = {k: max(getattr(o, k), key=lambda t: t.numel()) for k in ("indptr", "nbr", "nbr_local")}
+        for h in range(H):
+            o.set_hop(h, **({"indptr": room["indptr"]} if what in ("indptr", "all") else {}))
+            if what in ("nbr", "all"):                  # set_hop wants both lists of a hop to hold the same number of edges
+                o.set_hop(h, nbr=room["nbr"])
+                o.set_hop(h, nbr_local=room["nbr_local"] if what == "all" else torch.full_like(room["nbr_local"], -7))
+    ctx.sample_blocks_group(csr, [_i32(x) for x in lists], fanouts, 77, 3, outs,
+                            node_order=B.RG_ORDER_FIRST_SEEN if first_seen else B.RG_ORDER_ASCENDING)
+    order = oracle.ORDER_FIRST_SEEN if first_seen else oracle.ORDER_ASCENDING
+    for j, o in enumerate(outs):
+        orc = oracle.sample_blocks(rp, ci, lists[j], fanouts, 77, 3, order)
+        assert o.tier_off.cpu().tolist() == orc.tier_off.tolist()
+        assert np.array_equal(o.nodes[:orc.nodes.size].cpu().numpy(), orc.nodes)
+        for h in range(H):
+            last, e = h == H - 1, orc.nbr[h].size
+            if what != "all" or last:
+                assert np.array_equal(o.nbr_local[h][:e].cpu().numpy(), orc.nbr_local[h]), f"batch {j} hop {h}"
+            if what == "indptr" or last:
+                assert np.array_equal(o.nbr[h][:e].cpu().numpy(), orc.nbr[h]), f"batch {j} hop {h}"
+            if what == "nbr" or last:
+                assert np.array_equal(o.indptr[h][:orc.indptr[h].size].cpu().numpy(), orc.indptr[h]), f"batch {j} hop {h}"
+
+
 def test_decoupled_misses_wait_for_the_reader_of_their_buffer(B):
     """The miss rows of batch b + 2 go into batch b's output buffer: they wait for what on_batch queued on the gather stream,
     however late it runs (here behind a long spin)."""
