@@ -457,8 +457,13 @@ rg_status launch_copies(rg_ctx* ctx, const GatherScratch& scr, int64_t n, const 
     return RG_OK;
 }
 
-// Batches that k_gather_fused takes (see there).
-bool rg_fits_fused(int64_t n, int32_t dim) { return n > 0 && n * (int64_t)dim * 4 <= kFusedBytes && n < (1ll << kCountBits); }
+// Batches that k_gather_fused takes (see there).  On two streams of which one records a graph launch_copies forks from the hit
+// stream, which draws the miss stream into the graph, and joins it back; launch_fused waits for the miss stream first, a wait that
+// would lead out of the graph.
+bool rg_fits_fused(int64_t n, int32_t dim, hipStream_t sh, hipStream_t sm) {
+    if (n <= 0 || n * (int64_t)dim * 4 > kFusedBytes || n >= (1ll << kCountBits)) return false;
+    return sh == sm || (!rg_capturing(sh) && !rg_capturing(sm));
+}
 
 // The one-launch gather.  The miss rows keep their place in both streams' order: behind what miss_stream was given before, in
 // front of what either stream is given next.
@@ -580,12 +585,13 @@ rg_status rg_gather_features(rg_ctx* ctx, const int32_t* input_nodes, int64_t n,
         RG_HIP(ctx, hipSetDevice(ctx->device));
         if ((st = rg_check_device_readable(ctx, remote_store, "rg_gather_features: remote_store")) != RG_OK) return st;
     }
-    if (rg_fits_fused(n, dim) && !ctx->profiling) {            // while kernels are timed, HBM and miss rows have one each
+    hipStream_t sh = (hipStream_t)hit_stream;
+    hipStream_t sm = miss_stream ? (hipStream_t)miss_stream : sh;
+    if (!ctx->profiling && rg_fits_fused(n, dim, sh, sm)) {    // while kernels are timed, HBM and miss rows have one each
         if ((st = rg_gather_reserve(ctx, n)) != RG_OK) return st;
         ctx->gather_rows[0] = -1;
-        hipStream_t sh = (hipStream_t)hit_stream;
         st = launch_fused(ctx, ticket_scratch(ctx, 0), input_nodes, n, n_dev, cache, local_store, local_stride, remote_store, remote_stride,
-                          dim, out, out_stride, stats, sh, miss_stream ? (hipStream_t)miss_stream : sh);
+                          dim, out, out_stride, stats, sh, sm);
         if (st == RG_OK) ctx->gather_rows[0] = n;              // the ticket's lookups are there, as after rg_gather_prepare
         return st;
     }
@@ -634,7 +640,7 @@ rg_status rg_gather_features_static(rg_ctx* ctx, const int32_t* input_nodes, int
     hipStream_t sh = (hipStream_t)hit_stream;
     hipStream_t sm = miss_stream ? (hipStream_t)miss_stream : sh;
     const GatherScratch scr = static_scratch(ctx);
-    if (rg_fits_fused(n, dim))
+    if (rg_fits_fused(n, dim, sh, sm))
         return launch_fused(ctx, scr, input_nodes, n, n_dev, cache, local_store, local_stride, remote_store, remote_stride, dim, out,
                             out_stride, stats, sh, sm);
     if ((st = launch_classify(ctx, 1, &input_nodes, &n, &n_dev, cache, &stats, &scr, sh)) != RG_OK) return st;

@@ -424,6 +424,49 @@ def test_gather_one_launch_edges(B, ctx, rows, dim, stride, mirror):
             assert np.array_equal(out[:k, :dim].cpu().numpy(), want)
 
 
+# One launch up to 32 MiB of rows, three above.
+@pytest.mark.parametrize("rows", [1500, 16_384, 16_385])
+@pytest.mark.parametrize("static", [False, True])
+def test_gather_on_two_streams_captured(B, rows, static):
+    """The hit stream records a graph, the miss stream is another one: the library draws it into the graph and joins it back.
+    Replayed on changed inputs, with eager calls on the same two streams in between."""
+    log(f"[captured gather] rows={rows} static={static}")
+    rng, dim, n = np.random.default_rng(rows), 512, rows + 1000
+    x = rng.standard_normal((n, dim), dtype=np.float32)
+    tag = rng.integers(0, 3, n)
+    row = np.zeros(n, dtype=np.int64)
+    for t in range(3):
+        row[tag == t] = np.arange((tag == t).sum())
+    loc = (row + (tag << 30)).astype(np.uint32).view(np.int32)
+    local, rows_c = (torch.from_numpy(x[tag == t]).to(DEV) for t in (0, 1))
+    remote = torch.from_numpy(x[tag == 2]).pin_memory()
+    cache = B.FeatureCache(n, rows_c.shape[0], dim, DEV)
+    cache.cache_rows.copy_(rows_c)
+    cache.loc.copy_(torch.from_numpy(loc))
+    ctx, side = B.Context(0), torch.cuda.Stream()
+    ids, out = torch.zeros(rows, dtype=torch.int32, device=DEV), torch.zeros(rows, dim, device=DEV)
+    stats = torch.zeros(3, dtype=torch.int64, device=DEV)
+    ctx.gather_features(ids, rows, cache, local, remote, dim, out, stats, miss_stream=side)       # makes the scratch
+    gather = ctx.gather_features_static if static else ctx.gather_features
+    graph = _captured(lambda: gather(ids, rows, cache, local, remote, dim, out, stats, miss_stream=side))
+    for replay in range(3):
+        nodes = rng.integers(0, n, rows).astype(np.int32)
+        want, st = oracle.gather_features(x, nodes, loc)
+        for call in ("replay", "eager"):
+            ids.copy_(torch.from_numpy(nodes))
+            out.fill_(float("nan"))
+            stats.fill_(-1)
+            if call == "replay":
+                graph.replay()
+            else:
+                gather(ids, rows, cache, local, remote, dim, out, stats, miss_stream=side)
+            torch.cuda.synchronize()
+            assert tuple(stats.cpu().tolist()) == st, (replay, call)
+            assert np.array_equal(out.cpu().numpy(), want), (replay, call)
+    del graph
+    ctx.close()
+
+
 def test_mirrored_pulls_of_growing_calls(B):
     """Calls that grow from single batches: every size adds up, and the gathers of an epoch sampled that way are right."""
     import dataclasses
