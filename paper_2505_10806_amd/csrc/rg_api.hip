@@ -140,11 +140,13 @@ void rg_destroy(rg_ctx* ctx) {
     if (!ctx) return;
     (void)hipSetDevice(ctx->device);
     (void)hipDeviceSynchronize();
-    RgBuf* bufs[] = {&ctx->visited, &ctx->marked, &ctx->rank, &ctx->pos, &ctx->chunk_sum, &ctx->row_start, &ctx->row_deg, &ctx->first_key, &ctx->seen, &ctx->sched_keys, &ctx->sched_ids, &ctx->sched_buckets,
+    RgBuf* bufs[] = {&ctx->visited, &ctx->marked, &ctx->slice_marks, &ctx->pos, &ctx->chunk_sum, &ctx->row_start, &ctx->row_deg, &ctx->first_key, &ctx->seen, &ctx->sched_keys, &ctx->sched_ids, &ctx->sched_buckets,
                      &ctx->hist_bounds, &ctx->topk_ctl, &ctx->topk_blk, &ctx->topk_caps, &ctx->pf_list, &ctx->pf_ctl, &ctx->plan_cursor, &ctx->claim_bits, &ctx->claim_blk, &ctx->gather_src, &ctx->miss_list,
                      &ctx->gather_ctl};
     for (RgBuf* b : bufs)
         if (b->p) (void)hipFree(b->p);
+    for (RgBuf& b : ctx->rank)
+        if (b.p) (void)hipFree(b.p);
     for (auto& s : ctx->spans) { (void)hipEventDestroy(s.start); (void)hipEventDestroy(s.stop); }
     for (auto& p : ctx->free_events) { (void)hipEventDestroy(p.first); (void)hipEventDestroy(p.second); }
     if (ctx->ev_classified) (void)hipEventDestroy(ctx->ev_classified);
@@ -163,6 +165,7 @@ rg_status rg_reserve(rg_ctx* ctx, int64_t num_nodes, int64_t max_frontier, int64
     RG_HIP(ctx, hipSetDevice(ctx->device));
     rg_status st;
     if ((st = rg_sampler_reserve(ctx, num_nodes, max_frontier, sample_group)) != RG_OK) return st;
+    if ((st = rg_sampler_reserve_slices(ctx, num_nodes, RG_MAX_HOPS)) != RG_OK) return st;
     if ((st = rg_ensure(ctx, ctx->topk_blk, ((size_t)rg_div_up(num_nodes, 1024) + 2) * 8)) != RG_OK) return st;
     if ((st = rg_histogram_reserve(ctx, num_nodes)) != RG_OK) return st;
     if ((st = rg_gather_reserve(ctx, max_rows)) != RG_OK) return st;

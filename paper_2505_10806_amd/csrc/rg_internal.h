@@ -40,8 +40,9 @@ struct rg_ctx {
 
     // sampler scratch
     RgBuf visited;      // uint32[ceil(N/32)] bitmap of cumulative-frontier members
-    RgBuf marked;       // uint32[ceil(N/32)] bitmaps of the ids a hop has sampled (see SampleScratch)
-    RgBuf rank;         // {uint32, uint32}[ceil(N/32)] per hop: members of the hop's new tier and their positions
+    RgBuf marked;       // uint32[ceil(N/32)] bitmap of every id met (see SampleScratch)
+    RgBuf slice_marks;  // uint32[ceil(N/32)] bitmaps of the ids a hop has sampled (the same)
+    RgBuf rank[2];      // {uint32, uint32}[ceil(N/32)] per hop, of four hops each: members of the hop's new tier and their positions
     RgBuf pos;          // int32[N] position of a node in the cumulative frontier (valid for members only)
     RgBuf chunk_sum;    // int32[] per-chunk edge counts / bitmap block counts
     RgBuf row_start;    // int64[max_frontier] adjacency row start of every frontier node (current hop)
@@ -101,8 +102,10 @@ rg_status rg_histogram_reserve(rg_ctx* ctx, int64_t num_nodes);
 rg_status rg_gather_reserve(rg_ctx* ctx, int64_t rows);
 // Sizes the sampler scratch for `group` batches side by side on a graph of num_nodes nodes with cumulative
 // frontiers of up to max_frontier nodes (what rg_sample_blocks_group would otherwise grow on demand).
-rg_status rg_sampler_reserve(rg_ctx* ctx, int64_t num_nodes, int64_t max_frontier, int group, int hops = RG_MAX_HOPS,
-                             int64_t max_edges = 0, bool first_seen = false, bool sliced = true);
+rg_status rg_sampler_reserve(rg_ctx* ctx, int64_t num_nodes, int64_t max_frontier, int group, int64_t max_edges = 0,
+                             bool first_seen = false);
+// What the sliced tier kernels use on top of that, for calls of as many batches (nothing on graphs without slices).
+rg_status rg_sampler_reserve_slices(rg_ctx* ctx, int64_t num_nodes, int hops, bool first_seen = false);
 // Allows the sampler's kernels the LDS they use on ctx->device (the device must be current).
 rg_status rg_sampler_init(rg_ctx* ctx);
 // Resolves the device address of the file-scope gather scratch for ctx->device (the device must be current).

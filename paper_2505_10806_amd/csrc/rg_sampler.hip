@@ -47,6 +47,8 @@ constexpr int kSliceGroups = 256;    // workgroups the marking pass is split int
                                      // compute unit, which is what a full slice's LDS admits
 constexpr int kSplitEdges = 8192;    // edges per split at least, and two per bitmap word (a split writes its slice out once)
 constexpr int kTierWords = 512;      // bitmap words per workgroup in the tier kernels of kTierSliced
+constexpr int kRankHops = 4;         // hops whose rank words share a buffer
+static_assert(RG_MAX_HOPS <= 2 * kRankHops, "rank words of all hops");
 
 template <typename RP>
 __device__ __forceinline__ void rg_row_extent(const RP* __restrict__ row_ptr, int v, int64_t& start, int64_t& deg) {
@@ -271,8 +273,9 @@ struct SampleGroup {
 
 struct SampleScratch {
     uint32_t* visited;                // [group][words]
-    uint32_t* marked;                 // kTierAtomic: [group][words], every id met; kTierSliced: [group][splits][words], ids of a hop
-    uint2* rank;                      // kTierSliced: [group][hops][words], tier t + 1: {its members among the 32 ids, position of the first}
+    uint32_t* marked;                 // kTierAtomic: [group][words], every id met
+    uint32_t* slice_marks;            // kTierSliced: [group][splits][words], ids of a hop
+    uint2* rank[2];                   // kTierSliced (rg_rank_words): tier t + 1 of a batch: {its members among the 32 ids, position of the first}
     int32_t* pos;                     // [group][num_nodes] (kTierSliced: of the seeds only)
     int32_t* chunk_sum;               // [group][chunk_stride]
     int64_t* row_start;               // [group][frontier_stride]
@@ -299,6 +302,10 @@ __device__ __forceinline__ int rg_batch(const SampleScratch& S) {
 }
 __device__ __forceinline__ unsigned rg_block(const SampleScratch& S) {
     return S.xcd_map ? blockIdx.x / (unsigned)S.group : blockIdx.x % (gridDim.x / (unsigned)S.group);
+}
+// Rank words of the tier behind hop `hop` of batch g: [hop][group][words] in each buffer.
+__device__ __forceinline__ uint2* rg_rank_words(const SampleScratch& S, int g, int hop) {
+    return (hop < kRankHops ? S.rank[0] : S.rank[1]) + ((hop & (kRankHops - 1)) * S.group + g) * S.words;
 }
 __device__ __forceinline__ unsigned rg_blocks_per_batch(const SampleScratch& S) { return gridDim.x / (unsigned)S.group; }
 
@@ -603,7 +610,7 @@ __global__ void __launch_bounds__(256) k_hop_sample_thread(const int32_t* __rest
 }
 
 // ---------------------------------------------------------------------------- per hop: new tier, sliced
-// marked[split][w] = the ids of the hop's edges of that split, one workgroup per (batch, slice of ids, split of the edges).
+// slice_marks[split][w] = the ids of the hop's edges of that split, one workgroup per (batch, slice of ids, split of the edges).
 // The workgroups of a batch read the same list side by side, so all but the first read of a line hits L2.
 __device__ __forceinline__ void rg_slice_or(uint32_t* bits, int32_t u, uint32_t id0, uint32_t n_ids) {
     const uint32_t d = (uint32_t)u - id0;
@@ -654,7 +661,7 @@ __global__ void __launch_bounds__(1024) k_slice_mark(const SampleGroup G, const 
     const int tail = head + 4 * n4;
     if ((int)threadIdx.x < n - tail) rg_slice_or(slice_bits, nbr[tail + threadIdx.x], id0, n_ids);
     __syncthreads();
-    uint32_t* __restrict__ out = S.marked + ((int64_t)g * S.splits + split) * S.words + w0;
+    uint32_t* __restrict__ out = S.slice_marks + ((int64_t)g * S.splits + split) * S.words + w0;
     for (int w = threadIdx.x; w < n_words; w += 1024) out[w] = slice_bits[w];
 }
 
@@ -665,13 +672,13 @@ __global__ void __launch_bounds__(kTierWords) k_slice_count(const SampleScratch 
     const int g = rg_batch(S);
     const unsigned blk = rg_block(S);
     const int64_t w = (int64_t)blk * kTierWords + threadIdx.x;
-    uint32_t* __restrict__ marked = S.marked + (int64_t)g * S.splits * S.words;
+    uint32_t* __restrict__ marks = S.slice_marks + (int64_t)g * S.splits * S.words;
     uint32_t bits = 0u;
     if (w < S.words) {
 #pragma unroll 8
-        for (int s = 0; s < S.splits; ++s) bits |= marked[s * S.words + w];
+        for (int s = 0; s < S.splits; ++s) bits |= marks[s * S.words + w];
         bits &= ~S.visited[g * S.words + w];
-        marked[w] = bits;
+        marks[w] = bits;
     }
     const int c = rg_wave_sum(__popc(bits));
     if (rg_lane() == 0) part[threadIdx.x >> 6] = c;
@@ -702,7 +709,7 @@ __global__ void __launch_bounds__(kTierWords) k_slice_emit(const SampleGroup G, 
     for (unsigned c = threadIdx.x; c < blk; c += kTierWords) before += chunk_sum[c];
     before = rg_wave_sum(before);
     if (rg_lane() == 0) part[threadIdx.x >> 6] = before;
-    const uint32_t bits = w < S.words ? S.marked[(int64_t)g * S.splits * S.words + w] : 0u;
+    const uint32_t bits = w < S.words ? S.slice_marks[(int64_t)g * S.splits * S.words + w] : 0u;
     int total;
     int j = rg_block_excl_scan<NW>(__popc(bits), smem, &total);                // its barriers publish part[]
     int out = G.tier_off[g][hop + 1];
@@ -712,7 +719,7 @@ __global__ void __launch_bounds__(kTierWords) k_slice_emit(const SampleGroup G, 
     int32_t* __restrict__ nodes = G.nodes[g] + out;
     int32_t* dst = total <= kEmitIds ? ids : nodes;
     if (w < S.words) {
-        S.rank[((int64_t)g * S.hops + hop) * S.words + w] = make_uint2(bits, (uint32_t)(out + j));
+        rg_rank_words(S, g, hop)[w] = make_uint2(bits, (uint32_t)(out + j));
         if (bits) S.visited[g * S.words + w] |= bits;
         if (!RANKED_SEEN)
             for (uint32_t b = bits; b; b &= b - 1u) dst[j++] = (int32_t)(w << 5) + __ffs(b) - 1;
@@ -848,14 +855,15 @@ __global__ void __launch_bounds__(256) k_first_seen_emit(const SampleGroup G, co
 }
 
 // ---------------------------------------------------------------------------- per hop: first-seen order by rank words
-// Positions of U ids (-1: none) from the rank words of the hops' tiers, latest first (`rank` = those of hop's new tier), and from
-// pos[] for the seeds; the U reads of a tier are in flight together.
+// Positions of U ids (-1: none) from the rank words of the hops' tiers, latest first, and from pos[] for the seeds; the U reads of
+// a tier are in flight together.
 template <int U>
-__device__ __forceinline__ void rg_ranked_positions(const int32_t (&u)[U], const uint2* __restrict__ rank, int hop, int64_t words,
+__device__ __forceinline__ void rg_ranked_positions(const int32_t (&u)[U], const SampleScratch& S, int g, int hop,
                                                     const int32_t* __restrict__ pos, int32_t (&r)[U]) {
 #pragma unroll
     for (int q = 0; q < U; ++q) r[q] = u[q] >= 0 ? -1 : 0;
-    for (int t = hop; t >= 0; --t, rank -= words) {
+    for (int t = hop; t >= 0; --t) {
+        const uint2* __restrict__ rank = rg_rank_words(S, g, t);
         uint2 x[U];
 #pragma unroll
         for (int q = 0; q < U; ++q) x[q] = r[q] < 0 ? rank[(uint32_t)u[q] >> 5] : make_uint2(0u, 0u);
@@ -881,13 +889,12 @@ __global__ void __launch_bounds__(256) k_seen_rank(const SampleGroup G, const Sa
     const int64_t n = G.indptr[g][G.tier_off[g][hop + 1]];
     const int32_t* __restrict__ nbr = G.nbr[g];
     const int32_t* __restrict__ pos = S.pos + g * S.num_nodes;
-    const uint2* __restrict__ rank = S.rank + ((int64_t)g * S.hops + hop) * S.words;
     int32_t* __restrict__ nbr_local = G.nbr_local[g];
     for (int64_t e0 = (int64_t)rg_block(S) * 256 + threadIdx.x; e0 < n; e0 += stride * U) {
         int32_t u[U], r[U];
 #pragma unroll
         for (int q = 0; q < U; ++q) u[q] = e0 + stride * q < n ? nbr[e0 + stride * q] : -1;
-        rg_ranked_positions<U>(u, rank, hop, S.words, pos, r);
+        rg_ranked_positions<U>(u, S, g, hop, pos, r);
 #pragma unroll
         for (int q = 0; q < U; ++q)
             if (u[q] >= 0) nbr_local[e0 + stride * q] = r[q];
@@ -1035,14 +1042,13 @@ __global__ void __launch_bounds__(256) k_relabel(const RelabelGroup R, const Sam
         int32_t* __restrict__ nbr_local = R.nbr_local[hop][g];
         if (!nbr_local) continue;
         const int32_t* __restrict__ nbr = R.nbr[hop][g];
-        const uint2* __restrict__ rank = RANKED ? S.rank + ((int64_t)g * S.hops + hop) * S.words : nullptr;
         const int64_t n = R.indptr[hop][g][R.tier_off[g][hop + 1]];
         for (int64_t e0 = (int64_t)rg_block(S) * 256 + threadIdx.x; e0 < n; e0 += stride * U) {
             int32_t u[U], r[U];
 #pragma unroll
             for (int q = 0; q < U; ++q) u[q] = e0 + stride * q < n ? nbr[e0 + stride * q] : -1;
             if (RANKED) {
-                rg_ranked_positions<U>(u, rank, hop, S.words, pos, r);
+                rg_ranked_positions<U>(u, S, g, hop, pos, r);
             } else {
 #pragma unroll
                 for (int q = 0; q < U; ++q) r[q] = u[q] >= 0 ? pos[u[q]] : 0;
@@ -1229,14 +1235,16 @@ void sampler_scratch_shape(int64_t N, int64_t frontier, int64_t max_edges, Sampl
     S.words = rg_div_up(N, 32);
     S.num_nodes = N;
     S.frontier_stride = rg_max64(frontier, 1);
-    S.chunk_stride = rg_max64(rg_max64(rg_div_up(S.frontier_stride, kChunk), rg_div_up(max_edges, kEdgesPerBlock)),
+    // (a quarter of a count chunk per entry leaves room for the first-seen blocks of up to four edges per frontier node)
+    S.chunk_stride = rg_max64(rg_max64(rg_div_up(S.frontier_stride, kChunk / 4), rg_div_up(max_edges, kEdgesPerBlock)),
                               rg_max64(1, rg_div_up(S.words, kTierWords))) + 2;
     const int64_t slices = rg_max64(1, rg_div_up(S.words, kSliceWords));
     S.slices = slices <= kMaxSlices ? (int)slices : 0;       // 0: too large for the sliced marking
     S.slice_words = S.slices ? (int)rg_max64(1, rg_div_up(S.words, slices)) : 0;
     S.splits = 1;
     S.hops = 1;
-    S.rank = nullptr;
+    S.slice_marks = nullptr;
+    S.rank[0] = S.rank[1] = nullptr;
     S.first_edge = S.place = S.first_key = nullptr;
     S.group = 1;
     S.xcd_map = 1;
@@ -1304,25 +1312,29 @@ int grid_for(int64_t work_items, int per_block, int64_t cap) {
 
 }  // namespace
 
-// Scratch of the tier kernels that mark in slices, more than the others use.
-struct SlicedBytes { size_t marked, rank, seen; };
-static SlicedBytes sliced_bytes(const SampleScratch& S, int group, int hops, bool first_seen) {
-    const size_t g = (size_t)group, bitmaps = (size_t)rg_max64(group, kSliceGroups / S.slices);
-    return {bitmaps * S.words * 4, g * (size_t)hops * S.words * 8, first_seen ? g * S.frontier_stride * 8 : 0};
+// Scratch of the tier kernels that mark in slices, more than the others use, for `members` words of `visited` (all batches) and
+// `frontier` entries of row_start; rank: per buffer of four hops.  It is allocated for as much as those two hold, so that only a
+// call they have to grow for replaces any of it: were its size to follow the kind of call, its hops or its slices, a smaller
+// call would leave a captured graph with freed memory.  All splits of all batches are at most kSliceGroups slices, or one bitmap each.
+struct SlicedBytes { size_t marks, rank, seen; };
+static SlicedBytes sliced_bytes(int64_t members, int64_t frontier, bool first_seen) {
+    const int64_t marks = rg_max64(members, kSliceGroups * rg_min64(members, kSliceWords));
+    return {(size_t)marks * 4, (size_t)kRankHops * members * sizeof(uint2), first_seen ? (size_t)frontier * 8 : 0};
+}
+// Hops beyond kRankHops have a buffer of their own unless the first one holds them too.
+static bool rank_in_one(const rg_ctx* ctx, const SlicedBytes& need) { return ctx->rank[0].bytes >= 2 * need.rank; }
+static bool has_slices(const rg_ctx* ctx, const SlicedBytes& need, int hops) {
+    return ctx->slice_marks.bytes >= need.marks && ctx->seen.bytes >= need.seen && ctx->rank[0].bytes >= need.rank &&
+           (hops <= kRankHops || rank_in_one(ctx, need) || ctx->rank[1].bytes >= need.rank);
 }
 
-rg_status rg_sampler_reserve(rg_ctx* ctx, int64_t num_nodes, int64_t max_frontier, int group, int hops, int64_t max_edges, bool first_seen, bool sliced) {
+rg_status rg_sampler_reserve(rg_ctx* ctx, int64_t num_nodes, int64_t max_frontier, int group, int64_t max_edges, bool first_seen) {
     SampleScratch S;
     sampler_scratch_shape(num_nodes, max_frontier, max_edges, S);
     const size_t g = (size_t)group;
     rg_status st;
     if ((st = rg_ensure(ctx, ctx->visited, g * S.words * 4)) != RG_OK) return st;
-    // marked: one bitmap per batch, or one per batch and split of the sliced marking (which is bounded for all batches together)
-    sliced = sliced && S.slices;
-    const SlicedBytes extra = sliced ? sliced_bytes(S, group, hops, first_seen) : SlicedBytes{g * S.words * 4, 0, 0};
-    if ((st = rg_ensure(ctx, ctx->marked, extra.marked)) != RG_OK) return st;
-    if ((st = rg_ensure(ctx, ctx->rank, extra.rank)) != RG_OK) return st;
-    if ((st = rg_ensure(ctx, ctx->seen, extra.seen)) != RG_OK) return st;
+    if ((st = rg_ensure(ctx, ctx->marked, g * S.words * 4)) != RG_OK) return st;
     if ((st = rg_ensure(ctx, ctx->pos, g * (size_t)num_nodes * 4)) != RG_OK) return st;
     if ((st = rg_ensure(ctx, ctx->chunk_sum, g * S.chunk_stride * 4)) != RG_OK) return st;
     if ((st = rg_ensure(ctx, ctx->row_start, g * S.frontier_stride * 8)) != RG_OK) return st;
@@ -1330,6 +1342,18 @@ rg_status rg_sampler_reserve(rg_ctx* ctx, int64_t num_nodes, int64_t max_frontie
     // first-seen order: the first-edge keys must be all-zero between hops (every hop leaves them zeroed)
     if (first_seen && (st = rg_ensure(ctx, ctx->first_key, g * (size_t)num_nodes * 4, true)) != RG_OK) return st;
     return RG_OK;
+}
+
+rg_status rg_sampler_reserve_slices(rg_ctx* ctx, int64_t num_nodes, int hops, bool first_seen) {
+    SampleScratch S;
+    sampler_scratch_shape(num_nodes, 0, 0, S);
+    if (!S.slices) return RG_OK;
+    const SlicedBytes need = sliced_bytes((int64_t)(ctx->visited.bytes / 4), (int64_t)(ctx->row_start.bytes / 8), first_seen);
+    rg_status st;
+    if ((st = rg_ensure(ctx, ctx->slice_marks, need.marks)) != RG_OK) return st;
+    if ((st = rg_ensure(ctx, ctx->rank[0], need.rank * (hops > kRankHops && !ctx->rank[0].p ? 2 : 1))) != RG_OK) return st;
+    if (hops > kRankHops && !rank_in_one(ctx, need) && (st = rg_ensure(ctx, ctx->rank[1], need.rank)) != RG_OK) return st;
+    return rg_ensure(ctx, ctx->seen, need.seen);
 }
 
 // Slices use more LDS than a kernel may by default.
@@ -1462,24 +1486,26 @@ rg_status rg_sample_blocks_group(rg_ctx* ctx, const rg_csr* csr, int32_t group, 
         for (int h = 0; h < num_hops; ++h)
             ranked_seen = ranked_seen && eub_max[h] <= kRankedSeenEdges && out[g].nbr_local && out[g].nbr_local[h] && out[g].nbr_local[h] != out[g].nbr[h];
     TierMode mode = ranked_seen ? kTierRankedSeen : first_seen ? kTierFirstSeen : (rg_use_slices(S.slices, N, edges_bound) ? kTierSliced : kTierAtomic);
-    // Slices whose scratch is not there and cannot be allocated (a captured call, no memory): the atomic kernels, same results.
-    bool sliced = mode == kTierSliced || mode == kTierRankedSeen;
-    const TierMode unsliced = first_seen ? kTierFirstSeen : kTierAtomic;
-    if (sliced) {
-        const SlicedBytes need = sliced_bytes(S, group, num_hops, first_seen);
-        if ((ctx->marked.bytes < need.marked || ctx->rank.bytes < need.rank || ctx->seen.bytes < need.seen) && rg_capturing(s)) {
-            sliced = false;
-            mode = unsliced;
-        }
-    }
-    rg_status st = rg_sampler_reserve(ctx, N, fub_max[num_hops], group, num_hops, max_edges, first_seen, sliced);
-    if (st == RG_ERR_OOM && sliced) {
-        mode = unsliced;
-        st = rg_sampler_reserve(ctx, N, fub_max[num_hops], group, num_hops, max_edges, first_seen, false);
-    }
+    rg_status st = rg_sampler_reserve(ctx, N, fub_max[num_hops], group, max_edges, first_seen);
     if (st != RG_OK) return st;
+    int max_fanout = 0;
+    for (int h = 0; h < num_hops; ++h) max_fanout = fanouts[h] < 0 ? RG_MAX_FANOUT : (fanouts[h] > max_fanout ? fanouts[h] : max_fanout);
+    const bool small = !first_seen && rg_is_small(N, edges_bound) && max_fanout <= 32 && csr->num_edges < (1ll << 32);
+    // Slices whose scratch is not there and cannot be allocated (a captured call, no memory): the atomic kernels, same results.
+    if (!small && (mode == kTierSliced || mode == kTierRankedSeen)) {
+        const SlicedBytes need = sliced_bytes(group * words, group * S.frontier_stride, first_seen);
+        bool there = has_slices(ctx, need, num_hops);
+        if (!there && !rg_capturing(s)) {
+            st = rg_sampler_reserve_slices(ctx, N, num_hops, first_seen);
+            if (st != RG_OK && st != RG_ERR_OOM) return st;
+            there = st == RG_OK;
+        }
+        if (!there) mode = first_seen ? kTierFirstSeen : kTierAtomic;
+        S.rank[0] = (uint2*)ctx->rank[0].p;
+        S.rank[1] = rank_in_one(ctx, need) ? S.rank[0] + need.rank / sizeof(uint2) : (uint2*)ctx->rank[1].p;
+    }
     S.hops = num_hops;
-    S.rank = (uint2*)ctx->rank.p;
+    S.slice_marks = (uint32_t*)ctx->slice_marks.p;
     S.first_key = mode == kTierFirstSeen ? (int32_t*)ctx->first_key.p : nullptr;
     S.first_edge = (int32_t*)ctx->seen.p;
     S.place = S.first_edge + group * S.frontier_stride;
@@ -1505,9 +1531,7 @@ rg_status rg_sample_blocks_group(rg_ctx* ctx, const rg_csr* csr, int32_t group, 
     }
     const unsigned ug = (unsigned)group;
 
-    int max_fanout = 0;
-    for (int h = 0; h < num_hops; ++h) max_fanout = fanouts[h] < 0 ? RG_MAX_FANOUT : (fanouts[h] > max_fanout ? fanouts[h] : max_fanout);
-    if (!first_seen && rg_is_small(N, edges_bound) && max_fanout <= 32 && csr->num_edges < (1ll << 32)) {
+    if (small) {
         SmallGroup M = {};
         for (int g = 0; g < group; ++g) {
             M.seeds[g] = seeds[g];

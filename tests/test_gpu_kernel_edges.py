@@ -298,9 +298,9 @@ def test_captured_call_after_another_kind(B, warm_seeds, warm_fanouts, warm_seen
     lists = [rng.permutation(ids)[:k].astype(np.int32) for k in seeds]
     lists_d = [_i32(x) for x in lists]
     outs = [B.BlockBuffers(n, ci.size, k, fanouts, DEV) for k in seeds]
+    warm_d, warm_outs = [_i32(x) for x in warm], [B.BlockBuffers(n, ci.size, k, warm_fanouts, DEV) for k in warm_seeds]
     ctx = B.Context(0)
-    ctx.sample_blocks_group(csr, [_i32(x) for x in warm], warm_fanouts, 77, 0,
-                            [B.BlockBuffers(n, ci.size, k, warm_fanouts, DEV) for k in warm_seeds], node_order=kind(warm_seen))
+    ctx.sample_blocks_group(csr, warm_d, warm_fanouts, 77, 0, warm_outs, node_order=kind(warm_seen))
     graph = _captured(lambda: ctx.sample_blocks_group(csr, lists_d, fanouts, 77, 1, outs, node_order=kind(seen)))
     order = oracle.ORDER_FIRST_SEEN if seen else oracle.ORDER_ASCENDING
     want = [oracle.sample_blocks(rp, ci, x, fanouts, 77, 1, order) for x in lists]
@@ -311,6 +311,11 @@ def test_captured_call_after_another_kind(B, warm_seeds, warm_fanouts, warm_seen
         graph.replay()
         for j, o in enumerate(outs):
             assert_batch_equal(HipBatch(o, len(fanouts)), want[j], len(fanouts), f"batch {j} replay {replay}")
+        # calls of either kind between the replays make the scratch that the captured one did without, and free none of its own
+        ctx.sample_blocks_group(csr, lists_d, fanouts, 77, 1, outs, node_order=kind(seen))
+        ctx.sample_blocks_group(csr, warm_d, warm_fanouts, 77, 0, warm_outs, node_order=kind(warm_seen))
+        for j, o in enumerate(outs):
+            assert_batch_equal(HipBatch(o, len(fanouts)), want[j], len(fanouts), f"batch {j} after replay {replay}")
     del graph
     ctx.close()
 

@@ -23,3 +23,40 @@ rt.begin_capture(0x51)
 assert gather(c, {rows}, 512, hit=0x51, static={static}) == OK
 assert rt.end_capture() == 0 and len(kernels()) == len(eager)
 """)
+
+
+# (nodes, edges, seeds, fan-outs, order) of a call that may have been captured, then of one that needs no more of what every call
+# uses (members, positions, frontier): another order, more hops, more edges per hop, another number of slices, fewer but larger batches.
+_CALLS = {
+    "order": [(300_007, 9_000_000, [13_000] * 2, (5, 3), "FIRST_SEEN"), (300_007, 9_000_000, [1500] * 2, (25, 10), "ASCENDING"),
+              (300_007, 9_000_000, [1500] * 2, (25, 10), "FIRST_SEEN"), (300_007, 9_000_000, [1500] * 2, (25, 10), "ASCENDING")],
+    "hops": [(300_007, 9_000_000, [2000] * 4, (25, 10), "ASCENDING"), (300_007, 9_000_000, [200] * 4, (10, 3, 2, 2), "ASCENDING"),
+             (300_007, 9_000_000, [50] * 4, (10, 3, 2, 2, 1, 1), "ASCENDING")],
+    "edges": [(200_000, 9_000_000, [2000] * 4, (25, 10), "ASCENDING"), (200_000, 9_000_000, [2000] * 4, (25, 13), "FIRST_SEEN")],
+    "slices": [(1_300_000, 9_000_000, [2000] * 2, (25, 10), "ASCENDING"), (1_270_000, 9_000_000, [2000] * 2, (25, 10), "ASCENDING")],
+    "group": [(100_000, 9_000_000, [3000] * 8, (25, 10), "ASCENDING"), (700_000, 9_000_000, [2000], (25, 10), "ASCENDING")],
+    "reserved": [(300_007, 9_000_000, [600] * 8, (25, 5), "FIRST_SEEN"), (300_007, 9_000_000, [900] * 8, (25, 5), "FIRST_SEEN")],
+    "small": [(131_000, 9_000_000, [300] * 8, (10, 5), "ASCENDING"), (131_000, 9_000_000, [300] * 8, (10, 5), "FIRST_SEEN"),
+              (131_000, 9_000_000, [400] * 2, (10, 5), "ASCENDING")],
+}
+
+
+@pytest.mark.parametrize("name", list(_CALLS))
+@pytest.mark.parametrize("captured", [False, True])
+def test_sampler_scratch_outlives_calls_of_another_kind(name, captured):
+    """A graph holds the addresses of the scratch it was recorded with: calls that are no larger than the earlier ones free none."""
+    calls = ", ".join(f"({n}, {e}, {s}, {f}, {o})" for n, e, s, f, o in _CALLS[name])
+    host_calls.run(f"""
+c, calls = context(), [{calls}]
+if "{name}" == "reserved":
+    assert lib.rg_reserve(c, i64(300_007), i64(300_007), i64(0), i32(8)) == OK
+assert sample(c, *calls[0]) == OK
+if {captured}:                                            # what the second call records into a graph is there to stay
+    rt.begin_capture(0x51)
+    if sample(c, *calls[-1], stream=0x51) != OK:
+        assert any("in a graph" in x for x in log()), lib.rg_last_error(c)      # the call wants more than there is
+    rt.end_capture()
+for call in calls + calls:
+    assert sample(c, *call) == OK, lib.rg_last_error(c)
+    assert not log("free"), call
+""")
