@@ -926,18 +926,13 @@ int hist_range(const rg_ctx* ctx, int64_t num_nodes) {
     return (int)rg_max64(kHistRangeMin, rg_div_up(num_nodes, places * rounds));
 }
 
-// A call takes several launches rather than more scratch from kHistBoundsBatches batches per launch on; rg_reserve makes room for
-// twice as many of 8 hops.
-constexpr int64_t kHistBoundsBatches = 64;
-constexpr int64_t kHistBoundsMax = 2ll << 20;      // entries, or one batch
+// Entries of the bounds' scratch: 8 MB, whatever the call, so that it is allocated once and a graph that uses it never loses it.
+// One batch of 8 hops on 2^30 nodes needs 1.05 Mi; a call of more batches than fit takes several launches.
+constexpr int64_t kHistBoundsMax = 2ll << 20;
 
 }  // namespace
 
-rg_status rg_histogram_reserve(rg_ctx* ctx, int64_t num_nodes) {
-    if (num_nodes <= 0) return RG_OK;
-    const int64_t per_batch = RG_MAX_HOPS * (rg_div_up(num_nodes, hist_range(ctx, num_nodes)) + 1);
-    return rg_ensure(ctx, ctx->hist_bounds, (size_t)(per_batch * rg_max64(1, rg_min64(2 * kHistBoundsBatches, kHistBoundsMax / per_batch))) * 4);
-}
+rg_status rg_histogram_reserve(rg_ctx* ctx) { return rg_ensure(ctx, ctx->hist_bounds, (size_t)kHistBoundsMax * 4); }
 
 extern "C" {
 
@@ -972,12 +967,10 @@ rg_status rg_access_histogram_epoch(rg_ctx* ctx, const int32_t* nodes, int64_t b
     hipStream_t s = (hipStream_t)stream;
     const int range = hist_range(ctx, num_nodes);
     const int ranges = (int)rg_div_up(num_nodes, range);
+    // without the bounds' scratch, in a captured call or for want of memory, the counting kernel searches for itself
+    if (!ctx->hist_bounds.p && !rg_capturing(s)) (void)rg_histogram_reserve(ctx);
     // batches per launch: the bounds of their runs fit the scratch, and a grid's second dimension
     const int64_t per_batch = (int64_t)num_hops * (ranges + 1);
-    const int64_t most = rg_min64(num_batches, rg_max64(1, kHistBoundsMax / per_batch));
-    // without scratch for one batch's bounds, in a captured call or for want of memory, the counting kernel searches for itself
-    if ((int64_t)(ctx->hist_bounds.bytes / 4) < per_batch * rg_min64(most, kHistBoundsBatches) && !rg_capturing(s))
-        (void)rg_ensure(ctx, ctx->hist_bounds, (size_t)(per_batch * most) * 4);
     const int fit = (int)rg_min64((int64_t)(ctx->hist_bounds.bytes / 4) / per_batch, 65535 / num_hops);
     const int step = fit > 0 ? fit : num_batches;
     int32_t* bounds = fit > 0 ? (int32_t*)ctx->hist_bounds.p : nullptr;

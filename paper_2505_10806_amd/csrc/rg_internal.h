@@ -96,8 +96,8 @@ static inline bool rg_capturing(hipStream_t s) {
     if (hipStreamIsCapturing(s, &status) != hipSuccess) { (void)hipGetLastError(); return false; }
     return status == hipStreamCaptureStatusActive;
 }
-// Scratch with which an epoch histogram of any number of batches on num_nodes nodes allocates nothing.
-rg_status rg_histogram_reserve(rg_ctx* ctx, int64_t num_nodes);
+// Scratch with which no epoch histogram allocates anything.
+rg_status rg_histogram_reserve(rg_ctx* ctx);
 // Makes every gather ticket hold at least `rows` rows (a reallocation invalidates prepared tickets).
 rg_status rg_gather_reserve(rg_ctx* ctx, int64_t rows);
 // Sizes the sampler scratch for `group` batches side by side on a graph of num_nodes nodes with cumulative

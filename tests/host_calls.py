@@ -82,7 +82,7 @@ def run(program):
         folder = tempfile.mkdtemp()
         atexit.register(shutil.rmtree, folder, ignore_errors=True)
         _runtime = os.path.join(folder, "recording_runtime.so")
-        subprocess.run(["g++", "-O1", "-std=c++17", "-shared", "-fPIC", "-o", _runtime, os.path.join(HERE, "recording_runtime.cpp")],
+        subprocess.run(["g++", "-O1", "-std=c++17", "-Wno-format-security", "-shared", "-fPIC", "-o", _runtime, os.path.join(HERE, "recording_runtime.cpp")],
                        check=True)
     r = subprocess.run([sys.executable, "-c", _PRELUDE + program, _runtime, LIB], capture_output=True, text=True, timeout=120)
     assert r.returncode == 0, r.stdout + r.stderr

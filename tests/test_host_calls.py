@@ -60,3 +60,24 @@ for call in calls + calls:
     assert sample(c, *call) == OK, lib.rg_last_error(c)
     assert not log("free"), call
 """)
+
+
+def test_histogram_scratch_outlives_larger_calls():
+    """A graph that holds the address of the histogram's scratch is safe whatever is counted later: there is one size of it."""
+    host_calls.run("""
+c = context()
+assert histogram(c, 100_000, 10, 2) == OK
+log()
+rt.begin_capture(0x51)
+assert histogram(c, 100_000, 10, 2, stream=0x51) == OK
+rt.end_capture()
+for n, batches, hops in ((100_000, 64, 2), (100_000, 5000, 3), (10_000_000, 245, 3), (1 << 30, 3, 8)):
+    assert histogram(c, n, batches, hops) == OK and not log("free") and not log("malloc"), n
+assert lib.rg_reserve(c, i64(1 << 20), i64(100), i64(100), i32(2)) == OK
+assert not log("free")
+d = context()                                             # none there, and none to be had while the graph is recorded
+rt.begin_capture(0x51)
+assert histogram(d, 10_000_000, 245, 3, stream=0x51) == OK
+rt.end_capture()
+assert [k.split("<")[0] for k in kernels()] == ["k_histogram_seeds", "k_histogram_runs"]
+""")
