@@ -71,7 +71,7 @@ __global__ void __launch_bounds__(256) k_hist_bounds(const int32_t* __restrict__
 }
 
 // FIRST: also record, per id, the smallest batch index whose list contains it (first_batch[v] = min(old, b)); b0 = index of the
-// first of these batches.  bounds == NULL (no scratch to be had): the workgroup bisects every run for its range itself.
+// first of these batches.  bounds == NULL: the workgroup bisects every run for its range itself.
 template <bool FIRST>
 __global__ void __launch_bounds__(1024) k_histogram_runs(const int32_t* __restrict__ nodes, int64_t batch_stride,
                                                          const int32_t* __restrict__ tier_off, const int32_t* __restrict__ bounds,
@@ -972,8 +972,15 @@ rg_status rg_access_histogram_epoch(rg_ctx* ctx, const int32_t* nodes, int64_t b
     // batches per launch: the bounds of their runs fit the scratch, and a grid's second dimension
     const int64_t per_batch = (int64_t)num_hops * (ranges + 1);
     const int fit = (int)rg_min64((int64_t)(ctx->hist_bounds.bytes / 4) / per_batch, 65535 / num_hops);
-    const int step = fit > 0 ? fit : num_batches;
-    int32_t* bounds = fit > 0 ? (int32_t*)ctx->hist_bounds.p : nullptr;
+    // The counting kernel also searches where that is faster.  A few bounds are no work for a launch of their own: up to 1 Mi nodes
+    // and 8448 bounds 12.0-12.9 us against 14.4-15.2, at 12,312 bounds 16-18 / 15, on 2.4 M nodes 13-18 / 15 from 1539 bounds on.
+    // And a launch of few batches does little besides clearing and adding its ranges: 245 batches on 200 M nodes, 28 to a
+    // launch, 2.2-3.5 ms in one launch that searches against 2.7-5.0 ms (64 batches 0.7-1.2 / 0.75-1.6, but 32 batches in two launches
+    // 0.52-0.56 / 0.42-0.47); on 100 M nodes, 56 to a launch, 1.2-2.0 ms either way.
+    const bool few = num_nodes <= (1 << 20) && num_batches * per_batch <= 8448;
+    const bool search = fit == 0 || few || (fit < 48 && num_batches > 2 * fit);
+    const int step = search ? num_batches : fit;
+    int32_t* bounds = search ? nullptr : (int32_t*)ctx->hist_bounds.p;
     const int tok = rg_prof_begin(ctx, RG_K_HISTOGRAM, s);
     if (max_seeds > 0) {
         dim3 seed_grid((unsigned)rg_min64(rg_div_up(max_seeds, 256), 64), (unsigned)num_batches);

@@ -81,3 +81,18 @@ assert histogram(d, 10_000_000, 245, 3, stream=0x51) == OK
 rt.end_capture()
 assert [k.split("<")[0] for k in kernels()] == ["k_histogram_seeds", "k_histogram_runs"]
 """)
+
+
+# Few bounds; the most batches that one launch's scratch holds (28 on 200 M nodes), two launches, more than two.
+@pytest.mark.parametrize("n,batches,hops,search,launches", [
+    (1000, 5, 2, True, 1), (1 << 20, 5, 3, True, 1), (1 << 20, 6, 3, False, 1), ((1 << 20) + 1, 1, 1, False, 1),
+    (10_000_000, 454, 3, False, 1), (10_000_000, 2000, 3, False, 5), (200_000_000, 28, 3, False, 1), (200_000_000, 56, 3, False, 2),
+    (200_000_000, 57, 3, True, 1), (1 << 30, 1, 8, False, 1), (1 << 30, 245, 8, True, 1)])
+def test_histogram_searches_where_bounds_do_not_pay(n, batches, hops, search, launches):
+    host_calls.run(f"""
+c = context()
+assert histogram(c, {n}, {batches}, {hops}) == OK
+names = [k.split("<")[0] for k in kernels()]
+assert names.count("k_histogram_runs") == {launches}, names
+assert names.count("k_hist_bounds") == (0 if {search} else {launches}), names
+""")
