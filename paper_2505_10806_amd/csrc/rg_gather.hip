@@ -5,6 +5,8 @@
 // per row), counts the three classes and compacts the indices of the miss rows; the HBM kernel copies
 // local and cached rows; the miss kernel copies the remote rows and may run on a second stream so the
 // host-link transfers overlap the HBM copies.
+#include <atomic>
+
 #include "rg_rowcopy.h"
 
 // For small batches rg_gather_features and rg_gather_features_static do all of that in one launch (k_gather_fused).
@@ -32,14 +34,21 @@ namespace {
 struct GatherScratch {
     uint32_t* src;        // [rows] resolved location word per output row
     int32_t* miss_list;   // [2 * rows] (output row, remote row) pairs
-    uint32_t* gctl;       // [0] = number of misses; [2], [3] = the batch's running counts, zero between launches (rg_add_counts)
+    uint32_t* gctl;       // [0] = number of misses; from [2] on the running counts of a batch, kTurns 64-bit counters (rg_add_counts)
+    int turn;             // which of them this call counts in
 };
 
-GatherScratch ticket_scratch(rg_ctx* ctx, int t) {
+// A call counts in the counter behind the one of the scratch's last call, and clears the next one: after calls that overlapped, which
+// may leave anything in theirs, the next call finds a cleared counter all the same.
+constexpr int kTurns = 4;
+std::atomic<uint32_t> static_turns[16];   // of the static scratch, by device (any context of the device may be next)
+
+GatherScratch ticket_scratch(rg_ctx* ctx, int t, bool lookup) {
     GatherScratch g;
     g.src = (uint32_t*)ctx->gather_src.p + (int64_t)t * ctx->gather_cap;
     g.miss_list = (int32_t*)ctx->miss_list.p + (int64_t)t * 2 * ctx->gather_cap;
     g.gctl = (uint32_t*)ctx->gather_ctl.p + t * 16;
+    g.turn = lookup ? ctx->gather_turn[t]++ % kTurns : 0;
     return g;
 }
 
@@ -49,6 +58,7 @@ GatherScratch static_scratch(rg_ctx* ctx) {
     g.gctl = (uint32_t*)base;
     g.src = (uint32_t*)(base + kStaticCtlBytes);
     g.miss_list = (int32_t*)(base + kStaticCtlBytes + kStaticSrcBytes);
+    g.turn = (int)(static_turns[ctx->device & 15]++ % kTurns);
     return g;
 }
 
@@ -67,31 +77,44 @@ struct ClassifyGroup {
     uint32_t* src[RG_GATHER_TICKETS];
     int32_t* miss_list[RG_GATHER_TICKETS];
     uint32_t* gctl[RG_GATHER_TICKETS];
+    int turn[RG_GATHER_TICKETS];
     unsigned long long* stats[RG_GATHER_TICKETS];
 };
 
+__device__ __forceinline__ unsigned long long* rg_counter(uint32_t* gctl, int turn) {
+    return (unsigned long long*)(gctl + 2) + turn % kTurns;
+}
+
 __global__ void k_gather_reset(const ClassifyGroup C) {
     const int k = blockIdx.x;
-    if (threadIdx.x == 0) C.gctl[k][0] = 0u;
+    if (threadIdx.x == 0) { C.gctl[k][0] = 0u; *rg_counter(C.gctl[k], C.turn[k] + 1) = 0ull; }
     if (threadIdx.x < 3) C.stats[k][threadIdx.x] = 0ull;
+}
+
+// In front of a call that is recorded into a graph: its replays all count in the same counter, whatever happened in between.
+__global__ void k_clear_counters(const ClassifyGroup C) {
+    if (threadIdx.x == 0) *rg_counter(C.gctl[blockIdx.x], C.turn[blockIdx.x]) = 0ull;
 }
 
 // A batch's statistics without a launch that clears them first: every workgroup adds its misses, its hits and itself to one
 // 64-bit counter.  What it gets back is its place in the miss list, and the workgroup that completes the batch has the totals,
 // writes them out and leaves the counter zero.  (Additions to one address queue up at 12.5 ns each: few workgroups, one each.)
+// Places and the number of misses are bounded by the rows, so that a counter that calls spoilt by overlapping does not lead out
+// of the list.
 constexpr int kCountBits = 23;           // rows < 2^23; workgroups < 2^18
-__device__ __forceinline__ uint32_t rg_add_counts(uint32_t* gctl, unsigned long long* stats, int misses, int hits, int64_t rows,
+__device__ __forceinline__ uint32_t rg_add_counts(uint32_t* gctl, int turn, unsigned long long* stats, int misses, int hits, int64_t rows,
                                                   unsigned workgroups) {
     const unsigned long long mask = (1ull << kCountBits) - 1ull;
     const unsigned long long add = (unsigned long long)misses | ((unsigned long long)hits << kCountBits) | (1ull << (2 * kCountBits));
-    const unsigned long long before = atomicAdd((unsigned long long*)(gctl + 2), add), all = before + add;
+    if (blockIdx.x == 0) *rg_counter(gctl, turn + 1) = 0ull;
+    const unsigned long long before = atomicAdd(rg_counter(gctl, turn), add), all = before + add;
     if ((all >> (2 * kCountBits)) == workgroups) {
         const unsigned long long n_miss = all & mask, n_hit = (all >> kCountBits) & mask;
         stats[0] = (unsigned long long)rows - n_miss - n_hit;
         stats[1] = n_hit;
         stats[2] = n_miss;
-        gctl[0] = (uint32_t)n_miss;
-        *(unsigned long long*)(gctl + 2) = 0ull;
+        gctl[0] = (uint32_t)(n_miss < (unsigned long long)rows ? n_miss : (unsigned long long)rows);
+        *rg_counter(gctl, turn) = 0ull;
     }
     return (uint32_t)(before & mask);
 }
@@ -120,7 +143,7 @@ __global__ void __launch_bounds__(256) k_classify(const ClassifyGroup C, const i
     if (i0 >= n_act) {                                             // uniform per workgroup
         if (!WIDE && blockIdx.x == 0) {                            // an empty batch
             if (threadIdx.x < 3) stats[threadIdx.x] = 0ull;
-            if (threadIdx.x == 0) gctl[0] = 0u;
+            if (threadIdx.x == 0) { gctl[0] = 0u; *rg_counter(gctl, C.turn[b] + 1) = 0ull; }
         }
         return;
     }
@@ -166,7 +189,7 @@ __global__ void __launch_bounds__(256) k_classify(const ClassifyGroup C, const i
                 miss_base = atomicAdd(&gctl[0], (uint32_t)total_miss);
             }
         } else {
-            miss_base = rg_add_counts(gctl, stats, total_miss, hits, n_act, (unsigned)((n_act + 256 * kClassifyRows - 1) / (256 * kClassifyRows)));
+            miss_base = rg_add_counts(gctl, C.turn[b], stats, total_miss, hits, n_act, (unsigned)((n_act + 256 * kClassifyRows - 1) / (256 * kClassifyRows)));
         }
     }
     if (total_miss == 0) return;                                   // uniform
@@ -175,6 +198,7 @@ __global__ void __launch_bounds__(256) k_classify(const ClassifyGroup C, const i
     for (int k = 0; k < kClassifyRows; ++k)
         if ((w[k] >> RG_TAG_SHIFT) == RG_TAG_REMOTE) {   // (output row, remote row) pairs: the miss kernel needs no further lookup
             const int64_t j = (int64_t)miss_base + excl++;
+            if (j >= n_act) continue;
             miss_list[2 * j] = (int32_t)(i0 + k * 256 + threadIdx.x);
             miss_list[2 * j + 1] = (int32_t)(w[k] & RG_ROW_MASK);
         }
@@ -299,7 +323,7 @@ __global__ void __launch_bounds__(256) k_gather_fused(const int32_t* __restrict_
                                                       const float* __restrict__ remote_store, int64_t remote_stride,
                                                       float* __restrict__ out, int64_t out_stride, int cpr, int tail, int rpb,
                                                       uint32_t* __restrict__ src, int32_t* __restrict__ miss_list,
-                                                      uint32_t* __restrict__ gctl, unsigned long long* __restrict__ stats) {
+                                                      uint32_t* __restrict__ gctl, int turn, unsigned long long* __restrict__ stats) {
     typedef typename RgVec<VEC>::type V;
     __shared__ const V* from[RG_WAVE];
     const int64_t n_act = rg_actual_n(n, n_dev);
@@ -323,7 +347,7 @@ __global__ void __launch_bounds__(256) k_gather_fused(const int32_t* __restrict_
     if (threadIdx.x < RG_WAVE) {                                       // the answer is used behind the copies
         misses = __ballot((w >> RG_TAG_SHIFT) == RG_TAG_REMOTE);
         const unsigned long long hits = __ballot((w >> RG_TAG_SHIFT) == RG_TAG_CACHE);
-        if (threadIdx.x == 0) miss_base = rg_add_counts(gctl, stats, __popcll(misses), __popcll(hits), n_act, gridDim.x);
+        if (threadIdx.x == 0) miss_base = rg_add_counts(gctl, turn, stats, __popcll(misses), __popcll(hits), n_act, gridDim.x);
     }
     int r = (int)threadIdx.x / cpr, c = (int)threadIdx.x % cpr;
     const int dr = 256 / cpr, dc = 256 % cpr;
@@ -354,8 +378,10 @@ __global__ void __launch_bounds__(256) k_gather_fused(const int32_t* __restrict_
         miss_base = (uint32_t)__shfl((int)miss_base, 0, RG_WAVE);
         if ((misses >> threadIdx.x) & 1ull) {
             const int64_t j = (int64_t)miss_base + __popcll(misses & ((1ull << threadIdx.x) - 1ull));
-            miss_list[2 * j] = (int32_t)(row0 + threadIdx.x);
-            miss_list[2 * j + 1] = (int32_t)(w & RG_ROW_MASK);
+            if (j < n_act) {
+                miss_list[2 * j] = (int32_t)(row0 + threadIdx.x);
+                miss_list[2 * j + 1] = (int32_t)(w & RG_ROW_MASK);
+            }
         }
     }
 }
@@ -374,6 +400,7 @@ rg_status launch_classify(rg_ctx* ctx, int count, const int32_t* const* input_no
         C.src[k] = g.src;
         C.miss_list[k] = g.miss_list;
         C.gctl[k] = g.gctl;
+        C.turn[k] = g.turn;
         C.stats[k] = live ? (unsigned long long*)stats[k] : nullptr;
         if (live) n_max = rg_max64(n_max, n[k]);
     }
@@ -381,6 +408,9 @@ rg_status launch_classify(rg_ctx* ctx, int count, const int32_t* const* input_no
     if (wide) {
         k_gather_reset<<<count, 64, 0, s>>>(C);
         RG_LAUNCH_CHECK(ctx, "k_gather_reset");
+    } else if (rg_capturing(s)) {
+        k_clear_counters<<<count, 64, 0, s>>>(C);
+        RG_LAUNCH_CHECK(ctx, "k_clear_counters");
     }
     const dim3 grid((unsigned)rg_max64(1, rg_div_up(n_max, 256 * kClassifyRows)), (unsigned)count);
     const int32_t* home = cache->mirror_rows > 0 ? cache->home : nullptr;
@@ -460,16 +490,16 @@ rg_status launch_copies(rg_ctx* ctx, const GatherScratch& scr, int64_t n, const 
 // Batches that k_gather_fused takes (see there).  On two streams of which one records a graph launch_copies forks from the hit
 // stream, which draws the miss stream into the graph, and joins it back; launch_fused waits for the miss stream first, a wait that
 // would lead out of the graph.
-bool rg_fits_fused(int64_t n, int32_t dim, hipStream_t sh, hipStream_t sm) {
+bool rg_fits_fused(int64_t n, int32_t dim, hipStream_t sh, hipStream_t sm, bool captured) {
     if (n <= 0 || n * (int64_t)dim * 4 > kFusedBytes || n >= (1ll << kCountBits)) return false;
-    return sh == sm || (!rg_capturing(sh) && !rg_capturing(sm));
+    return sh == sm || (!captured && !rg_capturing(sm));
 }
 
 // The one-launch gather.  The miss rows keep their place in both streams' order: behind what miss_stream was given before, in
 // front of what either stream is given next.
 rg_status launch_fused(rg_ctx* ctx, const GatherScratch& scr, const int32_t* nodes, int64_t n, const int32_t* n_dev, const rg_cache* cache,
                        const float* local_store, int64_t local_stride, const float* remote_store, int64_t remote_stride, int32_t dim,
-                       float* out, int64_t out_stride, rg_gather_stats* stats, hipStream_t sh, hipStream_t sm) {
+                       float* out, int64_t out_stride, rg_gather_stats* stats, hipStream_t sh, hipStream_t sm, bool captured) {
     if (sm != sh) {
         RG_HIP(ctx, hipEventRecord(ctx->ev_classified, sm));
         RG_HIP(ctx, hipStreamWaitEvent(sh, ctx->ev_classified, 0));
@@ -482,10 +512,17 @@ rg_status launch_fused(rg_ctx* ctx, const GatherScratch& scr, const int32_t* nod
     const unsigned grid = (unsigned)rg_div_up(n, rpb);
     const float* cache_rows = cache->cache_rows ? cache->cache_rows : local_store;   // never dereferenced without cache words
     const int32_t* home = cache->mirror_rows > 0 ? cache->home : nullptr;
+    if (captured) {
+        ClassifyGroup C = {};
+        C.gctl[0] = scr.gctl;
+        C.turn[0] = scr.turn;
+        k_clear_counters<<<1, 64, 0, sh>>>(C);
+        RG_LAUNCH_CHECK(ctx, "k_clear_counters");
+    }
 #define RG_LAUNCH_FUSED(V, T)                                                                                           \
     k_gather_fused<V, T><<<grid, 256, 0, sh>>>(nodes, n, n_dev, cache->loc, home, local_store, local_stride, cache_rows, cache->row_stride, \
                                                remote_store, remote_stride, out, out_stride, shp.cpr, shp.tail, rpb, scr.src, scr.miss_list, \
-                                               scr.gctl, (unsigned long long*)stats)
+                                               scr.gctl, scr.turn, (unsigned long long*)stats)
     if (vec == 4) RG_LAUNCH_FUSED(4, 4); else if (vec == 2) RG_LAUNCH_FUSED(2, 4); else RG_LAUNCH_FUSED(1, 4);
 #undef RG_LAUNCH_FUSED
     RG_LAUNCH_CHECK(ctx, "k_gather_fused");
@@ -543,7 +580,7 @@ rg_status rg_gather_prepare(rg_ctx* ctx, int32_t first_ticket, int32_t count, co
     if (st != RG_OK) return st;
     GatherScratch scr[RG_GATHER_TICKETS];
     for (int k = 0; k < count; ++k) {
-        scr[k] = ticket_scratch(ctx, first_ticket + k);
+        scr[k] = ticket_scratch(ctx, first_ticket + k, true);
         ctx->gather_rows[first_ticket + k] = -1;
     }
     if ((st = launch_classify(ctx, count, input_nodes, n, n_dev, cache, stats, scr, (hipStream_t)stream)) != RG_OK) return st;
@@ -566,7 +603,7 @@ rg_status rg_gather_run(rg_ctx* ctx, int32_t ticket, int64_t n, const int32_t* n
     if ((st = rg_check_device_readable(ctx, remote_store, "rg_gather_run: remote_store")) != RG_OK) return st;
     hipStream_t sh = (hipStream_t)hit_stream;
     hipStream_t sm = miss_stream ? (hipStream_t)miss_stream : sh;
-    return launch_copies(ctx, ticket_scratch(ctx, ticket), n, n_dev, cache, local_store, local_stride, remote_store, remote_stride,
+    return launch_copies(ctx, ticket_scratch(ctx, ticket, false), n, n_dev, cache, local_store, local_stride, remote_store, remote_stride,
                          dim, out, out_stride, sh, sm, true);
 }
 
@@ -587,11 +624,12 @@ rg_status rg_gather_features(rg_ctx* ctx, const int32_t* input_nodes, int64_t n,
     }
     hipStream_t sh = (hipStream_t)hit_stream;
     hipStream_t sm = miss_stream ? (hipStream_t)miss_stream : sh;
-    if (!ctx->profiling && rg_fits_fused(n, dim, sh, sm)) {    // while kernels are timed, HBM and miss rows have one each
+    const bool captured = rg_capturing(sh);
+    if (!ctx->profiling && rg_fits_fused(n, dim, sh, sm, captured)) {    // while kernels are timed, HBM and miss rows have one each
         if ((st = rg_gather_reserve(ctx, n)) != RG_OK) return st;
         ctx->gather_rows[0] = -1;
-        st = launch_fused(ctx, ticket_scratch(ctx, 0), input_nodes, n, n_dev, cache, local_store, local_stride, remote_store, remote_stride,
-                          dim, out, out_stride, stats, sh, sm);
+        st = launch_fused(ctx, ticket_scratch(ctx, 0, true), input_nodes, n, n_dev, cache, local_store, local_stride, remote_store, remote_stride,
+                          dim, out, out_stride, stats, sh, sm, captured);
         if (st == RG_OK) ctx->gather_rows[0] = n;              // the ticket's lookups are there, as after rg_gather_prepare
         return st;
     }
@@ -617,7 +655,7 @@ rg_status rg_gather_run_part(rg_ctx* ctx, int32_t ticket, int32_t part, int64_t 
     RG_HIP(ctx, hipSetDevice(ctx->device));
     if ((st = rg_check_device_readable(ctx, remote_store, "rg_gather_run_part: remote_store")) != RG_OK) return st;
     hipStream_t s = (hipStream_t)stream;
-    return launch_copies(ctx, ticket_scratch(ctx, ticket), n, n_dev, cache, local_store, local_stride, remote_store, remote_stride,
+    return launch_copies(ctx, ticket_scratch(ctx, ticket, false), n, n_dev, cache, local_store, local_stride, remote_store, remote_stride,
                          dim, out, out_stride, s, s, true, part);
 }
 
@@ -640,9 +678,10 @@ rg_status rg_gather_features_static(rg_ctx* ctx, const int32_t* input_nodes, int
     hipStream_t sh = (hipStream_t)hit_stream;
     hipStream_t sm = miss_stream ? (hipStream_t)miss_stream : sh;
     const GatherScratch scr = static_scratch(ctx);
-    if (rg_fits_fused(n, dim, sh, sm))
+    const bool captured = rg_capturing(sh);
+    if (rg_fits_fused(n, dim, sh, sm, captured))
         return launch_fused(ctx, scr, input_nodes, n, n_dev, cache, local_store, local_stride, remote_store, remote_stride, dim, out,
-                            out_stride, stats, sh, sm);
+                            out_stride, stats, sh, sm, captured);
     if ((st = launch_classify(ctx, 1, &input_nodes, &n, &n_dev, cache, &stats, &scr, sh)) != RG_OK) return st;
     if (n == 0) return RG_OK;
     return launch_copies(ctx, scr, n, n_dev, cache, local_store, local_stride, remote_store, remote_stride, dim, out, out_stride,

@@ -70,7 +70,8 @@ struct rg_ctx {
     // RG_GATHER_TICKETS entries each, so that several batches can be classified by one launch ahead of their copies
     RgBuf gather_src;   // [ticket][gather_cap] uint32: resolved location word per output row
     RgBuf miss_list;    // [ticket][2 * gather_cap] int32: (output row, remote row) pairs of the miss rows
-    RgBuf gather_ctl;   // [ticket][16] uint32: [0] = number of misses
+    RgBuf gather_ctl;   // [ticket][16] uint32: [0] = number of misses, then running counts
+    uint8_t gather_turn[RG_GATHER_TICKETS] = {0};            // which of the running counts a ticket's next lookup uses
     int64_t gather_cap = 0;                                  // rows per ticket the buffers hold
     int64_t gather_rows[RG_GATHER_TICKETS] = {-1, -1, -1, -1, -1, -1, -1, -1};   // rows a ticket was prepared for (-1: none)
     hipEvent_t ev_classified = nullptr, ev_miss_done = nullptr;

@@ -472,6 +472,85 @@ def test_gather_on_two_streams_captured(B, rows, static):
     ctx.close()
 
 
+def test_gather_after_calls_that_overlapped(B):
+    """Two calls that overlap on the shared scratch (a caller's error) spoil their own statistics; the calls after them, eager or
+    replayed, find their counters clear."""
+    rng, rows, dim, n = np.random.default_rng(8), 20_000, 16, 25_000
+    x = rng.standard_normal((n, dim), dtype=np.float32)
+    tag = rng.integers(0, 3, n)
+    row = np.zeros(n, dtype=np.int64)
+    for t in range(3):
+        row[tag == t] = np.arange((tag == t).sum())
+    loc = (row + (tag << 30)).astype(np.uint32).view(np.int32)
+    local, rows_c = (torch.from_numpy(x[tag == t]).to(DEV) for t in (0, 1))
+    remote = torch.from_numpy(x[tag == 2]).pin_memory()
+    cache = B.FeatureCache(n, rows_c.shape[0], dim, DEV)
+    cache.cache_rows.copy_(rows_c)
+    cache.loc.copy_(torch.from_numpy(loc))
+    nodes = rng.integers(0, n, rows).astype(np.int32)
+    want, st = oracle.gather_features(x, nodes, loc)
+    ids, streams = _i32(nodes), [torch.cuda.Stream() for _ in range(2)]
+    outs = [torch.zeros(rows, dim, device=DEV) for _ in range(2)]
+    stats = [torch.zeros(3, dtype=torch.int64, device=DEV) for _ in range(2)]
+    ctx = B.Context(0)
+    call = lambda k: ctx.gather_features_static(ids, rows, cache, local, remote, dim, outs[k], stats[k])  # noqa: E731
+    call(0)
+    graph = _captured(lambda: call(0))
+    for _ in range(20):
+        torch.cuda.synchronize()
+        for k in range(2):                              # side by side on the two streams
+            with torch.cuda.stream(streams[k]):
+                call(k)
+        torch.cuda.synchronize()
+        for replay in (True, False):
+            outs[0].fill_(float("nan"))
+            stats[0].fill_(-1)
+            graph.replay() if replay else call(0)
+            torch.cuda.synchronize()
+            assert tuple(stats[0].cpu().tolist()) == st and np.array_equal(outs[0].cpu().numpy(), want), replay
+    del graph
+    ctx.close()
+
+
+# A packed counter up to 2^23 - 1 rows, separate ones above, for all batches of a group that has such a one.
+@pytest.mark.parametrize("wide", [False, True])
+def test_lookups_of_very_large_batches(B, wide):
+    log(f"[very large batches] wide={wide}")
+    sizes = [700, 0, (1 << 23) - 1, 3] if not wide else [700, (1 << 23), 0, 3]
+    n, dim = 10_000, 1
+    rng = np.random.default_rng(5)
+    x = rng.standard_normal((n, dim), dtype=np.float32)
+    tag = rng.choice([0, 1, 2], n, p=[0.2, 0.79, 0.01])
+    row = np.zeros(n, dtype=np.int64)
+    for t in range(3):
+        row[tag == t] = np.arange((tag == t).sum())
+    loc = (row + (tag << 30)).astype(np.uint32).view(np.int32)
+    local, rows_c = (torch.from_numpy(x[tag == t]).to(DEV) for t in (0, 1))
+    remote = torch.from_numpy(x[tag == 2]).pin_memory()
+    cache = B.FeatureCache(n, rows_c.shape[0], dim, DEV)
+    cache.cache_rows.copy_(rows_c)
+    cache.loc.copy_(torch.from_numpy(loc))
+    ctx = B.Context(0)
+    for sizes_now in (sizes, [500, 20_000, 0, 1], sizes):
+        batches = [rng.integers(0, n, size=k).astype(np.int32) for k in sizes_now]
+        ids = [_i32(b) if b.size else torch.zeros(1, dtype=torch.int32, device=DEV) for b in batches]
+        stats = torch.full((4, 3), -1, dtype=torch.int64, device=DEV)
+        ctx.gather_prepare(0, ids, sizes_now, cache, [stats[t] for t in range(4)])
+        for t, k in enumerate(sizes_now):
+            out = torch.full((max(k, 1), dim), float("nan"), device=DEV)
+            ctx.gather_run(t, k, cache, local, remote, dim, out)
+            if k:
+                want, st = oracle.gather_features(x, batches[t], loc)
+                assert np.array_equal(out.cpu().numpy(), want), (sizes_now, t)
+            assert tuple(stats[t].cpu().tolist()) == (st if k else (0, 0, 0)), (sizes_now, t)
+        k = sizes_now[0]                                # the same ticket in one launch
+        out = torch.full((k, dim), float("nan"), device=DEV)
+        ctx.gather_features(ids[0], k, cache, local, remote, dim, out, stats[0])
+        want, st = oracle.gather_features(x, batches[0], loc)
+        assert tuple(stats[0].cpu().tolist()) == st and np.array_equal(out.cpu().numpy(), want)
+    ctx.close()
+
+
 def test_mirrored_pulls_of_growing_calls(B):
     """Calls that grow from single batches: every size adds up, and the gathers of an epoch sampled that way are right."""
     import dataclasses
