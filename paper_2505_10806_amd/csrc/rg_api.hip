@@ -165,9 +165,7 @@ rg_status rg_reserve(rg_ctx* ctx, int64_t num_nodes, int64_t max_frontier, int64
     RG_HIP(ctx, hipSetDevice(ctx->device));
     rg_status st;
     if ((st = rg_sampler_reserve(ctx, num_nodes, max_frontier, sample_group)) != RG_OK) return st;
-    if ((st = rg_sampler_reserve_slices(ctx, num_nodes, RG_MAX_HOPS)) != RG_OK) return st;
     if ((st = rg_ensure(ctx, ctx->topk_blk, ((size_t)rg_div_up(num_nodes, 1024) + 2) * 8)) != RG_OK) return st;
-    if ((st = rg_histogram_reserve(ctx)) != RG_OK) return st;
     if ((st = rg_gather_reserve(ctx, max_rows)) != RG_OK) return st;
     if ((st = rg_ensure(ctx, ctx->pf_list, (size_t)max_rows * 8)) != RG_OK) return st;
     if ((st = rg_ensure(ctx, ctx->pf_ctl, 64)) != RG_OK) return st;
@@ -175,6 +173,10 @@ rg_status rg_reserve(rg_ctx* ctx, int64_t num_nodes, int64_t max_frontier, int64
     const int64_t words = rg_max64(1, rg_div_up(num_nodes, 32));
     if ((st = rg_ensure(ctx, ctx->claim_bits, (size_t)words * 4)) != RG_OK) return st;
     if ((st = rg_ensure(ctx, ctx->claim_blk, (size_t)rg_max64(1, rg_div_up(words, 1024)) * 4)) != RG_OK) return st;
+    // what calls can do without, behind everything they need
+    ctx->slices_denied = ~size_t(0);
+    if ((st = rg_sampler_reserve_slices(ctx, num_nodes, RG_MAX_HOPS)) != RG_OK && st != RG_ERR_OOM) return st;
+    if ((st = rg_histogram_reserve(ctx)) != RG_OK && st != RG_ERR_OOM) return st;
     return RG_OK;
 }
 

@@ -932,7 +932,11 @@ constexpr int64_t kHistBoundsMax = 2ll << 20;
 
 }  // namespace
 
-rg_status rg_histogram_reserve(rg_ctx* ctx) { return rg_ensure(ctx, ctx->hist_bounds, (size_t)kHistBoundsMax * 4); }
+rg_status rg_histogram_reserve(rg_ctx* ctx) {
+    const rg_status st = rg_ensure(ctx, ctx->hist_bounds, (size_t)kHistBoundsMax * 4);
+    ctx->bounds_denied = st == RG_ERR_OOM;
+    return st;
+}
 
 extern "C" {
 
@@ -968,7 +972,7 @@ rg_status rg_access_histogram_epoch(rg_ctx* ctx, const int32_t* nodes, int64_t b
     const int range = hist_range(ctx, num_nodes);
     const int ranges = (int)rg_div_up(num_nodes, range);
     // without the bounds' scratch, in a captured call or for want of memory, the counting kernel searches for itself
-    if (!ctx->hist_bounds.p && !rg_capturing(s)) (void)rg_histogram_reserve(ctx);
+    if (!ctx->hist_bounds.p && !ctx->bounds_denied && !rg_capturing(s)) (void)rg_histogram_reserve(ctx);
     // batches per launch: the bounds of their runs fit the scratch, and a grid's second dimension
     const int64_t per_batch = (int64_t)num_hops * (ranges + 1);
     const int fit = (int)rg_min64((int64_t)(ctx->hist_bounds.bytes / 4) / per_batch, 65535 / num_hops);

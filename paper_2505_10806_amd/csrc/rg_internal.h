@@ -43,6 +43,7 @@ struct rg_ctx {
     RgBuf marked;       // uint32[ceil(N/32)] bitmap of every id met (see SampleScratch)
     RgBuf slice_marks;  // uint32[ceil(N/32)] bitmaps of the ids a hop has sampled (the same)
     RgBuf rank[2];      // {uint32, uint32}[ceil(N/32)] per hop, of four hops each: members of the hop's new tier and their positions
+    size_t slices_denied = ~size_t(0);   // bytes of `visited` from which on slice_marks, rank and seen could not be had (rg_reserve tries again)
     RgBuf pos;          // int32[N] position of a node in the cumulative frontier (valid for members only)
     RgBuf chunk_sum;    // int32[] per-chunk edge counts / bitmap block counts
     RgBuf row_start;    // int64[max_frontier] adjacency row start of every frontier node (current hop)
@@ -56,6 +57,7 @@ struct rg_ctx {
     RgBuf sched_keys;   // uint64[n]
     RgBuf sched_ids;    // int32[n]
     RgBuf sched_buckets; // int32: pairs per bucket, scatter cursors, bucket starts
+    bool bounds_denied = false;   // hist_bounds could not be had (rg_reserve tries again)
     RgBuf hist_bounds;  // int32: where the id ranges of the epoch histogram begin in the runs of some batches
     // top-K scratch
     RgBuf topk_ctl;     // TopkCtl
@@ -97,7 +99,7 @@ static inline bool rg_capturing(hipStream_t s) {
     if (hipStreamIsCapturing(s, &status) != hipSuccess) { (void)hipGetLastError(); return false; }
     return status == hipStreamCaptureStatusActive;
 }
-// Scratch with which no epoch histogram allocates anything.
+// Scratch with which no epoch histogram allocates anything; the same.
 rg_status rg_histogram_reserve(rg_ctx* ctx);
 // Makes every gather ticket hold at least `rows` rows (a reallocation invalidates prepared tickets).
 rg_status rg_gather_reserve(rg_ctx* ctx, int64_t rows);
@@ -105,7 +107,8 @@ rg_status rg_gather_reserve(rg_ctx* ctx, int64_t rows);
 // frontiers of up to max_frontier nodes (what rg_sample_blocks_group would otherwise grow on demand).
 rg_status rg_sampler_reserve(rg_ctx* ctx, int64_t num_nodes, int64_t max_frontier, int group, int64_t max_edges = 0,
                              bool first_seen = false);
-// What the sliced tier kernels use on top of that, for calls of as many batches (nothing on graphs without slices).
+// What the sliced tier kernels use on top of that, for calls of as many batches (nothing on graphs without slices).  Calls do
+// without it where it cannot be had (RG_ERR_OOM).
 rg_status rg_sampler_reserve_slices(rg_ctx* ctx, int64_t num_nodes, int hops, bool first_seen = false);
 // Allows the sampler's kernels the LDS they use on ctx->device (the device must be current).
 rg_status rg_sampler_init(rg_ctx* ctx);

@@ -1348,12 +1348,27 @@ rg_status rg_sampler_reserve_slices(rg_ctx* ctx, int64_t num_nodes, int hops, bo
     SampleScratch S;
     sampler_scratch_shape(num_nodes, 0, 0, S);
     if (!S.slices) return RG_OK;
+    if (ctx->visited.bytes >= ctx->slices_denied) return rg_set_error(ctx, RG_ERR_OOM, "no memory for the sampler's slices at the last try");
     const SlicedBytes need = sliced_bytes((int64_t)(ctx->visited.bytes / 4), (int64_t)(ctx->row_start.bytes / 8), first_seen);
-    rg_status st;
-    if ((st = rg_ensure(ctx, ctx->slice_marks, need.marks)) != RG_OK) return st;
-    if ((st = rg_ensure(ctx, ctx->rank[0], need.rank * (hops > kRankHops && !ctx->rank[0].p ? 2 : 1))) != RG_OK) return st;
-    if (hops > kRankHops && !rank_in_one(ctx, need) && (st = rg_ensure(ctx, ctx->rank[1], need.rank)) != RG_OK) return st;
-    return rg_ensure(ctx, ctx->seen, need.seen);
+    const bool more_hops = hops > kRankHops;
+    RgBuf* bufs[4] = {&ctx->slice_marks, &ctx->rank[0], &ctx->rank[1], &ctx->seen};
+    void* had[4];
+    for (int j = 0; j < 4; ++j) had[j] = bufs[j]->p;
+    for (int j = 0; j < 4; ++j) {
+        const size_t bytes = j == 0 ? need.marks : j == 1 ? need.rank * (more_hops && !ctx->rank[0].p ? 2 : 1)
+                             : j == 2 ? (more_hops && !rank_in_one(ctx, need) ? need.rank : 0) : need.seen;
+        const rg_status st = rg_ensure(ctx, *bufs[j], bytes);
+        if (st == RG_OK) continue;
+        // what was to be had is of no use without the rest: it is given back, and calls of that size do not try again
+        if (st == RG_ERR_OOM) ctx->slices_denied = ctx->visited.bytes;
+        for (int k = 0; k < j; ++k)
+            if (bufs[k]->p != had[k]) {
+                (void)hipFree(bufs[k]->p);
+                *bufs[k] = RgBuf();
+            }
+        return st;
+    }
+    return RG_OK;
 }
 
 // Slices use more LDS than a kernel may by default.

@@ -96,3 +96,49 @@ names = [k.split("<")[0] for k in kernels()]
 assert names.count("k_histogram_runs") == {launches}, names
 assert names.count("k_hist_bounds") == (0 if {search} else {launches}), names
 """)
+
+
+def test_reserve_and_sampler_without_memory_for_what_they_can_do_without():
+    """Rank words, slices' bitmaps and range bounds that cannot be allocated: rg_reserve succeeds all the same, gives back what it
+    got of them, and the calls behind it neither ask again nor wait for the device."""
+    host_calls.run("""
+N, FRONTIER, GROUP, FANOUTS = 10_000_000, 4_000_000, 8, (15, 10, 5)
+RANK, MARKS = 8 * GROUP * (N // 32) * 8, 256 * 40_000 * 4
+reserve = lambda c: lib.rg_reserve(c, i64(N), i64(FRONTIER), i64(1000), i32(GROUP))
+call = lambda c, **kw: sample(c, N, 500_000_000, [2000] * GROUP, FANOUTS, **kw)
+full = context()
+assert reserve(full) == OK
+total = rt.memory_held()
+lib.rg_destroy(full)
+assert rt.memory_held() == 0
+for short in (1, RANK // 2, RANK, RANK + MARKS // 2):     # the bounds, the rank words, the bitmaps cannot be had
+    rt.limit_memory(total - short)
+    c = context()
+    assert reserve(c) == OK, lib.rg_last_error(c)
+    sliced = short < RANK // 2
+    assert rt.memory_held() <= total - (0 if sliced else RANK + MARKS) - (8 << 20 if sliced else 0), (short, rt.memory_held())
+    rt.limit_memory(rt.memory_held())
+    log()
+    for _ in range(2):
+        assert call(c) == OK and histogram(c, N, 20, 3) == OK
+        lines = log()
+        assert all(x.startswith("launch") for x in lines), lines
+        assert any("k_slice_emit" in x for x in lines) == sliced
+        assert any("k_tier_emit" in x for x in lines) == (not sliced)
+    rt.limit_memory(1 << 40)
+    assert reserve(c) == OK and call(c) == OK and "k_slice_mark" in kernels()
+    lib.rg_destroy(c)
+# without rg_reserve: one failed try, then none until less is wanted
+rt.limit_memory(1 << 40)
+c = context()
+assert call(c) == OK
+base = rt.memory_held()
+lib.rg_destroy(c)
+rt.limit_memory(base - RANK // 4)
+c = context()
+log()
+assert call(c) == OK
+first = log()
+assert any(x.startswith("no memory") for x in first) and any("k_tier_emit" in x for x in first)
+assert call(c) == OK and all(x.startswith("launch") for x in log())
+""")
