@@ -162,6 +162,9 @@ class EpochPipeline:
         self.ready = [torch.cuda.Event() for _ in range(self.queue_depth)]
         self.consumed = [torch.cuda.Event() for _ in range(self.queue_depth)]
         self.slot_free = [torch.cuda.Event() for _ in range(self.queue_depth)]   # the slot's batch copied and read on the gather stream
+        self.rows_done = [torch.cuda.Event() for _ in range(self.queue_depth)]   # its HBM half, where the next gather had another stream
+        self._rows_due = [False] * self.queue_depth
+        self._gather_stream = None                                               # of the last gather
         self.miss_done = [torch.cuda.Event() for _ in range(self.queue_depth)]   # miss half copied
         self.prep_done = [torch.cuda.Event(), torch.cuda.Event()]                # lookups of a group made (one per half of the tickets)
         self._fork_due = {}                                                      # first ticket of a prepared group -> its half
@@ -402,7 +405,12 @@ class EpochPipeline:
         q = self._gathered % self.queue_depth
         if self.decoupled and self._gathered:
             # whatever the caller queued on this stream after the previous gather (on_batch) belongs to that batch's slot
-            self.slot_free[(self._gathered - 1) % self.queue_depth].record(main)
+            last = (self._gathered - 1) % self.queue_depth
+            self.slot_free[last].record(main)
+            self._rows_due[last] = self._gather_stream != main
+            if self._rows_due[last]:                    # the caller has changed streams: that batch's own work is on the other one
+                self.rows_done[last].record(self._gather_stream)
+        self._gather_stream = main
         self._gathered += 1
         self.out = self.out_ring[q]
         if self.consumer:
@@ -421,6 +429,9 @@ class EpochPipeline:
             if half is not None:
                 side.wait_event(self.prep_done[half])   # the one fork of the group: the miss stream reads the lookups' lists
             side.wait_event(self.slot_free[q])          # the buffer's earlier batch: its HBM half and whoever reads it on the gather stream
+            if self._rows_due[q]:
+                side.wait_event(self.rows_done[q])
+                self._rows_due[q] = False
             if self.consumer:
                 side.wait_event(self.consumed[q])
             self.ctx.gather_run_part(ticket, B.RG_GATHER_PART_MISS, *args, stream=side)
