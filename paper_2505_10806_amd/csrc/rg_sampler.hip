@@ -1065,10 +1065,12 @@ __global__ void __launch_bounds__(256) k_relabel(const RelabelGroup R, const Sam
 // barriers instead of launches (12 launches for two hops, each bound by its own latency).  A thread draws for one frontier
 // node and has all its picks' col_idx reads in flight.  One launch against one per phase, by nodes and the bound on a batch's
 // edges: 10 k nodes 16.6 k edges 27 / 53 us, 36 k 45 / 52, 72 k 60 / 52; 100 k nodes 4.2 k 21 / 53, 16.6 k 44 / 51, 18 k 54 / 54;
-// 500 k nodes 4.2 k 27 / 51, 16.6 k 65 / 55 (eight batches: the same, on as many compute units).
+// 500 k nodes 4.2 k 27 / 51, 16.6 k 65 / 55 (eight batches: the same, on as many compute units).  The frontiers' nodes count like
+// edges: there may be more of them where a fan-out is 0 or the graph has few edges (500 k seeds 1320-1370 / 73-124 us).
 constexpr int64_t kSmallNodes = 512 * 1024;     // two bitmaps of 64 KB
-inline bool rg_is_small(int64_t num_nodes, int64_t edges_bound) {
-    return num_nodes > 0 && num_nodes <= kSmallNodes && edges_bound <= (num_nodes <= 128 * 1024 ? 20 * 1024 : 8 * 1024);
+inline bool rg_is_small(int64_t num_nodes, int64_t edges_bound, int64_t frontiers_bound) {
+    return num_nodes > 0 && num_nodes <= kSmallNodes &&
+           rg_max64(edges_bound, frontiers_bound) <= (num_nodes <= 128 * 1024 ? 20 * 1024 : 8 * 1024);
 }
 
 struct SmallGroup {
@@ -1493,8 +1495,8 @@ rg_status rg_sample_blocks_group(rg_ctx* ctx, const rg_csr* csr, int32_t group, 
     sampler_scratch_shape(N, fub_max[num_hops], max_edges, S);
     const int64_t words = S.words;
     ctx->last_sample_group = 0;                       // no membership bitmaps to add until this call has been queued
-    int64_t edges_bound = 0;
-    for (int h = 0; h < num_hops; ++h) edges_bound += eub_max[h];
+    int64_t edges_bound = 0, frontiers_bound = 0;
+    for (int h = 0; h < num_hops; ++h) { edges_bound += eub_max[h]; frontiers_bound += fub_max[h]; }
     // in first-seen order the edges' ascending positions are kept where their final ones go
     bool ranked_seen = first_seen && rg_use_ranked_seen(S.slices, N, edges_bound, group);
     for (int g = 0; g < group && ranked_seen; ++g)
@@ -1505,7 +1507,7 @@ rg_status rg_sample_blocks_group(rg_ctx* ctx, const rg_csr* csr, int32_t group, 
     if (st != RG_OK) return st;
     int max_fanout = 0;
     for (int h = 0; h < num_hops; ++h) max_fanout = fanouts[h] < 0 ? RG_MAX_FANOUT : (fanouts[h] > max_fanout ? fanouts[h] : max_fanout);
-    const bool small = !first_seen && rg_is_small(N, edges_bound) && max_fanout <= 32 && csr->num_edges < (1ll << 32);
+    const bool small = !first_seen && rg_is_small(N, edges_bound, frontiers_bound) && max_fanout <= 32 && csr->num_edges < (1ll << 32);
     // Slices whose scratch is not there and cannot be allocated (a captured call, no memory): the atomic kernels, same results.
     if (!small && (mode == kTierSliced || mode == kTierRankedSeen)) {
         const SlicedBytes need = sliced_bytes(group * words, group * S.frontier_stride, first_seen);

@@ -142,3 +142,17 @@ first = log()
 assert any(x.startswith("no memory") for x in first) and any("k_tier_emit" in x for x in first)
 assert call(c) == OK and all(x.startswith("launch") for x in log())
 """)
+
+
+@pytest.mark.parametrize("n,edges,seeds,fanouts,small", [
+    (131_072, 9_000_000, [315], (10, 5), True), (131_072, 9_000_000, [316], (10, 5), False), (131_073, 9_000_000, [126], (10, 5), True),
+    (131_073, 9_000_000, [127], (10, 5), False), (524_289, 9_000_000, [10], (10, 5), False), (10_000, 9_000_000, [10], (33,), False),
+    (131_072, 9_000_000, [20_480], (0,), True), (131_072, 9_000_000, [20_481], (0,), False),            # frontiers without edges
+    (500_000, 9_000_000, [2048] * 2, (0, 1, 1), True), (500_000, 9_000_000, [2049] * 2, (0, 1, 1), False), (500_000, 4000, [500_000], (5,), False)])
+def test_batches_that_one_launch_takes(n, edges, seeds, fanouts, small):
+    host_calls.run(f"""
+c = context()
+assert sample(c, {n}, {edges}, {seeds}, {fanouts}) == OK, lib.rg_last_error(c)
+names = kernels()
+assert ([k.split("<")[0] for k in names] == ["k_sample_small"]) == {small}, names
+""")
