@@ -332,6 +332,13 @@ __global__ void __launch_bounds__(256) k_mark_seeds(const SampleGroup G, const S
 // The same in one launch for graphs of up to kMaxSlices slices: a workgroup owns one slice of a batch's ids, collects the
 // seeds of its range in LDS and writes its part of `visited`.
 // copy: `marked` starts as `visited` (kTierAtomic).
+// Every slice's workgroup reads all seeds, 1024 at a time: for more than 8192 of them clearing and marking take less in launches
+// of their own, unless several batches make many workgroups of them.  One hop after it, one launch against two or three: one
+// batch of 4096 seeds, N = 1 M 38 / 39 us, of 8192 43 / 39, of 16 k 52 / 41, of 65 k 126 / 64, of 200 k 305 / 117, at N = 10 M 38 / 43,
+// 45 / 45, 57 / 53, 97 / 76, 192 / 130; 8 batches of 16 k, N = 1 M 104 / 97, N = 4 M 106 / 111, N = 10 M 127 / 134.
+inline bool rg_use_init(int slices, int group, int64_t seeds) {
+    return slices > 0 && (seeds <= 8192 || (group >= 4 && slices * group >= 32));
+}
 __global__ void __launch_bounds__(1024) k_sample_init(const SampleGroup G, const SampleScratch S, int copy) {
     extern __shared__ uint32_t slice_bits[];
     const int g = rg_batch(S);
@@ -1584,7 +1591,7 @@ rg_status rg_sample_blocks_group(rg_ctx* ctx, const rg_csr* csr, int32_t group, 
         }
         ctx->sampler_dirty = true;       // cleared again when every launch of this call has been queued
     }
-    if (S.slices) {
+    if (rg_use_init(S.slices, group, seeds_max)) {
         k_sample_init<<<(unsigned)S.slices * ug, 1024, (size_t)S.slice_words * 4, s>>>(G, S, mode == kTierAtomic ? 1 : 0);
         RG_LAUNCH_CHECK(ctx, "k_sample_init");
     } else {

@@ -53,6 +53,7 @@ def _sparse_graph(n, active, degree, rng):
     (1_280_001, 3000, 8, [40, 7, 0], (5, 3)),           # a second slice of few words
     (20_000, 20_000, 40, [700, 900], (32, 31)),         # over 8192 new ids within 512 words
     (200_001, 150_000, 30, [1000, 1, 999], (25, 10)),   # the edge list split between workgroups
+    (200_001, 150_000, 30, [9000, 1], (7, 2)),          # more seeds than one launch marks
     (3_000_017, 400_000, 12, [900] * 8, (40, 3)),       # wavefront-per-node draw in front of the slices
     (300_007, 250_000, 30, [1500, 0, 1200, 1, 900, 1500, 1500, 1500], (25, 10)),    # over 2 Mi edges: first-seen order by rank words
     (300_007, 250_000, 30, [1500] * 4, (40, 10)),

@@ -156,3 +156,14 @@ assert sample(c, {n}, {edges}, {seeds}, {fanouts}) == OK, lib.rg_last_error(c)
 names = kernels()
 assert ([k.split("<")[0] for k in names] == ["k_sample_small"]) == {small}, names
 """)
+
+
+@pytest.mark.parametrize("n,seeds,one", [(1_000_000, [8192], True), (1_000_000, [8193, 5], False), (4_000_000, [50_000] * 8, True),
+                                         (4_000_000, [50_000] * 7, False), (41_000_000, [10], False)])
+def test_seeds_that_one_launch_takes(n, seeds, one):
+    host_calls.run(f"""
+c = context()
+assert sample(c, {n}, 90_000_000, {seeds}, (10,)) == OK, lib.rg_last_error(c)
+names = kernels()
+assert ("k_sample_init" in names) == {one} and ("k_mark_seeds" in names) == (not {one}), names
+""")
