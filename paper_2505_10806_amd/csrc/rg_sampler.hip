@@ -28,8 +28,26 @@ constexpr int kWordsPerBlock = 1024; // bitmap words per workgroup in the tier k
 // per edge.  Whole call, sliced against atomic: 8 batches of 4096 seeds (15,10,5) at N = 10 M 715 / 1700 us, at 40 M 733 / 1026,
 // at 100 M (80 slices) 1312 / 841; 8 batches of 64 seeds (10,5) at N = 10 M 102 / 92 us, at 40 M 239 / 160; on smaller graphs
 // both are bound by their launches, of which the sliced way has fewer.
-inline bool rg_use_slices(int slices, int64_t num_nodes, int64_t edges_bound) {
-    return slices > 0 && (num_nodes <= (4ll << 20) || edges_bound >= num_nodes / 16);
+// The edges of this line, and of the other lines between kernels, are those of nodes of average degree (rg_expected_edges), not the
+// static bound, which for RG_FANOUT_ALL is every edge of the graph: one batch of 16 seeds, all neighbours of one / two / three hops,
+// N = 10 M with 20 edges per node 39 / 67 / 116 us by the atomic way, 50 / 106 / 172 by slices.
+inline bool rg_use_slices(int slices, int64_t num_nodes, int64_t edges) {
+    return slices > 0 && (num_nodes <= (4ll << 20) || edges >= num_nodes / 16);
+}
+// Edges per hop of a batch of `seeds` nodes whose degrees are the graph's average, eub[] at most; returns their sum.
+inline int64_t rg_expected_edges(int64_t num_nodes, int64_t num_edges, int64_t seeds, const int32_t* fanouts, int num_hops,
+                                 const int64_t* eub, int64_t* expected) {
+    const double degree = num_nodes > 0 ? (double)num_edges / (double)num_nodes : 0.0;
+    double frontier = (double)seeds;
+    int64_t sum = 0;
+    for (int h = 0; h < num_hops; ++h) {
+        const double per_node = fanouts[h] < 0 || (double)fanouts[h] > degree ? degree : (double)fanouts[h];
+        expected[h] = rg_min64(eub[h], (int64_t)(frontier * per_node) + 1);
+        frontier += (double)expected[h];
+        if (frontier > (double)num_nodes) frontier = (double)num_nodes;
+        sum += expected[h];
+    }
+    return sum;
 }
 enum TierMode { kTierSliced = 0, kTierAtomic = 1, kTierFirstSeen = 2, kTierRankedSeen = 3 };
 // First-seen order through rank words: four more launches per hop, cheaper edges.  Whole call against kTierFirstSeen by the bound
@@ -37,8 +55,8 @@ enum TierMode { kTierSliced = 0, kTierAtomic = 1, kTierFirstSeen = 2, kTierRanke
 // 409 / 650; 8 of 512, N = 1 M (4.3 M) 261 / 310; 8 of 1024 (25,10), N = 200 k (2.3 M) 146 / 165; one batch of 1024, N = 2.4 M
 // (1.1 M) 233 / 180; 8 of 512 (10,5), N = 1 M (0.3 M) 121 / 100.
 constexpr int64_t kRankedSeenMin = 2ll << 20;
-inline bool rg_use_ranked_seen(int slices, int64_t num_nodes, int64_t edges_bound, int group) {
-    return rg_use_slices(slices, num_nodes, edges_bound) && edges_bound * group >= kRankedSeenMin;
+inline bool rg_use_ranked_seen(int slices, int64_t num_nodes, int64_t edges, int group) {
+    return rg_use_slices(slices, num_nodes, edges) && edges * group >= kRankedSeenMin;
 }
 constexpr int64_t kRankedSeenEdges = 16ll << 20;     // per hop and batch: the emit kernel's workgroups add up the totals in front of them
 constexpr int kSliceWords = 40000;   // bitmap words of a slice: 160,000 of the 163,840 bytes of LDS a compute unit has
@@ -1504,12 +1522,14 @@ rg_status rg_sample_blocks_group(rg_ctx* ctx, const rg_csr* csr, int32_t group, 
     ctx->last_sample_group = 0;                       // no membership bitmaps to add until this call has been queued
     int64_t edges_bound = 0, frontiers_bound = 0;
     for (int h = 0; h < num_hops; ++h) { edges_bound += eub_max[h]; frontiers_bound += fub_max[h]; }
+    int64_t expected[RG_MAX_HOPS];
+    const int64_t edges = rg_expected_edges(N, csr->num_edges, seeds_max, fanouts, num_hops, eub_max, expected);
     // in first-seen order the edges' ascending positions are kept where their final ones go
-    bool ranked_seen = first_seen && rg_use_ranked_seen(S.slices, N, edges_bound, group);
+    bool ranked_seen = first_seen && rg_use_ranked_seen(S.slices, N, edges, group);
     for (int g = 0; g < group && ranked_seen; ++g)
         for (int h = 0; h < num_hops; ++h)
             ranked_seen = ranked_seen && eub_max[h] <= kRankedSeenEdges && out[g].nbr_local && out[g].nbr_local[h] && out[g].nbr_local[h] != out[g].nbr[h];
-    TierMode mode = ranked_seen ? kTierRankedSeen : first_seen ? kTierFirstSeen : (rg_use_slices(S.slices, N, edges_bound) ? kTierSliced : kTierAtomic);
+    TierMode mode = ranked_seen ? kTierRankedSeen : first_seen ? kTierFirstSeen : (rg_use_slices(S.slices, N, edges) ? kTierSliced : kTierAtomic);
     rg_status st = rg_sampler_reserve(ctx, N, fub_max[num_hops], group, max_edges, first_seen);
     if (st != RG_OK) return st;
     int max_fanout = 0;
@@ -1674,7 +1694,8 @@ rg_status rg_sample_blocks_group(rg_ctx* ctx, const rg_csr* csr, int32_t group, 
 
         if (mode == kTierSliced || mode == kTierRankedSeen) {
             const int64_t split_edges = rg_max64(kSplitEdges, 2 * (int64_t)S.slice_words);
-            S.splits = (int)rg_max64(1, rg_min64(eub_max[h] / split_edges, kSliceGroups / (S.slices * group)));
+            // (hubs among the frontier: up to eight times the edges of average nodes)
+            S.splits = (int)rg_max64(1, rg_min64(rg_min64(eub_max[h], 8 * expected[h]) / split_edges, kSliceGroups / (S.slices * group)));
             k_slice_mark<<<(unsigned)(S.slices * S.splits) * ug, 1024, (size_t)S.slice_words * 4, s>>>(G, S, h);
             RG_LAUNCH_CHECK(ctx, "k_slice_mark");
             const unsigned tier_blocks = (unsigned)rg_max64(1, rg_div_up(words, kTierWords));

@@ -167,3 +167,30 @@ assert sample(c, {n}, 90_000_000, {seeds}, (10,)) == OK, lib.rg_last_error(c)
 names = kernels()
 assert ("k_sample_init" in names) == {one} and ("k_mark_seeds" in names) == (not {one}), names
 """)
+
+
+@pytest.mark.parametrize("n,edges,seeds,fanouts,order,tier", [
+    (10_000_000, 200_000_000, [16], (-1, -1), "ASCENDING", "k_tier_emit"), (10_000_000, 200_000_000, [16], (1024, 64), "ASCENDING", "k_tier_emit"),
+    (10_000_000, 200_000_000, [1024], (-1, -1, -1), "ASCENDING", "k_slice_emit<false>"),
+    (10_000_000, 490_000_000, [4096] * 8, (15, 10, 5), "ASCENDING", "k_slice_emit<false>"),
+    (10_000_000, 490_000_000, [700], (15, 10, 5), "ASCENDING", "k_slice_emit<false>"),           # 16 N edges of average nodes
+    (10_000_000, 490_000_000, [500], (15, 10, 5), "ASCENDING", "k_tier_emit"),
+    (1_000_000, 16_000_000, [16] * 8, (-1, -1), "FIRST_SEEN", "k_first_seen_emit")])
+def test_tiers_by_the_edges_that_average_nodes_have(n, edges, seeds, fanouts, order, tier):
+    host_calls.run(f"""
+c = context()
+assert sample(c, {n}, {edges}, {seeds}, {fanouts}, {order}) == OK, lib.rg_last_error(c)
+names = kernels()
+assert "{tier}" in names, names
+""")
+
+
+def test_few_edges_are_not_split_between_many_workgroups():
+    """All neighbours of one seed: the marking pass is not cut up for every edge of the graph."""
+    host_calls.run("""
+c = context()
+for seeds, fanouts, most in (([1], (-1,), 1), ([16], (-1, -1), 1), ([1500] * 2, (25, 10), 12)):
+    assert sample(c, 1_000_000, 16_000_000, seeds, fanouts) == OK
+    grids = [int(x.split()[2]) for x in log("launch k_slice_mark")]
+    assert grids and max(grids) == most, grids
+""")
