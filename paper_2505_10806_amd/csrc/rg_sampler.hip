@@ -50,15 +50,22 @@ inline int64_t rg_expected_edges(int64_t num_nodes, int64_t num_edges, int64_t s
     return sum;
 }
 enum TierMode { kTierSliced = 0, kTierAtomic = 1, kTierFirstSeen = 2, kTierRankedSeen = 3 };
-// First-seen order through rank words: four more launches per hop, cheaper edges.  Whole call against kTierFirstSeen by the bound
-// on the edges of all batches: 8 batches of 4096 seeds (15,10,5) at N = 10 M 1395 / 2530 us; 8 of 1024, N = 2.4 M (8.6 M edges)
-// 409 / 650; 8 of 512, N = 1 M (4.3 M) 261 / 310; 8 of 1024 (25,10), N = 200 k (2.3 M) 146 / 165; one batch of 1024, N = 2.4 M
-// (1.1 M) 233 / 180; 8 of 512 (10,5), N = 1 M (0.3 M) 121 / 100.
-constexpr int64_t kRankedSeenMin = 2ll << 20;
+// First-seen order through rank words: four more launches per hop and a pass over the hop's edges for every kSeenSlice new nodes,
+// but cheaper edges where the first-edge keys of all batches (4 N bytes each) are far from fitting the L2s.  Whole call, ranked
+// against kTierFirstSeen, on graphs of 49-50 edges per node unless said otherwise:
+//   one batch    slower on all of 0.1 M to 10 M nodes: 1.12 (4.3 M edges, N = 10 M) to 1.67 times
+//   2 batches    N = 10 M 0.83-0.98 from 1.1 M edges each, N = 2.4 M 0.98-1.11, N = 1 M 1.12-1.22
+//   3            N = 10 M 0.79-0.86, N = 2.4 M 0.81-0.90, N = 1 M 0.89-0.99, N = 233 k 1.02-1.22
+//   4            N = 10 M 0.62-0.72, N = 2.4 M 0.73-0.84, N = 1 M 0.85-0.96, N = 233 k 0.93-1.10, N = 100 k 1.00-1.17
+//   8            N = 300 k, 20 edges per node, 0.52-0.73 for N edges per batch, 0.88 for 13 N
+// so by N and the square of the batches; 2.1 M edges in all are too few (1.08-1.12 at 4 batches of 64 and 3 neighbours).  The passes
+// bound it above: 2 batches, N = 10 M, 8 M edges each 0.80-0.82, 16 M 0.85-1.12; N = 40 M 0.87 and 0.94-1.10.
+constexpr int64_t kRankedSeenMin = 2200 * 1000;
 inline bool rg_use_ranked_seen(int slices, int64_t num_nodes, int64_t edges, int group) {
-    return rg_use_slices(slices, num_nodes, edges) && edges * group >= kRankedSeenMin;
+    return rg_use_slices(slices, num_nodes, edges) && group >= 2 && num_nodes * group * group >= 9000 * 1000 &&
+           edges * group >= kRankedSeenMin && edges <= 2 * group * num_nodes;
 }
-constexpr int64_t kRankedSeenEdges = 16ll << 20;     // per hop and batch: the emit kernel's workgroups add up the totals in front of them
+constexpr int64_t kRankedSeenEdges = 8ll << 20;      // per hop and batch at most
 constexpr int kSliceWords = 40000;   // bitmap words of a slice: 160,000 of the 163,840 bytes of LDS a compute unit has
 constexpr int kMaxSlices = 32;
 constexpr int kSliceGroups = 256;    // workgroups the marking pass is split into at most (slices x splits x batches): one per

@@ -55,8 +55,9 @@ def _sparse_graph(n, active, degree, rng):
     (200_001, 150_000, 30, [1000, 1, 999], (25, 10)),   # the edge list split between workgroups
     (200_001, 150_000, 30, [9000, 1], (7, 2)),          # more seeds than one launch marks
     (3_000_017, 400_000, 12, [900] * 8, (40, 3)),       # wavefront-per-node draw in front of the slices
-    (300_007, 250_000, 30, [1500, 0, 1200, 1, 900, 1500, 1500, 1500], (25, 10)),    # over 2 Mi edges: first-seen order by rank words
+    (300_007, 250_000, 30, [1500, 0, 1200, 1, 900, 1500, 1500, 1500], (25, 10)),    # over 2.2 M edges: first-seen order by rank words
     (300_007, 250_000, 30, [1500] * 4, (40, 10)),
+    (2_600_021, 2_500_000, 20, [2000, 1900, 0], (15, 10, 5)),
     (2_600_021, 900_000, 12, [2000] * 4, (15, 10, 5)),
     (4_194_337, 200_000, 12, [60, 50], (5, 3)),         # atomic marking on a graph that has slices
     (4_194_337, 200_000, 12, [3000, 2000], (15, 10)),   # slices again: the edges outweigh the bitmaps
@@ -281,7 +282,7 @@ def test_epoch_histogram_without_scratch(B, n, batches, hops):
 
 
 # Calls whose tier kernels want scratch that the context's earlier calls had no use for, captured: ascending order after first-seen
-# order, small first-seen calls after calls of over 2 Mi edges, more hops, and the other ways round.
+# order, small first-seen calls after calls of over 2.2 M edges, more hops, and the other ways round.
 @pytest.mark.parametrize("warm_seeds,warm_fanouts,warm_seen,seeds,fanouts,seen", [
     ([600, 500], (25, 10), True, [600, 500], (25, 10), False),
     ([600, 500], (25, 10), False, [600, 500], (24, 2, 2), False),

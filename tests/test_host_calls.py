@@ -194,3 +194,20 @@ for seeds, fanouts, most in (([1], (-1,), 1), ([16], (-1, -1), 1), ([1500] * 2, 
     grids = [int(x.split()[2]) for x in log("launch k_slice_mark")]
     assert grids and max(grids) == most, grids
 """)
+
+
+# 2.2 M edges in all, nodes times batches squared, a hop's and all edges above.
+@pytest.mark.parametrize("n,edges,seeds,fanouts,ranked", [
+    (10_000_000, 490_000_000, [4096], (15, 10, 5), False), (10_000_000, 490_000_000, [1100] * 2, (15, 10, 5), True),
+    (10_000_000, 490_000_000, [1000] * 2, (15, 10, 5), False), (2_250_000, 112_000_000, [4096] * 2, (15, 10, 5), True),
+    (2_240_000, 112_000_000, [4096] * 2, (15, 10, 5), False), (1_000_000, 49_000_000, [1024] * 3, (15, 10, 5), True),
+    (232_965, 114_000_000, [4096] * 4, (25, 10), False), (300_000, 6_000_000, [1500] * 8, (25, 10), True),
+    (150_000, 60_000_000, [1024] * 8, (15, 10, 5), True), (150_000, 60_000_000, [4000] * 8, (15, 10, 20), False),
+    (10_000_000, 490_000_000, [500_000] * 2, (16,), True), (10_000_000, 490_000_000, [600_000] * 2, (16,), False)])
+def test_first_seen_calls_that_rank_words_take(n, edges, seeds, fanouts, ranked):
+    host_calls.run(f"""
+c = context()
+assert sample(c, {n}, {edges}, {seeds}, {fanouts}, FIRST_SEEN) == OK, lib.rg_last_error(c)
+names = kernels()
+assert ("k_seen_emit" in names) == {ranked} and ("k_first_seen_emit" in names) == (not {ranked}), names
+""")
