@@ -439,8 +439,8 @@ __device__ __forceinline__ int rg_scan_in_place(int32_t* __restrict__ data, int6
     return carry_s;
 }
 
-// Chunk totals of a hop -> exclusive offsets; the hop's edge total goes behind the last indptr entry.  Only in front of the
-// wavefront-per-node draw: the thread-per-node draw adds up the totals in front of its own chunk itself.
+// Chunk totals of a hop -> exclusive offsets; the hop's edge total goes behind the last indptr entry.  In front of the
+// wavefront-per-node draw, and of the thread-per-node draw on frontiers of over kDrawSelfScan chunks.
 __global__ void __launch_bounds__(1024) k_scan_hop(const SampleGroup G, const SampleScratch S, int hop) {
     const int g = rg_batch(S);
     const int n_h = G.tier_off[g][hop + 1];
@@ -548,11 +548,12 @@ __global__ void __launch_bounds__(RG_WAVE) k_hop_sample_wave(const int32_t* __re
 // 8 batches of 4096 seeds 35 us, hop 1 235 us with its marking atomics; now 15 and 66).
 // NODES = 64 spreads the reads of a frontier that fills less than two workgroups of 256 nodes per compute unit.
 constexpr int kDrawLoads = 8;
+constexpr int kDrawSelfScan = 16384;    // count chunks up to which a workgroup adds up those in front of its own itself
 
 template <int KMAX, int NODES, int MODE>
 __global__ void __launch_bounds__(256) k_hop_sample_thread(const int32_t* __restrict__ col_idx, const SampleGroup G,
                                                            const SampleScratch S, int fanout, uint32_t hop, uint32_t k0,
-                                                           uint32_t k1, uint32_t epoch) {
+                                                           uint32_t k1, uint32_t epoch, int scanned) {
     extern __shared__ uint32_t staged[];                 // NODES * fanout col_idx offsets
     __shared__ int part[4];
     __shared__ int end_s;
@@ -578,7 +579,11 @@ __global__ void __launch_bounds__(256) k_hop_sample_thread(const int32_t* __rest
     // edges in front of this count chunk
     const int chunk = (int)(first / kChunk);
     int before = 0;
-    for (int c = threadIdx.x; c < chunk; c += 256) before += chunk_sum[c];
+    if (scanned) {
+        if (threadIdx.x == 0) before = chunk_sum[chunk];
+    } else {
+        for (int c = threadIdx.x; c < chunk; c += 256) before += chunk_sum[c];
+    }
     before = rg_wave_sum(before);
     if (rg_lane() == 0) part[threadIdx.x >> 6] = before;
     const int off0 = indptr[first];                      // of this workgroup's first node within the count chunk
@@ -1671,8 +1676,15 @@ rg_status rg_sample_blocks_group(rg_ctx* ctx, const rg_csr* csr, int32_t group, 
             const int nodes_per = few ? 64 : 256;
             const unsigned draw_blocks = (unsigned)grid_for(fub_max[h], nodes_per, 1ll << 30);
             const size_t lds = (size_t)nodes_per * F * sizeof(uint32_t);
+            // Adding up grows with the square of the frontier, a scan costs 3 us for a small one: of 1 M nodes 172 / 175 us, of 8 M
+            // 1206 / 1196, of 16 M 2555 / 2498, of 40 M 7213 / 6750.
+            const int scanned = rg_div_up(fub_max[h], kChunk) > kDrawSelfScan;
+            if (scanned) {
+                k_scan_hop<<<ug, 1024, 0, s>>>(G, S, h);
+                RG_LAUNCH_CHECK(ctx, "k_scan_hop");
+            }
 #define RG_LAUNCH_DRAW(KM, NP, MODE)                                                                                  \
-    k_hop_sample_thread<KM, NP, MODE><<<draw_blocks * ug, 256, lds, s>>>(csr->col_idx, G, S, F, (uint32_t)h, k0, k1, epoch)
+    k_hop_sample_thread<KM, NP, MODE><<<draw_blocks * ug, 256, lds, s>>>(csr->col_idx, G, S, F, (uint32_t)h, k0, k1, epoch, scanned)
 #define RG_LAUNCH_DRAW_K(NP, MODE)                                                                                    \
     do { if (F <= 8) RG_LAUNCH_DRAW(8, NP, MODE); else if (F <= 16) RG_LAUNCH_DRAW(16, NP, MODE); else RG_LAUNCH_DRAW(32, NP, MODE); } while (0)
 #define RG_LAUNCH_DRAW_N(MODE) do { if (few) RG_LAUNCH_DRAW_K(64, MODE); else RG_LAUNCH_DRAW_K(256, MODE); } while (0)

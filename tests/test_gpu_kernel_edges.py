@@ -95,6 +95,21 @@ def test_blocks_across_the_ways_to_build_a_tier(B, ctx, n, active, degree, seeds
             assert torch.equal(o.tier_off, w.tier_off) and torch.equal(o.nodes[:k], w.nodes[:k])
 
 
+# Count chunks of 1024 frontier nodes, 16,384 of them added up by the draw itself, more scanned by a launch of their own.
+@pytest.mark.parametrize("seeds", [16_777_216, 16_777_217])
+def test_blocks_of_very_large_frontiers(B, ctx, seeds):
+    log(f"[very large frontiers] seeds={seeds}")
+    n = 16_800_000
+    deg = (np.arange(n) * 7 % 4).astype(np.int64)       # 0 to 3 neighbours, two at most drawn
+    rp = np.concatenate([[0], np.cumsum(deg)])
+    ci = (np.arange(rp[-1]) * 7919 % n).astype(np.int32)
+    csr = B.CsrGraph(torch.as_tensor(rp, device=DEV).to(torch.int32), _i32(ci))
+    ids = np.random.default_rng(1).permutation(n)[:seeds].astype(np.int32)
+    out = B.BlockBuffers(n, ci.size, seeds, (2,), DEV)
+    ctx.sample_blocks(csr, _i32(ids), seeds, (2,), 77, 2, out)
+    assert_batch_equal(HipBatch(out, 1), oracle.sample_blocks(rp, ci, ids, (2,), 77, 2), 1)
+
+
 # One launch for all hops, slices, atomic marking; first-seen order by first edges and by rank words.
 @pytest.mark.parametrize("n,active,degree,seeds,fanouts,first_seen", [
     (131_072, 60_000, 30, [300, 40], (10, 5), False),

@@ -211,3 +211,12 @@ assert sample(c, {n}, {edges}, {seeds}, {fanouts}, FIRST_SEEN) == OK, lib.rg_las
 names = kernels()
 assert ("k_seen_emit" in names) == {ranked} and ("k_first_seen_emit" in names) == (not {ranked}), names
 """)
+
+
+@pytest.mark.parametrize("seeds,scan", [(16_384 * 1024, False), (16_384 * 1024 + 1, True)])
+def test_frontiers_whose_chunks_are_scanned(seeds, scan):
+    host_calls.run(f"""
+c = context()
+assert sample(c, 20_000_000, 90_000_000, [{seeds}], (3,)) == OK
+assert ("k_scan_hop" in kernels()) == {scan}
+""")
