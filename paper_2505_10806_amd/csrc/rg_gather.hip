@@ -311,10 +311,17 @@ __global__ void __launch_bounds__(1024) k_gather_miss(const int32_t* __restrict_
 // pairs as k_classify does (a later rg_gather_run of the ticket finds them), then the workgroup copies its rows from whichever
 // store holds them, T chunks in flight per lane.  Saves the launches of lookup and miss copy and everything between two streams
 // but their order.  4 k rows of 64 floats, 1.5 k of them misses: 24 -> 13 us on one stream, 58 -> 35 on two; 60 k rows of 100 floats
-// in HBM 57 -> 40 on two.  The copies of a workgroup wait for its lookups and a tail of workgroups is left at the end, so large
-// batches are slower than with a lookup pass of their own: 70 k rows of 211 floats (59 MB) 46 / 46 us on one stream, of 602 floats
-// (168 MB) 76 / 65, 794 k rows of 256 floats 362 / 313.  The line is kFusedBytes of rows.
-constexpr int64_t kFusedBytes = 32ll << 20;
+// in HBM 57 -> 40 on two.  The copies of a workgroup wait for its lookups, a tail of workgroups is left at the end and every one of
+// them adds to one counter, so batches of many rows or bytes are slower than with a lookup pass of their own.  The line is at
+// kFusedRows of kFusedBytes; separate and fused, all rows in HBM, on one stream:
+//   1 to 64 floats   48 k rows 18 / 12-14 us, 64 k 17-18 / 15-17, 96 k 17-18 / 21-24, 128 k 17-19 / 27-32, 500 k of 16 floats 30 / 98
+//   100, 128, 256    48 k rows 18 / 16 and 16 / 16, 64 k 16-17 / 20-21; 24 k of 256 17 / 15, 32 k 18 / 18
+//   narrow chunks    211 floats 16 k rows 18 / 16, 24 k 20 / 23; 602 floats of 8 bytes each 8 k 18 / 16, 16 k 22 / 28
+// and on two streams, whose events cost the separate kernels more: 96 k rows of up to 64 floats 42-51 / 38-43, 128 k 40-50 / 44-51;
+// 48 k rows of 256 floats 49 / 42, 16 k of 602 52 / 46, 24 k 51 / 57; 211 floats 16 k 48 / 41, 24 k 38 / 42.  (With a third of the rows
+// missing the link decides and fused is 0.9-0.98 of separate on both sides of the line.)
+constexpr int64_t kFusedRows[2] = {64 << 10, 96 << 10};                        // on one stream, on two
+constexpr int64_t kFusedBytes[3][2] = {{16 << 20, 16 << 20}, {20 << 20, 32 << 20}, {24 << 20, 32 << 20}};      // chunks of 4, 8, 16 bytes
 template <int VEC, int T>
 __global__ void __launch_bounds__(256) k_gather_fused(const int32_t* __restrict__ nodes, int64_t n, const int32_t* __restrict__ n_dev,
                                                       const int32_t* __restrict__ loc, const int32_t* __restrict__ mirror_home,
@@ -420,6 +427,13 @@ rg_status launch_classify(rg_ctx* ctx, int count, const int32_t* const* input_no
     return RG_OK;
 }
 
+int gather_vec(int32_t dim, const rg_cache* cache, const float* local_store, int64_t local_stride, const float* remote_store,
+               int64_t remote_stride, const float* out, int64_t out_stride) {
+    const void* ptrs[4] = {local_store, remote_store, cache->cache_rows, out};
+    const int64_t strides[4] = {local_stride, remote_stride, cache->cache_rows ? cache->row_stride : 0, out_stride};
+    return rg_pick_vec(dim, ptrs, 4, strides, 4);
+}
+
 // Copies the rows of one classified batch: HBM rows on sh, miss rows on sm (joined back into sh when they differ).
 // Every argument has been validated by the caller; `timed` brackets the kernels for rg_profile_read.
 rg_status launch_copies(rg_ctx* ctx, const GatherScratch& scr, int64_t n, const int32_t* n_dev, const rg_cache* cache,
@@ -432,9 +446,7 @@ rg_status launch_copies(rg_ctx* ctx, const GatherScratch& scr, int64_t n, const 
         RG_HIP(ctx, hipEventRecord(ctx->ev_classified, sh));
         RG_HIP(ctx, hipStreamWaitEvent(sm, ctx->ev_classified, 0));
     }
-    const void* ptrs[4] = {local_store, remote_store, cache->cache_rows, out};
-    const int64_t strides[4] = {local_stride, remote_stride, cache->cache_rows ? cache->row_stride : 0, out_stride};
-    const int vec = rg_pick_vec(dim, ptrs, 4, strides, 4);
+    const int vec = gather_vec(dim, cache, local_store, local_stride, remote_store, remote_stride, out, out_stride);
     const RgRowShape shp = rg_row_shape(dim, vec);
     constexpr int U = 4;                                    // rows in flight per lane group in the miss kernel
     // T chunks in flight per lane; swept on the device: 2 is best (T = 4: -2 %, T = 8: -12 %), and non-temporal
@@ -490,9 +502,10 @@ rg_status launch_copies(rg_ctx* ctx, const GatherScratch& scr, int64_t n, const 
 // Batches that k_gather_fused takes (see there).  On two streams of which one records a graph launch_copies forks from the hit
 // stream, which draws the miss stream into the graph, and joins it back; launch_fused waits for the miss stream first, a wait that
 // would lead out of the graph.
-bool rg_fits_fused(int64_t n, int32_t dim, hipStream_t sh, hipStream_t sm, bool captured) {
-    if (n <= 0 || n * (int64_t)dim * 4 > kFusedBytes || n >= (1ll << kCountBits)) return false;
-    return sh == sm || (!captured && !rg_capturing(sm));
+bool rg_fits_fused(int64_t n, int32_t dim, int vec, hipStream_t sh, hipStream_t sm, bool captured) {
+    const int two = sh != sm;
+    if (n <= 0 || n > kFusedRows[two] || n * (int64_t)dim * 4 > kFusedBytes[vec / 2][two]) return false;
+    return !two || (!captured && !rg_capturing(sm));
 }
 
 // The one-launch gather.  The miss rows keep their place in both streams' order: behind what miss_stream was given before, in
@@ -504,9 +517,7 @@ rg_status launch_fused(rg_ctx* ctx, const GatherScratch& scr, const int32_t* nod
         RG_HIP(ctx, hipEventRecord(ctx->ev_classified, sm));
         RG_HIP(ctx, hipStreamWaitEvent(sh, ctx->ev_classified, 0));
     }
-    const void* ptrs[4] = {local_store, remote_store, cache->cache_rows, out};
-    const int64_t strides[4] = {local_stride, remote_stride, cache->cache_rows ? cache->row_stride : 0, out_stride};
-    const int vec = rg_pick_vec(dim, ptrs, 4, strides, 4);
+    const int vec = gather_vec(dim, cache, local_store, local_stride, remote_store, remote_stride, out, out_stride);
     const RgRowShape shp = rg_row_shape(dim, vec);
     const int rpb = (int)rg_max64(8, rg_min64(RG_WAVE, n / (2 * ctx->num_cus)));   // two workgroups per compute unit, 8-64 rows each
     const unsigned grid = (unsigned)rg_div_up(n, rpb);
@@ -625,7 +636,8 @@ rg_status rg_gather_features(rg_ctx* ctx, const int32_t* input_nodes, int64_t n,
     hipStream_t sh = (hipStream_t)hit_stream;
     hipStream_t sm = miss_stream ? (hipStream_t)miss_stream : sh;
     const bool captured = rg_capturing(sh);
-    if (!ctx->profiling && rg_fits_fused(n, dim, sh, sm, captured)) {    // while kernels are timed, HBM and miss rows have one each
+    const int vec = gather_vec(dim, cache, local_store, local_stride, remote_store, remote_stride, out, out_stride);
+    if (!ctx->profiling && rg_fits_fused(n, dim, vec, sh, sm, captured)) {    // while kernels are timed, HBM and miss rows have one each
         if ((st = rg_gather_reserve(ctx, n)) != RG_OK) return st;
         ctx->gather_rows[0] = -1;
         st = launch_fused(ctx, ticket_scratch(ctx, 0, true), input_nodes, n, n_dev, cache, local_store, local_stride, remote_store, remote_stride,
@@ -679,7 +691,8 @@ rg_status rg_gather_features_static(rg_ctx* ctx, const int32_t* input_nodes, int
     hipStream_t sm = miss_stream ? (hipStream_t)miss_stream : sh;
     const GatherScratch scr = static_scratch(ctx);
     const bool captured = rg_capturing(sh);
-    if (rg_fits_fused(n, dim, sh, sm, captured))
+    const int vec = gather_vec(dim, cache, local_store, local_stride, remote_store, remote_stride, out, out_stride);
+    if (rg_fits_fused(n, dim, vec, sh, sm, captured))
         return launch_fused(ctx, scr, input_nodes, n, n_dev, cache, local_store, local_stride, remote_store, remote_stride, dim, out,
                             out_stride, stats, sh, sm, captured);
     if ((st = launch_classify(ctx, 1, &input_nodes, &n, &n_dev, cache, &stats, &scr, sh)) != RG_OK) return st;

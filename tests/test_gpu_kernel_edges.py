@@ -398,10 +398,10 @@ def test_mean_aggregate_lane_groups(B, ctx, dim, stride):
     assert torch.isnan(agg[:, dim:]).all()
 
 
-# One launch up to 32 MiB of rows (8-64 rows per workgroup), lookups of 1024 rows per workgroup; counters that have to be zero
+# One launch up to 64 Ki rows of 24 MiB on one stream, 96 Ki rows of 32 MiB on two (8-64 rows per workgroup), lookups of 1024 rows per workgroup; counters that have to be zero
 # again for the next call, whichever kernel makes it.
 @pytest.mark.parametrize("rows,dim,stride", [(1, 64, 64), (7, 602, 604), (513, 3, 3), (4097, 37, 40), (16_384, 512, 512), (16_385, 512, 512),
-                                             (131_000, 64, 64), (140_000, 64, 64)])
+                                             (131_000, 64, 64), (140_000, 64, 64), (65_536, 64, 64), (65_537, 64, 64), (98_304, 64, 64)])
 @pytest.mark.parametrize("mirror", [False, True])
 def test_gather_one_launch_edges(B, ctx, rows, dim, stride, mirror):
     log(f"[gather] rows={rows} dim={dim} mirror={mirror}")
@@ -446,7 +446,7 @@ def test_gather_one_launch_edges(B, ctx, rows, dim, stride, mirror):
             assert np.array_equal(out[:k, :dim].cpu().numpy(), want)
 
 
-# One launch up to 32 MiB of rows, three above.
+# One launch up to 32 MiB of rows on two streams that record nothing, three above.
 @pytest.mark.parametrize("rows", [1500, 16_384, 16_385])
 @pytest.mark.parametrize("static", [False, True])
 def test_gather_on_two_streams_captured(B, rows, static):

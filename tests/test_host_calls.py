@@ -4,7 +4,7 @@ import pytest
 import host_calls
 
 
-# One launch up to 32 MiB of rows, more above.
+# One launch up to 32 MiB of rows (24 on one stream), more above.
 @pytest.mark.parametrize("rows", [1500, 16_384, 16_385])
 @pytest.mark.parametrize("static", [False, True])
 def test_two_stream_gather_stays_inside_the_graph_it_is_recorded_into(rows, static):
@@ -19,6 +19,8 @@ assert gather(c, {rows}, 512, hit=0x51, miss=0x52, static={static}) == OK, lib.r
 assert rt.end_capture() == 0
 assert [k.split("<")[0] for k in kernels()] == ["k_clear_counters", "k_classify", "k_gather_hbm", "k_gather_miss"]
 assert (len(eager) == 1) == ({rows} <= 16384), eager
+assert gather(c, {rows}, 512, hit=0x51, static={static}) == OK
+eager = kernels()
 rt.begin_capture(0x51)
 assert gather(c, {rows}, 512, hit=0x51, static={static}) == OK
 assert rt.end_capture() == 0 and kernels() == ["k_clear_counters"] + eager         # a replay starts from clear counters
@@ -219,4 +221,22 @@ def test_frontiers_whose_chunks_are_scanned(seeds, scan):
 c = context()
 assert sample(c, 20_000_000, 90_000_000, [{seeds}], (3,)) == OK
 assert ("k_scan_hop" in kernels()) == {scan}
+""")
+
+
+# Rows, bytes of rows, bytes of rows in chunks of 8 or 4; on one stream and on two.
+@pytest.mark.parametrize("rows,dim,one,two", [
+    (65_536, 1, True, True), (65_537, 1, False, True), (98_304, 16, False, True), (98_305, 16, False, False), (8_000_000, 1, False, False),
+    (12_288, 512, True, True), (12_289, 512, False, True), (16_384, 512, False, True), (16_385, 512, False, False),
+    (8709, 602, True, True), (8710, 602, False, True), (13_934, 602, False, True), (13_935, 602, False, False), (19_878, 211, True, True), (19_879, 211, False, False)])
+def test_gathers_that_one_launch_takes(rows, dim, one, two):
+    host_calls.run(f"""
+c = context()
+for miss, expected in ((None, {one}), (0x52, {two})):
+    for static in (False, True):
+        if static and {rows} > 1 << 20:
+            continue
+        assert gather(c, {rows}, {dim}, hit=0x51, miss=miss, static=static) == OK, lib.rg_last_error(c)
+        names = [k.split("<")[0] for k in kernels()]
+        assert names == (["k_gather_fused"] if expected else ["k_classify", "k_gather_hbm", "k_gather_miss"]), (miss, static, names)
 """)
