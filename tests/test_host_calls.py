@@ -240,3 +240,13 @@ for miss, expected in ((None, {one}), (0x52, {two})):
         names = [k.split("<")[0] for k in kernels()]
         assert names == (["k_gather_fused"] if expected else ["k_classify", "k_gather_hbm", "k_gather_miss"]), (miss, static, names)
 """)
+
+
+def test_mean_aggregate_grid():
+    """Up to 64 workgroups per compute unit (of the 256 the recording runtime's device counts as)."""
+    host_calls.run("""
+c = context()
+for dst, grid in ((1, 1), (4 * 16_384, 16_384), (200_000, 16_384)):
+    assert lib.rg_mean_aggregate(c, p(address()), p(address()), i64(dst), None, p(address()), i64(256), i32(256), p(address()), i64(256), None) == OK
+    assert [int(x.split()[2]) for x in log("launch k_mean_aggregate")] == [grid]
+""")
