@@ -87,9 +87,9 @@ rg_status rg_mean_aggregate(rg_ctx* ctx, const int32_t* indptr, const int32_t* n
         }
     }
     const int rows_per_block = 4 * (RG_WAVE >> shp.log2L);
-    // (16 workgroups per compute unit instead of 64: 195 / 197 us for the 270 k destinations above, but 100 k of 10 edges and 256
-    // floats 118 / 115, 200 k of 5 and 128 84 / 80, 200 k of 1 and 256 60 / 55)
-    const int grid = (int)rg_max64(1, rg_min64(rg_div_up(n_dst, rows_per_block), (int64_t)ctx->num_cus * 64));
+    // 32 workgroups per compute unit; with 16 / 32 / 64 of them the 270 k destinations above take 195 / 195 / 197 us, 100 k of 10 edges
+    // and 256 floats 118 / 117 / 115, 200 k of 5 and 128 84 / 82 / 80, 200 k of 1 and 256 60 / 56 / 55.
+    const int grid = (int)rg_max64(1, rg_min64(rg_div_up(n_dst, rows_per_block), (int64_t)ctx->num_cus * 32));
     const int tok = rg_prof_begin(ctx, RG_K_AGGREGATE, s);
     if (vec == 4)
         k_mean_aggregate<4, 8><<<grid, 256, 0, s>>>(indptr, nbr_local, n_dst, n_dst_dev, feat, feat_stride, agg, agg_stride, shp.cpr, shp.log2L, shp.tail);

@@ -243,10 +243,10 @@ for miss, expected in ((None, {one}), (0x52, {two})):
 
 
 def test_mean_aggregate_grid():
-    """Up to 64 workgroups per compute unit (of the 256 the recording runtime's device counts as)."""
+    """Up to 32 workgroups per compute unit (of the 256 the recording runtime's device counts as)."""
     host_calls.run("""
 c = context()
-for dst, grid in ((1, 1), (4 * 16_384, 16_384), (200_000, 16_384)):
+for dst, grid in ((1, 1), (4 * 8192, 8192), (200_000, 8192)):
     assert lib.rg_mean_aggregate(c, p(address()), p(address()), i64(dst), None, p(address()), i64(256), i32(256), p(address()), i64(256), None) == OK
     assert [int(x.split()[2]) for x in log("launch k_mean_aggregate")] == [grid]
 """)
