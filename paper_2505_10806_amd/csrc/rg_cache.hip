@@ -277,10 +277,12 @@ __device__ __forceinline__ TopkState rg_topk_state(const TopkCtl* __restrict__ c
     return st;
 }
 
-// Histogram of byte `pass` (0 = most significant) of the counts of candidates that match the prefix.
+// Histogram of byte `pass` (0 = most significant) of the counts of candidates that match the prefix.  skip (or NULL): a flag that,
+// when set, says that nobody asks for it.
 __global__ void __launch_bounds__(256) k_topk_hist(const uint32_t* __restrict__ counts, const int32_t* __restrict__ home, int64_t n,
-                                                   int pass, int64_t capacity, TopkCtl* __restrict__ ctl) {
+                                                   int pass, int64_t capacity, TopkCtl* __restrict__ ctl, const uint32_t* __restrict__ skip) {
     __shared__ uint32_t h[256];
+    if (skip && *skip) return;                               // uniform
     const TopkState st = rg_topk_state<256>(ctl, capacity, pass);
     if (st.resolved) return;                                 // uniform
     h[threadIdx.x] = 0u;
@@ -1049,7 +1051,7 @@ rg_status rg_build_cache(rg_ctx* ctx, const uint32_t* counts, const int32_t* hom
     RG_LAUNCH_CHECK(ctx, "k_topk_hist_low");
     const int hist_grid = (int)rg_max64(1, rg_min64(rg_div_up(num_nodes, 256 * 8), (int64_t)ctx->num_cus * 8));
     for (int pass = 0; pass < 4; ++pass) {                   // return at once unless the threshold is in the clamped bin
-        k_topk_hist<<<hist_grid, 256, 0, s>>>(counts, home, num_nodes, pass, cache->capacity_rows, ctl);
+        k_topk_hist<<<hist_grid, 256, 0, s>>>(counts, home, num_nodes, pass, cache->capacity_rows, ctl, nullptr);
         RG_LAUNCH_CHECK(ctx, "k_topk_hist");
     }
     k_topk_count<<<(int)nblocks, 1024, 0, s>>>(counts, home, num_nodes, ctl, cache->capacity_rows, blk_gt, blk_eq, cache->num_cached);
@@ -1122,14 +1124,14 @@ rg_status rg_cache_hit_curve(rg_ctx* ctx, const uint32_t* counts, const int32_t*
     k_hit_curve_low<<<1, 256, 0, s>>>(ctl, caps_dev, num_capacities, (unsigned long long*)hits, (unsigned long long*)remote_total, resolved);
     RG_LAUNCH_CHECK(ctx, "k_hit_curve_low");
     // capacities whose threshold lies among counts >= kLowBins - 1 (never the case when the counts are bounded by a few
-    // hundred batches) go through the radix select one by one; for all others these kernels return at once
+    // hundred batches) go through the radix select one by one; for all others, capacities of all candidates among them, these kernels return at once
     for (int j = 0; j < num_capacities; ++j) {
         if (j > 0) {
             k_topk_init<<<4, 256, 0, s>>>(ctl, 1);
             RG_LAUNCH_CHECK(ctx, "k_topk_init");
         }
         for (int pass = 0; pass < 4; ++pass) {
-            k_topk_hist<<<grid, 256, 0, s>>>(counts, home, num_nodes, pass, capacities[j], ctl);
+            k_topk_hist<<<grid, 256, 0, s>>>(counts, home, num_nodes, pass, capacities[j], ctl, resolved + j);
             RG_LAUNCH_CHECK(ctx, "k_topk_hist");
         }
         k_hit_sum<<<grid, 256, 0, s>>>(counts, home, num_nodes, ctl, capacities[j], resolved + j, (unsigned long long*)hits + j);

@@ -376,6 +376,21 @@ def test_select_block_edges(B, ctx, n, large):
         assert cap == 0 or not cache.filled.any()
 
 
+def test_hit_curve_of_large_counts(B, ctx):
+    """Every count behind the clamped bin: capacities of all candidates are read off the sums, the others go through the radix
+    passes, in either order."""
+    rng = np.random.default_rng(6)
+    n = 30_000
+    remote = rng.random(n) < 0.7
+    home = np.where(remote, (2 << 30) + np.cumsum(remote) - 1, np.cumsum(~remote) - 1).astype(np.uint32).view(np.int32)
+    counts = rng.choice(np.array([2047, 2048, 70_000, 2 ** 31 + 5], dtype=np.uint32), n)
+    k = int(remote.sum())
+    for caps in ([k, k + 1, 10 ** 6], [0, 1, k - 1, k, 17, k + 1, 5000, 0]):
+        hits, total = ctx.cache_hit_curve(torch.from_numpy(counts.view(np.int32)).to(DEV), _i32(home), caps)
+        want, want_total = oracle.cache_hit_curve(counts, home, caps)
+        assert hits.cpu().numpy().astype(np.uint64).tolist() == want.tolist() and int(total.item()) == want_total
+
+
 # Lane groups of 64, 32 and 16 (65, 68, 80, 151 chunks of 16 bytes; 301 of 8), eight edges per step.
 @pytest.mark.parametrize("dim,stride", [(260, 260), (269, 272), (317, 320), (602, 604), (602, 602)])
 def test_mean_aggregate_lane_groups(B, ctx, dim, stride):
