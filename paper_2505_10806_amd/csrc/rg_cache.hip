@@ -190,7 +190,8 @@ __global__ void __launch_bounds__(256) k_topk_init(TopkCtl* __restrict__ ctl, in
 }
 
 // low[min(count, kLowBins - 1)] += 1 for every candidate; ovf_sum += count for those in the last bin.  One workgroup per
-// compute unit: with more of them their additions to the same few bins queue up (1196 workgroups 38 us at 2.4 M nodes).
+// compute unit: with more of them their additions to the same few bins queue up (1196 workgroups 38 us at 2.4 M nodes).  Above
+// 8 Mi nodes two, which read faster: the selection at 10 M nodes 110 -> 104 us, at 40 M 412 -> 364, at 100 M 972 -> 858.
 __global__ void __launch_bounds__(1024) k_topk_hist_low(const uint32_t* __restrict__ counts, const int32_t* __restrict__ home, int64_t n,
                                                         TopkCtl* __restrict__ ctl) {
     constexpr int U = 4;
@@ -897,6 +898,10 @@ __global__ void __launch_bounds__(256) k_zero_i32(int32_t* __restrict__ p, int n
     if (i < n) p[i] = 0;
 }
 
+int low_grid_of(const rg_ctx* ctx, int64_t num_nodes) {
+    return (int)rg_max64(1, rg_min64(rg_div_up(num_nodes, 4096), ctx->num_cus * (num_nodes > (8ll << 20) ? 2 : 1)));
+}
+
 // Launches the list-driven row copy.  `blocks` and `threads` bound the wavefronts in flight.
 rg_status launch_list_copy(rg_ctx* ctx, const int32_t* list, const uint32_t* pctl, const float* src, int64_t src_stride,
                            float* dst, int64_t dst_stride, int64_t dst_rows, int32_t dim, int64_t n_upper, int64_t blocks,
@@ -1046,7 +1051,7 @@ rg_status rg_build_cache(rg_ctx* ctx, const uint32_t* counts, const int32_t* hom
 
     k_topk_init<<<4, 256, 0, s>>>(ctl, 0);
     RG_LAUNCH_CHECK(ctx, "k_topk_init");
-    const int low_grid = (int)rg_max64(1, rg_min64(rg_div_up(num_nodes, 4096), ctx->num_cus));
+    const int low_grid = low_grid_of(ctx, num_nodes);
     k_topk_hist_low<<<low_grid, 1024, 0, s>>>(counts, home, num_nodes, ctl);
     RG_LAUNCH_CHECK(ctx, "k_topk_hist_low");
     const int hist_grid = (int)rg_max64(1, rg_min64(rg_div_up(num_nodes, 256 * 8), (int64_t)ctx->num_cus * 8));
@@ -1115,7 +1120,7 @@ rg_status rg_cache_hit_curve(rg_ctx* ctx, const uint32_t* counts, const int32_t*
         RG_LAUNCH_CHECK(ctx, "k_store_caps");
     }
     const int grid = (int)rg_max64(1, rg_min64(rg_div_up(num_nodes, 256 * 8), (int64_t)ctx->num_cus * 8));
-    const int low_grid = (int)rg_max64(1, rg_min64(rg_div_up(num_nodes, 4096), ctx->num_cus));
+    const int low_grid = low_grid_of(ctx, num_nodes);
     // one pass over the nodes gives the histogram of the counts; every capacity is read off it
     k_topk_init<<<4, 256, 0, s>>>(ctl, 0);
     RG_LAUNCH_CHECK(ctx, "k_topk_init");

@@ -250,3 +250,15 @@ for dst, grid in ((1, 1), (4 * 8192, 8192), (200_000, 8192)):
     assert lib.rg_mean_aggregate(c, p(address()), p(address()), i64(dst), None, p(address()), i64(256), i32(256), p(address()), i64(256), None) == OK
     assert [int(x.split()[2]) for x in log("launch k_mean_aggregate")] == [grid]
 """)
+
+
+def test_selection_grid():
+    """The counts' histogram: one workgroup per compute unit, two above 8 Mi nodes."""
+    host_calls.run("""
+c = context()
+for n, grid in ((1, 1), (4097, 2), (8 << 20, 256), ((8 << 20) + 1, 512)):
+    cache = Cache(address(), address(), 1000, 4, address(), address(), address(), 0, None)
+    assert lib.rg_build_cache(c, p(address()), p(address()), i64(n), None, i64(0), i32(4), byref(cache), None) == OK
+    assert [int(x.split()[2]) for x in log("launch k_topk_hist_low")] == [grid]
+    log()
+""")
