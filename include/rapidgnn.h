@@ -99,7 +99,9 @@ RG_API const char* rg_version(void);
  * graphs of up to num_nodes nodes, cumulative frontiers of up to max_frontier nodes, sampler
  * calls of up to sample_group batches (1 for rg_sample_blocks), gathers and per-batch prefetch
  * passes of up to max_rows rows.  Optional: every call grows the scratch on demand (a
- * synchronising allocation).  1 <= sample_group <= RG_MAX_GROUP. */
+ * synchronising allocation).  Scratch that calls can do without (they then run other kernels, with
+ * the same results) is reserved last; where it cannot be had the call succeeds all the same, and later
+ * calls of that size do not ask for it again.  1 <= sample_group <= RG_MAX_GROUP. */
 RG_API rg_status rg_reserve(rg_ctx* ctx, int64_t num_nodes, int64_t max_frontier, int64_t max_rows, int32_t sample_group);
 
 /* CSR adjacency in HBM: row v lists the nodes whose features v aggregates (Eq. 1, eta(v)). */
@@ -159,6 +161,9 @@ RG_API rg_status rg_blocks_bounds(int64_t num_nodes, int64_t num_edges, int64_t 
 
 /* seeds: device int32[num_seeds], distinct, num_seeds >= 0; fanouts: host int32[num_hops],
  * each in [0, RG_MAX_FANOUT] or RG_FANOUT_ALL; 1 <= num_hops <= RG_MAX_HOPS.
+ * A caller that keeps nothing but nbr_local may pass one nbr buffer (and one indptr buffer) for all hops:
+ * every hop's nbr_local is right, the shared lists hold the last hop's (with separate ones all hops are
+ * relabelled by one launch).
  * Errors: RG_ERR_INVALID_ARG; RG_ERR_OOM; RG_ERR_CAPACITY when a buffer is below its bound: nothing
  * is launched and nodes_cap, indptr_cap[h] and nbr_cap[h] of the offending rg_blocks are overwritten
  * with the required sizes (the values rg_blocks_bounds gives), so the caller can reallocate and retry. */
@@ -199,8 +204,8 @@ RG_API rg_status rg_access_histogram(rg_ctx* ctx, const int32_t* nodes, int64_t 
  * nodes[b * batch_stride .. + tier_off[b][num_hops + 1]), with tier_off[b] the num_hops + 2 tier
  * offsets rg_sample_blocks wrote for that batch.  Equivalent to one rg_access_histogram call per
  * batch, but ids that recur across batches are accumulated in LDS-private counters: each workgroup
- * owns an id range, finds its entries in every ascending tier by binary search and adds the range to
- * counts once.  Precondition: tiers 1..num_hops of every batch are ascending by id (as produced by
+ * owns an id range, whose entries in every ascending tier are found by their proportional place or by
+ * binary search, and adds the range to counts once.  Precondition: tiers 1..num_hops of every batch are ascending by id (as produced by
  * rg_sample_blocks); tier 0 (at most max_seeds seeds per batch) may be in any order.
  * With first_batch != NULL the same pass also records when each node is first needed:
  * first_batch[v] = min(first_batch[v], smallest b whose list contains v); the caller sets the array
@@ -338,7 +343,11 @@ RG_API rg_status rg_plan_sampled(rg_ctx* ctx, int32_t group, const rg_cache* cac
  * misses only).  stats = {#local rows, #cache hits, #misses}.
  * Rows served from HBM are copied on hit_stream; the miss rows are copied on miss_stream
  * concurrently (if it differs from hit_stream) and joined back: when the call returns, all
- * work is ordered before anything queued later on hit_stream.
+ * work is ordered before anything queued later on hit_stream.  Small batches are copied whole, by one
+ * launch on hit_stream, behind what miss_stream was given before and in front of what either stream
+ * is given next: up to 96 Ki rows and 32 MiB of them (on one stream 64 Ki and 24 MiB; 16 or 20 MiB where
+ * rows move in 4- or 8-byte chunks), unless kernels are being timed or, with two streams, one of them
+ * records a graph.
  * input_nodes: device int32[>= n]; n_dev: as for rg_access_histogram; out: device
  * float[n * out_stride]; stats: device int64[3]. */
 typedef struct { int64_t n_local, n_hit, n_miss; } rg_gather_stats;
@@ -356,8 +365,7 @@ RG_API rg_status rg_gather_features(rg_ctx* ctx, const int32_t* input_nodes, int
  * first_ticket + count - 1; rg_gather_run copies the rows of one prepared ticket (HBM rows on
  * hit_stream, miss rows on miss_stream, joined as in rg_gather_features).  Preparing several batches
  * at once pays the lookup launch once per group and leaves one copy kernel per batch on the stream.
- * rg_gather_features = prepare (ticket 0, one batch) + run (batches of up to 32 MiB of rows in one launch, unless kernels are
- * being timed).  A ticket is busy from its prepare until
+ * rg_gather_features = prepare (ticket 0, one batch) + run, small batches in one launch.  A ticket is busy from its prepare until
  * the work of its run has finished; prepare and run of a ticket are given the same n, n_dev and
  * cache and are ordered on their streams by the caller (trivially so on one stream).
  * rg_gather_run returns RG_ERR_STATE if the ticket was not prepared for n rows.
@@ -394,7 +402,8 @@ RG_API rg_status rg_gather_run_part(rg_ctx* ctx, int32_t ticket, int32_t part, i
  * RG_STATIC_GATHER_MAX_ROWS rows (12 B per row, about 12.6 MB, resident on every GPU the
  * library has run on until the process ends); n above that returns RG_ERR_CAPACITY and queues
  * nothing.  Every call on one GPU, from any context, shares that GPU's array: calls that
- * overlap in time on one GPU race, so the caller orders them (one stream, or events).  The
+ * overlap in time on one GPU race, so the caller orders them (one stream, or events); calls that
+ * did overlap may have wrong rows and statistics, the calls after them do not.  The
  * kernels are not bracketed for rg_profile_read. */
 #define RG_STATIC_GATHER_MAX_ROWS (1 << 20)
 RG_API rg_status rg_gather_features_static(rg_ctx* ctx, const int32_t* input_nodes, int64_t n, const int32_t* n_dev,
@@ -425,7 +434,7 @@ RG_API rg_status rg_mean_aggregate(rg_ctx* ctx, const int32_t* indptr, const int
 typedef enum {
     RG_K_GATHER_HBM = 0,   /* rows served from the local store and the cache */
     RG_K_GATHER_MISS = 1,  /* rows pulled from the remote store */
-    RG_K_SAMPLE = 2,       /* per-hop draw + neighbour read kernel */
+    RG_K_SAMPLE = 2,       /* per-hop draw + neighbour read kernel (small batches: the one kernel of all hops) */
     RG_K_HISTOGRAM = 3,
     RG_K_CACHE_FILL = 4,   /* bulk pull and per-batch prefetch pulls */
     RG_K_AGGREGATE = 5,

@@ -7,8 +7,8 @@ namespace {
 // agg[i] = (1/m_i) * sum over the block's edges e of row i, in edge order, of feat[nbr_local[e]].
 // A wavefront is split into groups of L lanes per destination row; each lane owns chunk c0 (+ L, + 2L, ...) of the
 // row and accumulates it in registers, E edges at a time so that E independent row loads are in flight.
-// Bound by the source rows' traffic behind L2 (27 % of the reads hit it on a power-law block; 270 k destinations of 5 edges,
-// 256 floats: 1.3 GB of rows in 196 us; 380 k distinct rows would be 0.4 GB).  E = 8 takes fan-outs of 5 in one step (E = 4: 206).
+// Bound by the source rows' traffic behind L2 (270 k destinations of 5 edges on a power-law block, 256 floats: 1.31 GB of rows
+// asked for, 27 % of the reads hit L2, so 0.96 GB from behind it, and 0.28 written in 196 us; 373 k distinct rows would be 0.38 GB).  E = 8 takes fan-outs of 5 in one step (E = 4: 206).
 // Cutting the columns into one part per XCD, so that every L2 holds its part of more rows, was slower (8 parts 228, 4 parts 205).
 template <int VEC, int E>
 __global__ void __launch_bounds__(256) k_mean_aggregate(const int32_t* __restrict__ indptr, const int32_t* __restrict__ nbr_local,

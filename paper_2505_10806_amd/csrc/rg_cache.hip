@@ -20,7 +20,7 @@ __global__ void __launch_bounds__(256) k_histogram(const int32_t* __restrict__ n
 // an LDS-private copy of its counters with LDS atomics and adds the range to `counts` once with plain coalesced
 // read-modify-writes: no global atomics, every id read once.
 // Where the ranges begin in every run is found first, by k_hist_bounds: searched for by every workgroup itself (two bisections
-// per run of 18 steps, whose lines no other lane shares) the 10 M random lines took 180 of 184 us for 76 M entries on 2.4 M
+// per run of 18 steps, whose lines no other lane shares) the 10 M random lines took 180 of 184 us for 72 M entries on 2.4 M
 // nodes with first batches.  The range is chosen so that the workgroups, two per compute unit, make whole rounds of the
 // device (598 on 512 places: 273 us).  Now 19 + 92 us.
 constexpr int kHistRangeMax = 8192;    // ids per workgroup at most (32 KB of LDS, 64 KB when first batches are tracked as well)

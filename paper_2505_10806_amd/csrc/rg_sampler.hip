@@ -1067,8 +1067,9 @@ struct RelabelGroup {
 
 // nbr_local[e] = position of nbr[e] in the extended frontier; the hop's edge count is indptr[n_h].
 // RANKED: the rank words of the tiers, latest first (a hop's edges mostly name its new tier), pos[] for the seeds.  The words
-// of one tier are N / 4 bytes (2.5 MB at N = 10 M, within one XCD's L2) where pos[] is 4 N: 142 us against 251 us for
-// 15.9 M edges; rank words alone, without the edges that name earlier tiers, would take 74 us.
+// of one tier are N / 4 bytes (2.5 MB at N = 10 M) where pos[] is 4 N.  Three hops of 8 batches of 4096 seeds, 20.6 M edges: 202 us,
+// bound by the rank words: three tiers of them are more than one XCD's L2, 71 % of the reads hit it.  (The 15.9 M edges of hop 2
+// by themselves: pos[] 251 us, the new tier's words and those of one more 142, the new tier's alone, which would not do, 74.)
 template <bool RANKED>
 __global__ void __launch_bounds__(256) k_relabel(const RelabelGroup R, const SampleScratch S) {
     constexpr int U = 4;                                 // edges in flight per thread

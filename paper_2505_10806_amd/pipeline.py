@@ -16,7 +16,8 @@ Further choices of the driver, each a constructor argument:
 * the pull stream can be bound to a few compute units of its own, every other stream to the rest (pull_cus; the
   caller then works on work_stream);
 * when batches can have miss rows, their copies follow each other on the miss stream instead of being forked and
-  joined per batch (decoupled_misses); when they cannot, the empty miss pass stays on the gather stream.
+  joined per batch (decoupled_misses); when they cannot, there is no miss pass (with a cache the caller has put in place of
+  the pipeline's, which may leave rows out, it runs on the gather stream).
 
 Host code only sequences library calls and owns the buffers; every step runs in the library's kernels.
 No host synchronisation happens inside the offline stage: frontier sizes stay on the device.  They are
@@ -136,10 +137,11 @@ class EpochPipeline:
         if mirror_pulls not in ("group", "batch"):
             raise ValueError("mirror_pulls must be 'group' or 'batch'")
         self.group_pulls = self.mirror and mirror_pulls == "group"
-        # Short sampler calls in front cost the host about 0.1 ms each, so they have to save link time: they do from about
-        # 512 MB that one batch may name.  Whole epochs with and without them, by that bound: 14 batches 33 MB 2.0 / 1.5 ms, 19
-        # batches 9 MB 2.1 / 1.6; 40 batches 300 MB 7.13 / 7.16 and 6.93 / 6.87; 20 batches 300 MB 6.18 / 6.09 and 6.88 / 7.02,
-        # 768 MB 15.3 / 16.6, 1.1 GB 19.1 / 19.4.
+        # Short sampler calls in front cost the host about 0.1 ms each, so they have to save link time: they do where one batch
+        # may name hundreds of MB.  Whole epochs with and without them, by that bound: 14 batches 33 MB 2.0 / 1.5 ms, 19 batches
+        # 9 MB 2.1 / 1.6, 40 batches 150 MB 9.14 / 8.96; 300 MB, six shapes, 0.98-1.03 times as fast with them; 384-480 MB 1.00-1.07
+        # (20 batches of 4096 seeds 8.10 / 8.60 and 10.3 / 10.9, 40 of 1024 9.89 / 9.93); 528-653 MB 1.02-1.06; 768 MB 15.35 / 16.45;
+        # 1.1 GB 19.1 / 19.4.  Where two hops name few of the rows they may, 708 MB, 0.99.  At 512 MB every shape of three hops gains.
         self.ramp = self.group_pulls and min(wl.n_remote, self.slot) * wl.stride * 4 >= 512_000_000
         self.states = [_EpochState(wl, self.H, self.slot, self.max_batches, device, keep, mirror=self.mirror)
                        for _ in range(2 if double_buffer else 1)]
@@ -422,7 +424,7 @@ class EpochPipeline:
             self._prepare(st, [b])
         # With a cache that can hold the whole remote partition no batch has miss rows once its pulls are done: the miss pass
         # is left out (empty, it cost each of 20 gathers of 195 us another 15); with a cache the caller has put in its
-        # place it stays on this stream, since the fork to the miss stream and the join back cost more than the pass itself.
+        # place it runs on this stream, since the fork to the miss stream and the join back cost more than the pass itself.
         if self.decoupled:
             side, args = self.side, (n, st.cache, self.wl.local_store, self.wl.remote_store, self.cfg.feat_dim, self.out)
             half = self._fork_due.pop(ticket, None)
