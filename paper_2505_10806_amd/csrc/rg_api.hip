@@ -147,6 +147,7 @@ void rg_destroy(rg_ctx* ctx) {
         if (b->p) (void)hipFree(b->p);
     for (RgBuf& b : ctx->rank)
         if (b.p) (void)hipFree(b.p);
+    for (void* p : ctx->outgrown) (void)hipFree(p);
     for (auto& s : ctx->spans) { (void)hipEventDestroy(s.start); (void)hipEventDestroy(s.stop); }
     for (auto& p : ctx->free_events) { (void)hipEventDestroy(p.first); (void)hipEventDestroy(p.second); }
     if (ctx->ev_classified) (void)hipEventDestroy(ctx->ev_classified);
@@ -176,7 +177,8 @@ rg_status rg_reserve(rg_ctx* ctx, int64_t num_nodes, int64_t max_frontier, int64
     // what calls can do without, behind everything they need
     ctx->slices_denied = ~size_t(0);
     if ((st = rg_sampler_reserve_slices(ctx, num_nodes, RG_MAX_HOPS)) != RG_OK && st != RG_ERR_OOM) return st;
-    if ((st = rg_histogram_reserve(ctx)) != RG_OK && st != RG_ERR_OOM) return st;
+    ctx->bounds_denied = false;
+    if ((st = rg_histogram_reserve(ctx, num_nodes)) != RG_OK && st != RG_ERR_OOM) return st;
     return RG_OK;
 }
 

@@ -933,16 +933,30 @@ int hist_range(const rg_ctx* ctx, int64_t num_nodes) {
     return (int)rg_max64(kHistRangeMin, rg_div_up(num_nodes, places * rounds));
 }
 
-// Entries of the bounds' scratch: 8 MB, whatever the call, so that it is allocated once and a graph that uses it never loses it.
-// One batch of 8 hops on 2^30 nodes needs 1.05 Mi; a call of more batches than fit takes several launches.
+// Most entries of the bounds' scratch (8 MB; one batch of 8 hops on 2^30 nodes needs half of that): a call of more batches takes
+// several launches.
 constexpr int64_t kHistBoundsMax = 2ll << 20;
 
 }  // namespace
 
-rg_status rg_histogram_reserve(rg_ctx* ctx) {
-    const rg_status st = rg_ensure(ctx, ctx->hist_bounds, (size_t)kHistBoundsMax * 4);
+// Room for `entries` bounds.  An outgrown buffer stays allocated: a histogram needed no scratch once, and a graph that holds this
+// one must survive any later call.  A buffer has at least twice its predecessor's size, up to the 8 MB: less than 16 MB in all.
+static rg_status hist_bounds_grow(rg_ctx* ctx, int64_t entries) {
+    RgBuf& buf = ctx->hist_bounds;
+    if (buf.bytes >= (size_t)entries * 4 || ctx->bounds_denied) return RG_OK;
+    RgBuf larger;
+    const rg_status st = rg_ensure(ctx, larger, (size_t)rg_max64(entries * 4, rg_min64((int64_t)buf.bytes * 2, kHistBoundsMax * 4)));
     ctx->bounds_denied = st == RG_ERR_OOM;
-    return st;
+    if (st != RG_OK) return st;
+    if (buf.p) ctx->outgrown.push_back(buf.p);
+    buf = larger;
+    return RG_OK;
+}
+
+rg_status rg_histogram_reserve(rg_ctx* ctx, int64_t num_nodes) {
+    if (num_nodes <= 0) return RG_OK;
+    const int64_t per_batch = RG_MAX_HOPS * (rg_div_up(num_nodes, hist_range(ctx, num_nodes)) + 1);
+    return hist_bounds_grow(ctx, per_batch * rg_max64(1, rg_min64(128, kHistBoundsMax / per_batch)));
 }
 
 extern "C" {
@@ -978,10 +992,12 @@ rg_status rg_access_histogram_epoch(rg_ctx* ctx, const int32_t* nodes, int64_t b
     hipStream_t s = (hipStream_t)stream;
     const int range = hist_range(ctx, num_nodes);
     const int ranges = (int)rg_div_up(num_nodes, range);
-    // without the bounds' scratch, in a captured call or for want of memory, the counting kernel searches for itself
-    if (!ctx->hist_bounds.p && !ctx->bounds_denied && !rg_capturing(s)) (void)rg_histogram_reserve(ctx);
-    // batches per launch: the bounds of their runs fit the scratch, and a grid's second dimension
+    // batches per launch: the bounds of their runs fit the scratch, and a grid's second dimension.  (From 128 batches per launch on
+    // a call takes more launches rather than more scratch, so that rg_reserve can make room for any.)  Without scratch, in a captured
+    // call or for want of memory, the counting kernel searches for itself.
     const int64_t per_batch = (int64_t)num_hops * (ranges + 1);
+    const int64_t most = rg_min64(num_batches, rg_max64(1, kHistBoundsMax / per_batch));
+    if ((int64_t)(ctx->hist_bounds.bytes / 4) < per_batch * rg_min64(most, 128) && !rg_capturing(s)) (void)hist_bounds_grow(ctx, per_batch * most);
     const int fit = (int)rg_min64((int64_t)(ctx->hist_bounds.bytes / 4) / per_batch, 65535 / num_hops);
     // The counting kernel also searches where that is faster.  A few bounds are no work for a launch of their own: up to 1 Mi nodes
     // and 8448 bounds 12.0-12.9 us against 14.4-15.2, at 12,312 bounds 16-18 / 15, on 2.4 M nodes 13-18 / 15 from 1539 bounds on.

@@ -59,6 +59,7 @@ struct rg_ctx {
     RgBuf sched_buckets; // int32: pairs per bucket, scatter cursors, bucket starts
     bool bounds_denied = false;   // hist_bounds could not be had (rg_reserve tries again)
     RgBuf hist_bounds;  // int32: where the id ranges of the epoch histogram begin in the runs of some batches
+    std::vector<void*> outgrown;   // its predecessors, which graphs may hold (rg_destroy frees them)
     // top-K scratch
     RgBuf topk_ctl;     // TopkCtl
     RgBuf topk_blk;     // int32[2 * nblocks]
@@ -93,14 +94,15 @@ rg_status rg_set_error(rg_ctx* ctx, rg_status code, const char* fmt, ...);
 rg_status rg_ensure(rg_ctx* ctx, RgBuf& buf, size_t bytes, bool zero_new = false);
 // RG_OK if kernels on the ctx's device may dereference p (device, managed or pinned/registered host memory).
 rg_status rg_check_device_readable(rg_ctx* ctx, const void* p, const char* what);
-// True while s records a graph: nothing may be allocated then.
+// True while s records a graph: nothing may be allocated then.  (The NULL stream cannot; the question costs 0.3 us.)
 static inline bool rg_capturing(hipStream_t s) {
+    if (!s) return false;
     hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
     if (hipStreamIsCapturing(s, &status) != hipSuccess) { (void)hipGetLastError(); return false; }
     return status == hipStreamCaptureStatusActive;
 }
-// Scratch with which no epoch histogram allocates anything; the same.
-rg_status rg_histogram_reserve(rg_ctx* ctx);
+// Scratch with which no epoch histogram on num_nodes nodes allocates anything; the same.
+rg_status rg_histogram_reserve(rg_ctx* ctx, int64_t num_nodes);
 // Makes every gather ticket hold at least `rows` rows (a reallocation invalidates prepared tickets).
 rg_status rg_gather_reserve(rg_ctx* ctx, int64_t rows);
 // Sizes the sampler scratch for `group` batches side by side on a graph of num_nodes nodes with cumulative

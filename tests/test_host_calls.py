@@ -65,23 +65,39 @@ for call in calls + calls:
 
 
 def test_histogram_scratch_outlives_larger_calls():
-    """A graph that holds the address of the histogram's scratch is safe whatever is counted later: there is one size of it."""
+    """A graph that holds the address of the histogram's scratch is safe whatever is counted later: outgrown scratch stays."""
     host_calls.run("""
 c = context()
-assert histogram(c, 100_000, 10, 2) == OK
+assert histogram(c, 100_000, 100, 2) == OK
 log()
 rt.begin_capture(0x51)
-assert histogram(c, 100_000, 10, 2, stream=0x51) == OK
+assert histogram(c, 100_000, 100, 2, stream=0x51) == OK
 rt.end_capture()
-for n, batches, hops in ((100_000, 64, 2), (100_000, 5000, 3), (10_000_000, 245, 3), (1 << 30, 3, 8)):
-    assert histogram(c, n, batches, hops) == OK and not log("free") and not log("malloc"), n
+for n, batches, hops in ((100_000, 300, 2), (100_000, 5000, 3), (10_000_000, 245, 3), (1 << 30, 3, 8), (1 << 30, 300, 8)):
+    assert histogram(c, n, batches, hops) == OK and not log("free"), n
 assert lib.rg_reserve(c, i64(1 << 20), i64(100), i64(100), i32(2)) == OK
 assert not log("free")
+assert rt.memory_held() < 200 << 20
+lib.rg_destroy(c)
+assert rt.memory_held() == 0
+c = context()                                             # rg_reserve makes room for any histogram of such a graph
+assert lib.rg_reserve(c, i64(3_000_000), i64(100), i64(100), i32(1)) == OK
+log()
+for batches, hops in ((5, 8), (64, 8), (2000, 8), (2000, 1)):
+    assert histogram(c, 3_000_000, batches, hops) == OK and not log("malloc"), batches
 d = context()                                             # none there, and none to be had while the graph is recorded
+log()
 rt.begin_capture(0x51)
 assert histogram(d, 10_000_000, 245, 3, stream=0x51) == OK
 rt.end_capture()
 assert [k.split("<")[0] for k in kernels()] == ["k_histogram_seeds", "k_histogram_runs"]
+e = context()                                             # some there: as many batches to a launch as fit, if that pays
+assert histogram(e, 10_000_000, 60, 3) == OK
+log()
+rt.begin_capture(0x51)
+assert histogram(e, 10_000_000, 180, 3, stream=0x51) == OK
+rt.end_capture()
+assert [k.split("<")[0] for k in kernels()] == ["k_histogram_seeds"] + 3 * ["k_hist_bounds", "k_histogram_runs"]
 """)
 
 
@@ -118,7 +134,7 @@ for short in (1, RANK // 2, RANK, RANK + MARKS // 2):     # the bounds, the rank
     c = context()
     assert reserve(c) == OK, lib.rg_last_error(c)
     sliced = short < RANK // 2
-    assert rt.memory_held() <= total - (0 if sliced else RANK + MARKS) - (8 << 20 if sliced else 0), (short, rt.memory_held())
+    assert rt.memory_held() < total - (0 if sliced else RANK + MARKS), (short, rt.memory_held())
     rt.limit_memory(rt.memory_held())
     log()
     for _ in range(2):
