@@ -6,7 +6,7 @@ namespace {
 
 // agg[i] = (1/m_i) * sum over the block's edges e of row i, in edge order, of feat[nbr_local[e]].
 // A wavefront is split into groups of L lanes per destination row; each lane owns chunk c0 (+ L, + 2L, ...) of the
-// row and accumulates it in registers, E edges at a time so that E independent row loads are in flight.
+// row and accumulates it in registers, E edges at a time so that E independent row loads are in flight.  Up to few_rows rows: L = 64.
 // Bound by the source rows' traffic behind L2 (270 k destinations of 5 edges on a power-law block, 256 floats: 1.31 GB of rows
 // asked for, 27 % of the reads hit L2, so 0.96 GB from behind it, and 0.28 written in 196 us; 373 k distinct rows would be 0.38 GB).  E = 8 takes fan-outs of 5 in one step (E = 4: 206).
 // Cutting the columns into one part per XCD, so that every L2 holds its part of more rows, was slower (8 parts 228, 4 parts 205).
@@ -14,10 +14,12 @@ template <int VEC, int E>
 __global__ void __launch_bounds__(256) k_mean_aggregate(const int32_t* __restrict__ indptr, const int32_t* __restrict__ nbr_local,
                                                         int64_t n_dst, const int32_t* __restrict__ n_dst_dev,
                                                         const float* __restrict__ feat, int64_t feat_stride,
-                                                        float* __restrict__ agg, int64_t agg_stride, int cpr, int log2L, int tail) {
+                                                        float* __restrict__ agg, int64_t agg_stride, int cpr, int log2L, int tail,
+                                                        int64_t few_rows) {
     typedef typename RgVec<VEC>::type V;
     int64_t n_act = n_dst;
     if (n_dst_dev) { const int64_t d = *n_dst_dev; n_act = d < n_dst ? d : n_dst; }
+    if (n_act <= few_rows) log2L = 6;
     const int lane = rg_lane();
     const int L = 1 << log2L;
     const int R = RG_WAVE >> log2L;
@@ -58,6 +60,8 @@ __global__ void __launch_bounds__(256) k_mean_aggregate(const int32_t* __restric
     }
 }
 
+constexpr int64_t kFewRows = 8192;     // rows up to which a wavefront has one to itself (see rg_mean_aggregate)
+
 }  // namespace
 
 extern "C" {
@@ -76,27 +80,30 @@ rg_status rg_mean_aggregate(rg_ctx* ctx, const int32_t* indptr, const int32_t* n
     const int64_t strides[2] = {feat_stride, agg_stride};
     const int vec = rg_pick_vec(dim, ptrs, 2, strides, 2);
     RgRowShape shp = rg_row_shape(dim, vec);
-    // Rows longer than a wavefront whose last step would idle most lanes: a group of 32 or 16 lanes instead if that takes a
-    // quarter fewer lane steps (80 chunks, 25 edges: 64 lanes 119 us, 32 lanes 94, 16 lanes 77; 151 chunks, 160 / 192 steps: all 74;
-    // 301 chunks of 8 bytes, 304 / 320: 97 with 16 lanes, 84 with 64).
-    if (shp.cpr > RG_WAVE) {
-        int64_t best = rg_div_up(shp.cpr, RG_WAVE) * RG_WAVE * 4 / 5 + 1;
-        for (int l = 5; l >= 4; --l) {
-            const int64_t steps = rg_div_up(shp.cpr, 1 << l) << l;
-            if (steps < best) { best = steps; shp.log2L = l; }
-        }
+    // Rows longer than a wavefront whose last step would idle most lanes: groups of 32 lanes instead if that takes a quarter fewer
+    // lane steps and three lanes in four work, of 16 if none of theirs is idle (15 edges; 33 k rows of 80 chunks: 64 lanes 98 us, 32 lanes
+    // 90, 16 lanes 82, of 76 chunks 101 / 97 / 98; 100 k rows of 65 chunks 298 / 311 / 354; 151 chunks, 160 / 192 steps: all 74; 301 chunks
+    // of 8 bytes, 304 / 320: 97 with 16 lanes, 84 with 64).  A row then takes its group two to five passes over its edges one after the
+    // other, so up to kFewRows rows, which leave wavefronts idle, keep whole ones (80 chunks, 15 edges: 256 rows 10 / 11 / 15 us, 2048 14 / 17 /
+    // 28, 8192 26 / 26 / 34, 10,000 38 / 29 / 36, 16,384 50 / 43 / 43).
+    int64_t few_rows = 0;
+    if (shp.cpr > RG_WAVE && n_dst > kFewRows) {
+        const int64_t whole = rg_div_up(shp.cpr, RG_WAVE) * RG_WAVE, half = rg_div_up(shp.cpr, 32) * 32;
+        if (half * 5 <= whole * 4 && shp.cpr * 4 >= half * 3) shp.log2L = 5;
+        if (shp.cpr * 5 <= whole * 4 && shp.cpr % 16 == 0 && shp.cpr < half) shp.log2L = 4;
+        if (shp.log2L < 6) few_rows = kFewRows;
     }
     const int rows_per_block = 4 * (RG_WAVE >> shp.log2L);
     // 32 workgroups per compute unit; with 16 / 32 / 64 of them the 270 k destinations above take 195 / 195 / 197 us, 100 k of 10 edges
     // and 256 floats 118 / 117 / 115, 200 k of 5 and 128 84 / 82 / 80, 200 k of 1 and 256 60 / 56 / 55.
-    const int grid = (int)rg_max64(1, rg_min64(rg_div_up(n_dst, rows_per_block), (int64_t)ctx->num_cus * 32));
+    const int grid = (int)rg_max64(few_rows / 4, rg_max64(1, rg_min64(rg_div_up(n_dst, rows_per_block), (int64_t)ctx->num_cus * 32)));
     const int tok = rg_prof_begin(ctx, RG_K_AGGREGATE, s);
     if (vec == 4)
-        k_mean_aggregate<4, 8><<<grid, 256, 0, s>>>(indptr, nbr_local, n_dst, n_dst_dev, feat, feat_stride, agg, agg_stride, shp.cpr, shp.log2L, shp.tail);
+        k_mean_aggregate<4, 8><<<grid, 256, 0, s>>>(indptr, nbr_local, n_dst, n_dst_dev, feat, feat_stride, agg, agg_stride, shp.cpr, shp.log2L, shp.tail, few_rows);
     else if (vec == 2)
-        k_mean_aggregate<2, 8><<<grid, 256, 0, s>>>(indptr, nbr_local, n_dst, n_dst_dev, feat, feat_stride, agg, agg_stride, shp.cpr, shp.log2L, shp.tail);
+        k_mean_aggregate<2, 8><<<grid, 256, 0, s>>>(indptr, nbr_local, n_dst, n_dst_dev, feat, feat_stride, agg, agg_stride, shp.cpr, shp.log2L, shp.tail, few_rows);
     else
-        k_mean_aggregate<1, 8><<<grid, 256, 0, s>>>(indptr, nbr_local, n_dst, n_dst_dev, feat, feat_stride, agg, agg_stride, shp.cpr, shp.log2L, shp.tail);
+        k_mean_aggregate<1, 8><<<grid, 256, 0, s>>>(indptr, nbr_local, n_dst, n_dst_dev, feat, feat_stride, agg, agg_stride, shp.cpr, shp.log2L, shp.tail, few_rows);
     rg_prof_end(ctx, tok, s);
     RG_LAUNCH_CHECK(ctx, "k_mean_aggregate");
     return RG_OK;

@@ -413,6 +413,29 @@ def test_mean_aggregate_lane_groups(B, ctx, dim, stride):
     assert torch.isnan(agg[:, dim:]).all()
 
 
+# More than 8192 rows: groups of 64, 32 and 16 lanes (65, 76, 96 and 80, 144 chunks), and whole wavefronts again where the device counts fewer.
+@pytest.mark.parametrize("dim", [260, 302, 384, 320, 576])
+def test_mean_aggregate_many_rows(B, ctx, dim):
+    rng = np.random.default_rng(dim)
+    n, stride = 8203, -(-dim // 4) * 4
+    m = rng.integers(0, 10, n)
+    indptr = np.concatenate([[0], np.cumsum(m)]).astype(np.int32)
+    nbr = rng.integers(0, 900, indptr[-1]).astype(np.int32)
+    feat = torch.zeros(900, stride, device=DEV)
+    feat[:, :dim] = torch.from_numpy(rng.standard_normal((900, dim)).astype(np.float32)).to(DEV)
+    x = feat[:, :dim].cpu().numpy()
+    want = np.zeros((n, dim), dtype=np.float32)
+    for e in range(9):                                  # the same fp32 sums in edge order, then one division
+        rows = np.flatnonzero(m > e)
+        want[rows] += x[nbr[indptr[rows] + e]]
+    want[m > 0] /= m[m > 0, None].astype(np.float32)
+    for count in (None, 8203, 8193, 8192, 1):
+        agg = torch.full((n, stride), -7.0, device=DEV)
+        ctx.mean_aggregate(_i32(indptr), _i32(nbr), n, feat, dim, agg, n_dst_dev=None if count is None else _i32([count]))
+        got, k = agg.cpu().numpy(), n if count is None else count
+        assert np.array_equal(got[:k, :dim], want[:k]) and np.all(got[k:] == -7.0)
+
+
 # One launch up to 64 Ki rows of 24 MiB on one stream, 96 Ki rows of 32 MiB on two (8-64 rows per workgroup), lookups of 1024 rows per workgroup; counters that have to be zero
 # again for the next call, whichever kernel makes it.
 @pytest.mark.parametrize("rows,dim,stride", [(1, 64, 64), (7, 602, 604), (513, 3, 3), (4097, 37, 40), (16_384, 512, 512), (16_385, 512, 512),

@@ -268,6 +268,17 @@ for dst, grid in ((1, 1), (4 * 8192, 8192), (200_000, 8192)):
 """)
 
 
+# Rows of 80 chunks take 16 lanes each, of 76 chunks 32, of 65 a wavefront; up to 8192 rows all do, whose wavefronts have their workgroups.
+@pytest.mark.parametrize("dim,dst,grid", [(320, 2, 1), (320, 1000, 250), (320, 8192, 2048), (320, 8193, 2048), (320, 40_000, 2500),
+                                          (304, 8192, 2048), (304, 40_000, 5000), (260, 20_000, 5000)])
+def test_mean_aggregate_lanes_per_row(dim, dst, grid):
+    host_calls.run(f"""
+c = context()
+assert lib.rg_mean_aggregate(c, p(address()), p(address()), i64({dst}), None, p(address()), i64({dim}), i32({dim}), p(address()), i64({dim}), None) == OK
+assert [int(x.split()[2]) for x in log("launch k_mean_aggregate")] == [{grid}]
+""")
+
+
 def test_selection_grid():
     """The counts' histogram: one workgroup per compute unit, two above 8 Mi nodes."""
     host_calls.run("""
