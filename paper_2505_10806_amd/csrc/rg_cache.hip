@@ -313,31 +313,49 @@ __global__ void k_store_caps(int64_t* __restrict__ dst, const CapChunk chunk, in
 __global__ void __launch_bounds__(256) k_hit_curve_low(const TopkCtl* __restrict__ ctl, const int64_t* __restrict__ capacities,
                                                        int num_capacities, unsigned long long* __restrict__ hits,
                                                        unsigned long long* __restrict__ total_out, uint32_t* __restrict__ resolved_flag) {
+    constexpr int PER = kLowBins / 256;                      // thread t owns bins kLowBins-1-PER*t downwards
     __shared__ uint32_t cnt_above[kLowBins];                 // candidates with a larger clamped count
     __shared__ unsigned long long sum_above[kLowBins];       // and the sum of their counts
-    __shared__ unsigned long long grand_s;
-    if (threadIdx.x == 0) {
-        uint32_t cnt = 0u;
-        unsigned long long sum = 0ull;
-        for (int b = kLowBins - 1; b >= 1; --b) {
-            cnt_above[b] = cnt;
-            sum_above[b] = sum;
-            const uint32_t hb = ctl->low[b];
-            cnt += hb;
-            sum += b == kLowBins - 1 ? ctl->ovf_sum : (unsigned long long)hb * (unsigned long long)b;
-        }
-        cnt_above[0] = cnt;                                  // = number of candidates (bin 0 holds none)
-        sum_above[0] = sum;
-        grand_s = sum;
-        if (total_out) *total_out = sum;
+    __shared__ unsigned long long part[256];
+    __shared__ int smem[256 / RG_WAVE + 1];
+    const int top = kLowBins - 1 - PER * (int)threadIdx.x;
+    uint32_t h[PER];
+    unsigned long long w[PER], sum = 0ull;
+    int cnt = 0, total;
+#pragma unroll
+    for (int j = 0; j < PER; ++j) {
+        const int bin = top - j;                             // bin 0 is empty
+        h[j] = ctl->low[bin];
+        w[j] = bin == kLowBins - 1 ? ctl->ovf_sum : (unsigned long long)h[j] * (unsigned long long)bin;
+        cnt += (int)h[j];
+        sum += w[j];
+    }
+    uint32_t above = (uint32_t)rg_block_excl_scan<256 / RG_WAVE>(cnt, smem, &total);
+    part[threadIdx.x] = sum;
+    for (int off = 1; off < 256; off <<= 1) {
+        __syncthreads();
+        const unsigned long long x = (int)threadIdx.x >= off ? part[threadIdx.x - off] : 0ull;
+        __syncthreads();
+        part[threadIdx.x] += x;
     }
     __syncthreads();
-    const uint32_t n_cand = cnt_above[0];
+    const unsigned long long grand = part[255];
+    sum = part[threadIdx.x] - sum;
+#pragma unroll
+    for (int j = 0; j < PER; ++j) {
+        cnt_above[top - j] = above;
+        sum_above[top - j] = sum;
+        above += h[j];
+        sum += w[j];
+    }
+    if (threadIdx.x == 0 && total_out) *total_out = grand;
+    __syncthreads();
+    const uint32_t n_cand = (uint32_t)total;
     for (int j = threadIdx.x; j < num_capacities; j += 256) {
         const uint64_t cap = (uint64_t)capacities[j];
         const uint32_t k = cap < (uint64_t)n_cand ? (uint32_t)cap : n_cand;
         if (k == 0u) { hits[j] = 0ull; resolved_flag[j] = 1u; continue; }
-        if (k == n_cand) { hits[j] = grand_s; resolved_flag[j] = 1u; continue; }
+        if (k == n_cand) { hits[j] = grand; resolved_flag[j] = 1u; continue; }
         // the threshold bin T holds the k-th best candidate: cnt_above[T] < k <= cnt_above[T - 1].  cnt_above falls as
         // the bin index rises and cnt_above[kLowBins - 1] = 0 < k, so T is the smallest bin with cnt_above[T] < k.
         int lo = 1, hi = kLowBins - 1;

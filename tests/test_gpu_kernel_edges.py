@@ -249,6 +249,19 @@ def test_epoch_histogram_range_edges(B, ctx, n, batches, hops, skew):
     assert np.array_equal(counts.cpu().numpy().view(np.uint32), 2 * want)
 
 
+# Every capacity of a small curve against sorted counts: bins at both ends of a thread's share, the clamped bin and sums above 2^32.
+@pytest.mark.parametrize("values", [[1], [7, 8, 9], [2040, 2046, 2047, 2048], [1, 15, 16, 2039, 2040, 3_000_000_000]])
+def test_hit_curve_bins(B, ctx, values):
+    log(f"[hit curve bins] {values}")
+    n = 37
+    counts = np.random.default_rng(len(values)).choice(np.array(values + [0], dtype=np.uint32), n)
+    home = np.where(np.arange(n) % 5 == 0, np.arange(n), (2 << 30) + np.arange(n)).astype(np.uint32).view(np.int32)
+    best = np.sort(np.where(np.arange(n) % 5 == 0, 0, counts).astype(np.uint64))[::-1]
+    caps = list(range(n + 2))
+    hits, total = ctx.cache_hit_curve(torch.as_tensor(counts.view(np.int32), device=DEV), torch.as_tensor(home, device=DEV), caps)
+    assert hits.tolist() == [int(best[:k].sum()) for k in caps] and int(total) == int(best.sum())
+
+
 def _captured(call):
     """The call recorded into a graph on a side stream."""
     graph, side = torch.cuda.CUDAGraph(), torch.cuda.Stream()
