@@ -2,6 +2,8 @@
 // against cache size (Section V), and VectorPull (Alg. 1 line 4) in its two forms: one bulk pull, or pulls by
 // first use ahead of the gathers (the prefetcher of Section III: with a per-batch claim pass or from a
 // per-epoch plan).
+#include <math.h>
+
 #include "rg_rowcopy.h"
 
 namespace {
@@ -90,7 +92,7 @@ __global__ void __launch_bounds__(1024) k_histogram_runs(const int32_t* __restri
         if (FIRST) firstb[j] = 0xFFFFFFFFu;
     }
     const int num_runs = num_batches * num_hops;
-    const int wave = threadIdx.x >> 6, lane = rg_lane(), nwaves = blockDim.x >> 6;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = rg_lane(), nwaves = blockDim.x >> 6;
     for (int tile = 0; tile < num_runs; tile += kHistRunTile) {
         __syncthreads();                                  // priv zeroed / previous tile's segments consumed
         const int r = tile + threadIdx.x;
@@ -116,16 +118,26 @@ __global__ void __launch_bounds__(1024) k_histogram_runs(const int32_t* __restri
         __syncthreads();
         const int in_tile = num_runs - tile < kHistRunTile ? num_runs - tile : kHistRunTile;
         for (int q = wave; q < in_tile; q += nwaves) {                  // one wavefront per run segment
+            const int lo = __builtin_amdgcn_readfirstlane(seg_lo[q]), hi = __builtin_amdgcn_readfirstlane(seg_hi[q]);
+            if (lo >= hi) continue;
             const int b = (tile + q) / num_hops;
             const int32_t* base = nodes + (int64_t)b * batch_stride;
-            const int hi = seg_hi[q];
-            for (int e0 = seg_lo[q] + lane; e0 < hi; e0 += RG_WAVE * U) {
+            int e0 = lo + lane;
+            if (hi - lo <= RG_WAVE) {                                   // short segments, of which a call may have mostly
+                const uint32_t off = e0 < hi ? (uint32_t)(base[e0] - (int)v0) : 0xFFFFFFFFu;
+                if (off < (uint32_t)range) {                            // always true inside an ascending segment
+                    atomicAdd(&priv[off], 1u);
+                    if (FIRST) atomicMin(&firstb[off], (uint32_t)(b0 + b));
+                }
+                continue;
+            }
+            for (; e0 < hi; e0 += RG_WAVE * U) {
                 uint32_t off[U];
 #pragma unroll
                 for (int u = 0; u < U; ++u) off[u] = e0 + RG_WAVE * u < hi ? (uint32_t)(base[e0 + RG_WAVE * u] - (int)v0) : 0xFFFFFFFFu;
 #pragma unroll
                 for (int u = 0; u < U; ++u)
-                    if (off[u] < (uint32_t)range) {                     // always true inside an ascending segment
+                    if (off[u] < (uint32_t)range) {
                         atomicAdd(&priv[off[u]], 1u);
                         if (FIRST) atomicMin(&firstb[off[u]], (uint32_t)(b0 + b));
                     }
@@ -944,11 +956,15 @@ rg_status launch_list_copy(rg_ctx* ctx, const int32_t* list, const uint32_t* pct
     return RG_OK;
 }
 
-// Id ranges of the epoch histogram: whole rounds of two workgroups per compute unit.
-int hist_range(const rg_ctx* ctx, int64_t num_nodes) {
+// Id ranges of the epoch histogram: whole rounds of two workgroups per compute unit, but no more ranges than runs of up to run_len
+// entries pay for.  A range costs every run a search and a segment (50 ns per thousand), and saves its share of the LDS atomics: least
+// in sum near sqrt(4.4 run_len) ranges.
+int hist_range(const rg_ctx* ctx, int64_t num_nodes, int64_t run_len) {
     const int64_t places = 2ll * ctx->num_cus;
     const int64_t rounds = rg_max64(1, rg_div_up(num_nodes, places * kHistRangeMax));
-    return (int)rg_max64(kHistRangeMin, rg_div_up(num_nodes, places * rounds));
+    const int64_t even = rg_max64(kHistRangeMin, rg_div_up(num_nodes, places * rounds));
+    const int64_t worth = rg_max64(1, (int64_t)sqrt(4.4 * (double)run_len));
+    return (int)rg_min64(kHistRangeMax, rg_max64(even, rg_div_up(num_nodes, worth)));
 }
 
 // Most entries of the bounds' scratch (8 MB; one batch of 8 hops on 2^30 nodes needs half of that): a call of more batches takes
@@ -973,7 +989,8 @@ static rg_status hist_bounds_grow(rg_ctx* ctx, int64_t entries) {
 
 rg_status rg_histogram_reserve(rg_ctx* ctx, int64_t num_nodes) {
     if (num_nodes <= 0) return RG_OK;
-    const int64_t per_batch = RG_MAX_HOPS * (rg_div_up(num_nodes, hist_range(ctx, num_nodes)) + 1);
+    ctx->hist_reserved = true;
+    const int64_t per_batch = RG_MAX_HOPS * (rg_div_up(num_nodes, hist_range(ctx, num_nodes, kHistBoundsMax)) + 1);
     return hist_bounds_grow(ctx, per_batch * rg_max64(1, rg_min64(128, kHistBoundsMax / per_batch)));
 }
 
@@ -1008,22 +1025,29 @@ rg_status rg_access_histogram_epoch(rg_ctx* ctx, const int32_t* nodes, int64_t b
     RG_REQUIRE(ctx, nodes && tier_off && counts, "rg_access_histogram_epoch: null pointer");
     RG_HIP(ctx, hipSetDevice(ctx->device));
     hipStream_t s = (hipStream_t)stream;
-    const int range = hist_range(ctx, num_nodes);
+    const int64_t run_len = batch_stride / num_hops;
+    const int range = hist_range(ctx, num_nodes, run_len);
     const int ranges = (int)rg_div_up(num_nodes, range);
-    // batches per launch: the bounds of their runs fit the scratch, and a grid's second dimension.  (From 128 batches per launch on
-    // a call takes more launches rather than more scratch, so that rg_reserve can make room for any.)  Without scratch, in a captured
-    // call or for want of memory, the counting kernel searches for itself.
+    // batches per launch: the bounds of their runs fit the scratch, and a grid's second dimension.  (After rg_reserve, which leaves
+    // room for 128 batches or more, a call takes more launches rather than more scratch.)  Without scratch, in a captured call or for
+    // want of memory, the counting kernel searches for itself.
     const int64_t per_batch = (int64_t)num_hops * (ranges + 1);
     const int64_t most = rg_min64(num_batches, rg_max64(1, kHistBoundsMax / per_batch));
-    if ((int64_t)(ctx->hist_bounds.bytes / 4) < per_batch * rg_min64(most, 128) && !rg_capturing(s)) (void)hist_bounds_grow(ctx, per_batch * most);
-    const int fit = (int)rg_min64((int64_t)(ctx->hist_bounds.bytes / 4) / per_batch, 65535 / num_hops);
-    // The counting kernel also searches where that is faster.  A few bounds are no work for a launch of their own: up to 1 Mi nodes
-    // and 8448 bounds 12.0-12.9 us against 14.4-15.2, at 12,312 bounds 16-18 / 15, on 2.4 M nodes 13-18 / 15 from 1539 bounds on.
+    // The counting kernel also searches where that is faster, for two reasons.  The launch of its own that the bounds take costs 3 us, more
+    // than few or short runs are worth: the chains of probes weigh runs x ranges x log2(entries)^4 (1 M nodes, 25 runs of 30,000
+    // entries, 4.45e8: 11.4-11.8 us against 14-15, 60 of them 15.8 / 15.5; 750 of 300, 4.3e8, 29 / 26; 2.4 M nodes, 60 of 3000, 3.1e8:
+    // 12.5 / 14.7, 8 of 300,000, 4.5e8, 19 / 15).  Above a round of the device the probes of every round add up, so only very short runs are
+    // searched (10 M nodes, 180 runs of 30, 1.4e8: 15 / 18, 360 of them 25 / 23; 24 of 300: 16 / 15, one of 30,000: 20 / 14).
+    const double steps = log2((double)run_len + 2.0);
+    const double weight = (double)num_batches * (double)per_batch * steps * steps * steps * steps;
+    const bool few = num_nodes <= (1 << 22) ? weight <= 4.46e8 : run_len <= 64 && weight <= 2e8;
     // And a launch of few batches does little besides clearing and adding its ranges: 245 batches on 200 M nodes, 28 to a
     // launch, 2.2-3.5 ms in one launch that searches against 2.7-5.0 ms (64 batches 0.7-1.2 / 0.75-1.6, but 32 batches in two launches
     // 0.52-0.56 / 0.42-0.47); on 100 M nodes, 56 to a launch, 1.2-2.0 ms either way.
-    const bool few = num_nodes <= (1 << 20) && num_batches * per_batch <= 8448;
-    const bool search = fit == 0 || few || (fit < 48 && num_batches > 2 * fit);
+    const int64_t wanted = per_batch * (ctx->hist_reserved ? rg_min64(most, 128) : most);
+    if (!few && (int64_t)(ctx->hist_bounds.bytes / 4) < wanted && !rg_capturing(s)) (void)hist_bounds_grow(ctx, wanted);
+    const int fit = (int)rg_min64((int64_t)(ctx->hist_bounds.bytes / 4) / per_batch, 65535 / num_hops);
+    const bool search = few || fit == 0 || (fit < 48 && num_batches > 2 * fit);
     const int step = search ? num_batches : fit;
     int32_t* bounds = search ? nullptr : (int32_t*)ctx->hist_bounds.p;
     const int tok = rg_prof_begin(ctx, RG_K_HISTOGRAM, s);

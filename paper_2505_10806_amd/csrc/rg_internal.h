@@ -58,6 +58,7 @@ struct rg_ctx {
     RgBuf sched_ids;    // int32[n]
     RgBuf sched_buckets; // int32: pairs per bucket, scatter cursors, bucket starts
     bool bounds_denied = false;   // hist_bounds could not be had (rg_reserve tries again)
+    bool hist_reserved = false;   // rg_reserve has sized hist_bounds: calls take it as it is where it holds 128 batches
     RgBuf hist_bounds;  // int32: where the id ranges of the epoch histogram begin in the runs of some batches
     std::vector<void*> outgrown;   // its predecessors, which graphs may hold (rg_destroy frees them)
     // top-K scratch

@@ -221,7 +221,7 @@ def test_ordered_plan_chunk_edges(B, ctx, slots, pattern):
 
 
 # Ranges of 512 ids at least, two workgroups per compute unit, 2 Mi bounds per launch; runs whose ids are far from proportional.
-@pytest.mark.parametrize("n,batches,hops", [(511, 3, 1), (513, 3, 2), (262_145, 9, 2), (300_000, 5000, 1), (5_000_011, 2, 3)])
+@pytest.mark.parametrize("n,batches,hops", [(511, 3, 1), (513, 3, 2), (262_145, 9, 2), (300_000, 5000, 1), (300_000, 12_000, 1), (5_000_011, 2, 3)])
 @pytest.mark.parametrize("skew", [1, 4])
 def test_epoch_histogram_range_edges(B, ctx, n, batches, hops, skew):
     log(f"[histogram ranges] N={n} batches={batches} hops={hops} skew={skew}")
@@ -247,6 +247,25 @@ def test_epoch_histogram_range_edges(B, ctx, n, batches, hops, skew):
     assert np.array_equal(got_first.cpu().numpy().view(np.uint32), first)
     ctx.access_histogram_epoch(_i32(arena), _i32(tier_offs), batches, hops, most, counts)
     assert np.array_equal(counts.cpu().numpy().view(np.uint32), 2 * want)
+
+
+# Segments of one wavefront's lanes, one more, one round of loads and one more, with and without bounds found first.
+@pytest.mark.parametrize("batches", [1, 10_000])
+def test_epoch_histogram_segment_lengths(B, ctx, batches):
+    log(f"[histogram segments] batches={batches}")
+    lengths = [0, 1, 63, 64, 65, 255, 256, 257, 400]
+    runs = [np.sort(np.random.default_rng(k).permutation(400)[:k]) for k in lengths]
+    arena, tier_offs = np.zeros((batches, 1370), dtype=np.int32), np.zeros((batches, 10), dtype=np.int32)
+    arena[:, :1361] = np.concatenate(runs)
+    tier_offs[:, 2:] = np.cumsum(lengths[1:])
+    want = np.bincount(arena[0, :1361], minlength=1024).astype(np.uint32)
+    first = np.where(want > 0, 0, 0xFFFFFFFF).astype(np.uint32)
+    counts, got = torch.zeros(1024, dtype=torch.int32, device=DEV), torch.full((1024,), -1, dtype=torch.int32, device=DEV)
+    ctx.access_histogram_epoch(_i32(arena), _i32(tier_offs), batches, 8, 0, counts, first_batch=got)
+    assert np.array_equal(counts.cpu().numpy().view(np.uint32), batches * want)
+    assert np.array_equal(got.cpu().numpy().view(np.uint32), first)
+    ctx.access_histogram_epoch(_i32(arena), _i32(tier_offs), batches, 8, 0, counts)
+    assert np.array_equal(counts.cpu().numpy().view(np.uint32), 2 * batches * want)
 
 
 # Every capacity of a small curve against sorted counts: bins at both ends of a thread's share, the clamped bin and sums above 2^32.

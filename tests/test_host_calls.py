@@ -98,18 +98,36 @@ rt.begin_capture(0x51)
 assert histogram(e, 10_000_000, 180, 3, stream=0x51) == OK
 rt.end_capture()
 assert [k.split("<")[0] for k in kernels()] == ["k_histogram_seeds"] + 3 * ["k_hist_bounds", "k_histogram_runs"]
+f = context()                                             # room for half of the batches: more room, where none was reserved
+assert histogram(f, 300_000, 130, 1) == OK
+log()
+assert histogram(f, 300_000, 260, 1) == OK
+assert [k.split("<")[0] for k in kernels()] == ["k_histogram_seeds", "k_hist_bounds", "k_histogram_runs"]
 """)
 
 
-# Few bounds; the most batches that one launch's scratch holds (28 on 200 M nodes), two launches, more than two.
-@pytest.mark.parametrize("n,batches,hops,search,launches", [
-    (1000, 5, 2, True, 1), (1 << 20, 5, 3, True, 1), (1 << 20, 6, 3, False, 1), ((1 << 20) + 1, 1, 1, False, 1),
-    (10_000_000, 454, 3, False, 1), (10_000_000, 2000, 3, False, 5), (200_000_000, 28, 3, False, 1), (200_000_000, 56, 3, False, 2),
-    (200_000_000, 57, 3, True, 1), (1 << 30, 1, 8, False, 1), (1 << 30, 245, 8, True, 1)])
-def test_histogram_searches_where_bounds_do_not_pay(n, batches, hops, search, launches):
+# No more ranges than sqrt(4.4 entries) of a run, of at most 8192 ids; whole rounds of the device where the runs are long.
+@pytest.mark.parametrize("n,stride,ranges", [(1000, 1 << 24, 2), (334_000, 3, 41), (334_000, 3000, 114), (334_000, 30_000, 363), (334_000, 300_000, 512),
+                                             (10_000_000, 30_000, 1221), (10_000_000, 1 << 24, 1536)])
+def test_histogram_ranges(n, stride, ranges):
     host_calls.run(f"""
 c = context()
-assert histogram(c, {n}, {batches}, {hops}) == OK
+assert histogram(c, {n}, 60, 1, stride={stride}) == OK
+assert [int(x.split()[2]) for x in log("launch k_histogram_runs")] == [{ranges}]
+""")
+
+
+# Few or short runs; the most batches that one launch's scratch holds (28 on 200 M nodes), two launches, more than two.
+@pytest.mark.parametrize("n,batches,hops,stride,search,launches", [
+    (1000, 5, 2, 1 << 24, True, 1), (300_000, 100, 2, 1000, True, 1), (1 << 20, 25, 1, 30_000, True, 1), (1 << 20, 26, 1, 30_000, False, 1),
+    (1 << 22, 17, 1, 30_000, True, 1), (1 << 22, 18, 1, 30_000, False, 1), (10_000_000, 122, 1, 64, True, 1), (10_000_000, 123, 1, 64, False, 1),
+    (10_000_000, 1, 1, 65, False, 1), (10_000_000, 454, 3, 1 << 24, False, 1), (10_000_000, 2000, 3, 1 << 24, False, 5),
+    (200_000_000, 28, 3, 1 << 24, False, 1), (200_000_000, 56, 3, 1 << 24, False, 2), (200_000_000, 57, 3, 1 << 24, True, 1),
+    (1 << 30, 1, 8, 1 << 24, False, 1), (1 << 30, 245, 8, 1 << 24, True, 1)])
+def test_histogram_searches_where_bounds_do_not_pay(n, batches, hops, stride, search, launches):
+    host_calls.run(f"""
+c = context()
+assert histogram(c, {n}, {batches}, {hops}, stride={stride}) == OK
 names = [k.split("<")[0] for k in kernels()]
 assert names.count("k_histogram_runs") == {launches}, names
 assert names.count("k_hist_bounds") == (0 if {search} else {launches}), names
