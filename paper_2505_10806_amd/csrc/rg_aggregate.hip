@@ -6,7 +6,8 @@ namespace {
 
 // agg[i] = (1/m_i) * sum over the block's edges e of row i, in edge order, of feat[nbr_local[e]].
 // A wavefront is split into groups of L lanes per destination row; each lane owns chunk c0 (+ L, + 2L, ...) of the
-// row and accumulates it in registers, E edges at a time so that E independent row loads are in flight.  Up to few_rows rows: L = 64.
+// row and accumulates it in registers, E edges at a time so that E independent row loads are in flight.  Up to few_rows rows: L = 64, up to twice
+// as many at least 32.
 // Bound by the source rows' traffic behind L2 (270 k destinations of 5 edges on a power-law block, 256 floats: 1.31 GB of rows
 // asked for, 27 % of the reads hit L2, so 0.96 GB from behind it, and 0.28 written in 196 us; 373 k distinct rows would be 0.38 GB).  E = 8 takes fan-outs of 5 in one step (E = 4: 206).
 // Cutting the columns into one part per XCD, so that every L2 holds its part of more rows, was slower (8 parts 228, 4 parts 205).
@@ -20,6 +21,7 @@ __global__ void __launch_bounds__(256) k_mean_aggregate(const int32_t* __restric
     int64_t n_act = n_dst;
     if (n_dst_dev) { const int64_t d = *n_dst_dev; n_act = d < n_dst ? d : n_dst; }
     if (n_act <= few_rows) log2L = 6;
+    else if (n_act < 2 * few_rows && log2L == 4) log2L = 5;
     const int lane = rg_lane();
     const int L = 1 << log2L;
     const int R = RG_WAVE >> log2L;
@@ -85,7 +87,8 @@ rg_status rg_mean_aggregate(rg_ctx* ctx, const int32_t* indptr, const int32_t* n
     // 90, 16 lanes 82, of 76 chunks 101 / 97 / 98; 100 k rows of 65 chunks 298 / 311 / 354; 151 chunks, 160 / 192 steps: all 74; 301 chunks
     // of 8 bytes, 304 / 320: 97 with 16 lanes, 84 with 64).  A row then takes its group two to five passes over its edges one after the
     // other, so up to kFewRows rows, which leave wavefronts idle, keep whole ones (80 chunks, 15 edges: 256 rows 10 / 11 / 15 us, 2048 14 / 17 /
-    // 28, 8192 26 / 26 / 34, 10,000 38 / 29 / 36, 16,384 50 / 43 / 43).
+    // 28, 8192 26 / 26 / 34, 10,000 38 / 29 / 36, 16,384 51 / 44 / 43; of 2 edges 144 chunks, 8193 rows 12 / 12 / 15), and up to twice as many
+    // take 32 lanes rather than 16.
     int64_t few_rows = 0;
     if (shp.cpr > RG_WAVE && n_dst > kFewRows) {
         const int64_t whole = rg_div_up(shp.cpr, RG_WAVE) * RG_WAVE, half = rg_div_up(shp.cpr, 32) * 32;

@@ -445,11 +445,11 @@ def test_mean_aggregate_lane_groups(B, ctx, dim, stride):
     assert torch.isnan(agg[:, dim:]).all()
 
 
-# More than 8192 rows: groups of 64, 32 and 16 lanes (65, 76, 96 and 80, 144 chunks), and whole wavefronts again where the device counts fewer.
+# More than 16,383 rows: groups of 64, 32 and 16 lanes (65, 76, 96 and 80, 144 chunks); wider ones where the device counts fewer.
 @pytest.mark.parametrize("dim", [260, 302, 384, 320, 576])
 def test_mean_aggregate_many_rows(B, ctx, dim):
     rng = np.random.default_rng(dim)
-    n, stride = 8203, -(-dim // 4) * 4
+    n, stride = 16_389, -(-dim // 4) * 4
     m = rng.integers(0, 10, n)
     indptr = np.concatenate([[0], np.cumsum(m)]).astype(np.int32)
     nbr = rng.integers(0, 900, indptr[-1]).astype(np.int32)
@@ -461,7 +461,7 @@ def test_mean_aggregate_many_rows(B, ctx, dim):
         rows = np.flatnonzero(m > e)
         want[rows] += x[nbr[indptr[rows] + e]]
     want[m > 0] /= m[m > 0, None].astype(np.float32)
-    for count in (None, 8203, 8193, 8192, 1):
+    for count in (None, 16_384, 16_383, 8193, 8192, 1):
         agg = torch.full((n, stride), -7.0, device=DEV)
         ctx.mean_aggregate(_i32(indptr), _i32(nbr), n, feat, dim, agg, n_dst_dev=None if count is None else _i32([count]))
         got, k = agg.cpu().numpy(), n if count is None else count

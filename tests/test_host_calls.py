@@ -286,7 +286,8 @@ for dst, grid in ((1, 1), (4 * 8192, 8192), (200_000, 8192)):
 """)
 
 
-# Rows of 80 chunks take 16 lanes each, of 76 chunks 32, of 65 a wavefront; up to 8192 rows all do, whose wavefronts have their workgroups.
+# Rows of 80 chunks take 16 lanes each, of 76 chunks 32, of 65 a wavefront; up to 8192 rows all do, up to 16,384 at least 32 lanes: workgroups
+# for as many whatever the device counts.
 @pytest.mark.parametrize("dim,dst,grid", [(320, 2, 1), (320, 1000, 250), (320, 8192, 2048), (320, 8193, 2048), (320, 40_000, 2500),
                                           (304, 8192, 2048), (304, 40_000, 5000), (260, 20_000, 5000)])
 def test_mean_aggregate_lanes_per_row(dim, dst, grid):
