@@ -736,37 +736,47 @@ __global__ void __launch_bounds__(256) k_plan_scatter(const int32_t* __restrict_
 constexpr int kPlanChunk = 1024;     // slots per workgroup, one per thread
 constexpr int kPlanKeyBits = 10;
 
+// Chunks in use, one at least: a cache may hold far fewer rows than its capacity.
+__device__ __forceinline__ int rg_plan_chunks(int64_t num_cached, int nblocks) {
+    const int64_t used = (num_cached + kPlanChunk - 1) / kPlanChunk;
+    return used < 1 ? 1 : used < nblocks ? (int)used : nblocks;
+}
+
 __device__ __forceinline__ int rg_plan_key(const uint32_t* __restrict__ first_batch, int32_t v, int num_batches) {
     const uint32_t f = first_batch[v];
     return f < (uint32_t)num_batches ? (int)f : num_batches;
 }
 
-// hist[key * nblocks + blk] = number of slots of chunk blk first used by batch `key`.
+// hist[key * nblocks + blk] = number of slots of chunk blk first used by batch `key`, for the chunks in use.
 __global__ void __launch_bounds__(1024) k_plan_block_hist(const int32_t* __restrict__ cache_ids, const int64_t* __restrict__ num_cached,
                                                           const uint32_t* __restrict__ first_batch, int num_batches, int nblocks,
                                                           int32_t* __restrict__ hist) {
     __shared__ int h[1024];
+    const int64_t k = *num_cached;
+    if ((int)blockIdx.x >= rg_plan_chunks(k, nblocks)) return;          // uniform
     const int n_seg = num_batches + 1;
     if ((int)threadIdx.x < n_seg) h[threadIdx.x] = 0;
     __syncthreads();
     const int64_t s = (int64_t)blockIdx.x * kPlanChunk + threadIdx.x;
-    if (s < *num_cached) atomicAdd(&h[rg_plan_key(first_batch, cache_ids[s], num_batches)], 1);
+    if (s < k) atomicAdd(&h[rg_plan_key(first_batch, cache_ids[s], num_batches)], 1);
     __syncthreads();
     if ((int)threadIdx.x < n_seg) hist[(int64_t)threadIdx.x * nblocks + blockIdx.x] = h[threadIdx.x];
 }
 
 // One workgroup per key: in-place exclusive scan of the key's chunks, its total to total[key].  (One workgroup for all keys
 // took 39 us for 193 keys x 180 chunks.)
-__global__ void __launch_bounds__(256) k_plan_row_scan(int32_t* __restrict__ hist, int nblocks, int32_t* __restrict__ total) {
+__global__ void __launch_bounds__(256) k_plan_row_scan(const int64_t* __restrict__ num_cached, int32_t* __restrict__ hist, int nblocks,
+                                                       int32_t* __restrict__ total) {
     __shared__ int smem[256 / RG_WAVE + 1];
     int32_t* __restrict__ row = hist + (int64_t)blockIdx.x * nblocks;
+    const int used = rg_plan_chunks(*num_cached, nblocks);
     int carry = 0;
-    for (int base = 0; base < nblocks; base += 256) {
+    for (int base = 0; base < used; base += 256) {
         const int i = base + threadIdx.x;
-        const int x = i < nblocks ? row[i] : 0;
+        const int x = i < used ? row[i] : 0;
         int sum;
         const int excl = rg_block_excl_scan<256 / RG_WAVE>(x, smem, &sum);
-        if (i < nblocks) row[i] = carry + excl;
+        if (i < used) row[i] = carry + excl;
         carry += sum;
     }
     if (threadIdx.x == 0) total[blockIdx.x] = carry;
@@ -784,10 +794,11 @@ __global__ void __launch_bounds__(kPlanChunk) k_plan_block_scatter(const int32_t
     __shared__ uint16_t cnt[NW][1024];   // slots of a key in the wavefront, then in the earlier wavefronts
     __shared__ int key_base[1024];
     __shared__ int smem[NW + 1];
+    const int64_t k = *num_cached;
+    if ((int)blockIdx.x >= rg_plan_chunks(k, nblocks)) return;          // uniform
     const int n_seg = num_batches + 1;
     const int wave = threadIdx.x >> 6, lane = rg_lane();
     for (int i = threadIdx.x; i < NW * 1024 / 2; i += kPlanChunk) ((uint32_t*)cnt)[i] = 0u;
-    const int64_t k = *num_cached;
     const int64_t s = (int64_t)blockIdx.x * kPlanChunk + threadIdx.x;
     const int32_t v = s < k ? cache_ids[s] : 0;
     const int key = s < k ? rg_plan_key(first_batch, v, num_batches) : 1 << kPlanKeyBits;   // no key: matches only its like
@@ -1263,7 +1274,7 @@ rg_status rg_plan_prefetch(rg_ctx* ctx, const rg_cache* cache, const int32_t* ho
         }
         k_plan_block_hist<<<nblocks, 1024, 0, s>>>(cache->cache_ids, cache->num_cached, first_batch, plan->num_batches, nblocks, hist);
         RG_LAUNCH_CHECK(ctx, "k_plan_block_hist");
-        k_plan_row_scan<<<n_seg, 256, 0, s>>>(hist, nblocks, total);
+        k_plan_row_scan<<<n_seg, 256, 0, s>>>(cache->num_cached, hist, nblocks, total);
         RG_LAUNCH_CHECK(ctx, "k_plan_row_scan");
         k_plan_block_scatter<<<nblocks, kPlanChunk, 0, s>>>(cache->cache_ids, cache->num_cached, first_batch, home, plan->num_batches,
                                                             nblocks, hist, total, plan->offsets, plan->list);

@@ -220,6 +220,26 @@ def test_ordered_plan_chunk_edges(B, ctx, slots, pattern):
     assert np.array_equal(plan.offsets.cpu().numpy(), np.searchsorted(key[order], np.arange(nb + 2)))
 
 
+# Fewer rows cached than the capacity has chunks for: none, the edges of a chunk, after a plan of all rows.
+@pytest.mark.parametrize("cached", [0, 1, 1023, 1024, 1025, 300_000])
+def test_ordered_plan_of_few_cached_rows(B, ctx, cached):
+    log(f"[plan] cached={cached}")
+    n, nb = 300_000, 7
+    home, first = _i32((2 << 30) + np.arange(n, dtype=np.int64) - (1 << 32)), np.arange(n, dtype=np.int32)[::-1] % (nb + 1)
+    cache, plan = B.FeatureCache(n, n, 4, DEV), B.PrefetchPlan(n, nb, DEV)
+    for k in (n, cached):
+        ids = np.random.default_rng(k).permutation(n)[:k]
+        counts = torch.zeros(n, dtype=torch.int32, device=DEV)
+        counts[torch.as_tensor(ids, device=DEV)] = 1
+        ctx.build_cache(counts, home, None, 4, cache)
+        ctx.plan_prefetch(cache, home, _i32(first), plan)
+        ids = np.sort(ids)                              # slots in ascending id
+        order = np.argsort(first[ids], kind="stable")
+        pairs = plan.list.cpu().numpy().reshape(-1, 2)[:k]
+        assert np.array_equal(pairs[:, 0], order) and np.array_equal(pairs[:, 1], ids[order])
+        assert np.array_equal(plan.offsets.cpu().numpy(), np.searchsorted(first[ids][order], np.arange(nb + 2)))
+
+
 # Ranges of 512 ids at least, two workgroups per compute unit, 2 Mi bounds per launch; runs whose ids are far from proportional.
 @pytest.mark.parametrize("n,batches,hops", [(511, 3, 1), (513, 3, 2), (262_145, 9, 2), (300_000, 5000, 1), (300_000, 12_000, 1), (5_000_011, 2, 3)])
 @pytest.mark.parametrize("skew", [1, 4])
