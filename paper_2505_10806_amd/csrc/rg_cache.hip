@@ -971,12 +971,13 @@ rg_status launch_list_copy(rg_ctx* ctx, const int32_t* list, const uint32_t* pct
 
 // Id ranges of the epoch histogram: whole rounds of two workgroups per compute unit, but no more ranges than runs of up to run_len
 // entries pay for.  A range costs every run a search and a segment (50 ns per thousand), and saves its share of the LDS atomics: least
-// in sum near sqrt(4.4 run_len) ranges.
+// in sum near sqrt(4.4 run_len) ranges.  Up to 136 they are on compute units that would idle (750 runs, 64 entries a step: 334 k nodes, 30
+// entries each, 41 ranges 21 us, 64 18, 128 16; 20 k nodes, 3 each, 3 ranges 18 us, 40 11).
 int hist_range(const rg_ctx* ctx, int64_t num_nodes, int64_t run_len) {
     const int64_t places = 2ll * ctx->num_cus;
     const int64_t rounds = rg_max64(1, rg_div_up(num_nodes, places * kHistRangeMax));
     const int64_t even = rg_max64(kHistRangeMin, rg_div_up(num_nodes, places * rounds));
-    const int64_t worth = rg_max64(1, (int64_t)sqrt(4.4 * (double)run_len));
+    const int64_t worth = rg_max64(136, (int64_t)sqrt(4.4 * (double)run_len));
     return (int)rg_min64(kHistRangeMax, rg_max64(even, rg_div_up(num_nodes, worth)));
 }
 

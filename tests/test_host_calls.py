@@ -106,8 +106,8 @@ assert [k.split("<")[0] for k in kernels()] == ["k_histogram_seeds", "k_hist_bou
 """)
 
 
-# No more ranges than sqrt(4.4 entries) of a run, of at most 8192 ids; whole rounds of the device where the runs are long.
-@pytest.mark.parametrize("n,stride,ranges", [(1000, 1 << 24, 2), (334_000, 3, 41), (334_000, 3000, 114), (334_000, 30_000, 363), (334_000, 300_000, 512),
+# No more ranges than 136 or sqrt(4.4 entries) of a run, of 512 to 8192 ids; whole rounds of the device where the runs are long.
+@pytest.mark.parametrize("n,stride,ranges", [(1000, 1 << 24, 2), (20_000, 3, 40), (334_000, 3, 136), (334_000, 3000, 136), (334_000, 30_000, 363), (334_000, 300_000, 512),
                                              (10_000_000, 30_000, 1221), (10_000_000, 1 << 24, 1536)])
 def test_histogram_ranges(n, stride, ranges):
     host_calls.run(f"""
