@@ -284,6 +284,8 @@ __global__ void __launch_bounds__(512) k_sched_sort(const int32_t* __restrict__ 
 // far smaller than the device (hop 0 of a 4096-seed batch is 16 workgroups), so a group fills it better and pays
 // every launch once.
 constexpr int kMaxGroup = RG_MAX_GROUP;
+constexpr unsigned kXcds = 8;
+constexpr int kSharedNodes = 4096;
 
 struct SampleGroup {
     const int32_t* seeds[kMaxGroup];
@@ -327,6 +329,14 @@ __device__ __forceinline__ int rg_batch(const SampleScratch& S) {
 }
 __device__ __forceinline__ unsigned rg_block(const SampleScratch& S) {
     return S.xcd_map ? blockIdx.x / (unsigned)S.group : blockIdx.x % (gridDim.x / (unsigned)S.group);
+}
+// The same for the kernels that read the graph at the ids of an ascending frontier: workgroups 8 apart, on one XCD, take `run`
+// consecutive blocks of every batch in turn.
+__device__ __forceinline__ void rg_shared_rows(const SampleScratch& S, int run, int& g, unsigned& blk) {
+    if (run == 0) { g = rg_batch(S); blk = rg_block(S); return; }
+    const unsigned seq = blockIdx.x / kXcds, group = (unsigned)S.group, r = (unsigned)run;
+    g = (int)(seq % group);
+    blk = (seq / group / r * kXcds + blockIdx.x % kXcds) * r + seq / group % r;
 }
 // Rank words of the tier behind hop `hop` of batch g: [hop][group][words] in each buffer.
 __device__ __forceinline__ uint2* rg_rank_words(const SampleScratch& S, int g, int hop) {
@@ -394,28 +404,61 @@ __global__ void __launch_bounds__(1024) k_sample_init(const SampleGroup G, const
 
 // ---------------------------------------------------------------------------- per hop: sizes
 // indptr[i] = exclusive prefix of m within the node's kChunk-node chunk; chunk_sum[b] = chunk total;
-// row_start[i], row_deg[i] = the node's adjacency row.  Bound by the random row_ptr lines: 3.2 M nodes in 61 us.
+// row_start[i], row_deg[i] = the node's adjacency row.  Bound by the random row_ptr lines, so every thread has kCountNodes of
+// them in flight.
+constexpr int kCountNodes = 4;
+
 template <typename RP>
-__global__ void __launch_bounds__(kChunk) k_hop_count(const RP* __restrict__ row_ptr, const SampleGroup G, const SampleScratch S,
-                                                      int hop, int fanout) {
-    __shared__ int smem[kChunk / RG_WAVE + 1];
-    const int g = rg_batch(S);
-    const unsigned blk = rg_block(S);
+__global__ void __launch_bounds__(kChunk / kCountNodes) k_hop_count(const RP* __restrict__ row_ptr, const SampleGroup G, const SampleScratch S,
+                                                                    int hop, int fanout, int run) {
+    constexpr int T = kChunk / kCountNodes, NW = T / RG_WAVE;
+    __shared__ int smem[NW + 1];
+    int g;
+    unsigned blk;
+    rg_shared_rows(S, run, g, blk);
     const int n_h = G.tier_off[g][hop + 1];
     const int64_t first = (int64_t)blk * kChunk;
     if (first >= n_h) return;                       // uniform per workgroup
-    const int64_t i = first + threadIdx.x;
-    int m = 0;
-    if (i < n_h) {
-        int64_t start, deg;
-        rg_row_extent(row_ptr, G.nodes[g][i], start, deg);
-        m = (fanout < 0 || deg <= fanout) ? (int)deg : fanout;
-        S.row_start[g * S.frontier_stride + i] = start;   // kept for the draw kernel: one coalesced read there instead
-        S.row_deg[g * S.frontier_stride + i] = (int32_t)deg;   // of a second random lookup of row_ptr
+    const int n_here = (int)(n_h - first < kChunk ? n_h - first : kChunk);
+    const int32_t* __restrict__ nodes = G.nodes[g] + first;
+    int32_t* __restrict__ indptr = G.indptr[g] + first;
+    int64_t* __restrict__ row_start = S.row_start + g * S.frontier_stride + first;
+    int32_t* __restrict__ row_deg = S.row_deg + g * S.frontier_stride + first;
+    int32_t v[kCountNodes];
+    RP a[kCountNodes], b[kCountNodes];
+    int m[kCountNodes], before[kCountNodes];
+    const int wave = threadIdx.x >> 6, i0 = wave * RG_WAVE * kCountNodes + rg_lane();      // a wavefront takes consecutive nodes
+#pragma unroll
+    for (int q = 0; q < kCountNodes; ++q) v[q] = i0 + q * RG_WAVE < n_here ? nodes[i0 + q * RG_WAVE] : -1;
+#pragma unroll
+    for (int q = 0; q < kCountNodes; ++q) {
+        a[q] = b[q] = 0;
+        if (v[q] >= 0) { a[q] = row_ptr[v[q]]; b[q] = row_ptr[v[q] + 1]; }
     }
-    int total;
-    const int excl = rg_block_excl_scan<kChunk / RG_WAVE>(m, smem, &total);
-    if (i < n_h) G.indptr[g][i] = excl;
+    int sum = 0;
+#pragma unroll
+    for (int q = 0; q < kCountNodes; ++q) {
+        const int64_t deg = (int64_t)(b[q] - a[q]);
+        m[q] = (fanout < 0 || deg <= fanout) ? (int)deg : fanout;
+        const int incl = rg_wave_incl_scan(m[q]);
+        before[q] = sum + incl - m[q];
+        sum += __shfl(incl, RG_WAVE - 1, RG_WAVE);
+        if (v[q] >= 0) {
+            row_start[i0 + q * RG_WAVE] = (int64_t)a[q];   // kept for the draw kernel: one coalesced read there instead
+            row_deg[i0 + q * RG_WAVE] = (int32_t)deg;      // of a second random lookup of row_ptr
+        }
+    }
+    if (rg_lane() == 0) smem[wave] = sum;
+    __syncthreads();
+    int base = 0, total = 0;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) {
+        if (w < wave) base += smem[w];
+        total += smem[w];
+    }
+#pragma unroll
+    for (int q = 0; q < kCountNodes; ++q)
+        if (v[q] >= 0) indptr[i0 + q * RG_WAVE] = base + before[q];
     if (threadIdx.x == 0) S.chunk_sum[g * S.chunk_stride + blk] = total;
 }
 
@@ -553,12 +596,13 @@ constexpr int kDrawSelfScan = 16384;    // count chunks up to which a workgroup 
 template <int KMAX, int NODES, int MODE>
 __global__ void __launch_bounds__(256) k_hop_sample_thread(const int32_t* __restrict__ col_idx, const SampleGroup G,
                                                            const SampleScratch S, int fanout, uint32_t hop, uint32_t k0,
-                                                           uint32_t k1, uint32_t epoch, int scanned) {
+                                                           uint32_t k1, uint32_t epoch, int scanned, int run) {
     extern __shared__ uint32_t staged[];                 // NODES * fanout col_idx offsets
     __shared__ int part[4];
     __shared__ int end_s;
-    const int g = rg_batch(S);
-    const unsigned blk = rg_block(S);
+    int g;
+    unsigned blk;
+    rg_shared_rows(S, run, g, blk);
     const int n_h = G.tier_off[g][hop + 1];
     int32_t* __restrict__ indptr = G.indptr[g];
     const int64_t first = (int64_t)blk * NODES;
@@ -1651,6 +1695,16 @@ rg_status rg_sample_blocks_group(rg_ctx* ctx, const rg_csr* csr, int32_t group, 
         RG_LAUNCH_CHECK(ctx, "k_relabel");
         return RG_OK;
     };
+    // Blocks of `per` frontier nodes and how they are dealt out (rg_shared_rows).
+    const auto shared_run = [&](int64_t frontier, int per, unsigned& grid) -> int {
+        const int64_t blocks = grid_for(frontier, per, 1ll << 30);
+        grid = (unsigned)blocks * ug;
+        if (group == 1 || first_seen || !S.xcd_map) return 0;
+        const int64_t run = rg_min64(kSharedNodes / per, blocks / (8 * kXcds));
+        if (run < 1) return 0;
+        grid = (unsigned)(rg_div_up(blocks, kXcds * run) * kXcds * run) * ug;
+        return (int)run;
+    };
     for (int h = 0; h < num_hops; ++h) {
         for (int g = 0; g < group; ++g) {
             G.indptr[g] = out[g].indptr[h];
@@ -1662,11 +1716,12 @@ rg_status rg_sample_blocks_group(rg_ctx* ctx, const rg_csr* csr, int32_t group, 
             R.nbr_local[h][g] = out[g].nbr_local && eub_max[h] > 0 ? out[g].nbr_local[h] : nullptr;
             if (R.nbr_local[h][g]) relabel_edges = rg_max64(relabel_edges, eub_max[h]);
         }
-        const unsigned count_blocks = (unsigned)grid_for(fub_max[h], kChunk, 1ll << 30);
+        unsigned count_grid;
+        const int count_run = shared_run(fub_max[h], kChunk, count_grid);
         if (rp64)
-            k_hop_count<int64_t><<<count_blocks * ug, kChunk, 0, s>>>((const int64_t*)csr->row_ptr, G, S, h, fanouts[h]);
+            k_hop_count<int64_t><<<count_grid, kChunk / kCountNodes, 0, s>>>((const int64_t*)csr->row_ptr, G, S, h, fanouts[h], count_run);
         else
-            k_hop_count<int32_t><<<count_blocks * ug, kChunk, 0, s>>>((const int32_t*)csr->row_ptr, G, S, h, fanouts[h]);
+            k_hop_count<int32_t><<<count_grid, kChunk / kCountNodes, 0, s>>>((const int32_t*)csr->row_ptr, G, S, h, fanouts[h], count_run);
         RG_LAUNCH_CHECK(ctx, "k_hop_count");
 
         const int F = fanouts[h];
@@ -1675,7 +1730,8 @@ rg_status rg_sample_blocks_group(rg_ctx* ctx, const rg_csr* csr, int32_t group, 
             // 64 nodes per workgroup while 256 would leave compute units without two workgroups (see the kernel)
             const bool few = rg_div_up(fub_max[h], 256) * group < 2ll * ctx->num_cus;
             const int nodes_per = few ? 64 : 256;
-            const unsigned draw_blocks = (unsigned)grid_for(fub_max[h], nodes_per, 1ll << 30);
+            unsigned draw_grid;
+            const int draw_run = shared_run(fub_max[h], nodes_per, draw_grid);
             const size_t lds = (size_t)nodes_per * F * sizeof(uint32_t);
             // Adding up grows with the square of the frontier, a scan costs 3 us for a small one: of 1 M nodes 172 / 175 us, of 8 M
             // 1206 / 1196, of 16 M 2555 / 2498, of 40 M 7213 / 6750.
@@ -1685,7 +1741,7 @@ rg_status rg_sample_blocks_group(rg_ctx* ctx, const rg_csr* csr, int32_t group, 
                 RG_LAUNCH_CHECK(ctx, "k_scan_hop");
             }
 #define RG_LAUNCH_DRAW(KM, NP, MODE)                                                                                  \
-    k_hop_sample_thread<KM, NP, MODE><<<draw_blocks * ug, 256, lds, s>>>(csr->col_idx, G, S, F, (uint32_t)h, k0, k1, epoch, scanned)
+    k_hop_sample_thread<KM, NP, MODE><<<draw_grid, 256, lds, s>>>(csr->col_idx, G, S, F, (uint32_t)h, k0, k1, epoch, scanned, draw_run)
 #define RG_LAUNCH_DRAW_K(NP, MODE)                                                                                    \
     do { if (F <= 8) RG_LAUNCH_DRAW(8, NP, MODE); else if (F <= 16) RG_LAUNCH_DRAW(16, NP, MODE); else RG_LAUNCH_DRAW(32, NP, MODE); } while (0)
 #define RG_LAUNCH_DRAW_N(MODE) do { if (few) RG_LAUNCH_DRAW_K(64, MODE); else RG_LAUNCH_DRAW_K(256, MODE); } while (0)
