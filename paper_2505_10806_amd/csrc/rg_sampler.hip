@@ -71,9 +71,14 @@ constexpr int kMaxSlices = 32;
 constexpr int kSliceGroups = 256;    // workgroups the marking pass is split into at most (slices x splits x batches): one per
                                      // compute unit, which is what a full slice's LDS admits
 constexpr int kSplitEdges = 8192;    // edges per split at least, and two per bitmap word (a split writes its slice out once)
-constexpr int kTierWords = 512;      // bitmap words per workgroup in the tier kernels of kTierSliced
-constexpr int kRankHops = 4;         // hops whose rank words share a buffer
-static_assert(RG_MAX_HOPS <= 2 * kRankHops, "rank words of all hops");
+constexpr int kTierWords = 768;      // bitmap words per workgroup in the tier kernels of kTierSliced
+constexpr int kTierWordsSmall = 192; // the same where few workgroups come of that
+constexpr int kRankIds = 48;         // ids to a rank block, two to three bitmap words (see rg_rank_blocks)
+constexpr int kBaseIds = kRankIds * 1024;      // ids to a base: the members among them are counted in 16 bits
+static_assert(kBaseIds % (32 * kTierWords) == 0 && kBaseIds % (32 * kTierWordsSmall) == 0 && kTierWords % 3 == 0 && kTierWordsSmall % 3 == 0,
+              "whole rank blocks and bases");
+constexpr int kRankHops = 4;         // hops whose rank blocks share a buffer
+static_assert(RG_MAX_HOPS <= 2 * kRankHops && kRankHops == 4, "rank blocks of all hops");
 
 template <typename RP>
 __device__ __forceinline__ void rg_row_extent(const RP* __restrict__ row_ptr, int v, int64_t& start, int64_t& deg) {
@@ -302,7 +307,7 @@ struct SampleScratch {
     uint32_t* visited;                // [group][words]
     uint32_t* marked;                 // kTierAtomic: [group][words], every id met
     uint32_t* slice_marks;            // kTierSliced: [group][splits][words], ids of a hop
-    uint2* rank[2];                   // kTierSliced (rg_rank_words): tier t + 1 of a batch: {its members among the 32 ids, position of the first}
+    uint4* rank[2];                   // kTierSliced: rank blocks and bases of four hops each (rg_rank_blocks)
     int32_t* pos;                     // [group][num_nodes] (kTierSliced: of the seeds only)
     int32_t* chunk_sum;               // [group][chunk_stride]
     int64_t* row_start;               // [group][frontier_stride]
@@ -311,7 +316,7 @@ struct SampleScratch {
     int32_t* place;                   // the same: ascending position -> position
     int32_t* first_key;               // [group][num_nodes], kTierFirstSeen only: 0x7FFFFFFF - (index of the first edge of
                                       // the current hop that names the node), 0 = not named (kept all-zero between hops)
-    int64_t words, num_nodes, chunk_stride, frontier_stride;
+    int64_t words, rank_blocks, rank_bases, num_nodes, chunk_stride, frontier_stride;
     int hops;
     int slices, splits;               // of the marking pass: id ranges of slice_words bitmap words, parts of the edge list
     int slice_words;
@@ -338,9 +343,32 @@ __device__ __forceinline__ void rg_shared_rows(const SampleScratch& S, int run, 
     g = (int)(seq % group);
     blk = (seq / group / r * kXcds + blockIdx.x % kXcds) * r + seq / group % r;
 }
-// Rank words of the tier behind hop `hop` of batch g: [hop][group][words] in each buffer.
-__device__ __forceinline__ uint2* rg_rank_words(const SampleScratch& S, int g, int hop) {
-    return (hop < kRankHops ? S.rank[0] : S.rank[1]) + ((hop & (kRankHops - 1)) * S.group + g) * S.words;
+// Rank blocks: which of kRankIds ids are in a tier (the low 48 bits), and the position of the first of them as what it is above
+// the base of its kBaseIds ids (the upper 16).  The blocks of the last hop's tier and of the one before it lie side by side, and so
+// on backwards, so that one 16-byte read asks two tiers; an odd first tier has its blocks to itself.
+// A random read costs the same for 4 to 16 bytes (258 G/s from L2 on the whole device, 197 from a table of 5 MB per XCD), so what
+// counts is the number of reads, and that the tables of a batch fit its XCD's 4 MB: N / 3 bytes per pair.
+// [pair][group][rank_blocks], kRankHops / 2 pairs to a buffer, then the bases, [hop][group][rank_bases].
+struct RankBlocks {
+    uint2* at;
+    int stride;
+};
+__device__ __forceinline__ uint4* rg_rank_pair(const SampleScratch& S, int g, int pair) {
+    return S.rank[pair >> 1] + ((pair & 1) * S.group + g) * S.rank_blocks;
+}
+__device__ __forceinline__ RankBlocks rg_rank_blocks(const SampleScratch& S, int g, int hop) {
+    const int d = S.hops - 1 - hop;
+    uint2* p = (uint2*)rg_rank_pair(S, g, d >> 1);
+    return hop == 0 && (d & 1) == 0 ? RankBlocks{p, 1} : RankBlocks{p + (d & 1), 2};
+}
+__device__ __forceinline__ int32_t* rg_rank_bases(const SampleScratch& S, int g, int hop) {
+    const int d = S.hops - 1 - hop;
+    return (int32_t*)(S.rank[d >> 2] + 2 * S.group * S.rank_blocks) + ((d & 3) * S.group + g) * S.rank_bases;
+}
+// Bytes of one buffer for `group` batches of `words` bitmap words each, `members` words in all at most.
+inline int64_t rg_rank_bytes(int64_t members) {
+    const int64_t blocks = 2 * (members / 3 + kMaxGroup), bases = members / (kBaseIds / 32) + kMaxGroup;
+    return kRankHops * (blocks * (int64_t)sizeof(uint2) + bases * 4);
 }
 __device__ __forceinline__ unsigned rg_blocks_per_batch(const SampleScratch& S) { return gridDim.x / (unsigned)S.group; }
 
@@ -746,22 +774,40 @@ __global__ void __launch_bounds__(1024) k_slice_mark(const SampleGroup G, const 
     for (int w = threadIdx.x; w < n_words; w += 1024) out[w] = slice_bits[w];
 }
 
-// The splits' bitmaps -> the new tier's bits (into split 0) and the number of them per kTierWords words.
-__global__ void __launch_bounds__(kTierWords) k_slice_count(const SampleScratch S) {
-    constexpr int NW = kTierWords / RG_WAVE;
+// W consecutive words from w on; words behind the end read as 0.
+template <int W>
+__device__ __forceinline__ void rg_load_words(const uint32_t* __restrict__ p, int64_t w, int64_t words, uint32_t (&x)[W]) {
+#pragma unroll
+    for (int q = 0; q < W; ++q) x[q] = w + q < words ? p[w + q] : 0u;
+}
+
+// The splits' bitmaps -> the new tier's bits (into split 0) and the number of them per workgroup of T threads, W words each.
+template <int T, int W>
+__global__ void __launch_bounds__(T) k_slice_count(const SampleScratch S) {
+    constexpr int NW = T / RG_WAVE;
     __shared__ int part[NW];
     const int g = rg_batch(S);
     const unsigned blk = rg_block(S);
-    const int64_t w = (int64_t)blk * kTierWords + threadIdx.x;
+    const int64_t w = ((int64_t)blk * T + threadIdx.x) * W;
     uint32_t* __restrict__ marks = S.slice_marks + (int64_t)g * S.splits * S.words;
-    uint32_t bits = 0u;
-    if (w < S.words) {
+    uint32_t bits[W], members[W];
+    rg_load_words<W>(S.visited + g * S.words, w, S.words, members);
+    rg_load_words<W>(marks, w, S.words, bits);
 #pragma unroll 8
-        for (int s = 0; s < S.splits; ++s) bits |= marks[s * S.words + w];
-        bits &= ~S.visited[g * S.words + w];
-        marks[w] = bits;
+    for (int s = 1; s < S.splits; ++s) {
+        uint32_t more[W];
+        rg_load_words<W>(marks + s * S.words, w, S.words, more);
+#pragma unroll
+        for (int q = 0; q < W; ++q) bits[q] |= more[q];
     }
-    const int c = rg_wave_sum(__popc(bits));
+    int c = 0;
+#pragma unroll
+    for (int q = 0; q < W; ++q) {
+        bits[q] &= ~members[q];
+        if (w + q < S.words) marks[w + q] = bits[q];
+        c += __popc(bits[q]);
+    }
+    c = rg_wave_sum(c);
     if (rg_lane() == 0) part[threadIdx.x >> 6] = c;
     __syncthreads();
     if (threadIdx.x < RG_WAVE) {
@@ -770,44 +816,84 @@ __global__ void __launch_bounds__(kTierWords) k_slice_count(const SampleScratch 
     }
 }
 
-// Emits the new tier behind the current frontier, ascending, with its rank words, and makes its ids frontier members.  The
+// Emits the new tier behind the current frontier, ascending, with its rank blocks, and makes its ids frontier members.  The
 // ids go through LDS so that they are stored by consecutive lanes (thread by thread: 135 us at hop 2 of 8 batches, 7.5 M ids;
-// now 30); a workgroup with more new ids than fit there (over half of its range) stores them directly.
-constexpr int kEmitIds = 8192;
-
+// now 30); a workgroup with more new ids than fit there (over a third of its range) stores them directly.
+// A thread takes W words: three, which are two rank blocks, or one where few workgroups leave the serial walk over the bits of a
+// word as what takes time; the words then meet in LDS.
 // RANKED_SEEN: the positions are ascending ones only, the nodes come later.
-template <bool RANKED_SEEN>
-__global__ void __launch_bounds__(kTierWords) k_slice_emit(const SampleGroup G, const SampleScratch S, int hop) {
-    constexpr int NW = kTierWords / RG_WAVE;
+template <bool RANKED_SEEN, int T, int W>
+__device__ __forceinline__ void rg_slice_emit(const SampleGroup& G, const SampleScratch& S, int hop) {
+    constexpr int NW = T / RG_WAVE, kEmitIds = T * W * 32 / 3;
+    constexpr unsigned per_base = kBaseIds / (32 * T * W);               // workgroups to a base
     __shared__ int smem[NW + 1];
     __shared__ int part[NW];
     __shared__ int32_t ids[RANKED_SEEN ? 1 : kEmitIds];
+    __shared__ uint32_t word_bits[W == 1 ? T : 1];
+    __shared__ int word_rank[W == 1 ? T : 1];
     const int g = rg_batch(S);
     const unsigned blk = rg_block(S);
-    const int64_t w = (int64_t)blk * kTierWords + threadIdx.x;
+    const int64_t w = ((int64_t)blk * T + threadIdx.x) * W;
     const int32_t* __restrict__ chunk_sum = S.chunk_sum + g * S.chunk_stride;
+    uint32_t* __restrict__ visited = S.visited + g * S.words;
+    uint32_t bits[W], members[W];
+    rg_load_words<W>(S.slice_marks + (int64_t)g * S.splits * S.words, w, S.words, bits);
+    rg_load_words<W>(visited, w, S.words, members);
     int before = 0;                                      // new ids in front of this workgroup's words
-    for (unsigned c = threadIdx.x; c < blk; c += kTierWords) before += chunk_sum[c];
+    for (unsigned c = threadIdx.x; c < blk; c += T) before += chunk_sum[c];
     before = rg_wave_sum(before);
     if (rg_lane() == 0) part[threadIdx.x >> 6] = before;
-    const uint32_t bits = w < S.words ? S.slice_marks[(int64_t)g * S.splits * S.words + w] : 0u;
+    int mine = 0;
+#pragma unroll
+    for (int q = 0; q < W; ++q) mine += __popc(bits[q]);
     int total;
-    int j = rg_block_excl_scan<NW>(__popc(bits), smem, &total);                // its barriers publish part[]
+    int j = rg_block_excl_scan<NW>(mine, smem, &total);                        // its barriers publish part[]
     int out = G.tier_off[g][hop + 1];
 #pragma unroll
     for (int q = 0; q < NW; ++q) out += part[q];
     if (threadIdx.x == 0 && blk + 1 == rg_blocks_per_batch(S)) G.tier_off[g][hop + 2] = out + total;
+    int base = out;                                      // position of the first new id behind the last base's first id
+    for (unsigned c = blk / per_base * per_base; c < blk; ++c) base -= chunk_sum[c];
+    if (threadIdx.x == 0 && blk % per_base == 0) rg_rank_bases(S, g, hop)[blk / per_base] = base;
     int32_t* __restrict__ nodes = G.nodes[g] + out;
     int32_t* dst = total <= kEmitIds ? ids : nodes;
-    if (w < S.words) {
-        rg_rank_words(S, g, hop)[w] = make_uint2(bits, (uint32_t)(out + j));
-        if (bits) S.visited[g * S.words + w] |= bits;
-        if (!RANKED_SEEN)
-            for (uint32_t b = bits; b; b &= b - 1u) dst[j++] = (int32_t)(w << 5) + __ffs(b) - 1;
+    const RankBlocks rank = rg_rank_blocks(S, g, hop);
+    const auto store_rank = [&](int64_t r, uint32_t b0, uint32_t b1, uint32_t b2, uint32_t above) {      // three words: two rank blocks
+        rank.at[2 * r * rank.stride] = make_uint2(b0, (b1 & 0xFFFFu) | above << 16);
+        above += (uint32_t)(__popc(b0) + __popc(b1 & 0xFFFFu));
+        rank.at[(2 * r + 1) * rank.stride] = make_uint2(b1 >> 16 | b2 << 16, b2 >> 16 | above << 16);
+    };
+    if (W == 3) {
+        if (w < S.words) store_rank(w / 3, bits[0], bits[W / 3], bits[W - 1], (uint32_t)(out + j - base));
+    } else {
+        word_bits[threadIdx.x] = bits[0];
+        word_rank[threadIdx.x] = out + j - base;
     }
-    if (RANKED_SEEN || total > kEmitIds) return;         // uniform
+#pragma unroll
+    for (int q = 0; q < W; ++q) {
+        if (bits[q]) visited[w + q] = members[q] | bits[q];
+        if (!RANKED_SEEN)
+            for (uint32_t b = bits[q]; b; b &= b - 1u) dst[j++] = (int32_t)((w + q) << 5) + __ffs(b) - 1;
+    }
+    if (W == 3 && (RANKED_SEEN || total > kEmitIds)) return;             // uniform
     __syncthreads();
-    for (int i = threadIdx.x; i < total; i += kTierWords) nodes[i] = ids[i];
+    if (W == 1 && threadIdx.x < T / 3) {
+        const int q = 3 * threadIdx.x;
+        const int64_t r = (int64_t)blk * (T / 3) + threadIdx.x;
+        if (3 * r < S.words) store_rank(r, word_bits[q], word_bits[q + 1], word_bits[q + 2], (uint32_t)word_rank[q]);
+    }
+    if (RANKED_SEEN || total > kEmitIds) return;
+    for (int i = threadIdx.x; i < total; i += T) nodes[i] = ids[i];
+}
+
+template <bool RANKED_SEEN>
+__global__ void __launch_bounds__(kTierWords / 3) k_slice_emit(const SampleGroup G, const SampleScratch S, int hop) {
+    rg_slice_emit<RANKED_SEEN, kTierWords / 3, 3>(G, S, hop);
+}
+
+template <bool RANKED_SEEN>
+__global__ void __launch_bounds__(kTierWordsSmall) k_slice_emit_small(const SampleGroup G, const SampleScratch S, int hop) {
+    rg_slice_emit<RANKED_SEEN, kTierWordsSmall, 1>(G, S, hop);
 }
 
 // ---------------------------------------------------------------------------- per hop: new tier, from `marked`
@@ -936,24 +1022,64 @@ __global__ void __launch_bounds__(256) k_first_seen_emit(const SampleGroup G, co
 }
 
 // ---------------------------------------------------------------------------- per hop: first-seen order by rank words
-// Positions of U ids (-1: none) from the rank words of the hops' tiers, latest first, and from pos[] for the seeds; the U reads of
-// a tier are in flight together.
+// The bases of a batch's tiers, [hop][rank_bases], into LDS.
+__device__ __forceinline__ void rg_load_bases(const SampleScratch& S, int g, int hops, int32_t* bases) {
+    const int n = (int)S.rank_bases;
+    for (int hop = 0; hop < hops; ++hop) {
+        const int32_t* __restrict__ from = rg_rank_bases(S, g, hop);
+        for (int i = threadIdx.x; i < n; i += blockDim.x) bases[hop * n + i] = from[i];
+    }
+    __syncthreads();
+}
+
+// Positions of U ids (-1: none) from the rank blocks of the hops' tiers, latest first, and from pos[] for the seeds; the U reads of
+// a step are in flight together.
 template <int U>
 __device__ __forceinline__ void rg_ranked_positions(const int32_t (&u)[U], const SampleScratch& S, int g, int hop,
-                                                    const int32_t* __restrict__ pos, int32_t (&r)[U]) {
+                                                    const int32_t* __restrict__ pos, const int32_t* bases, int32_t (&r)[U]) {
+    uint32_t at[U], bit[U][2], below[U][2];              // the id's rank block, its bit there and the bits below it
+    const int nb = (int)S.rank_bases;
 #pragma unroll
-    for (int q = 0; q < U; ++q) r[q] = u[q] >= 0 ? -1 : 0;
-    for (int t = hop; t >= 0; --t) {
-        const uint2* __restrict__ rank = rg_rank_words(S, g, t);
-        uint2 x[U];
-#pragma unroll
-        for (int q = 0; q < U; ++q) x[q] = r[q] < 0 ? rank[(uint32_t)u[q] >> 5] : make_uint2(0u, 0u);
+    for (int q = 0; q < U; ++q) {
+        r[q] = u[q] >= 0 ? -1 : 0;
+        at[q] = (uint32_t)u[q] / (uint32_t)kRankIds;
+        const uint32_t in = (uint32_t)u[q] - at[q] * (uint32_t)kRankIds, b = 1u << (in & 31u);
+        bit[q][0] = in < 32u ? b : 0u;
+        bit[q][1] = in < 32u ? 0u : b;
+        below[q][0] = bit[q][0] - 1u;                    // (all ones where the bit is in the upper word)
+        below[q][1] = in < 32u ? 0u : b - 1u;
+    }
+    for (int t = hop; t >= 0;) {                         // tiers t and below are left
+        const int d = S.hops - 1 - t;
+        const char* __restrict__ rank = (const char*)rg_rank_pair(S, g, d >> 1);
         bool open = false;
+        if (t == 0 && (d & 1) == 0) {
+            uint2 x[U];
 #pragma unroll
-        for (int q = 0; q < U; ++q) {
-            const uint32_t bit = 1u << (u[q] & 31);
-            if (x[q].x & bit) r[q] = (int32_t)x[q].y + __popc(x[q].x & (bit - 1u));
-            open = open || r[q] < 0;
+            for (int q = 0; q < U; ++q) x[q] = r[q] < 0 ? *(const uint2*)(rank + at[q] * 8u) : make_uint2(0u, 0u);
+#pragma unroll
+            for (int q = 0; q < U; ++q) {
+                if ((x[q].x & bit[q][0]) | (x[q].y & bit[q][1]))
+                    r[q] = bases[at[q] >> 10] + (int)(x[q].y >> 16) + __popc(x[q].x & below[q][0]) + __popc(x[q].y & below[q][1]);
+                open = open || r[q] < 0;
+            }
+            t = -1;
+        } else {
+            const uint32_t ask = d & 1 ? 0u : ~0u;       // the later tier of the pair is not there yet in front of its hop
+            const int earlier = d & 1 ? t : t - 1;
+            uint4 x[U];
+#pragma unroll
+            for (int q = 0; q < U; ++q) x[q] = r[q] < 0 ? *(const uint4*)(rank + at[q] * 16u) : make_uint4(0u, 0u, 0u, 0u);
+#pragma unroll
+            for (int q = 0; q < U; ++q) {
+                const bool late = (((x[q].x & bit[q][0]) | (x[q].y & bit[q][1])) & ask) != 0u;
+                const uint32_t lo = late ? x[q].x : x[q].z, hi = late ? x[q].y : x[q].w;
+                if ((lo & bit[q][0]) | (hi & bit[q][1]))
+                    r[q] = bases[(late ? earlier + 1 : earlier) * nb + (int)(at[q] >> 10)] + (int)(hi >> 16) + __popc(lo & below[q][0]) +
+                           __popc(hi & below[q][1]);
+                open = open || r[q] < 0;
+            }
+            t = earlier - 1;
         }
         if (!__any(open)) return;
     }
@@ -964,8 +1090,10 @@ __device__ __forceinline__ void rg_ranked_positions(const int32_t (&u)[U], const
 
 // nbr_local[e] = ascending position of nbr[e].
 __global__ void __launch_bounds__(256) k_seen_rank(const SampleGroup G, const SampleScratch S, int hop) {
-    constexpr int U = 4;
+    extern __shared__ int32_t bases[];
+    constexpr int U = 2;
     const int g = rg_batch(S);
+    rg_load_bases(S, g, hop + 1, bases);
     const int64_t stride = (int64_t)rg_blocks_per_batch(S) * 256;
     const int64_t n = G.indptr[g][G.tier_off[g][hop + 1]];
     const int32_t* __restrict__ nbr = G.nbr[g];
@@ -975,7 +1103,7 @@ __global__ void __launch_bounds__(256) k_seen_rank(const SampleGroup G, const Sa
         int32_t u[U], r[U];
 #pragma unroll
         for (int q = 0; q < U; ++q) u[q] = e0 + stride * q < n ? nbr[e0 + stride * q] : -1;
-        rg_ranked_positions<U>(u, S, g, hop, pos, r);
+        rg_ranked_positions<U>(u, S, g, hop, pos, bases, r);
 #pragma unroll
         for (int q = 0; q < U; ++q)
             if (u[q] >= 0) nbr_local[e0 + stride * q] = r[q];
@@ -1116,10 +1244,12 @@ struct RelabelGroup {
 // by themselves: pos[] 251 us, the new tier's words and those of one more 142, the new tier's alone, which would not do, 74.)
 template <bool RANKED>
 __global__ void __launch_bounds__(256) k_relabel(const RelabelGroup R, const SampleScratch S) {
-    constexpr int U = 4;                                 // edges in flight per thread
+    extern __shared__ int32_t bases[];
+    constexpr int U = RANKED ? 2 : 4;                    // edges in flight per thread
     const int g = rg_batch(S);
     const int64_t stride = (int64_t)rg_blocks_per_batch(S) * 256;
     const int32_t* __restrict__ pos = S.pos + g * S.num_nodes;
+    if (RANKED) rg_load_bases(S, g, S.hops, bases);
     for (int hop = S.hops - 1; hop >= 0; --hop) {
         int32_t* __restrict__ nbr_local = R.nbr_local[hop][g];
         if (!nbr_local) continue;
@@ -1130,7 +1260,7 @@ __global__ void __launch_bounds__(256) k_relabel(const RelabelGroup R, const Sam
 #pragma unroll
             for (int q = 0; q < U; ++q) u[q] = e0 + stride * q < n ? nbr[e0 + stride * q] : -1;
             if (RANKED) {
-                rg_ranked_positions<U>(u, S, g, hop, pos, r);
+                rg_ranked_positions<U>(u, S, g, hop, pos, bases, r);
             } else {
 #pragma unroll
                 for (int q = 0; q < U; ++q) r[q] = u[q] >= 0 ? pos[u[q]] : 0;
@@ -1317,11 +1447,13 @@ __global__ void __launch_bounds__(256) k_seen_relabel(const RelabelGroup R, cons
 // max_edges: the largest per-hop edge bound when tiers are built from the edge list (first-seen order), else 0.
 void sampler_scratch_shape(int64_t N, int64_t frontier, int64_t max_edges, SampleScratch& S) {
     S.words = rg_div_up(N, 32);
+    S.rank_blocks = 2 * rg_div_up(S.words, 3);
+    S.rank_bases = rg_div_up(N, kBaseIds);
     S.num_nodes = N;
     S.frontier_stride = rg_max64(frontier, 1);
     // (a quarter of a count chunk per entry leaves room for the first-seen blocks of up to four edges per frontier node)
     S.chunk_stride = rg_max64(rg_max64(rg_div_up(S.frontier_stride, kChunk / 4), rg_div_up(max_edges, kEdgesPerBlock)),
-                              rg_max64(1, rg_div_up(S.words, kTierWords))) + 2;
+                              rg_max64(1, rg_div_up(S.words, kTierWordsSmall))) + 2;
     const int64_t slices = rg_max64(1, rg_div_up(S.words, kSliceWords));
     S.slices = slices <= kMaxSlices ? (int)slices : 0;       // 0: too large for the sliced marking
     S.slice_words = S.slices ? (int)rg_max64(1, rg_div_up(S.words, slices)) : 0;
@@ -1403,7 +1535,8 @@ int grid_for(int64_t work_items, int per_block, int64_t cap) {
 struct SlicedBytes { size_t marks, rank, seen; };
 static SlicedBytes sliced_bytes(int64_t members, int64_t frontier, bool first_seen) {
     const int64_t marks = rg_max64(members, kSliceGroups * rg_min64(members, kSliceWords));
-    return {(size_t)marks * 4, (size_t)kRankHops * members * sizeof(uint2), first_seen ? (size_t)frontier * 8 : 0};
+    const int64_t rank = rg_max64(kRankHops * members * 8, rg_rank_bytes(members));      // (more than enough for any but small graphs)
+    return {(size_t)marks * 4, (size_t)rank, first_seen ? (size_t)frontier * 8 : 0};
 }
 // Hops beyond kRankHops have a buffer of their own unless the first one holds them too.
 static bool rank_in_one(const rg_ctx* ctx, const SlicedBytes& need) { return ctx->rank[0].bytes >= 2 * need.rank; }
@@ -1602,8 +1735,8 @@ rg_status rg_sample_blocks_group(rg_ctx* ctx, const rg_csr* csr, int32_t group, 
             there = st == RG_OK;
         }
         if (!there) mode = first_seen ? kTierFirstSeen : kTierAtomic;
-        S.rank[0] = (uint2*)ctx->rank[0].p;
-        S.rank[1] = rank_in_one(ctx, need) ? S.rank[0] + need.rank / sizeof(uint2) : (uint2*)ctx->rank[1].p;
+        S.rank[0] = (uint4*)ctx->rank[0].p;
+        S.rank[1] = rank_in_one(ctx, need) ? S.rank[0] + need.rank / sizeof(uint4) : (uint4*)ctx->rank[1].p;
     }
     S.hops = num_hops;
     S.slice_marks = (uint32_t*)ctx->slice_marks.p;
@@ -1688,8 +1821,8 @@ rg_status rg_sample_blocks_group(rg_ctx* ctx, const rg_csr* csr, int32_t group, 
     for (int g = 0; g < group; ++g) R.tier_off[g] = out[g].tier_off;
     const auto relabel = [&]() -> rg_status {              // every hop that R names
         if (relabel_edges == 0) return RG_OK;
-        const unsigned blocks = (unsigned)grid_for(relabel_edges, 1024, (int64_t)ctx->num_cus * 16);
-        if (mode == kTierSliced) k_relabel<true><<<blocks * ug, 256, 0, s>>>(R, S);
+        const unsigned blocks = (unsigned)grid_for(relabel_edges, 1024, rg_div_up((int64_t)ctx->num_cus * 32, group));
+        if (mode == kTierSliced) k_relabel<true><<<blocks * ug, 256, (size_t)(num_hops * S.rank_bases) * 4, s>>>(R, S);
         else if (mode == kTierRankedSeen) k_seen_relabel<<<blocks * ug, 256, 0, s>>>(R, S);
         else k_relabel<false><<<blocks * ug, 256, 0, s>>>(R, S);
         RG_LAUNCH_CHECK(ctx, "k_relabel");
@@ -1774,15 +1907,21 @@ rg_status rg_sample_blocks_group(rg_ctx* ctx, const rg_csr* csr, int32_t group, 
             S.splits = (int)rg_max64(1, rg_min64(rg_min64(eub_max[h], 8 * expected[h]) / split_edges, kSliceGroups / (S.slices * group)));
             k_slice_mark<<<(unsigned)(S.slices * S.splits) * ug, 1024, (size_t)S.slice_words * 4, s>>>(G, S, h);
             RG_LAUNCH_CHECK(ctx, "k_slice_mark");
-            const unsigned tier_blocks = (unsigned)rg_max64(1, rg_div_up(words, kTierWords));
-            k_slice_count<<<tier_blocks * ug, kTierWords, 0, s>>>(S);
-            RG_LAUNCH_CHECK(ctx, "k_slice_count");
-            if (mode == kTierSliced) k_slice_emit<false><<<tier_blocks * ug, kTierWords, 0, s>>>(G, S, h);
-            else k_slice_emit<true><<<tier_blocks * ug, kTierWords, 0, s>>>(G, S, h);
-            RG_LAUNCH_CHECK(ctx, "k_slice_emit");
+            const bool small_tier = rg_div_up(words, kTierWords) * group < ctx->num_cus;
+            const unsigned tier_blocks = (unsigned)rg_max64(1, rg_div_up(words, small_tier ? kTierWordsSmall : kTierWords)) * ug;
+#define RG_LAUNCH_TIER(EMIT, T, W)                                                                                    \
+    do {                                                                                                              \
+        k_slice_count<T, W><<<tier_blocks, T, 0, s>>>(S);                                                        \
+        RG_LAUNCH_CHECK(ctx, "k_slice_count");                                                                        \
+        if (mode == kTierSliced) EMIT<false><<<tier_blocks, T, 0, s>>>(G, S, h);             \
+        else EMIT<true><<<tier_blocks, T, 0, s>>>(G, S, h);                                   \
+        RG_LAUNCH_CHECK(ctx, "k_slice_emit");                                                                         \
+    } while (0)
+            if (small_tier) RG_LAUNCH_TIER(k_slice_emit_small, kTierWordsSmall, 1); else RG_LAUNCH_TIER(k_slice_emit, kTierWords / 3, 3);
+#undef RG_LAUNCH_TIER
             if (mode == kTierRankedSeen) {
                 // the edges that open a node, counted per block of the edge list, emitted in edge order
-                k_seen_rank<<<(unsigned)grid_for(eub_max[h], 1024, (int64_t)ctx->num_cus * 16) * ug, 256, 0, s>>>(G, S, h);
+                k_seen_rank<<<(unsigned)grid_for(eub_max[h], 1024, (int64_t)ctx->num_cus * 16) * ug, 256, (size_t)((h + 1) * S.rank_bases) * 4, s>>>(G, S, h);
                 RG_LAUNCH_CHECK(ctx, "k_seen_rank");
                 const int64_t most_new = rg_min64(N, eub_max[h]);
                 k_seen_min<<<(unsigned)grid_for(most_new, kSeenSlice, 1 << 30) * ug, 1024, (size_t)rg_min64(most_new, kSeenSlice) * 4, s>>>(G, S, h);
