@@ -291,6 +291,7 @@ __global__ void __launch_bounds__(512) k_sched_sort(const int32_t* __restrict__ 
 constexpr int kMaxGroup = RG_MAX_GROUP;
 constexpr unsigned kXcds = 8;
 constexpr int kSharedNodes = 4096;
+constexpr int64_t kLaneDraws = 1 << 18;
 
 struct SampleGroup {
     const int32_t* seeds[kMaxGroup];
@@ -716,6 +717,82 @@ __global__ void __launch_bounds__(256) k_hop_sample_thread(const int32_t* __rest
             if (MODE == kTierAtomic) rg_mark(u[q], marked);
         }
     }
+}
+
+// The same for few frontier nodes: KMAX lanes per node, one draw each, no staging.  Floyd's set by itself: draw s is taken already if an
+// earlier draw has its value, or if its value is the last position j_l of an earlier step l that found its own draw taken.
+template <int KMAX, int MODE>
+__global__ void __launch_bounds__(256) k_hop_sample_lanes(const int32_t* __restrict__ col_idx, const SampleGroup G,
+                                                          const SampleScratch S, int fanout, uint32_t hop, uint32_t k0,
+                                                          uint32_t k1, uint32_t epoch) {
+    constexpr int NODES = 256 / KMAX;
+    static_assert(RG_WAVE % KMAX == 0 && kChunk % NODES == 0, "a node's lanes share a wavefront, a workgroup's nodes a chunk");
+    __shared__ int part[4];
+    const int g = rg_batch(S);
+    const unsigned blk = rg_block(S);
+    const int n_h = G.tier_off[g][hop + 1];
+    int32_t* __restrict__ indptr = G.indptr[g];
+    const int64_t first = (int64_t)blk * NODES;
+    if (first >= n_h) {                                  // uniform per workgroup
+        if (n_h == 0 && blk == 0 && threadIdx.x == 0) {
+            indptr[0] = 0;
+            if (G.edges_out[g]) *G.edges_out[g] = 0;
+        }
+        return;
+    }
+    const int32_t* __restrict__ chunk_sum = S.chunk_sum + g * S.chunk_stride;
+    const int lane = (int)threadIdx.x & (KMAX - 1), k = fanout;
+    const int64_t i = first + threadIdx.x / KMAX;
+    const bool live = i < n_h;
+    int32_t v = 0;
+    int64_t start = 0, deg = 0;
+    int off = 0;
+    if (live) {
+        v = G.nodes[g][i];
+        start = S.row_start[g * S.frontier_stride + i];
+        deg = S.row_deg[g * S.frontier_stride + i];
+        off = indptr[i];
+    }
+    int before = 0;                                      // edges in front of this count chunk
+    for (int c = threadIdx.x; c < (int)(first / kChunk); c += 256) before += chunk_sum[c];
+    before = rg_wave_sum(before);
+    if (rg_lane() == 0) part[threadIdx.x >> 6] = before;
+    uint32_t at = (uint32_t)lane;                        // whole row, CSR order
+    if (__any(live && deg > k)) {
+        uint32_t w[4];
+        rg_philox4x32_10((uint32_t)v, hop, (uint32_t)lane >> 2, epoch, k0, k1, w);
+        const uint32_t word = lane & 2 ? (lane & 1 ? w[3] : w[2]) : (lane & 1 ? w[1] : w[0]);
+        const uint32_t j0 = (uint32_t)(deg - k), j = j0 + (uint32_t)lane;      // Floyd: j = d-k+s, t uniform in [0, j]
+        const uint32_t t = __umulhi(word, j + 1u);
+        bool taken = false;
+        for (int l = 0; l + 1 < k; ++l) taken |= (uint32_t)__shfl((int)t, l, KMAX) == t && l < lane;
+        const int node0 = rg_lane() & ~(KMAX - 1);
+        const int l = (int)(t - j0);                     // the step whose last position t is
+        const bool late = deg > k && t >= j0 && l < lane;
+        for (;;) {                                       // a step is added to the taken ones at most once: k rounds at most
+            const unsigned long long all = __ballot(taken);
+            const bool more = late && !taken && ((all >> (node0 + l)) & 1ull);
+            if (!__any(more)) break;
+            taken |= more;
+        }
+        if (deg > k) at = taken ? j : t;
+    }
+    __syncthreads();
+    if (!live) return;
+    off += part[0] + part[1] + part[2] + part[3];
+    const int m = (int)(deg <= k ? deg : k);
+    if (lane == 0) {
+        indptr[i] = off;
+        if (i == n_h - 1) {
+            indptr[n_h] = off + m;
+            if (G.edges_out[g]) *G.edges_out[g] = off + m;
+        }
+    }
+    if (lane >= m) return;
+    const int32_t u = col_idx[start + at];
+    G.nbr[g][off + lane] = u;
+    if (MODE == kTierFirstSeen) rg_note_first_edge(u, off + lane, S.visited + g * S.words, S.first_key + g * S.num_nodes);
+    if (MODE == kTierAtomic) rg_mark(u, S.marked + g * S.words);
 }
 
 // ---------------------------------------------------------------------------- per hop: new tier, sliced
@@ -1866,6 +1943,7 @@ rg_status rg_sample_blocks_group(rg_ctx* ctx, const rg_csr* csr, int32_t group, 
             unsigned draw_grid;
             const int draw_run = shared_run(fub_max[h], nodes_per, draw_grid);
             const size_t lds = (size_t)nodes_per * F * sizeof(uint32_t);
+            const bool lanes = fub_max[h] * group * (F <= 8 ? 8 : F <= 16 ? 16 : 32) <= kLaneDraws;
             // Adding up grows with the square of the frontier, a scan costs 3 us for a small one: of 1 M nodes 172 / 175 us, of 8 M
             // 1206 / 1196, of 16 M 2555 / 2498, of 40 M 7213 / 6750.
             const int scanned = rg_div_up(fub_max[h], kChunk) > kDrawSelfScan;
@@ -1875,13 +1953,19 @@ rg_status rg_sample_blocks_group(rg_ctx* ctx, const rg_csr* csr, int32_t group, 
             }
 #define RG_LAUNCH_DRAW(KM, NP, MODE)                                                                                  \
     k_hop_sample_thread<KM, NP, MODE><<<draw_grid, 256, lds, s>>>(csr->col_idx, G, S, F, (uint32_t)h, k0, k1, epoch, scanned, draw_run)
+#define RG_LAUNCH_LANES(KM, MODE)                                                                                     \
+    k_hop_sample_lanes<KM, MODE><<<(unsigned)grid_for(fub_max[h], 256 / KM, 1ll << 30) * ug, 256, 0, s>>>(csr->col_idx, G, S, F, (uint32_t)h, k0, k1, epoch)
 #define RG_LAUNCH_DRAW_K(NP, MODE)                                                                                    \
     do { if (F <= 8) RG_LAUNCH_DRAW(8, NP, MODE); else if (F <= 16) RG_LAUNCH_DRAW(16, NP, MODE); else RG_LAUNCH_DRAW(32, NP, MODE); } while (0)
-#define RG_LAUNCH_DRAW_N(MODE) do { if (few) RG_LAUNCH_DRAW_K(64, MODE); else RG_LAUNCH_DRAW_K(256, MODE); } while (0)
+#define RG_LAUNCH_LANES_K(MODE)                                                                                       \
+    do { if (F <= 8) RG_LAUNCH_LANES(8, MODE); else if (F <= 16) RG_LAUNCH_LANES(16, MODE); else RG_LAUNCH_LANES(32, MODE); } while (0)
+#define RG_LAUNCH_DRAW_N(MODE) do { if (lanes) RG_LAUNCH_LANES_K(MODE); else if (few) RG_LAUNCH_DRAW_K(64, MODE); else RG_LAUNCH_DRAW_K(256, MODE); } while (0)
             if (mode == kTierSliced || mode == kTierRankedSeen) RG_LAUNCH_DRAW_N(kTierSliced);
             else if (mode == kTierAtomic) RG_LAUNCH_DRAW_N(kTierAtomic);
             else RG_LAUNCH_DRAW_N(kTierFirstSeen);
 #undef RG_LAUNCH_DRAW_N
+#undef RG_LAUNCH_LANES_K
+#undef RG_LAUNCH_LANES
 #undef RG_LAUNCH_DRAW_K
 #undef RG_LAUNCH_DRAW
             rg_prof_end(ctx, tok, s);
