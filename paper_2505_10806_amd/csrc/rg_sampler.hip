@@ -88,6 +88,15 @@ __device__ __forceinline__ void rg_row_extent(const RP* __restrict__ row_ptr, in
     deg = (int64_t)(b - a);
 }
 
+struct RowPtr {                      // a row_ptr array of either width
+    const void* p;
+    int wide;
+};
+__device__ __forceinline__ void rg_row_extent(const RowPtr& row_ptr, int v, int64_t& start, int64_t& deg) {
+    if (row_ptr.wide) rg_row_extent((const int64_t*)row_ptr.p, v, start, deg);
+    else rg_row_extent((const int32_t*)row_ptr.p, v, start, deg);
+}
+
 // ---------------------------------------------------------------------------- schedule
 // The keys are Philox words, spread evenly whatever the ids, so their top bits are a perfect first radix digit: the (key, id)
 // pairs are counted into 2^log2_buckets buckets of about 1024-2048, scattered there, and every bucket is finished by one
@@ -310,7 +319,8 @@ struct SampleScratch {
     uint32_t* slice_marks;            // kTierSliced: [group][splits][words], ids of a hop
     uint4* rank[2];                   // kTierSliced: rank blocks and bases of four hops each (rg_rank_blocks)
     int32_t* pos;                     // [group][num_nodes] (kTierSliced: of the seeds only)
-    int32_t* chunk_sum;               // [group][chunk_stride]
+    int32_t* chunk_sum;               // [group][chunk_stride]: new ids per workgroup of the tier kernels
+    int32_t* hop_sum[2];              // the same: edges of the even and the odd hops per kChunk frontier nodes
     int64_t* row_start;               // [group][frontier_stride]
     int32_t* row_deg;                 // [group][frontier_stride]
     int32_t* first_edge;              // kTierRankedSeen: [group][frontier_stride], by ascending position (see there)
@@ -403,14 +413,35 @@ __global__ void __launch_bounds__(256) k_mark_seeds(const SampleGroup G, const S
 inline bool rg_use_init(int slices, int group, int64_t seeds) {
     return slices > 0 && (seeds <= 8192 || (group >= 4 && slices * group >= 32));
 }
-__global__ void __launch_bounds__(1024) k_sample_init(const SampleGroup G, const SampleScratch S, int copy) {
+// The workgroups behind the slices do for the seeds what k_hop_count does.
+__global__ void __launch_bounds__(1024) k_sample_init(const RowPtr row_ptr, const SampleGroup G, const SampleScratch S, int fanout, int copy) {
     extern __shared__ uint32_t slice_bits[];
     const int g = rg_batch(S);
     const unsigned slice = rg_block(S);
+    const int num_seeds = G.num_seeds[g];
+    if (slice >= (unsigned)S.slices) {
+        const unsigned chunk = slice - (unsigned)S.slices;
+        const int i = (int)(chunk * kChunk + threadIdx.x);
+        int m = 0;
+        if (i < num_seeds) {
+            int64_t start, deg;
+            rg_row_extent(row_ptr, G.seeds[g][i], start, deg);
+            S.row_start[g * S.frontier_stride + i] = start;
+            S.row_deg[g * S.frontier_stride + i] = (int32_t)deg;
+            m = deg <= fanout ? (int)deg : fanout;
+        }
+        m = rg_wave_sum(m);
+        if (rg_lane() == 0) slice_bits[threadIdx.x >> 6] = (uint32_t)m;
+        __syncthreads();
+        if (threadIdx.x < RG_WAVE) {
+            m = rg_wave_sum(threadIdx.x < 1024 / RG_WAVE ? (int)slice_bits[threadIdx.x] : 0);
+            if (threadIdx.x == 0) S.hop_sum[0][g * S.chunk_stride + chunk] = m;
+        }
+        return;
+    }
     const int64_t w0 = (int64_t)slice * S.slice_words;
     const int n_words = (int)(S.words - w0 < S.slice_words ? S.words - w0 : S.slice_words);
     for (int w = threadIdx.x; w < n_words; w += 1024) slice_bits[w] = 0u;
-    const int num_seeds = G.num_seeds[g];
     if (slice == 0 && threadIdx.x == 0) { G.tier_off[g][0] = 0; G.tier_off[g][1] = num_seeds; }
     __syncthreads();
     const uint32_t id0 = (uint32_t)(w0 << 5), n_ids = (uint32_t)n_words << 5;
@@ -432,14 +463,14 @@ __global__ void __launch_bounds__(1024) k_sample_init(const SampleGroup G, const
 }
 
 // ---------------------------------------------------------------------------- per hop: sizes
-// indptr[i] = exclusive prefix of m within the node's kChunk-node chunk; chunk_sum[b] = chunk total;
-// row_start[i], row_deg[i] = the node's adjacency row.  Bound by the random row_ptr lines, so every thread has kCountNodes of
-// them in flight.
+// hop_sum[b] = edges of the kChunk nodes from b * kChunk on; row_start[i], row_deg[i] = the node's adjacency row; indptr[i] (where
+// `offsets` asks for it) = exclusive prefix of m within the node's chunk.  Bound by the random row_ptr lines, so every thread has
+// kCountNodes of them in flight.
 constexpr int kCountNodes = 4;
 
 template <typename RP>
 __global__ void __launch_bounds__(kChunk / kCountNodes) k_hop_count(const RP* __restrict__ row_ptr, const SampleGroup G, const SampleScratch S,
-                                                                    int hop, int fanout, int run) {
+                                                                    int hop, int fanout, int run, int offsets) {
     constexpr int T = kChunk / kCountNodes, NW = T / RG_WAVE;
     __shared__ int smem[NW + 1];
     int g;
@@ -487,8 +518,8 @@ __global__ void __launch_bounds__(kChunk / kCountNodes) k_hop_count(const RP* __
     }
 #pragma unroll
     for (int q = 0; q < kCountNodes; ++q)
-        if (v[q] >= 0) indptr[i0 + q * RG_WAVE] = base + before[q];
-    if (threadIdx.x == 0) S.chunk_sum[g * S.chunk_stride + blk] = total;
+        if (offsets && v[q] >= 0) indptr[i0 + q * RG_WAVE] = base + before[q];
+    if (threadIdx.x == 0) S.hop_sum[hop & 1][g * S.chunk_stride + blk] = total;
 }
 
 // In-place exclusive scan of data[0..n) by one workgroup; returns (to thread 0) the grand total.
@@ -516,7 +547,7 @@ __device__ __forceinline__ int rg_scan_in_place(int32_t* __restrict__ data, int6
 __global__ void __launch_bounds__(1024) k_scan_hop(const SampleGroup G, const SampleScratch S, int hop) {
     const int g = rg_batch(S);
     const int n_h = G.tier_off[g][hop + 1];
-    const int total = rg_scan_in_place(S.chunk_sum + g * S.chunk_stride, ((int64_t)n_h + kChunk - 1) / kChunk);
+    const int total = rg_scan_in_place(S.hop_sum[hop & 1] + g * S.chunk_stride, ((int64_t)n_h + kChunk - 1) / kChunk);
     if (threadIdx.x == 0) {
         G.indptr[g][n_h] = total;
         if (G.edges_out[g]) *G.edges_out[g] = total;
@@ -563,7 +594,7 @@ __global__ void __launch_bounds__(RG_WAVE) k_hop_sample_wave(const int32_t* __re
     const int32_t* __restrict__ nodes = G.nodes[g];
     int32_t* __restrict__ indptr = G.indptr[g];
     int32_t* __restrict__ nbr = G.nbr[g];
-    const int32_t* __restrict__ chunk_sum = S.chunk_sum + g * S.chunk_stride;
+    const int32_t* __restrict__ hop_sum = S.hop_sum[hop & 1] + g * S.chunk_stride;
     const int64_t* __restrict__ row_start = S.row_start + g * S.frontier_stride;
     const int32_t* __restrict__ row_deg = S.row_deg + g * S.frontier_stride;
     const uint32_t* __restrict__ visited = S.visited + g * S.words;
@@ -573,7 +604,7 @@ __global__ void __launch_bounds__(RG_WAVE) k_hop_sample_wave(const int32_t* __re
     for (int64_t i = blk; i < n_h; i += rg_blocks_per_batch(S)) {
         const int32_t v = nodes[i];
         const int64_t start = row_start[i], deg = row_deg[i];
-        const int base = indptr[i] + chunk_sum[i / kChunk];
+        const int base = indptr[i] + hop_sum[i / kChunk];
         __syncthreads();                               // every lane has read indptr[i] before it is rewritten
         if (lane == 0) indptr[i] = base;
         if (fanout < 0 || deg <= fanout) {             // whole row, CSR order
@@ -622,13 +653,32 @@ __global__ void __launch_bounds__(RG_WAVE) k_hop_sample_wave(const int32_t* __re
 constexpr int kDrawLoads = 8;
 constexpr int kDrawSelfScan = 16384;    // count chunks up to which a workgroup adds up those in front of its own itself
 
+// A thread's part (of a workgroup of 256) of the edges in front of frontier node `first`: the chunks in front of its own, then the
+// nodes in front of it within the chunk.
+__device__ __forceinline__ int rg_edges_before(const SampleScratch& S, int g, int hop, int64_t first, int fanout, int scanned) {
+    const int32_t* __restrict__ hop_sum = S.hop_sum[hop & 1] + g * S.chunk_stride;
+    const int32_t* __restrict__ row_deg = S.row_deg + g * S.frontier_stride;
+    const int chunk = (int)(first / kChunk);
+    int before = 0;
+    for (int64_t i = (int64_t)chunk * kChunk + threadIdx.x; i < first; i += 256) {
+        const int deg = row_deg[i];
+        before += deg <= fanout ? deg : fanout;
+    }
+    if (scanned) {
+        if (threadIdx.x == 0) before += hop_sum[chunk];
+    } else {
+        for (int c = threadIdx.x; c < chunk; c += 256) before += hop_sum[c];
+    }
+    return rg_wave_sum(before);
+}
+
 template <int KMAX, int NODES, int MODE>
 __global__ void __launch_bounds__(256) k_hop_sample_thread(const int32_t* __restrict__ col_idx, const SampleGroup G,
                                                            const SampleScratch S, int fanout, uint32_t hop, uint32_t k0,
                                                            uint32_t k1, uint32_t epoch, int scanned, int run) {
     extern __shared__ uint32_t staged[];                 // NODES * fanout col_idx offsets
     __shared__ int part[4];
-    __shared__ int end_s;
+    __shared__ int smem[5];
     int g;
     unsigned blk;
     rg_shared_rows(S, run, g, blk);
@@ -643,30 +693,24 @@ __global__ void __launch_bounds__(256) k_hop_sample_thread(const int32_t* __rest
         return;
     }
     int32_t* __restrict__ nbr = G.nbr[g];
-    const int32_t* __restrict__ chunk_sum = S.chunk_sum + g * S.chunk_stride;
     const uint32_t* __restrict__ visited = S.visited + g * S.words;
     uint32_t* __restrict__ marked = S.marked + g * S.words;
     int32_t* __restrict__ first_key = MODE == kTierFirstSeen ? S.first_key + g * S.num_nodes : nullptr;
     const int64_t i = first + threadIdx.x;
     const int k = fanout;
-    // edges in front of this count chunk
-    const int chunk = (int)(first / kChunk);
-    int before = 0;
-    if (scanned) {
-        if (threadIdx.x == 0) before = chunk_sum[chunk];
-    } else {
-        for (int c = threadIdx.x; c < chunk; c += 256) before += chunk_sum[c];
-    }
-    before = rg_wave_sum(before);
-    if (rg_lane() == 0) part[threadIdx.x >> 6] = before;
-    const int off0 = indptr[first];                      // of this workgroup's first node within the count chunk
     const int n_here = (int)(n_h - first < NODES ? n_h - first : NODES);
-    int off = 0;
+    int32_t v = 0;
+    int64_t start = 0, deg = 0;
     if ((int)threadIdx.x < n_here) {
-        const int32_t v = G.nodes[g][i];
-        const int64_t start = S.row_start[g * S.frontier_stride + i], deg = S.row_deg[g * S.frontier_stride + i];
-        off = indptr[i] - off0;
-        if ((int)threadIdx.x == n_here - 1) end_s = off + (int)(deg <= k ? deg : k);
+        v = G.nodes[g][i];
+        start = S.row_start[g * S.frontier_stride + i];
+        deg = S.row_deg[g * S.frontier_stride + i];
+    }
+    const int before = rg_edges_before(S, g, (int)hop, first, k, scanned);
+    if (rg_lane() == 0) part[threadIdx.x >> 6] = before;
+    int n_edges;
+    const int off = rg_block_excl_scan<4>((int)(deg <= k ? deg : k), smem, &n_edges);       // its barriers publish part[]
+    if ((int)threadIdx.x < n_here) {
         if (deg <= k) {                                  // whole row, CSR order
             for (int t = 0; t < (int)deg; ++t) staged[off + t] = (uint32_t)(start + t);
         } else {
@@ -696,8 +740,7 @@ __global__ void __launch_bounds__(256) k_hop_sample_thread(const int32_t* __rest
         }
     }
     __syncthreads();
-    const int base = part[0] + part[1] + part[2] + part[3] + off0;
-    const int n_edges = end_s;
+    const int base = part[0] + part[1] + part[2] + part[3];
     if ((int)threadIdx.x < n_here) indptr[i] = base + off;
     if (threadIdx.x == 0 && first + NODES >= n_h) {
         indptr[n_h] = base + n_edges;
@@ -728,6 +771,7 @@ __global__ void __launch_bounds__(256) k_hop_sample_lanes(const int32_t* __restr
     constexpr int NODES = 256 / KMAX;
     static_assert(RG_WAVE % KMAX == 0 && kChunk % NODES == 0, "a node's lanes share a wavefront, a workgroup's nodes a chunk");
     __shared__ int part[4];
+    __shared__ int smem[5];
     const int g = rg_batch(S);
     const unsigned blk = rg_block(S);
     const int n_h = G.tier_off[g][hop + 1];
@@ -740,22 +784,18 @@ __global__ void __launch_bounds__(256) k_hop_sample_lanes(const int32_t* __restr
         }
         return;
     }
-    const int32_t* __restrict__ chunk_sum = S.chunk_sum + g * S.chunk_stride;
     const int lane = (int)threadIdx.x & (KMAX - 1), k = fanout;
     const int64_t i = first + threadIdx.x / KMAX;
     const bool live = i < n_h;
     int32_t v = 0;
     int64_t start = 0, deg = 0;
-    int off = 0;
     if (live) {
         v = G.nodes[g][i];
         start = S.row_start[g * S.frontier_stride + i];
         deg = S.row_deg[g * S.frontier_stride + i];
-        off = indptr[i];
     }
-    int before = 0;                                      // edges in front of this count chunk
-    for (int c = threadIdx.x; c < (int)(first / kChunk); c += 256) before += chunk_sum[c];
-    before = rg_wave_sum(before);
+    const int m = (int)(deg <= k ? deg : k);
+    const int before = rg_edges_before(S, g, (int)hop, first, k, 0);
     if (rg_lane() == 0) part[threadIdx.x >> 6] = before;
     uint32_t at = (uint32_t)lane;                        // whole row, CSR order
     if (__any(live && deg > k)) {
@@ -777,10 +817,10 @@ __global__ void __launch_bounds__(256) k_hop_sample_lanes(const int32_t* __restr
         }
         if (deg > k) at = taken ? j : t;
     }
-    __syncthreads();
+    int total;
+    int off = rg_block_excl_scan<4>(lane == 0 ? m : 0, smem, &total);          // its barriers publish part[]
+    off = __shfl(off, 0, KMAX) + part[0] + part[1] + part[2] + part[3];
     if (!live) return;
-    off += part[0] + part[1] + part[2] + part[3];
-    const int m = (int)(deg <= k ? deg : k);
     if (lane == 0) {
         indptr[i] = off;
         if (i == n_h - 1) {
@@ -808,6 +848,8 @@ __global__ void __launch_bounds__(1024) k_slice_mark(const SampleGroup G, const 
     constexpr int U = 4;                                 // 16-byte loads in flight per thread
     const int g = rg_batch(S);
     const unsigned blk = rg_block(S);
+    int32_t* __restrict__ next_sum = S.hop_sum[(hop + 1) & 1] + g * S.chunk_stride;        // k_slice_emit adds to it
+    for (int64_t c = (int64_t)blk * 1024 + threadIdx.x; c < S.chunk_stride; c += (int64_t)rg_blocks_per_batch(S) * 1024) next_sum[c] = 0;
     const int slice = (int)(blk % (unsigned)S.slices), split = (int)(blk / (unsigned)S.slices);
     const int64_t w0 = (int64_t)slice * S.slice_words;
     const int n_words = (int)(S.words - w0 < S.slice_words ? S.words - w0 : S.slice_words);
@@ -851,11 +893,16 @@ __global__ void __launch_bounds__(1024) k_slice_mark(const SampleGroup G, const 
     for (int w = threadIdx.x; w < n_words; w += 1024) out[w] = slice_bits[w];
 }
 
-// W consecutive words from w on; words behind the end read as 0.
+// W consecutive words from w on; words behind the end read as 0 (`whole`, uniform: none are).
 template <int W>
-__device__ __forceinline__ void rg_load_words(const uint32_t* __restrict__ p, int64_t w, int64_t words, uint32_t (&x)[W]) {
+__device__ __forceinline__ void rg_load_words(const uint32_t* __restrict__ p, int64_t w, int64_t words, bool whole, uint32_t (&x)[W]) {
+    if (whole) {
 #pragma unroll
-    for (int q = 0; q < W; ++q) x[q] = w + q < words ? p[w + q] : 0u;
+        for (int q = 0; q < W; ++q) x[q] = p[w + q];
+    } else {
+#pragma unroll
+        for (int q = 0; q < W; ++q) x[q] = w + q < words ? p[w + q] : 0u;
+    }
 }
 
 // The splits' bitmaps -> the new tier's bits (into split 0) and the number of them per workgroup of T threads, W words each.
@@ -867,16 +914,20 @@ __global__ void __launch_bounds__(T) k_slice_count(const SampleScratch S) {
     const unsigned blk = rg_block(S);
     const int64_t w = ((int64_t)blk * T + threadIdx.x) * W;
     uint32_t* __restrict__ marks = S.slice_marks + (int64_t)g * S.splits * S.words;
+    const bool whole = ((int64_t)blk + 1) * T * W <= S.words;
     uint32_t bits[W], members[W];
-    rg_load_words<W>(S.visited + g * S.words, w, S.words, members);
-    rg_load_words<W>(marks, w, S.words, bits);
+    rg_load_words<W>(S.visited + g * S.words, w, S.words, whole, members);
+    rg_load_words<W>(marks, w, S.words, whole, bits);
+    const auto join = [&](bool all) {
 #pragma unroll 8
-    for (int s = 1; s < S.splits; ++s) {
-        uint32_t more[W];
-        rg_load_words<W>(marks + s * S.words, w, S.words, more);
+        for (int s = 1; s < S.splits; ++s) {
+            uint32_t more[W];
+            rg_load_words<W>(marks + s * S.words, w, S.words, all, more);
 #pragma unroll
-        for (int q = 0; q < W; ++q) bits[q] |= more[q];
-    }
+            for (int q = 0; q < W; ++q) bits[q] |= more[q];
+        }
+    };
+    if (whole) join(true); else join(false);
     int c = 0;
 #pragma unroll
     for (int q = 0; q < W; ++q) {
@@ -899,27 +950,54 @@ __global__ void __launch_bounds__(T) k_slice_count(const SampleScratch S) {
 // A thread takes W words: three, which are two rank blocks, or one where few workgroups leave the serial walk over the bits of a
 // word as what takes time; the words then meet in LDS.
 // RANKED_SEEN: the positions are ascending ones only, the nodes come later.
+// next_fanout >= 0: also what k_hop_count does for the next hop, the new nodes' rows here, where their ids are at hand and ascending, and
+// their edges per chunk; those of the nodes in front of them by the workgroups behind the tier_blocks.
 template <bool RANKED_SEEN, int T, int W>
-__device__ __forceinline__ void rg_slice_emit(const SampleGroup& G, const SampleScratch& S, int hop) {
-    constexpr int NW = T / RG_WAVE, kEmitIds = T * W * 32 / 3;
+__device__ __forceinline__ void rg_slice_emit(const RowPtr& row_ptr, const SampleGroup& G, const SampleScratch& S, int hop,
+                                              unsigned tier_blocks, int next_fanout, int run) {
+    constexpr int NW = T / RG_WAVE, kEmitIds = W == 1 ? T * 32 : T * W * 32 / 3;
     constexpr unsigned per_base = kBaseIds / (32 * T * W);               // workgroups to a base
     __shared__ int smem[NW + 1];
-    __shared__ int part[NW];
+    __shared__ int part[NW], part_above[NW];
     __shared__ int32_t ids[RANKED_SEEN ? 1 : kEmitIds];
     __shared__ uint32_t word_bits[W == 1 ? T : 1];
     __shared__ int word_rank[W == 1 ? T : 1];
-    const int g = rg_batch(S);
-    const unsigned blk = rg_block(S);
+    __shared__ int edges[T * W * 32 / kChunk + 2];
+    int g;
+    unsigned blk;
+    rg_shared_rows(S, run, g, blk);
+    int32_t* __restrict__ next_sum = S.hop_sum[(hop + 1) & 1] + g * S.chunk_stride;
+    if (!RANKED_SEEN && blk >= tier_blocks) {
+        const int chunk = (int)(blk - tier_blocks), n_h = G.tier_off[g][hop + 1];
+        if (chunk * kChunk >= n_h) return;                               // uniform
+        const int32_t* __restrict__ row_deg = S.row_deg + g * S.frontier_stride;
+        int m = 0;
+        for (int i = chunk * kChunk + threadIdx.x; i < n_h && i < (chunk + 1) * kChunk; i += T) {
+            const int deg = row_deg[i];
+            m += deg <= next_fanout ? deg : next_fanout;
+        }
+        m = rg_wave_sum(m);
+        if (rg_lane() == 0 && m) atomicAdd(&next_sum[chunk], m);
+        return;
+    }
+    if (!RANKED_SEEN) for (int i = threadIdx.x; i < (int)(sizeof(edges) / sizeof(int)); i += T) edges[i] = 0;
     const int64_t w = ((int64_t)blk * T + threadIdx.x) * W;
     const int32_t* __restrict__ chunk_sum = S.chunk_sum + g * S.chunk_stride;
     uint32_t* __restrict__ visited = S.visited + g * S.words;
     uint32_t bits[W], members[W];
-    rg_load_words<W>(S.slice_marks + (int64_t)g * S.splits * S.words, w, S.words, bits);
-    rg_load_words<W>(visited, w, S.words, members);
-    int before = 0;                                      // new ids in front of this workgroup's words
-    for (unsigned c = threadIdx.x; c < blk; c += T) before += chunk_sum[c];
+    const bool whole = ((int64_t)blk + 1) * T * W <= S.words;
+    rg_load_words<W>(S.slice_marks + (int64_t)g * S.splits * S.words, w, S.words, whole, bits);
+    rg_load_words<W>(visited, w, S.words, whole, members);
+    int before = 0, above = 0;                           // new ids in front of this workgroup's words, those behind the last base
+    const unsigned base_blk = blk / per_base * per_base;
+    for (unsigned c = threadIdx.x; c < blk; c += T) {
+        const int n = chunk_sum[c];
+        before += n;
+        if (c >= base_blk) above += n;
+    }
     before = rg_wave_sum(before);
-    if (rg_lane() == 0) part[threadIdx.x >> 6] = before;
+    above = rg_wave_sum(above);
+    if (rg_lane() == 0) { part[threadIdx.x >> 6] = before; part_above[threadIdx.x >> 6] = above; }
     int mine = 0;
 #pragma unroll
     for (int q = 0; q < W; ++q) mine += __popc(bits[q]);
@@ -928,10 +1006,11 @@ __device__ __forceinline__ void rg_slice_emit(const SampleGroup& G, const Sample
     int out = G.tier_off[g][hop + 1];
 #pragma unroll
     for (int q = 0; q < NW; ++q) out += part[q];
-    if (threadIdx.x == 0 && blk + 1 == rg_blocks_per_batch(S)) G.tier_off[g][hop + 2] = out + total;
-    int base = out;                                      // position of the first new id behind the last base's first id
-    for (unsigned c = blk / per_base * per_base; c < blk; ++c) base -= chunk_sum[c];
-    if (threadIdx.x == 0 && blk % per_base == 0) rg_rank_bases(S, g, hop)[blk / per_base] = base;
+    if (threadIdx.x == 0 && blk + 1 == tier_blocks) G.tier_off[g][hop + 2] = out + total;
+    int base = out;
+#pragma unroll
+    for (int q = 0; q < NW; ++q) base -= part_above[q];
+    if (threadIdx.x == 0 && blk == base_blk) rg_rank_bases(S, g, hop)[blk / per_base] = base;
     int32_t* __restrict__ nodes = G.nodes[g] + out;
     int32_t* dst = total <= kEmitIds ? ids : nodes;
     const RankBlocks rank = rg_rank_blocks(S, g, hop);
@@ -952,25 +1031,61 @@ __device__ __forceinline__ void rg_slice_emit(const SampleGroup& G, const Sample
         if (!RANKED_SEEN)
             for (uint32_t b = bits[q]; b; b &= b - 1u) dst[j++] = (int32_t)((w + q) << 5) + __ffs(b) - 1;
     }
-    if (W == 3 && (RANKED_SEEN || total > kEmitIds)) return;             // uniform
-    __syncthreads();
+    if (RANKED_SEEN && W == 3) return;
+    __syncthreads();                                     // ids, nodes, words and edges are there
     if (W == 1 && threadIdx.x < T / 3) {
         const int q = 3 * threadIdx.x;
         const int64_t r = (int64_t)blk * (T / 3) + threadIdx.x;
         if (3 * r < S.words) store_rank(r, word_bits[q], word_bits[q + 1], word_bits[q + 2], (uint32_t)word_rank[q]);
     }
-    if (RANKED_SEEN || total > kEmitIds) return;
-    for (int i = threadIdx.x; i < total; i += T) nodes[i] = ids[i];
+    if (RANKED_SEEN) return;
+    constexpr int U = 4;                                 // rows in flight per thread
+    int64_t* __restrict__ row_start = S.row_start + g * S.frontier_stride + out;
+    int32_t* __restrict__ row_deg = S.row_deg + g * S.frontier_stride + out;
+    for (int i0 = threadIdx.x; i0 < total; i0 += T * U) {
+        int32_t v[U];
+        int64_t start[U], deg[U];
+#pragma unroll
+        for (int q = 0; q < U; ++q) {
+            v[q] = -1;
+            if (i0 + T * q < total) v[q] = total <= kEmitIds ? ids[i0 + T * q] : nodes[i0 + T * q];
+        }
+        if (total <= kEmitIds) {
+#pragma unroll
+            for (int q = 0; q < U; ++q)
+                if (v[q] >= 0) nodes[i0 + T * q] = v[q];
+        }
+        if (next_fanout < 0) continue;
+        const auto rows = [&](auto* p) {
+#pragma unroll
+            for (int q = 0; q < U; ++q)
+                if (v[q] >= 0) rg_row_extent(p, v[q], start[q], deg[q]);
+        };
+        if (row_ptr.wide) rows((const int64_t*)row_ptr.p); else rows((const int32_t*)row_ptr.p);
+#pragma unroll
+        for (int q = 0; q < U; ++q)
+            if (v[q] >= 0) {
+                row_start[i0 + T * q] = start[q];
+                row_deg[i0 + T * q] = (int32_t)deg[q];
+                atomicAdd(&edges[(out + i0 + T * q) / kChunk - out / kChunk], (int)(deg[q] <= next_fanout ? deg[q] : next_fanout));
+            }
+    }
+    if (next_fanout < 0) return;
+    __syncthreads();
+    for (int i = threadIdx.x; i < (int)(sizeof(edges) / sizeof(int)); i += T)
+        if (edges[i]) atomicAdd(&next_sum[out / kChunk + i], edges[i]);
 }
 
 template <bool RANKED_SEEN>
-__global__ void __launch_bounds__(kTierWords / 3) k_slice_emit(const SampleGroup G, const SampleScratch S, int hop) {
-    rg_slice_emit<RANKED_SEEN, kTierWords / 3, 3>(G, S, hop);
+__global__ void __launch_bounds__(kTierWords / 3) k_slice_emit(const RowPtr row_ptr, const SampleGroup G, const SampleScratch S, int hop,
+                                                               unsigned tier_blocks, int next_fanout, int run) {
+    rg_slice_emit<RANKED_SEEN, kTierWords / 3, 3>(row_ptr, G, S, hop, tier_blocks, next_fanout, run);
 }
 
 template <bool RANKED_SEEN>
-__global__ void __launch_bounds__(kTierWordsSmall) k_slice_emit_small(const SampleGroup G, const SampleScratch S, int hop) {
-    rg_slice_emit<RANKED_SEEN, kTierWordsSmall, 1>(G, S, hop);
+__global__ void __launch_bounds__(kTierWordsSmall) k_slice_emit_small(const RowPtr row_ptr, const SampleGroup G, const SampleScratch S, int hop,
+                                                                      unsigned tier_blocks, int next_fanout, int run) {
+    rg_slice_emit<RANKED_SEEN, kTierWordsSmall, 1>(row_ptr, G, S, hop, tier_blocks, next_fanout, run);
 }
 
 // ---------------------------------------------------------------------------- per hop: new tier, from `marked`
@@ -1630,7 +1745,7 @@ rg_status rg_sampler_reserve(rg_ctx* ctx, int64_t num_nodes, int64_t max_frontie
     if ((st = rg_ensure(ctx, ctx->visited, g * S.words * 4)) != RG_OK) return st;
     if ((st = rg_ensure(ctx, ctx->marked, g * S.words * 4)) != RG_OK) return st;
     if ((st = rg_ensure(ctx, ctx->pos, g * (size_t)num_nodes * 4)) != RG_OK) return st;
-    if ((st = rg_ensure(ctx, ctx->chunk_sum, g * S.chunk_stride * 4)) != RG_OK) return st;
+    if ((st = rg_ensure(ctx, ctx->chunk_sum, 3 * g * S.chunk_stride * 4)) != RG_OK) return st;
     if ((st = rg_ensure(ctx, ctx->row_start, g * S.frontier_stride * 8)) != RG_OK) return st;
     if ((st = rg_ensure(ctx, ctx->row_deg, g * S.frontier_stride * 4)) != RG_OK) return st;
     // first-seen order: the first-edge keys must be all-zero between hops (every hop leaves them zeroed)
@@ -1826,6 +1941,8 @@ rg_status rg_sample_blocks_group(rg_ctx* ctx, const rg_csr* csr, int32_t group, 
     S.marked = (uint32_t*)ctx->marked.p;
     S.pos = (int32_t*)ctx->pos.p;
     S.chunk_sum = (int32_t*)ctx->chunk_sum.p;
+    S.hop_sum[0] = S.chunk_sum + group * S.chunk_stride;
+    S.hop_sum[1] = S.hop_sum[0] + group * S.chunk_stride;
     S.row_start = (int64_t*)ctx->row_start.p;
     S.row_deg = (int32_t*)ctx->row_deg.p;
     const uint32_t k0 = (uint32_t)(seed & 0xffffffffu), k1 = (uint32_t)(seed >> 32);
@@ -1878,8 +1995,15 @@ rg_status rg_sample_blocks_group(rg_ctx* ctx, const rg_csr* csr, int32_t group, 
         }
         ctx->sampler_dirty = true;       // cleared again when every launch of this call has been queued
     }
+    const RowPtr row_ptr = {csr->row_ptr, rp64};
+    // Hops that a thread or a few lanes per node draw for; these need no offsets per node.
+    const auto drawn_by_threads = [&](int h) { return fanouts[h] >= 1 && fanouts[h] <= 32 && csr->num_edges < (1ll << 32); };
+    int counted = -1;                                  // the hop whose sizes are there already
     if (rg_use_init(S.slices, group, seeds_max)) {
-        k_sample_init<<<(unsigned)S.slices * ug, 1024, (size_t)S.slice_words * 4, s>>>(G, S, mode == kTierAtomic ? 1 : 0);
+        const unsigned count_blocks = drawn_by_threads(0) ? (unsigned)rg_div_up(seeds_max, kChunk) : 0u;
+        const size_t lds = (size_t)rg_max64(S.slice_words, 1024 / RG_WAVE) * 4;
+        k_sample_init<<<((unsigned)S.slices + count_blocks) * ug, 1024, lds, s>>>(row_ptr, G, S, fanouts[0], mode == kTierAtomic ? 1 : 0);
+        if (count_blocks) counted = 0;
         RG_LAUNCH_CHECK(ctx, "k_sample_init");
     } else {
         const int64_t group_words = (int64_t)group * words;
@@ -1905,13 +2029,11 @@ rg_status rg_sample_blocks_group(rg_ctx* ctx, const rg_csr* csr, int32_t group, 
         RG_LAUNCH_CHECK(ctx, "k_relabel");
         return RG_OK;
     };
-    // Blocks of `per` frontier nodes and how they are dealt out (rg_shared_rows).
-    const auto shared_run = [&](int64_t frontier, int per, unsigned& grid) -> int {
-        const int64_t blocks = grid_for(frontier, per, 1ll << 30);
+    // How `blocks` workgroups per batch are dealt out (rg_shared_rows), `longest` consecutive ones at most.
+    const auto shared_run = [&](int64_t blocks, int64_t longest, unsigned& grid) -> int {
         grid = (unsigned)blocks * ug;
-        if (group == 1 || first_seen || !S.xcd_map) return 0;
-        const int64_t run = rg_min64(kSharedNodes / per, blocks / (8 * kXcds));
-        if (run < 1) return 0;
+        const int64_t run = rg_min64(longest, blocks / (8 * kXcds));
+        if (group == 1 || first_seen || !S.xcd_map || run < 1) return 0;
         grid = (unsigned)(rg_div_up(blocks, kXcds * run) * kXcds * run) * ug;
         return (int)run;
     };
@@ -1926,22 +2048,25 @@ rg_status rg_sample_blocks_group(rg_ctx* ctx, const rg_csr* csr, int32_t group, 
             R.nbr_local[h][g] = out[g].nbr_local && eub_max[h] > 0 ? out[g].nbr_local[h] : nullptr;
             if (R.nbr_local[h][g]) relabel_edges = rg_max64(relabel_edges, eub_max[h]);
         }
-        unsigned count_grid;
-        const int count_run = shared_run(fub_max[h], kChunk, count_grid);
-        if (rp64)
-            k_hop_count<int64_t><<<count_grid, kChunk / kCountNodes, 0, s>>>((const int64_t*)csr->row_ptr, G, S, h, fanouts[h], count_run);
-        else
-            k_hop_count<int32_t><<<count_grid, kChunk / kCountNodes, 0, s>>>((const int32_t*)csr->row_ptr, G, S, h, fanouts[h], count_run);
-        RG_LAUNCH_CHECK(ctx, "k_hop_count");
+        if (counted != h) {
+            unsigned count_grid;
+            const int count_run = shared_run(grid_for(fub_max[h], kChunk, 1ll << 30), kSharedNodes / kChunk, count_grid);
+            const int offsets = drawn_by_threads(h) ? 0 : 1;
+            if (rp64)
+                k_hop_count<int64_t><<<count_grid, kChunk / kCountNodes, 0, s>>>((const int64_t*)csr->row_ptr, G, S, h, fanouts[h], count_run, offsets);
+            else
+                k_hop_count<int32_t><<<count_grid, kChunk / kCountNodes, 0, s>>>((const int32_t*)csr->row_ptr, G, S, h, fanouts[h], count_run, offsets);
+            RG_LAUNCH_CHECK(ctx, "k_hop_count");
+        }
 
         const int F = fanouts[h];
-        if (F >= 1 && F <= 32 && csr->num_edges < (1ll << 32)) {
+        if (drawn_by_threads(h)) {
             const int tok = rg_prof_begin(ctx, RG_K_SAMPLE, s);
             // 64 nodes per workgroup while 256 would leave compute units without two workgroups (see the kernel)
             const bool few = rg_div_up(fub_max[h], 256) * group < 2ll * ctx->num_cus;
             const int nodes_per = few ? 64 : 256;
             unsigned draw_grid;
-            const int draw_run = shared_run(fub_max[h], nodes_per, draw_grid);
+            const int draw_run = shared_run(grid_for(fub_max[h], nodes_per, 1ll << 30), kSharedNodes / nodes_per, draw_grid);
             const size_t lds = (size_t)nodes_per * F * sizeof(uint32_t);
             const bool lanes = fub_max[h] * group * (F <= 8 ? 8 : F <= 16 ? 16 : 32) <= kLaneDraws;
             // Adding up grows with the square of the frontier, a scan costs 3 us for a small one: of 1 M nodes 172 / 175 us, of 8 M
@@ -1989,16 +2114,21 @@ rg_status rg_sample_blocks_group(rg_ctx* ctx, const rg_csr* csr, int32_t group, 
             const int64_t split_edges = rg_max64(kSplitEdges, 2 * (int64_t)S.slice_words);
             // (hubs among the frontier: up to eight times the edges of average nodes)
             S.splits = (int)rg_max64(1, rg_min64(rg_min64(eub_max[h], 8 * expected[h]) / split_edges, kSliceGroups / (S.slices * group)));
+            const bool small_tier = rg_div_up(words, kTierWords) * group < ctx->num_cus;
+            const unsigned tier_blocks = (unsigned)rg_max64(1, rg_div_up(words, small_tier ? kTierWordsSmall : kTierWords));
             k_slice_mark<<<(unsigned)(S.slices * S.splits) * ug, 1024, (size_t)S.slice_words * 4, s>>>(G, S, h);
             RG_LAUNCH_CHECK(ctx, "k_slice_mark");
-            const bool small_tier = rg_div_up(words, kTierWords) * group < ctx->num_cus;
-            const unsigned tier_blocks = (unsigned)rg_max64(1, rg_div_up(words, small_tier ? kTierWordsSmall : kTierWords)) * ug;
+            const bool count_next = mode == kTierSliced && h + 1 < num_hops && drawn_by_threads(h + 1);
+            const int next_fanout = count_next ? fanouts[h + 1] : -1;
+            unsigned emit_grid = tier_blocks * ug;
+            const int emit_run = count_next ? shared_run((int64_t)tier_blocks + rg_div_up(fub_max[h], kChunk), 1, emit_grid) : 0;
+            if (count_next) counted = h + 1;
 #define RG_LAUNCH_TIER(EMIT, T, W)                                                                                    \
     do {                                                                                                              \
-        k_slice_count<T, W><<<tier_blocks, T, 0, s>>>(S);                                                        \
+        k_slice_count<T, W><<<tier_blocks * ug, T, 0, s>>>(S);                                                        \
         RG_LAUNCH_CHECK(ctx, "k_slice_count");                                                                        \
-        if (mode == kTierSliced) EMIT<false><<<tier_blocks, T, 0, s>>>(G, S, h);             \
-        else EMIT<true><<<tier_blocks, T, 0, s>>>(G, S, h);                                   \
+        if (mode == kTierSliced) EMIT<false><<<emit_grid, T, 0, s>>>(row_ptr, G, S, h, tier_blocks, next_fanout, emit_run);             \
+        else EMIT<true><<<tier_blocks * ug, T, 0, s>>>(row_ptr, G, S, h, tier_blocks, -1, 0);                                   \
         RG_LAUNCH_CHECK(ctx, "k_slice_emit");                                                                         \
     } while (0)
             if (small_tier) RG_LAUNCH_TIER(k_slice_emit_small, kTierWordsSmall, 1); else RG_LAUNCH_TIER(k_slice_emit, kTierWords / 3, 3);
