@@ -54,9 +54,11 @@ struct rg_ctx {
     int64_t last_sample_nodes = 0; // input-node sets (rg_access_histogram_sampled), on graphs of this many nodes
     bool sampler_dirty = false;   // a sampling call was cut short by an error: the first-edge keys may hold stale entries
     // schedule scratch
-    RgBuf sched_keys;   // uint64[n]
-    RgBuf sched_ids;    // int32[n]
-    RgBuf sched_buckets; // int32: pairs per bucket, scatter cursors, bucket starts
+    RgBuf sched_pairs;  // {32 bits of the key, id} of every bucket, as many as it has room for
+    RgBuf sched_late;   // int32[n]: ids that found their bucket full
+    RgBuf sched_buckets; // int32: three sets of pairs per bucket, bucket starts
+    int sched_turn = 0;                 // the set of the next call
+    int64_t sched_dirty[2] = {0, 0};    // counters of a set that are not zero
     bool bounds_denied = false;   // hist_bounds could not be had (rg_reserve tries again)
     bool hist_reserved = false;   // rg_reserve has sized hist_bounds: calls take it as it is where it holds 128 batches
     RgBuf hist_bounds;  // int32: where the id ranges of the epoch histogram begin in the runs of some batches

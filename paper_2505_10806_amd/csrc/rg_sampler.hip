@@ -98,16 +98,17 @@ __device__ __forceinline__ void rg_row_extent(const RowPtr& row_ptr, int v, int6
 }
 
 // ---------------------------------------------------------------------------- schedule
-// The keys are Philox words, spread evenly whatever the ids, so their top bits are a perfect first radix digit: the (key, id)
-// pairs are counted into 2^log2_buckets buckets of about 1024-2048, scattered there, and every bucket is finished by one
-// workgroup in LDS (a second digit of kSubBits bits leaves about one pair per sub-bucket).  Three passes over the pairs in
-// place of the log^2 n passes of a sorting network: 4096 ids 43 -> 15 us, 1 M 394 -> 46, 8 M 2889 -> 347, 30 M 16.3 -> 3.4 ms.
-// Bound by launches and by the scattered 12-byte writes of the middle pass.
-constexpr int kSchedLds = 4096;          // pairs one workgroup sorts in LDS; a fuller bucket is sorted in place in HBM
+// The keys are Philox words, spread evenly whatever the ids, so their top bits are a perfect first radix digit: the pairs (32 more
+// bits of the key, id) go to one of 2^log2_buckets buckets, each of which has room for kSchedRoom of them where about 1024-2048
+// come, and every bucket is finished by one workgroup in LDS (a second digit of kSubBits bits leaves about one pair per sub-bucket;
+// pairs alike in the bits at hand have their keys worked out again).  Ids that find their bucket full, which only ids picked for
+// their keys do, wait in a list.  Nothing is counted beforehand: the keys are worked out once, and a call is two launches.
+// Bound by launches, the Philox blocks (3.3 us for 1 M ids on the whole device) and the scattered 8-byte writes.
+constexpr int kSchedLds = 4096;          // pairs one workgroup sorts in LDS
 constexpr int kSchedAvg = 2048;          // pairs per bucket on average, at most
-constexpr int kSchedChunk = 4096;        // ids per workgroup in the count and scatter kernels
+constexpr int kSchedRoom = 2560;         // eleven standard deviations more
 constexpr int kSchedLdsBuckets = 4096;   // buckets whose counters a workgroup keeps in LDS; with more (n > 8 Mi) every id
-                                         // adds to the counter in HBM
+                                         // adds to the counter in HBM, and the counters are scanned by a launch of their own
 constexpr int kSubBits = 11;
 
 __device__ __forceinline__ uint64_t rg_sched_key(int32_t v, uint32_t epoch, uint32_t k0, uint32_t k1) {
@@ -116,36 +117,9 @@ __device__ __forceinline__ uint64_t rg_sched_key(int32_t v, uint32_t epoch, uint
     return ((uint64_t)w[0] << 32) | (uint64_t)w[1];
 }
 
-__device__ __forceinline__ bool rg_pair_less(uint64_t ka, int32_t ia, uint64_t kb, int32_t ib) {
-    return ka < kb || (ka == kb && ia < ib);
-}
-
 __global__ void __launch_bounds__(256) k_sched_clear(int32_t* __restrict__ p, int64_t n) {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i < n) p[i] = 0;
-}
-
-template <bool LDS>
-__global__ void __launch_bounds__(256) k_sched_count(const int32_t* __restrict__ train_ids, int64_t n, int log2_buckets, uint32_t k0,
-                                                     uint32_t k1, uint32_t epoch, int32_t* __restrict__ count) {
-    __shared__ int32_t h[LDS ? kSchedLdsBuckets : 1];
-    const int buckets = 1 << log2_buckets;
-    if (LDS) {
-        for (int b = threadIdx.x; b < buckets; b += 256) h[b] = 0;
-        __syncthreads();
-    }
-    const int64_t i0 = (int64_t)blockIdx.x * kSchedChunk;
-#pragma unroll 4
-    for (int j = 0; j < kSchedChunk / 256; ++j) {
-        const int64_t i = i0 + j * 256 + threadIdx.x;
-        if (i >= n) break;
-        const int b = (int)(rg_sched_key(train_ids[i], epoch, k0, k1) >> (64 - log2_buckets));
-        atomicAdd(LDS ? &h[b] : &count[b], 1);
-    }
-    if (!LDS) return;
-    __syncthreads();
-    for (int b = threadIdx.x; b < buckets; b += 256)
-        if (h[b]) atomicAdd(&count[b], h[b]);
 }
 
 // start[b] = pairs in the buckets in front of b, start[buckets] = n.  One workgroup.
@@ -163,105 +137,128 @@ __global__ void __launch_bounds__(1024) k_sched_scan(const int32_t* __restrict__
     if (threadIdx.x == 0) start[buckets] = carry;
 }
 
-// Pairs go to their bucket's part of (keys, ids); the order inside a bucket is left to k_sched_sort.
-template <bool LDS>
-__global__ void __launch_bounds__(256) k_sched_scatter(const int32_t* __restrict__ train_ids, int64_t n, int log2_buckets, uint32_t k0,
-                                                       uint32_t k1, uint32_t epoch, const int32_t* __restrict__ start,
-                                                       int32_t* __restrict__ cursor, uint64_t* __restrict__ keys, int32_t* __restrict__ ids) {
+// Pairs go to their bucket; the order inside is left to k_sched_sort.  count[b] = pairs of bucket b, those without room among them;
+// count[buckets] = ids in the list `late`.  PER ids per thread.
+template <bool LDS, int PER>
+__global__ void __launch_bounds__(1024) k_sched_scatter(const int32_t* __restrict__ train_ids, int64_t n, int log2_buckets, uint32_t k0,
+                                                        uint32_t k1, uint32_t epoch, int32_t* __restrict__ count,
+                                                        uint2* __restrict__ pairs, int32_t* __restrict__ late) {
     __shared__ int32_t h[LDS ? kSchedLdsBuckets : 1];
     const int buckets = 1 << log2_buckets;
-    constexpr int PER = kSchedChunk / 256;
-    const int64_t i0 = (int64_t)blockIdx.x * kSchedChunk;
+    const int64_t i0 = (int64_t)blockIdx.x * (1024 * PER);
     int32_t v[PER];
     uint64_t key[PER];
 #pragma unroll
     for (int j = 0; j < PER; ++j) {
-        const int64_t i = i0 + j * 256 + threadIdx.x;
+        const int64_t i = i0 + j * 1024 + threadIdx.x;
         v[j] = i < n ? train_ids[i] : 0;
+    }
+    if (LDS) {
+        for (int b = threadIdx.x; b < buckets; b += 1024) h[b] = 0;
+        __syncthreads();
     }
 #pragma unroll
     for (int j = 0; j < PER; ++j) key[j] = rg_sched_key(v[j], epoch, k0, k1);
+    int32_t rank[PER];
+#pragma unroll
+    for (int j = 0; j < PER; ++j)
+        if (i0 + j * 1024 + threadIdx.x < n) rank[j] = atomicAdd(&(LDS ? h : count)[key[j] >> (64 - log2_buckets)], 1);
     if (LDS) {
-        int32_t rank[PER];
-        for (int b = threadIdx.x; b < buckets; b += 256) h[b] = 0;
         __syncthreads();
-#pragma unroll
-        for (int j = 0; j < PER; ++j)
-            if (i0 + j * 256 + threadIdx.x < n) rank[j] = atomicAdd(&h[(int)(key[j] >> (64 - log2_buckets))], 1);
+        for (int b = threadIdx.x; b < buckets; b += 1024)                // a place for this workgroup's pairs of the bucket
+            if (h[b]) h[b] = atomicAdd(&count[b], h[b]);
         __syncthreads();
-        for (int b = threadIdx.x; b < buckets; b += 256)                 // a place for this workgroup's pairs of the bucket
-            if (h[b]) h[b] = start[b] + atomicAdd(&cursor[b], h[b]);
-        __syncthreads();
+    }
 #pragma unroll
-        for (int j = 0; j < PER; ++j)
-            if (i0 + j * 256 + threadIdx.x < n) {
-                const int at = h[(int)(key[j] >> (64 - log2_buckets))] + rank[j];
-                keys[at] = key[j];
-                ids[at] = v[j];
-            }
-    } else {
-#pragma unroll
-        for (int j = 0; j < PER; ++j)
-            if (i0 + j * 256 + threadIdx.x < n) {
-                const int64_t b = (int64_t)(key[j] >> (64 - log2_buckets));
-                const int at = start[b] + atomicAdd(&cursor[b], 1);
-                keys[at] = key[j];
-                ids[at] = v[j];
-            }
+    for (int j = 0; j < PER; ++j) {
+        if (i0 + j * 1024 + threadIdx.x >= n) continue;
+        const int64_t b = (int64_t)(key[j] >> (64 - log2_buckets));
+        const int32_t at = (LDS ? h[b] : 0) + rank[j];
+        if (at < kSchedRoom) pairs[b * kSchedRoom + at] = make_uint2((uint32_t)(key[j] >> (32 - log2_buckets)), (uint32_t)v[j]);
+        else late[atomicAdd(&count[buckets], 1)] = v[j];
     }
 }
 
-// One workgroup per bucket: its pairs in order, the ids to their final places.  start == NULL: a single bucket, the n train
-// ids themselves.
+// One workgroup per bucket: its pairs in order, the ids to their final places.  CAP: pairs it has room for in LDS.
+// SINGLE: one bucket, the n train ids themselves.  start == NULL: the workgroup adds up the counts in front of its own.
+// `clear` (or NULL): n_clear counters that the next call will use.
+template <int CAP, bool SINGLE>
 __global__ void __launch_bounds__(512) k_sched_sort(const int32_t* __restrict__ train_ids, int64_t n, int log2_buckets, uint32_t k0,
-                                                    uint32_t k1, uint32_t epoch, const int32_t* __restrict__ start,
-                                                    uint64_t* __restrict__ keys, int32_t* __restrict__ ids, int32_t* __restrict__ order_out) {
-    constexpr int T = 512, PER = kSchedLds / T, SUB = 1 << kSubBits;
-    __shared__ uint64_t sk[kSchedLds];
-    __shared__ int32_t si[kSchedLds];
+                                                    uint32_t k1, uint32_t epoch, const int32_t* __restrict__ count,
+                                                    const int32_t* __restrict__ start, const uint2* __restrict__ pairs,
+                                                    const int32_t* __restrict__ late, int32_t* order_out,
+                                                    int32_t* __restrict__ clear, int n_clear) {
+    constexpr int T = 512, PER = CAP / T, SUB = 1 << kSubBits;
+    __shared__ uint32_t sk[CAP];
+    __shared__ int32_t si[CAP];
     __shared__ int32_t sub[SUB + 1];
     __shared__ int smem[T / RG_WAVE + 1];
-    const int64_t s0 = start ? start[blockIdx.x] : 0;
-    const int64_t m = (start ? start[blockIdx.x + 1] : n) - s0;
+    const int64_t bucket = blockIdx.x;
+    if (clear) for (int64_t i = bucket * T + threadIdx.x; i < n_clear; i += (int64_t)gridDim.x * T) clear[i] = 0;
+    int64_t s0 = 0, m = n;
+    if (!SINGLE) {
+        m = count[bucket];
+        if (start) {
+            s0 = start[bucket];
+        } else {
+            int before = 0, total;
+            for (int b = threadIdx.x; b < (int)bucket; b += T) before += count[b];
+            (void)rg_block_excl_scan<T / RG_WAVE>(before, smem, &total);
+            s0 = total;
+        }
+    }
     if (m == 0) return;                                                  // uniform
-    int32_t* __restrict__ out = order_out + s0;
-    if (m > kSchedLds) {
-        // Only ids picked for their keys get here.  Sorting network over the bucket in HBM, every comparison ascending, so that
-        // the places behind its end count as larger than everything and are never touched.
-        uint64_t* k = keys + s0;
-        int32_t* v = ids + s0;
-        int64_t size = 2 * kSchedLds;
+    int32_t* out = order_out + s0;
+    const auto full_key = [&](int32_t v) { return rg_sched_key(v, epoch, k0, k1); };
+    if (!SINGLE && m > kSchedRoom) {
+        // Only ids picked for their keys get here: the bucket's and those of the list that belong to it, sorted where they will be,
+        // by a network whose every comparison is ascending, so that the places behind its end count as larger than everything and are
+        // never touched.
+        int32_t* fill = sub;
+        if (threadIdx.x == 0) *fill = kSchedRoom;
+        for (int i = threadIdx.x; i < kSchedRoom; i += T) out[i] = (int32_t)pairs[bucket * kSchedRoom + i].y;
+        __syncthreads();
+        const int n_late = count[1ll << log2_buckets];
+        for (int i = threadIdx.x; i < n_late; i += T) {
+            const int32_t v = late[i];
+            if ((int64_t)(full_key(v) >> (64 - log2_buckets)) == bucket) out[atomicAdd(fill, 1)] = v;
+        }
+        int64_t size = 2;
         while (size < m) size <<= 1;
         for (int64_t w = 2; w <= size; w <<= 1)
             for (int64_t d = w - 1; d > 0; d = d == w - 1 ? w >> 2 : d >> 1) {
                 __syncthreads();
                 for (int64_t i = threadIdx.x; i < m; i += T) {
                     const int64_t l = i ^ d;
-                    if (l > i && l < m && rg_pair_less(k[l], v[l], k[i], v[i])) {
-                        const uint64_t kt = k[i]; k[i] = k[l]; k[l] = kt;
-                        const int32_t vt = v[i]; v[i] = v[l]; v[l] = vt;
-                    }
+                    if (l <= i || l >= m) continue;
+                    const int32_t a = out[i], b = out[l];
+                    const uint64_t ka = full_key(a), kb = full_key(b);
+                    if (kb < ka || (kb == ka && b < a)) { out[i] = b; out[l] = a; }
                 }
             }
-        __syncthreads();
-        for (int64_t i = threadIdx.x; i < m; i += T) out[i] = v[i];
         return;
     }
-    uint64_t key[PER];
+    uint32_t key[PER];
     int32_t id[PER], rank[PER];
     for (int b = threadIdx.x; b <= SUB; b += T) sub[b] = 0;
 #pragma unroll
     for (int j = 0; j < PER; ++j) {
         const int i = j * T + threadIdx.x;
         if (i < m) {
-            id[j] = start ? ids[s0 + i] : train_ids[i];
-            key[j] = start ? keys[s0 + i] : rg_sched_key(id[j], epoch, k0, k1);
+            if (SINGLE) {
+                id[j] = train_ids[i];
+                key[j] = (uint32_t)(full_key(id[j]) >> 32);
+            } else {
+                const uint2 x = pairs[bucket * kSchedRoom + i];
+                key[j] = x.x;
+                id[j] = (int32_t)x.y;
+            }
         }
     }
     __syncthreads();
 #pragma unroll
     for (int j = 0; j < PER; ++j)
-        if (j * T + (int)threadIdx.x < m) rank[j] = atomicAdd(&sub[(int)((key[j] << log2_buckets) >> (64 - kSubBits))], 1);
+        if (j * T + (int)threadIdx.x < m) rank[j] = atomicAdd(&sub[key[j] >> (32 - kSubBits)], 1);
     __syncthreads();
     int mine[SUB / T], sum = 0;                                          // counts -> starts, SUB / T consecutive ones per thread
 #pragma unroll
@@ -275,7 +272,7 @@ __global__ void __launch_bounds__(512) k_sched_sort(const int32_t* __restrict__ 
 #pragma unroll
     for (int j = 0; j < PER; ++j)
         if (j * T + (int)threadIdx.x < m) {
-            const int p = sub[(int)((key[j] << log2_buckets) >> (64 - kSubBits))] + rank[j];
+            const int p = sub[key[j] >> (32 - kSubBits)] + rank[j];
             sk[p] = key[j];
             si[p] = id[j];
         }
@@ -283,11 +280,17 @@ __global__ void __launch_bounds__(512) k_sched_sort(const int32_t* __restrict__ 
 #pragma unroll
     for (int j = 0; j < PER; ++j)
         if (j * T + (int)threadIdx.x < m) {
-            const int b = (int)((key[j] << log2_buckets) >> (64 - kSubBits));
+            const int b = (int)(key[j] >> (32 - kSubBits));
             const int lo = sub[b], hi = sub[b + 1], me = lo + rank[j];
             int place = lo;
-            for (int q = lo; q < hi; ++q)                                // (equal pairs, which distinct ids do not give, keep their places)
-                place += rg_pair_less(sk[q], si[q], key[j], id[j]) || (q < me && sk[q] == key[j] && si[q] == id[j]);
+            for (int q = lo; q < hi; ++q) {
+                if (sk[q] != key[j]) {
+                    place += sk[q] < key[j];
+                } else if (q != me) {                                    // (equal pairs, which distinct ids do not give, keep their places)
+                    const uint64_t mine_ = full_key(id[j]), other = full_key(si[q]);
+                    place += other != mine_ ? other < mine_ : (si[q] != id[j] ? si[q] < id[j] : q < me);
+                }
+            }
             out[place] = id[j];
         }
 }
@@ -1804,7 +1807,7 @@ rg_status rg_epoch_schedule(rg_ctx* ctx, const int32_t* train_ids, int64_t n, ui
     hipStream_t s = (hipStream_t)stream;
     const uint32_t k0 = (uint32_t)(seed & 0xffffffffu), k1 = (uint32_t)(seed >> 32);
     if (n <= kSchedLds) {
-        k_sched_sort<<<1, 512, 0, s>>>(train_ids, n, 0, k0, k1, epoch, nullptr, nullptr, nullptr, order_out);
+        k_sched_sort<kSchedLds, true><<<1, 512, 0, s>>>(train_ids, n, 0, k0, k1, epoch, nullptr, nullptr, nullptr, nullptr, order_out, nullptr, 0);
         RG_LAUNCH_CHECK(ctx, "k_sched_sort");
         return RG_OK;
     }
@@ -1813,28 +1816,46 @@ rg_status rg_epoch_schedule(rg_ctx* ctx, const int32_t* train_ids, int64_t n, ui
     const int64_t buckets = 1ll << lb;
     rg_status st;
     // sized for the largest n of as many buckets, so that a call of another such n, captured perhaps, allocates nothing
-    if ((st = rg_ensure(ctx, ctx->sched_keys, (size_t)(kSchedAvg * buckets) * 8)) != RG_OK) return st;
-    if ((st = rg_ensure(ctx, ctx->sched_ids, (size_t)(kSchedAvg * buckets) * 4)) != RG_OK) return st;
-    if ((st = rg_ensure(ctx, ctx->sched_buckets, (size_t)(3 * buckets + 1) * 4)) != RG_OK) return st;
-    uint64_t* keys = (uint64_t*)ctx->sched_keys.p;
-    int32_t* ids = (int32_t*)ctx->sched_ids.p;
-    int32_t* count = (int32_t*)ctx->sched_buckets.p;
-    int32_t* cursor = count + buckets;
-    int32_t* start = cursor + buckets;
-    const int g = (int)rg_div_up(n, kSchedChunk);
+    if ((st = rg_ensure(ctx, ctx->sched_pairs, (size_t)(kSchedRoom * buckets) * 8)) != RG_OK) return st;
+    if ((st = rg_ensure(ctx, ctx->sched_late, (size_t)(kSchedAvg * buckets) * 4)) != RG_OK) return st;
+    const void* counters = ctx->sched_buckets.p;
+    if ((st = rg_ensure(ctx, ctx->sched_buckets, (size_t)(4 * (buckets + 1)) * 4, true)) != RG_OK) return st;
+    if (ctx->sched_buckets.p != counters) ctx->sched_dirty[0] = ctx->sched_dirty[1] = 0;
+    uint2* pairs = (uint2*)ctx->sched_pairs.p;
+    int32_t* late = (int32_t*)ctx->sched_late.p;
+    // Three sets of counters, and the starts.  Calls take the first two in turn, each clearing the other one's for the next; a call that
+    // is recorded into a graph keeps to the third, which its replays clear themselves.
+    const int64_t set = (int64_t)(ctx->sched_buckets.bytes / 16);
+    const bool captured = rg_capturing(s);
+    const int turn = captured ? 2 : ctx->sched_turn, other = 1 - ctx->sched_turn;
+    int32_t* count = (int32_t*)ctx->sched_buckets.p + turn * set;
+    int32_t* start = buckets > kSchedLdsBuckets ? (int32_t*)ctx->sched_buckets.p + 3 * set : nullptr;
+    if (captured || ctx->sched_dirty[turn]) {            // (dirty: the call before this one ended with an error)
+        const int64_t to_clear = captured ? buckets + 1 : ctx->sched_dirty[turn];
+        k_sched_clear<<<(int)rg_div_up(to_clear, 256), 256, 0, s>>>(count, to_clear);
+        RG_LAUNCH_CHECK(ctx, "k_sched_clear");
+    }
+    if (!captured) ctx->sched_dirty[turn] = buckets + 1;
     const bool lds = buckets <= kSchedLdsBuckets;
-    k_sched_clear<<<(int)rg_div_up(2 * buckets, 256), 256, 0, s>>>(count, 2 * buckets);
-    RG_LAUNCH_CHECK(ctx, "k_sched_clear");
-    if (lds) k_sched_count<true><<<g, 256, 0, s>>>(train_ids, n, lb, k0, k1, epoch, count);
-    else k_sched_count<false><<<g, 256, 0, s>>>(train_ids, n, lb, k0, k1, epoch, count);
-    RG_LAUNCH_CHECK(ctx, "k_sched_count");
-    k_sched_scan<<<1, 1024, 0, s>>>(count, (int)buckets, start);
-    RG_LAUNCH_CHECK(ctx, "k_sched_scan");
-    if (lds) k_sched_scatter<true><<<g, 256, 0, s>>>(train_ids, n, lb, k0, k1, epoch, start, cursor, keys, ids);
-    else k_sched_scatter<false><<<g, 256, 0, s>>>(train_ids, n, lb, k0, k1, epoch, start, cursor, keys, ids);
+    // 1024 ids to a workgroup while that leaves compute units without one
+    const bool few = n <= 1024ll * ctx->num_cus;
+    const int g = (int)rg_div_up(n, few ? 1024 : 4096);
+    if (few) k_sched_scatter<true, 1><<<g, 1024, 0, s>>>(train_ids, n, lb, k0, k1, epoch, count, pairs, late);
+    else if (lds) k_sched_scatter<true, 4><<<g, 1024, 0, s>>>(train_ids, n, lb, k0, k1, epoch, count, pairs, late);
+    else k_sched_scatter<false, 4><<<g, 1024, 0, s>>>(train_ids, n, lb, k0, k1, epoch, count, pairs, late);
     RG_LAUNCH_CHECK(ctx, "k_sched_scatter");
-    k_sched_sort<<<(unsigned)buckets, 512, 0, s>>>(train_ids, n, lb, k0, k1, epoch, start, keys, ids, order_out);
+    if (start) {
+        k_sched_scan<<<1, 1024, 0, s>>>(count, (int)buckets, start);
+        RG_LAUNCH_CHECK(ctx, "k_sched_scan");
+    }
+    int32_t* clear = captured || !ctx->sched_dirty[other] ? nullptr : (int32_t*)ctx->sched_buckets.p + other * set;
+    k_sched_sort<kSchedRoom, false><<<(unsigned)buckets, 512, 0, s>>>(nullptr, n, lb, k0, k1, epoch, count, start, pairs, late, order_out, clear,
+                                                                      clear ? (int)ctx->sched_dirty[other] : 0);
     RG_LAUNCH_CHECK(ctx, "k_sched_sort");
+    if (!captured) {
+        ctx->sched_dirty[other] = 0;
+        ctx->sched_turn = other;
+    }
     return RG_OK;
 }
 

@@ -389,6 +389,34 @@ def test_captured_call_after_another_kind(B, warm_seeds, warm_fanouts, warm_seen
     ctx.close()
 
 
+@pytest.mark.parametrize("copies", [2560, 2561, 4000])
+def test_schedule_of_ids_given_many_times(ctx, copies):
+    """Seven ids a few thousand times each fill their buckets up to the last place and beyond; the others stay empty."""
+    ids = np.random.default_rng(copies).permutation(np.repeat(np.arange(7, dtype=np.int32) * 977, copies))
+    got = ctx.epoch_schedule(_i32(ids), 11, 3)
+    assert np.array_equal(got.cpu().numpy(), oracle.epoch_schedule(ids, 11, 3))
+
+
+def test_schedule_counters_between_calls(B):
+    """Calls of other sizes and replays of a recorded one, on one context: every call finds its counters cleared."""
+    ctx = B.Context(0)
+    sizes = [300_000, 9_000, 5_000, 4_097, 300_000, 70_000, 9_000]
+    ids = {n: np.random.default_rng(n).permutation(3 * n)[:n].astype(np.int32) for n in sizes}
+    dev = {n: _i32(ids[n]) for n in sizes}
+    want = {n: oracle.epoch_schedule(ids[n], 5, 2) for n in sizes}
+    ctx.epoch_schedule(dev[300_000], 5, 2)
+    recorded = torch.zeros(9_000, dtype=torch.int32, device=DEV)
+    graph = _captured(lambda: ctx.epoch_schedule(dev[9_000], 5, 2, recorded))
+    for n in sizes:
+        got = ctx.epoch_schedule(dev[n], 5, 2)
+        recorded.zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert np.array_equal(got.cpu().numpy(), want[n]), n
+        assert np.array_equal(recorded.cpu().numpy(), want[9_000]), n
+    ctx.close()
+
+
 def test_schedule_captured_after_a_smaller_one(B):
     """A schedule of no more than twice as many ids, up to the next power of two, finds the scratch of an earlier call."""
     few, many = 4097, 8192
