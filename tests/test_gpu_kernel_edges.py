@@ -389,6 +389,27 @@ def test_captured_call_after_another_kind(B, warm_seeds, warm_fanouts, warm_seen
     ctx.close()
 
 
+# A wavefront counts 64 words of ids, a word of all batches in a lane; the batches come in any order, some under one index.
+@pytest.mark.parametrize("n,group", [(31, 2), (2048, 16), (2049, 5), (70_001, 1), (70_001, 9)])
+def test_bitmap_counts_of_batches_in_any_order(B, ctx, n, group):
+    log(f"[bitmap counts] N={n} group={group}")
+    rng = np.random.default_rng(n + group)
+    rp = np.arange(n + 1, dtype=np.int64)
+    ci = rng.integers(0, n, n).astype(np.int32)
+    seeds = [rng.permutation(n)[:rng.integers(0, n // 2 + 1)].astype(np.int32) for _ in range(group)]
+    outs = [B.BlockBuffers(n, n, max(x.size, 1), (1,), DEV, with_local=False) for x in seeds]
+    ctx.sample_blocks_group(B.CsrGraph(torch.as_tensor(rp, device=DEV), _i32(ci)), [_i32(x) for x in seeds], (1,), 3, 1, outs)
+    index = [int(x) for x in rng.integers(0, max(2, group - 2), group)]
+    counts, first = torch.ones(n, dtype=torch.int32, device=DEV), torch.full((n,), 2, dtype=torch.int32, device=DEV)
+    ctx.access_histogram_sampled(group, counts, batch_index=index, first_batch=first)
+    want, want_first = np.ones(n, dtype=np.int64), np.full(n, 2, dtype=np.int64)
+    for x, b in zip(seeds, index):
+        named = np.union1d(x, ci[x])
+        want[named] += 1
+        want_first[named] = np.minimum(want_first[named], b)
+    assert np.array_equal(counts.cpu().numpy(), want) and np.array_equal(first.cpu().numpy(), want_first)
+
+
 @pytest.mark.parametrize("copies", [2560, 2561, 4000])
 def test_schedule_of_ids_given_many_times(ctx, copies):
     """Seven ids a few thousand times each fill their buckets up to the last place and beyond; the others stay empty."""
