@@ -5,6 +5,8 @@
 // three ways (TierMode below); a member's position comes from the tier's rank words or from `pos[v]`.  All sizes that
 // depend on the data (frontier and edge counts) stay on the device: launches are sized by static upper bounds and
 // kernels read the actual counts.
+#include <string.h>
+
 #include "rg_internal.h"
 
 namespace {
@@ -297,7 +299,7 @@ __global__ void __launch_bounds__(512) k_sched_sort(const int32_t* __restrict__ 
 
 // ---------------------------------------------------------------------------- batches of a group
 // Several batches are sampled by the same launches: blockIdx.y selects the batch, which brings its own outputs
-// (SampleGroup, passed by value) and its own slice of the scratch (SampleScratch).  Most kernels of one batch are
+// (BatchTable) and its own slice of the scratch (SampleScratch).  Most kernels of one batch are
 // far smaller than the device (hop 0 of a 4096-seed batch is 16 workgroups), so a group fills it better and pays
 // every launch once.
 constexpr int kMaxGroup = RG_MAX_GROUP;
@@ -305,18 +307,20 @@ constexpr unsigned kXcds = 8;
 constexpr int kSharedNodes = 4096;
 constexpr int64_t kLaneDraws = 1 << 18;
 
-struct SampleGroup {
-    const int32_t* seeds[kMaxGroup];
-    int32_t num_seeds[kMaxGroup];
-    int32_t* nodes[kMaxGroup];
-    int32_t* tier_off[kMaxGroup];
-    int32_t* indptr[kMaxGroup];       // of the current hop
-    int32_t* nbr[kMaxGroup];
-    int32_t* nbr_local[kMaxGroup];    // kTierRankedSeen only
-    int32_t* edges_out[kMaxGroup];    // may be NULL
+// The batches' buffers: a table of 8-byte entries, [field][batch].  It goes to the first kernel as an argument, which leaves a copy in the
+// scratch for the others: arguments are read over the host link, and every kilobyte of them costs a launch 1.4 us of
+// the host's time and 0.7 of the device's.
+enum BatchField { kSeeds, kNumSeeds, kNodes, kTierOff, kEdgesOut, kHopFields };      // then kIndptr, kNbr, kNbrLocal of every hop
+enum HopField { kIndptr, kNbr, kNbrLocal, kHopFieldCount };
+constexpr int kTableFew = 32, kTableSome = 128, kTableMost = 480;       // sizes of the argument: one batch of three hops takes 14 entries
+static_assert(kMaxGroup * (kHopFields + kHopFieldCount * RG_MAX_HOPS) <= kTableMost, "a table of the largest group");
+template <int N>
+struct BatchTable {
+    uint64_t v[N];
 };
 
 struct SampleScratch {
+    const uint64_t* table;
     uint32_t* visited;                // [group][words]
     uint32_t* marked;                 // kTierAtomic: [group][words], every id met
     uint32_t* slice_marks;            // kTierSliced: [group][splits][words], ids of a hop
@@ -335,8 +339,29 @@ struct SampleScratch {
     int slices, splits;               // of the marking pass: id ranges of slice_words bitmap words, parts of the edge list
     int slice_words;
     int group;                        // batches in this call
+    int table_entries;
     int xcd_map;                      // 1: consecutive workgroups belong to consecutive batches (see rg_batch)
 };
+
+// Entries of the table: read through the constant address space, so that a pointer is uniform, and used as an address of global memory
+// (a flat access is slower: 53 us against 44 in k_slice_mark).
+__device__ __forceinline__ int32_t* rg_global(uint64_t address) { return (int32_t*)(__attribute__((address_space(1))) int32_t*)address; }
+__device__ __forceinline__ uint64_t rg_entry(const SampleScratch& S, int field, int g) {
+    return ((const __attribute__((address_space(4))) uint64_t*)(uintptr_t)S.table)[field * S.group + g];
+}
+__device__ __forceinline__ int32_t* rg_nodes(const SampleScratch& S, int g) { return rg_global(rg_entry(S, kNodes, g)); }
+__device__ __forceinline__ int32_t* rg_tier_off(const SampleScratch& S, int g) { return rg_global(rg_entry(S, kTierOff, g)); }
+__device__ __forceinline__ int32_t* rg_hop_list(const SampleScratch& S, int g, int hop, HopField f) {
+    return rg_global(rg_entry(S, kHopFields + kHopFieldCount * hop + f, g));
+}
+__device__ __forceinline__ void rg_put_edges(const SampleScratch& S, int g, int hop, int edges) {
+    int32_t* out = rg_global(rg_entry(S, kEdgesOut, g));               // may be NULL
+    if (out) out[hop] = edges;
+}
+template <int N>
+__device__ __forceinline__ void rg_copy_table(const SampleScratch& S, const BatchTable<N>& B) {
+    for (int i = threadIdx.x; i < S.table_entries; i += blockDim.x) ((uint64_t*)S.table)[i] = B.v[i];
+}
 
 // Workgroup -> (batch, block within the batch) for the per-batch kernels, launched as one 1-D grid of blocks x group
 // workgroups.  The device hands consecutive workgroup ids to its 8 XCDs in turn, and every XCD has an L2 of its own.
@@ -392,19 +417,25 @@ __global__ void __launch_bounds__(256) k_clear_words(uint32_t* __restrict__ w, i
     if (i < n) w[i] = 0u;
 }
 
-__global__ void __launch_bounds__(256) k_mark_seeds(const SampleGroup G, const SampleScratch S) {
+template <int N>
+__device__ __forceinline__ void rg_mark_seeds(const BatchTable<N>& B, const SampleScratch& S) {
     const int g = rg_batch(S);
     const unsigned blk = rg_block(S);
-    const int num_seeds = G.num_seeds[g];
+    if (blockIdx.x == 0) rg_copy_table(S, B);
+    const int num_seeds = (int)B.v[kNumSeeds * S.group + g];
     const int i = blk * blockDim.x + threadIdx.x;
-    if (i == 0) { G.tier_off[g][0] = 0; G.tier_off[g][1] = num_seeds; }
+    int32_t* __restrict__ tier_off = rg_global(B.v[kTierOff * S.group + g]);
+    if (i == 0) { tier_off[0] = 0; tier_off[1] = num_seeds; }
     if (i >= num_seeds) return;
-    const int32_t v = G.seeds[g][i];
-    G.nodes[g][i] = v;
+    const int32_t v = rg_global(B.v[kSeeds * S.group + g])[i];
+    rg_global(B.v[kNodes * S.group + g])[i] = v;
     S.pos[g * S.num_nodes + v] = i;
     atomicOr(&S.visited[g * S.words + ((uint32_t)v >> 5)], 1u << (v & 31));
     atomicOr(&S.marked[g * S.words + ((uint32_t)v >> 5)], 1u << (v & 31));
 }
+
+__global__ void __launch_bounds__(256) k_mark_seeds(const BatchTable<kTableSome> B, const SampleScratch S) { rg_mark_seeds(B, S); }
+__global__ void __launch_bounds__(256) k_mark_seeds_most(const BatchTable<kTableMost> B, const SampleScratch S) { rg_mark_seeds(B, S); }
 
 // The same in one launch for graphs of up to kMaxSlices slices: a workgroup owns one slice of a batch's ids, collects the
 // seeds of its range in LDS and writes its part of `visited`.
@@ -417,18 +448,21 @@ inline bool rg_use_init(int slices, int group, int64_t seeds) {
     return slices > 0 && (seeds <= 8192 || (group >= 4 && slices * group >= 32));
 }
 // The workgroups behind the slices do for the seeds what k_hop_count does.
-__global__ void __launch_bounds__(1024) k_sample_init(const RowPtr row_ptr, const SampleGroup G, const SampleScratch S, int fanout, int copy) {
+template <int N>
+__device__ __forceinline__ void rg_sample_init(const RowPtr& row_ptr, const BatchTable<N>& B, const SampleScratch& S, int fanout, int copy) {
     extern __shared__ uint32_t slice_bits[];
     const int g = rg_batch(S);
     const unsigned slice = rg_block(S);
-    const int num_seeds = G.num_seeds[g];
+    if (blockIdx.x == 0) rg_copy_table(S, B);
+    const int num_seeds = (int)B.v[kNumSeeds * S.group + g];
+    const int32_t* __restrict__ seeds = rg_global(B.v[kSeeds * S.group + g]);
     if (slice >= (unsigned)S.slices) {
         const unsigned chunk = slice - (unsigned)S.slices;
         const int i = (int)(chunk * kChunk + threadIdx.x);
         int m = 0;
         if (i < num_seeds) {
             int64_t start, deg;
-            rg_row_extent(row_ptr, G.seeds[g][i], start, deg);
+            rg_row_extent(row_ptr, seeds[i], start, deg);
             S.row_start[g * S.frontier_stride + i] = start;
             S.row_deg[g * S.frontier_stride + i] = (int32_t)deg;
             m = deg <= fanout ? (int)deg : fanout;
@@ -445,14 +479,16 @@ __global__ void __launch_bounds__(1024) k_sample_init(const RowPtr row_ptr, cons
     const int64_t w0 = (int64_t)slice * S.slice_words;
     const int n_words = (int)(S.words - w0 < S.slice_words ? S.words - w0 : S.slice_words);
     for (int w = threadIdx.x; w < n_words; w += 1024) slice_bits[w] = 0u;
-    if (slice == 0 && threadIdx.x == 0) { G.tier_off[g][0] = 0; G.tier_off[g][1] = num_seeds; }
+    int32_t* __restrict__ tier_off = rg_global(B.v[kTierOff * S.group + g]);
+    int32_t* __restrict__ nodes = rg_global(B.v[kNodes * S.group + g]);
+    if (slice == 0 && threadIdx.x == 0) { tier_off[0] = 0; tier_off[1] = num_seeds; }
     __syncthreads();
     const uint32_t id0 = (uint32_t)(w0 << 5), n_ids = (uint32_t)n_words << 5;
     for (int i = threadIdx.x; i < num_seeds; i += 1024) {
-        const int32_t v = G.seeds[g][i];
+        const int32_t v = seeds[i];
         const uint32_t d = (uint32_t)v - id0;
         if (d >= n_ids) continue;
-        G.nodes[g][i] = v;
+        nodes[i] = v;
         S.pos[g * S.num_nodes + v] = i;
         atomicOr(&slice_bits[d >> 5], 1u << (d & 31u));
     }
@@ -465,6 +501,13 @@ __global__ void __launch_bounds__(1024) k_sample_init(const RowPtr row_ptr, cons
     }
 }
 
+__global__ void __launch_bounds__(1024) k_sample_init(const RowPtr row_ptr, const BatchTable<kTableSome> B, const SampleScratch S, int fanout, int copy) {
+    rg_sample_init(row_ptr, B, S, fanout, copy);
+}
+__global__ void __launch_bounds__(1024) k_sample_init_most(const RowPtr row_ptr, const BatchTable<kTableMost> B, const SampleScratch S, int fanout, int copy) {
+    rg_sample_init(row_ptr, B, S, fanout, copy);
+}
+
 // ---------------------------------------------------------------------------- per hop: sizes
 // hop_sum[b] = edges of the kChunk nodes from b * kChunk on; row_start[i], row_deg[i] = the node's adjacency row; indptr[i] (where
 // `offsets` asks for it) = exclusive prefix of m within the node's chunk.  Bound by the random row_ptr lines, so every thread has
@@ -472,19 +515,19 @@ __global__ void __launch_bounds__(1024) k_sample_init(const RowPtr row_ptr, cons
 constexpr int kCountNodes = 4;
 
 template <typename RP>
-__global__ void __launch_bounds__(kChunk / kCountNodes) k_hop_count(const RP* __restrict__ row_ptr, const SampleGroup G, const SampleScratch S,
+__global__ void __launch_bounds__(kChunk / kCountNodes) k_hop_count(const RP* __restrict__ row_ptr, const SampleScratch S,
                                                                     int hop, int fanout, int run, int offsets) {
     constexpr int T = kChunk / kCountNodes, NW = T / RG_WAVE;
     __shared__ int smem[NW + 1];
     int g;
     unsigned blk;
     rg_shared_rows(S, run, g, blk);
-    const int n_h = G.tier_off[g][hop + 1];
+    const int n_h = rg_tier_off(S, g)[hop + 1];
     const int64_t first = (int64_t)blk * kChunk;
     if (first >= n_h) return;                       // uniform per workgroup
     const int n_here = (int)(n_h - first < kChunk ? n_h - first : kChunk);
-    const int32_t* __restrict__ nodes = G.nodes[g] + first;
-    int32_t* __restrict__ indptr = G.indptr[g] + first;
+    const int32_t* __restrict__ nodes = rg_nodes(S, g) + first;
+    int32_t* __restrict__ indptr = rg_hop_list(S, g, (int)hop, kIndptr) + first;
     int64_t* __restrict__ row_start = S.row_start + g * S.frontier_stride + first;
     int32_t* __restrict__ row_deg = S.row_deg + g * S.frontier_stride + first;
     int32_t v[kCountNodes];
@@ -547,21 +590,21 @@ __device__ __forceinline__ int rg_scan_in_place(int32_t* __restrict__ data, int6
 
 // Chunk totals of a hop -> exclusive offsets; the hop's edge total goes behind the last indptr entry.  In front of the
 // wavefront-per-node draw, and of the thread-per-node draw on frontiers of over kDrawSelfScan chunks.
-__global__ void __launch_bounds__(1024) k_scan_hop(const SampleGroup G, const SampleScratch S, int hop) {
+__global__ void __launch_bounds__(1024) k_scan_hop(const SampleScratch S, int hop) {
     const int g = rg_batch(S);
-    const int n_h = G.tier_off[g][hop + 1];
+    const int n_h = rg_tier_off(S, g)[hop + 1];
     const int total = rg_scan_in_place(S.hop_sum[hop & 1] + g * S.chunk_stride, ((int64_t)n_h + kChunk - 1) / kChunk);
     if (threadIdx.x == 0) {
-        G.indptr[g][n_h] = total;
-        if (G.edges_out[g]) *G.edges_out[g] = total;
+        rg_hop_list(S, g, hop, kIndptr)[n_h] = total;
+        rg_put_edges(S, g, hop, total);
     }
 }
 
 // Per-block counts of fresh ids -> exclusive offsets; the end of the new tier goes to tier_off[hop + 2].
-__global__ void __launch_bounds__(1024) k_scan_tier(const SampleGroup G, const SampleScratch S, int hop, int tier_blocks) {
+__global__ void __launch_bounds__(1024) k_scan_tier(const SampleScratch S, int hop, int tier_blocks) {
     const int g = rg_batch(S);
     const int total = rg_scan_in_place(S.chunk_sum + g * S.chunk_stride, tier_blocks);
-    if (threadIdx.x == 0) G.tier_off[g][hop + 2] = G.tier_off[g][hop + 1] + total;
+    if (threadIdx.x == 0) rg_tier_off(S, g)[hop + 2] = rg_tier_off(S, g)[hop + 1] + total;
 }
 
 // ---------------------------------------------------------------------------- per hop: draw + read
@@ -586,17 +629,16 @@ __device__ __forceinline__ void rg_note_first_edge(int32_t u, int64_t e, const u
 // General sampler: one wavefront (= one 64-thread workgroup) per frontier node, any fan-out up to
 // RG_MAX_FANOUT.  The Floyd set lives in LDS; step i tests membership of t with all lanes.
 template <int MODE>
-__global__ void __launch_bounds__(RG_WAVE) k_hop_sample_wave(const int32_t* __restrict__ col_idx, const SampleGroup G,
-                                                            const SampleScratch S, int fanout, uint32_t hop, uint32_t k0,
+__global__ void __launch_bounds__(RG_WAVE) k_hop_sample_wave(const int32_t* __restrict__ col_idx, const SampleScratch S, int fanout, uint32_t hop, uint32_t k0,
                                                             uint32_t k1, uint32_t epoch) {
     __shared__ uint32_t draws[RG_MAX_FANOUT];
     __shared__ uint32_t chosen[RG_MAX_FANOUT];
     const int g = rg_batch(S);
     const unsigned blk = rg_block(S);
-    const int n_h = G.tier_off[g][hop + 1];
-    const int32_t* __restrict__ nodes = G.nodes[g];
-    int32_t* __restrict__ indptr = G.indptr[g];
-    int32_t* __restrict__ nbr = G.nbr[g];
+    const int n_h = rg_tier_off(S, g)[hop + 1];
+    const int32_t* __restrict__ nodes = rg_nodes(S, g);
+    int32_t* __restrict__ indptr = rg_hop_list(S, g, (int)hop, kIndptr);
+    int32_t* __restrict__ nbr = rg_hop_list(S, g, (int)hop, kNbr);
     const int32_t* __restrict__ hop_sum = S.hop_sum[hop & 1] + g * S.chunk_stride;
     const int64_t* __restrict__ row_start = S.row_start + g * S.frontier_stride;
     const int32_t* __restrict__ row_deg = S.row_deg + g * S.frontier_stride;
@@ -676,8 +718,7 @@ __device__ __forceinline__ int rg_edges_before(const SampleScratch& S, int g, in
 }
 
 template <int KMAX, int NODES, int MODE>
-__global__ void __launch_bounds__(256) k_hop_sample_thread(const int32_t* __restrict__ col_idx, const SampleGroup G,
-                                                           const SampleScratch S, int fanout, uint32_t hop, uint32_t k0,
+__global__ void __launch_bounds__(256) k_hop_sample_thread(const int32_t* __restrict__ col_idx, const SampleScratch S, int fanout, uint32_t hop, uint32_t k0,
                                                            uint32_t k1, uint32_t epoch, int scanned, int run) {
     extern __shared__ uint32_t staged[];                 // NODES * fanout col_idx offsets
     __shared__ int part[4];
@@ -685,17 +726,17 @@ __global__ void __launch_bounds__(256) k_hop_sample_thread(const int32_t* __rest
     int g;
     unsigned blk;
     rg_shared_rows(S, run, g, blk);
-    const int n_h = G.tier_off[g][hop + 1];
-    int32_t* __restrict__ indptr = G.indptr[g];
+    const int n_h = rg_tier_off(S, g)[hop + 1];
+    int32_t* __restrict__ indptr = rg_hop_list(S, g, (int)hop, kIndptr);
     const int64_t first = (int64_t)blk * NODES;
     if (first >= n_h) {                                  // uniform per workgroup
         if (n_h == 0 && blk == 0 && threadIdx.x == 0) {
             indptr[0] = 0;
-            if (G.edges_out[g]) *G.edges_out[g] = 0;
+            rg_put_edges(S, g, (int)hop, 0);
         }
         return;
     }
-    int32_t* __restrict__ nbr = G.nbr[g];
+    int32_t* __restrict__ nbr = rg_hop_list(S, g, (int)hop, kNbr);
     const uint32_t* __restrict__ visited = S.visited + g * S.words;
     uint32_t* __restrict__ marked = S.marked + g * S.words;
     int32_t* __restrict__ first_key = MODE == kTierFirstSeen ? S.first_key + g * S.num_nodes : nullptr;
@@ -705,7 +746,7 @@ __global__ void __launch_bounds__(256) k_hop_sample_thread(const int32_t* __rest
     int32_t v = 0;
     int64_t start = 0, deg = 0;
     if ((int)threadIdx.x < n_here) {
-        v = G.nodes[g][i];
+        v = rg_nodes(S, g)[i];
         start = S.row_start[g * S.frontier_stride + i];
         deg = S.row_deg[g * S.frontier_stride + i];
     }
@@ -747,7 +788,7 @@ __global__ void __launch_bounds__(256) k_hop_sample_thread(const int32_t* __rest
     if ((int)threadIdx.x < n_here) indptr[i] = base + off;
     if (threadIdx.x == 0 && first + NODES >= n_h) {
         indptr[n_h] = base + n_edges;
-        if (G.edges_out[g]) *G.edges_out[g] = base + n_edges;
+        rg_put_edges(S, g, (int)hop, base + n_edges);
     }
     for (int e0 = threadIdx.x; e0 < n_edges; e0 += 256 * kDrawLoads) {
         int32_t u[kDrawLoads];
@@ -768,8 +809,7 @@ __global__ void __launch_bounds__(256) k_hop_sample_thread(const int32_t* __rest
 // The same for few frontier nodes: KMAX lanes per node, one draw each, no staging.  Floyd's set by itself: draw s is taken already if an
 // earlier draw has its value, or if its value is the last position j_l of an earlier step l that found its own draw taken.
 template <int KMAX, int MODE>
-__global__ void __launch_bounds__(256) k_hop_sample_lanes(const int32_t* __restrict__ col_idx, const SampleGroup G,
-                                                          const SampleScratch S, int fanout, uint32_t hop, uint32_t k0,
+__global__ void __launch_bounds__(256) k_hop_sample_lanes(const int32_t* __restrict__ col_idx, const SampleScratch S, int fanout, uint32_t hop, uint32_t k0,
                                                           uint32_t k1, uint32_t epoch) {
     constexpr int NODES = 256 / KMAX;
     static_assert(RG_WAVE % KMAX == 0 && kChunk % NODES == 0, "a node's lanes share a wavefront, a workgroup's nodes a chunk");
@@ -777,13 +817,13 @@ __global__ void __launch_bounds__(256) k_hop_sample_lanes(const int32_t* __restr
     __shared__ int smem[5];
     const int g = rg_batch(S);
     const unsigned blk = rg_block(S);
-    const int n_h = G.tier_off[g][hop + 1];
-    int32_t* __restrict__ indptr = G.indptr[g];
+    const int n_h = rg_tier_off(S, g)[hop + 1];
+    int32_t* __restrict__ indptr = rg_hop_list(S, g, (int)hop, kIndptr);
     const int64_t first = (int64_t)blk * NODES;
     if (first >= n_h) {                                  // uniform per workgroup
         if (n_h == 0 && blk == 0 && threadIdx.x == 0) {
             indptr[0] = 0;
-            if (G.edges_out[g]) *G.edges_out[g] = 0;
+            rg_put_edges(S, g, (int)hop, 0);
         }
         return;
     }
@@ -793,7 +833,7 @@ __global__ void __launch_bounds__(256) k_hop_sample_lanes(const int32_t* __restr
     int32_t v = 0;
     int64_t start = 0, deg = 0;
     if (live) {
-        v = G.nodes[g][i];
+        v = rg_nodes(S, g)[i];
         start = S.row_start[g * S.frontier_stride + i];
         deg = S.row_deg[g * S.frontier_stride + i];
     }
@@ -828,12 +868,12 @@ __global__ void __launch_bounds__(256) k_hop_sample_lanes(const int32_t* __restr
         indptr[i] = off;
         if (i == n_h - 1) {
             indptr[n_h] = off + m;
-            if (G.edges_out[g]) *G.edges_out[g] = off + m;
+            rg_put_edges(S, g, (int)hop, off + m);
         }
     }
     if (lane >= m) return;
     const int32_t u = col_idx[start + at];
-    G.nbr[g][off + lane] = u;
+    rg_hop_list(S, g, (int)hop, kNbr)[off + lane] = u;
     if (MODE == kTierFirstSeen) rg_note_first_edge(u, off + lane, S.visited + g * S.words, S.first_key + g * S.num_nodes);
     if (MODE == kTierAtomic) rg_mark(u, S.marked + g * S.words);
 }
@@ -846,7 +886,7 @@ __device__ __forceinline__ void rg_slice_or(uint32_t* bits, int32_t u, uint32_t 
     if (d < n_ids) atomicOr(&bits[d >> 5], 1u << (d & 31u));
 }
 
-__global__ void __launch_bounds__(1024) k_slice_mark(const SampleGroup G, const SampleScratch S, int hop) {
+__global__ void __launch_bounds__(1024) k_slice_mark(const SampleScratch S, int hop) {
     extern __shared__ uint32_t slice_bits[];
     constexpr int U = 4;                                 // 16-byte loads in flight per thread
     const int g = rg_batch(S);
@@ -857,10 +897,10 @@ __global__ void __launch_bounds__(1024) k_slice_mark(const SampleGroup G, const 
     const int64_t w0 = (int64_t)slice * S.slice_words;
     const int n_words = (int)(S.words - w0 < S.slice_words ? S.words - w0 : S.slice_words);
     for (int w = threadIdx.x; w < n_words; w += 1024) slice_bits[w] = 0u;
-    const int64_t n_edges = G.indptr[g][G.tier_off[g][hop + 1]];
+    const int64_t n_edges = rg_hop_list(S, g, (int)hop, kIndptr)[rg_tier_off(S, g)[hop + 1]];
     const int64_t e0 = n_edges * split / S.splits;
     const int n = (int)(n_edges * (split + 1) / S.splits - e0);
-    const int32_t* __restrict__ nbr = G.nbr[g] + e0;
+    const int32_t* __restrict__ nbr = rg_hop_list(S, g, (int)hop, kNbr) + e0;
     const uint32_t id0 = (uint32_t)(w0 << 5), n_ids = (uint32_t)n_words << 5;
     __syncthreads();
     // the list may start at any 4-byte address: single ids up to the first 16-byte boundary and behind the last one
@@ -956,7 +996,7 @@ __global__ void __launch_bounds__(T) k_slice_count(const SampleScratch S) {
 // next_fanout >= 0: also what k_hop_count does for the next hop, the new nodes' rows here, where their ids are at hand and ascending, and
 // their edges per chunk; those of the nodes in front of them by the workgroups behind the tier_blocks.
 template <bool RANKED_SEEN, int T, int W>
-__device__ __forceinline__ void rg_slice_emit(const RowPtr& row_ptr, const SampleGroup& G, const SampleScratch& S, int hop,
+__device__ __forceinline__ void rg_slice_emit(const RowPtr& row_ptr, const SampleScratch& S, int hop,
                                               unsigned tier_blocks, int next_fanout, int run) {
     constexpr int NW = T / RG_WAVE, kEmitIds = W == 1 ? T * 32 : T * W * 32 / 3;
     constexpr unsigned per_base = kBaseIds / (32 * T * W);               // workgroups to a base
@@ -971,7 +1011,7 @@ __device__ __forceinline__ void rg_slice_emit(const RowPtr& row_ptr, const Sampl
     rg_shared_rows(S, run, g, blk);
     int32_t* __restrict__ next_sum = S.hop_sum[(hop + 1) & 1] + g * S.chunk_stride;
     if (!RANKED_SEEN && blk >= tier_blocks) {
-        const int chunk = (int)(blk - tier_blocks), n_h = G.tier_off[g][hop + 1];
+        const int chunk = (int)(blk - tier_blocks), n_h = rg_tier_off(S, g)[hop + 1];
         if (chunk * kChunk >= n_h) return;                               // uniform
         const int32_t* __restrict__ row_deg = S.row_deg + g * S.frontier_stride;
         int m = 0;
@@ -1006,15 +1046,15 @@ __device__ __forceinline__ void rg_slice_emit(const RowPtr& row_ptr, const Sampl
     for (int q = 0; q < W; ++q) mine += __popc(bits[q]);
     int total;
     int j = rg_block_excl_scan<NW>(mine, smem, &total);                        // its barriers publish part[]
-    int out = G.tier_off[g][hop + 1];
+    int out = rg_tier_off(S, g)[hop + 1];
 #pragma unroll
     for (int q = 0; q < NW; ++q) out += part[q];
-    if (threadIdx.x == 0 && blk + 1 == tier_blocks) G.tier_off[g][hop + 2] = out + total;
+    if (threadIdx.x == 0 && blk + 1 == tier_blocks) rg_tier_off(S, g)[hop + 2] = out + total;
     int base = out;
 #pragma unroll
     for (int q = 0; q < NW; ++q) base -= part_above[q];
     if (threadIdx.x == 0 && blk == base_blk) rg_rank_bases(S, g, hop)[blk / per_base] = base;
-    int32_t* __restrict__ nodes = G.nodes[g] + out;
+    int32_t* __restrict__ nodes = rg_nodes(S, g) + out;
     int32_t* dst = total <= kEmitIds ? ids : nodes;
     const RankBlocks rank = rg_rank_blocks(S, g, hop);
     const auto store_rank = [&](int64_t r, uint32_t b0, uint32_t b1, uint32_t b2, uint32_t above) {      // three words: two rank blocks
@@ -1080,15 +1120,15 @@ __device__ __forceinline__ void rg_slice_emit(const RowPtr& row_ptr, const Sampl
 }
 
 template <bool RANKED_SEEN>
-__global__ void __launch_bounds__(kTierWords / 3) k_slice_emit(const RowPtr row_ptr, const SampleGroup G, const SampleScratch S, int hop,
+__global__ void __launch_bounds__(kTierWords / 3) k_slice_emit(const RowPtr row_ptr, const SampleScratch S, int hop,
                                                                unsigned tier_blocks, int next_fanout, int run) {
-    rg_slice_emit<RANKED_SEEN, kTierWords / 3, 3>(row_ptr, G, S, hop, tier_blocks, next_fanout, run);
+    rg_slice_emit<RANKED_SEEN, kTierWords / 3, 3>(row_ptr, S, hop, tier_blocks, next_fanout, run);
 }
 
 template <bool RANKED_SEEN>
-__global__ void __launch_bounds__(kTierWordsSmall) k_slice_emit_small(const RowPtr row_ptr, const SampleGroup G, const SampleScratch S, int hop,
+__global__ void __launch_bounds__(kTierWordsSmall) k_slice_emit_small(const RowPtr row_ptr, const SampleScratch S, int hop,
                                                                       unsigned tier_blocks, int next_fanout, int run) {
-    rg_slice_emit<RANKED_SEEN, kTierWordsSmall, 1>(row_ptr, G, S, hop, tier_blocks, next_fanout, run);
+    rg_slice_emit<RANKED_SEEN, kTierWordsSmall, 1>(row_ptr, S, hop, tier_blocks, next_fanout, run);
 }
 
 // ---------------------------------------------------------------------------- per hop: new tier, from `marked`
@@ -1111,13 +1151,13 @@ __global__ void __launch_bounds__(256) k_tier_count(const SampleScratch S) {
 
 // Emit the new ids (marked, not yet visited) in ascending order behind the current frontier, record their positions
 // and make them frontier members (visited = marked).  chunk_sum holds exclusive block offsets.
-__global__ void __launch_bounds__(256) k_tier_emit(const SampleGroup G, const SampleScratch S, int hop) {
+__global__ void __launch_bounds__(256) k_tier_emit(const SampleScratch S, int hop) {
     __shared__ int smem[256 / RG_WAVE + 1];
     const int g = rg_batch(S);
     const unsigned blk = rg_block(S);
     const uint32_t* __restrict__ marked = S.marked + g * S.words;
     uint32_t* __restrict__ visited = S.visited + g * S.words;
-    int32_t* __restrict__ nodes = G.nodes[g];
+    int32_t* __restrict__ nodes = rg_nodes(S, g);
     int32_t* __restrict__ pos = S.pos + g * S.num_nodes;
     const int64_t w0 = (int64_t)blk * kWordsPerBlock + threadIdx.x * 4;
     uint32_t bits[4];
@@ -1130,7 +1170,7 @@ __global__ void __launch_bounds__(256) k_tier_emit(const SampleGroup G, const Sa
     int total;
     const int excl = rg_block_excl_scan<256 / RG_WAVE>(c, smem, &total);
     if (total == 0) return;                          // uniform: nothing fresh in this block
-    int out = G.tier_off[g][hop + 1] + S.chunk_sum[g * S.chunk_stride + blk] + excl;
+    int out = rg_tier_off(S, g)[hop + 1] + S.chunk_sum[g * S.chunk_stride + blk] + excl;
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
         uint32_t b = bits[q];
@@ -1157,12 +1197,12 @@ __device__ __forceinline__ bool rg_opens_node(const int32_t* __restrict__ nbr, c
     return first_key[nbr[e]] == 0x7FFFFFFF - (int32_t)e;
 }
 
-__global__ void __launch_bounds__(256) k_first_seen_count(const SampleGroup G, const SampleScratch S, int hop) {
+__global__ void __launch_bounds__(256) k_first_seen_count(const SampleScratch S, int hop) {
     const int g = rg_batch(S);
     const unsigned blk = rg_block(S);
-    const int32_t* __restrict__ nbr = G.nbr[g];
+    const int32_t* __restrict__ nbr = rg_hop_list(S, g, (int)hop, kNbr);
     const int32_t* __restrict__ first_key = S.first_key + g * S.num_nodes;
-    const int64_t n_edges = G.indptr[g][G.tier_off[g][hop + 1]];
+    const int64_t n_edges = rg_hop_list(S, g, (int)hop, kIndptr)[rg_tier_off(S, g)[hop + 1]];
     const int64_t e0 = (int64_t)blk * kEdgesPerBlock + threadIdx.x * 4;
     int c = 0;
 #pragma unroll
@@ -1177,16 +1217,16 @@ __global__ void __launch_bounds__(256) k_first_seen_count(const SampleGroup G, c
 
 // Appends the opened nodes behind the current frontier in edge order, records their positions, marks them visited
 // and clears their first-edge keys (the array is all-zero again when the hop is done).
-__global__ void __launch_bounds__(256) k_first_seen_emit(const SampleGroup G, const SampleScratch S, int hop) {
+__global__ void __launch_bounds__(256) k_first_seen_emit(const SampleScratch S, int hop) {
     __shared__ int smem[256 / RG_WAVE + 1];
     const int g = rg_batch(S);
     const unsigned blk = rg_block(S);
-    const int32_t* __restrict__ nbr = G.nbr[g];
+    const int32_t* __restrict__ nbr = rg_hop_list(S, g, (int)hop, kNbr);
     int32_t* __restrict__ first_key = S.first_key + g * S.num_nodes;
     uint32_t* __restrict__ visited = S.visited + g * S.words;
-    int32_t* __restrict__ nodes = G.nodes[g];
+    int32_t* __restrict__ nodes = rg_nodes(S, g);
     int32_t* __restrict__ pos = S.pos + g * S.num_nodes;
-    const int64_t n_edges = G.indptr[g][G.tier_off[g][hop + 1]];
+    const int64_t n_edges = rg_hop_list(S, g, (int)hop, kIndptr)[rg_tier_off(S, g)[hop + 1]];
     const int64_t e0 = (int64_t)blk * kEdgesPerBlock + threadIdx.x * 4;
     if ((int64_t)blk * kEdgesPerBlock >= n_edges) return;          // uniform per workgroup
     int32_t u[4];
@@ -1204,7 +1244,7 @@ __global__ void __launch_bounds__(256) k_first_seen_emit(const SampleGroup G, co
     int total;
     const int excl = rg_block_excl_scan<256 / RG_WAVE>(c, smem, &total);
     if (total == 0) return;                                               // uniform
-    int out = G.tier_off[g][hop + 1] + S.chunk_sum[g * S.chunk_stride + blk] + excl;
+    int out = rg_tier_off(S, g)[hop + 1] + S.chunk_sum[g * S.chunk_stride + blk] + excl;
 #pragma unroll
     for (int q = 0; q < 4; ++q)
         if (opens[q]) {
@@ -1284,16 +1324,16 @@ __device__ __forceinline__ void rg_ranked_positions(const int32_t (&u)[U], const
 }
 
 // nbr_local[e] = ascending position of nbr[e].
-__global__ void __launch_bounds__(256) k_seen_rank(const SampleGroup G, const SampleScratch S, int hop) {
+__global__ void __launch_bounds__(256) k_seen_rank(const SampleScratch S, int hop) {
     extern __shared__ int32_t bases[];
     constexpr int U = 2;
     const int g = rg_batch(S);
     rg_load_bases(S, g, hop + 1, bases);
     const int64_t stride = (int64_t)rg_blocks_per_batch(S) * 256;
-    const int64_t n = G.indptr[g][G.tier_off[g][hop + 1]];
-    const int32_t* __restrict__ nbr = G.nbr[g];
+    const int64_t n = rg_hop_list(S, g, (int)hop, kIndptr)[rg_tier_off(S, g)[hop + 1]];
+    const int32_t* __restrict__ nbr = rg_hop_list(S, g, (int)hop, kNbr);
     const int32_t* __restrict__ pos = S.pos + g * S.num_nodes;
-    int32_t* __restrict__ nbr_local = G.nbr_local[g];
+    int32_t* __restrict__ nbr_local = rg_hop_list(S, g, (int)hop, kNbrLocal);
     for (int64_t e0 = (int64_t)rg_block(S) * 256 + threadIdx.x; e0 < n; e0 += stride * U) {
         int32_t u[U], r[U];
 #pragma unroll
@@ -1314,17 +1354,17 @@ __device__ __forceinline__ void rg_seen_min(int32_t* first, int32_t a, int64_t e
     if (d < n) atomicMin(&first[d], (int32_t)e);
 }
 
-__global__ void __launch_bounds__(1024) k_seen_min(const SampleGroup G, const SampleScratch S, int hop) {
+__global__ void __launch_bounds__(1024) k_seen_min(const SampleScratch S, int hop) {
     extern __shared__ int32_t slice_first[];
     constexpr int U = 4;                                 // 16-byte loads in flight per thread
     const int g = rg_batch(S);
-    const int n_h = G.tier_off[g][hop + 1];
-    const int64_t a0 = n_h + (int64_t)rg_block(S) * kSeenSlice, left = G.tier_off[g][hop + 2] - a0;
+    const int n_h = rg_tier_off(S, g)[hop + 1];
+    const int64_t a0 = n_h + (int64_t)rg_block(S) * kSeenSlice, left = rg_tier_off(S, g)[hop + 2] - a0;
     if (left <= 0) return;                               // uniform per workgroup
     const int n_here = (int)(left < kSeenSlice ? left : kSeenSlice);
     for (int i = threadIdx.x; i < n_here; i += 1024) slice_first[i] = 0x7FFFFFFF;
-    const int n = G.indptr[g][n_h];
-    const int32_t* __restrict__ at = G.nbr_local[g];
+    const int n = rg_hop_list(S, g, (int)hop, kIndptr)[n_h];
+    const int32_t* __restrict__ at = rg_hop_list(S, g, (int)hop, kNbrLocal);
     __syncthreads();
     const int to_line = (int)((16u - ((uint32_t)(uintptr_t)at & 15u)) & 15u) / 4;      // at[] may start at any 4-byte address
     const int head = to_line < n ? to_line : n;
@@ -1354,14 +1394,14 @@ __global__ void __launch_bounds__(1024) k_seen_min(const SampleGroup G, const Sa
 
 constexpr int kSeenEdges = 4096;       // edges per workgroup: 1024 threads x 4
 
-__global__ void __launch_bounds__(1024) k_seen_count(const SampleGroup G, const SampleScratch S, int hop) {
+__global__ void __launch_bounds__(1024) k_seen_count(const SampleScratch S, int hop) {
     __shared__ int part[1024 / RG_WAVE];
     const int g = rg_batch(S);
     const unsigned blk = rg_block(S);
-    const int n_h = G.tier_off[g][hop + 1];
-    const int64_t n = G.indptr[g][n_h], first = (int64_t)blk * kSeenEdges;
+    const int n_h = rg_tier_off(S, g)[hop + 1];
+    const int64_t n = rg_hop_list(S, g, (int)hop, kIndptr)[n_h], first = (int64_t)blk * kSeenEdges;
     if (first >= n) return;                              // uniform per workgroup
-    const int32_t* __restrict__ at = G.nbr_local[g];
+    const int32_t* __restrict__ at = rg_hop_list(S, g, (int)hop, kNbrLocal);
     const int32_t* __restrict__ first_edge = S.first_edge + g * S.frontier_stride;
     int c = 0;
 #pragma unroll
@@ -1380,17 +1420,17 @@ __global__ void __launch_bounds__(1024) k_seen_count(const SampleGroup G, const 
 }
 
 // The nodes that edges open, in edge order, and where each ascending position ended up.
-__global__ void __launch_bounds__(1024) k_seen_emit(const SampleGroup G, const SampleScratch S, int hop) {
+__global__ void __launch_bounds__(1024) k_seen_emit(const SampleScratch S, int hop) {
     constexpr int NW = 1024 / RG_WAVE;
     __shared__ int smem[NW + 1];
     __shared__ int part[NW];
     const int g = rg_batch(S);
     const unsigned blk = rg_block(S);
-    const int n_h = G.tier_off[g][hop + 1];
-    const int64_t n = G.indptr[g][n_h], first = (int64_t)blk * kSeenEdges;
+    const int n_h = rg_tier_off(S, g)[hop + 1];
+    const int64_t n = rg_hop_list(S, g, (int)hop, kIndptr)[n_h], first = (int64_t)blk * kSeenEdges;
     if (first >= n) return;                              // uniform per workgroup
-    const int32_t* __restrict__ at = G.nbr_local[g];
-    const int32_t* __restrict__ nbr = G.nbr[g];
+    const int32_t* __restrict__ at = rg_hop_list(S, g, (int)hop, kNbrLocal);
+    const int32_t* __restrict__ nbr = rg_hop_list(S, g, (int)hop, kNbr);
     const int32_t* __restrict__ first_edge = S.first_edge + g * S.frontier_stride;
     const int32_t* __restrict__ chunk_sum = S.chunk_sum + g * S.chunk_stride;
     int before = 0;                                      // nodes opened by the edges in front of this workgroup's
@@ -1412,7 +1452,7 @@ __global__ void __launch_bounds__(1024) k_seen_emit(const SampleGroup G, const S
     int out = n_h + rg_block_excl_scan<NW>(c, smem, &total);               // its barriers publish part[]
 #pragma unroll
     for (int q = 0; q < NW; ++q) out += part[q];
-    int32_t* __restrict__ nodes = G.nodes[g];
+    int32_t* __restrict__ nodes = rg_nodes(S, g);
     int32_t* __restrict__ place = S.place + g * S.frontier_stride;
 #pragma unroll
     for (int q = 0; q < 4; ++q)
@@ -1425,31 +1465,24 @@ __global__ void __launch_bounds__(1024) k_seen_emit(const SampleGroup G, const S
 // ---------------------------------------------------------------------------- relabelling, all hops in one launch
 // A member's position never changes, so nbr_local of every hop can be written after the last one, if every hop's lists are still
 // there by then (rg_hops_share_buffers).
-struct RelabelGroup {
-    const int32_t* indptr[RG_MAX_HOPS][kMaxGroup];
-    const int32_t* nbr[RG_MAX_HOPS][kMaxGroup];
-    int32_t* nbr_local[RG_MAX_HOPS][kMaxGroup];   // may be NULL
-    const int32_t* tier_off[kMaxGroup];
-};
-
 // nbr_local[e] = position of nbr[e] in the extended frontier; the hop's edge count is indptr[n_h].
 // RANKED: the rank words of the tiers, latest first (a hop's edges mostly name its new tier), pos[] for the seeds.  The words
 // of one tier are N / 4 bytes (2.5 MB at N = 10 M) where pos[] is 4 N.  Three hops of 8 batches of 4096 seeds, 20.6 M edges: 202 us,
 // bound by the rank words: three tiers of them are more than one XCD's L2, 71 % of the reads hit it.  (The 15.9 M edges of hop 2
 // by themselves: pos[] 251 us, the new tier's words and those of one more 142, the new tier's alone, which would not do, 74.)
 template <bool RANKED>
-__global__ void __launch_bounds__(256) k_relabel(const RelabelGroup R, const SampleScratch S) {
+__global__ void __launch_bounds__(256) k_relabel(const SampleScratch S, int first_hop, int last_hop) {
     extern __shared__ int32_t bases[];
     constexpr int U = RANKED ? 2 : 4;                    // edges in flight per thread
     const int g = rg_batch(S);
     const int64_t stride = (int64_t)rg_blocks_per_batch(S) * 256;
     const int32_t* __restrict__ pos = S.pos + g * S.num_nodes;
-    if (RANKED) rg_load_bases(S, g, S.hops, bases);
-    for (int hop = S.hops - 1; hop >= 0; --hop) {
-        int32_t* __restrict__ nbr_local = R.nbr_local[hop][g];
+    if (RANKED) rg_load_bases(S, g, last_hop + 1, bases);
+    for (int hop = last_hop; hop >= first_hop; --hop) {
+        int32_t* __restrict__ nbr_local = rg_hop_list(S, g, hop, kNbrLocal);
         if (!nbr_local) continue;
-        const int32_t* __restrict__ nbr = R.nbr[hop][g];
-        const int64_t n = R.indptr[hop][g][R.tier_off[g][hop + 1]];
+        const int32_t* __restrict__ nbr = rg_hop_list(S, g, hop, kNbr);
+        const int64_t n = rg_hop_list(S, g, hop, kIndptr)[rg_tier_off(S, g)[hop + 1]];
         for (int64_t e0 = (int64_t)rg_block(S) * 256 + threadIdx.x; e0 < n; e0 += stride * U) {
             int32_t u[U], r[U];
 #pragma unroll
@@ -1480,18 +1513,12 @@ inline bool rg_is_small(int64_t num_nodes, int64_t edges_bound, int64_t frontier
            rg_max64(edges_bound, frontiers_bound) <= (num_nodes <= 128 * 1024 ? 20 * 1024 : 8 * 1024);
 }
 
-struct SmallGroup {
-    RelabelGroup r;
-    const int32_t* seeds[kMaxGroup];
-    int32_t* nodes[kMaxGroup];
-    int32_t* tier_off[kMaxGroup];
-    int32_t* edges_out[kMaxGroup];    // [hops]; may be NULL
-    int32_t num_seeds[kMaxGroup];
-    int32_t fanout[RG_MAX_HOPS];
+struct Fanouts {
+    int32_t v[RG_MAX_HOPS];
 };
 
-template <typename RP, int KMAX>
-__global__ void __launch_bounds__(1024) k_sample_small(const RP* __restrict__ row_ptr, const int32_t* __restrict__ col_idx, const SmallGroup G,
+template <typename RP, int KMAX, int N>
+__global__ void __launch_bounds__(1024) k_sample_small(const RP* __restrict__ row_ptr, const int32_t* __restrict__ col_idx, const BatchTable<N> B, int group, const Fanouts fanouts,
                                                        uint32_t* __restrict__ visited_out, int64_t words64, int32_t* pos_all, int64_t num_nodes,
                                                        int hops, uint32_t k0, uint32_t k1, uint32_t epoch) {
     extern __shared__ uint32_t small_bits[];
@@ -1499,14 +1526,17 @@ __global__ void __launch_bounds__(1024) k_sample_small(const RP* __restrict__ ro
     const int g = blockIdx.x, words = (int)words64;
     uint32_t* visited = small_bits;
     uint32_t* marked = small_bits + words;                             // members and the ids the hop has sampled
-    int32_t* nodes = G.nodes[g];
-    int32_t* tier_off = G.tier_off[g];
+    const auto entry = [&](int field) { return rg_global(B.v[field * group + g]); };
+    const int32_t* seeds = entry(kSeeds);
+    int32_t* nodes = entry(kNodes);
+    int32_t* tier_off = entry(kTierOff);
+    int32_t* edges_out = entry(kEdgesOut);
     int32_t* pos = pos_all + g * num_nodes;
     for (int w = threadIdx.x; w < 2 * words; w += 1024) small_bits[w] = 0u;
-    int n_h = G.num_seeds[g];
+    int n_h = (int)B.v[kNumSeeds * group + g];
     __syncthreads();
     for (int i = threadIdx.x; i < n_h; i += 1024) {
-        const int32_t v = G.seeds[g][i];
+        const int32_t v = seeds[i];
         nodes[i] = v;
         pos[v] = i;
         atomicOr(&visited[(uint32_t)v >> 5], 1u << (v & 31));
@@ -1516,9 +1546,9 @@ __global__ void __launch_bounds__(1024) k_sample_small(const RP* __restrict__ ro
     const int per = (words + 1023) / 1024 | 1;                         // consecutive bitmap words per thread, odd: no two lanes on a bank
     const int w0 = (int)threadIdx.x * per, w1 = w0 + per < words ? w0 + per : words;
     for (int hop = 0; hop < hops; ++hop) {
-        const int k = G.fanout[hop];
-        int32_t* indptr = (int32_t*)G.r.indptr[hop][g];
-        int32_t* nbr = (int32_t*)G.r.nbr[hop][g];
+        const int k = fanouts.v[hop];
+        int32_t* indptr = entry(kHopFields + kHopFieldCount * hop + kIndptr);
+        int32_t* nbr = entry(kHopFields + kHopFieldCount * hop + kNbr);
         int edges = 0;
         __syncthreads();                                               // nodes[] and the bits are complete
         for (int i0 = 0; i0 < n_h; i0 += 1024) {
@@ -1574,7 +1604,7 @@ __global__ void __launch_bounds__(1024) k_sample_small(const RP* __restrict__ ro
         }
         if (threadIdx.x == 0) {
             indptr[n_h] = edges;
-            if (G.edges_out[g]) G.edges_out[g][hop] = edges;
+            if (edges_out) edges_out[hop] = edges;
         }
         __syncthreads();                                               // the marks and nbr[] are complete
         int fresh = 0;
@@ -1593,7 +1623,7 @@ __global__ void __launch_bounds__(1024) k_sample_small(const RP* __restrict__ ro
         }
         n_h += total;
         if (threadIdx.x == 0) tier_off[hop + 2] = n_h;
-        int32_t* nbr_local = G.r.nbr_local[hop][g];
+        int32_t* nbr_local = entry(kHopFields + kHopFieldCount * hop + kNbrLocal);
         if (nbr_local) {                                               // uniform
             __syncthreads();                                           // pos[] is complete
             for (int e0 = threadIdx.x; e0 < edges; e0 += 4096) {
@@ -1614,16 +1644,16 @@ __global__ void __launch_bounds__(1024) k_sample_small(const RP* __restrict__ ro
 }
 
 // kTierRankedSeen: nbr_local holds ascending positions; the seeds' are their own.
-__global__ void __launch_bounds__(256) k_seen_relabel(const RelabelGroup R, const SampleScratch S) {
+__global__ void __launch_bounds__(256) k_seen_relabel(const SampleScratch S, int first_hop, int last_hop) {
     constexpr int U = 4;
     const int g = rg_batch(S);
     const int64_t stride = (int64_t)rg_blocks_per_batch(S) * 256;
     const int32_t* __restrict__ place = S.place + g * S.frontier_stride;
-    const int seeds = R.tier_off[g][1];
-    for (int hop = S.hops - 1; hop >= 0; --hop) {
-        int32_t* __restrict__ nbr_local = R.nbr_local[hop][g];
+    const int seeds = rg_tier_off(S, g)[1];
+    for (int hop = last_hop; hop >= first_hop; --hop) {
+        int32_t* __restrict__ nbr_local = rg_hop_list(S, g, hop, kNbrLocal);
         if (!nbr_local) continue;
-        const int64_t n = R.indptr[hop][g][R.tier_off[g][hop + 1]];
+        const int64_t n = rg_hop_list(S, g, hop, kIndptr)[rg_tier_off(S, g)[hop + 1]];
         for (int64_t e0 = (int64_t)rg_block(S) * 256 + threadIdx.x; e0 < n; e0 += stride * U) {
             int32_t a[U];
 #pragma unroll
@@ -1772,7 +1802,7 @@ rg_status rg_sampler_reserve(rg_ctx* ctx, int64_t num_nodes, int64_t max_frontie
     if ((st = rg_ensure(ctx, ctx->visited, g * S.words * 4)) != RG_OK) return st;
     if ((st = rg_ensure(ctx, ctx->marked, g * S.words * 4)) != RG_OK) return st;
     if ((st = rg_ensure(ctx, ctx->pos, g * (size_t)num_nodes * 4)) != RG_OK) return st;
-    if ((st = rg_ensure(ctx, ctx->chunk_sum, 3 * g * S.chunk_stride * 4)) != RG_OK) return st;
+    if ((st = rg_ensure(ctx, ctx->chunk_sum, kTableMost * 8 + 3 * g * S.chunk_stride * 4)) != RG_OK) return st;
     if ((st = rg_ensure(ctx, ctx->row_start, g * S.frontier_stride * 8)) != RG_OK) return st;
     if ((st = rg_ensure(ctx, ctx->row_deg, g * S.frontier_stride * 4)) != RG_OK) return st;
     // first-seen order: the first-edge keys must be all-zero between hops (every hop leaves them zeroed)
@@ -1810,10 +1840,12 @@ rg_status rg_sampler_reserve_slices(rg_ctx* ctx, int64_t num_nodes, int hops, bo
 // Slices use more LDS than a kernel may by default.
 rg_status rg_sampler_init(rg_ctx* ctx) {
     RG_HIP(ctx, hipFuncSetAttribute((const void*)k_sample_init, hipFuncAttributeMaxDynamicSharedMemorySize, kSliceWords * 4));
+    RG_HIP(ctx, hipFuncSetAttribute((const void*)k_sample_init_most, hipFuncAttributeMaxDynamicSharedMemorySize, kSliceWords * 4));
     RG_HIP(ctx, hipFuncSetAttribute((const void*)k_slice_mark, hipFuncAttributeMaxDynamicSharedMemorySize, kSliceWords * 4));
     RG_HIP(ctx, hipFuncSetAttribute((const void*)k_seen_min, hipFuncAttributeMaxDynamicSharedMemorySize, kSeenSlice * 4));
-    const void* small[] = {(const void*)k_sample_small<int32_t, 8>, (const void*)k_sample_small<int32_t, 16>, (const void*)k_sample_small<int32_t, 32>,
-                           (const void*)k_sample_small<int64_t, 8>, (const void*)k_sample_small<int64_t, 16>, (const void*)k_sample_small<int64_t, 32>};
+#define RG_SMALL(RP, N) (const void*)k_sample_small<RP, 8, N>, (const void*)k_sample_small<RP, 16, N>, (const void*)k_sample_small<RP, 32, N>
+    const void* small[] = {RG_SMALL(int32_t, kTableFew), RG_SMALL(int32_t, kTableMost), RG_SMALL(int64_t, kTableFew), RG_SMALL(int64_t, kTableMost)};
+#undef RG_SMALL
     for (const void* f : small) RG_HIP(ctx, hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)(kSmallNodes / 4)));
     return RG_OK;
 }
@@ -1985,7 +2017,7 @@ rg_status rg_sample_blocks_group(rg_ctx* ctx, const rg_csr* csr, int32_t group, 
     S.visited = (uint32_t*)ctx->visited.p;
     S.marked = (uint32_t*)ctx->marked.p;
     S.pos = (int32_t*)ctx->pos.p;
-    S.chunk_sum = (int32_t*)ctx->chunk_sum.p;
+    S.chunk_sum = (int32_t*)((uint64_t*)ctx->chunk_sum.p + kTableMost);
     S.hop_sum[0] = S.chunk_sum + group * S.chunk_stride;
     S.hop_sum[1] = S.hop_sum[0] + group * S.chunk_stride;
     S.row_start = (int64_t*)ctx->row_start.p;
@@ -1993,39 +2025,43 @@ rg_status rg_sample_blocks_group(rg_ctx* ctx, const rg_csr* csr, int32_t group, 
     const uint32_t k0 = (uint32_t)(seed & 0xffffffffu), k1 = (uint32_t)(seed >> 32);
     const bool rp64 = csr->row_ptr_bits == 64;
 
-    SampleGroup G;
-    for (int g = 0; g < kMaxGroup; ++g) {
-        const bool live = g < group;
-        G.seeds[g] = live ? seeds[g] : nullptr;
-        G.num_seeds[g] = live ? num_seeds[g] : 0;
-        G.nodes[g] = live ? out[g].nodes : nullptr;
-        G.tier_off[g] = live ? out[g].tier_off : nullptr;
-        G.indptr[g] = G.nbr[g] = G.nbr_local[g] = G.edges_out[g] = nullptr;
+    BatchTable<kTableMost> table;
+    S.table = (const uint64_t*)ctx->chunk_sum.p;
+    S.table_entries = (kHopFields + kHopFieldCount * num_hops) * group;
+    for (int g = 0; g < group; ++g) {
+        const auto put = [&](int field, const void* p) { table.v[field * group + g] = (uint64_t)(uintptr_t)p; };
+        put(kSeeds, seeds[g]);
+        table.v[kNumSeeds * group + g] = (uint64_t)num_seeds[g];
+        put(kNodes, out[g].nodes);
+        put(kTierOff, out[g].tier_off);
+        put(kEdgesOut, out[g].num_edges);
+        for (int h = 0; h < num_hops; ++h) {
+            put(kHopFields + kHopFieldCount * h + kIndptr, out[g].indptr[h]);
+            put(kHopFields + kHopFieldCount * h + kNbr, out[g].nbr[h]);
+            put(kHopFields + kHopFieldCount * h + kNbrLocal, out[g].nbr_local && eub_max[h] > 0 ? out[g].nbr_local[h] : nullptr);
+        }
     }
+    BatchTable<kTableSome> some;
+    const bool most = S.table_entries > kTableSome;
+    if (!most) memcpy(some.v, table.v, (size_t)S.table_entries * 8);
     const unsigned ug = (unsigned)group;
 
     if (small) {
-        SmallGroup M = {};
-        for (int g = 0; g < group; ++g) {
-            M.seeds[g] = seeds[g];
-            M.nodes[g] = out[g].nodes;
-            M.tier_off[g] = out[g].tier_off;
-            M.edges_out[g] = out[g].num_edges;
-            M.num_seeds[g] = num_seeds[g];
-            for (int h = 0; h < num_hops; ++h) {
-                M.r.indptr[h][g] = out[g].indptr[h];
-                M.r.nbr[h][g] = out[g].nbr[h];
-                M.r.nbr_local[h][g] = out[g].nbr_local && eub_max[h] > 0 ? out[g].nbr_local[h] : nullptr;
-            }
-        }
-        for (int h = 0; h < num_hops; ++h) M.fanout[h] = fanouts[h];
+        Fanouts fan = {};
+        for (int h = 0; h < num_hops; ++h) fan.v[h] = fanouts[h];
+        BatchTable<kTableFew> few;
+        const bool is_few = S.table_entries <= kTableFew;
+        if (is_few) memcpy(few.v, table.v, (size_t)S.table_entries * 8);
         const int tok = rg_prof_begin(ctx, RG_K_SAMPLE, s);
-#define RG_LAUNCH_SMALL(RP, KM)                                                                                       \
-    k_sample_small<RP, KM><<<ug, 1024, (size_t)words * 8, s>>>((const RP*)csr->row_ptr, csr->col_idx, M, S.visited, words, S.pos, N, num_hops, \
-                                                               k0, k1, epoch)
+#define RG_LAUNCH_SMALL_N(RP, KM, N, TABLE)                                                                           \
+    k_sample_small<RP, KM, N><<<ug, 1024, (size_t)words * 8, s>>>((const RP*)csr->row_ptr, csr->col_idx, TABLE, group, fan, S.visited, words, \
+                                                                  S.pos, N_nodes, num_hops, k0, k1, epoch)
+#define RG_LAUNCH_SMALL(RP, KM) do { if (is_few) RG_LAUNCH_SMALL_N(RP, KM, kTableFew, few); else RG_LAUNCH_SMALL_N(RP, KM, kTableMost, table); } while (0)
+        const int64_t N_nodes = N;
         if (rp64) { if (max_fanout <= 8) RG_LAUNCH_SMALL(int64_t, 8); else if (max_fanout <= 16) RG_LAUNCH_SMALL(int64_t, 16); else RG_LAUNCH_SMALL(int64_t, 32); }
         else { if (max_fanout <= 8) RG_LAUNCH_SMALL(int32_t, 8); else if (max_fanout <= 16) RG_LAUNCH_SMALL(int32_t, 16); else RG_LAUNCH_SMALL(int32_t, 32); }
 #undef RG_LAUNCH_SMALL
+#undef RG_LAUNCH_SMALL_N
         rg_prof_end(ctx, tok, s);
         RG_LAUNCH_CHECK(ctx, "k_sample_small");
         ctx->last_sample_group = group;
@@ -2047,7 +2083,10 @@ rg_status rg_sample_blocks_group(rg_ctx* ctx, const rg_csr* csr, int32_t group, 
     if (rg_use_init(S.slices, group, seeds_max)) {
         const unsigned count_blocks = drawn_by_threads(0) ? (unsigned)rg_div_up(seeds_max, kChunk) : 0u;
         const size_t lds = (size_t)rg_max64(S.slice_words, 1024 / RG_WAVE) * 4;
-        k_sample_init<<<((unsigned)S.slices + count_blocks) * ug, 1024, lds, s>>>(row_ptr, G, S, fanouts[0], mode == kTierAtomic ? 1 : 0);
+        const unsigned init_blocks = ((unsigned)S.slices + count_blocks) * ug;
+        const int copy = mode == kTierAtomic ? 1 : 0;
+        if (most) k_sample_init_most<<<init_blocks, 1024, lds, s>>>(row_ptr, table, S, fanouts[0], copy);
+        else k_sample_init<<<init_blocks, 1024, lds, s>>>(row_ptr, some, S, fanouts[0], copy);
         if (count_blocks) counted = 0;
         RG_LAUNCH_CHECK(ctx, "k_sample_init");
     } else {
@@ -2058,19 +2097,21 @@ rg_status rg_sample_blocks_group(rg_ctx* ctx, const rg_csr* csr, int32_t group, 
             k_clear_words<<<(int)rg_div_up(group_words, 256), 256, 0, s>>>(S.marked, group_words);
             RG_LAUNCH_CHECK(ctx, "k_clear_words");
         }
-        k_mark_seeds<<<(unsigned)(grid_for(seeds_max, 256, 1 << 30)) * ug, 256, 0, s>>>(G, S);
+        const unsigned mark_blocks = (unsigned)(grid_for(seeds_max, 256, 1 << 30)) * ug;
+        if (most) k_mark_seeds_most<<<mark_blocks, 256, 0, s>>>(table, S); else k_mark_seeds<<<mark_blocks, 256, 0, s>>>(some, S);
         RG_LAUNCH_CHECK(ctx, "k_mark_seeds");
     }
 
-    RelabelGroup R = {};
-    int64_t relabel_edges = 0;
-    for (int g = 0; g < group; ++g) R.tier_off[g] = out[g].tier_off;
-    const auto relabel = [&]() -> rg_status {              // every hop that R names
-        if (relabel_edges == 0) return RG_OK;
-        const unsigned blocks = (unsigned)grid_for(relabel_edges, 1024, rg_div_up((int64_t)ctx->num_cus * 32, group));
-        if (mode == kTierSliced) k_relabel<true><<<blocks * ug, 256, (size_t)(num_hops * S.rank_bases) * 4, s>>>(R, S);
-        else if (mode == kTierRankedSeen) k_seen_relabel<<<blocks * ug, 256, 0, s>>>(R, S);
-        else k_relabel<false><<<blocks * ug, 256, 0, s>>>(R, S);
+    const auto relabel = [&](int first_hop, int last_hop) -> rg_status {
+        int64_t edges_most = 0;
+        for (int h = first_hop; h <= last_hop; ++h)
+            for (int g = 0; g < group; ++g)
+                if (out[g].nbr_local) edges_most = rg_max64(edges_most, eub_max[h]);
+        if (edges_most == 0) return RG_OK;
+        const unsigned blocks = (unsigned)grid_for(edges_most, 1024, rg_div_up((int64_t)ctx->num_cus * 32, group));
+        if (mode == kTierSliced) k_relabel<true><<<blocks * ug, 256, (size_t)((last_hop + 1) * S.rank_bases) * 4, s>>>(S, first_hop, last_hop);
+        else if (mode == kTierRankedSeen) k_seen_relabel<<<blocks * ug, 256, 0, s>>>(S, first_hop, last_hop);
+        else k_relabel<false><<<blocks * ug, 256, 0, s>>>(S, first_hop, last_hop);
         RG_LAUNCH_CHECK(ctx, "k_relabel");
         return RG_OK;
     };
@@ -2083,24 +2124,14 @@ rg_status rg_sample_blocks_group(rg_ctx* ctx, const rg_csr* csr, int32_t group, 
         return (int)run;
     };
     for (int h = 0; h < num_hops; ++h) {
-        for (int g = 0; g < group; ++g) {
-            G.indptr[g] = out[g].indptr[h];
-            G.nbr[g] = out[g].nbr[h];
-            G.nbr_local[g] = out[g].nbr_local ? out[g].nbr_local[h] : nullptr;
-            G.edges_out[g] = out[g].num_edges ? out[g].num_edges + h : nullptr;
-            R.indptr[h][g] = out[g].indptr[h];
-            R.nbr[h][g] = out[g].nbr[h];
-            R.nbr_local[h][g] = out[g].nbr_local && eub_max[h] > 0 ? out[g].nbr_local[h] : nullptr;
-            if (R.nbr_local[h][g]) relabel_edges = rg_max64(relabel_edges, eub_max[h]);
-        }
         if (counted != h) {
             unsigned count_grid;
             const int count_run = shared_run(grid_for(fub_max[h], kChunk, 1ll << 30), kSharedNodes / kChunk, count_grid);
             const int offsets = drawn_by_threads(h) ? 0 : 1;
             if (rp64)
-                k_hop_count<int64_t><<<count_grid, kChunk / kCountNodes, 0, s>>>((const int64_t*)csr->row_ptr, G, S, h, fanouts[h], count_run, offsets);
+                k_hop_count<int64_t><<<count_grid, kChunk / kCountNodes, 0, s>>>((const int64_t*)csr->row_ptr, S, h, fanouts[h], count_run, offsets);
             else
-                k_hop_count<int32_t><<<count_grid, kChunk / kCountNodes, 0, s>>>((const int32_t*)csr->row_ptr, G, S, h, fanouts[h], count_run, offsets);
+                k_hop_count<int32_t><<<count_grid, kChunk / kCountNodes, 0, s>>>((const int32_t*)csr->row_ptr, S, h, fanouts[h], count_run, offsets);
             RG_LAUNCH_CHECK(ctx, "k_hop_count");
         }
 
@@ -2118,13 +2149,13 @@ rg_status rg_sample_blocks_group(rg_ctx* ctx, const rg_csr* csr, int32_t group, 
             // 1206 / 1196, of 16 M 2555 / 2498, of 40 M 7213 / 6750.
             const int scanned = rg_div_up(fub_max[h], kChunk) > kDrawSelfScan;
             if (scanned) {
-                k_scan_hop<<<ug, 1024, 0, s>>>(G, S, h);
+                k_scan_hop<<<ug, 1024, 0, s>>>(S, h);
                 RG_LAUNCH_CHECK(ctx, "k_scan_hop");
             }
 #define RG_LAUNCH_DRAW(KM, NP, MODE)                                                                                  \
-    k_hop_sample_thread<KM, NP, MODE><<<draw_grid, 256, lds, s>>>(csr->col_idx, G, S, F, (uint32_t)h, k0, k1, epoch, scanned, draw_run)
+    k_hop_sample_thread<KM, NP, MODE><<<draw_grid, 256, lds, s>>>(csr->col_idx, S, F, (uint32_t)h, k0, k1, epoch, scanned, draw_run)
 #define RG_LAUNCH_LANES(KM, MODE)                                                                                     \
-    k_hop_sample_lanes<KM, MODE><<<(unsigned)grid_for(fub_max[h], 256 / KM, 1ll << 30) * ug, 256, 0, s>>>(csr->col_idx, G, S, F, (uint32_t)h, k0, k1, epoch)
+    k_hop_sample_lanes<KM, MODE><<<(unsigned)grid_for(fub_max[h], 256 / KM, 1ll << 30) * ug, 256, 0, s>>>(csr->col_idx, S, F, (uint32_t)h, k0, k1, epoch)
 #define RG_LAUNCH_DRAW_K(NP, MODE)                                                                                    \
     do { if (F <= 8) RG_LAUNCH_DRAW(8, NP, MODE); else if (F <= 16) RG_LAUNCH_DRAW(16, NP, MODE); else RG_LAUNCH_DRAW(32, NP, MODE); } while (0)
 #define RG_LAUNCH_LANES_K(MODE)                                                                                       \
@@ -2141,12 +2172,12 @@ rg_status rg_sample_blocks_group(rg_ctx* ctx, const rg_csr* csr, int32_t group, 
             rg_prof_end(ctx, tok, s);
         } else {
             // chunk sums -> exclusive offsets; total edge count -> indptr[n_h]
-            k_scan_hop<<<ug, 1024, 0, s>>>(G, S, h);
+            k_scan_hop<<<ug, 1024, 0, s>>>(S, h);
             RG_LAUNCH_CHECK(ctx, "k_scan_hop");
             const int tok = rg_prof_begin(ctx, RG_K_SAMPLE, s);
             const unsigned sample_blocks = (unsigned)grid_for(fub_max[h], 1, (int64_t)ctx->num_cus * 64);
 #define RG_LAUNCH_WAVE(MODE)                                                                                          \
-    k_hop_sample_wave<MODE><<<sample_blocks * ug, RG_WAVE, 0, s>>>(csr->col_idx, G, S, F, (uint32_t)h, k0, k1, epoch)
+    k_hop_sample_wave<MODE><<<sample_blocks * ug, RG_WAVE, 0, s>>>(csr->col_idx, S, F, (uint32_t)h, k0, k1, epoch)
             if (mode == kTierSliced || mode == kTierRankedSeen) RG_LAUNCH_WAVE(kTierSliced);
             else if (mode == kTierAtomic) RG_LAUNCH_WAVE(kTierAtomic);
             else RG_LAUNCH_WAVE(kTierFirstSeen);
@@ -2161,7 +2192,7 @@ rg_status rg_sample_blocks_group(rg_ctx* ctx, const rg_csr* csr, int32_t group, 
             S.splits = (int)rg_max64(1, rg_min64(rg_min64(eub_max[h], 8 * expected[h]) / split_edges, kSliceGroups / (S.slices * group)));
             const bool small_tier = rg_div_up(words, kTierWords) * group < ctx->num_cus;
             const unsigned tier_blocks = (unsigned)rg_max64(1, rg_div_up(words, small_tier ? kTierWordsSmall : kTierWords));
-            k_slice_mark<<<(unsigned)(S.slices * S.splits) * ug, 1024, (size_t)S.slice_words * 4, s>>>(G, S, h);
+            k_slice_mark<<<(unsigned)(S.slices * S.splits) * ug, 1024, (size_t)S.slice_words * 4, s>>>(S, h);
             RG_LAUNCH_CHECK(ctx, "k_slice_mark");
             const bool count_next = mode == kTierSliced && h + 1 < num_hops && drawn_by_threads(h + 1);
             const int next_fanout = count_next ? fanouts[h + 1] : -1;
@@ -2172,51 +2203,47 @@ rg_status rg_sample_blocks_group(rg_ctx* ctx, const rg_csr* csr, int32_t group, 
     do {                                                                                                              \
         k_slice_count<T, W><<<tier_blocks * ug, T, 0, s>>>(S);                                                        \
         RG_LAUNCH_CHECK(ctx, "k_slice_count");                                                                        \
-        if (mode == kTierSliced) EMIT<false><<<emit_grid, T, 0, s>>>(row_ptr, G, S, h, tier_blocks, next_fanout, emit_run);             \
-        else EMIT<true><<<tier_blocks * ug, T, 0, s>>>(row_ptr, G, S, h, tier_blocks, -1, 0);                                   \
+        if (mode == kTierSliced) EMIT<false><<<emit_grid, T, 0, s>>>(row_ptr, S, h, tier_blocks, next_fanout, emit_run);             \
+        else EMIT<true><<<tier_blocks * ug, T, 0, s>>>(row_ptr, S, h, tier_blocks, -1, 0);                                   \
         RG_LAUNCH_CHECK(ctx, "k_slice_emit");                                                                         \
     } while (0)
             if (small_tier) RG_LAUNCH_TIER(k_slice_emit_small, kTierWordsSmall, 1); else RG_LAUNCH_TIER(k_slice_emit, kTierWords / 3, 3);
 #undef RG_LAUNCH_TIER
             if (mode == kTierRankedSeen) {
                 // the edges that open a node, counted per block of the edge list, emitted in edge order
-                k_seen_rank<<<(unsigned)grid_for(eub_max[h], 1024, (int64_t)ctx->num_cus * 16) * ug, 256, (size_t)((h + 1) * S.rank_bases) * 4, s>>>(G, S, h);
+                k_seen_rank<<<(unsigned)grid_for(eub_max[h], 1024, (int64_t)ctx->num_cus * 16) * ug, 256, (size_t)((h + 1) * S.rank_bases) * 4, s>>>(S, h);
                 RG_LAUNCH_CHECK(ctx, "k_seen_rank");
                 const int64_t most_new = rg_min64(N, eub_max[h]);
-                k_seen_min<<<(unsigned)grid_for(most_new, kSeenSlice, 1 << 30) * ug, 1024, (size_t)rg_min64(most_new, kSeenSlice) * 4, s>>>(G, S, h);
+                k_seen_min<<<(unsigned)grid_for(most_new, kSeenSlice, 1 << 30) * ug, 1024, (size_t)rg_min64(most_new, kSeenSlice) * 4, s>>>(S, h);
                 RG_LAUNCH_CHECK(ctx, "k_seen_min");
                 const unsigned seen_blocks = (unsigned)grid_for(eub_max[h], kSeenEdges, 1 << 30);
-                k_seen_count<<<seen_blocks * ug, 1024, 0, s>>>(G, S, h);
+                k_seen_count<<<seen_blocks * ug, 1024, 0, s>>>(S, h);
                 RG_LAUNCH_CHECK(ctx, "k_seen_count");
-                k_seen_emit<<<seen_blocks * ug, 1024, 0, s>>>(G, S, h);
+                k_seen_emit<<<seen_blocks * ug, 1024, 0, s>>>(S, h);
                 RG_LAUNCH_CHECK(ctx, "k_seen_emit");
             }
         } else if (mode == kTierFirstSeen) {
             // new tier: edges that open a node, counted per block of the edge list, scanned, emitted in edge order
             const int fs_blocks = (int)rg_max64(1, rg_div_up(eub_max[h], kEdgesPerBlock));
-            k_first_seen_count<<<(unsigned)(fs_blocks) * ug, 256, 0, s>>>(G, S, h);
+            k_first_seen_count<<<(unsigned)(fs_blocks) * ug, 256, 0, s>>>(S, h);
             RG_LAUNCH_CHECK(ctx, "k_first_seen_count");
-            k_scan_tier<<<ug, 1024, 0, s>>>(G, S, h, fs_blocks);
+            k_scan_tier<<<ug, 1024, 0, s>>>(S, h, fs_blocks);
             RG_LAUNCH_CHECK(ctx, "k_scan_tier");
-            k_first_seen_emit<<<(unsigned)(fs_blocks) * ug, 256, 0, s>>>(G, S, h);
+            k_first_seen_emit<<<(unsigned)(fs_blocks) * ug, 256, 0, s>>>(S, h);
             RG_LAUNCH_CHECK(ctx, "k_first_seen_emit");
         } else {
             // new tier: count fresh bits per block, scan, emit ascending
             const int tier_blocks = (int)rg_max64(1, rg_div_up(words, kWordsPerBlock));
             k_tier_count<<<(unsigned)(tier_blocks) * ug, 256, 0, s>>>(S);
             RG_LAUNCH_CHECK(ctx, "k_tier_count");
-            k_scan_tier<<<ug, 1024, 0, s>>>(G, S, h, tier_blocks);
+            k_scan_tier<<<ug, 1024, 0, s>>>(S, h, tier_blocks);
             RG_LAUNCH_CHECK(ctx, "k_scan_tier");
-            k_tier_emit<<<(unsigned)(tier_blocks) * ug, 256, 0, s>>>(G, S, h);
+            k_tier_emit<<<(unsigned)(tier_blocks) * ug, 256, 0, s>>>(S, h);
             RG_LAUNCH_CHECK(ctx, "k_tier_emit");
         }
-        if (shared) {
-            if ((st = relabel()) != RG_OK) return st;
-            for (int g = 0; g < group; ++g) R.nbr_local[h][g] = nullptr;
-            relabel_edges = 0;
-        }
+        if (shared && (st = relabel(h, h)) != RG_OK) return st;
     }
-    if ((st = relabel()) != RG_OK) return st;
+    if (!shared && (st = relabel(0, num_hops - 1)) != RG_OK) return st;
     ctx->sampler_dirty = false;
     ctx->last_sample_group = group;
     ctx->last_sample_nodes = N;
