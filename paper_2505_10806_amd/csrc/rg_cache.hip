@@ -24,7 +24,8 @@ __global__ void __launch_bounds__(256) k_histogram(const int32_t* __restrict__ n
 // Where the ranges begin in every run is found first, by k_hist_bounds: searched for by every workgroup itself (two bisections
 // per run of 18 steps, whose lines no other lane shares) the 10 M random lines took 180 of 184 us for 72 M entries on 2.4 M
 // nodes with first batches.  The range is chosen so that the workgroups, two per compute unit, make whole rounds of the
-// device (598 on 512 places: 273 us).  Now 19 + 92 us.
+// device (598 on 512 places: 273 us).  The counting is bound by latency, LDS atomics and VALU alike (a third of the time each for
+// the last two): with a step's loads waited for before the next one's began it took 95 us, now 66, and the bounds 19.
 constexpr int kHistRangeMax = 8192;    // ids per workgroup at most (32 KB of LDS, 64 KB when first batches are tracked as well)
 constexpr int kHistRangeMin = 512;
 constexpr int kHistRunTile = 1024;     // runs whose bounds are in LDS at a time
@@ -117,31 +118,61 @@ __global__ void __launch_bounds__(1024) k_histogram_runs(const int32_t* __restri
         }
         __syncthreads();
         const int in_tile = num_runs - tile < kHistRunTile ? num_runs - tile : kHistRunTile;
-        for (int q = wave; q < in_tile; q += nwaves) {                  // one wavefront per run segment
-            const int lo = __builtin_amdgcn_readfirstlane(seg_lo[q]), hi = __builtin_amdgcn_readfirstlane(seg_hi[q]);
-            if (lo >= hi) continue;
-            const int b = (tile + q) / num_hops;
-            const int32_t* base = nodes + (int64_t)b * batch_stride;
-            int e0 = lo + lane;
-            if (hi - lo <= RG_WAVE) {                                   // short segments, of which a call may have mostly
-                const uint32_t off = e0 < hi ? (uint32_t)(base[e0] - (int)v0) : 0xFFFFFFFFu;
-                if (off < (uint32_t)range) {                            // always true inside an ascending segment
-                    atomicAdd(&priv[off], 1u);
-                    if (FIRST) atomicMin(&firstb[off], (uint32_t)(b0 + b));
+        // One wavefront per run segment, 64 * U entries a step.  The entries of its next step are on their way while it counts: lanes
+        // behind the segment's end read its last entry again, and behind the last segment something else that is there, so that
+        // every step has the same loads in flight and the wait for one does not take in the other's.
+        int q = wave - nwaves, e = 0, hi = 0;
+        int b = tile / num_hops, t = tile % num_hops + wave;              // batch and hop of run tile + q + nwaves
+        b += t / num_hops;
+        t %= num_hops;
+        const int db = nwaves / num_hops, dt = nwaves % num_hops;
+        int at_b = 0;
+        const int32_t* base = tier_off;
+        const auto fetch = [&](uint32_t (&id)[U], int& left, int& batch) {
+            while (e >= hi && q < in_tile) {
+                q += nwaves;
+                if (q < in_tile) {
+                    e = __builtin_amdgcn_readfirstlane(seg_lo[q]);
+                    hi = __builtin_amdgcn_readfirstlane(seg_hi[q]);
+                    base = nodes + (int64_t)b * batch_stride;
+                    at_b = b0 + b;
+                    b += db;
+                    t += dt;
+                    if (t >= num_hops) { t -= num_hops; ++b; }
+                } else {
+                    base = tier_off;
+                    e = hi = 0;
                 }
-                continue;
             }
-            for (; e0 < hi; e0 += RG_WAVE * U) {
-                uint32_t off[U];
+            left = hi - e;
+            const int last = left > 0 ? left - 1 : 0;
 #pragma unroll
-                for (int u = 0; u < U; ++u) off[u] = e0 + RG_WAVE * u < hi ? (uint32_t)(base[e0 + RG_WAVE * u] - (int)v0) : 0xFFFFFFFFu;
-#pragma unroll
-                for (int u = 0; u < U; ++u)
-                    if (off[u] < (uint32_t)range) {
-                        atomicAdd(&priv[off[u]], 1u);
-                        if (FIRST) atomicMin(&firstb[off[u]], (uint32_t)(b0 + b));
-                    }
+            for (int u = 0; u < U; ++u) {
+                const int i = RG_WAVE * u + lane;
+                id[u] = (uint32_t)base[e + (i < last ? i : last)];
             }
+            e = e + RG_WAVE * U < hi ? e + RG_WAVE * U : hi;
+            batch = at_b;
+        };
+        const auto count = [&](const uint32_t (&id)[U], int left, int batch) {
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const uint32_t off = id[u] - (uint32_t)v0;
+                if (RG_WAVE * u + lane < left && off < (uint32_t)range) {            // (always in the range inside an ascending segment)
+                    atomicAdd(&priv[off], 1u);
+                    if (FIRST) atomicMin(&firstb[off], (uint32_t)batch);
+                }
+            }
+        };
+        uint32_t x[U], y[U];
+        int bx, by, nx, ny;
+        fetch(x, nx, bx);
+        while (nx > 0) {
+            fetch(y, ny, by);
+            count(x, nx, bx);
+            if (ny <= 0) break;
+            fetch(x, nx, bx);
+            count(y, ny, by);
         }
     }
     __syncthreads();
