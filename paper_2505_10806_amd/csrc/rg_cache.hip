@@ -3,6 +3,7 @@
 // first use ahead of the gathers (the prefetcher of Section III: with a per-batch claim pass or from a
 // per-epoch plan).
 #include <math.h>
+#include <stddef.h>
 
 #include "rg_rowcopy.h"
 
@@ -201,10 +202,11 @@ __global__ void __launch_bounds__(256) k_histogram_seeds(const int32_t* __restri
 // ---------------------------------------------------------------------------- threshold select
 // Finds the count threshold T of the K_eff-th best candidate.  Access counts are bounded by the number of batches of
 // the period (a few hundred), so one streaming pass with a histogram of the counts clamped to kLowBins - 1 resolves T
-// whenever T < kLowBins - 1.  Only when the K_eff-th best candidate sits in the clamped last bin do the four byte passes
-// of a most-significant-byte-first radix select run; otherwise their kernels return at once.
-// The histograms stay in TopkCtl and the kernels up to the count read the threshold off them themselves (rg_topk_state, 8 KB
-// from L2 per workgroup): a launch of one workgroup between two passes costs 4.5 us, and there were five of them.
+// whenever T < kLowBins - 1, and its last workgroup says so.  Only when the K_eff-th best candidate sits in the clamped last bin do
+// the three passes of a most-significant-digit-first radix select (11 + 11 + 10 bits) run; otherwise their kernels return at once.
+// What they find stays in TopkCtl and is read off there by the kernels up to the count (rg_topk_state).
+// Bound by launches: with four passes of 8 bits, every kernel working out the state from the bins for itself and the bins cleared by a
+// launch in front, selection at 2.4 M nodes took 60 us, now 37 (at 10 M nodes 107, now 70; at 40 M 362, now 239).  The emit clears them for the next call.
 constexpr int kLowBins = 2048;
 constexpr int kBallotBins = 4;       // counts 1..kBallotBins are tallied with wave ballots instead of LDS atomics
 
@@ -215,12 +217,22 @@ struct TopkState {
     uint32_t resolved;   // 1: T and need are final without radix passes
 };
 
-struct TopkCtl {
-    uint32_t hist[4][256];
+constexpr int kRadixPasses = 3;
+constexpr int kRadixBins = 2048;
+struct TopkCtl {                     // everything up to `low_state` is zero in front of a selection
+    uint32_t hist[kRadixPasses][kRadixBins];
     uint32_t low[kLowBins];          // candidates per clamped count
     unsigned long long ovf_sum;      // sum of the counts of the candidates in the last (clamped) bin
+    uint32_t done, pad;              // workgroups of k_topk_hist_low that have added theirs
+    TopkState low_state;             // from `low` alone, by the last of them
     TopkState state;                 // as k_topk_count found it
 };
+constexpr int kCtlClear = offsetof(TopkCtl, low_state) / 4;
+
+// Digit `pass` of a count, and the bits in front of it.
+__device__ __forceinline__ int rg_radix_shift(int pass) { return pass == 0 ? 21 : (pass == 1 ? 10 : 0); }
+__device__ __forceinline__ uint32_t rg_radix_digit(uint32_t c, int pass) { return (c >> rg_radix_shift(pass)) & (pass == 2 ? 1023u : 2047u); }
+__device__ __forceinline__ uint32_t rg_radix_front(uint32_t c, int pass) { return pass == 0 ? 0u : c >> (pass == 1 ? 21 : 10); }
 
 __device__ __forceinline__ bool rg_is_candidate(uint32_t home_word, uint32_t count) {
     return (home_word >> RG_TAG_SHIFT) == RG_TAG_REMOTE && count >= 1u;
@@ -228,17 +240,92 @@ __device__ __forceinline__ bool rg_is_candidate(uint32_t home_word, uint32_t cou
 
 __global__ void __launch_bounds__(256) k_topk_init(TopkCtl* __restrict__ ctl, int hist_only) {
     uint32_t* w = (uint32_t*)ctl;
-    const int n = (int)((hist_only ? sizeof(ctl->hist) : sizeof(TopkCtl)) / 4);      // hist_only: a later selection of the hit curve
+    const int n = hist_only ? (int)(sizeof(ctl->hist) / 4) : kCtlClear;              // hist_only: a later selection of the hit curve
     for (int i = blockIdx.x * 256 + threadIdx.x; i < n; i += gridDim.x * 256) w[i] = 0u;
+}
+
+// The bin of one of 2048 that holds the need-th best, bins in descending order, `n` of them in bin h[j] of this thread
+// (bins 2047 - PER * t downwards): its index, and through `need` how many of it are wanted.  Every thread of the workgroup calls it.
+template <int NT>
+__device__ __forceinline__ void rg_pick_bin(const uint32_t (&h)[kRadixBins / NT], uint32_t need, int* smem, uint32_t* bin_s, uint32_t* need_s) {
+    constexpr int PER = kRadixBins / NT;
+    int mine = 0;
+#pragma unroll
+    for (int j = 0; j < PER; ++j) mine += (int)h[j];
+    int total;
+    uint32_t above = (uint32_t)rg_block_excl_scan<NT / RG_WAVE>(mine, smem, &total);
+#pragma unroll
+    for (int j = 0; j < PER; ++j) {
+        if (above < need && need <= above + h[j]) {                       // exactly one bin satisfies this
+            *bin_s = (uint32_t)(kRadixBins - 1 - (PER * (int)threadIdx.x + j));
+            *need_s = need - above;
+        }
+        above += h[j];
+    }
+    __syncthreads();
+}
+
+// K_eff = min(capacity, #candidates) and its threshold as far as the low histogram knows it.
+template <int NT>
+__device__ __forceinline__ TopkState rg_low_state(const TopkCtl* ctl, int64_t capacity) {
+    static_assert(kLowBins == kRadixBins, "one way to look a bin up");
+    __shared__ int smem[NT / RG_WAVE + 1];
+    __shared__ uint32_t bin, need;
+    constexpr int PER = kLowBins / NT;
+    uint32_t h[PER];
+    int mine = 0, total;
+#pragma unroll
+    for (int j = 0; j < PER; ++j) {      // (the last workgroup of k_topk_hist_low reads what others have just added)
+        h[j] = __hip_atomic_load(&ctl->low[kLowBins - 1 - (PER * (int)threadIdx.x + j)], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        mine += (int)h[j];
+    }
+    (void)rg_block_excl_scan<NT / RG_WAVE>(mine, smem, &total);
+    const uint64_t k = (uint64_t)capacity < (uint64_t)total ? (uint64_t)capacity : (uint64_t)total;
+    if (k == 0) return TopkState{0xFFFFFFFFu, 0u, 0u, 1u};                // uniform; a threshold no count reaches
+    rg_pick_bin<NT>(h, (uint32_t)k, smem, &bin, &need);
+    return bin < (uint32_t)(kLowBins - 1) ? TopkState{bin, need, (uint32_t)k, 1u}
+                                          : TopkState{0u, (uint32_t)k, (uint32_t)k, 0u};      // the clamped bin: radix passes decide
+}
+
+// The same with what the first `passes` radix histograms say where the low one leaves it open.
+template <int NT>
+__device__ __forceinline__ TopkState rg_topk_state(const TopkCtl* ctl, TopkState st, int passes) {
+    __shared__ int smem[NT / RG_WAVE + 1];
+    __shared__ uint32_t bin, need;
+    constexpr int PER = kRadixBins / NT;
+    if (st.resolved) return st;                                           // uniform
+    for (int pass = 0; pass < passes; ++pass) {
+        uint32_t h[PER];
+#pragma unroll
+        for (int j = 0; j < PER; ++j) h[j] = ctl->hist[pass][kRadixBins - 1 - (PER * (int)threadIdx.x + j)];
+        rg_pick_bin<NT>(h, st.need, smem, &bin, &need);
+        st.T |= bin << rg_radix_shift(pass);
+        st.need = need;
+        __syncthreads();
+    }
+    return st;
+}
+
+// Four consecutive words from i on, 0 behind the end: one 16-byte access where the array and all four allow it.
+__device__ __forceinline__ void rg_load4(const void* __restrict__ p, int64_t i, int64_t n, uint32_t (&x)[4]) {
+    const uint32_t* w = (const uint32_t*)p;
+    if (((uintptr_t)w & 15u) == 0u && i + 3 < n) {
+        const uint4 v = *(const uint4*)(w + i);
+        x[0] = v.x; x[1] = v.y; x[2] = v.z; x[3] = v.w;
+    } else {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) x[q] = i + q < n ? w[i + q] : 0u;
+    }
 }
 
 // low[min(count, kLowBins - 1)] += 1 for every candidate; ovf_sum += count for those in the last bin.  One workgroup per
 // compute unit: with more of them their additions to the same few bins queue up (1196 workgroups 38 us at 2.4 M nodes).  Above
 // 8 Mi nodes two, which read faster: the selection at 10 M nodes 110 -> 104 us, at 40 M 412 -> 364, at 100 M 972 -> 858.
 __global__ void __launch_bounds__(1024) k_topk_hist_low(const uint32_t* __restrict__ counts, const int32_t* __restrict__ home, int64_t n,
-                                                        TopkCtl* __restrict__ ctl) {
+                                                        TopkCtl* ctl, int64_t capacity) {
     constexpr int U = 4;
     __shared__ uint32_t h[kLowBins];
+    __shared__ int last_s;
     __shared__ unsigned long long ovf_s;
     for (int i = threadIdx.x; i < kLowBins; i += 1024) h[i] = 0u;
     if (threadIdx.x == 0) ovf_s = 0ull;
@@ -247,12 +334,8 @@ __global__ void __launch_bounds__(1024) k_topk_hist_low(const uint32_t* __restri
     const int lane = rg_lane();
     for (int64_t v0 = (int64_t)blockIdx.x * (1024 * U); v0 < n; v0 += (int64_t)gridDim.x * (1024 * U)) {   // uniform per workgroup
         uint32_t c[U], hw[U];
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int64_t v = v0 + u * 1024 + threadIdx.x;
-            c[u] = v < n ? counts[v] : 0u;
-            hw[u] = v < n ? (uint32_t)home[v] : 0u;
-        }
+        rg_load4(counts, v0 + 4 * threadIdx.x, n, c);
+        rg_load4(home, v0 + 4 * threadIdx.x, n, hw);
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             uint32_t bin = 0u;                               // bin 0: not a candidate
@@ -273,74 +356,39 @@ __global__ void __launch_bounds__(1024) k_topk_hist_low(const uint32_t* __restri
     __syncthreads();
     for (int i = threadIdx.x; i < kLowBins; i += 1024) {
         const uint32_t mine = h[i];
-        if (mine) atomicAdd(&ctl->low[i], mine);
+        // (with the old value awaited the addition has been made when the workgroup says so below; a fence instead, which writes back
+        // the L2, took 65 us)
+        if (mine) { const uint32_t old = atomicAdd(&ctl->low[i], mine); asm volatile("" :: "v"(old)); }
     }
     if (threadIdx.x == 0 && ovf_s) atomicAdd(&ctl->ovf_sum, ovf_s);
-}
-
-// K_eff = min(capacity, #candidates) and its threshold, from the low histogram and, where that leaves it open, the first
-// `passes` byte histograms.  Every thread of a workgroup of NT threads calls it.
-template <int NT>
-__device__ __forceinline__ TopkState rg_topk_state(const TopkCtl* __restrict__ ctl, int64_t capacity, int passes) {
-    __shared__ int smem[NT / RG_WAVE + 1];
-    __shared__ TopkState st;
-    constexpr int PER = kLowBins / NT;                       // thread t owns bins kLowBins-1-PER*t downwards
-    uint32_t h[PER];
-    int mine = 0;
-#pragma unroll
-    for (int j = 0; j < PER; ++j) {
-        h[j] = ctl->low[kLowBins - 1 - (PER * (int)threadIdx.x + j)];
-        mine += (int)h[j];
-    }
-    int total;
-    int above = rg_block_excl_scan<NT / RG_WAVE>(mine, smem, &total);     // candidates in strictly larger bins
-    const uint64_t k = (uint64_t)capacity < (uint64_t)total ? (uint64_t)capacity : (uint64_t)total;
-    if (k == 0) return TopkState{0xFFFFFFFFu, 0u, 0u, 1u};                // uniform; a threshold no count reaches
-#pragma unroll
-    for (int j = 0; j < PER; ++j) {
-        const int bin = kLowBins - 1 - (PER * (int)threadIdx.x + j);
-        if ((uint64_t)above < k && k <= (uint64_t)above + h[j])           // exactly one bin satisfies this
-            st = bin < kLowBins - 1 ? TopkState{(uint32_t)bin, (uint32_t)(k - above), (uint32_t)k, 1u}
-                                    : TopkState{0u, (uint32_t)k, (uint32_t)k, 0u};   // the clamped bin: radix passes decide
-        above += (int)h[j];
-    }
+    if (capacity < 0) return;                                             // the hit curve looks its capacities up itself
+    __syncthreads();                                                      // every addition of this workgroup is made
+    if (threadIdx.x == 0) last_s = atomicAdd(&ctl->done, 1u) == gridDim.x - 1;
     __syncthreads();
-    if (st.resolved) return st;                                           // uniform
-    for (int pass = 0; pass < passes; ++pass) {                           // the byte value holding the need-th largest remaining candidate
-        const int d = 255 - (int)threadIdx.x;
-        const int n = d >= 0 ? (int)ctl->hist[pass][d] : 0;
-        const int larger = rg_block_excl_scan<NT / RG_WAVE>(n, smem, &total);
-        const uint32_t need = st.need;
-        __syncthreads();
-        if ((uint32_t)larger < need && need <= (uint32_t)larger + (uint32_t)n) {      // exactly one byte value satisfies this
-            st.T |= (uint32_t)d << (24 - 8 * pass);
-            st.need = need - (uint32_t)larger;
-        }
-        __syncthreads();
-    }
-    return st;
+    if (!last_s) return;                                                  // uniform
+    const TopkState st = rg_low_state<1024>(ctl, capacity);
+    if (threadIdx.x == 0) ctl->low_state = st;
 }
 
-// Histogram of byte `pass` (0 = most significant) of the counts of candidates that match the prefix.  skip (or NULL): a flag that,
-// when set, says that nobody asks for it.
-__global__ void __launch_bounds__(256) k_topk_hist(const uint32_t* __restrict__ counts, const int32_t* __restrict__ home, int64_t n,
-                                                   int pass, int64_t capacity, TopkCtl* __restrict__ ctl, const uint32_t* __restrict__ skip) {
-    __shared__ uint32_t h[256];
-    if (skip && *skip) return;                               // uniform
-    const TopkState st = rg_topk_state<256>(ctl, capacity, pass);
+// Histogram of digit `pass` (0 = most significant) of the counts of candidates that match the digits in front.  skip: of the hit curve, a
+// flag that, when set, says that nobody asks for it; NULL: the low state is there.
+__global__ void __launch_bounds__(1024) k_topk_hist(const uint32_t* __restrict__ counts, const int32_t* __restrict__ home, int64_t n,
+                                                   int pass, int64_t capacity, TopkCtl* ctl, const uint32_t* __restrict__ skip) {
+    __shared__ uint32_t h[kRadixBins];
+    if (skip ? *skip : ctl->low_state.resolved) return;      // uniform
+    const TopkState st = rg_topk_state<1024>(ctl, skip ? rg_low_state<1024>(ctl, capacity) : ctl->low_state, pass);
     if (st.resolved) return;                                 // uniform
-    h[threadIdx.x] = 0u;
+    for (int i = threadIdx.x; i < kRadixBins; i += 1024) h[i] = 0u;
     __syncthreads();
-    const int shift = 24 - 8 * pass;
+    const uint32_t front = rg_radix_front(st.T, pass);
     for (int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; v < n; v += (int64_t)gridDim.x * blockDim.x) {
         const uint32_t c = counts[v];
-        if (!rg_is_candidate((uint32_t)home[v], c)) continue;
-        if (pass > 0 && (c >> (shift + 8)) != (st.T >> (shift + 8))) continue;
-        atomicAdd(&h[(c >> shift) & 255u], 1u);
+        if (!rg_is_candidate((uint32_t)home[v], c) || rg_radix_front(c, pass) != front) continue;
+        atomicAdd(&h[rg_radix_digit(c, pass)], 1u);
     }
     __syncthreads();
-    const uint32_t mine = h[threadIdx.x];
-    if (mine) atomicAdd(&ctl->hist[pass][threadIdx.x], mine);
+    for (int i = threadIdx.x; i < kRadixBins; i += 1024)
+        if (h[i]) atomicAdd(&ctl->hist[pass][i], h[i]);
 }
 
 constexpr int kCapChunk = 64;
@@ -419,18 +467,17 @@ constexpr int kTopkSelfScan = 4096;    // blocks up to which the emit kernel add
 
 // Per block: number of candidates above the threshold and number tied with it; the number of rows selected.
 __global__ void __launch_bounds__(1024) k_topk_count(const uint32_t* __restrict__ counts, const int32_t* __restrict__ home, int64_t n,
-                                                     TopkCtl* __restrict__ ctl, int64_t capacity, int32_t* __restrict__ blk_gt,
+                                                     TopkCtl* ctl, int32_t* __restrict__ blk_gt,
                                                      int32_t* __restrict__ blk_eq, int64_t* __restrict__ num_cached) {
     __shared__ int part[1024 / RG_WAVE];
     const int64_t v0 = (int64_t)blockIdx.x * kNodesPerBlock + threadIdx.x * 4;
-    uint32_t c[4];
+    uint32_t c[4], hw[4];
     bool cand[4];
+    rg_load4(counts, v0, n, c);
+    rg_load4(home, v0, n, hw);
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-        c[q] = v0 + q < n ? counts[v0 + q] : 0u;
-        cand[q] = v0 + q < n && rg_is_candidate((uint32_t)home[v0 + q], c[q]);
-    }
-    const TopkState st = rg_topk_state<1024>(ctl, capacity, 4);
+    for (int q = 0; q < 4; ++q) cand[q] = v0 + q < n && rg_is_candidate(hw[q], c[q]);
+    const TopkState st = rg_topk_state<1024>(ctl, ctl->low_state, kRadixPasses);
     int both = 0;                                            // above the threshold << 16 | tied with it: at most 4096 of either
 #pragma unroll
     for (int q = 0; q < 4; ++q) both += cand[q] ? (c[q] > st.T ? 1 << 16 : c[q] == st.T) : 0;
@@ -468,7 +515,7 @@ __global__ void __launch_bounds__(1024) k_topk_scan(int32_t* __restrict__ blk_gt
 // Slots are handed out in ascending id, so cache_ids comes out sorted.  scanned: the per-block counts are exclusive prefixes
 // already.  filled (NULL: left alone): bit s = `resident` for every selected slot, 0 behind them.
 __global__ void __launch_bounds__(1024) k_topk_emit(const uint32_t* __restrict__ counts, const int32_t* __restrict__ home, int64_t n,
-                                                    const TopkCtl* __restrict__ ctl, const int32_t* __restrict__ blk_gt,
+                                                    TopkCtl* ctl, const int32_t* __restrict__ blk_gt,
                                                     const int32_t* __restrict__ blk_eq, int scanned, int32_t* __restrict__ cache_ids,
                                                     int32_t* __restrict__ loc, uint32_t* __restrict__ filled, int64_t filled_words,
                                                     int resident) {
@@ -477,11 +524,8 @@ __global__ void __launch_bounds__(1024) k_topk_emit(const uint32_t* __restrict__
     __shared__ int pg[NW], pe[NW];
     const int64_t v0 = (int64_t)blockIdx.x * kNodesPerBlock + threadIdx.x * 4;
     uint32_t hw[4], c[4];
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-        c[q] = v0 + q < n ? counts[v0 + q] : 0u;
-        hw[q] = v0 + q < n ? (uint32_t)home[v0 + q] : 0u;
-    }
+    rg_load4(counts, v0, n, c);
+    rg_load4(home, v0, n, hw);
     int gt_before = 0, eq_before = 0;
     if (scanned) {
         gt_before = blk_gt[blockIdx.x];
@@ -497,6 +541,7 @@ __global__ void __launch_bounds__(1024) k_topk_emit(const uint32_t* __restrict__
         for (int w = 0; w < NW; ++w) { gt_before += pg[w]; eq_before += pe[w]; }
     }
     const TopkState st = ctl->state;
+    for (int i = blockIdx.x * 1024 + threadIdx.x; i < kCtlClear; i += gridDim.x * 1024) ((uint32_t*)ctl)[i] = 0u;      // for the next call
     const int need = (int)st.need;
     if (filled) {
         for (int64_t w = (int64_t)blockIdx.x * 1024 + threadIdx.x; w < filled_words; w += (int64_t)gridDim.x * 1024) {
@@ -528,24 +573,28 @@ __global__ void __launch_bounds__(1024) k_topk_emit(const uint32_t* __restrict__
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
         const int64_t v = v0 + q;
-        if (v >= n) break;
         if (sel[q]) {
             cache_ids[slot] = (int32_t)v;
-            loc[v] = (int32_t)((RG_TAG_CACHE << RG_TAG_SHIFT) | (uint32_t)slot);
+            hw[q] = (RG_TAG_CACHE << RG_TAG_SHIFT) | (uint32_t)slot;
             ++slot;
-        } else {
-            loc[v] = (int32_t)hw[q];
         }
+    }
+    if (((uintptr_t)loc & 15u) == 0u && v0 + 3 < n) {
+        *(uint4*)(loc + v0) = make_uint4(hw[0], hw[1], hw[2], hw[3]);
+    } else {
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+            if (v0 + q < n) loc[v0 + q] = (int32_t)hw[q];
     }
 }
 
 // Radix path of the hit curve: hits += sum of the counts above the threshold plus (ties taken) x threshold.
 // `resolved` = 1 when the histogram pass already produced this capacity's value.
 __global__ void __launch_bounds__(256) k_hit_sum(const uint32_t* __restrict__ counts, const int32_t* __restrict__ home, int64_t n,
-                                                 const TopkCtl* __restrict__ ctl, int64_t capacity, const uint32_t* __restrict__ resolved,
+                                                 const TopkCtl* ctl, int64_t capacity, const uint32_t* __restrict__ resolved,
                                                  unsigned long long* __restrict__ hits) {
     if (*resolved) return;                                   // uniform
-    const TopkState st = rg_topk_state<256>(ctl, capacity, 4);
+    const TopkState st = rg_topk_state<256>(ctl, rg_low_state<256>(ctl, capacity), kRadixPasses);
     const uint32_t T = st.T;
     unsigned long long above = 0ull;
     for (int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; v < n; v += (int64_t)gridDim.x * blockDim.x) {
@@ -1152,17 +1201,22 @@ rg_status rg_build_cache(rg_ctx* ctx, const uint32_t* counts, const int32_t* hom
     int32_t* blk_gt = (int32_t*)ctx->topk_blk.p;
     int32_t* blk_eq = blk_gt + nblocks;
 
-    k_topk_init<<<4, 256, 0, s>>>(ctl, 0);
-    RG_LAUNCH_CHECK(ctx, "k_topk_init");
+    // the emit of the call before this one has left the histograms zero; a recorded call does not count on it
+    const bool captured = rg_capturing(s);
+    if (captured || !ctx->topk_clean) {
+        k_topk_init<<<4, 256, 0, s>>>(ctl, 0);
+        RG_LAUNCH_CHECK(ctx, "k_topk_init");
+    }
+    if (!captured) ctx->topk_clean = false;                  // until the emit has been queued
     const int low_grid = low_grid_of(ctx, num_nodes);
-    k_topk_hist_low<<<low_grid, 1024, 0, s>>>(counts, home, num_nodes, ctl);
+    k_topk_hist_low<<<low_grid, 1024, 0, s>>>(counts, home, num_nodes, ctl, cache->capacity_rows);
     RG_LAUNCH_CHECK(ctx, "k_topk_hist_low");
-    const int hist_grid = (int)rg_max64(1, rg_min64(rg_div_up(num_nodes, 256 * 8), (int64_t)ctx->num_cus * 8));
-    for (int pass = 0; pass < 4; ++pass) {                   // return at once unless the threshold is in the clamped bin
-        k_topk_hist<<<hist_grid, 256, 0, s>>>(counts, home, num_nodes, pass, cache->capacity_rows, ctl, nullptr);
+    const int hist_grid = (int)rg_max64(1, rg_min64(rg_div_up(num_nodes, 1024 * 8), (int64_t)ctx->num_cus * 2));
+    for (int pass = 0; pass < kRadixPasses; ++pass) {        // return at once unless the threshold is in the clamped bin
+        k_topk_hist<<<hist_grid, 1024, 0, s>>>(counts, home, num_nodes, pass, cache->capacity_rows, ctl, nullptr);
         RG_LAUNCH_CHECK(ctx, "k_topk_hist");
     }
-    k_topk_count<<<(int)nblocks, 1024, 0, s>>>(counts, home, num_nodes, ctl, cache->capacity_rows, blk_gt, blk_eq, cache->num_cached);
+    k_topk_count<<<(int)nblocks, 1024, 0, s>>>(counts, home, num_nodes, ctl, blk_gt, blk_eq, cache->num_cached);
     RG_LAUNCH_CHECK(ctx, "k_topk_count");
     const int scanned = nblocks > kTopkSelfScan;
     if (scanned) {
@@ -1173,6 +1227,7 @@ rg_status rg_build_cache(rg_ctx* ctx, const uint32_t* counts, const int32_t* hom
     k_topk_emit<<<(int)nblocks, 1024, 0, s>>>(counts, home, num_nodes, ctl, blk_gt, blk_eq, scanned, cache->cache_ids,
                                               cache->loc, filled_words > 0 ? cache->filled : nullptr, filled_words, remote_store ? 1 : 0);
     RG_LAUNCH_CHECK(ctx, "k_topk_emit");
+    if (!captured) ctx->topk_clean = true;
 
     if (may_select && remote_store) {
         const void* ptrs[2] = {remote_store, cache->cache_rows};
@@ -1223,11 +1278,16 @@ rg_status rg_cache_hit_curve(rg_ctx* ctx, const uint32_t* counts, const int32_t*
         RG_LAUNCH_CHECK(ctx, "k_store_caps");
     }
     const int grid = (int)rg_max64(1, rg_min64(rg_div_up(num_nodes, 256 * 8), (int64_t)ctx->num_cus * 8));
+    const int hist_grid = (int)rg_max64(1, rg_min64(rg_div_up(num_nodes, 1024 * 8), (int64_t)ctx->num_cus * 2));
     const int low_grid = low_grid_of(ctx, num_nodes);
     // one pass over the nodes gives the histogram of the counts; every capacity is read off it
-    k_topk_init<<<4, 256, 0, s>>>(ctl, 0);
-    RG_LAUNCH_CHECK(ctx, "k_topk_init");
-    k_topk_hist_low<<<low_grid, 1024, 0, s>>>(counts, home, num_nodes, ctl);
+    const bool captured = rg_capturing(s);
+    if (captured || !ctx->topk_clean) {
+        k_topk_init<<<4, 256, 0, s>>>(ctl, 0);
+        RG_LAUNCH_CHECK(ctx, "k_topk_init");
+    }
+    if (!captured) ctx->topk_clean = false;                  // until it has been cleared again
+    k_topk_hist_low<<<low_grid, 1024, 0, s>>>(counts, home, num_nodes, ctl, -1);
     RG_LAUNCH_CHECK(ctx, "k_topk_hist_low");
     k_hit_curve_low<<<1, 256, 0, s>>>(ctl, caps_dev, num_capacities, (unsigned long long*)hits, (unsigned long long*)remote_total, resolved);
     RG_LAUNCH_CHECK(ctx, "k_hit_curve_low");
@@ -1238,13 +1298,16 @@ rg_status rg_cache_hit_curve(rg_ctx* ctx, const uint32_t* counts, const int32_t*
             k_topk_init<<<4, 256, 0, s>>>(ctl, 1);
             RG_LAUNCH_CHECK(ctx, "k_topk_init");
         }
-        for (int pass = 0; pass < 4; ++pass) {
-            k_topk_hist<<<grid, 256, 0, s>>>(counts, home, num_nodes, pass, capacities[j], ctl, resolved + j);
+        for (int pass = 0; pass < kRadixPasses; ++pass) {
+            k_topk_hist<<<hist_grid, 1024, 0, s>>>(counts, home, num_nodes, pass, capacities[j], ctl, resolved + j);
             RG_LAUNCH_CHECK(ctx, "k_topk_hist");
         }
         k_hit_sum<<<grid, 256, 0, s>>>(counts, home, num_nodes, ctl, capacities[j], resolved + j, (unsigned long long*)hits + j);
         RG_LAUNCH_CHECK(ctx, "k_hit_sum");
     }
+    k_topk_init<<<4, 256, 0, s>>>(ctl, 0);
+    RG_LAUNCH_CHECK(ctx, "k_topk_init");
+    if (!captured) ctx->topk_clean = true;
     return RG_OK;
 }
 

@@ -65,6 +65,7 @@ struct rg_ctx {
     std::vector<void*> outgrown;   // its predecessors, which graphs may hold (rg_destroy frees them)
     // top-K scratch
     RgBuf topk_ctl;     // TopkCtl
+    bool topk_clean = false;            // its histograms are zero
     RgBuf topk_blk;     // int32[2 * nblocks]
     RgBuf topk_caps;    // rg_cache_hit_curve: int64[num_capacities] capacities, then uint32[num_capacities] flags
     // prefetch scratch

@@ -410,6 +410,37 @@ def test_bitmap_counts_of_batches_in_any_order(B, ctx, n, group):
     assert np.array_equal(counts.cpu().numpy(), want) and np.array_equal(first.cpu().numpy(), want_first)
 
 
+def test_selection_after_other_selections(B):
+    """Selections that the clamped counts settle and that they do not, hit curves and replays of recorded calls of either, on one
+    context: each finds the histograms as it needs them."""
+    ctx, n, cap = B.Context(0), 70_003, 9_000
+    rng = np.random.default_rng(8)
+    home = np.where(rng.random(n) < 0.3, np.arange(n), np.arange(n) + (2 << 30) - (1 << 32)).astype(np.int32)
+    few, many = (rng.pareto(0.8, n) * 2).astype(np.int64) % 300, rng.integers(0, 1 << 32, n)
+    counts = {k: _i32(np.where(x > 0x7FFFFFFF, x - (1 << 32), x)) for k, x in (("few", few), ("many", many))}
+    want = {k: oracle.build_cache(x.astype(np.uint32), home, cap) for k, x in (("few", few), ("many", many))}
+    home_d, caches, graphs = _i32(home), {}, {}
+    for k in counts:
+        caches[k] = B.FeatureCache(n, cap, 4, DEV)
+        ctx.build_cache(counts[k], home_d, None, 4, caches[k])
+        graphs[k] = _captured(lambda: ctx.build_cache(counts[k], home_d, None, 4, caches[k]))
+    ctx.cache_hit_curve(counts["many"], home_d, [cap, 100, n])
+    graphs["curve"] = _captured(lambda: ctx.cache_hit_curve(counts["many"], home_d, [cap, 100, n]))
+    for how in ("few", "curve", "few", "many", "replay few", "many", "replay many", "few", "curve", "replay few", "replay curve", "many", "few"):
+        k = how.split()[-1]
+        if how.startswith("replay") or k == "curve":
+            graphs[k].replay()
+        else:
+            ctx.build_cache(counts[k], home_d, None, 4, caches[k])
+        torch.cuda.synchronize()
+        if k == "curve":
+            continue
+        ids, loc = want[k]
+        assert int(caches[k].num_cached) == ids.size, how
+        assert np.array_equal(caches[k].cache_ids[:ids.size].cpu().numpy(), ids) and np.array_equal(caches[k].loc.cpu().numpy(), loc), how
+    ctx.close()
+
+
 @pytest.mark.parametrize("copies", [2560, 2561, 4000])
 def test_schedule_of_ids_given_many_times(ctx, copies):
     """Seven ids a few thousand times each fill their buckets up to the last place and beyond; the others stay empty."""
