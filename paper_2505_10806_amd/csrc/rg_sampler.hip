@@ -1517,6 +1517,35 @@ struct Fanouts {
     int32_t v[RG_MAX_HOPS];
 };
 
+// Floyd's picks for one node, all in registers (whole row: its places in order).
+template <int KMAX>
+__device__ __forceinline__ void rg_draw(int32_t v, int64_t deg, int k, uint32_t hop, uint32_t k0, uint32_t k1, uint32_t epoch, uint32_t (&c)[KMAX]) {
+    if (deg <= k) {
+#pragma unroll
+        for (int s = 0; s < KMAX; ++s) c[s] = (uint32_t)s;             // whole row, CSR order
+        return;
+    }
+#pragma unroll
+    for (int blk = 0; blk < KMAX / 4; ++blk) {
+        if (blk * 4 < k) {
+            uint32_t w[4];
+            rg_philox4x32_10((uint32_t)v, hop, (uint32_t)blk, epoch, k0, k1, w);
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const int s = blk * 4 + q;
+                if (s < k) {                                           // Floyd: j = d-k+s, t uniform in [0, j]
+                    const uint32_t j = (uint32_t)(deg - k + s);
+                    const uint32_t t = __umulhi(w[q], j + 1u);
+                    bool found = false;
+#pragma unroll
+                    for (int l = 0; l < s; ++l) found |= (c[l] == t);
+                    c[s] = found ? j : t;
+                }
+            }
+        }
+    }
+}
+
 template <typename RP, int KMAX, int N>
 __global__ void __launch_bounds__(1024) k_sample_small(const RP* __restrict__ row_ptr, const int32_t* __restrict__ col_idx, const BatchTable<N> B, int group, const Fanouts fanouts,
                                                        uint32_t* __restrict__ visited_out, int64_t words64, int32_t* pos_all, int64_t num_nodes,
@@ -1567,30 +1596,7 @@ __global__ void __launch_bounds__(1024) k_sample_small(const RP* __restrict__ ro
             if (i >= n_h) continue;
             indptr[i] = at;
             uint32_t c[KMAX];
-            if (deg <= k) {
-#pragma unroll
-                for (int s = 0; s < KMAX; ++s) c[s] = (uint32_t)s;     // whole row, CSR order
-            } else {
-#pragma unroll
-                for (int blk = 0; blk < KMAX / 4; ++blk) {
-                    if (blk * 4 < k) {
-                        uint32_t w[4];
-                        rg_philox4x32_10((uint32_t)v, (uint32_t)hop, (uint32_t)blk, epoch, k0, k1, w);
-#pragma unroll
-                        for (int q = 0; q < 4; ++q) {
-                            const int s = blk * 4 + q;
-                            if (s < k) {                               // Floyd: j = d-k+s, t uniform in [0, j]
-                                const uint32_t j = (uint32_t)(deg - k + s);
-                                const uint32_t t = __umulhi(w[q], j + 1u);
-                                bool found = false;
-#pragma unroll
-                                for (int l = 0; l < s; ++l) found |= (c[l] == t);
-                                c[s] = found ? j : t;
-                            }
-                        }
-                    }
-                }
-            }
+            rg_draw<KMAX>(v, deg, k, (uint32_t)hop, k0, k1, epoch, c);
             int32_t u[KMAX];
 #pragma unroll
             for (int s = 0; s < KMAX; ++s)
@@ -1640,6 +1646,154 @@ __global__ void __launch_bounds__(1024) k_sample_small(const RP* __restrict__ ro
         }
     }
     __syncthreads();
+    for (int w = threadIdx.x; w < words; w += 1024) visited_out[g * words64 + w] = visited[w];
+}
+
+// A barrier for what is in LDS: global stores and loads stay in flight across it.
+__device__ __forceinline__ void rg_lds_barrier() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+// rg_block_excl_scan over 16 wavefronts with such barriers.
+__device__ __forceinline__ int rg_lds_excl_scan(int x, int* smem, int* total) {
+    const int wave = threadIdx.x >> 6, incl = rg_wave_incl_scan(x);
+    rg_lds_barrier();
+    if (rg_lane() == RG_WAVE - 1) smem[wave] = incl;
+    rg_lds_barrier();
+    int base = 0, tot = 0;
+#pragma unroll
+    for (int w = 0; w < 1024 / RG_WAVE; ++w) {
+        if (w < wave) base += smem[w];
+        tot += smem[w];
+    }
+    *total = tot;
+    return base + incl - x;
+}
+
+// Graphs and batches whose lists fit LDS as 16-bit numbers: positions, a hop's edges and the frontier, of which keep_hops tiers are kept:
+// the last one, which is not drawn for, only where there is room.  Nothing is then read back
+// from memory, the lists are written by consecutive lanes, and the only waits are for the rows and columns; the rows of a
+// round's nodes are on their way while the round before is drawn for.  256 seeds (10,5) on 10,000 nodes 25.6 -> 17.8 us, 8 x 300 on
+// 30,000 37.6 -> 24.6.
+inline int64_t rg_small_lists_bytes(int64_t num_nodes, int64_t frontier, int64_t edges) {
+    return 2 * rg_div_up(num_nodes, 32) * 4 + 2 * (num_nodes + frontier + edges) + 8;
+}
+constexpr int64_t kSmallLds = 160 * 1024 - 512;
+// Whose lists fit: by edges up to which one launch is the faster way.  Its time grows with the edges, that of a launch per phase with
+// the hops: (10,5) 26 k edges 25-30 us / 46, 29 k on 4000 nodes 42 / 48, 32 k there 54 / 50, 62 k on 10,000 45 / 52; (10,10,10)
+// 27 k 30-36 / 62, 42 k on 30,000 nodes 52 / 62, of 16 batches 73 / 69; (5,5,5,5) 67 k 48 / 83.  A thread draws for a node, so larger fan-outs take
+// longer: (25,10) 26 k 40-60 / 48, 37 k 50-79 / 50, (32,16) 28 k 54 / 46.
+constexpr int64_t kSmallEdgesPerHop = 13500;
+inline bool rg_small_lists_fit(int64_t num_nodes, int64_t frontier, int64_t hop_edges) {
+    return num_nodes > 0 && num_nodes <= 65536 && rg_small_lists_bytes(num_nodes, frontier, hop_edges) <= kSmallLds;
+}
+
+template <typename RP, int KMAX, int N>
+__global__ void __launch_bounds__(1024) k_sample_small_lists(const RP* __restrict__ row_ptr, const int32_t* __restrict__ col_idx,
+                                                             const BatchTable<N> B, int group, const Fanouts fanouts,
+                                                             uint32_t* __restrict__ visited_out, int64_t words64, int64_t num_nodes,
+                                                             int frontier_most, int keep_hops, int hops, uint32_t k0, uint32_t k1,
+                                                             uint32_t epoch) {
+    extern __shared__ uint32_t small_bits[];
+    __shared__ int smem[1024 / RG_WAVE + 1];
+    const int g = blockIdx.x, words = (int)words64;
+    uint32_t* visited = small_bits;
+    uint32_t* marked = small_bits + words;                             // members and the ids the hop has sampled
+    uint16_t* pos = (uint16_t*)(small_bits + 2 * words);
+    uint16_t* front = pos + num_nodes;
+    uint16_t* list = front + frontier_most;
+    const auto entry = [&](int field) { return rg_global(B.v[field * group + g]); };
+    const int32_t* __restrict__ seeds = entry(kSeeds);
+    int32_t* __restrict__ nodes = entry(kNodes);
+    int32_t* __restrict__ tier_off = entry(kTierOff);
+    int32_t* __restrict__ edges_out = entry(kEdgesOut);
+    for (int w = threadIdx.x; w < 2 * words; w += 1024) small_bits[w] = 0u;
+    int n_h = (int)B.v[kNumSeeds * group + g];
+    rg_lds_barrier();
+    for (int i = threadIdx.x; i < n_h; i += 1024) {
+        const int32_t v = seeds[i];
+        nodes[i] = v;
+        front[i] = (uint16_t)v;
+        pos[v] = (uint16_t)i;
+        atomicOr(&visited[(uint32_t)v >> 5], 1u << (v & 31));
+        atomicOr(&marked[(uint32_t)v >> 5], 1u << (v & 31));
+    }
+    if (threadIdx.x == 0) { tier_off[0] = 0; tier_off[1] = n_h; }
+    const int per = (words + 1023) / 1024 | 1;                         // consecutive bitmap words per thread, odd: no two lanes on a bank
+    const int w0 = (int)threadIdx.x * per, w1 = w0 + per < words ? w0 + per : words;
+    for (int hop = 0; hop < hops; ++hop) {
+        const int k = fanouts.v[hop];
+        int32_t* __restrict__ indptr = entry(kHopFields + kHopFieldCount * hop + kIndptr);
+        int32_t* __restrict__ nbr = entry(kHopFields + kHopFieldCount * hop + kNbr);
+        int32_t* __restrict__ nbr_local = entry(kHopFields + kHopFieldCount * hop + kNbrLocal);
+        int edges = 0;
+        rg_lds_barrier();                                              // the frontier and the bits are complete
+        int32_t v_next = 0;
+        RP a_next = 0, b_next = 0;
+        const auto rows_of = [&](int i) {
+            if (i < n_h) {
+                v_next = front[i];
+                a_next = row_ptr[v_next];
+                b_next = row_ptr[v_next + 1];
+            }
+        };
+        rows_of((int)threadIdx.x);
+        for (int i0 = 0; i0 < n_h; i0 += 1024) {
+            const int i = i0 + (int)threadIdx.x;
+            const int32_t v = v_next;
+            const int64_t start = (int64_t)a_next, deg = i < n_h ? (int64_t)(b_next - a_next) : 0;
+            rows_of(i + 1024);
+            const int m = deg <= k ? (int)deg : k;
+            int total;
+            const int at = edges + rg_lds_excl_scan(m, smem, &total);
+            edges += total;
+            if (i >= n_h) continue;
+            indptr[i] = at;
+            uint32_t c[KMAX];
+            rg_draw<KMAX>(v, deg, k, (uint32_t)hop, k0, k1, epoch, c);
+            int32_t u[KMAX];
+#pragma unroll
+            for (int s = 0; s < KMAX; ++s)
+                if (s < m) u[s] = col_idx[start + (int64_t)c[s]];
+#pragma unroll
+            for (int s = 0; s < KMAX; ++s)
+                if (s < m) {
+                    list[at + s] = (uint16_t)u[s];
+                    atomicOr(&marked[(uint32_t)u[s] >> 5], 1u << (u[s] & 31));
+                }
+        }
+        if (threadIdx.x == 0) {
+            indptr[n_h] = edges;
+            if (edges_out) edges_out[hop] = edges;
+        }
+        rg_lds_barrier();                                              // the marks and the list are complete
+        int fresh = 0;
+        for (int w = w0; w < w1; ++w) fresh += __popc(marked[w] & ~visited[w]);
+        int total;
+        int out = n_h + rg_lds_excl_scan(fresh, smem, &total);
+        for (int w = w0; w < w1; ++w) {
+            uint32_t b = marked[w] & ~visited[w];
+            if (b == 0u) continue;
+            visited[w] |= b;
+            for (; b; b &= b - 1u) {
+                const int id = (w << 5) + __ffs(b) - 1;
+                if (hop < keep_hops) front[out] = (uint16_t)id; else nodes[out] = id;
+                pos[id] = (uint16_t)out++;
+            }
+        }
+        rg_lds_barrier();                                              // the new tier is there
+        if (hop < keep_hops)
+            for (int i = n_h + (int)threadIdx.x; i < n_h + total; i += 1024) nodes[i] = front[i];
+        n_h += total;
+        if (threadIdx.x == 0) tier_off[hop + 2] = n_h;
+        for (int e = threadIdx.x; e < edges; e += 1024) {
+            const int id = list[e];
+            nbr[e] = id;
+            if (nbr_local) nbr_local[e] = pos[id];
+        }
+    }
+    rg_lds_barrier();
     for (int w = threadIdx.x; w < words; w += 1024) visited_out[g * words64 + w] = visited[w];
 }
 
@@ -1847,6 +2001,10 @@ rg_status rg_sampler_init(rg_ctx* ctx) {
     const void* small[] = {RG_SMALL(int32_t, kTableFew), RG_SMALL(int32_t, kTableMost), RG_SMALL(int64_t, kTableFew), RG_SMALL(int64_t, kTableMost)};
 #undef RG_SMALL
     for (const void* f : small) RG_HIP(ctx, hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)(kSmallNodes / 4)));
+#define RG_SMALL(RP, N) (const void*)k_sample_small_lists<RP, 8, N>, (const void*)k_sample_small_lists<RP, 16, N>, (const void*)k_sample_small_lists<RP, 32, N>
+    const void* lists[] = {RG_SMALL(int32_t, kTableFew), RG_SMALL(int32_t, kTableMost), RG_SMALL(int64_t, kTableFew), RG_SMALL(int64_t, kTableMost)};
+#undef RG_SMALL
+    for (const void* f : lists) RG_HIP(ctx, hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kSmallLds));
     return RG_OK;
 }
 
@@ -1993,7 +2151,12 @@ rg_status rg_sample_blocks_group(rg_ctx* ctx, const rg_csr* csr, int32_t group, 
     if (st != RG_OK) return st;
     int max_fanout = 0;
     for (int h = 0; h < num_hops; ++h) max_fanout = fanouts[h] < 0 ? RG_MAX_FANOUT : (fanouts[h] > max_fanout ? fanouts[h] : max_fanout);
-    const bool small = !first_seen && rg_is_small(N, edges_bound, frontiers_bound) && max_fanout <= 32 && csr->num_edges < (1ll << 32);
+    int64_t hop_edges = 0;
+    for (int h = 0; h < num_hops; ++h) hop_edges = rg_max64(hop_edges, eub_max[h]);
+    const bool in_lds = rg_small_lists_fit(N, fub_max[num_hops - 1], hop_edges);
+    const bool small = !first_seen && max_fanout <= 32 && csr->num_edges < (1ll << 32) &&
+                       (rg_is_small(N, edges_bound, frontiers_bound) ||
+                        (in_lds && max_fanout <= 16 && rg_max64(edges_bound, frontiers_bound) <= kSmallEdgesPerHop * num_hops));
     // Slices whose scratch is not there and cannot be allocated (a captured call, no memory): the atomic kernels, same results.
     if (!small && (mode == kTierSliced || mode == kTierRankedSeen)) {
         const SlicedBytes need = sliced_bytes(group * words, group * S.frontier_stride, first_seen);
@@ -2053,9 +2216,15 @@ rg_status rg_sample_blocks_group(rg_ctx* ctx, const rg_csr* csr, int32_t group, 
         const bool is_few = S.table_entries <= kTableFew;
         if (is_few) memcpy(few.v, table.v, (size_t)S.table_entries * 8);
         const int tok = rg_prof_begin(ctx, RG_K_SAMPLE, s);
+        const int keep_hops = rg_small_lists_fit(N, fub_max[num_hops], hop_edges) ? num_hops : num_hops - 1;
+        const int64_t lists = rg_small_lists_bytes(N, fub_max[keep_hops], hop_edges);
 #define RG_LAUNCH_SMALL_N(RP, KM, N, TABLE)                                                                           \
-    k_sample_small<RP, KM, N><<<ug, 1024, (size_t)words * 8, s>>>((const RP*)csr->row_ptr, csr->col_idx, TABLE, group, fan, S.visited, words, \
-                                                                  S.pos, N_nodes, num_hops, k0, k1, epoch)
+    do {                                                                                                              \
+        if (in_lds) k_sample_small_lists<RP, KM, N><<<ug, 1024, (size_t)lists, s>>>((const RP*)csr->row_ptr, csr->col_idx, TABLE, group, fan, \
+                                                S.visited, words, N_nodes, (int)fub_max[keep_hops], keep_hops, num_hops, k0, k1, epoch); \
+        else k_sample_small<RP, KM, N><<<ug, 1024, (size_t)words * 8, s>>>((const RP*)csr->row_ptr, csr->col_idx, TABLE, group, fan, S.visited, \
+                                                                           words, S.pos, N_nodes, num_hops, k0, k1, epoch); \
+    } while (0)
 #define RG_LAUNCH_SMALL(RP, KM) do { if (is_few) RG_LAUNCH_SMALL_N(RP, KM, kTableFew, few); else RG_LAUNCH_SMALL_N(RP, KM, kTableMost, table); } while (0)
         const int64_t N_nodes = N;
         if (rp64) { if (max_fanout <= 8) RG_LAUNCH_SMALL(int64_t, 8); else if (max_fanout <= 16) RG_LAUNCH_SMALL(int64_t, 16); else RG_LAUNCH_SMALL(int64_t, 32); }

@@ -389,6 +389,34 @@ def test_captured_call_after_another_kind(B, warm_seeds, warm_fanouts, warm_seen
     ctx.close()
 
 
+# One launch with its lists in LDS: whole words and parts of one to a thread, ids of 16 bits at most, rounds of 1024 nodes, the
+# largest lists that fit, hops without edges, more edges than one launch takes.
+@pytest.mark.parametrize("n,degree,seeds,fanouts", [
+    (31, 4, [31, 1, 0], (3, 2)), (4096, 9, [100, 4096], (1, 1)), (4097, 9, [300], (10, 5)), (8193, 30, [50] * 9, (5, 5, 5, 5)),
+    (16_384, 12, [1025, 1024], (7, 2)), (16_385, 40, [20, 0, 37], (16, 16, 2)), (65_536, 8, [90] * 3, (10, 5)), (65_537, 8, [90], (10, 5)),
+    (40_000, 20, [400], (16, 0, 3)), (20_000, 70, [9], (32, 32)), (10_000, 20, [490] * 2, (10, 5)), (10_000, 20, [491], (10, 5)),
+    (24_000, 30, [2000], (5, 3))])
+def test_batches_of_one_launch(B, ctx, n, degree, seeds, fanouts):
+    log(f"[one launch] N={n} seeds={seeds} fanouts={fanouts}")
+    rng = np.random.default_rng(n + len(fanouts))
+    rp, ci, ids = _sparse_graph(n, n, degree, rng)
+    csr = B.CsrGraph(torch.as_tensor(rp, device=DEV).to(torch.int64 if n % 2 else torch.int32), _i32(ci))
+    lists = [rng.permutation(ids)[:k].astype(np.int32) for k in seeds]
+    outs = [B.BlockBuffers(n, ci.size, max(k, 1), fanouts, DEV, with_local=n != 4097) for k in seeds]
+    for epoch in range(2):
+        ctx.sample_blocks_group(csr, [_i32(x) for x in lists], fanouts, 5, epoch, outs)
+        counts, want = torch.zeros(n, dtype=torch.int32, device=DEV), np.zeros(n, dtype=np.uint32)
+        ctx.access_histogram_sampled(len(seeds), counts)
+        for j, o in enumerate(outs):
+            orc = oracle.sample_blocks(rp, ci, lists[j], fanouts, 5, epoch)
+            hip = HipBatch(o, len(fanouts))
+            if n == 4097:
+                hip.nbr_local = orc.nbr_local
+            assert_batch_equal(hip, orc, len(fanouts), f"batch {j} epoch {epoch}")
+            oracle.access_histogram(orc.input_nodes, want)
+        assert np.array_equal(counts.cpu().numpy().view(np.uint32), want)
+
+
 # A wavefront counts 64 words of ids, a word of all batches in a lane; the batches come in any order, some under one index.
 @pytest.mark.parametrize("n,group", [(31, 2), (2048, 16), (2049, 5), (70_001, 1), (70_001, 9)])
 def test_bitmap_counts_of_batches_in_any_order(B, ctx, n, group):
