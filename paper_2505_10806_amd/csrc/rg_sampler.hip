@@ -74,7 +74,8 @@ constexpr int kSliceGroups = 256;    // workgroups the marking pass is split int
                                      // compute unit, which is what a full slice's LDS admits
 constexpr int kSplitEdges = 8192;    // edges per split at least, and two per bitmap word (a split writes its slice out once)
 constexpr int kTierWords = 768;      // bitmap words per workgroup in the tier kernels of kTierSliced
-constexpr int kTierWordsSmall = 192; // the same where few workgroups come of that
+constexpr int kTierWordsSmall = 192; // the same where few workgroups come of that, which then are larger than their words: the rows
+constexpr int kEmitThreadsSmall = 384;       // of up to 6144 new ids wait to be read (192 threads 119 us a call, 384 116; 768 are up to 12 % slower in groups)
 constexpr int kRankIds = 48;         // ids to a rank block, two to three bitmap words (see rg_rank_blocks)
 constexpr int kBaseIds = kRankIds * 1024;      // ids to a base: the members among them are counted in 16 bits
 static_assert(kBaseIds % (32 * kTierWords) == 0 && kBaseIds % (32 * kTierWordsSmall) == 0 && kTierWords % 3 == 0 && kTierWordsSmall % 3 == 0,
@@ -995,17 +996,18 @@ __global__ void __launch_bounds__(T) k_slice_count(const SampleScratch S) {
 // RANKED_SEEN: the positions are ascending ones only, the nodes come later.
 // next_fanout >= 0: also what k_hop_count does for the next hop, the new nodes' rows here, where their ids are at hand and ascending, and
 // their edges per chunk; those of the nodes in front of them by the workgroups behind the tier_blocks.
-template <bool RANKED_SEEN, int T, int W>
+template <bool RANKED_SEEN, int T, int W, int WORDS = T * W>
 __device__ __forceinline__ void rg_slice_emit(const RowPtr& row_ptr, const SampleScratch& S, int hop,
                                               unsigned tier_blocks, int next_fanout, int run) {
-    constexpr int NW = T / RG_WAVE, kEmitIds = W == 1 ? T * 32 : T * W * 32 / 3;
-    constexpr unsigned per_base = kBaseIds / (32 * T * W);               // workgroups to a base
+    constexpr int NW = T / RG_WAVE, kEmitIds = W == 1 ? WORDS * 32 : WORDS * 32 / 3;
+    constexpr int TW = WORDS / W;                        // threads that take words
+    constexpr unsigned per_base = kBaseIds / (32 * WORDS);               // workgroups to a base
     __shared__ int smem[NW + 1];
     __shared__ int part[NW], part_above[NW];
     __shared__ int32_t ids[RANKED_SEEN ? 1 : kEmitIds];
-    __shared__ uint32_t word_bits[W == 1 ? T : 1];
-    __shared__ int word_rank[W == 1 ? T : 1];
-    __shared__ int edges[T * W * 32 / kChunk + 2];
+    __shared__ uint32_t word_bits[W == 1 ? TW : 1];
+    __shared__ int word_rank[W == 1 ? TW : 1];
+    __shared__ int edges[WORDS * 32 / kChunk + 2];
     int g;
     unsigned blk;
     rg_shared_rows(S, run, g, blk);
@@ -1024,11 +1026,11 @@ __device__ __forceinline__ void rg_slice_emit(const RowPtr& row_ptr, const Sampl
         return;
     }
     if (!RANKED_SEEN) for (int i = threadIdx.x; i < (int)(sizeof(edges) / sizeof(int)); i += T) edges[i] = 0;
-    const int64_t w = ((int64_t)blk * T + threadIdx.x) * W;
+    const int64_t w = TW == T || (int)threadIdx.x < TW ? ((int64_t)blk * TW + threadIdx.x) * W : S.words;
     const int32_t* __restrict__ chunk_sum = S.chunk_sum + g * S.chunk_stride;
     uint32_t* __restrict__ visited = S.visited + g * S.words;
     uint32_t bits[W], members[W];
-    const bool whole = ((int64_t)blk + 1) * T * W <= S.words;
+    const bool whole = TW == T && ((int64_t)blk + 1) * WORDS <= S.words;
     rg_load_words<W>(S.slice_marks + (int64_t)g * S.splits * S.words, w, S.words, whole, bits);
     rg_load_words<W>(visited, w, S.words, whole, members);
     int before = 0, above = 0;                           // new ids in front of this workgroup's words, those behind the last base
@@ -1065,8 +1067,10 @@ __device__ __forceinline__ void rg_slice_emit(const RowPtr& row_ptr, const Sampl
     if (W == 3) {
         if (w < S.words) store_rank(w / 3, bits[0], bits[W / 3], bits[W - 1], (uint32_t)(out + j - base));
     } else {
-        word_bits[threadIdx.x] = bits[0];
-        word_rank[threadIdx.x] = out + j - base;
+        if (TW == T || (int)threadIdx.x < TW) {
+            word_bits[threadIdx.x] = bits[0];
+            word_rank[threadIdx.x] = out + j - base;
+        }
     }
 #pragma unroll
     for (int q = 0; q < W; ++q) {
@@ -1076,9 +1080,9 @@ __device__ __forceinline__ void rg_slice_emit(const RowPtr& row_ptr, const Sampl
     }
     if (RANKED_SEEN && W == 3) return;
     __syncthreads();                                     // ids, nodes, words and edges are there
-    if (W == 1 && threadIdx.x < T / 3) {
+    if (W == 1 && threadIdx.x < TW / 3) {
         const int q = 3 * threadIdx.x;
-        const int64_t r = (int64_t)blk * (T / 3) + threadIdx.x;
+        const int64_t r = (int64_t)blk * (TW / 3) + threadIdx.x;
         if (3 * r < S.words) store_rank(r, word_bits[q], word_bits[q + 1], word_bits[q + 2], (uint32_t)word_rank[q]);
     }
     if (RANKED_SEEN) return;
@@ -1126,9 +1130,9 @@ __global__ void __launch_bounds__(kTierWords / 3) k_slice_emit(const RowPtr row_
 }
 
 template <bool RANKED_SEEN>
-__global__ void __launch_bounds__(kTierWordsSmall) k_slice_emit_small(const RowPtr row_ptr, const SampleScratch S, int hop,
+__global__ void __launch_bounds__(kEmitThreadsSmall) k_slice_emit_small(const RowPtr row_ptr, const SampleScratch S, int hop,
                                                                       unsigned tier_blocks, int next_fanout, int run) {
-    rg_slice_emit<RANKED_SEEN, kTierWordsSmall, 1>(row_ptr, S, hop, tier_blocks, next_fanout, run);
+    rg_slice_emit<RANKED_SEEN, kEmitThreadsSmall, 1, kTierWordsSmall>(row_ptr, S, hop, tier_blocks, next_fanout, run);
 }
 
 // ---------------------------------------------------------------------------- per hop: new tier, from `marked`
@@ -2368,15 +2372,15 @@ rg_status rg_sample_blocks_group(rg_ctx* ctx, const rg_csr* csr, int32_t group, 
             unsigned emit_grid = tier_blocks * ug;
             const int emit_run = count_next ? shared_run((int64_t)tier_blocks + rg_div_up(fub_max[h], kChunk), 1, emit_grid) : 0;
             if (count_next) counted = h + 1;
-#define RG_LAUNCH_TIER(EMIT, T, W)                                                                                    \
+#define RG_LAUNCH_TIER(EMIT, TE, T, W)                                                                                    \
     do {                                                                                                              \
         k_slice_count<T, W><<<tier_blocks * ug, T, 0, s>>>(S);                                                        \
         RG_LAUNCH_CHECK(ctx, "k_slice_count");                                                                        \
-        if (mode == kTierSliced) EMIT<false><<<emit_grid, T, 0, s>>>(row_ptr, S, h, tier_blocks, next_fanout, emit_run);             \
-        else EMIT<true><<<tier_blocks * ug, T, 0, s>>>(row_ptr, S, h, tier_blocks, -1, 0);                                   \
+        if (mode == kTierSliced) EMIT<false><<<emit_grid, TE, 0, s>>>(row_ptr, S, h, tier_blocks, next_fanout, emit_run);             \
+        else EMIT<true><<<tier_blocks * ug, TE, 0, s>>>(row_ptr, S, h, tier_blocks, -1, 0);                                   \
         RG_LAUNCH_CHECK(ctx, "k_slice_emit");                                                                         \
     } while (0)
-            if (small_tier) RG_LAUNCH_TIER(k_slice_emit_small, kTierWordsSmall, 1); else RG_LAUNCH_TIER(k_slice_emit, kTierWords / 3, 3);
+            if (small_tier) RG_LAUNCH_TIER(k_slice_emit_small, kEmitThreadsSmall, kTierWordsSmall, 1); else RG_LAUNCH_TIER(k_slice_emit, kTierWords / 3, kTierWords / 3, 3);
 #undef RG_LAUNCH_TIER
             if (mode == kTierRankedSeen) {
                 // the edges that open a node, counted per block of the edge list, emitted in edge order
