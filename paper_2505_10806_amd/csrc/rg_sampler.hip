@@ -305,8 +305,9 @@ __global__ void __launch_bounds__(512) k_sched_sort(const int32_t* __restrict__ 
 // every launch once.
 constexpr int kMaxGroup = RG_MAX_GROUP;
 constexpr unsigned kXcds = 8;
+// Frontier nodes in a row to an XCD, where a batch has 64 such blocks or more (with fewer the XCDs would be unequal): batches' tiers are not cut
+// alike, so short runs miss each other (hop 2 of 8 batches, 256 nodes 700 us a call, 1024 to 8192 679, 16,384 689, not shared 717).
 constexpr int kSharedNodes = 4096;
-constexpr int64_t kLaneDraws = 1 << 18;
 
 // The batches' buffers: a table of 8-byte entries, [field][batch].  It goes to the first kernel as an argument, which leaves a copy in the
 // scratch for the others: arguments are read over the host link, and every kilobyte of them costs a launch 1.4 us of
@@ -807,7 +808,11 @@ __global__ void __launch_bounds__(256) k_hop_sample_thread(const int32_t* __rest
     }
 }
 
-// The same for few frontier nodes: KMAX lanes per node, one draw each, no staging.  Floyd's set by itself: draw s is taken already if an
+// Draws (lanes) of a hop for which k_hop_sample_lanes is faster: 1024 nodes of 25 neighbours 9.8 -> 6.5 us, three batches' 78 k nodes of 10
+// (1.25 M lanes) make the call 66 us against 63.  With fan-outs up to 16 a thread per node takes less (10: 5.4 against 7.4 us, 5: 4.7 / 6.6).
+constexpr int64_t kLaneDraws = 1 << 18;
+
+// The same for few frontier nodes of large fan-outs: KMAX lanes per node, one draw each, no staging.  Floyd's set by itself: draw s is taken already if an
 // earlier draw has its value, or if its value is the last position j_l of an earlier step l that found its own draw taken.
 template <int KMAX, int MODE>
 __global__ void __launch_bounds__(256) k_hop_sample_lanes(const int32_t* __restrict__ col_idx, const SampleScratch S, int fanout, uint32_t hop, uint32_t k0,
@@ -2317,7 +2322,7 @@ rg_status rg_sample_blocks_group(rg_ctx* ctx, const rg_csr* csr, int32_t group, 
             unsigned draw_grid;
             const int draw_run = shared_run(grid_for(fub_max[h], nodes_per, 1ll << 30), kSharedNodes / nodes_per, draw_grid);
             const size_t lds = (size_t)nodes_per * F * sizeof(uint32_t);
-            const bool lanes = fub_max[h] * group * (F <= 8 ? 8 : F <= 16 ? 16 : 32) <= kLaneDraws;
+            const bool lanes = F > 16 && fub_max[h] * group * 32 <= kLaneDraws;
             // Adding up grows with the square of the frontier, a scan costs 3 us for a small one: of 1 M nodes 172 / 175 us, of 8 M
             // 1206 / 1196, of 16 M 2555 / 2498, of 40 M 7213 / 6750.
             const int scanned = rg_div_up(fub_max[h], kChunk) > kDrawSelfScan;
@@ -2331,14 +2336,11 @@ rg_status rg_sample_blocks_group(rg_ctx* ctx, const rg_csr* csr, int32_t group, 
     k_hop_sample_lanes<KM, MODE><<<(unsigned)grid_for(fub_max[h], 256 / KM, 1ll << 30) * ug, 256, 0, s>>>(csr->col_idx, S, F, (uint32_t)h, k0, k1, epoch)
 #define RG_LAUNCH_DRAW_K(NP, MODE)                                                                                    \
     do { if (F <= 8) RG_LAUNCH_DRAW(8, NP, MODE); else if (F <= 16) RG_LAUNCH_DRAW(16, NP, MODE); else RG_LAUNCH_DRAW(32, NP, MODE); } while (0)
-#define RG_LAUNCH_LANES_K(MODE)                                                                                       \
-    do { if (F <= 8) RG_LAUNCH_LANES(8, MODE); else if (F <= 16) RG_LAUNCH_LANES(16, MODE); else RG_LAUNCH_LANES(32, MODE); } while (0)
-#define RG_LAUNCH_DRAW_N(MODE) do { if (lanes) RG_LAUNCH_LANES_K(MODE); else if (few) RG_LAUNCH_DRAW_K(64, MODE); else RG_LAUNCH_DRAW_K(256, MODE); } while (0)
+#define RG_LAUNCH_DRAW_N(MODE) do { if (lanes) RG_LAUNCH_LANES(32, MODE); else if (few) RG_LAUNCH_DRAW_K(64, MODE); else RG_LAUNCH_DRAW_K(256, MODE); } while (0)
             if (mode == kTierSliced || mode == kTierRankedSeen) RG_LAUNCH_DRAW_N(kTierSliced);
             else if (mode == kTierAtomic) RG_LAUNCH_DRAW_N(kTierAtomic);
             else RG_LAUNCH_DRAW_N(kTierFirstSeen);
 #undef RG_LAUNCH_DRAW_N
-#undef RG_LAUNCH_LANES_K
 #undef RG_LAUNCH_LANES
 #undef RG_LAUNCH_DRAW_K
 #undef RG_LAUNCH_DRAW

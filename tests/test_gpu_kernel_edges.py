@@ -438,6 +438,28 @@ def test_bitmap_counts_of_batches_in_any_order(B, ctx, n, group):
     assert np.array_equal(counts.cpu().numpy(), want) and np.array_equal(first.cpu().numpy(), want_first)
 
 
+# Runs long enough to be read ahead of the count, and with room for fewer entries not: empty ones, ones of a whole step and one more,
+# more of them than a tile has.
+@pytest.mark.parametrize("batches,hops,room", [(3, 2, 3200), (1, 1, 1700), (400, 3, 4700), (350, 3, 4500), (5, 7, 10_800)])
+def test_epoch_histogram_reading_ahead(B, ctx, batches, hops, room):
+    log(f"[histogram ahead] batches={batches} hops={hops} room={room}")
+    n, rng = 2000, np.random.default_rng(batches + hops)
+    arena, tiers = np.zeros((batches, room), dtype=np.int32), np.zeros((batches, hops + 2), dtype=np.int32)
+    want, first = np.zeros(n, dtype=np.int64), np.full(n, -1, dtype=np.int64)
+    for b in range(batches):
+        for h in range(hops):
+            k = int(rng.choice([0, 1, 64, 255, 256, 257, 511, 700])) if room > hops * 700 else int(rng.integers(0, room // hops))
+            ids = np.sort(rng.integers(0, n, k)).astype(np.int32)        # repeats count each time
+            at = tiers[b, h + 1]
+            arena[b, at:at + k] = ids
+            tiers[b, h + 2] = at + k
+            np.add.at(want, ids, 1)
+            first[ids[first[ids] < 0]] = b
+    counts, got = torch.zeros(n, dtype=torch.int32, device=DEV), torch.full((n,), -1, dtype=torch.int32, device=DEV)
+    ctx.access_histogram_epoch(_i32(arena), _i32(tiers), batches, hops, 0, counts, first_batch=got)
+    assert np.array_equal(counts.cpu().numpy(), want) and np.array_equal(got.cpu().numpy(), first)
+
+
 def test_selection_after_other_selections(B):
     """Selections that the clamped counts settle and that they do not, hit curves and replays of recorded calls of either, on one
     context: each finds the histograms as it needs them."""
