@@ -42,10 +42,10 @@ struct rg_ctx {
     RgBuf visited;      // uint32[ceil(N/32)] bitmap of cumulative-frontier members
     RgBuf marked;       // uint32[ceil(N/32)] bitmap of every id met (see SampleScratch)
     RgBuf slice_marks;  // uint32[ceil(N/32)] bitmaps of the ids a hop has sampled (the same)
-    RgBuf rank[2];      // {uint32, uint32}[ceil(N/32)] per hop, of four hops each: members of the hop's new tier and their positions
+    RgBuf rank[2];      // rank blocks and bases of four hops each: members of the hops' new tiers and their positions
     size_t slices_denied = ~size_t(0);   // bytes of `visited` from which on slice_marks, rank and seen could not be had (rg_reserve tries again)
     RgBuf pos;          // int32[N] position of a node in the cumulative frontier (valid for members only)
-    RgBuf chunk_sum;    // int32[] per-chunk edge counts / bitmap block counts
+    RgBuf chunk_sum;    // the batches' table, then int32[]: new ids per tier workgroup, edges per frontier chunk of even and of odd hops
     RgBuf row_start;    // int64[max_frontier] adjacency row start of every frontier node (current hop)
     RgBuf row_deg;      // int32[max_frontier] its degree
     RgBuf first_key;    // int32[N] per batch, first-seen node order only (see SampleScratch)

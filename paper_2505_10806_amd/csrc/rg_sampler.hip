@@ -2,7 +2,7 @@
 //
 // Data layout in HBM: CSR (row_ptr int32/int64, col_idx int32) is read-only; the batch's cumulative
 // frontier `nodes` grows tier by tier; `visited` is the N-bit bitmap of its members.  A hop's new tier is found in one of
-// three ways (TierMode below); a member's position comes from the tier's rank words or from `pos[v]`.  All sizes that
+// three ways (TierMode below); a member's position comes from the tier's rank blocks or from `pos[v]`.  All sizes that
 // depend on the data (frontier and edge counts) stay on the device: launches are sized by static upper bounds and
 // kernels read the actual counts.
 #include <string.h>
@@ -11,7 +11,7 @@
 
 namespace {
 
-constexpr int kChunk = 1024;         // frontier nodes per workgroup in the count kernel: the unit of chunk_sum
+constexpr int kChunk = 1024;         // frontier nodes per workgroup in the count kernel: the unit of hop_sum
 constexpr int kWordsPerBlock = 1024; // bitmap words per workgroup in the tier kernels of kTierAtomic (256 threads x 4)
 
 // How the ids a hop has sampled become its new tier.
@@ -23,12 +23,12 @@ constexpr int kWordsPerBlock = 1024; // bitmap words per workgroup in the tier k
 //  kTierAtomic    (ascending order) one probe and at most one atomicOr per edge on the bitmap `marked`.
 //  kTierFirstSeen (first-seen order) the first edge of the hop that names a node is kept per node (atomicMax).
 //  kTierRankedSeen (first-seen order) the tier is found as in kTierSliced, which gives its nodes their ascending positions; the
-//                 first edges are kept by those (N / 4 bytes of rank words and 4 bytes per new node instead of 4 N scattered
+//                 first edges are kept by those (N / 6 bytes of rank blocks and 4 bytes per new node instead of 4 N scattered
 //                 bytes), edges that open a node are counted and emitted in edge order, and `place` maps one position to the
 //                 other.  See rg_use_ranked_seen for the line between the two.
 // The sliced way moves about N bytes per hop whatever the edges, and every slice reads every edge; the atomic way costs 27 ps
-// per edge.  Whole call, sliced against atomic: 8 batches of 4096 seeds (15,10,5) at N = 10 M 715 / 1700 us, at 40 M 733 / 1026,
-// at 100 M (80 slices) 1312 / 841; 8 batches of 64 seeds (10,5) at N = 10 M 102 / 92 us, at 40 M 239 / 160; on smaller graphs
+// per edge.  Whole call, sliced against atomic: 8 batches of 4096 seeds (15,10,5) at N = 10 M 586 / 1700 us, at 40 M 733 / 1026 (before
+// rows were shared and ranks packed, which made it 715 at 10 M), at 100 M (80 slices) 1312 / 841; 8 batches of 64 seeds (10,5) at N = 10 M 102 / 92 us, at 40 M 239 / 160; on smaller graphs
 // both are bound by their launches, of which the sliced way has fewer.
 // The edges of this line, and of the other lines between kernels, are those of nodes of average degree (rg_expected_edges), not the
 // static bound, which for RG_FANOUT_ALL is every edge of the graph: one batch of 16 seeds, all neighbours of one / two / three hops,
@@ -52,7 +52,7 @@ inline int64_t rg_expected_edges(int64_t num_nodes, int64_t num_edges, int64_t s
     return sum;
 }
 enum TierMode { kTierSliced = 0, kTierAtomic = 1, kTierFirstSeen = 2, kTierRankedSeen = 3 };
-// First-seen order through rank words: four more launches per hop and a pass over the hop's edges for every kSeenSlice new nodes,
+// First-seen order through rank blocks: four more launches per hop and a pass over the hop's edges for every kSeenSlice new nodes,
 // but cheaper edges where the first-edge keys of all batches (4 N bytes each) are far from fitting the L2s.  Whole call, ranked
 // against kTierFirstSeen, on graphs of 49-50 edges per node unless said otherwise:
 //   one batch    slower on all of 0.1 M to 10 M nodes: 1.12 (4.3 M edges, N = 10 M) to 1.67 times
@@ -406,7 +406,7 @@ __device__ __forceinline__ int32_t* rg_rank_bases(const SampleScratch& S, int g,
     const int d = S.hops - 1 - hop;
     return (int32_t*)(S.rank[d >> 2] + 2 * S.group * S.rank_blocks) + ((d & 3) * S.group + g) * S.rank_bases;
 }
-// Bytes of one buffer for `group` batches of `words` bitmap words each, `members` words in all at most.
+// Bytes of one buffer for batches of `members` bitmap words in all.
 inline int64_t rg_rank_bytes(int64_t members) {
     const int64_t blocks = 2 * (members / 3 + kMaxGroup), bases = members / (kBaseIds / 32) + kMaxGroup;
     return kRankHops * (blocks * (int64_t)sizeof(uint2) + bases * 4);
@@ -995,12 +995,13 @@ __global__ void __launch_bounds__(T) k_slice_count(const SampleScratch S) {
 
 // Emits the new tier behind the current frontier, ascending, with its rank blocks, and makes its ids frontier members.  The
 // ids go through LDS so that they are stored by consecutive lanes (thread by thread: 135 us at hop 2 of 8 batches, 7.5 M ids;
-// now 30); a workgroup with more new ids than fit there (over a third of its range) stores them directly.
+// now 25); a workgroup with more new ids than fit there (over a third of its range) stores them directly.
 // A thread takes W words: three, which are two rank blocks, or one where few workgroups leave the serial walk over the bits of a
 // word as what takes time; the words then meet in LDS.
 // RANKED_SEEN: the positions are ascending ones only, the nodes come later.
 // next_fanout >= 0: also what k_hop_count does for the next hop, the new nodes' rows here, where their ids are at hand and ascending, and
-// their edges per chunk; those of the nodes in front of them by the workgroups behind the tier_blocks.
+// their edges per chunk; those of the nodes in front of them by the workgroups behind the tier_blocks.  (Hop 1 of the same batches,
+// 3.3 M rows: 49 us with the next hop's sizes, 20 + 44 apart; on XCDs of their own, without sharing lines of row_ptr, 65.)
 template <bool RANKED_SEEN, int T, int W, int WORDS = T * W>
 __device__ __forceinline__ void rg_slice_emit(const RowPtr& row_ptr, const SampleScratch& S, int hop,
                                               unsigned tier_blocks, int next_fanout, int run) {
@@ -1265,7 +1266,7 @@ __global__ void __launch_bounds__(256) k_first_seen_emit(const SampleScratch S, 
         }
 }
 
-// ---------------------------------------------------------------------------- per hop: first-seen order by rank words
+// ---------------------------------------------------------------------------- per hop: first-seen order by rank blocks
 // The bases of a batch's tiers, [hop][rank_bases], into LDS.
 __device__ __forceinline__ void rg_load_bases(const SampleScratch& S, int g, int hops, int32_t* bases) {
     const int n = (int)S.rank_bases;
@@ -1475,10 +1476,10 @@ __global__ void __launch_bounds__(1024) k_seen_emit(const SampleScratch S, int h
 // A member's position never changes, so nbr_local of every hop can be written after the last one, if every hop's lists are still
 // there by then (rg_hops_share_buffers).
 // nbr_local[e] = position of nbr[e] in the extended frontier; the hop's edge count is indptr[n_h].
-// RANKED: the rank words of the tiers, latest first (a hop's edges mostly name its new tier), pos[] for the seeds.  The words
-// of one tier are N / 4 bytes (2.5 MB at N = 10 M) where pos[] is 4 N.  Three hops of 8 batches of 4096 seeds, 20.6 M edges: 202 us,
-// bound by the rank words: three tiers of them are more than one XCD's L2, 71 % of the reads hit it.  (The 15.9 M edges of hop 2
-// by themselves: pos[] 251 us, the new tier's words and those of one more 142, the new tier's alone, which would not do, 74.)
+// RANKED: the rank blocks of the tiers, latest first, pos[] for the seeds.  N / 3 bytes for two tiers (3.3 MB at N = 10 M) where pos[]
+// is 4 N.  Three hops of 8 batches of 4096 seeds, 20.6 M edges: 148 us, bound by random reads of L2, 25.6 M of them (a quarter of the edges
+// name the first tier, whose blocks are a second read; 3.6 M miss).  With 8 bytes per 32 ids and tier, 32 M reads of which 9.2 M
+// missed, 200; with 16 bytes per 96 ids and tier, 32 M and 3.4 M, 186.  Two edges in flight per thread: four take 85 registers and 6 us more.
 template <bool RANKED>
 __global__ void __launch_bounds__(256) k_relabel(const SampleScratch S, int first_hop, int last_hop) {
     extern __shared__ int32_t bases[];
