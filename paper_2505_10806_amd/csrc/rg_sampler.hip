@@ -2366,8 +2366,8 @@ rg_status rg_sample_blocks_group(rg_ctx* ctx, const rg_csr* csr, int32_t group, 
             const int64_t split_edges = rg_max64(kSplitEdges, 2 * (int64_t)S.slice_words);
             // (hubs among the frontier: up to eight times the edges of average nodes)
             S.splits = (int)rg_max64(1, rg_min64(rg_min64(eub_max[h], 8 * expected[h]) / split_edges, kSliceGroups / (S.slices * group)));
-            // Small workgroups while large ones would leave compute units without work: one batch on 233 k nodes 70 us a call with large, 57 with
-            // small ones; 393 of them (3 batches, 3 M nodes) 147 / 157, 656 (8 batches, 2 M) 120 / 139.
+            // Small workgroups while large ones would leave compute units without work: one batch on 233 k nodes 69 us a call with large, 56 with
+            // small ones, on 380 k 150 / 117; 369 large ones (3 batches, 3 M nodes) 147 / 158, 648 (8 batches, 2 M) 120 / 140.
             const bool small_tier = rg_div_up(words, kTierWords) * group < ctx->num_cus;
             const unsigned tier_blocks = (unsigned)rg_max64(1, rg_div_up(words, small_tier ? kTierWordsSmall : kTierWords));
             k_slice_mark<<<(unsigned)(S.slices * S.splits) * ug, 1024, (size_t)S.slice_words * 4, s>>>(S, h);
