@@ -110,8 +110,10 @@ def test_blocks_of_very_large_frontiers(B, ctx, seeds):
     assert_batch_equal(HipBatch(out, 1), oracle.sample_blocks(rp, ci, ids, (2,), 77, 2), 1)
 
 
-# One launch for all hops, slices, atomic marking; first-seen order by first edges and by rank words.
+# One launch for all hops (with its lists in LDS up to 65,536 nodes), slices, atomic marking; first-seen order by first edges and by rank words.
 @pytest.mark.parametrize("n,active,degree,seeds,fanouts,first_seen", [
+    (10_000, 10_000, 20, [250, 61, 0], (5, 4, 3), False),
+    (65_536, 50_000, 9, [1030, 1, 1024], (2, 2, 1), False),
     (131_072, 60_000, 30, [300, 40], (10, 5), False),
     (300_007, 250_000, 30, [1500, 0, 900], (25, 10, 3), False),
     (4_194_337, 200_000, 12, [60, 50], (5, 3), False),
@@ -152,6 +154,24 @@ def test_blocks_with_one_list_buffer_for_all_hops(B, ctx, n, active, degree, see
                 assert np.array_equal(o.nbr[h][:e].cpu().numpy(), orc.nbr[h]), f"batch {j} hop {h}"
             if what == "nbr" or last:
                 assert np.array_equal(o.indptr[h][:orc.indptr[h].size].cpu().numpy(), orc.indptr[h]), f"batch {j} hop {h}"
+
+
+@pytest.mark.parametrize("n", [10_000, 131_072, 300_007])
+def test_blocks_whose_positions_replace_the_ids(B, ctx, n):
+    """One list for a hop's ids and positions: the positions are what stays."""
+    rng, fanouts, seeds = np.random.default_rng(n), (5, 4, 3), [250, 61]
+    rp, ci, ids = _sparse_graph(n, n // 2, 20, rng)
+    csr = B.CsrGraph(torch.as_tensor(rp, device=DEV).to(torch.int32), _i32(ci))
+    lists = [rng.permutation(ids)[:k].astype(np.int32) for k in seeds]
+    outs = [B.BlockBuffers(n, ci.size, k, fanouts, DEV) for k in seeds]
+    for o in outs:
+        for h in range(len(fanouts)):
+            o.set_hop(h, nbr_local=o.nbr[h])
+    ctx.sample_blocks_group(csr, [_i32(x) for x in lists], fanouts, 77, 3, outs)
+    for j, o in enumerate(outs):
+        orc, hip = oracle.sample_blocks(rp, ci, lists[j], fanouts, 77, 3), HipBatch(o, len(fanouts))
+        hip.nbr = orc.nbr
+        assert_batch_equal(hip, orc, len(fanouts), f"batch {j}")
 
 
 def test_decoupled_misses_wait_for_the_reader_of_their_buffer(B):
