@@ -400,9 +400,11 @@ __global__ void __launch_bounds__(1024) k_topk_hist_low(const uint32_t* __restri
     __syncthreads();
     for (int i = threadIdx.x; i < kLowBins; i += 1024) {
         const uint32_t mine = h[i];
-        // (with the old value awaited the addition has been made when the workgroup says so below; a fence instead, which writes back
-        // the L2, took 65 us)
-        if (mine) { const uint32_t old = atomicAdd(&ctl->low[i], mine); asm volatile("" :: "v"(old)); }
+        // The last workgroup reads what the others have added without a fence, which writes back the L2 and took 65 us.  That holds
+        // because low[] is touched in this kernel by additions and loads of agent scope alone, which are made where every XCD sees
+        // them, and because an addition whose old value has arrived has been made: `done` is raised behind the wait for those values
+        // (and the barrier below).  A plain store, or one of a smaller scope, to something the last workgroup reads would need the fence.
+        if (mine) { const uint32_t old = atomicAdd(&ctl->low[i], mine); asm volatile("" :: "v"(old) : "memory"); }
     }
     if (threadIdx.x == 0 && ovf_s) atomicAdd(&ctl->ovf_sum, ovf_s);
     if (capacity < 0) return;                                             // the hit curve looks its capacities up itself
