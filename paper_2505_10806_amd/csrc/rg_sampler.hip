@@ -1684,9 +1684,10 @@ __device__ __forceinline__ int rg_lds_excl_scan(int x, int* smem, int* total) {
 // Graphs and batches whose lists fit LDS as 16-bit numbers: positions, a hop's edges and the frontier, of which keep_hops tiers are kept:
 // the last one, which is not drawn for, only where there is room.  Nothing is then read back
 // from memory, the lists are written by consecutive lanes, and the only waits are for the rows and columns; the rows of a
-// round's nodes are on their way while the round before is drawn for.  The barriers do not wait for what is stored: an entry of a list is
-// stored by the same thread in every hop, except the last offset (thread 0 in its hop, another one in the next), so where hops share
-// lists (`shared`) each begins with a barrier that does.  nbr and nbr_local of a hop may be one list: the second store is the later one.
+// round's nodes are on their way while the round before is drawn for.  The barriers order what is in LDS only, but for the one that a hop
+// begins with: hops may share their lists, and the offset behind the last node is stored by thread 0 in its hop and by another one in the
+// next (any other entry by the same thread in every hop).  It takes no wait for the stores: those of one workgroup reach the
+// cache of its compute unit in order.  nbr and nbr_local of a hop may be one list: the second store is the later one.
 // 256 seeds (10,5) on 10,000 nodes 25.6 -> 17.8 us, 8 x 300 on 30,000 37.6 -> 24.6.
 inline int64_t rg_small_lists_bytes(int64_t num_nodes, int64_t frontier, int64_t edges) {
     return 2 * rg_div_up(num_nodes, 32) * 4 + 2 * (num_nodes + frontier + edges) + 8;
@@ -1703,7 +1704,7 @@ inline bool rg_small_lists_fit(int64_t num_nodes, int64_t frontier, int64_t hop_
 
 template <typename RP, int KMAX, int N>
 __global__ void __launch_bounds__(1024) k_sample_small_lists(const RP* __restrict__ row_ptr, const int32_t* __restrict__ col_idx,
-                                                             const BatchTable<N> B, int group, int shared, const Fanouts fanouts,
+                                                             const BatchTable<N> B, int group, const Fanouts fanouts,
                                                              uint32_t* __restrict__ visited_out, int64_t words64, int64_t num_nodes,
                                                              int frontier_most, int keep_hops, int hops, uint32_t k0, uint32_t k1,
                                                              uint32_t epoch) {
@@ -1740,7 +1741,7 @@ __global__ void __launch_bounds__(1024) k_sample_small_lists(const RP* __restric
         int32_t* nbr = entry(kHopFields + kHopFieldCount * hop + kNbr);
         int32_t* nbr_local = entry(kHopFields + kHopFieldCount * hop + kNbrLocal);
         int edges = 0;
-        if (shared) __syncthreads(); else rg_lds_barrier();            // the frontier and the bits are complete
+        __syncthreads();                                               // the frontier and the bits are complete, and the last hop's stores made
         int32_t v_next = 0;
         RP a_next = 0, b_next = 0;
         const auto rows_of = [&](int i) {
@@ -1918,11 +1919,12 @@ __global__ void __launch_bounds__(256) k_histogram_bitmaps(const uint32_t* __res
 }
 
 // True if a later hop writes into a list of an earlier one (a caller that keeps nothing but nbr_local may pass one nbr or indptr
-// buffer for all hops): every hop has to be relabelled before the next one is drawn, and its stores come first.
+// buffer for all hops): every hop has to be relabelled before the next one is drawn.
 bool rg_hops_share_buffers(const rg_blocks& o, int num_hops, const int64_t* fub, const int64_t* eub) {
+    if (!o.nbr_local) return false;
     struct Range { uintptr_t lo, hi; } r[RG_MAX_HOPS][3];
     for (int h = 0; h < num_hops; ++h) {
-        const int32_t* p[3] = {o.indptr[h], o.nbr[h], o.nbr_local ? o.nbr_local[h] : nullptr};
+        const int32_t* p[3] = {o.indptr[h], o.nbr[h], o.nbr_local[h]};
         const int64_t n[3] = {fub[h] + 1, eub[h], eub[h]};
         for (int j = 0; j < 3; ++j) r[h][j] = {(uintptr_t)p[j], (uintptr_t)p[j] + (uintptr_t)(p[j] ? 4 * n[j] : 0)};
         for (int e = 0; e < h; ++e)
@@ -2105,7 +2107,7 @@ rg_status rg_sample_blocks_group(rg_ctx* ctx, const rg_csr* csr, int32_t group, 
     // static bounds: per batch for the capacity checks, their maximum for the launch shapes
     int64_t fub_max[RG_MAX_HOPS + 1] = {0}, eub_max[RG_MAX_HOPS] = {0};
     int32_t seeds_max = 0;
-    bool capacity_error = false, shared = false, shared_unlabelled = false;
+    bool capacity_error = false, shared = false;
     for (int g = 0; g < group; ++g) {
         rg_blocks* o = out + g;
         RG_REQUIRE(ctx, num_seeds[g] >= 0, "rg_sample_blocks: num_seeds is negative (batch %d)", g);
@@ -2132,7 +2134,7 @@ rg_status rg_sample_blocks_group(rg_ctx* ctx, const rg_csr* csr, int32_t group, 
             for (int h = 0; h < num_hops; ++h) { o->indptr_cap[h] = fub[h] + 1; o->nbr_cap[h] = eub[h]; }
             capacity_error = true;
         }
-        if (rg_hops_share_buffers(*o, num_hops, fub, eub)) (o->nbr_local ? shared : shared_unlabelled) = true;
+        shared = shared || rg_hops_share_buffers(*o, num_hops, fub, eub);
         for (int h = 0; h <= num_hops; ++h) fub_max[h] = rg_max64(fub_max[h], fub[h]);
         seeds_max = num_seeds[g] > seeds_max ? num_seeds[g] : seeds_max;
     }
@@ -2231,8 +2233,8 @@ rg_status rg_sample_blocks_group(rg_ctx* ctx, const rg_csr* csr, int32_t group, 
         const int64_t lists = rg_small_lists_bytes(N, fub_max[keep_hops], hop_edges);
 #define RG_LAUNCH_SMALL_N(RP, KM, N, TABLE)                                                                           \
     do {                                                                                                              \
-        if (in_lds) k_sample_small_lists<RP, KM, N><<<ug, 1024, (size_t)lists, s>>>((const RP*)csr->row_ptr, csr->col_idx, TABLE, group, \
-                                                shared || shared_unlabelled, fan, S.visited, words, N_nodes, (int)fub_max[keep_hops], keep_hops, num_hops, k0, k1, epoch); \
+        if (in_lds) k_sample_small_lists<RP, KM, N><<<ug, 1024, (size_t)lists, s>>>((const RP*)csr->row_ptr, csr->col_idx, TABLE, group, fan, \
+                                                S.visited, words, N_nodes, (int)fub_max[keep_hops], keep_hops, num_hops, k0, k1, epoch); \
         else k_sample_small<RP, KM, N><<<ug, 1024, (size_t)words * 8, s>>>((const RP*)csr->row_ptr, csr->col_idx, TABLE, group, fan, S.visited, \
                                                                            words, S.pos, N_nodes, num_hops, k0, k1, epoch); \
     } while (0)

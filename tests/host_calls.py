@@ -44,16 +44,15 @@ def log(prefix=""):
 def kernels():
     return [x.split()[1] for x in log("launch")]
 
-def sample(c, n, nnz, seeds, fanouts, order=ASCENDING, stream=0, local=True, one=()):
-    """rg_sample_blocks_group of len(seeds) batches on a graph of n nodes and nnz edges.  one: the lists (0 indptr, 1 nbr, 2 nbr_local)
-    that all hops of the last batch share."""
+def sample(c, n, nnz, seeds, fanouts, order=ASCENDING, stream=0, local=True):
+    """rg_sample_blocks_group of len(seeds) batches on a graph of n nodes and nnz edges."""
     H, g = len(fanouts), len(seeds)
     csr, outs, keep = Csr(n, nnz, address(), 64, address()), (Blocks * g)(), []
     fo = (i32 * H)(*fanouts)
     for j, k in enumerate(seeds):
         fub, eub = (i64 * (H + 1))(), (i64 * H)()
         assert lib.rg_blocks_bounds(i64(n), i64(nnz), i64(k), fo, H, fub, eub) == OK
-        arrays = [(p * H)(*([address()] * H if a in one and j == g - 1 else [address() for _ in range(H)])) for a in range(3)]
+        arrays = [(p * H)(*[address() for _ in range(H)]) for _ in range(3)]
         caps = (i64 * H)(*[fub[h] + 1 for h in range(H)]), (i64 * H)(*eub)
         keep += arrays + list(caps)
         outs[j] = Blocks(address(), fub[H], address(), arrays[0], caps[0], arrays[1], arrays[2] if local else None, caps[1], address())

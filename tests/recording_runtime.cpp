@@ -23,8 +23,6 @@ static std::set<void*> capturing, joined_back;            // streams that record
 static void* origin;
 static std::map<void*, std::pair<void*, bool>> events;    // event -> stream it was recorded on, in a graph or not
 static struct { Dim3 grid, block; size_t shmem; void* stream; } pushed;
-static std::string watched;                               // kernels whose argument `watched_at`, an int, is written down
-static int watched_at;
 
 template <typename... A> static void note(const char* fmt, A... a) {
     char buf[512];
@@ -38,7 +36,6 @@ extern "C" {
 // ---- for the test
 const char* recorded() { return log_text.c_str(); }
 void forget() { log_text.clear(); }
-void watch_argument(const char* kernel, int index) { watched = kernel; watched_at = index; }
 void limit_memory(size_t bytes) { limit = bytes; }
 size_t memory_held() { return held; }
 void begin_capture(void* s) { capturing = {s}; joined_back = {s}; origin = s; }
@@ -106,8 +103,7 @@ int __hipPopCallConfiguration(Dim3* grid, Dim3* block, size_t* shmem, void** s) 
     *grid = pushed.grid; *block = pushed.block; *shmem = pushed.shmem; *s = pushed.stream;
     return kOk;
 }
-int hipLaunchKernel(const void* f, Dim3 grid, Dim3 block, void** args, size_t shmem, void* s) {
-    if (!watched.empty() && kernels[f].compare(0, watched.size(), watched) == 0) note("argument %d", *(const int*)args[watched_at]);
+int hipLaunchKernel(const void* f, Dim3 grid, Dim3 block, void**, size_t shmem, void* s) {
     note("launch %s %u %u %u %zu %p", kernels[f].c_str(), grid.x, grid.y, block.x, shmem, s);
     return kOk;
 }

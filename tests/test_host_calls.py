@@ -205,21 +205,6 @@ assert ("k_sample_init" in names) == {one} and ("k_mark_seeds" in names) == (not
 """)
 
 
-def test_one_launch_waits_between_hops_that_share_lists():
-    """Its barriers leave global stores in flight, but where a later hop writes into a list of an earlier one, with or without positions."""
-    host_calls.run("""
-c = context()
-rt.watch_argument(b"k_sample_small_lists", 4)
-for seeds in ([250], [0, 40, 250]):
-    for local in (False, True):
-        for one in ((), (0,), (1,), (0, 1, 2)):
-            assert sample(c, 10_000, 200_000, seeds, (5, 4, 3), local=local, one=one) == OK, lib.rg_last_error(c)
-            assert [k.split("<")[0] for k in kernels()] == ["k_sample_small_lists"]
-            assert sample(c, 10_000, 200_000, seeds, (5, 4, 3), local=local, one=one) == OK
-            assert [int(x.split()[1]) for x in log("argument")] == [bool(one)], (seeds, local, one)
-""")
-
-
 @pytest.mark.parametrize("n,edges,seeds,fanouts,order,tier", [
     (10_000_000, 200_000_000, [16], (-1, -1), "ASCENDING", "k_tier_emit"), (10_000_000, 200_000_000, [16], (1024, 64), "ASCENDING", "k_tier_emit"),
     (10_000_000, 200_000_000, [1024], (-1, -1, -1), "ASCENDING", "k_slice_emit<false>"),
