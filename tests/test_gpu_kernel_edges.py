@@ -220,6 +220,23 @@ def test_schedule_of_ids_picked_for_one_bucket(ctx):
     assert np.array_equal(got.cpu().numpy(), oracle.epoch_schedule(ids, seed, epoch))
 
 
+# A bucket has room for 2560 ids; an overfull one is sorted in tiles of 2048 that are merged.
+@pytest.mark.parametrize("in_bucket", [2560, 2561, 4096, 4097, 10_001, 16_500])
+def test_schedule_bucket_with_more_ids_than_room(ctx, in_bucket):
+    """17,000 ids in sixteen buckets, the third of which gets in_bucket of them."""
+    n, seed, epoch = 17_000, 2025, 4
+    ids = np.arange(400_000, dtype=np.int32)
+    order = oracle.epoch_schedule(ids, seed, epoch)     # ascending by key: 25,000 ids or so to each of the sixteen
+    key = lambda v: oracle.philox4x32_10(np.array([v, 0xFFFFFFFF, 0, epoch]), np.array([seed, 0]))[0] >> 28  # noqa: E731
+    lo, hi = np.searchsorted([key(v) for v in order[::16]], [3, 4]) * 16
+    third, rng = order[lo:hi - 16], np.random.default_rng(in_bucket)
+    rest = np.concatenate([order[:lo - 16], order[hi:]])
+    ids = rng.permutation(np.concatenate([rng.permutation(third)[:in_bucket], rng.permutation(rest)[:n - in_bucket]]))
+    assert (np.array([key(v) for v in ids]) == 3).sum() == in_bucket
+    got = ctx.epoch_schedule(_i32(ids), seed, epoch)
+    assert np.array_equal(got.cpu().numpy(), oracle.epoch_schedule(ids, seed, epoch))
+
+
 # Chunks of 1024 slots, wavefronts of 64; one key for all slots, a key per slot, keys in descending order.
 @pytest.mark.parametrize("slots", [1, 63, 65, 1024, 1025, 70_001])
 @pytest.mark.parametrize("pattern", ["one", "cycle", "descending", "random"])
