@@ -95,6 +95,27 @@ def test_blocks_across_the_ways_to_build_a_tier(B, ctx, n, active, degree, seeds
             assert torch.equal(o.tier_off, w.tier_off) and torch.equal(o.nodes[:k], w.nodes[:k])
 
 
+# All neighbours of nodes that have far more of them than the average.
+@pytest.mark.parametrize("first_seen", [False, True])
+def test_blocks_of_hubs(B, ctx, first_seen):
+    """16 batches with over twice the edges that the kernels which walk their lists are launched for."""
+    log(f"[hubs] first_seen={first_seen}")
+    n, hubs, rng = 400_000, 16, np.random.default_rng(9)
+    ids = rng.permutation(n)[:hubs].astype(np.int32)
+    deg = rng.integers(0, 3, n)
+    deg[ids] = rng.integers(140_000, 160_000, hubs)
+    rp = np.concatenate([[0], np.cumsum(deg)])
+    ci = rng.integers(0, n, rp[-1]).astype(np.int32)
+    csr = B.CsrGraph(torch.as_tensor(rp, device=DEV).to(torch.int32), _i32(ci))
+    for fanouts in ((-1,), (-1, 1)):
+        outs = [B.BlockBuffers(n, ci.size, 1, fanouts, DEV) for _ in range(hubs)]
+        ctx.sample_blocks_group(csr, [_i32(ids[j:j + 1]) for j in range(hubs)], fanouts, 77, 1, outs,
+                                node_order=B.RG_ORDER_FIRST_SEEN if first_seen else B.RG_ORDER_ASCENDING)
+        for j, o in enumerate(outs):
+            orc = oracle.sample_blocks(rp, ci, ids[j:j + 1], fanouts, 77, 1, oracle.ORDER_FIRST_SEEN if first_seen else oracle.ORDER_ASCENDING)
+            assert_batch_equal(HipBatch(o, len(fanouts)), orc, len(fanouts), f"batch {j}")
+
+
 # Count chunks of 1024 frontier nodes, 16,384 of them added up by the draw itself, more scanned by a launch of their own.
 @pytest.mark.parametrize("seeds", [16_777_216, 16_777_217])
 def test_blocks_of_very_large_frontiers(B, ctx, seeds):

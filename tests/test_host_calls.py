@@ -232,6 +232,25 @@ for seeds, fanouts, most in (([1], (-1,), 1), ([16], (-1, -1), 1), ([1500] * 2, 
 """)
 
 
+@pytest.mark.parametrize("group", [1, 2, 16])
+def test_few_edges_are_not_walked_by_workgroups_for_the_whole_graph(group):
+    """All neighbours of a few seeds: the kernels that walk the hops' edges are launched for those of average nodes, eightfold, four
+    workgroups per compute unit (of the 256 the recording runtime's device counts as) at least."""
+    host_calls.run(f"""
+c = context()
+for order, names in ((ASCENDING, ["k_relabel"]), (FIRST_SEEN, ["k_first_seen_count", "k_first_seen_emit", "k_relabel"])):
+    for local in (True, False):
+        assert sample(c, 190_610, 35_400_000, [6] * {group}, (-1, 5), order, local=local) == OK, lib.rg_last_error(c)
+        launches = log("launch")
+        for name in names:
+            grids = [int(x.split()[2]) for x in launches if x.split()[1].startswith(name)]
+            assert max(grids, default=0) <= 1024 and (grids or not local and name == "k_relabel"), (name, grids)
+    assert sample(c, 190_610, 35_400_000, [1024] * {group}, (25, 10), order) == OK              # nodes have them all: as many as the bound
+    grids = [int(x.split()[2]) for x in log("launch") if x.split()[1].startswith("k_relabel") or x.split()[1].startswith("k_seen_relabel")]
+    assert grids == [min(1024 * 26 * 10 // 1024, 8192 // {group}) * {group}], grids
+""")
+
+
 # 2.2 M edges in all, nodes times batches squared, a hop's and all edges above.
 @pytest.mark.parametrize("n,edges,seeds,fanouts,ranked", [
     (10_000_000, 490_000_000, [4096], (15, 10, 5), False), (10_000_000, 490_000_000, [1100] * 2, (15, 10, 5), True),
