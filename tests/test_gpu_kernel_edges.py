@@ -51,15 +51,18 @@ def _sparse_graph(n, active, degree, rng):
     (524_289, 80_000, 30, [120, 64], (10, 5)),
     (1_279_999, 3000, 8, [40, 7], (5, 3)),              # one slice, last word partial
     (1_280_001, 3000, 8, [40, 7, 0], (5, 3)),           # a second slice of few words
-    (20_000, 20_000, 40, [700, 900], (32, 31)),         # over 8192 new ids within 512 words
+    (20_000, 20_000, 40, [700, 900], (32, 31)),         # most ids of a tier workgroup's words are new
     (200_001, 150_000, 30, [1000, 1, 999], (25, 10)),   # the edge list split between workgroups
     (200_001, 150_000, 30, [9000, 1], (7, 2)),          # more seeds than one launch marks
+    (200_001, 150_000, 30, [9000] + [40, 0, 1] * 5, (3, 2)),         # the same with the longest table of buffers
+    (300_007, 250_000, 30, [600] * 4, (10, 10, 40)),    # over 65,536 frontier nodes counted by a launch of their own
     (3_000_017, 400_000, 12, [900] * 8, (40, 3)),       # wavefront-per-node draw in front of the slices
     (300_007, 250_000, 30, [1500, 0, 1200, 1, 900, 1500, 1500, 1500], (25, 10)),    # over 2.2 M edges: first-seen order by rank words
     (300_007, 250_000, 30, [1500] * 4, (40, 10)),
     (2_600_021, 2_500_000, 20, [2000, 1900, 0], (15, 10, 5)),
     (2_600_021, 900_000, 12, [2000] * 4, (15, 10, 5)),
     (4_194_337, 200_000, 12, [60, 50], (5, 3)),         # atomic marking on a graph that has slices
+    (4_194_337, 200_000, 30, [60, 50], (25, 20)),       # the same by a lane per draw
     (4_194_337, 200_000, 12, [3000, 2000], (15, 10)),   # slices again: the edges outweigh the bitmaps
     (41_000_033, 200_000, 12, [300, 200], (5, 3)),      # no slices
 ])
@@ -93,6 +96,27 @@ def test_blocks_across_the_ways_to_build_a_tier(B, ctx, n, active, degree, seeds
         for o, w in zip(again, outs):
             k = int(o.tier_off[-1])
             assert torch.equal(o.tier_off, w.tier_off) and torch.equal(o.nodes[:k], w.nodes[:k])
+
+
+# A tier workgroup of 24,576 ids has room for a third of them; more are stored and read back for the next hop's rows.
+@pytest.mark.parametrize("fanouts,full_hop", [((15, 10, 5), 1), ((15, 20), 1), ((40, 10, 3), 0)])
+def test_tiers_of_more_new_ids_than_a_workgroup_has_room_for(B, ctx, fanouts, full_hop):
+    log(f"[dense tiers] fanouts={fanouts}")
+    n, rng, per = 1_000_003, np.random.default_rng(5), 24_576
+    active = np.concatenate([np.arange(4 * per - 100, 5 * per + 50), [0, 300_000, n - 1]])
+    deg = np.zeros(n, dtype=np.int64)
+    deg[active] = rng.integers(20, 60, active.size)
+    rp = np.concatenate([[0], np.cumsum(deg)])
+    ci = active[rng.integers(0, active.size, rp[-1])].astype(np.int32)
+    csr = B.CsrGraph(torch.as_tensor(rp, device=DEV).to(torch.int32), _i32(ci))
+    lists = [rng.permutation(active)[:k].astype(np.int32) for k in ([700] * 7 + [3])]
+    outs = [B.BlockBuffers(n, ci.size, k.size, fanouts, DEV) for k in lists]
+    ctx.sample_blocks_group(csr, [_i32(x) for x in lists], fanouts, 77, 1, outs)
+    for j, o in enumerate(outs):
+        orc = oracle.sample_blocks(rp, ci, lists[j], fanouts, 77, 1)
+        tier = orc.nodes[orc.tier_off[full_hop + 1]:orc.tier_off[full_hop + 2]]
+        assert j == 7 or np.bincount(tier // per).max() > per // 3
+        assert_batch_equal(HipBatch(o, len(fanouts)), orc, len(fanouts), f"batch {j}")
 
 
 # All neighbours of nodes that have far more of them than the average.
