@@ -55,7 +55,7 @@ def _sparse_graph(n, active, degree, rng):
     (200_001, 150_000, 30, [1000, 1, 999], (25, 10)),   # the edge list split between workgroups
     (200_001, 150_000, 30, [9000, 1], (7, 2)),          # more seeds than one launch marks
     (200_001, 150_000, 30, [9000] + [40, 0, 1] * 5, (3, 2)),         # the same with the longest table of buffers
-    (300_007, 250_000, 30, [600] * 4, (10, 10, 40)),    # over 65,536 frontier nodes counted by a launch of their own
+    (300_007, 250_000, 30, [1300, 600, 0], (10, 10, 40)),            # over 131,072 frontier nodes counted by a launch of their own
     (3_000_017, 400_000, 12, [900] * 8, (40, 3)),       # wavefront-per-node draw in front of the slices
     (300_007, 250_000, 30, [1500, 0, 1200, 1, 900, 1500, 1500, 1500], (25, 10)),    # over 2.2 M edges: first-seen order by rank words
     (300_007, 250_000, 30, [1500] * 4, (40, 10)),
