@@ -1920,14 +1920,18 @@ struct BatchIndices {
     uint8_t batch[kMaxGroup];         // of the group, in that order
 };
 
-template <bool FIRST>
+// PARTS wavefronts share the counting of 64 words.  With first batches every two words are a read that is waited for, behind the additions
+// in front of it, so on graphs of up to 4 Mi nodes eight do: 8 batches of 1024 seeds (15,10) on 1 M nodes 19.5 -> 8.2 us, on 2.4 M 20.0 -> 9.7,
+// on 5 M 21.5 -> 15.6, but there 4 of 64 (10,5) 9.2 -> 10.3.  Without them nothing is waited for.
+template <bool FIRST, int PARTS>
 __global__ void __launch_bounds__(256) k_histogram_bitmaps(const uint32_t* __restrict__ visited, int64_t words, int group,
                                                            const BatchIndices order, uint32_t* __restrict__ counts,
                                                            uint32_t* __restrict__ first_batch, int64_t num_nodes) {
     constexpr int C = 5, F = 4;                       // planes: up to 16 batches, the ordinal of the first of them
     static_assert(kMaxGroup <= 16, "planes");
     const int lane = rg_lane();
-    const int64_t w0 = ((int64_t)blockIdx.x * 4 + (threadIdx.x >> 6)) * RG_WAVE;
+    const int wave = blockIdx.x * 4 + (threadIdx.x >> 6);
+    const int64_t w0 = (int64_t)(wave / PARTS) * RG_WAVE;
     const bool in = w0 + lane < words;
     uint32_t bits[kMaxGroup];
 #pragma unroll
@@ -1952,7 +1956,8 @@ __global__ void __launch_bounds__(256) k_histogram_bitmaps(const uint32_t* __res
     }
     const unsigned long long named = __ballot(any != 0u);
     const int bit = lane & 31;
-    for (int w = 0; w < RG_WAVE; w += 2) {
+    for (int pair = 0; pair < RG_WAVE / 2 / PARTS; ++pair) {
+        const int w = 2 * (PARTS == 1 ? pair : pair * PARTS + __builtin_amdgcn_readfirstlane(wave % PARTS));
         if (((named >> w) & 3ull) == 0ull) continue;                      // uniform
         const int from = w + (lane >> 5);
         uint32_t c = 0u, f = 0u;
@@ -2511,10 +2516,14 @@ rg_status rg_access_histogram_sampled(rg_ctx* ctx, int32_t group, const int32_t*
     RG_HIP(ctx, hipSetDevice(ctx->device));
     hipStream_t s = (hipStream_t)stream;
     const int64_t words = rg_div_up(num_nodes, 32);
-    const unsigned blocks = (unsigned)rg_div_up(words, 4 * RG_WAVE);
+    const int64_t waves = rg_div_up(words, RG_WAVE);
+    const int parts = first_batch && waves <= 8ll * ctx->num_cus ? 8 : 1;
+    const unsigned blocks = (unsigned)rg_div_up(waves * parts, 4);
     const int tok = rg_prof_begin(ctx, RG_K_HISTOGRAM, s);
-    if (first_batch) k_histogram_bitmaps<true><<<blocks, 256, 0, s>>>((const uint32_t*)ctx->visited.p, words, group, order, counts, first_batch, num_nodes);
-    else k_histogram_bitmaps<false><<<blocks, 256, 0, s>>>((const uint32_t*)ctx->visited.p, words, group, order, counts, nullptr, num_nodes);
+#define RG_LAUNCH_BITMAPS(FIRST, PARTS)                                                                                   \
+    k_histogram_bitmaps<FIRST, PARTS><<<blocks, 256, 0, s>>>((const uint32_t*)ctx->visited.p, words, group, order, counts, first_batch, num_nodes)
+    if (!first_batch) RG_LAUNCH_BITMAPS(false, 1); else if (parts == 1) RG_LAUNCH_BITMAPS(true, 1); else RG_LAUNCH_BITMAPS(true, 8);
+#undef RG_LAUNCH_BITMAPS
     rg_prof_end(ctx, tok, s);
     RG_LAUNCH_CHECK(ctx, "k_histogram_bitmaps");
     return RG_OK;

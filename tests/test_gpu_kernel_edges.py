@@ -499,8 +499,9 @@ def test_batches_of_one_launch(B, ctx, n, degree, seeds, fanouts):
         assert np.array_equal(counts.cpu().numpy().view(np.uint32), want)
 
 
-# A wavefront counts 64 words of ids, a word of all batches in a lane; the batches come in any order, some under one index.
-@pytest.mark.parametrize("n,group", [(31, 2), (2048, 16), (2049, 5), (70_001, 1), (70_001, 9)])
+# A wavefront (eight of them on up to 2048 x 2048 nodes) counts 64 words of ids, a word of all batches in a lane; the batches come in any
+# order, some under one index.
+@pytest.mark.parametrize("n,group", [(31, 2), (2048, 16), (2049, 5), (70_001, 1), (70_001, 9), (2048 * 2048, 3), (2048 * 2048 + 1, 2)])
 def test_bitmap_counts_of_batches_in_any_order(B, ctx, n, group):
     log(f"[bitmap counts] N={n} group={group}")
     rng = np.random.default_rng(n + group)
