@@ -30,8 +30,10 @@ __global__ void __launch_bounds__(256) k_histogram(const int32_t* __restrict__ n
 constexpr int kHistRangeMax = 8192;    // ids per workgroup at most (32 KB of LDS, 64 KB when first batches are tracked as well)
 constexpr int kHistRangeMin = 512;
 constexpr int kHistRunTile = 1024;     // runs whose bounds are in LDS at a time
-constexpr int kHistAhead = 384;        // entries of a run per range (by the lists' room, about twice what is in them) from which on reading ahead
-                                       // pays: 704 at 192 batches of 2.4 M nodes 95 -> 66 us; 122 and 245 on 1 M nodes 64 / 66 and 72 / 73, 16 on 10 M 125 / 148
+// Entries of a run per range (by the lists' room, about twice what is in them) from which on reading ahead is never slower.  Without and with it,
+// clearing included: 62 33 / 37 us, 114 31 / 33, 173 57 / 62, 206 56 / 57 and 80 / 78, 255 66 / 61, 29 / 26 and 43 / 35, but 260 63 / 66, 275 61 / 60
+// and 54 / 52, 344 65 / 65 and 65 / 63; 412 57 / 53, 481 111 / 95, 584 125 / 102, 651 56 / 54 to 74 / 67, 704 141 / 113, 1100 63 / 57.
+constexpr int kHistAhead = 384;
 
 // bounds[r * (ranges + 1) + j] = first entry of run r with an id >= j * range, as an index into the batch's list.  Consecutive
 // threads search one run for consecutive keys.  Bound by the lines the probes touch: ids sampled at random lie within a few

@@ -2,7 +2,7 @@
 //
 // Data layout in HBM: CSR (row_ptr int32/int64, col_idx int32) is read-only; the batch's cumulative
 // frontier `nodes` grows tier by tier; `visited` is the N-bit bitmap of its members.  A hop's new tier is found in one of
-// three ways (TierMode below); a member's position comes from the tier's rank blocks or from `pos[v]`.  All sizes that
+// four ways (TierMode below); a member's position comes from the tier's rank blocks or from `pos[v]`.  All sizes that
 // depend on the data (frontier and edge counts) stay on the device: launches are sized by static upper bounds and
 // kernels read the actual counts.
 #include <string.h>
@@ -17,9 +17,9 @@ constexpr int kWordsPerBlock = 1024; // bitmap words per workgroup in the tier k
 // How the ids a hop has sampled become its new tier.
 //  kTierSliced    (ascending order) no marking during the draw.  A workgroup owns an id range of slice_words * 32 ids as a bitmap
 //                 in LDS and reads the hop's whole edge list (or one split of it) for the ids of its range.  Measured on hop 2
-//                 of 8 batches of 4096 seeds at N = 10 M (15.9 M edges): reading col_idx and writing nbr takes 207 us, with
+//                 of 8 batches of 4096 seeds at N = 10 M (15.9 M edges): reading col_idx and writing nbr took 207 us, with
 //                 one global atomicOr per edge behind a probe 717 us (37 G atomics/s, the same for every scope), with a
-//                 byte store per edge 341 us; the LDS pass adds 44 us.
+//                 byte store per edge 341 us; the LDS pass adds 44 us.  (Since batches share lines of col_idx the reading takes 163.)
 //  kTierAtomic    (ascending order) one probe and at most one atomicOr per edge on the bitmap `marked`.
 //  kTierFirstSeen (first-seen order) the first edge of the hop that names a node is kept per node (atomicMax).
 //  kTierRankedSeen (first-seen order) the tier is found as in kTierSliced, which gives its nodes their ascending positions; the
@@ -341,14 +341,15 @@ __global__ void __launch_bounds__(512) k_sched_sort(const int32_t* __restrict__ 
 }
 
 // ---------------------------------------------------------------------------- batches of a group
-// Several batches are sampled by the same launches: blockIdx.y selects the batch, which brings its own outputs
+// Several batches are sampled by the same launches: every workgroup belongs to one (rg_batch), which brings its own outputs
 // (BatchTable) and its own slice of the scratch (SampleScratch).  Most kernels of one batch are
 // far smaller than the device (hop 0 of a 4096-seed batch is 16 workgroups), so a group fills it better and pays
 // every launch once.
 constexpr int kMaxGroup = RG_MAX_GROUP;
 constexpr unsigned kXcds = 8;
-// Frontier nodes in a row to an XCD, where a batch has 64 such blocks or more (with fewer the XCDs would be unequal): batches' tiers are not cut
-// alike, so short runs miss each other (hop 2 of 8 batches, 256 nodes 700 us a call, 1024 to 8192 679, 16,384 689, not shared 717).
+// Frontier nodes in a row to an XCD at most, for the kernels that draw and count, and no more than a 64th of a batch's, or the XCDs would be
+// unequal (fewer than 64 workgroups are not shared; the emit's go one by one): batches' tiers are not cut alike, so
+// short runs miss each other (hop 2 of 8 batches, 256 nodes 700 us a call, 1024 to 8192 679, 16,384 689, not shared 717).
 constexpr int kSharedNodes = 4096;
 
 // The batches' buffers: a table of 8-byte entries, [field][batch].  It goes to the first kernel as an argument, which leaves a copy in the
@@ -855,7 +856,7 @@ __global__ void __launch_bounds__(256) k_hop_sample_thread(const int32_t* __rest
     }
 }
 
-// Draws (lanes) of a hop for which k_hop_sample_lanes is faster: 1024 nodes of 25 neighbours 9.8 -> 6.5 us, three batches' 78 k nodes of 10
+// Draws (lanes) of a hop for which k_hop_sample_lanes is faster: 1024 nodes of 25 neighbours 11.2 -> 7.2 us, three batches' 78 k nodes of 10
 // (1.25 M lanes) make the call 66 us against 63.  With fan-outs up to 16 a thread per node takes less (10: 5.4 against 7.4 us, 5: 4.7 / 6.6).
 constexpr int64_t kLaneDraws = 1 << 18;
 
@@ -1565,9 +1566,14 @@ __global__ void __launch_bounds__(256) k_relabel(const SampleScratch S, int firs
 // All hops of a small batch by one workgroup: the membership bits and the hop's marks are in LDS, the phases are separated by
 // barriers instead of launches (12 launches for two hops, each bound by its own latency).  A thread draws for one frontier
 // node and has all its picks' col_idx reads in flight.  One launch against one per phase, by nodes and the bound on a batch's
-// edges: 10 k nodes 16.6 k edges 27 / 53 us, 36 k 45 / 52, 72 k 60 / 52; 100 k nodes 4.2 k 21 / 53, 16.6 k 44 / 51, 18 k 54 / 54;
-// 500 k nodes 4.2 k 27 / 51, 16.6 k 65 / 55 (eight batches: the same, on as many compute units).  The frontiers' nodes count like
-// edges: there may be more of them where a fan-out is 0 or the graph has few edges (500 k seeds 1320-1370 / 73-124 us).
+// edges, (10,5) on graphs of 20 / 50 / 400 neighbours per node on average, of power-law degrees: 100 k nodes 8 k edges 23 / 28 / 30 us
+// against 45, 16 k 34 / 43 / 53 against 46, 20 k 40 / 51 / 68 against 46, of 16 batches 28 / 31 / 38 against 46, 40 / 59 / 71 against 49 and
+// 49 / 73 / 85 against 49 (of eight as of one, on as many compute units); 500 k nodes 8 k 30 / 35 / 37 against 48, of 16 batches 37 / 47 / 52
+// against 50.  A hop more is 17 us for the launches, and little here: (10,10,10) 20 k 39 / 56 / 70 against 63.  So the lines suit graphs many of
+// whose nodes have fewer neighbours than are drawn; where nearly all have more, and the bound's edges come, calls just below them lose.
+// The frontiers' nodes count like edges: there may be more of them where a fan-out is 0 or the graph has few edges (500 k seeds 1320-1370 /
+// 73-124 us).  Fan-outs above 16 (KMAX = 32) take 42 to 47 registers more than the 128 that 1024 threads have each, and keep them in scratch
+// memory (172 to 192 bytes a thread): (25,10) on 100 k nodes 12 k 34 / 44 / 56 against 45, 20 k 40 / 60 / 83 against 46.
 constexpr int64_t kSmallNodes = 512 * 1024;     // two bitmaps of 64 KB
 inline bool rg_is_small(int64_t num_nodes, int64_t edges_bound, int64_t frontiers_bound) {
     return num_nodes > 0 && num_nodes <= kSmallNodes &&
@@ -1745,9 +1751,10 @@ inline int64_t rg_small_lists_bytes(int64_t num_nodes, int64_t frontier, int64_t
 }
 constexpr int64_t kSmallLds = 160 * 1024 - 512;
 // Whose lists fit: by edges up to which one launch is the faster way.  Its time grows with the edges, that of a launch per phase with
-// the hops: (10,5) 26 k edges 25-30 us / 46, 29 k on 4000 nodes 42 / 48, 32 k there 54 / 50, 62 k on 10,000 45 / 52; (10,10,10)
-// 27 k 30-36 / 62, 42 k on 30,000 nodes 52 / 62, of 16 batches 73 / 69; (5,5,5,5) 67 k 48 / 83.  A thread draws for a node, so larger fan-outs take
-// longer: (25,10) 26 k 40-60 / 48, 37 k 50-79 / 50, (32,16) 28 k 54 / 46.
+// the hops.  Just below the line, on graphs of 20 / 50 / 400 neighbours as above: (10,5) on 10,000 nodes 22 / 24 / 33 us against 46, on 30,000
+// 24 / 28 / 45 against 46, (16,8) on 40,000 24 / 32 / 47 against 47, (10,10,10) on 30,000 29 / 39 / 67 against 64.
+// The number of batches is left out: of 16 the same take 24 / 27 / 46, 27 / 32 / 53, 28 / 37 / 58 and 36 / 46 / 78 against 50, 50, 50
+// and 66-75, so a lower line for them would win up to a tenth where all nodes have more neighbours than are drawn and lose up to half elsewhere.  A thread draws for a node, so larger fan-outs take longer and keep to rg_is_small: (25,10) 26 k 40-60 / 48, (32,16) 28 k 54 / 46.
 constexpr int64_t kSmallEdgesPerHop = 13500;
 inline bool rg_small_lists_fit(int64_t num_nodes, int64_t frontier, int64_t hop_edges) {
     return num_nodes > 0 && num_nodes <= 65536 && rg_small_lists_bytes(num_nodes, frontier, hop_edges) <= kSmallLds;
