@@ -163,7 +163,7 @@ RG_API rg_status rg_blocks_bounds(int64_t num_nodes, int64_t num_edges, int64_t 
  * each in [0, RG_MAX_FANOUT] or RG_FANOUT_ALL; 1 <= num_hops <= RG_MAX_HOPS.
  * A caller that keeps nothing but nbr_local may pass one nbr buffer (and one indptr buffer) for all hops:
  * every hop's nbr_local is right, the shared lists hold the last hop's (with separate ones all hops are
- * relabelled by one launch).
+ * relabelled by one launch).  nbr_local[h] may be nbr[h] itself: the positions are what stays.
  * Errors: RG_ERR_INVALID_ARG; RG_ERR_OOM; RG_ERR_CAPACITY when a buffer is below its bound: nothing
  * is launched and nodes_cap, indptr_cap[h] and nbr_cap[h] of the offending rg_blocks are overwritten
  * with the required sizes (the values rg_blocks_bounds gives), so the caller can reallocate and retry. */

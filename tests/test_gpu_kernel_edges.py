@@ -201,10 +201,13 @@ def test_blocks_with_one_list_buffer_for_all_hops(B, ctx, n, active, degree, see
                 assert np.array_equal(o.indptr[h][:orc.indptr[h].size].cpu().numpy(), orc.indptr[h]), f"batch {j} hop {h}"
 
 
-@pytest.mark.parametrize("n", [10_000, 131_072, 300_007])
-def test_blocks_whose_positions_replace_the_ids(B, ctx, n):
+# One launch with its lists in LDS and without, slices, first edges; enough edges for rank words, which need lists of their own.
+@pytest.mark.parametrize("n,seeds,fanouts,first_seen", [
+    (10_000, [250, 61], (5, 4, 3), False), (131_072, [250, 61], (5, 4, 3), False), (300_007, [250, 61], (5, 4, 3), False),
+    (10_000, [250, 61], (5, 4, 3), True), (300_007, [1500] * 8, (25, 10), True)])
+def test_blocks_whose_positions_replace_the_ids(B, ctx, n, seeds, fanouts, first_seen):
     """One list for a hop's ids and positions: the positions are what stays."""
-    rng, fanouts, seeds = np.random.default_rng(n), (5, 4, 3), [250, 61]
+    rng, order = np.random.default_rng(n), oracle.ORDER_FIRST_SEEN if first_seen else oracle.ORDER_ASCENDING
     rp, ci, ids = _sparse_graph(n, n // 2, 20, rng)
     csr = B.CsrGraph(torch.as_tensor(rp, device=DEV).to(torch.int32), _i32(ci))
     lists = [rng.permutation(ids)[:k].astype(np.int32) for k in seeds]
@@ -212,9 +215,10 @@ def test_blocks_whose_positions_replace_the_ids(B, ctx, n):
     for o in outs:
         for h in range(len(fanouts)):
             o.set_hop(h, nbr_local=o.nbr[h])
-    ctx.sample_blocks_group(csr, [_i32(x) for x in lists], fanouts, 77, 3, outs)
+    ctx.sample_blocks_group(csr, [_i32(x) for x in lists], fanouts, 77, 3, outs,
+                            node_order=B.RG_ORDER_FIRST_SEEN if first_seen else B.RG_ORDER_ASCENDING)
     for j, o in enumerate(outs):
-        orc, hip = oracle.sample_blocks(rp, ci, lists[j], fanouts, 77, 3), HipBatch(o, len(fanouts))
+        orc, hip = oracle.sample_blocks(rp, ci, lists[j], fanouts, 77, 3, order), HipBatch(o, len(fanouts))
         hip.nbr = orc.nbr
         assert_batch_equal(hip, orc, len(fanouts), f"batch {j}")
 
