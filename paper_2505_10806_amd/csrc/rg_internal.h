@@ -155,13 +155,16 @@ static inline int64_t rg_max64(int64_t a, int64_t b) { return a > b ? a : b; }
 // Philox4x32-10 block function (Salmon et al., SC'11, Section 3.3).  Bound by the multiplier: one 32 x 32 -> 64 bit product gives
 // both halves (v_mad_u64_u32), one v_bitop3_b32 both exclusive ors (0x96 is the table of a ^ b ^ c).  A wavefront's block takes 200
 // cycles of its SIMD; with separate high and low products 370, with two v_xor_b32 instead of one v_bitop3_b32 280.
+// SCALAR: c1 and c2 are the same in every lane, and so is what the first round makes of them, which then stays out of the vector
+// registers (v_bitop3_b32 has no scalar form): for kernels that have none to spare.
+template <bool SCALAR = false>
 __device__ __forceinline__ void rg_philox4x32_10(uint32_t c0, uint32_t c1, uint32_t c2, uint32_t c3,
                                                  uint32_t k0, uint32_t k1, uint32_t out[4]) {
 #pragma unroll
     for (int r = 0; r < 10; ++r) {
         const uint64_t p0 = (uint64_t)0xD2511F53u * c0;
         const uint64_t p1 = (uint64_t)0xCD9E8D57u * c2;
-        c0 = __builtin_amdgcn_bitop3_b32((uint32_t)(p1 >> 32), c1, k0, 0x96);
+        c0 = SCALAR && r == 0 ? (uint32_t)(p1 >> 32) ^ c1 ^ k0 : __builtin_amdgcn_bitop3_b32((uint32_t)(p1 >> 32), c1, k0, 0x96);
         c2 = __builtin_amdgcn_bitop3_b32((uint32_t)(p0 >> 32), c3, k1, 0x96);
         c1 = (uint32_t)p1;
         c3 = (uint32_t)p0;

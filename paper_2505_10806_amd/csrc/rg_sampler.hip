@@ -1572,8 +1572,7 @@ __global__ void __launch_bounds__(256) k_relabel(const SampleScratch S, int firs
 // against 50.  A hop more is 17 us for the launches, and little here: (10,10,10) 20 k 39 / 56 / 70 against 63.  So the lines suit graphs many of
 // whose nodes have fewer neighbours than are drawn; where nearly all have more, and the bound's edges come, calls just below them lose.
 // The frontiers' nodes count like edges: there may be more of them where a fan-out is 0 or the graph has few edges (500 k seeds 1320-1370 /
-// 73-124 us).  Fan-outs above 16 (KMAX = 32) take 42 to 47 registers more than the 128 that 1024 threads have each, and keep them in scratch
-// memory (172 to 192 bytes a thread): (25,10) on 100 k nodes 12 k 34 / 44 / 56 against 45, 20 k 40 / 60 / 83 against 46.
+// 73-124 us).  Larger fan-outs take longer above 65,536 nodes: (25,10) on 100 k nodes 12 k 29 / 38 / 49 against 45, 20 k 34 / 53 / 72 against 46.
 constexpr int64_t kSmallNodes = 512 * 1024;     // two bitmaps of 64 KB
 inline bool rg_is_small(int64_t num_nodes, int64_t edges_bound, int64_t frontiers_bound) {
     return num_nodes > 0 && num_nodes <= kSmallNodes &&
@@ -1583,6 +1582,11 @@ inline bool rg_is_small(int64_t num_nodes, int64_t edges_bound, int64_t frontier
 struct Fanouts {
     int32_t v[RG_MAX_HOPS];
 };
+
+// Picks whose columns a thread has on their way: all of them, but with KMAX = 32 eight.  1024 threads have 128 registers each, and with 32 on
+// their way, and the first Philox round in vector registers, 42 to 47 did not fit and went to scratch memory: (25,10) on 366 k nodes 47 us, on
+// 30,000 31, now (5 to 10 registers) 41 and 24; (32,16) on 30,000 36 and 27.
+constexpr int rg_small_reads(int kmax) { return kmax > 16 ? 8 : kmax; }
 
 // Floyd's picks for one node, all in registers (whole row: its places in order).
 template <int KMAX>
@@ -1596,7 +1600,7 @@ __device__ __forceinline__ void rg_draw(int32_t v, int64_t deg, int k, uint32_t 
     for (int blk = 0; blk < KMAX / 4; ++blk) {
         if (blk * 4 < k) {
             uint32_t w[4];
-            rg_philox4x32_10((uint32_t)v, hop, (uint32_t)blk, epoch, k0, k1, w);
+            rg_philox4x32_10<(KMAX > 16)>((uint32_t)v, hop, (uint32_t)blk, epoch, k0, k1, w);
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
                 const int s = blk * 4 + q;
@@ -1664,16 +1668,21 @@ __global__ void __launch_bounds__(1024) k_sample_small(const RP* __restrict__ ro
             indptr[i] = at;
             uint32_t c[KMAX];
             rg_draw<KMAX>(v, deg, k, (uint32_t)hop, k0, k1, epoch, c);
-            int32_t u[KMAX];
+            constexpr int U = rg_small_reads(KMAX);
 #pragma unroll
-            for (int s = 0; s < KMAX; ++s)
-                if (s < m) u[s] = col_idx[start + (int64_t)c[s]];
+            for (int s0 = 0; s0 < KMAX; s0 += U) {
+                int32_t u[U];
+                if (s0) __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-            for (int s = 0; s < KMAX; ++s)
-                if (s < m) {
-                    nbr[at + s] = u[s];
-                    atomicOr(&marked[(uint32_t)u[s] >> 5], 1u << (u[s] & 31));
-                }
+                for (int s = 0; s < U; ++s)
+                    if (s0 + s < m) u[s] = col_idx[start + (int64_t)c[s0 + s]];
+#pragma unroll
+                for (int s = 0; s < U; ++s)
+                    if (s0 + s < m) {
+                        nbr[at + s0 + s] = u[s];
+                        atomicOr(&marked[(uint32_t)u[s] >> 5], 1u << (u[s] & 31));
+                    }
+            }
         }
         if (threadIdx.x == 0) {
             indptr[n_h] = edges;
@@ -1754,7 +1763,9 @@ constexpr int64_t kSmallLds = 160 * 1024 - 512;
 // the hops.  Just below the line, on graphs of 20 / 50 / 400 neighbours as above: (10,5) on 10,000 nodes 22 / 24 / 33 us against 46, on 30,000
 // 24 / 28 / 45 against 46, (16,8) on 40,000 24 / 32 / 47 against 47, (10,10,10) on 30,000 29 / 39 / 67 against 64.
 // The number of batches is left out: of 16 the same take 24 / 27 / 46, 27 / 32 / 53, 28 / 37 / 58 and 36 / 46 / 78 against 50, 50, 50
-// and 66-75, so a lower line for them would win up to a tenth where all nodes have more neighbours than are drawn and lose up to half elsewhere.  A thread draws for a node, so larger fan-outs take longer and keep to rg_is_small: (25,10) 26 k 40-60 / 48, (32,16) 28 k 54 / 46.
+// and 66-75, so a lower line for them would win up to a tenth where all nodes have more neighbours than are drawn and lose up to half elsewhere.
+// Fan-outs above 16 keep to rg_is_small, which was their line when they left registers in scratch memory (40-60 us at 26 k edges); since then
+// (25,10) 26 k on 30,000 nodes takes 28 / 33 / 50 against 46, of 16 batches 31 / 37 / 62 against 46-52.
 constexpr int64_t kSmallEdgesPerHop = 13500;
 inline bool rg_small_lists_fit(int64_t num_nodes, int64_t frontier, int64_t hop_edges) {
     return num_nodes > 0 && num_nodes <= 65536 && rg_small_lists_bytes(num_nodes, frontier, hop_edges) <= kSmallLds;
@@ -1823,16 +1834,21 @@ __global__ void __launch_bounds__(1024) k_sample_small_lists(const RP* __restric
             indptr[i] = at;
             uint32_t c[KMAX];
             rg_draw<KMAX>(v, deg, k, (uint32_t)hop, k0, k1, epoch, c);
-            int32_t u[KMAX];
+            constexpr int U = rg_small_reads(KMAX);
 #pragma unroll
-            for (int s = 0; s < KMAX; ++s)
-                if (s < m) u[s] = col_idx[start + (int64_t)c[s]];
+            for (int s0 = 0; s0 < KMAX; s0 += U) {
+                int32_t u[U];
+                if (s0) __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-            for (int s = 0; s < KMAX; ++s)
-                if (s < m) {
-                    list[at + s] = (uint16_t)u[s];
-                    atomicOr(&marked[(uint32_t)u[s] >> 5], 1u << (u[s] & 31));
-                }
+                for (int s = 0; s < U; ++s)
+                    if (s0 + s < m) u[s] = col_idx[start + (int64_t)c[s0 + s]];
+#pragma unroll
+                for (int s = 0; s < U; ++s)
+                    if (s0 + s < m) {
+                        list[at + s0 + s] = (uint16_t)u[s];
+                        atomicOr(&marked[(uint32_t)u[s] >> 5], 1u << (u[s] & 31));
+                    }
+            }
         }
         if (threadIdx.x == 0) {
             indptr[n_h] = edges;
