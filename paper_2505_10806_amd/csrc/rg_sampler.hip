@@ -646,7 +646,7 @@ __global__ void __launch_bounds__(1024) k_scan_hop(const SampleScratch S, int ho
 }
 
 // Per-block counts of fresh ids -> exclusive offsets; the end of the new tier goes to tier_off[hop + 2].  block_edges: a block is
-// that many of the hop's edges; 0: there are tier_blocks of them.
+// that many of the hop's edges, of which there may be more or fewer than were launched for; 0: there are tier_blocks of them.
 __global__ void __launch_bounds__(1024) k_scan_tier(const SampleScratch S, int hop, int tier_blocks, int block_edges) {
     const int g = rg_batch(S);
     if (block_edges) {
@@ -1262,7 +1262,8 @@ __global__ void __launch_bounds__(256) k_first_seen_count(const SampleScratch S,
     const int32_t* __restrict__ first_key = S.first_key + g * S.num_nodes;
     const int64_t n_edges = rg_hop_list(S, g, (int)hop, kIndptr)[rg_tier_off(S, g)[hop + 1]];
     __shared__ int part[4];
-    for (int64_t chunk = blk; chunk * kEdgesPerBlock < n_edges; chunk += rg_blocks_per_batch(S)) {
+    int64_t chunk = blk;
+    do {                                                           // (a workgroup without an edge writes a zero)
         const int64_t e0 = chunk * kEdgesPerBlock + threadIdx.x * 4;
         int c = 0;
 #pragma unroll
@@ -1273,7 +1274,8 @@ __global__ void __launch_bounds__(256) k_first_seen_count(const SampleScratch S,
         if (rg_lane() == 0) part[threadIdx.x >> 6] = c;
         __syncthreads();
         if (threadIdx.x == 0) S.chunk_sum[g * S.chunk_stride + chunk] = part[0] + part[1] + part[2] + part[3];
-    }
+        chunk += rg_blocks_per_batch(S);
+    } while (chunk * kEdgesPerBlock < n_edges);
 }
 
 // Appends the opened nodes behind the current frontier in edge order, records their positions, marks them visited
@@ -2494,7 +2496,8 @@ rg_status rg_sample_blocks_group(rg_ctx* ctx, const rg_csr* csr, int32_t group, 
             const int fs_blocks = (int)rg_max64(1, rg_div_up(launch_edges(h), kEdgesPerBlock));
             k_first_seen_count<<<(unsigned)(fs_blocks) * ug, 256, 0, s>>>(S, h);
             RG_LAUNCH_CHECK(ctx, "k_first_seen_count");
-            k_scan_tier<<<ug, 1024, 0, s>>>(S, h, 0, kEdgesPerBlock);
+            // (the edges there are make one block per workgroup where it was launched for the bound; asking for them takes 1 us a hop)
+            k_scan_tier<<<ug, 1024, 0, s>>>(S, h, fs_blocks, launch_edges(h) < eub_max[h] ? kEdgesPerBlock : 0);
             RG_LAUNCH_CHECK(ctx, "k_scan_tier");
             k_first_seen_emit<<<(unsigned)(fs_blocks) * ug, 256, 0, s>>>(S, h);
             RG_LAUNCH_CHECK(ctx, "k_first_seen_emit");
