@@ -2,7 +2,7 @@
 //
 // Data layout in HBM: CSR (row_ptr int32/int64, col_idx int32) is read-only; the batch's cumulative
 // frontier `nodes` grows tier by tier; `visited` is the N-bit bitmap of its members.  A hop's new tier is found in one of
-// four ways (TierMode below); a member's position comes from the tier's rank blocks or from `pos[v]`.  All sizes that
+// five ways (TierMode below); a member's position comes from the tier's rank blocks or from `pos[v]`.  All sizes that
 // depend on the data (frontier and edge counts) stay on the device: launches are sized by static upper bounds and
 // kernels read the actual counts.
 #include <string.h>
@@ -12,7 +12,6 @@
 namespace {
 
 constexpr int kChunk = 1024;         // frontier nodes per workgroup in the count kernel: the unit of hop_sum
-constexpr int kWordsPerBlock = 1024; // bitmap words per workgroup in the tier kernels of kTierAtomic (256 threads x 4)
 
 // How the ids a hop has sampled become its new tier.
 //  kTierSliced    (ascending order) no marking during the draw.  A workgroup owns an id range of slice_words * 32 ids as a bitmap
@@ -21,6 +20,7 @@ constexpr int kWordsPerBlock = 1024; // bitmap words per workgroup in the tier k
 //                 one global atomicOr per edge behind a probe 717 us (37 G atomics/s, the same for every scope), with a
 //                 byte store per edge 341 us; the LDS pass adds 44 us.  (Since batches share lines of col_idx the reading takes 163.)
 //  kTierAtomic    (ascending order) one probe and at most one atomicOr per edge on the bitmap `marked`.
+//  kTierBytes     (ascending order) a byte store per edge by the draw, then one or two launches per hop where slices take three.
 //  kTierFirstSeen (first-seen order) the first edge of the hop that names a node is kept per node (atomicMax).
 //  kTierRankedSeen (first-seen order) the tier is found as in kTierSliced, which gives its nodes their ascending positions; the
 //                 first edges are kept by those (N / 6 bytes of rank blocks and 4 bytes per new node instead of 4 N scattered
@@ -51,7 +51,7 @@ inline int64_t rg_expected_edges(int64_t num_nodes, int64_t num_edges, int64_t s
     }
     return sum;
 }
-enum TierMode { kTierSliced = 0, kTierAtomic = 1, kTierFirstSeen = 2, kTierRankedSeen = 3 };
+enum TierMode { kTierSliced = 0, kTierAtomic = 1, kTierFirstSeen = 2, kTierRankedSeen = 3, kTierBytes = 4 };
 // First-seen order through rank blocks: four more launches per hop and a pass over the hop's edges for every kSeenSlice new nodes,
 // but cheaper edges where the first-edge keys of all batches (4 N bytes each) are far from fitting the L2s.  Whole call, ranked
 // against kTierFirstSeen, on graphs of 49-50 edges per node unless said otherwise:
@@ -76,6 +76,31 @@ constexpr int kSplitEdges = 8192;    // edges per split at least, and two per bi
 constexpr int kTierWords = 768;      // bitmap words per workgroup in the tier kernels of kTierSliced
 constexpr int kTierWordsSmall = 192; // the same where few workgroups come of that, which then are larger than their words: the rows
 constexpr int kEmitThreadsSmall = 384;       // of up to 6144 new ids wait to be read (192 threads 119 us a call, 384 116; 768 are up to 12 % slower in groups)
+constexpr unsigned kTierSelfScan = 4096;     // workgroups up to which k_tier_emit adds up the counts in front of its own itself
+// kTierBytes saves launches (two hops 6 instead of 10, or 8 where the tiers are counted by launches of their own), which are what bounds calls
+// of few edges, on the host as on the device; its stores cost 9 ps each, more where the bytes of all batches, which every hop clears and reads,
+// outgrow an XCD's L2 (two maps of 2 MB).  So the line is by the product of the batches' edges and nodes, and lower from 2 M nodes in all on;
+// whole call, bytes against slices:
+//   below it   one batch of 356 k edges on 186 k nodes 59 / 77 us, 459 k on 40 k 58 / 83, 299 k on 254 k 61 / 78, 1.4 M on 673 k 88 / 110, 30 k on
+//              865 k 43 / 55, 80 k on 2 M 48 / 61; two of 527 k on 236 k 73 / 88, of 486 k on 972 k 86 / 96; four of 285 k on 59 k 66 / 85;
+//              eight of 61 k on 209 k 50 / 56, of 246 k on 119 k 81 / 90, of 25 k on 583 k 48 / 55
+//   above it   two of 190 k on 2.3 M 61 / 72, of 286 k on 3.1 M 69 / 72, four of 75 k on 1.9 M 60 / 65, two of 670 k on 1.8 M 87 / 82, of 1 M on
+//              1.1 M 121 / 126, one of 3.1 M on 2.8 M 165 / 148, two of 1 M on 3.1 M 150 / 133, four of 419 k on 1.6 M 103 / 89, eight of 178 k on 2.2 M 103 / 89
+// An atomic on a bitmap in place of the byte makes words that many edges name queue up (dense-social batch 95 / 57); above 4 Mi nodes, where few
+// edges take it, it reads an eighth (one batch on 5-11 M nodes 46-52 us, with bytes 52-61).
+constexpr double kBytesEdgesNodes[2] = {4e12, 1.1e12};
+constexpr int64_t kBytesFit = 2 * 1000 * 1000;
+constexpr int64_t kBytesNodes = 4 << 20;
+// Two byte maps for all batches fit where slices' bitmaps do (sliced_bytes).
+inline bool rg_use_bytes(int64_t num_nodes, int64_t words, int64_t edges, int group) {
+    return num_nodes <= kBytesNodes &&
+           (double)edges * group * ((double)num_nodes * group) <= kBytesEdgesNodes[num_nodes * group >= kBytesFit] &&
+           group * words * 32 <= (int64_t)kSliceGroups * kSliceWords * 4;
+}
+// Bitmap words up to which a tier workgroup counts the bytes in front of its own itself, and the bytes all of them read for that: one batch on
+// 133 k nodes 37.4 us a call, 38.3 with a launch that counts, 177 k 60.1 / 58.7, 254 k 63.5 / 60.7, 486 k 75 / 62; eight on 119 k 82 / 86; four on
+// 59 k 66 / 71.
+constexpr int64_t kBytesSelfWords = 5000, kBytesSelfRead = 12 * 1000 * 1000;
 constexpr int kRankIds = 48;         // ids to a rank block, two to three bitmap words (see rg_rank_blocks)
 constexpr int kBaseIds = kRankIds * 1024;      // ids to a base: the members among them are counted in 16 bits
 static_assert(kBaseIds % (32 * kTierWords) == 0 && kBaseIds % (32 * kTierWordsSmall) == 0 && kTierWords % 3 == 0 && kTierWordsSmall % 3 == 0,
@@ -368,7 +393,7 @@ struct SampleScratch {
     const uint64_t* table;
     uint32_t* visited;                // [group][words]
     uint32_t* marked;                 // kTierAtomic: [group][words], every id met
-    uint32_t* slice_marks;            // kTierSliced: [group][splits][words], ids of a hop
+    uint32_t* slice_marks;            // kTierSliced: [group][splits][words], ids of a hop; kTierBytes: rg_bytes
     uint4* rank[2];                   // kTierSliced: rank blocks and bases of four hops each (rg_rank_blocks)
     int32_t* pos;                     // [group][num_nodes] (kTierSliced: of the seeds only)
     int32_t* chunk_sum;               // [group][chunk_stride]: new ids per workgroup of the tier kernels
@@ -399,6 +424,8 @@ __device__ __forceinline__ int32_t* rg_tier_off(const SampleScratch& S, int g) {
 __device__ __forceinline__ int32_t* rg_hop_list(const SampleScratch& S, int g, int hop, HopField f) {
     return rg_global(rg_entry(S, kHopFields + kHopFieldCount * hop + f, g));
 }
+// kTierBytes: a byte per id, 1 for those the hop has sampled.
+__device__ __forceinline__ uint8_t* rg_bytes(const SampleScratch& S, int g) { return (uint8_t*)S.slice_marks + g * S.words * 32; }
 __device__ __forceinline__ void rg_put_edges(const SampleScratch& S, int g, int hop, int edges) {
     int32_t* out = rg_global(rg_entry(S, kEdgesOut, g));               // may be NULL
     if (out) out[hop] = edges;
@@ -484,7 +511,7 @@ __global__ void __launch_bounds__(256) k_mark_seeds_most(const BatchTable<kTable
 
 // The same in one launch for graphs of up to kMaxSlices slices: a workgroup owns one slice of a batch's ids, collects the
 // seeds of its range in LDS and writes its part of `visited`.
-// copy: `marked` starts as `visited` (kTierAtomic).
+// `marked` starts as `visited` (kTierAtomic), the bytes as zeros (kTierBytes).
 // Every slice's workgroup reads all seeds, 1024 at a time: for more than 8192 of them clearing and marking take less in launches
 // of their own, unless several batches make many workgroups of them.  One hop after it, one launch against two or three: one
 // batch of 4096 seeds, N = 1 M 38 / 39 us, of 8192 43 / 39, of 16 k 52 / 41, of 65 k 126 / 64, of 200 k 305 / 117, at N = 10 M 38 / 43,
@@ -494,13 +521,17 @@ inline bool rg_use_init(int slices, int group, int64_t seeds) {
 }
 // The workgroups behind the slices do for the seeds what k_hop_count does.
 template <int N>
-__device__ __forceinline__ void rg_sample_init(const RowPtr& row_ptr, const BatchTable<N>& B, const SampleScratch& S, int fanout, int copy) {
+__device__ __forceinline__ void rg_sample_init(const RowPtr& row_ptr, const BatchTable<N>& B, const SampleScratch& S, int fanout, int mode) {
     extern __shared__ uint32_t slice_bits[];
     const int g = rg_batch(S);
     const unsigned slice = rg_block(S);
     if (blockIdx.x == 0) rg_copy_table(S, B);
     const int num_seeds = (int)B.v[kNumSeeds * S.group + g];
     const int32_t* __restrict__ seeds = rg_global(B.v[kSeeds * S.group + g]);
+    if (mode == kTierBytes) {                            // (words * 32 of them: whole 16-byte chunks)
+        uint4* __restrict__ bytes = (uint4*)rg_bytes(S, g);
+        for (int64_t i = (int64_t)slice * 1024 + threadIdx.x; i < S.words * 2; i += (int64_t)rg_blocks_per_batch(S) * 1024) bytes[i] = make_uint4(0u, 0u, 0u, 0u);
+    }
     if (slice >= (unsigned)S.slices) {
         const unsigned chunk = slice - (unsigned)S.slices;
         const int i = (int)(chunk * kChunk + threadIdx.x);
@@ -542,15 +573,15 @@ __device__ __forceinline__ void rg_sample_init(const RowPtr& row_ptr, const Batc
     uint32_t* __restrict__ marked = S.marked + g * S.words + w0;
     for (int w = threadIdx.x; w < n_words; w += 1024) {
         visited[w] = slice_bits[w];
-        if (copy) marked[w] = slice_bits[w];
+        if (mode == kTierAtomic) marked[w] = slice_bits[w];
     }
 }
 
-__global__ void __launch_bounds__(1024) k_sample_init(const RowPtr row_ptr, const BatchTable<kTableSome> B, const SampleScratch S, int fanout, int copy) {
-    rg_sample_init(row_ptr, B, S, fanout, copy);
+__global__ void __launch_bounds__(1024) k_sample_init(const RowPtr row_ptr, const BatchTable<kTableSome> B, const SampleScratch S, int fanout, int mode) {
+    rg_sample_init(row_ptr, B, S, fanout, mode);
 }
-__global__ void __launch_bounds__(1024) k_sample_init_most(const RowPtr row_ptr, const BatchTable<kTableMost> B, const SampleScratch S, int fanout, int copy) {
-    rg_sample_init(row_ptr, B, S, fanout, copy);
+__global__ void __launch_bounds__(1024) k_sample_init_most(const RowPtr row_ptr, const BatchTable<kTableMost> B, const SampleScratch S, int fanout, int mode) {
+    rg_sample_init(row_ptr, B, S, fanout, mode);
 }
 
 // ---------------------------------------------------------------------------- per hop: sizes
@@ -666,6 +697,9 @@ __device__ __forceinline__ void rg_mark(int32_t u, uint32_t* __restrict__ marked
     atomicOr(&marked[w], bit);
 }
 
+// kTierBytes: a byte store, which waits for nothing, where an atomic on a word that many edges name waits for all of theirs.
+__device__ __forceinline__ void rg_mark_byte(const SampleScratch& S, int g, int32_t u) { rg_bytes(S, g)[u] = 1; }
+
 // First-seen order: instead of a bit, remember the first edge of the hop that names a node outside the frontier.
 __device__ __forceinline__ void rg_note_first_edge(int32_t u, int64_t e, const uint32_t* __restrict__ visited,
                                                    int32_t* __restrict__ first_key) {
@@ -674,6 +708,12 @@ __device__ __forceinline__ void rg_note_first_edge(int32_t u, int64_t e, const u
     const int32_t key = 0x7FFFFFFF - (int32_t)e;
     if (first_key[u] >= key) return;                  // a stale read only costs a redundant atomic
     atomicMax(&first_key[u], key);
+}
+
+// kTierAtomic: k_tier_emit adds to the next hop's sums, which the draw in front of it clears.
+__device__ __forceinline__ void rg_clear_next_sum(const SampleScratch& S, int g, uint32_t hop, int64_t thread, int64_t threads) {
+    int32_t* __restrict__ next_sum = S.hop_sum[(hop + 1) & 1] + g * S.chunk_stride;
+    for (int64_t c = thread; c <= S.frontier_stride / kChunk; c += threads) next_sum[c] = 0;
 }
 
 // General sampler: one wavefront (= one 64-thread workgroup) per frontier node, any fan-out up to
@@ -696,6 +736,7 @@ __global__ void __launch_bounds__(RG_WAVE) k_hop_sample_wave(const int32_t* __re
     uint32_t* __restrict__ marked = S.marked + g * S.words;
     int32_t* __restrict__ first_key = MODE == kTierFirstSeen ? S.first_key + g * S.num_nodes : nullptr;
     const int lane = threadIdx.x;
+    if (MODE == kTierAtomic || MODE == kTierBytes) rg_clear_next_sum(S, g, hop, (int64_t)blk * RG_WAVE + lane, (int64_t)rg_blocks_per_batch(S) * RG_WAVE);
     for (int64_t i = blk; i < n_h; i += rg_blocks_per_batch(S)) {
         const int32_t v = nodes[i];
         const int64_t start = row_start[i], deg = row_deg[i];
@@ -779,6 +820,7 @@ __global__ void __launch_bounds__(256) k_hop_sample_thread(const int32_t* __rest
     const int n_h = rg_tier_off(S, g)[hop + 1];
     int32_t* __restrict__ indptr = rg_hop_list(S, g, (int)hop, kIndptr);
     const int64_t first = (int64_t)blk * NODES;
+    if (MODE == kTierAtomic || MODE == kTierBytes) rg_clear_next_sum(S, g, hop, (int64_t)blk * 256 + threadIdx.x, (int64_t)rg_blocks_per_batch(S) * 256);
     if (first >= n_h) {                                  // uniform per workgroup
         if (n_h == 0 && blk == 0 && threadIdx.x == 0) {
             indptr[0] = 0;
@@ -852,6 +894,7 @@ __global__ void __launch_bounds__(256) k_hop_sample_thread(const int32_t* __rest
             nbr[base + e] = u[q];
             if (MODE == kTierFirstSeen) rg_note_first_edge(u[q], base + e, visited, first_key);
             if (MODE == kTierAtomic) rg_mark(u[q], marked);
+            if (MODE == kTierBytes) rg_mark_byte(S, g, u[q]);
         }
     }
 }
@@ -874,6 +917,7 @@ __global__ void __launch_bounds__(256) k_hop_sample_lanes(const int32_t* __restr
     const int n_h = rg_tier_off(S, g)[hop + 1];
     int32_t* __restrict__ indptr = rg_hop_list(S, g, (int)hop, kIndptr);
     const int64_t first = (int64_t)blk * NODES;
+    if (MODE == kTierAtomic || MODE == kTierBytes) rg_clear_next_sum(S, g, hop, (int64_t)blk * 256 + threadIdx.x, (int64_t)rg_blocks_per_batch(S) * 256);
     if (first >= n_h) {                                  // uniform per workgroup
         if (n_h == 0 && blk == 0 && threadIdx.x == 0) {
             indptr[0] = 0;
@@ -930,6 +974,7 @@ __global__ void __launch_bounds__(256) k_hop_sample_lanes(const int32_t* __restr
     rg_hop_list(S, g, (int)hop, kNbr)[off + lane] = u;
     if (MODE == kTierFirstSeen) rg_note_first_edge(u, off + lane, S.visited + g * S.words, S.first_key + g * S.num_nodes);
     if (MODE == kTierAtomic) rg_mark(u, S.marked + g * S.words);
+    if (MODE == kTierBytes) rg_mark_byte(S, g, u);
 }
 
 // ---------------------------------------------------------------------------- per hop: new tier, sliced
@@ -1041,6 +1086,70 @@ __global__ void __launch_bounds__(T) k_slice_count(const SampleScratch S) {
     }
 }
 
+// What k_hop_count does for the next hop, by the kernels that emit a tier of ascending ids: the rows of its `total` nodes from position
+// `out` on, and their edges per chunk; the edges of the nodes in front of them, a chunk to a workgroup.
+// in_lds: the new ids are in LDS and go to nodes[] here; else they are there already.  POS: their positions go to pos[] too.
+template <int T, bool POS>
+__device__ __forceinline__ void rg_new_rows(const RowPtr& row_ptr, const SampleScratch& S, int g, int hop, int out, int total,
+                                            int32_t* __restrict__ nodes, const int32_t* ids, bool in_lds, int* edges, int num_chunks, int next_fanout) {
+    constexpr int U = 4;                                 // rows in flight per thread
+    int32_t* __restrict__ pos = S.pos + g * S.num_nodes;
+    int64_t* __restrict__ row_start = S.row_start + g * S.frontier_stride + out;
+    int32_t* __restrict__ row_deg = S.row_deg + g * S.frontier_stride + out;
+    for (int i0 = threadIdx.x; i0 < total; i0 += T * U) {
+        int32_t v[U];
+        int64_t start[U], deg[U];
+#pragma unroll
+        for (int q = 0; q < U; ++q) {
+            v[q] = -1;
+            if (i0 + T * q < total) v[q] = in_lds ? ids[i0 + T * q] : nodes[i0 + T * q];
+        }
+        if (in_lds) {
+#pragma unroll
+            for (int q = 0; q < U; ++q)
+                if (v[q] >= 0) nodes[i0 + T * q] = v[q];
+        }
+        if (POS) {
+#pragma unroll
+            for (int q = 0; q < U; ++q)
+                if (v[q] >= 0) pos[v[q]] = out + i0 + T * q;
+        }
+        if (next_fanout < 0) continue;
+        const auto rows = [&](auto* p) {
+#pragma unroll
+            for (int q = 0; q < U; ++q)
+                if (v[q] >= 0) rg_row_extent(p, v[q], start[q], deg[q]);
+        };
+        if (row_ptr.wide) rows((const int64_t*)row_ptr.p); else rows((const int32_t*)row_ptr.p);
+#pragma unroll
+        for (int q = 0; q < U; ++q)
+            if (v[q] >= 0) {
+                row_start[i0 + T * q] = start[q];
+                row_deg[i0 + T * q] = (int32_t)deg[q];
+                atomicAdd(&edges[(out + i0 + T * q) / kChunk - out / kChunk], (int)(deg[q] <= next_fanout ? deg[q] : next_fanout));
+            }
+    }
+    if (next_fanout < 0) return;
+    __syncthreads();
+    int32_t* __restrict__ next_sum = S.hop_sum[(hop + 1) & 1] + g * S.chunk_stride;
+    for (int i = threadIdx.x; i < num_chunks; i += T)
+        if (edges[i]) atomicAdd(&next_sum[out / kChunk + i], edges[i]);
+}
+
+template <int T>
+__device__ __forceinline__ void rg_old_edges(const SampleScratch& S, int g, int hop, int chunk, int next_fanout) {
+    const int n_h = rg_tier_off(S, g)[hop + 1];
+    if (chunk * kChunk >= n_h) return;                                   // uniform
+    const int32_t* __restrict__ row_deg = S.row_deg + g * S.frontier_stride;
+    int m = 0;
+    for (int i = chunk * kChunk + threadIdx.x; i < n_h && i < (chunk + 1) * kChunk; i += T) {
+        const int deg = row_deg[i];
+        m += deg <= next_fanout ? deg : next_fanout;
+    }
+    m = rg_wave_sum(m);
+    if (rg_lane() == 0 && m) atomicAdd(&S.hop_sum[(hop + 1) & 1][g * S.chunk_stride + chunk], m);
+}
+
 // Emits the new tier behind the current frontier, ascending, with its rank blocks, and makes its ids frontier members.  The
 // ids go through LDS so that they are stored by consecutive lanes (thread by thread: 135 us at hop 2 of 8 batches, 7.5 M ids;
 // now 25); a workgroup with more new ids than fit there (over a third of its range) stores them directly.
@@ -1065,18 +1174,8 @@ __device__ __forceinline__ void rg_slice_emit(const RowPtr& row_ptr, const Sampl
     int g;
     unsigned blk;
     rg_shared_rows(S, run, g, blk);
-    int32_t* __restrict__ next_sum = S.hop_sum[(hop + 1) & 1] + g * S.chunk_stride;
     if (!RANKED_SEEN && blk >= tier_blocks) {
-        const int chunk = (int)(blk - tier_blocks), n_h = rg_tier_off(S, g)[hop + 1];
-        if (chunk * kChunk >= n_h) return;                               // uniform
-        const int32_t* __restrict__ row_deg = S.row_deg + g * S.frontier_stride;
-        int m = 0;
-        for (int i = chunk * kChunk + threadIdx.x; i < n_h && i < (chunk + 1) * kChunk; i += T) {
-            const int deg = row_deg[i];
-            m += deg <= next_fanout ? deg : next_fanout;
-        }
-        m = rg_wave_sum(m);
-        if (rg_lane() == 0 && m) atomicAdd(&next_sum[chunk], m);
+        rg_old_edges<T>(S, g, hop, (int)(blk - tier_blocks), next_fanout);
         return;
     }
     if (!RANKED_SEEN) for (int i = threadIdx.x; i < (int)(sizeof(edges) / sizeof(int)); i += T) edges[i] = 0;
@@ -1140,41 +1239,7 @@ __device__ __forceinline__ void rg_slice_emit(const RowPtr& row_ptr, const Sampl
         if (3 * r < S.words) store_rank(r, word_bits[q], word_bits[q + 1], word_bits[q + 2], (uint32_t)word_rank[q]);
     }
     if (RANKED_SEEN) return;
-    constexpr int U = 4;                                 // rows in flight per thread
-    int64_t* __restrict__ row_start = S.row_start + g * S.frontier_stride + out;
-    int32_t* __restrict__ row_deg = S.row_deg + g * S.frontier_stride + out;
-    for (int i0 = threadIdx.x; i0 < total; i0 += T * U) {
-        int32_t v[U];
-        int64_t start[U], deg[U];
-#pragma unroll
-        for (int q = 0; q < U; ++q) {
-            v[q] = -1;
-            if (i0 + T * q < total) v[q] = total <= kEmitIds ? ids[i0 + T * q] : nodes[i0 + T * q];
-        }
-        if (total <= kEmitIds) {
-#pragma unroll
-            for (int q = 0; q < U; ++q)
-                if (v[q] >= 0) nodes[i0 + T * q] = v[q];
-        }
-        if (next_fanout < 0) continue;
-        const auto rows = [&](auto* p) {
-#pragma unroll
-            for (int q = 0; q < U; ++q)
-                if (v[q] >= 0) rg_row_extent(p, v[q], start[q], deg[q]);
-        };
-        if (row_ptr.wide) rows((const int64_t*)row_ptr.p); else rows((const int32_t*)row_ptr.p);
-#pragma unroll
-        for (int q = 0; q < U; ++q)
-            if (v[q] >= 0) {
-                row_start[i0 + T * q] = start[q];
-                row_deg[i0 + T * q] = (int32_t)deg[q];
-                atomicAdd(&edges[(out + i0 + T * q) / kChunk - out / kChunk], (int)(deg[q] <= next_fanout ? deg[q] : next_fanout));
-            }
-    }
-    if (next_fanout < 0) return;
-    __syncthreads();
-    for (int i = threadIdx.x; i < (int)(sizeof(edges) / sizeof(int)); i += T)
-        if (edges[i]) atomicAdd(&next_sum[out / kChunk + i], edges[i]);
+    rg_new_rows<T, false>(row_ptr, S, g, hop, out, total, nodes, ids, total <= kEmitIds, edges, (int)(sizeof(edges) / sizeof(int)), next_fanout);
 }
 
 template <bool RANKED_SEEN>
@@ -1190,60 +1255,144 @@ __global__ void __launch_bounds__(kEmitThreadsSmall) k_slice_emit_small(const Ro
 }
 
 // ---------------------------------------------------------------------------- per hop: new tier, from `marked`
-__global__ void __launch_bounds__(256) k_tier_count(const SampleScratch S) {
+// chunk_sum[b] = new ids (marked, not yet visited) of the words_per words of workgroup b.
+__global__ void __launch_bounds__(256) k_tier_count(const SampleScratch S, int words_per) {
+    __shared__ int part[4];
     const int g = rg_batch(S);
     const unsigned blk = rg_block(S);
     const uint32_t* __restrict__ marked = S.marked + g * S.words;
     const uint32_t* __restrict__ visited = S.visited + g * S.words;
-    const int64_t w0 = (int64_t)blk * kWordsPerBlock + threadIdx.x * 4;
+    const int64_t w0 = (int64_t)blk * words_per, w1 = w0 + words_per < S.words ? w0 + words_per : S.words;
     int c = 0;
-#pragma unroll
-    for (int q = 0; q < 4; ++q)
-        if (w0 + q < S.words) c += __popc(marked[w0 + q] & ~visited[w0 + q]);
+    for (int64_t w = w0 + threadIdx.x; w < w1; w += 256) c += __popc(marked[w] & ~visited[w]);
     c = rg_wave_sum(c);
-    __shared__ int part[4];
     if (rg_lane() == 0) part[threadIdx.x >> 6] = c;
     __syncthreads();
     if (threadIdx.x == 0) S.chunk_sum[g * S.chunk_stride + blk] = part[0] + part[1] + part[2] + part[3];
 }
 
-// Emit the new ids (marked, not yet visited) in ascending order behind the current frontier, record their positions
-// and make them frontier members (visited = marked).  chunk_sum holds exclusive block offsets.
-__global__ void __launch_bounds__(256) k_tier_emit(const SampleScratch S, int hop) {
-    __shared__ int smem[256 / RG_WAVE + 1];
+// The 32 bytes of word w as bits.
+__device__ __forceinline__ uint32_t rg_byte_word(const uint8_t* __restrict__ bytes, int64_t w) {
+    const uint4* p = (const uint4*)bytes + 2 * w;
+    const uint4 lo = p[0], hi = p[1];
+    const auto four = [](uint32_t x) { return (x * 0x01020408u) >> 24 & 0xFu; };       // (sums of single bits, none of which meet)
+    return four(lo.x) | four(lo.y) << 4 | four(lo.z) << 8 | four(lo.w) << 12 | four(hi.x) << 16 | four(hi.y) << 20 | four(hi.z) << 24 | four(hi.w) << 28;
+}
+
+// kTierBytes on larger graphs: the same as k_tier_count, and the bytes as bits.
+__global__ void __launch_bounds__(256) k_bytes_count(const SampleScratch S, int words_per, int clear) {
+    __shared__ int part[4];
     const int g = rg_batch(S);
     const unsigned blk = rg_block(S);
-    const uint32_t* __restrict__ marked = S.marked + g * S.words;
-    uint32_t* __restrict__ visited = S.visited + g * S.words;
-    int32_t* __restrict__ nodes = rg_nodes(S, g);
-    int32_t* __restrict__ pos = S.pos + g * S.num_nodes;
-    const int64_t w0 = (int64_t)blk * kWordsPerBlock + threadIdx.x * 4;
-    uint32_t bits[4];
+    uint32_t* __restrict__ marked = S.marked + g * S.words;
+    uint8_t* __restrict__ bytes = rg_bytes(S, g);
+    const uint32_t* __restrict__ visited = S.visited + g * S.words;
+    const int64_t w0 = (int64_t)blk * words_per, w1 = w0 + words_per < S.words ? w0 + words_per : S.words;
     int c = 0;
+    for (int64_t w = w0 + threadIdx.x; w < w1; w += 256) {
+        const uint32_t members = visited[w], bits = rg_byte_word(bytes, w) | members;
+        marked[w] = bits;
+        if (clear) ((uint4*)bytes)[2 * w] = ((uint4*)bytes)[2 * w + 1] = make_uint4(0u, 0u, 0u, 0u);
+        c += __popc(bits & ~members);
+    }
+    c = rg_wave_sum(c);
+    if (rg_lane() == 0) part[threadIdx.x >> 6] = c;
+    __syncthreads();
+    if (threadIdx.x == 0) S.chunk_sum[g * S.chunk_stride + blk] = part[0] + part[1] + part[2] + part[3];
+}
+
+// Emits the new tier behind the current frontier, ascending, makes its ids frontier members and does for the next hop what rg_slice_emit
+// does; the positions go to pos[].  A workgroup takes WORDS words, a thread one or three of them.
+// What is in front of a workgroup's words: it counts them in the bytes itself (BYTES; `before` is then read by all of them and `after`
+// written, two bitmaps that take turns, as do the bytes, of which those of the next hop are cleared here), it adds up what k_tier_count
+// found, or k_scan_tier did (scanned).
+template <int T, int WORDS, bool BYTES>
+__device__ __forceinline__ void rg_tier_emit(const RowPtr& row_ptr, const SampleScratch& S, int hop, unsigned tier_blocks, int next_fanout, int run,
+                                             int scanned, const uint32_t* before_all, uint32_t* after_all, uint8_t* next_bytes) {
+    constexpr int NW = T / RG_WAVE, W = WORDS > T ? WORDS / T : 1, TW = WORDS / W, kEmitIds = W == 1 ? WORDS * 32 : WORDS * 32 / 3;
+    __shared__ int smem[NW + 1];
+    __shared__ int part[NW];
+    __shared__ int32_t ids[kEmitIds];
+    __shared__ int edges[WORDS * 32 / kChunk + 2];
+    int g;
+    unsigned blk;
+    rg_shared_rows(S, run, g, blk);
+    if (blk >= tier_blocks) {
+        rg_old_edges<T>(S, g, hop, (int)(blk - tier_blocks), next_fanout);
+        return;
+    }
+    const int num_chunks = (int)(sizeof(edges) / sizeof(int));
+    for (int i = threadIdx.x; i < num_chunks; i += T) edges[i] = 0;
+    const uint32_t* __restrict__ marked = S.marked + g * S.words;
+    const uint8_t* __restrict__ bytes = rg_bytes(S, g);
+    const uint32_t* before = before_all + g * S.words;
+    uint32_t* after = after_all + g * S.words;
+    const int n_h = rg_tier_off(S, g)[hop + 1];
+    const int64_t w = TW == T || (int)threadIdx.x < TW ? ((int64_t)blk * TW + threadIdx.x) * W : S.words;
+    uint32_t bits[W], members[W];
+    const bool whole = TW == T && ((int64_t)blk + 1) * WORDS <= S.words;
+    rg_load_words<W>(before, w, S.words, whole, members);
+    if (BYTES) {
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-        bits[q] = (w0 + q < S.words) ? marked[w0 + q] & ~visited[w0 + q] : 0u;
-        c += __popc(bits[q]);
+        for (int q = 0; q < W; ++q) {
+            bits[q] = 0u;
+            if (w + q < S.words) {
+                bits[q] = rg_byte_word(bytes, w + q) | members[q];
+                if (next_bytes) {
+                    uint4* clear = (uint4*)(next_bytes + g * S.words * 32) + 2 * (w + q);
+                    clear[0] = clear[1] = make_uint4(0u, 0u, 0u, 0u);
+                }
+            }
+        }
+    } else {
+        rg_load_words<W>(marked, w, S.words, whole, bits);
+    }
+    int c = 0;
+    if (BYTES) {
+        const int w_end = (int)blk * WORDS;
+#pragma unroll 8
+        for (int i = threadIdx.x; i < w_end; i += T) c += __popc(rg_byte_word(bytes, i) & ~before[i]);
+    } else if (!scanned) {
+        for (unsigned b = threadIdx.x; b < blk; b += T) c += S.chunk_sum[g * S.chunk_stride + b];
+    } else if (threadIdx.x == 0) {
+        c = S.chunk_sum[g * S.chunk_stride + blk];
+    }
+    c = rg_wave_sum(c);
+    if (rg_lane() == 0) part[threadIdx.x >> 6] = c;
+    int mine = 0;
+#pragma unroll
+    for (int q = 0; q < W; ++q) {
+        if (w + q < S.words && (BYTES || bits[q] != members[q])) after[w + q] = bits[q];
+        bits[q] &= ~members[q];
+        mine += __popc(bits[q]);
     }
     int total;
-    const int excl = rg_block_excl_scan<256 / RG_WAVE>(c, smem, &total);
-    if (total == 0) return;                          // uniform: nothing fresh in this block
-    int out = rg_tier_off(S, g)[hop + 1] + S.chunk_sum[g * S.chunk_stride + blk] + excl;
+    int j = rg_block_excl_scan<NW>(mine, smem, &total);                        // its barriers publish part[]
+    int out = n_h;
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-        uint32_t b = bits[q];
-        if (b == 0u) continue;
-        visited[w0 + q] |= b;
-        const int32_t id0 = (int32_t)((w0 + q) << 5);
-        while (b) {
-            const int bit = __ffs(b) - 1;
-            b &= b - 1u;
-            const int32_t id = id0 + bit;
-            nodes[out] = id;
-            pos[id] = out;
-            ++out;
-        }
-    }
+    for (int q = 0; q < NW; ++q) out += part[q];
+    if (threadIdx.x == 0 && blk + 1 == tier_blocks) rg_tier_off(S, g)[hop + 2] = out + total;
+    if (total == 0) return;                              // uniform
+    int32_t* __restrict__ nodes = rg_nodes(S, g) + out;
+    int32_t* dst = total <= kEmitIds ? ids : nodes;
+#pragma unroll
+    for (int q = 0; q < W; ++q)
+        for (uint32_t b = bits[q]; b; b &= b - 1u) dst[j++] = (int32_t)((w + q) << 5) + __ffs(b) - 1;
+    __syncthreads();                                     // ids, nodes and edges are there
+    rg_new_rows<T, true>(row_ptr, S, g, hop, out, total, nodes, ids, total <= kEmitIds, edges, num_chunks, next_fanout);
+}
+
+__global__ void __launch_bounds__(kTierWords / 3) k_tier_emit(const RowPtr row_ptr, const SampleScratch S, int hop, unsigned tier_blocks,
+                                                              int next_fanout, int run, int scanned) {
+    rg_tier_emit<kTierWords / 3, kTierWords, false>(row_ptr, S, hop, tier_blocks, next_fanout, run, scanned, S.visited, S.visited, nullptr);
+}
+__global__ void __launch_bounds__(kEmitThreadsSmall) k_tier_emit_small(const RowPtr row_ptr, const SampleScratch S, int hop, unsigned tier_blocks,
+                                                                       int next_fanout, int run, int scanned) {
+    rg_tier_emit<kEmitThreadsSmall, kTierWordsSmall, false>(row_ptr, S, hop, tier_blocks, next_fanout, run, scanned, S.visited, S.visited, nullptr);
+}
+__global__ void __launch_bounds__(kEmitThreadsSmall) k_bytes_emit_small(const RowPtr row_ptr, const SampleScratch S, int hop, unsigned tier_blocks,
+                                                                        int next_fanout, int run, const uint32_t* before, uint32_t* after, uint8_t* next_bytes) {
+    rg_tier_emit<kEmitThreadsSmall, kTierWordsSmall, true>(row_ptr, S, hop, tier_blocks, next_fanout, run, 0, before, after, next_bytes);
 }
 
 // ---------------------------------------------------------------------------- per hop: new tier in first-seen order
@@ -2240,7 +2389,10 @@ rg_status rg_sample_blocks_group(rg_ctx* ctx, const rg_csr* csr, int32_t group, 
     for (int g = 0; g < group && ranked_seen; ++g)
         for (int h = 0; h < num_hops; ++h)
             ranked_seen = ranked_seen && eub_max[h] <= kRankedSeenEdges && out[g].nbr_local && out[g].nbr_local[h] && out[g].nbr_local[h] != out[g].nbr[h];
+    bool by_threads = csr->num_edges < (1ll << 32);
+    for (int h = 0; h < num_hops; ++h) by_threads = by_threads && fanouts[h] >= 1 && fanouts[h] <= 32;
     TierMode mode = ranked_seen ? kTierRankedSeen : first_seen ? kTierFirstSeen : (rg_use_slices(S.slices, N, edges) ? kTierSliced : kTierAtomic);
+    if (!first_seen && by_threads && rg_use_bytes(N, words, edges, group)) mode = kTierBytes;
     rg_status st = rg_sampler_reserve(ctx, N, fub_max[num_hops], group, max_edges, first_seen);
     if (st != RG_OK) return st;
     int max_fanout = 0;
@@ -2252,7 +2404,7 @@ rg_status rg_sample_blocks_group(rg_ctx* ctx, const rg_csr* csr, int32_t group, 
                        (rg_is_small(N, edges_bound, frontiers_bound) ||
                         (in_lds && max_fanout <= 16 && rg_max64(edges_bound, frontiers_bound) <= kSmallEdgesPerHop * num_hops));
     // Slices whose scratch is not there and cannot be allocated (a captured call, no memory): the atomic kernels, same results.
-    if (!small && (mode == kTierSliced || mode == kTierRankedSeen)) {
+    if (!small && (mode == kTierSliced || mode == kTierRankedSeen || mode == kTierBytes)) {
         const SlicedBytes need = sliced_bytes(group * words, group * S.frontier_stride, first_seen);
         bool there = has_slices(ctx, need, num_hops);
         if (!there && !rg_capturing(s)) {
@@ -2343,25 +2495,41 @@ rg_status rg_sample_blocks_group(rg_ctx* ctx, const rg_csr* csr, int32_t group, 
     // Hops that a thread or a few lanes per node draw for; these need no offsets per node.
     const auto drawn_by_threads = [&](int h) { return fanouts[h] >= 1 && fanouts[h] <= 32 && csr->num_edges < (1ll << 32); };
     int counted = -1;                                  // the hop whose sizes are there already
+    // Small workgroups for the tiers while large ones would leave compute units without work: one batch on 233 k nodes 69 us a call with large, 56 with
+    // small ones, on 380 k 150 / 117; 369 large ones (3 batches, 3 M nodes) 147 / 158, 648 (8 batches, 2 M) 120 / 140.
+    const bool small_tier = mode != kTierAtomic && rg_div_up(words, kTierWords) * group < ctx->num_cus;
+    const unsigned tier_blocks = (unsigned)rg_max64(1, rg_div_up(words, small_tier ? kTierWordsSmall : kTierWords));
+    const bool self_count = mode == kTierBytes && small_tier && words <= kBytesSelfWords && (int64_t)tier_blocks * group * words * 16 <= kBytesSelfRead;
+    uint32_t* const bytes_at[2] = {S.slice_marks, S.slice_marks + (self_count ? group * words * 8 : 0)};
+    // Counted so, the members after the last hop are to be in `visited`.
+    const auto members = [&](int h) { return self_count && ((num_hops - h) & 1) ? S.marked : S.visited; };
+    uint32_t* const seeds_at = members(0);
     if (rg_use_init(S.slices, group, seeds_max)) {
         const unsigned count_blocks = drawn_by_threads(0) ? (unsigned)rg_div_up(seeds_max, kChunk) : 0u;
         const size_t lds = (size_t)rg_max64(S.slice_words, 1024 / RG_WAVE) * 4;
         const unsigned init_blocks = ((unsigned)S.slices + count_blocks) * ug;
-        const int copy = mode == kTierAtomic ? 1 : 0;
-        if (most) k_sample_init_most<<<init_blocks, 1024, lds, s>>>(row_ptr, table, S, fanouts[0], copy);
-        else k_sample_init<<<init_blocks, 1024, lds, s>>>(row_ptr, some, S, fanouts[0], copy);
+        SampleScratch S0 = S;
+        S0.visited = seeds_at;
+        if (most) k_sample_init_most<<<init_blocks, 1024, lds, s>>>(row_ptr, table, S0, fanouts[0], mode);
+        else k_sample_init<<<init_blocks, 1024, lds, s>>>(row_ptr, some, S0, fanouts[0], mode);
         if (count_blocks) counted = 0;
         RG_LAUNCH_CHECK(ctx, "k_sample_init");
     } else {
         const int64_t group_words = (int64_t)group * words;
-        k_clear_words<<<(int)rg_div_up(group_words, 256), 256, 0, s>>>(S.visited, group_words);
+        k_clear_words<<<(int)rg_div_up(group_words, 256), 256, 0, s>>>(seeds_at, group_words);
         RG_LAUNCH_CHECK(ctx, "k_clear_words");
+        if (mode == kTierBytes) {
+            k_clear_words<<<(int)rg_div_up(group_words * 8, 256), 256, 0, s>>>(S.slice_marks, group_words * 8);
+            RG_LAUNCH_CHECK(ctx, "k_clear_words");
+        }
         if (mode == kTierAtomic) {
             k_clear_words<<<(int)rg_div_up(group_words, 256), 256, 0, s>>>(S.marked, group_words);
             RG_LAUNCH_CHECK(ctx, "k_clear_words");
         }
         const unsigned mark_blocks = (unsigned)(grid_for(seeds_max, 256, 1 << 30)) * ug;
-        if (most) k_mark_seeds_most<<<mark_blocks, 256, 0, s>>>(table, S); else k_mark_seeds<<<mark_blocks, 256, 0, s>>>(some, S);
+        SampleScratch S0 = S;
+        S0.visited = seeds_at;
+        if (most) k_mark_seeds_most<<<mark_blocks, 256, 0, s>>>(table, S0); else k_mark_seeds<<<mark_blocks, 256, 0, s>>>(some, S0);
         RG_LAUNCH_CHECK(ctx, "k_mark_seeds");
     }
 
@@ -2406,6 +2574,7 @@ rg_status rg_sample_blocks_group(rg_ctx* ctx, const rg_csr* csr, int32_t group, 
         }
 
         const int F = fanouts[h];
+        if (mode == kTierBytes) S.slice_marks = bytes_at[h & 1];
         if (drawn_by_threads(h)) {
             const int tok = rg_prof_begin(ctx, RG_K_SAMPLE, s);
             // 64 nodes per workgroup while 256 would leave compute units without two workgroups (see the kernel)
@@ -2431,6 +2600,7 @@ rg_status rg_sample_blocks_group(rg_ctx* ctx, const rg_csr* csr, int32_t group, 
 #define RG_LAUNCH_DRAW_N(MODE) do { if (lanes) RG_LAUNCH_LANES(32, MODE); else if (few) RG_LAUNCH_DRAW_K(64, MODE); else RG_LAUNCH_DRAW_K(256, MODE); } while (0)
             if (mode == kTierSliced || mode == kTierRankedSeen) RG_LAUNCH_DRAW_N(kTierSliced);
             else if (mode == kTierAtomic) RG_LAUNCH_DRAW_N(kTierAtomic);
+            else if (mode == kTierBytes) RG_LAUNCH_DRAW_N(kTierBytes);
             else RG_LAUNCH_DRAW_N(kTierFirstSeen);
 #undef RG_LAUNCH_DRAW_N
 #undef RG_LAUNCH_LANES
@@ -2457,10 +2627,6 @@ rg_status rg_sample_blocks_group(rg_ctx* ctx, const rg_csr* csr, int32_t group, 
             const int64_t split_edges = rg_max64(kSplitEdges, 2 * (int64_t)S.slice_words);
             // (hubs among the frontier: up to eight times the edges of average nodes)
             S.splits = (int)rg_max64(1, rg_min64(rg_min64(eub_max[h], 8 * expected[h]) / split_edges, kSliceGroups / (S.slices * group)));
-            // Small workgroups while large ones would leave compute units without work: one batch on 233 k nodes 69 us a call with large, 56 with
-            // small ones, on 380 k 150 / 117; 369 large ones (3 batches, 3 M nodes) 147 / 158, 648 (8 batches, 2 M) 120 / 140.
-            const bool small_tier = rg_div_up(words, kTierWords) * group < ctx->num_cus;
-            const unsigned tier_blocks = (unsigned)rg_max64(1, rg_div_up(words, small_tier ? kTierWordsSmall : kTierWords));
             k_slice_mark<<<(unsigned)(S.slices * S.splits) * ug, 1024, (size_t)S.slice_words * 4, s>>>(S, h);
             RG_LAUNCH_CHECK(ctx, "k_slice_mark");
             const bool count_next = mode == kTierSliced && h + 1 < num_hops && drawn_by_threads(h + 1);
@@ -2502,13 +2668,30 @@ rg_status rg_sample_blocks_group(rg_ctx* ctx, const rg_csr* csr, int32_t group, 
             k_first_seen_emit<<<(unsigned)(fs_blocks) * ug, 256, 0, s>>>(S, h);
             RG_LAUNCH_CHECK(ctx, "k_first_seen_emit");
         } else {
-            // new tier: count fresh bits per block, scan, emit ascending
-            const int tier_blocks = (int)rg_max64(1, rg_div_up(words, kWordsPerBlock));
-            k_tier_count<<<(unsigned)(tier_blocks) * ug, 256, 0, s>>>(S);
-            RG_LAUNCH_CHECK(ctx, "k_tier_count");
-            k_scan_tier<<<ug, 1024, 0, s>>>(S, h, tier_blocks, 0);
-            RG_LAUNCH_CHECK(ctx, "k_scan_tier");
-            k_tier_emit<<<(unsigned)(tier_blocks) * ug, 256, 0, s>>>(S, h);
+            const int words_per = small_tier ? kTierWordsSmall : kTierWords, scanned = tier_blocks > kTierSelfScan;
+            if (mode == kTierBytes && !self_count) {
+                k_bytes_count<<<tier_blocks * ug, 256, 0, s>>>(S, words_per, h + 1 < num_hops);
+                RG_LAUNCH_CHECK(ctx, "k_bytes_count");
+            } else if (!self_count) {
+                k_tier_count<<<tier_blocks * ug, 256, 0, s>>>(S, words_per);
+                RG_LAUNCH_CHECK(ctx, "k_tier_count");
+                if (scanned) {
+                    k_scan_tier<<<ug, 1024, 0, s>>>(S, h, (int)tier_blocks, 0);
+                    RG_LAUNCH_CHECK(ctx, "k_scan_tier");
+                }
+            }
+            const bool count_next = h + 1 < num_hops && drawn_by_threads(h + 1);
+            const int next_fanout = count_next ? fanouts[h + 1] : -1;
+            unsigned emit_grid = tier_blocks * ug;
+            const int emit_run = count_next ? shared_run((int64_t)tier_blocks + rg_div_up(fub_max[h], kChunk), 1, emit_grid) : 0;
+            if (count_next) counted = h + 1;
+            if (self_count) {
+                uint8_t* next = h + 1 < num_hops ? (uint8_t*) bytes_at[(h + 1) & 1] : nullptr;
+                k_bytes_emit_small<<<emit_grid, kEmitThreadsSmall, 0, s>>>(row_ptr, S, h, tier_blocks, next_fanout, emit_run, members(h), members(h + 1), next);
+            } else {
+                if (small_tier) k_tier_emit_small<<<emit_grid, kEmitThreadsSmall, 0, s>>>(row_ptr, S, h, tier_blocks, next_fanout, emit_run, scanned);
+                else k_tier_emit<<<emit_grid, kTierWords / 3, 0, s>>>(row_ptr, S, h, tier_blocks, next_fanout, emit_run, scanned);
+            }
             RG_LAUNCH_CHECK(ctx, "k_tier_emit");
         }
         if (shared && (st = relabel(h, h)) != RG_OK) return st;

@@ -901,3 +901,45 @@ def test_mirrored_pulls_of_growing_calls(B):
             assert torch.equal(rows, wl.features[pipe.arena[b, :pipe.sizes[b]].long()]), f"batch {b}"
         assert int(pipe.stats[:, 2].sum()) == 0
     pipe.close()
+
+
+# Tiers from bytes: workgroups of 192 bitmap words, which count what is in front of their words up to 160,000 nodes and 12 MB of bytes (of 768
+# words where many batches make enough of those); hops that clear the other map for the next one; a hub that most edges name.
+@pytest.mark.parametrize("n,seeds,fanouts", [
+    (6143, [380, 383, 0], (32, 31)), (6145, [384, 1], (32, 5, 3)), (24_577, [1536] * 16, (25, 10)), (159_999, [3000], (10, 10, 10, 2)),
+    (160_000, [900, 0, 850], (25, 10)), (160_001, [900, 0, 850], (25, 10)), (150_000, [700] * 16, (20, 3)), (1_600_000, [90] * 16, (10, 5)), (4_194_304, [300, 299], (10, 5))])
+@pytest.mark.parametrize("captured", [False, True])
+def test_tiers_from_bytes(B, ctx, n, seeds, fanouts, captured):
+    log(f"[bytes] N={n} seeds={seeds} fanouts={fanouts} captured={captured}")
+    rng = np.random.default_rng(n)
+    deg = rng.integers(0, 60, n) * (rng.random(n) < min(1.0, 200_000 / n))
+    deg[[0, n - 1]] = 300
+    rp = np.concatenate([[0], np.cumsum(deg)])
+    ci = rng.integers(0, n, rp[-1]).astype(np.int32)
+    ci[rng.random(ci.size) < 0.3] = n - 1
+    csr = B.CsrGraph(torch.as_tensor(rp, device=DEV).to(torch.int32), _i32(ci))
+    ids = np.unique(np.concatenate([[0, n - 1], np.flatnonzero(deg)]))
+    outs = [B.BlockBuffers(n, ci.size, max(k, 1), fanouts, DEV) for k in seeds]
+    bufs = [torch.zeros(max(k, 1), dtype=torch.int32, device=DEV) for k in seeds]
+    run = lambda: ctx.sample_blocks_group(csr, [b[:k] for b, k in zip(bufs, seeds)], fanouts, 77, 1, outs)  # noqa: E731
+    for b, k in zip(bufs, seeds):
+        b[:k] = _i32(rng.permutation(ids)[:k])
+    run()
+    if captured:
+        torch.cuda.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph):
+            run()
+    for _ in range(3 if captured else 1):               # (replays with other seeds, and an eager call of its own seeds in front of each)
+        lists = [rng.permutation(ids)[:k].astype(np.int32) for k in seeds]
+        if captured:
+            run()
+        for b, x in zip(bufs, lists):
+            b[:x.size] = _i32(x)
+        if captured:
+            graph.replay()
+        else:
+            run()
+        for j, o in enumerate(outs):
+            orc = oracle.sample_blocks(rp, ci, lists[j], fanouts, 77, 1)
+            assert_batch_equal(HipBatch(o, len(fanouts)), orc, len(fanouts), f"batch {j}")
