@@ -690,27 +690,52 @@ __global__ void __launch_bounds__(1024) k_scan_tier(const SampleScratch S, int h
 
 // ---------------------------------------------------------------------------- per hop: draw + read
 // `marked` holds every id a batch has met so far: the frontier members (`visited`) plus the ids the current hop has
-// sampled.  One probe per sampled edge; the hop's new tier is marked & ~visited.
-__device__ __forceinline__ void rg_mark(int32_t u, uint32_t* __restrict__ marked) {
-    const uint32_t w = (uint32_t)u >> 5, bit = 1u << (u & 31);
-    if (marked[w] & bit) return;                      // a stale read only costs a redundant atomic
-    atomicOr(&marked[w], bit);
+// sampled.  One probe per sampled edge; the hop's new tier is marked & ~visited.  A stale probe only costs a redundant atomic.
+// The probes of a thread's U ids (those whose bit of `live` is set) are on their way together: one behind the other a draw of 8 ids a thread
+// waited for them twice as long as for its columns.
+template <int U>
+__device__ __forceinline__ void rg_mark(const int32_t (&u)[U], uint32_t live, uint32_t* __restrict__ marked) {
+    uint32_t old[U];
+#pragma unroll
+    for (int q = 0; q < U; ++q) old[q] = (live >> q) & 1u ? marked[(uint32_t)u[q] >> 5] : ~0u;
+#pragma unroll
+    for (int q = 0; q < U; ++q)
+        if (!((old[q] >> (u[q] & 31)) & 1u) && ((live >> q) & 1u)) atomicOr(&marked[(uint32_t)u[q] >> 5], 1u << (u[q] & 31));
 }
 
 // kTierBytes: a byte store, which waits for nothing, where an atomic on a word that many edges name waits for all of theirs.
 __device__ __forceinline__ void rg_mark_byte(const SampleScratch& S, int g, int32_t u) { rg_bytes(S, g)[u] = 1; }
 
-// First-seen order: instead of a bit, remember the first edge of the hop that names a node outside the frontier.
-__device__ __forceinline__ void rg_note_first_edge(int32_t u, int64_t e, const uint32_t* __restrict__ visited,
-                                                   int32_t* __restrict__ first_key) {
-    const uint32_t w = (uint32_t)u >> 5, bit = 1u << (u & 31);
-    if (visited[w] & bit) return;
-    const int32_t key = 0x7FFFFFFF - (int32_t)e;
-    if (first_key[u] >= key) return;                  // a stale read only costs a redundant atomic
-    atomicMax(&first_key[u], key);
+// First-seen order: instead of a bit, remember the first edge of the hop that names a node outside the frontier.  Edge of u[q]: e + q * step.
+template <int U>
+__device__ __forceinline__ void rg_note_first_edges(const int32_t (&u)[U], uint32_t live, int64_t e, int step, const uint32_t* __restrict__ visited,
+                                                    int32_t* __restrict__ first_key) {
+    uint32_t members[U];
+    int32_t old[U];
+#pragma unroll
+    for (int q = 0; q < U; ++q) {
+        members[q] = ~0u;
+        old[q] = 0;
+        if ((live >> q) & 1u) { members[q] = visited[(uint32_t)u[q] >> 5]; old[q] = first_key[u[q]]; }
+    }
+#pragma unroll
+    for (int q = 0; q < U; ++q) {
+        const int32_t key = 0x7FFFFFFF - (int32_t)(e + q * step);
+        if (!((members[q] >> (u[q] & 31)) & 1u) && old[q] < key && ((live >> q) & 1u)) atomicMax(&first_key[u[q]], key);
+    }
+}
+template <int MODE, int U>
+__device__ __forceinline__ void rg_note(const SampleScratch& S, int g, const int32_t (&u)[U], uint32_t live, int64_t e, int step) {
+    if (MODE == kTierFirstSeen) rg_note_first_edges<U>(u, live, e, step, S.visited + g * S.words, S.first_key + g * S.num_nodes);
+    if (MODE == kTierAtomic) rg_mark<U>(u, live, S.marked + g * S.words);
+    if (MODE == kTierBytes) {
+#pragma unroll
+        for (int q = 0; q < U; ++q)
+            if ((live >> q) & 1u) rg_mark_byte(S, g, u[q]);
+    }
 }
 
-// kTierAtomic: k_tier_emit adds to the next hop's sums, which the draw in front of it clears.
+// The tiers' emits add to the next hop's sums, which the draw in front of them clears (with slices k_slice_mark does).
 __device__ __forceinline__ void rg_clear_next_sum(const SampleScratch& S, int g, uint32_t hop, int64_t thread, int64_t threads) {
     int32_t* __restrict__ next_sum = S.hop_sum[(hop + 1) & 1] + g * S.chunk_stride;
     for (int64_t c = thread; c <= S.frontier_stride / kChunk; c += threads) next_sum[c] = 0;
@@ -732,11 +757,8 @@ __global__ void __launch_bounds__(RG_WAVE) k_hop_sample_wave(const int32_t* __re
     const int32_t* __restrict__ hop_sum = S.hop_sum[hop & 1] + g * S.chunk_stride;
     const int64_t* __restrict__ row_start = S.row_start + g * S.frontier_stride;
     const int32_t* __restrict__ row_deg = S.row_deg + g * S.frontier_stride;
-    const uint32_t* __restrict__ visited = S.visited + g * S.words;
-    uint32_t* __restrict__ marked = S.marked + g * S.words;
-    int32_t* __restrict__ first_key = MODE == kTierFirstSeen ? S.first_key + g * S.num_nodes : nullptr;
     const int lane = threadIdx.x;
-    if (MODE == kTierAtomic || MODE == kTierBytes) rg_clear_next_sum(S, g, hop, (int64_t)blk * RG_WAVE + lane, (int64_t)rg_blocks_per_batch(S) * RG_WAVE);
+    if (MODE != kTierSliced) rg_clear_next_sum(S, g, hop, (int64_t)blk * RG_WAVE + lane, (int64_t)rg_blocks_per_batch(S) * RG_WAVE);
     for (int64_t i = blk; i < n_h; i += rg_blocks_per_batch(S)) {
         const int32_t v = nodes[i];
         const int64_t start = row_start[i], deg = row_deg[i];
@@ -745,10 +767,9 @@ __global__ void __launch_bounds__(RG_WAVE) k_hop_sample_wave(const int32_t* __re
         if (lane == 0) indptr[i] = base;
         if (fanout < 0 || deg <= fanout) {             // whole row, CSR order
             for (int64_t t = lane; t < deg; t += RG_WAVE) {
-                const int32_t u = col_idx[start + t];
-                nbr[base + t] = u;
-                if (MODE == kTierFirstSeen) rg_note_first_edge(u, base + t, visited, first_key);
-                if (MODE == kTierAtomic) rg_mark(u, marked);
+                const int32_t u[1] = {col_idx[start + t]};
+                nbr[base + t] = u[0];
+                rg_note<MODE, 1>(S, g, u, 1u, base + t, 0);
             }
             continue;
         }
@@ -772,10 +793,9 @@ __global__ void __launch_bounds__(RG_WAVE) k_hop_sample_wave(const int32_t* __re
             __syncthreads();
         }
         for (int t = lane; t < k; t += RG_WAVE) {
-            const int32_t u = col_idx[start + (int64_t)chosen[t]];
-            nbr[base + t] = u;
-            if (MODE == kTierFirstSeen) rg_note_first_edge(u, base + t, visited, first_key);
-            if (MODE == kTierAtomic) rg_mark(u, marked);
+            const int32_t u[1] = {col_idx[start + (int64_t)chosen[t]]};
+            nbr[base + t] = u[0];
+            rg_note<MODE, 1>(S, g, u, 1u, base + t, 0);
         }
     }
 }
@@ -820,7 +840,7 @@ __global__ void __launch_bounds__(256) k_hop_sample_thread(const int32_t* __rest
     const int n_h = rg_tier_off(S, g)[hop + 1];
     int32_t* __restrict__ indptr = rg_hop_list(S, g, (int)hop, kIndptr);
     const int64_t first = (int64_t)blk * NODES;
-    if (MODE == kTierAtomic || MODE == kTierBytes) rg_clear_next_sum(S, g, hop, (int64_t)blk * 256 + threadIdx.x, (int64_t)rg_blocks_per_batch(S) * 256);
+    if (MODE != kTierSliced) rg_clear_next_sum(S, g, hop, (int64_t)blk * 256 + threadIdx.x, (int64_t)rg_blocks_per_batch(S) * 256);
     if (first >= n_h) {                                  // uniform per workgroup
         if (n_h == 0 && blk == 0 && threadIdx.x == 0) {
             indptr[0] = 0;
@@ -829,9 +849,6 @@ __global__ void __launch_bounds__(256) k_hop_sample_thread(const int32_t* __rest
         return;
     }
     int32_t* __restrict__ nbr = rg_hop_list(S, g, (int)hop, kNbr);
-    const uint32_t* __restrict__ visited = S.visited + g * S.words;
-    uint32_t* __restrict__ marked = S.marked + g * S.words;
-    int32_t* __restrict__ first_key = MODE == kTierFirstSeen ? S.first_key + g * S.num_nodes : nullptr;
     const int64_t i = first + threadIdx.x;
     const int k = fanout;
     const int n_here = (int)(n_h - first < NODES ? n_h - first : NODES);
@@ -887,15 +904,15 @@ __global__ void __launch_bounds__(256) k_hop_sample_thread(const int32_t* __rest
 #pragma unroll
         for (int q = 0; q < kDrawLoads; ++q)
             if (e0 + 256 * q < n_edges) u[q] = col_idx[staged[e0 + 256 * q]];
+        uint32_t live = 0u;
 #pragma unroll
         for (int q = 0; q < kDrawLoads; ++q) {
             const int e = e0 + 256 * q;
             if (e >= n_edges) break;
             nbr[base + e] = u[q];
-            if (MODE == kTierFirstSeen) rg_note_first_edge(u[q], base + e, visited, first_key);
-            if (MODE == kTierAtomic) rg_mark(u[q], marked);
-            if (MODE == kTierBytes) rg_mark_byte(S, g, u[q]);
+            live |= 1u << q;
         }
+        rg_note<MODE, kDrawLoads>(S, g, u, live, base + e0, 256);
     }
 }
 
@@ -917,7 +934,7 @@ __global__ void __launch_bounds__(256) k_hop_sample_lanes(const int32_t* __restr
     const int n_h = rg_tier_off(S, g)[hop + 1];
     int32_t* __restrict__ indptr = rg_hop_list(S, g, (int)hop, kIndptr);
     const int64_t first = (int64_t)blk * NODES;
-    if (MODE == kTierAtomic || MODE == kTierBytes) rg_clear_next_sum(S, g, hop, (int64_t)blk * 256 + threadIdx.x, (int64_t)rg_blocks_per_batch(S) * 256);
+    if (MODE != kTierSliced) rg_clear_next_sum(S, g, hop, (int64_t)blk * 256 + threadIdx.x, (int64_t)rg_blocks_per_batch(S) * 256);
     if (first >= n_h) {                                  // uniform per workgroup
         if (n_h == 0 && blk == 0 && threadIdx.x == 0) {
             indptr[0] = 0;
@@ -970,11 +987,9 @@ __global__ void __launch_bounds__(256) k_hop_sample_lanes(const int32_t* __restr
         }
     }
     if (lane >= m) return;
-    const int32_t u = col_idx[start + at];
-    rg_hop_list(S, g, (int)hop, kNbr)[off + lane] = u;
-    if (MODE == kTierFirstSeen) rg_note_first_edge(u, off + lane, S.visited + g * S.words, S.first_key + g * S.num_nodes);
-    if (MODE == kTierAtomic) rg_mark(u, S.marked + g * S.words);
-    if (MODE == kTierBytes) rg_mark_byte(S, g, u);
+    const int32_t u[1] = {col_idx[start + at]};
+    rg_hop_list(S, g, (int)hop, kNbr)[off + lane] = u[0];
+    rg_note<MODE, 1>(S, g, u, 1u, off + lane, 0);
 }
 
 // ---------------------------------------------------------------------------- per hop: new tier, sliced
@@ -1400,8 +1415,18 @@ __global__ void __launch_bounds__(kEmitThreadsSmall) k_bytes_emit_small(const Ro
 // compaction over the hop's edge list: counts per kEdgesPerBlock edges, the scan of k_scan_tier, then the emit below.
 constexpr int kEdgesPerBlock = 1024;   // 256 threads x 4 consecutive edges
 
-__device__ __forceinline__ bool rg_opens_node(const int32_t* __restrict__ nbr, const int32_t* __restrict__ first_key, int64_t e) {
-    return first_key[nbr[e]] == 0x7FFFFFFF - (int32_t)e;
+// Which of a thread's 4 edges from e0 on open a node; their ids.
+__device__ __forceinline__ uint32_t rg_opens_nodes(const int32_t* __restrict__ nbr, const int32_t* __restrict__ first_key, int64_t e0, int64_t n_edges,
+                                                   int32_t (&u)[4]) {
+    int32_t key[4];
+    uint32_t opens = 0u;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) u[q] = e0 + q < n_edges ? nbr[e0 + q] : -1;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) key[q] = u[q] >= 0 ? first_key[u[q]] : 0;                // (no edge has the key 0)
+#pragma unroll
+    for (int q = 0; q < 4; ++q) opens |= (uint32_t)(key[q] == 0x7FFFFFFF - (int32_t)(e0 + q)) << q;
+    return opens;
 }
 
 __global__ void __launch_bounds__(256) k_first_seen_count(const SampleScratch S, int hop) {
@@ -1413,11 +1438,8 @@ __global__ void __launch_bounds__(256) k_first_seen_count(const SampleScratch S,
     __shared__ int part[4];
     int64_t chunk = blk;
     do {                                                           // (a workgroup without an edge writes a zero)
-        const int64_t e0 = chunk * kEdgesPerBlock + threadIdx.x * 4;
-        int c = 0;
-#pragma unroll
-        for (int q = 0; q < 4; ++q)
-            if (e0 + q < n_edges) c += rg_opens_node(nbr, first_key, e0 + q);
+        int32_t u[4];
+        int c = __popc(rg_opens_nodes(nbr, first_key, chunk * kEdgesPerBlock + threadIdx.x * 4, n_edges, u));
         c = rg_wave_sum(c);
         __syncthreads();                                           // part[] of the chunk before has been read
         if (rg_lane() == 0) part[threadIdx.x >> 6] = c;
@@ -1427,45 +1449,84 @@ __global__ void __launch_bounds__(256) k_first_seen_count(const SampleScratch S,
     } while (chunk * kEdgesPerBlock < n_edges);
 }
 
+// The row of a new node for the next hop, read while the workgroup's other new nodes' are, and its edges, which the caller adds up.
+__device__ __forceinline__ int rg_put_row(const SampleScratch& S, int g, int at, int64_t start, int64_t deg, int next_fanout) {
+    S.row_start[g * S.frontier_stride + at] = start;
+    S.row_deg[g * S.frontier_stride + at] = (int32_t)deg;
+    return (int)(deg <= next_fanout ? deg : next_fanout);
+}
+
 // Appends the opened nodes behind the current frontier in edge order, records their positions, marks them visited
-// and clears their first-edge keys (the array is all-zero again when the hop is done).
-__global__ void __launch_bounds__(256) k_first_seen_emit(const SampleScratch S, int hop) {
-    __shared__ int smem[256 / RG_WAVE + 1];
+// and clears their first-edge keys (the array is all-zero again when the hop is done).  next_fanout >= 0: also the next hop's sizes, as in
+// rg_new_rows.  scanned: chunk_sum holds exclusive offsets, and the
+// tier's end is known; else every workgroup adds up the counts in front of its own.
+__global__ void __launch_bounds__(256) k_first_seen_emit(const RowPtr row_ptr, const SampleScratch S, int hop, int next_fanout, int scanned) {
+    constexpr int NW = 256 / RG_WAVE;
+    __shared__ int smem[NW + 1];
+    __shared__ int part[NW];
+    __shared__ int edges[2];
     const int g = rg_batch(S);
     const unsigned blk = rg_block(S);
+    const unsigned edge_blocks = rg_blocks_per_batch(S);
     const int32_t* __restrict__ nbr = rg_hop_list(S, g, (int)hop, kNbr);
     int32_t* __restrict__ first_key = S.first_key + g * S.num_nodes;
     uint32_t* __restrict__ visited = S.visited + g * S.words;
     int32_t* __restrict__ nodes = rg_nodes(S, g);
     int32_t* __restrict__ pos = S.pos + g * S.num_nodes;
-    const int64_t n_edges = rg_hop_list(S, g, (int)hop, kIndptr)[rg_tier_off(S, g)[hop + 1]];
-    for (int64_t chunk = blk; chunk * kEdgesPerBlock < n_edges; chunk += rg_blocks_per_batch(S)) {
+    const int32_t* __restrict__ chunk_sum = S.chunk_sum + g * S.chunk_stride;
+    int32_t* __restrict__ next_sum = S.hop_sum[(hop + 1) & 1] + g * S.chunk_stride;
+    const int n_h = rg_tier_off(S, g)[hop + 1];
+    const int64_t n_edges = rg_hop_list(S, g, (int)hop, kIndptr)[n_h];
+    if (!scanned && n_edges == 0 && blk == 0 && threadIdx.x == 0) rg_tier_off(S, g)[hop + 2] = n_h;
+    if (next_fanout >= 0)                                          // (the last workgroups are the ones that may have no edges)
+        for (int64_t chunk = edge_blocks - 1 - blk; chunk * kChunk < n_h; chunk += edge_blocks) rg_old_edges<256>(S, g, hop, (int)chunk, next_fanout);
+    int64_t added = 0;                                             // chunks whose counts are in `before`
+    int before = n_h;
+    for (int64_t chunk = blk; chunk * kEdgesPerBlock < n_edges; chunk += edge_blocks) {
+        int c = 0;
+        if (!scanned) {
+            for (int64_t b = added + threadIdx.x; b < chunk; b += 256) c += chunk_sum[b];
+            added = chunk;
+        } else if (threadIdx.x == 0) {
+            c = chunk_sum[chunk];
+            before = n_h;
+        }
+        c = rg_wave_sum(c);
+        __syncthreads();                                           // part[] and edges[] of the chunk before have been read
+        if (rg_lane() == 0) part[threadIdx.x >> 6] = c;
+        if (threadIdx.x < 2) edges[threadIdx.x] = 0;
         const int64_t e0 = chunk * kEdgesPerBlock + threadIdx.x * 4;
         int32_t u[4];
-        bool opens[4];
-        int c = 0;
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            opens[q] = false;
-            if (e0 + q < n_edges) {
-                u[q] = nbr[e0 + q];
-                opens[q] = first_key[u[q]] == 0x7FFFFFFF - (int32_t)(e0 + q);
-            }
-            c += opens[q];
-        }
+        const uint32_t opens = rg_opens_nodes(nbr, first_key, e0, n_edges, u);
         int total;
-        const int excl = rg_block_excl_scan<256 / RG_WAVE>(c, smem, &total);
+        const int excl = rg_block_excl_scan<NW>(__popc(opens), smem, &total);      // its barriers publish part[] and edges[]
+#pragma unroll
+        for (int q = 0; q < NW; ++q) before += part[q];
+        if (!scanned && threadIdx.x == 0 && (chunk + 1) * kEdgesPerBlock >= n_edges) rg_tier_off(S, g)[hop + 2] = before + total;
         if (total == 0) continue;                                         // uniform
-        int out = rg_tier_off(S, g)[hop + 1] + S.chunk_sum[g * S.chunk_stride + chunk] + excl;
+        int out = before + excl;
+        int64_t start[4], deg[4];
+        if (next_fanout >= 0) {
+            const auto rows = [&](auto* p) {
+#pragma unroll
+                for (int q = 0; q < 4; ++q)
+                    if ((opens >> q) & 1u) rg_row_extent(p, u[q], start[q], deg[q]);
+            };
+            if (row_ptr.wide) rows((const int64_t*)row_ptr.p); else rows((const int32_t*)row_ptr.p);
+        }
 #pragma unroll
         for (int q = 0; q < 4; ++q)
-            if (opens[q]) {
+            if ((opens >> q) & 1u) {
                 nodes[out] = u[q];
                 pos[u[q]] = out;
-                ++out;
                 atomicOr(&visited[(uint32_t)u[q] >> 5], 1u << (u[q] & 31));
                 first_key[u[q]] = 0;                  // only the opening edge's thread touches this entry now
+                if (next_fanout >= 0) atomicAdd(&edges[out / kChunk - before / kChunk], rg_put_row(S, g, out, start[q], deg[q], next_fanout));
+                ++out;
             }
+        if (next_fanout < 0) continue;
+        __syncthreads();
+        if (threadIdx.x < 2 && edges[threadIdx.x]) atomicAdd(&next_sum[before / kChunk + threadIdx.x], edges[threadIdx.x]);
     }
 }
 
@@ -1617,12 +1678,13 @@ __global__ void __launch_bounds__(1024) k_seen_count(const SampleScratch S, int 
     const int32_t* __restrict__ at = rg_hop_list(S, g, (int)hop, kNbrLocal);
     const int32_t* __restrict__ first_edge = S.first_edge + g * S.frontier_stride;
     int c = 0;
+    int32_t a[4], f[4];
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-        const int64_t e = first + q * 1024 + threadIdx.x;
-        const int32_t a = e < n ? at[e] : -1;
-        c += a >= n_h && first_edge[a] == (int32_t)e;
-    }
+    for (int q = 0; q < 4; ++q) a[q] = first + q * 1024 + threadIdx.x < n ? at[first + q * 1024 + threadIdx.x] : -1;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) f[q] = a[q] >= n_h ? first_edge[a[q]] : -1;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) c += f[q] == (int32_t)(first + q * 1024 + threadIdx.x);
     c = rg_wave_sum(c);
     if (rg_lane() == 0) part[threadIdx.x >> 6] = c;
     __syncthreads();
@@ -1651,14 +1713,16 @@ __global__ void __launch_bounds__(1024) k_seen_emit(const SampleScratch S, int h
     before = rg_wave_sum(before);
     if (rg_lane() == 0) part[threadIdx.x >> 6] = before;
     const int64_t e0 = first + threadIdx.x * 4;
-    int32_t a[4];
+    int32_t a[4], f[4];
     bool opens[4];
     int c = 0;
 #pragma unroll
     for (int q = 0; q < 4; ++q) a[q] = e0 + q < n ? at[e0 + q] : -1;
 #pragma unroll
+    for (int q = 0; q < 4; ++q) f[q] = a[q] >= n_h ? first_edge[a[q]] : -1;
+#pragma unroll
     for (int q = 0; q < 4; ++q) {
-        opens[q] = a[q] >= n_h && first_edge[a[q]] == (int32_t)(e0 + q);
+        opens[q] = f[q] == (int32_t)(e0 + q);
         c += opens[q];
     }
     int total;
@@ -2662,10 +2726,16 @@ rg_status rg_sample_blocks_group(rg_ctx* ctx, const rg_csr* csr, int32_t group, 
             const int fs_blocks = (int)rg_max64(1, rg_div_up(launch_edges(h), kEdgesPerBlock));
             k_first_seen_count<<<(unsigned)(fs_blocks) * ug, 256, 0, s>>>(S, h);
             RG_LAUNCH_CHECK(ctx, "k_first_seen_count");
-            // (the edges there are make one block per workgroup where it was launched for the bound; asking for them takes 1 us a hop)
-            k_scan_tier<<<ug, 1024, 0, s>>>(S, h, fs_blocks, launch_edges(h) < eub_max[h] ? kEdgesPerBlock : 0);
-            RG_LAUNCH_CHECK(ctx, "k_scan_tier");
-            k_first_seen_emit<<<(unsigned)(fs_blocks) * ug, 256, 0, s>>>(S, h);
+            // Adding up grows with the square of the chunks, a scan takes a launch.  (The edges there are make one chunk per workgroup where it was
+            // launched for the bound; asking for them takes 1 us a hop.)
+            const int scanned = rg_div_up(eub_max[h], kEdgesPerBlock) > kTierSelfScan;
+            if (scanned) {
+                k_scan_tier<<<ug, 1024, 0, s>>>(S, h, fs_blocks, launch_edges(h) < eub_max[h] ? kEdgesPerBlock : 0);
+                RG_LAUNCH_CHECK(ctx, "k_scan_tier");
+            }
+            const bool count_next = h + 1 < num_hops && drawn_by_threads(h + 1);
+            if (count_next) counted = h + 1;
+            k_first_seen_emit<<<(unsigned)(fs_blocks) * ug, 256, 0, s>>>(row_ptr, S, h, count_next ? fanouts[h + 1] : -1, scanned);
             RG_LAUNCH_CHECK(ctx, "k_first_seen_emit");
         } else {
             const int words_per = small_tier ? kTierWordsSmall : kTierWords, scanned = tier_blocks > kTierSelfScan;
