@@ -33,8 +33,11 @@ constexpr int kChunk = 1024;         // frontier nodes per workgroup in the coun
 // The edges of this line, and of the other lines between kernels, are those of nodes of average degree (rg_expected_edges), not the
 // static bound, which for RG_FANOUT_ALL is every edge of the graph: one batch of 16 seeds, all neighbours of one / two / three hops,
 // N = 10 M with 20 edges per node 39 / 67 / 116 us by the atomic way, 50 / 106 / 172 by slices.
-inline bool rg_use_slices(int slices, int64_t num_nodes, int64_t edges) {
-    return slices > 0 && (num_nodes <= (4ll << 20) || edges >= num_nodes / 16);
+// by_threads: every hop is drawn by threads or lanes.  Such calls of less than N / 16 edges take the atomic way from 512 Ki nodes on, where they
+// don't take bytes: eight batches of 19 k edges on 1.2 M nodes 50 / 58 us, on 2 M 52 / 61, of 9 k in three hops on 1.2 M 61 / 78, four of 38 k on
+// 1.5 M 50 / 60; up to N / 4 edges it would be 0.84 (one batch of 224 k on 3.4 M) to 1.9 times (eight of 264 k on 1.5 M).
+inline bool rg_use_slices(int slices, int64_t num_nodes, int64_t edges, bool by_threads) {
+    return slices > 0 && (num_nodes <= (by_threads ? 512ll << 10 : 4ll << 20) || edges >= num_nodes / 16);
 }
 // Edges per hop of a batch of `seeds` nodes whose degrees are the graph's average, eub[] at most; returns their sum.
 inline int64_t rg_expected_edges(int64_t num_nodes, int64_t num_edges, int64_t seeds, const int32_t* fanouts, int num_hops,
@@ -64,7 +67,7 @@ enum TierMode { kTierSliced = 0, kTierAtomic = 1, kTierFirstSeen = 2, kTierRanke
 // bound it above: 2 batches, N = 10 M, 8 M edges each 0.80-0.82, 16 M 0.85-1.12; N = 40 M 0.87 and 0.94-1.10.
 constexpr int64_t kRankedSeenMin = 2200 * 1000;
 inline bool rg_use_ranked_seen(int slices, int64_t num_nodes, int64_t edges, int group) {
-    return rg_use_slices(slices, num_nodes, edges) && group >= 2 && num_nodes * group * group >= 9000 * 1000 &&
+    return rg_use_slices(slices, num_nodes, edges, false) && group >= 2 && num_nodes * group * group >= 9000 * 1000 &&
            edges * group >= kRankedSeenMin && edges <= 2 * group * num_nodes;
 }
 constexpr int64_t kRankedSeenEdges = 8ll << 20;      // per hop and batch at most
@@ -2448,14 +2451,14 @@ rg_status rg_sample_blocks_group(rg_ctx* ctx, const rg_csr* csr, int32_t group, 
     for (int h = 0; h < num_hops; ++h) { edges_bound += eub_max[h]; frontiers_bound += fub_max[h]; }
     int64_t expected[RG_MAX_HOPS];
     const int64_t edges = rg_expected_edges(N, csr->num_edges, seeds_max, fanouts, num_hops, eub_max, expected);
+    bool by_threads = csr->num_edges < (1ll << 32);
+    for (int h = 0; h < num_hops; ++h) by_threads = by_threads && fanouts[h] >= 1 && fanouts[h] <= 32;
     // in first-seen order the edges' ascending positions are kept where their final ones go
     bool ranked_seen = first_seen && rg_use_ranked_seen(S.slices, N, edges, group);
     for (int g = 0; g < group && ranked_seen; ++g)
         for (int h = 0; h < num_hops; ++h)
             ranked_seen = ranked_seen && eub_max[h] <= kRankedSeenEdges && out[g].nbr_local && out[g].nbr_local[h] && out[g].nbr_local[h] != out[g].nbr[h];
-    bool by_threads = csr->num_edges < (1ll << 32);
-    for (int h = 0; h < num_hops; ++h) by_threads = by_threads && fanouts[h] >= 1 && fanouts[h] <= 32;
-    TierMode mode = ranked_seen ? kTierRankedSeen : first_seen ? kTierFirstSeen : (rg_use_slices(S.slices, N, edges) ? kTierSliced : kTierAtomic);
+    TierMode mode = ranked_seen ? kTierRankedSeen : first_seen ? kTierFirstSeen : (rg_use_slices(S.slices, N, edges, by_threads) ? kTierSliced : kTierAtomic);
     if (!first_seen && by_threads && rg_use_bytes(N, words, edges, group)) mode = kTierBytes;
     rg_status st = rg_sampler_reserve(ctx, N, fub_max[num_hops], group, max_edges, first_seen);
     if (st != RG_OK) return st;
