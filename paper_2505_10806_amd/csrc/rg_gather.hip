@@ -443,8 +443,8 @@ rg_status launch_copies(rg_ctx* ctx, const GatherScratch& scr, int64_t n, const 
     const bool do_hbm = parts & RG_GATHER_PART_HBM, do_miss = parts & RG_GATHER_PART_MISS;
     const bool two_streams = sm != sh && do_hbm && do_miss;      // one part alone: no fork, no join, the caller orders the streams
     if (two_streams) {
-        RG_HIP(ctx, hipEventRecord(ctx->ev_classified, sh));
-        RG_HIP(ctx, hipStreamWaitEvent(sm, ctx->ev_classified, 0));
+        const rg_status st = rg_stream_after(ctx, sm, sh, ctx->ev_classified);
+        if (st != RG_OK) return st;
     }
     const int vec = gather_vec(dim, cache, local_store, local_stride, remote_store, remote_stride, out, out_stride);
     const RgRowShape shp = rg_row_shape(dim, vec);
@@ -493,8 +493,8 @@ rg_status launch_copies(rg_ctx* ctx, const GatherScratch& scr, int64_t n, const 
         RG_LAUNCH_CHECK(ctx, "k_gather_miss");
     }
     if (two_streams) {
-        RG_HIP(ctx, hipEventRecord(ctx->ev_miss_done, sm));
-        RG_HIP(ctx, hipStreamWaitEvent(sh, ctx->ev_miss_done, 0));
+        const rg_status st = rg_stream_after(ctx, sh, sm, ctx->ev_miss_done);
+        if (st != RG_OK) return st;
     }
     return RG_OK;
 }
@@ -514,8 +514,8 @@ rg_status launch_fused(rg_ctx* ctx, const GatherScratch& scr, const int32_t* nod
                        const float* local_store, int64_t local_stride, const float* remote_store, int64_t remote_stride, int32_t dim,
                        float* out, int64_t out_stride, rg_gather_stats* stats, hipStream_t sh, hipStream_t sm, bool captured) {
     if (sm != sh) {
-        RG_HIP(ctx, hipEventRecord(ctx->ev_classified, sm));
-        RG_HIP(ctx, hipStreamWaitEvent(sh, ctx->ev_classified, 0));
+        const rg_status st = rg_stream_after(ctx, sh, sm, ctx->ev_classified);
+        if (st != RG_OK) return st;
     }
     const int vec = gather_vec(dim, cache, local_store, local_stride, remote_store, remote_stride, out, out_stride);
     const RgRowShape shp = rg_row_shape(dim, vec);
@@ -538,8 +538,8 @@ rg_status launch_fused(rg_ctx* ctx, const GatherScratch& scr, const int32_t* nod
 #undef RG_LAUNCH_FUSED
     RG_LAUNCH_CHECK(ctx, "k_gather_fused");
     if (sm != sh) {
-        RG_HIP(ctx, hipEventRecord(ctx->ev_miss_done, sh));
-        RG_HIP(ctx, hipStreamWaitEvent(sm, ctx->ev_miss_done, 0));
+        const rg_status st = rg_stream_after(ctx, sm, sh, ctx->ev_miss_done);
+        if (st != RG_OK) return st;
     }
     return RG_OK;
 }

@@ -15,6 +15,12 @@ struct RgBuf {
     size_t bytes = 0;
 };
 
+// Eight bytes that one stream writes and another waits for; `value` is what was last to be written.
+struct RgSignal {
+    uint64_t* at = nullptr;
+    uint64_t value = 0;
+};
+
 struct RgProfSpan {
     hipEvent_t start, stop;
     int kernel;
@@ -82,6 +88,9 @@ struct rg_ctx {
     int64_t gather_cap = 0;                                  // rows per ticket the buffers hold
     int64_t gather_rows[RG_GATHER_TICKETS] = {-1, -1, -1, -1, -1, -1, -1, -1};   // rows a ticket was prepared for (-1: none)
     hipEvent_t ev_classified = nullptr, ev_miss_done = nullptr;
+    RgSignal signals[128];             // of rg_stream_after, used in turn
+    uint64_t signal_value = 0;        // the last value that one of them was to be given
+    bool stream_values = false;       // the device waits for values in memory
     void* static_scratch = nullptr;   // device address of the library's file-scope gather scratch on ctx->device
     std::vector<hipStream_t> streams;   // streams made by rg_stream_create and not yet destroyed (rg_destroy takes the rest)
 
@@ -105,6 +114,8 @@ static inline bool rg_capturing(hipStream_t s) {
     if (hipStreamIsCapturing(s, &status) != hipSuccess) { (void)hipGetLastError(); return false; }
     return status == hipStreamCaptureStatusActive;
 }
+// What `later` is given from now on waits for what `earlier` has been given.  `event` is for calls that the streams' values cannot serve.
+rg_status rg_stream_after(rg_ctx* ctx, hipStream_t later, hipStream_t earlier, hipEvent_t event);
 // Scratch with which no epoch histogram on num_nodes nodes allocates anything; the same.
 rg_status rg_histogram_reserve(rg_ctx* ctx, int64_t num_nodes);
 // Makes every gather ticket hold at least `rows` rows (a reallocation invalidates prepared tickets).

@@ -943,3 +943,31 @@ def test_tiers_from_bytes(B, ctx, n, seeds, fanouts, captured):
         for j, o in enumerate(outs):
             orc = oracle.sample_blocks(rp, ci, lists[j], fanouts, 77, 1)
             assert_batch_equal(HipBatch(o, len(fanouts)), orc, len(fanouts), f"batch {j}")
+
+
+# One launch, and lookup and copies apart; more calls on their way than there are signals for the streams' order.
+@pytest.mark.parametrize("rows", [2000, 30_000])
+def test_two_stream_gathers_keep_their_place_in_both_streams(B, ctx, rows):
+    """The miss rows of a call come behind what the miss stream was given before it and in front of what either stream is given next."""
+    log(f"[order] rows={rows}")
+    dim, n, calls, side = 256, 40_000, 100, torch.cuda.Stream()
+    ids = torch.randperm(n, device=DEV, dtype=torch.int32)[:rows].contiguous()
+    cache = B.FeatureCache(n, 1, dim, DEV)
+    cache.loc.copy_(torch.where(torch.arange(n, device=DEV) % 4 == 0, torch.arange(n, device=DEV) // 4 - 2 ** 31, torch.arange(n, device=DEV)).int())
+    remote = torch.zeros(n // 4, dim, pin_memory=True)
+    local, out = torch.zeros(n, dim, device=DEV), torch.zeros(rows, dim, device=DEV)
+    stats, taken, source = torch.zeros(3, dtype=torch.int64, device=DEV), [], torch.zeros(n // 4, dim, device=DEV)
+    missing = (ids % 4 == 0).nonzero().flatten()
+    torch.cuda.synchronize()
+    for k in range(calls):
+        with torch.cuda.stream(side):                   # late, and only for this call
+            torch.cuda._sleep(20_000)
+            remote.copy_(source.fill_(k + 1), non_blocking=True)
+        ctx.gather_features(ids, rows, cache, local, remote, dim, out, stats, miss_stream=side)
+        with torch.cuda.stream(side):
+            remote.copy_(source.fill_(-1), non_blocking=True)
+        taken.append(out[missing].amin().reshape(1))
+        taken.append(out[missing].amax().reshape(1))
+    got = torch.cat(taken).reshape(calls, 2).cpu()
+    assert torch.equal(got, torch.arange(1, calls + 1, dtype=torch.float32).reshape(-1, 1).expand(-1, 2)), got.flatten().tolist()
+    assert stats.cpu().tolist() == [rows - missing.numel(), 0, missing.numel()]
