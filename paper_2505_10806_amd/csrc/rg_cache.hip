@@ -35,15 +35,42 @@ constexpr int kHistRunTile = 1024;     // runs whose bounds are in LDS at a time
 // and 54 / 52, 344 65 / 65 and 65 / 63; 412 57 / 53, 481 111 / 95, 584 125 / 102, 651 56 / 54 to 74 / 67, 704 141 / 113, 1100 63 / 57.
 constexpr int kHistAhead = 384;
 
+// Seeds of batch b, by blocks of 256 threads, `block` of `blocks`.  They are in caller order (not sorted): one global atomic each.
+__device__ __forceinline__ void rg_count_seeds(const int32_t* __restrict__ nodes, int64_t batch_stride, const int32_t* __restrict__ tier_off,
+                                               int num_hops, int b, int block, int blocks, uint32_t* __restrict__ counts,
+                                               uint32_t* __restrict__ first_batch) {
+    const int n_seeds = tier_off[(int64_t)b * (num_hops + 2) + 1];
+    const int32_t* base = nodes + (int64_t)b * batch_stride;
+    for (int i = block * 256 + threadIdx.x; i < n_seeds; i += blocks * 256) {
+        atomicAdd(&counts[base[i]], 1u);
+        if (first_batch) atomicMin(&first_batch[base[i]], (uint32_t)b);
+    }
+}
+
+__global__ void __launch_bounds__(256) k_histogram_seeds(const int32_t* __restrict__ nodes, int64_t batch_stride,
+                                                         const int32_t* __restrict__ tier_off, int num_hops,
+                                                         uint32_t* __restrict__ counts, uint32_t* __restrict__ first_batch) {
+    rg_count_seeds(nodes, batch_stride, tier_off, num_hops, blockIdx.y, blockIdx.x, gridDim.x, counts, first_batch);
+}
+
+constexpr int kSeedsBeside = 256;      // seeds per batch from which on k_hist_bounds counts them
+
 // bounds[r * (ranges + 1) + j] = first entry of run r with an id >= j * range, as an index into the batch's list.  Consecutive
 // threads search one run for consecutive keys.  Bound by the lines the probes touch: ids sampled at random lie within a few
 // sqrt(len) / 2 entries of their proportional place and a correction from there ends a few entries away, so about four lines
 // per bound instead of the ten or more a bisection reads (any other run of ids only takes more steps): 295 k bounds in runs
 // of up to 283 k entries 19 us, with a bisection of the 4 sqrt(len) entries around the proportional place 41.
+// seed_batches: the first workgroups count the seeds of so many batches meanwhile, whose atomics wait for memory where the searches wait for
+// their probes: 192 batches of 1024 seeds, 393 k atomics, beside the 295 k bounds 29.6 us, in launches of their own 17.5 + 19.
 __global__ void __launch_bounds__(256) k_hist_bounds(const int32_t* __restrict__ nodes, int64_t batch_stride,
                                                      const int32_t* __restrict__ tier_off, int num_hops, int64_t num_nodes, int range,
-                                                     int ranges, int32_t* __restrict__ bounds) {
-    const int r = blockIdx.y;
+                                                     int ranges, int32_t* __restrict__ bounds, int seed_batches,
+                                                     uint32_t* __restrict__ counts, uint32_t* __restrict__ first_batch) {
+    const int r = (int)blockIdx.y - seed_batches;
+    if (r < 0) {
+        rg_count_seeds(nodes, batch_stride, tier_off, num_hops, blockIdx.y, blockIdx.x, gridDim.x, counts, first_batch);
+        return;
+    }
     const int j = blockIdx.x * 256 + threadIdx.x;
     if (j > ranges) return;
     const int b = r / num_hops, t = r % num_hops + 1;                  // tier t of batch b
@@ -232,24 +259,11 @@ __global__ void __launch_bounds__(1024) k_histogram_runs(const int32_t* __restri
     }
 }
 
-// Seeds are in caller order (not sorted): one global atomic each.
-__global__ void __launch_bounds__(256) k_histogram_seeds(const int32_t* __restrict__ nodes, int64_t batch_stride,
-                                                         const int32_t* __restrict__ tier_off, int num_hops,
-                                                         uint32_t* __restrict__ counts, uint32_t* __restrict__ first_batch) {
-    const int b = blockIdx.y;
-    const int n_seeds = tier_off[(int64_t)b * (num_hops + 2) + 1];
-    const int32_t* base = nodes + (int64_t)b * batch_stride;
-    for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n_seeds; i += gridDim.x * blockDim.x) {
-        atomicAdd(&counts[base[i]], 1u);
-        if (first_batch) atomicMin(&first_batch[base[i]], (uint32_t)b);
-    }
-}
-
 // ---------------------------------------------------------------------------- threshold select
 // Finds the count threshold T of the K_eff-th best candidate.  Access counts are bounded by the number of batches of
 // the period (a few hundred), so one streaming pass with a histogram of the counts clamped to kLowBins - 1 resolves T
 // whenever T < kLowBins - 1, and its last workgroup says so.  Only when the K_eff-th best candidate sits in the clamped last bin do
-// the three passes of a most-significant-digit-first radix select (11 + 11 + 10 bits) run; otherwise their kernels return at once.
+// the passes of a most-significant-digit-first radix select (11 + 11 + 10 bits, the first of them by the streaming pass) run; otherwise their kernels return at once.
 // What they find stays in TopkCtl and is read off there by the kernels up to the count (rg_topk_state).
 // Bound by launches: with four passes of 8 bits, every kernel working out the state from the bins for itself and the bins cleared by a
 // launch in front, selection at 2.4 M nodes took 60 us, now 37 (at 10 M nodes 107, now 70; at 40 M 362, now 239).  The emit clears them for the next call.
@@ -286,8 +300,8 @@ __device__ __forceinline__ bool rg_is_candidate(uint32_t home_word, uint32_t cou
 
 __global__ void __launch_bounds__(256) k_topk_init(TopkCtl* __restrict__ ctl, int hist_only) {
     uint32_t* w = (uint32_t*)ctl;
-    const int n = hist_only ? (int)(sizeof(ctl->hist) / 4) : kCtlClear;              // hist_only: a later selection of the hit curve
-    for (int i = blockIdx.x * 256 + threadIdx.x; i < n; i += gridDim.x * 256) w[i] = 0u;
+    const int n = hist_only ? (int)(sizeof(ctl->hist) / 4) : kCtlClear;              // hist_only: a later selection of the hit curve, the same first digits
+    for (int i = (hist_only ? kRadixBins : 0) + blockIdx.x * 256 + threadIdx.x; i < n; i += gridDim.x * 256) w[i] = 0u;
 }
 
 // The bin of one of 2048 that holds the need-th best, bins in descending order, `n` of them in bin h[j] of this thread
@@ -364,16 +378,17 @@ __device__ __forceinline__ void rg_load4(const void* __restrict__ p, int64_t i, 
     }
 }
 
-// low[min(count, kLowBins - 1)] += 1 for every candidate; ovf_sum += count for those in the last bin.  One workgroup per
+// low[min(count, kLowBins - 1)] += 1 for every candidate; ovf_sum += count for those in the last bin, and the histogram of their first
+// digits, with which the radix select begins where the threshold is one of them.  One workgroup per
 // compute unit: with more of them their additions to the same few bins queue up (1196 workgroups 38 us at 2.4 M nodes).  Above
 // 8 Mi nodes two, which read faster: the selection at 10 M nodes 110 -> 104 us, at 40 M 412 -> 364, at 100 M 972 -> 858.
 __global__ void __launch_bounds__(1024) k_topk_hist_low(const uint32_t* __restrict__ counts, const int32_t* __restrict__ home, int64_t n,
                                                         TopkCtl* ctl, int64_t capacity) {
     constexpr int U = 4;
-    __shared__ uint32_t h[kLowBins];
+    __shared__ uint32_t h[kLowBins], top[kRadixBins];
     __shared__ int last_s;
     __shared__ unsigned long long ovf_s;
-    for (int i = threadIdx.x; i < kLowBins; i += 1024) h[i] = 0u;
+    for (int i = threadIdx.x; i < kLowBins; i += 1024) h[i] = top[i] = 0u;
     if (threadIdx.x == 0) ovf_s = 0ull;
     __syncthreads();
     unsigned long long ovf = 0ull;
@@ -387,7 +402,10 @@ __global__ void __launch_bounds__(1024) k_topk_hist_low(const uint32_t* __restri
             uint32_t bin = 0u;                               // bin 0: not a candidate
             if (rg_is_candidate(hw[u], c[u])) {
                 bin = c[u] < (uint32_t)(kLowBins - 1) ? c[u] : (uint32_t)(kLowBins - 1);
-                if (c[u] >= (uint32_t)(kLowBins - 1)) ovf += c[u];
+                if (c[u] >= (uint32_t)(kLowBins - 1)) {
+                    ovf += c[u];
+                    atomicAdd(&top[rg_radix_digit(c[u], 0)], 1u);
+                }
             }
             // most candidates of a long-tailed distribution have a count of 1..4: one LDS atomic per wavefront for each
 #pragma unroll
@@ -409,6 +427,9 @@ __global__ void __launch_bounds__(1024) k_topk_hist_low(const uint32_t* __restri
         if (mine) { const uint32_t old = atomicAdd(&ctl->low[i], mine); asm volatile("" :: "v"(old) : "memory"); }
     }
     if (threadIdx.x == 0 && ovf_s) atomicAdd(&ctl->ovf_sum, ovf_s);
+    if (ovf_s)                                               // uniform; read by launches behind this one
+        for (int i = threadIdx.x; i < kRadixBins; i += 1024)
+            if (top[i]) atomicAdd(&ctl->hist[0][i], top[i]);
     if (capacity < 0) return;                                             // the hit curve looks its capacities up itself
     __syncthreads();                                                      // every addition of this workgroup is made
     if (threadIdx.x == 0) last_s = atomicAdd(&ctl->done, 1u) == gridDim.x - 1;
@@ -418,7 +439,7 @@ __global__ void __launch_bounds__(1024) k_topk_hist_low(const uint32_t* __restri
     if (threadIdx.x == 0) ctl->low_state = st;
 }
 
-// Histogram of digit `pass` (0 = most significant) of the counts of candidates that match the digits in front.  skip: of the hit curve, a
+// Histogram of digit `pass` (1 or 2; 0, the most significant, is k_topk_hist_low's) of the counts of candidates that match the digits in front.  skip: of the hit curve, a
 // flag that, when set, says that nobody asks for it; NULL: the low state is there.
 __global__ void __launch_bounds__(1024) k_topk_hist(const uint32_t* __restrict__ counts, const int32_t* __restrict__ home, int64_t n,
                                                    int pass, int64_t capacity, TopkCtl* ctl, const uint32_t* __restrict__ skip) {
@@ -876,8 +897,11 @@ __device__ __forceinline__ int rg_plan_key(const uint32_t* __restrict__ first_ba
 }
 
 // hist[key * nblocks + blk] = number of slots of chunk blk first used by batch `key`, for the chunks in use.
+// by_chunk: hist[blk * keys + key] instead, which k_plan_block_scatter adds up itself: with few chunks that takes less than a launch that
+// scans them (5 k to 49 k slots, 20 to 400 batches: a call 11.6 us instead of 14.6; the reads of 48 chunks take as long as that launch).
+constexpr int kPlanFewChunks = 48;
 __global__ void __launch_bounds__(1024) k_plan_block_hist(const int32_t* __restrict__ cache_ids, const int64_t* __restrict__ num_cached,
-                                                          const uint32_t* __restrict__ first_batch, int num_batches, int nblocks,
+                                                          const uint32_t* __restrict__ first_batch, int num_batches, int nblocks, int by_chunk,
                                                           int32_t* __restrict__ hist) {
     __shared__ int h[1024];
     const int64_t k = *num_cached;
@@ -888,7 +912,7 @@ __global__ void __launch_bounds__(1024) k_plan_block_hist(const int32_t* __restr
     const int64_t s = (int64_t)blockIdx.x * kPlanChunk + threadIdx.x;
     if (s < k) atomicAdd(&h[rg_plan_key(first_batch, cache_ids[s], num_batches)], 1);
     __syncthreads();
-    if ((int)threadIdx.x < n_seg) hist[(int64_t)threadIdx.x * nblocks + blockIdx.x] = h[threadIdx.x];
+    if ((int)threadIdx.x < n_seg) hist[by_chunk ? (int64_t)blockIdx.x * n_seg + threadIdx.x : (int64_t)threadIdx.x * nblocks + blockIdx.x] = h[threadIdx.x];
 }
 
 // One workgroup per key: in-place exclusive scan of the key's chunks, its total to total[key].  (One workgroup for all keys
@@ -915,7 +939,7 @@ __global__ void __launch_bounds__(256) k_plan_row_scan(const int64_t* __restrict
 // meet in LDS.  (One thread per key walking the chunk's keys took 169 us for 367 k slots, 193 keys; now 13.)
 __global__ void __launch_bounds__(kPlanChunk) k_plan_block_scatter(const int32_t* __restrict__ cache_ids, const int64_t* __restrict__ num_cached,
                                                                    const uint32_t* __restrict__ first_batch, const int32_t* __restrict__ home,
-                                                                   int num_batches, int nblocks, const int32_t* __restrict__ hist,
+                                                                   int num_batches, int nblocks, int by_chunk, const int32_t* __restrict__ hist,
                                                                    const int32_t* __restrict__ total, int32_t* __restrict__ offsets,
                                                                    int32_t* __restrict__ list) {
     constexpr int NW = kPlanChunk / RG_WAVE;
@@ -931,11 +955,24 @@ __global__ void __launch_bounds__(kPlanChunk) k_plan_block_scatter(const int32_t
     const int32_t v = s < k ? cache_ids[s] : 0;
     const int key = s < k ? rg_plan_key(first_batch, v, num_batches) : 1 << kPlanKeyBits;   // no key: matches only its like
     const int32_t row = s < k ? (int32_t)((uint32_t)home[v] & RG_ROW_MASK) : 0;
-    int sum;
-    const int mine = (int)threadIdx.x < n_seg ? total[threadIdx.x] : 0;
+    int sum, mine = 0, earlier = 0;                                   // of this thread's key: all slots, those of earlier chunks
+    if ((int)threadIdx.x < n_seg) {
+        if (by_chunk) {
+            const int used = rg_plan_chunks(k, nblocks);
+#pragma unroll 8
+            for (int b = 0; b < used; ++b) {
+                const int x = hist[b * n_seg + threadIdx.x];
+                mine += x;
+                earlier += b < (int)blockIdx.x ? x : 0;
+            }
+        } else {
+            mine = total[threadIdx.x];
+            earlier = hist[(int64_t)threadIdx.x * nblocks + blockIdx.x];
+        }
+    }
     const int before = rg_block_excl_scan<NW>(mine, smem, &sum);      // its barriers also end the clearing of cnt
     if ((int)threadIdx.x < n_seg) {
-        key_base[threadIdx.x] = before + hist[(int64_t)threadIdx.x * nblocks + blockIdx.x];
+        key_base[threadIdx.x] = before + earlier;
         if (blockIdx.x == 0) offsets[threadIdx.x] = before;
     }
     if (blockIdx.x == 0 && threadIdx.x == 0) offsets[n_seg] = sum;
@@ -1188,14 +1225,16 @@ rg_status rg_access_histogram_epoch(rg_ctx* ctx, const int32_t* nodes, int64_t b
     // 0.52-0.56 / 0.42-0.47); on 100 M nodes, 56 to a launch, 1.2-2.0 ms either way.
     const int64_t wanted = per_batch * (ctx->hist_reserved ? rg_min64(most, 128) : most);
     if (!few && (int64_t)(ctx->hist_bounds.bytes / 4) < wanted && !rg_capturing(s)) (void)hist_bounds_grow(ctx, wanted);
-    const int fit = (int)rg_min64((int64_t)(ctx->hist_bounds.bytes / 4) / per_batch, 65535 / num_hops);
+    const int fit = (int)rg_min64((int64_t)(ctx->hist_bounds.bytes / 4) / per_batch, 65535 / (num_hops + 1));
     const bool search = few || fit == 0 || (fit < 48 && num_batches > 2 * fit);
     const int step = search ? num_batches : fit;
     int32_t* bounds = search ? nullptr : (int32_t*)ctx->hist_bounds.p;
     const RunStep by = {16 / num_hops, 16 % num_hops, kHistRunTile / num_hops, kHistRunTile % num_hops};
     const bool ahead = run_len >= (int64_t)kHistAhead * ranges;
     const int tok = rg_prof_begin(ctx, RG_K_HISTOGRAM, s);
-    if (max_seeds > 0) {
+    // Batches of a workgroup's seeds or more are counted beside the bounds.
+    const bool beside = bounds && max_seeds >= kSeedsBeside && num_batches <= fit;
+    if (max_seeds > 0 && !beside) {
         dim3 seed_grid((unsigned)rg_min64(rg_div_up(max_seeds, 256), 64), (unsigned)num_batches);
         k_histogram_seeds<<<seed_grid, 256, 0, s>>>(nodes, batch_stride, tier_off, num_hops, counts, first_batch);
     }
@@ -1204,8 +1243,8 @@ rg_status rg_access_histogram_epoch(rg_ctx* ctx, const int32_t* nodes, int64_t b
         const int32_t* list = nodes + (int64_t)b0 * batch_stride;
         const int32_t* tiers = tier_off + (int64_t)b0 * (num_hops + 2);
         if (bounds)
-            k_hist_bounds<<<dim3((unsigned)rg_div_up(ranges + 1, 256), (unsigned)(nb * num_hops)), 256, 0, s>>>(
-                list, batch_stride, tiers, num_hops, num_nodes, range, ranges, bounds);
+            k_hist_bounds<<<dim3((unsigned)rg_div_up(ranges + 1, 256), (unsigned)(nb * num_hops + (beside ? nb : 0))), 256, 0, s>>>(
+                list, batch_stride, tiers, num_hops, num_nodes, range, ranges, bounds, beside ? nb : 0, counts, first_batch);
 #define RG_LAUNCH_RUNS(FIRST, AHEAD)                                                                                      \
     k_histogram_runs<FIRST, AHEAD><<<ranges, 1024, 0, s>>>(list, batch_stride, tiers, bounds, nb, num_hops, b0, counts, first_batch, num_nodes, range, by)
         if (first_batch) { if (ahead) RG_LAUNCH_RUNS(true, true); else RG_LAUNCH_RUNS(true, false); }
@@ -1263,7 +1302,7 @@ rg_status rg_build_cache(rg_ctx* ctx, const uint32_t* counts, const int32_t* hom
     k_topk_hist_low<<<low_grid, 1024, 0, s>>>(counts, home, num_nodes, ctl, cache->capacity_rows);
     RG_LAUNCH_CHECK(ctx, "k_topk_hist_low");
     const int hist_grid = (int)rg_max64(1, rg_min64(rg_div_up(num_nodes, 1024 * 8), (int64_t)ctx->num_cus * 2));
-    for (int pass = 0; pass < kRadixPasses; ++pass) {        // return at once unless the threshold is in the clamped bin
+    for (int pass = 1; pass < kRadixPasses; ++pass) {        // return at once unless the threshold is in the clamped bin
         k_topk_hist<<<hist_grid, 1024, 0, s>>>(counts, home, num_nodes, pass, cache->capacity_rows, ctl, nullptr);
         RG_LAUNCH_CHECK(ctx, "k_topk_hist");
     }
@@ -1349,7 +1388,7 @@ rg_status rg_cache_hit_curve(rg_ctx* ctx, const uint32_t* counts, const int32_t*
             k_topk_init<<<4, 256, 0, s>>>(ctl, 1);
             RG_LAUNCH_CHECK(ctx, "k_topk_init");
         }
-        for (int pass = 0; pass < kRadixPasses; ++pass) {
+        for (int pass = 1; pass < kRadixPasses; ++pass) {
             k_topk_hist<<<hist_grid, 1024, 0, s>>>(counts, home, num_nodes, pass, capacities[j], ctl, resolved + j);
             RG_LAUNCH_CHECK(ctx, "k_topk_hist");
         }
@@ -1413,17 +1452,20 @@ rg_status rg_plan_prefetch(rg_ctx* ctx, const rg_cache* cache, const int32_t* ho
         if ((st = rg_ensure(ctx, ctx->plan_cursor, (size_t)(n_hist + n_seg) * 4)) != RG_OK) return st;
         int32_t* hist = (int32_t*)ctx->plan_cursor.p;
         int32_t* total = hist + n_hist;
+        const int by_chunk = nblocks <= kPlanFewChunks;
         if (rows_ub == 0) {
             k_zero_i32<<<(n_seg + 1 + 255) / 256, 256, 0, s>>>(plan->offsets, n_seg + 1);
             RG_LAUNCH_CHECK(ctx, "k_zero_i32");
             return RG_OK;
         }
-        k_plan_block_hist<<<nblocks, 1024, 0, s>>>(cache->cache_ids, cache->num_cached, first_batch, plan->num_batches, nblocks, hist);
+        k_plan_block_hist<<<nblocks, 1024, 0, s>>>(cache->cache_ids, cache->num_cached, first_batch, plan->num_batches, nblocks, by_chunk, hist);
         RG_LAUNCH_CHECK(ctx, "k_plan_block_hist");
-        k_plan_row_scan<<<n_seg, 256, 0, s>>>(cache->num_cached, hist, nblocks, total);
-        RG_LAUNCH_CHECK(ctx, "k_plan_row_scan");
+        if (!by_chunk) {
+            k_plan_row_scan<<<n_seg, 256, 0, s>>>(cache->num_cached, hist, nblocks, total);
+            RG_LAUNCH_CHECK(ctx, "k_plan_row_scan");
+        }
         k_plan_block_scatter<<<nblocks, kPlanChunk, 0, s>>>(cache->cache_ids, cache->num_cached, first_batch, home, plan->num_batches,
-                                                            nblocks, hist, total, plan->offsets, plan->list);
+                                                            nblocks, by_chunk, hist, total, plan->offsets, plan->list);
         RG_LAUNCH_CHECK(ctx, "k_plan_block_scatter");
         return RG_OK;
     }
