@@ -1003,47 +1003,61 @@ __global__ void __launch_bounds__(kPlanChunk) k_plan_block_scatter(const int32_t
 // group is the first to name are the new bits of their union against `claimed` (all nodes any earlier group named)
 // whose home is the remote store: two streaming passes over N/32 words and one home[] lookup per new node, instead of
 // one lookup and one probe per input node of every batch.  The pairs come out ascending by node id, i.e. by remote row.
-constexpr int kClaimWordsPerBlock = 1024;   // 256 threads x 4 words
+// A workgroup takes kClaimWords words; a wavefront asks for the home words of two of them at a time, a lane per id, kClaimPairs steps
+// together.  (With a thread per word, which asked for one id after the other, a call that names most nodes waited 32 times in a row: eight
+// batches of 4096 seeds (15,10,5) on 1 M nodes 75 us, now 16; on 10 M 92 / 35.)
+constexpr int kClaimWords = 256, kClaimPairs = 8;
+constexpr int kClaimSelfScan = 4096;        // workgroups up to which the emit adds up the counts in front of its own itself
+static_assert(kClaimWords == 256 && kClaimWords / 2 % (4 * kClaimPairs) == 0, "a thread per word, whole steps of the four wavefronts");
 
-__device__ __forceinline__ int rg_count_remote(uint32_t bits, int64_t word, const int32_t* __restrict__ home) {
-    int c = 0;
-    while (bits) {
-        const int j = __ffs(bits) - 1;
-        bits &= bits - 1u;
-        c += ((uint32_t)home[(word << 5) + j] >> RG_TAG_SHIFT) == RG_TAG_REMOTE;
+// f(pair, lane's id, lane's bit, its home word) for the pairs of words of the workgroup that this wavefront takes.
+template <typename F>
+__device__ __forceinline__ void rg_claim_pairs(const uint32_t* bits, int64_t w0, const int32_t* __restrict__ home, F f) {
+    const int lane = rg_lane();
+    for (int p0 = (threadIdx.x >> 6) * (kClaimWords / 8); p0 < ((int)(threadIdx.x >> 6) + 1) * (kClaimWords / 8); p0 += kClaimPairs) {
+        uint32_t hw[kClaimPairs];
+        bool set[kClaimPairs];
+#pragma unroll
+        for (int q = 0; q < kClaimPairs; ++q) {
+            set[q] = (bits[2 * (p0 + q) + (lane >> 5)] >> (lane & 31)) & 1u;
+            hw[q] = set[q] ? (uint32_t)home[((w0 + 2 * (p0 + q)) << 5) + lane] : 0u;
+        }
+#pragma unroll
+        for (int q = 0; q < kClaimPairs; ++q) f(p0 + q, lane, set[q], hw[q]);
     }
-    return c;
 }
 
+// newbits = the ids that this group is the first to name and whose home is the remote store; their number per workgroup.
 __global__ void __launch_bounds__(256) k_claim_count(const uint32_t* __restrict__ visited, int64_t words, int group,
                                                      uint32_t* __restrict__ claimed, uint32_t* __restrict__ newbits,
                                                      const int32_t* __restrict__ home, int32_t* __restrict__ blk_count) {
-    const int64_t w0 = (int64_t)blockIdx.x * kClaimWordsPerBlock + threadIdx.x * 4;
-    int c = 0;
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-        const int64_t w = w0 + q;
-        if (w >= words) break;
+    __shared__ uint32_t bits[kClaimWords];
+    __shared__ int part[4];
+    const int64_t w0 = (int64_t)blockIdx.x * kClaimWords, w = w0 + threadIdx.x;
+    uint32_t nw = 0u;
+    if (w < words) {
         uint32_t u = 0u;
         for (int g = 0; g < group; ++g) u |= visited[g * words + w];
         const uint32_t old = claimed[w];
-        const uint32_t nw = u & ~old;
-        newbits[w] = nw;
-        if (nw) {
-            claimed[w] = old | nw;
-            c += rg_count_remote(nw, w, home);
-        }
+        nw = u & ~old;
+        if (nw) claimed[w] = old | nw;
     }
-    c = rg_wave_sum(c);
-    __shared__ int part[4];
+    bits[threadIdx.x] = nw;
+    __syncthreads();
+    int c = 0;
+    rg_claim_pairs(bits, w0, home, [&](int pair, int lane, bool set, uint32_t hw) {
+        const unsigned long long m = __ballot(set && (hw >> RG_TAG_SHIFT) == RG_TAG_REMOTE);
+        if (lane < 2) bits[2 * pair + lane] = (uint32_t)(m >> (32 * lane));            // (this wavefront's own words)
+        c += __popcll(m);
+    });
     if (rg_lane() == 0) part[threadIdx.x >> 6] = c;
     __syncthreads();
+    if (w < words) newbits[w] = bits[threadIdx.x];
     if (threadIdx.x == 0) blk_count[blockIdx.x] = part[0] + part[1] + part[2] + part[3];
 }
 
-// One workgroup: block counts -> exclusive offsets; the segment's end goes behind its start in the plan's offsets.
-__global__ void __launch_bounds__(1024) k_claim_scan(int32_t* __restrict__ blk_count, int nblocks, int32_t* __restrict__ seg_off,
-                                                     int64_t list_capacity) {
+// One workgroup: block counts -> exclusive offsets, their sum behind them.
+__global__ void __launch_bounds__(1024) k_claim_scan(int32_t* __restrict__ blk_count, int nblocks) {
     __shared__ int smem[1024 / RG_WAVE + 1];
     __shared__ int carry_s;
     if (threadIdx.x == 0) carry_s = 0;
@@ -1059,46 +1073,50 @@ __global__ void __launch_bounds__(1024) k_claim_scan(int32_t* __restrict__ blk_c
         if (threadIdx.x == 0) carry_s = carry + total;
         __syncthreads();
     }
-    if (threadIdx.x == 0) {
-        // a list that cannot take the segment (it holds one pair per remote row, so this means a caller error) gets an
-        // empty segment instead of an overrun
-        const int64_t end = (int64_t)seg_off[0] + carry_s;
-        seg_off[1] = end <= list_capacity ? (int32_t)end : seg_off[0];
-    }
+    if (threadIdx.x == 0) blk_count[nblocks] = carry_s;
 }
 
+// The pairs, ascending; the segment's end goes behind its start in the plan's offsets.  scanned: blk_count is k_claim_scan's.
 __global__ void __launch_bounds__(256) k_claim_emit(const uint32_t* __restrict__ newbits, int64_t words, const int32_t* __restrict__ home,
-                                                    const int32_t* __restrict__ blk_off, const int32_t* __restrict__ seg_off,
-                                                    int32_t* __restrict__ list) {
+                                                    const int32_t* __restrict__ blk_count, int scanned, int32_t* __restrict__ seg_off,
+                                                    int64_t list_capacity, int32_t* __restrict__ list) {
+    __shared__ uint32_t bits[kClaimWords];
+    __shared__ int first[kClaimWords];                                // new ids in front of the word
     __shared__ int smem[256 / RG_WAVE + 1];
-    if (seg_off[1] == seg_off[0]) return;                             // nothing new (or refused): uniform
-    const int64_t w0 = (int64_t)blockIdx.x * kClaimWordsPerBlock + threadIdx.x * 4;
-    uint32_t bits[4];
-    int c = 0;
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-        bits[q] = w0 + q < words ? newbits[w0 + q] : 0u;
-        if (bits[q]) c += rg_count_remote(bits[q], w0 + q, home);
-    }
-    int total;
-    const int excl = rg_block_excl_scan<256 / RG_WAVE>(c, smem, &total);
-    if (total == 0) return;                                           // uniform
-    int64_t j = (int64_t)seg_off[0] + blk_off[blockIdx.x] + excl;
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-        uint32_t b = bits[q];
-        while (b) {
-            const int bit = __ffs(b) - 1;
-            b &= b - 1u;
-            const uint32_t hw = (uint32_t)home[((w0 + q) << 5) + bit];
-            if ((hw >> RG_TAG_SHIFT) == RG_TAG_REMOTE) {
-                const int32_t row = (int32_t)(hw & RG_ROW_MASK);
-                list[2 * j] = row;                                    // mirrored cache: the row's place is its remote-store row
-                list[2 * j + 1] = row;
-                ++j;
-            }
+    __shared__ int part[2][4];
+    int before = 0, all = 0;
+    if (scanned) {
+        if (threadIdx.x == 0) { before = blk_count[blockIdx.x]; all = blk_count[gridDim.x]; }
+    } else {
+        for (unsigned b = threadIdx.x; b < gridDim.x; b += 256) {
+            const int x = blk_count[b];
+            all += x;
+            before += b < blockIdx.x ? x : 0;
         }
     }
+    before = rg_wave_sum(before);
+    all = rg_wave_sum(all);
+    if (rg_lane() == 0) { part[0][threadIdx.x >> 6] = before; part[1][threadIdx.x >> 6] = all; }
+    const int64_t w0 = (int64_t)blockIdx.x * kClaimWords, w = w0 + threadIdx.x;
+    const uint32_t nw = w < words ? newbits[w] : 0u;
+    bits[threadIdx.x] = nw;
+    int total;
+    first[threadIdx.x] = rg_block_excl_scan<256 / RG_WAVE>(__popc(nw), smem, &total);       // its barriers publish part[]
+    all = part[1][0] + part[1][1] + part[1][2] + part[1][3];
+    // a list that cannot take the segment (it holds one pair per remote row, so this means a caller error) gets an
+    // empty segment instead of an overrun
+    const int64_t begin = seg_off[0];
+    const bool fits = begin + all <= list_capacity;
+    if (blockIdx.x == 0 && threadIdx.x == 0) seg_off[1] = (int32_t)(fits ? begin + all : begin);
+    if (!fits || total == 0) return;                                  // uniform
+    __syncthreads();
+    list += 2 * (begin + part[0][0] + part[0][1] + part[0][2] + part[0][3]);
+    rg_claim_pairs(bits, w0, home, [&](int pair, int lane, bool set, uint32_t hw) {
+        if (!set) return;
+        const int word = 2 * pair + (lane >> 5);
+        const int64_t j = first[word] + __popc(bits[word] & ((1u << (lane & 31)) - 1u));
+        list[2 * j] = list[2 * j + 1] = (int32_t)(hw & RG_ROW_MASK);  // mirrored cache: the row's place is its remote-store row
+    });
 }
 
 __global__ void __launch_bounds__(256) k_zero_i32(int32_t* __restrict__ p, int n) {
@@ -1521,17 +1539,20 @@ rg_status rg_plan_sampled(rg_ctx* ctx, int32_t group, const rg_cache* cache, uin
     RG_HIP(ctx, hipSetDevice(ctx->device));
     hipStream_t s = (hipStream_t)stream;
     const int64_t words = rg_div_up(num_nodes, 32);
-    const int nblocks = (int)rg_max64(1, rg_div_up(words, kClaimWordsPerBlock));
+    const int nblocks = (int)rg_max64(1, rg_div_up(words, kClaimWords));
     rg_status st;
     if ((st = rg_ensure(ctx, ctx->claim_bits, (size_t)rg_max64(words, 1) * 4)) != RG_OK) return st;
-    if ((st = rg_ensure(ctx, ctx->claim_blk, (size_t)nblocks * 4)) != RG_OK) return st;
+    if ((st = rg_ensure(ctx, ctx->claim_blk, (size_t)(nblocks + 1) * 4)) != RG_OK) return st;
     uint32_t* newbits = (uint32_t*)ctx->claim_bits.p;
     int32_t* blk = (int32_t*)ctx->claim_blk.p;
     k_claim_count<<<nblocks, 256, 0, s>>>((const uint32_t*)ctx->visited.p, words, group, claimed, newbits, cache->home, blk);
     RG_LAUNCH_CHECK(ctx, "k_claim_count");
-    k_claim_scan<<<1, 1024, 0, s>>>(blk, nblocks, plan->offsets + segment, plan->list_capacity);
-    RG_LAUNCH_CHECK(ctx, "k_claim_scan");
-    k_claim_emit<<<nblocks, 256, 0, s>>>(newbits, words, cache->home, blk, plan->offsets + segment, plan->list);
+    const int scanned = nblocks > kClaimSelfScan;
+    if (scanned) {
+        k_claim_scan<<<1, 1024, 0, s>>>(blk, nblocks);
+        RG_LAUNCH_CHECK(ctx, "k_claim_scan");
+    }
+    k_claim_emit<<<nblocks, 256, 0, s>>>(newbits, words, cache->home, blk, scanned, plan->offsets + segment, plan->list_capacity, plan->list);
     RG_LAUNCH_CHECK(ctx, "k_claim_emit");
     return RG_OK;
 }
