@@ -49,6 +49,7 @@ class _EpochState:
         self.own_cache = True
         self.stats = torch.zeros(max_batches, 3, dtype=torch.int64, device=device)
         self.pf_events = [torch.cuda.Event() for _ in range(max_batches)]
+        self.pull_of = list(range(max_batches))   # the batch with whose event a batch's pull is done
         self.sampled = [torch.cuda.Event() for _ in range(max_batches)]
         self.first_batch = None                # per node: first batch of the epoch that needs it (planned prefetch)
         self.plan = None
@@ -323,8 +324,8 @@ class EpochPipeline:
                     st.claim_done[call].record(s or head)
                     self.pf_stream.wait_event(st.claim_done[call])
                     self.ctx.prefetch_planned(st.plan, call, st.cache, self.wl.remote_store, cfg.feat_dim, stream=self.pf_stream)
-                    for i in range(i0, i1):
-                        st.pf_events[i].record(self.pf_stream)
+                    st.pf_events[i0].record(self.pf_stream)               # one pull, one event
+                    st.pull_of[i0:i1] = [i0] * (i1 - i0)
                 elif self.mirror:                         # each batch's not-yet-resident remote rows, batch by batch
                     st.sampled[i0].record(s or head)
                     self.pf_stream.wait_event(st.sampled[i0])
@@ -503,6 +504,7 @@ class EpochPipeline:
         # group before, which is complete), so the miss stream finds the next group's lists ready when it gets there.
         G = B.RG_GATHER_TICKETS // 2 if self.decoupled else B.RG_GATHER_TICKETS
         group_of = lambda b0: list(range(b0, min(b0 + G, n_batches)))
+        pulled = -1
         for b in range(n_batches):
             if b % G == 0:
                 if not self.decoupled or b == 0:
@@ -513,7 +515,9 @@ class EpochPipeline:
                 if not st.pulls_queued:
                     self.prefetch_rows(b, stream=self.pf_stream)
                     st.pf_events[b].record(self.pf_stream)
-                main.wait_event(st.pf_events[b])
+                if st.pull_of[b] != pulled:             # (batches of one pull wait for it once)
+                    pulled = st.pull_of[b]
+                    main.wait_event(st.pf_events[pulled])
             self.gather(b)
             if on_batch:
                 on_batch(self, b)
