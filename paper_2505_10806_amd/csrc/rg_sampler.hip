@@ -403,7 +403,7 @@ struct SampleScratch {
     int32_t* hop_sum[2];              // the same: edges of the even and the odd hops per kChunk frontier nodes
     int64_t* row_start;               // [group][frontier_stride]
     int32_t* row_deg;                 // [group][frontier_stride]
-    int32_t* first_edge;              // kTierRankedSeen: [group][frontier_stride], by ascending position (see there)
+    int32_t* first_edge;              // kTierRankedSeen: [group][frontier_stride], by ascending position (k_seen_min)
     int32_t* place;                   // the same: ascending position -> position
     int32_t* first_key;               // [group][num_nodes], kTierFirstSeen only: 0x7FFFFFFF - (index of the first edge of
                                       // the current hop that names the node), 0 = not named (kept all-zero between hops)
@@ -1624,7 +1624,8 @@ __global__ void __launch_bounds__(256) k_seen_rank(const SampleScratch S, int ho
 
 // first_edge[position] = the first edge of the hop that names the new node.  A workgroup owns kSeenSlice of the new positions in
 // LDS and reads every edge's position.  With one global atomicMin per edge behind a read (the positions in 1.1 MB per batch) hop 2
-// of 8 batches of 1024 seeds, 4.6 M edges, took 180 us.
+// of 8 batches of 1024 seeds, 4.6 M edges, took 180 us.  Cutting the edges into parts as well, with a bitmap of the positions that each part names,
+// is no faster (4 to 16 parts 40 + 7 us against 34): clearing and reading out the slices then take the time.
 constexpr int kSeenSlice = 40000;
 __device__ __forceinline__ void rg_seen_min(int32_t* first, int32_t a, int64_t e, uint32_t a0, uint32_t n) {
     const uint32_t d = (uint32_t)a - a0;
@@ -1669,7 +1670,11 @@ __global__ void __launch_bounds__(1024) k_seen_min(const SampleScratch S, int ho
     for (int i = threadIdx.x; i < n_here; i += 1024) out[i] = slice_first[i];
 }
 
-constexpr int kSeenEdges = 4096;       // edges per workgroup: 1024 threads x 4
+constexpr int kSeenEdges = 4096;       // edges per workgroup of the count and the emit: 1024 threads x 4
+constexpr uint32_t kOpens = 0x80000000u;         // in nbr_local, from the count to the relabelling: the edge opens a node
+
+// The edges that open a node, marked in nbr_local, where the emit meets them (looking their first edges up again it took 32 us at that hop,
+// now 25), and their number per workgroup.
 
 __global__ void __launch_bounds__(1024) k_seen_count(const SampleScratch S, int hop) {
     __shared__ int part[1024 / RG_WAVE];
@@ -1678,16 +1683,20 @@ __global__ void __launch_bounds__(1024) k_seen_count(const SampleScratch S, int 
     const int n_h = rg_tier_off(S, g)[hop + 1];
     const int64_t n = rg_hop_list(S, g, (int)hop, kIndptr)[n_h], first = (int64_t)blk * kSeenEdges;
     if (first >= n) return;                              // uniform per workgroup
-    const int32_t* __restrict__ at = rg_hop_list(S, g, (int)hop, kNbrLocal);
+    int32_t* __restrict__ at = rg_hop_list(S, g, (int)hop, kNbrLocal) + first;
     const int32_t* __restrict__ first_edge = S.first_edge + g * S.frontier_stride;
     int c = 0;
     int32_t a[4], f[4];
 #pragma unroll
-    for (int q = 0; q < 4; ++q) a[q] = first + q * 1024 + threadIdx.x < n ? at[first + q * 1024 + threadIdx.x] : -1;
+    for (int q = 0; q < 4; ++q) a[q] = first + q * 1024 + threadIdx.x < n ? at[q * 1024 + threadIdx.x] : -1;
 #pragma unroll
     for (int q = 0; q < 4; ++q) f[q] = a[q] >= n_h ? first_edge[a[q]] : -1;
 #pragma unroll
-    for (int q = 0; q < 4; ++q) c += f[q] == (int32_t)(first + q * 1024 + threadIdx.x);
+    for (int q = 0; q < 4; ++q)
+        if (f[q] == (int32_t)(first + q * 1024 + threadIdx.x)) {
+            ++c;
+            at[q * 1024 + threadIdx.x] = (int32_t)((uint32_t)a[q] | kOpens);
+        }
     c = rg_wave_sum(c);
     if (rg_lane() == 0) part[threadIdx.x >> 6] = c;
     __syncthreads();
@@ -1697,49 +1706,82 @@ __global__ void __launch_bounds__(1024) k_seen_count(const SampleScratch S, int 
     }
 }
 
-// The nodes that edges open, in edge order, and where each ascending position ended up.
-__global__ void __launch_bounds__(1024) k_seen_emit(const SampleScratch S, int hop) {
+// The nodes that edges open, in edge order, and where each ascending position ended up; edge_blocks workgroups per batch.  next_fanout >= 0:
+// also the next hop's sizes, as in rg_new_rows, those of the nodes in front of the tier by the workgroups behind.
+__global__ void __launch_bounds__(1024) k_seen_emit(const RowPtr row_ptr, const SampleScratch S, int hop, unsigned edge_blocks, int next_fanout) {
     constexpr int NW = 1024 / RG_WAVE;
     __shared__ int smem[NW + 1];
     __shared__ int part[NW];
+    __shared__ int edges[kSeenEdges / kChunk + 2];
     const int g = rg_batch(S);
     const unsigned blk = rg_block(S);
+    if (blk >= edge_blocks) {
+        rg_old_edges<1024>(S, g, hop, (int)(blk - edge_blocks), next_fanout);
+        return;
+    }
     const int n_h = rg_tier_off(S, g)[hop + 1];
     const int64_t n = rg_hop_list(S, g, (int)hop, kIndptr)[n_h], first = (int64_t)blk * kSeenEdges;
     if (first >= n) return;                              // uniform per workgroup
     const int32_t* __restrict__ at = rg_hop_list(S, g, (int)hop, kNbrLocal);
     const int32_t* __restrict__ nbr = rg_hop_list(S, g, (int)hop, kNbr);
-    const int32_t* __restrict__ first_edge = S.first_edge + g * S.frontier_stride;
     const int32_t* __restrict__ chunk_sum = S.chunk_sum + g * S.chunk_stride;
     int before = 0;                                      // nodes opened by the edges in front of this workgroup's
     for (unsigned c = threadIdx.x; c < blk; c += 1024) before += chunk_sum[c];
     before = rg_wave_sum(before);
     if (rg_lane() == 0) part[threadIdx.x >> 6] = before;
+    if (threadIdx.x < sizeof(edges) / sizeof(int)) edges[threadIdx.x] = 0;
     const int64_t e0 = first + threadIdx.x * 4;
-    int32_t a[4], f[4];
-    bool opens[4];
-    int c = 0;
+    int32_t a[4], u[4];
+    uint32_t opens = 0u;
 #pragma unroll
-    for (int q = 0; q < 4; ++q) a[q] = e0 + q < n ? at[e0 + q] : -1;
-#pragma unroll
-    for (int q = 0; q < 4; ++q) f[q] = a[q] >= n_h ? first_edge[a[q]] : -1;
+    for (int q = 0; q < 4; ++q) a[q] = e0 + q < n ? at[e0 + q] : 0;
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
-        opens[q] = f[q] == (int32_t)(e0 + q);
-        c += opens[q];
+        u[q] = -1;
+        if (a[q] < 0) { u[q] = nbr[e0 + q]; opens |= 1u << q; }
     }
     int total;
-    int out = n_h + rg_block_excl_scan<NW>(c, smem, &total);               // its barriers publish part[]
+    int out = n_h + rg_block_excl_scan<NW>(__popc(opens), smem, &total);   // its barriers publish part[] and edges[]
+    before = n_h;
 #pragma unroll
-    for (int q = 0; q < NW; ++q) out += part[q];
+    for (int q = 0; q < NW; ++q) { out += part[q]; before += part[q]; }
+    int64_t start[4], deg[4];
+    if (next_fanout >= 0) {
+        const auto rows = [&](auto* p) {
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+                if ((opens >> q) & 1u) rg_row_extent(p, u[q], start[q], deg[q]);
+        };
+        if (row_ptr.wide) rows((const int64_t*)row_ptr.p); else rows((const int32_t*)row_ptr.p);
+    }
     int32_t* __restrict__ nodes = rg_nodes(S, g);
     int32_t* __restrict__ place = S.place + g * S.frontier_stride;
+    const int chunk0 = out / kChunk - before / kChunk;
+    int in_first = 0, in_next = 0;                       // edges of this thread's nodes in the chunk of the first of them, and in the one behind
 #pragma unroll
     for (int q = 0; q < 4; ++q)
-        if (opens[q]) {
-            nodes[out] = nbr[e0 + q];
-            place[a[q]] = out++;
+        if ((opens >> q) & 1u) {
+            nodes[out] = u[q];
+            place[(uint32_t)a[q] & ~kOpens] = out;
+            if (next_fanout >= 0) {
+                const int m = rg_put_row(S, g, out, start[q], deg[q], next_fanout);
+                if (out / kChunk - before / kChunk == chunk0) in_first += m; else in_next += m;
+            }
+            ++out;
         }
+    if (next_fanout < 0) return;
+    // one addition for a wavefront whose nodes share a chunk: lanes that add to one address queue up
+    const int lead = __builtin_amdgcn_readfirstlane(chunk0);
+    if (__all(chunk0 == lead && in_next == 0)) {
+        in_first = rg_wave_sum(in_first);
+        if (rg_lane() == 0 && in_first) atomicAdd(&edges[lead], in_first);
+    } else {
+        if (in_first) atomicAdd(&edges[chunk0], in_first);
+        if (in_next) atomicAdd(&edges[chunk0 + 1], in_next);
+    }
+    __syncthreads();
+    if (threadIdx.x < sizeof(edges) / sizeof(int) && edges[threadIdx.x])
+        atomicAdd(&S.hop_sum[(hop + 1) & 1][g * S.chunk_stride + before / kChunk + threadIdx.x], edges[threadIdx.x]);
 }
 
 // ---------------------------------------------------------------------------- relabelling, all hops in one launch
@@ -2116,7 +2158,7 @@ __global__ void __launch_bounds__(256) k_seen_relabel(const SampleScratch S, int
         for (int64_t e0 = (int64_t)rg_block(S) * 256 + threadIdx.x; e0 < n; e0 += stride * U) {
             int32_t a[U];
 #pragma unroll
-            for (int q = 0; q < U; ++q) a[q] = e0 + stride * q < n ? nbr_local[e0 + stride * q] : -1;
+            for (int q = 0; q < U; ++q) a[q] = e0 + stride * q < n ? nbr_local[e0 + stride * q] & (int32_t)~kOpens : -1;
 #pragma unroll
             for (int q = 0; q < U; ++q)
                 if (a[q] >= seeds) a[q] = place[a[q]];
@@ -2721,7 +2763,10 @@ rg_status rg_sample_blocks_group(rg_ctx* ctx, const rg_csr* csr, int32_t group, 
                 const unsigned seen_blocks = (unsigned)grid_for(eub_max[h], kSeenEdges, 1 << 30);
                 k_seen_count<<<seen_blocks * ug, 1024, 0, s>>>(S, h);
                 RG_LAUNCH_CHECK(ctx, "k_seen_count");
-                k_seen_emit<<<seen_blocks * ug, 1024, 0, s>>>(S, h);
+                const bool sizes = h + 1 < num_hops && drawn_by_threads(h + 1);
+                if (sizes) counted = h + 1;
+                k_seen_emit<<<(seen_blocks + (sizes ? (unsigned)rg_div_up(fub_max[h], kChunk) : 0u)) * ug, 1024, 0, s>>>(row_ptr, S, h, seen_blocks,
+                                                                                                                        sizes ? fanouts[h + 1] : -1);
                 RG_LAUNCH_CHECK(ctx, "k_seen_emit");
             }
         } else if (mode == kTierFirstSeen) {
