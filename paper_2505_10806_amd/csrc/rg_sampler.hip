@@ -130,17 +130,22 @@ __device__ __forceinline__ void rg_row_extent(const RowPtr& row_ptr, int v, int6
 
 // ---------------------------------------------------------------------------- schedule
 // The keys are Philox words, spread evenly whatever the ids, so their top bits are a perfect first radix digit: the pairs (32 more
-// bits of the key, id) go to one of 2^log2_buckets buckets, each of which has room for kSchedRoom of them where about 1024-2048
-// come, and every bucket is finished by one workgroup in LDS (a second digit of kSubBits bits leaves about one pair per sub-bucket;
+// bits of the key, id) go to one of 2^log2_buckets buckets, each of which has room for kSchedRoom of them where half of kSchedAvg to
+// all of it come, and every bucket is finished by one workgroup in LDS (a second digit of kSubBits bits leaves about one pair per sub-bucket;
 // pairs alike in the bits at hand have their keys worked out again).  Ids that find their bucket full, which only ids picked for
 // their keys do, wait in a list.  Nothing is counted beforehand: the keys are worked out once, and a call is two launches.
 // Bound by launches, the Philox blocks (3.3 us for 1 M ids on the whole device) and the scattered 8-byte writes.
-constexpr int kSchedLds = 4096;          // pairs one workgroup sorts in LDS
-constexpr int kSchedAvg = 2048;          // pairs per bucket on average, at most
-constexpr int kSchedRoom = 2560;         // eleven standard deviations more
+// Few ids get small buckets, whose sort is a shorter chain of LDS passes (100 k ids 9.5 us, in buckets of 2048 12.0; 10 k 7.2 / 9.3; 400 k 14.8 / 15.9),
+// many get large ones, to whose counters the workgroups add less often (700 k 24.7 / 19.3).  Up to 3072 ids one workgroup does it all (1000 5.0 us, in
+// buckets 7.1; 3072 7.2 either way), of 1024 threads (4096 ids 9.6 us, with 512 threads 12.3).
+constexpr int kSchedLds = 3072;          // pairs one workgroup sorts in LDS
+constexpr int kSchedAvg[2] = {512, 2048};          // pairs per bucket on average, at most
+constexpr int kSchedRoom[2] = {1024, 2560};        // eleven standard deviations more and above
+constexpr int64_t kSchedFew = 400 * 1000;          // ids that get the small ones
+constexpr int64_t kSchedFewBuckets = 1024;         // of the most of these
+static_assert(kSchedFew <= kSchedFewBuckets * kSchedAvg[0], "buckets for them");
 constexpr int kSchedLdsBuckets = 4096;   // buckets whose counters a workgroup keeps in LDS; with more (n > 8 Mi) every id
                                          // adds to the counter in HBM, and the counters are scanned by a launch of their own
-constexpr int kSubBits = 11;
 
 __device__ __forceinline__ uint64_t rg_sched_key(int32_t v, uint32_t epoch, uint32_t k0, uint32_t k1) {
     uint32_t w[4];
@@ -170,7 +175,7 @@ __global__ void __launch_bounds__(1024) k_sched_scan(const int32_t* __restrict__
 
 // Pairs go to their bucket; the order inside is left to k_sched_sort.  count[b] = pairs of bucket b, those without room among them;
 // count[buckets] = ids in the list `late`.  PER ids per thread.
-template <bool LDS, int PER>
+template <bool LDS, int PER, int ROOM>
 __global__ void __launch_bounds__(1024) k_sched_scatter(const int32_t* __restrict__ train_ids, int64_t n, int log2_buckets, uint32_t k0,
                                                         uint32_t k1, uint32_t epoch, int32_t* __restrict__ count,
                                                         uint2* __restrict__ pairs, int32_t* __restrict__ late) {
@@ -205,7 +210,7 @@ __global__ void __launch_bounds__(1024) k_sched_scatter(const int32_t* __restric
         if (i0 + j * 1024 + threadIdx.x >= n) continue;
         const int64_t b = (int64_t)(key[j] >> (64 - log2_buckets));
         const int32_t at = (LDS ? h[b] : 0) + rank[j];
-        if (at < kSchedRoom) pairs[b * kSchedRoom + at] = make_uint2((uint32_t)(key[j] >> (32 - log2_buckets)), (uint32_t)v[j]);
+        if (at < ROOM) pairs[b * ROOM + at] = make_uint2((uint32_t)(key[j] >> (32 - log2_buckets)), (uint32_t)v[j]);
         else late[atomicAdd(&count[buckets], 1)] = v[j];
     }
 }
@@ -213,15 +218,17 @@ __global__ void __launch_bounds__(1024) k_sched_scatter(const int32_t* __restric
 // One workgroup per bucket: its pairs in order, the ids to their final places.  CAP: pairs it has room for in LDS.
 // SINGLE: one bucket, the n train ids themselves.  start == NULL: the workgroup adds up the counts in front of its own.
 // `clear` (or NULL): n_clear counters that the next call will use.
-template <int CAP, bool SINGLE>
-__global__ void __launch_bounds__(512) k_sched_sort(const int32_t* __restrict__ train_ids, int64_t n, int log2_buckets, uint32_t k0,
+template <int CAP, bool SINGLE, int T>
+__global__ void __launch_bounds__(T) k_sched_sort(const int32_t* __restrict__ train_ids, int64_t n, int log2_buckets, uint32_t k0,
                                                     uint32_t k1, uint32_t epoch, const int32_t* __restrict__ count,
                                                     const int32_t* __restrict__ start, const uint2* __restrict__ pairs,
                                                     const int32_t* __restrict__ late, int32_t* order_out,
                                                     int32_t* __restrict__ clear, int n_clear) {
-    constexpr int T = 512, PER = CAP / T, SUB = 1 << kSubBits;
-    __shared__ uint32_t sk[CAP];
-    __shared__ int32_t si[CAP];
+    constexpr int kTile = SINGLE ? 0 : 2048;            // of an overfull bucket
+    constexpr int PER = CAP / T, kSubBits = CAP > 1024 ? 11 : 10, SUB = 1 << kSubBits;
+    static_assert(CAP % T == 0 && SUB % T == 0, "whole rounds");
+    __shared__ uint32_t sk[CAP > kTile ? CAP : kTile];
+    __shared__ int32_t si[CAP > kTile ? CAP : kTile];
     __shared__ int32_t sub[SUB + 1];
     __shared__ int smem[T / RG_WAVE + 1];
     const int64_t bucket = blockIdx.x;
@@ -241,16 +248,15 @@ __global__ void __launch_bounds__(512) k_sched_sort(const int32_t* __restrict__ 
     if (m == 0) return;                                                  // uniform
     int32_t* out = order_out + s0;
     const auto full_key = [&](int32_t v) { return rg_sched_key(v, epoch, k0, k1); };
-    if (!SINGLE && m > kSchedRoom) {
+    if (!SINGLE && m > CAP) {
         // Only ids picked for their keys get here: the bucket's and those of the list that belong to it, sorted where they will be,
         // by a network whose every comparison is ascending, so that the places behind its end count as larger than everything and are
         // never touched.  Steps within kTile ids are made in LDS, tile by tile; of the others there are few, which work the keys out
         // from the ids.  A call of 100,000 ids of which 5000 belong to one bucket 136 us, 50,000 of them 1.8 ms (with all steps in
         // global memory 374 and 5.0 ms; 12 where every bucket has room), one of 1 M ids with 4000 in a bucket 94 (277; 24).
-        constexpr int kTile = 2048;
         int32_t* fill = sub;
-        if (threadIdx.x == 0) *fill = kSchedRoom;
-        for (int i = threadIdx.x; i < kSchedRoom; i += T) out[i] = (int32_t)pairs[bucket * kSchedRoom + i].y;
+        if (threadIdx.x == 0) *fill = CAP;
+        for (int i = threadIdx.x; i < CAP; i += T) out[i] = (int32_t)pairs[bucket * CAP + i].y;
         __syncthreads();
         const int n_late = count[1ll << log2_buckets];
         for (int i = threadIdx.x; i < n_late; i += T) {
@@ -278,7 +284,7 @@ __global__ void __launch_bounds__(512) k_sched_sort(const int32_t* __restrict__ 
                 }
                 for (int w = first ? 2 : 2 * kTile; w <= (first ? kTile : 2 * kTile); w <<= 1)
                     for (int d = first ? w - 1 : kTile / 2; d > 0; d = d == w - 1 ? w >> 2 : d >> 1) {
-                        constexpr int P = kTile / 2 / T;                 // pairs per thread
+                        constexpr int P = kTile / 2 / T + SINGLE;                 // pairs per thread
                         const int top = d == w - 1 ? w >> 1 : d;         // the bit of i that l has and i has not
                         uint32_t ka[P], kb[P];
                         int32_t a[P], b[P];
@@ -318,7 +324,7 @@ __global__ void __launch_bounds__(512) k_sched_sort(const int32_t* __restrict__ 
                 id[j] = train_ids[i];
                 key[j] = (uint32_t)(full_key(id[j]) >> 32);
             } else {
-                const uint2 x = pairs[bucket * kSchedRoom + i];
+                const uint2 x = pairs[bucket * CAP + i];
                 key[j] = x.x;
                 id[j] = (int32_t)x.y;
             }
@@ -2384,19 +2390,23 @@ rg_status rg_epoch_schedule(rg_ctx* ctx, const int32_t* train_ids, int64_t n, ui
     hipStream_t s = (hipStream_t)stream;
     const uint32_t k0 = (uint32_t)(seed & 0xffffffffu), k1 = (uint32_t)(seed >> 32);
     if (n <= kSchedLds) {
-        k_sched_sort<kSchedLds, true><<<1, 512, 0, s>>>(train_ids, n, 0, k0, k1, epoch, nullptr, nullptr, nullptr, nullptr, order_out, nullptr, 0);
+        k_sched_sort<kSchedLds, true, 1024><<<1, 1024, 0, s>>>(train_ids, n, 0, k0, k1, epoch, nullptr, nullptr, nullptr, nullptr, order_out, nullptr, 0);
         RG_LAUNCH_CHECK(ctx, "k_sched_sort");
         return RG_OK;
     }
+    const int many = n > kSchedFew;
     int lb = 1;
-    while (((int64_t)kSchedAvg << lb) < n) ++lb;
+    while (((int64_t)kSchedAvg[many] << lb) < n) ++lb;
     const int64_t buckets = 1ll << lb;
     rg_status st;
-    // sized for the largest n of as many buckets, so that a call of another such n, captured perhaps, allocates nothing
-    if ((st = rg_ensure(ctx, ctx->sched_pairs, (size_t)(kSchedRoom * buckets) * 8)) != RG_OK) return st;
-    if ((st = rg_ensure(ctx, ctx->sched_late, (size_t)(kSchedAvg * buckets) * 4)) != RG_OK) return st;
+    // sized for the largest n of as many buckets, so that a call of another such n, captured perhaps, allocates nothing, and where there are
+    // many ids for few as well, whose buckets take more
+    const int64_t most_buckets = many ? rg_max64(buckets, kSchedFewBuckets) : buckets;
+    const int64_t most_pairs = rg_max64(kSchedRoom[many] * buckets, many ? kSchedRoom[0] * kSchedFewBuckets : 0);
+    if ((st = rg_ensure(ctx, ctx->sched_pairs, (size_t)most_pairs * 8)) != RG_OK) return st;
+    if ((st = rg_ensure(ctx, ctx->sched_late, (size_t)rg_max64(kSchedAvg[many] * buckets, many ? kSchedAvg[0] * kSchedFewBuckets : 0) * 4)) != RG_OK) return st;
     const void* counters = ctx->sched_buckets.p;
-    if ((st = rg_ensure(ctx, ctx->sched_buckets, (size_t)(4 * (buckets + 1)) * 4, true)) != RG_OK) return st;
+    if ((st = rg_ensure(ctx, ctx->sched_buckets, (size_t)(4 * (most_buckets + 1)) * 4, true)) != RG_OK) return st;
     if (ctx->sched_buckets.p != counters) ctx->sched_dirty[0] = ctx->sched_dirty[1] = 0;
     uint2* pairs = (uint2*)ctx->sched_pairs.p;
     int32_t* late = (int32_t*)ctx->sched_late.p;
@@ -2417,17 +2427,22 @@ rg_status rg_epoch_schedule(rg_ctx* ctx, const int32_t* train_ids, int64_t n, ui
     // 1024 ids to a workgroup while that leaves compute units without one
     const bool few = n <= 1024ll * ctx->num_cus;
     const int g = (int)rg_div_up(n, few ? 1024 : 4096);
-    if (few) k_sched_scatter<true, 1><<<g, 1024, 0, s>>>(train_ids, n, lb, k0, k1, epoch, count, pairs, late);
-    else if (lds) k_sched_scatter<true, 4><<<g, 1024, 0, s>>>(train_ids, n, lb, k0, k1, epoch, count, pairs, late);
-    else k_sched_scatter<false, 4><<<g, 1024, 0, s>>>(train_ids, n, lb, k0, k1, epoch, count, pairs, late);
+#define RG_SCATTER(LDS, PER, MANY) k_sched_scatter<LDS, PER, kSchedRoom[MANY]><<<g, 1024, 0, s>>>(train_ids, n, lb, k0, k1, epoch, count, pairs, late)
+    if (!many) { if (few) RG_SCATTER(true, 1, 0); else RG_SCATTER(true, 4, 0); }
+    else if (lds) RG_SCATTER(true, 4, 1);
+    else RG_SCATTER(false, 4, 1);
+#undef RG_SCATTER
     RG_LAUNCH_CHECK(ctx, "k_sched_scatter");
     if (start) {
         k_sched_scan<<<1, 1024, 0, s>>>(count, (int)buckets, start);
         RG_LAUNCH_CHECK(ctx, "k_sched_scan");
     }
     int32_t* clear = captured || !ctx->sched_dirty[other] ? nullptr : (int32_t*)ctx->sched_buckets.p + other * set;
-    k_sched_sort<kSchedRoom, false><<<(unsigned)buckets, 512, 0, s>>>(nullptr, n, lb, k0, k1, epoch, count, start, pairs, late, order_out, clear,
-                                                                      clear ? (int)ctx->sched_dirty[other] : 0);
+#define RG_SORT(MANY)                                                                                                 \
+    k_sched_sort<kSchedRoom[MANY], false, 512><<<(unsigned)buckets, 512, 0, s>>>(nullptr, n, lb, k0, k1, epoch, count, start, pairs, late, order_out, \
+                                                                                clear, clear ? (int)ctx->sched_dirty[other] : 0)
+    if (many) RG_SORT(1); else RG_SORT(0);
+#undef RG_SORT
     RG_LAUNCH_CHECK(ctx, "k_sched_sort");
     if (!captured) {
         ctx->sched_dirty[other] = 0;

@@ -971,3 +971,35 @@ def test_two_stream_gathers_keep_their_place_in_both_streams(B, ctx, rows):
     got = torch.cat(taken).reshape(calls, 2).cpu()
     assert torch.equal(got, torch.arange(1, calls + 1, dtype=torch.float32).reshape(-1, 1).expand(-1, 2)), got.flatten().tolist()
     assert stats.cpu().tolist() == [rows - missing.numel(), 0, missing.numel()]
+
+
+# One workgroup up to 3072 ids, buckets of 512 on average up to 400,000, of 2048 above; a bucket of 256 to 512 with room for 1024.
+@pytest.mark.parametrize("n", [1025, 3071, 3072, 3073, 16_384, 16_385, 262_144, 400_000, 400_001])
+def test_schedule_bucket_sizes(ctx, n):
+    log(f"[schedule sizes] n={n}")
+    ids = np.random.default_rng(n).permutation(2 * n)[:n].astype(np.int32)
+    assert np.array_equal(ctx.epoch_schedule(_i32(ids), 21, 4).cpu().numpy(), oracle.epoch_schedule(ids, 21, 4))
+
+
+@pytest.mark.parametrize("in_bucket", [1000, 1024, 1025, 2048, 2500, 5000])
+def test_schedule_small_bucket_with_more_ids_than_room(ctx, in_bucket):
+    log(f"[small bucket] {in_bucket}")
+    order = oracle.epoch_schedule(np.arange(2_000_000, dtype=np.int32), 21, 4)         # ascending by key: 7800 ids or so to each of 256 buckets
+    rng = np.random.default_rng(in_bucket)
+    ids = rng.permutation(np.concatenate([order[:in_bucket], order[20_000:][rng.permutation(1_980_000)[:70_000]]])).astype(np.int32)
+    assert np.array_equal(ctx.epoch_schedule(_i32(ids), 21, 4).cpu().numpy(), oracle.epoch_schedule(ids, 21, 4))
+
+
+def test_schedule_recorded_for_many_ids_survives_few(B):
+    """Large buckets and small ones take different scratch: what a graph holds is there for both."""
+    ctx = B.Context(0)
+    ids = {n: np.random.default_rng(n).permutation(2 * n)[:n].astype(np.int32) for n in (400_001, 390_000)}
+    dev, out = {n: _i32(x) for n, x in ids.items()}, torch.empty(400_001, dtype=torch.int32, device=DEV)
+    ctx.epoch_schedule(dev[400_001], 5, 2, out)
+    graph = _captured(lambda: ctx.epoch_schedule(dev[400_001], 5, 2, out))
+    for _ in range(3):
+        assert np.array_equal(ctx.epoch_schedule(dev[390_000], 5, 2).cpu().numpy(), oracle.epoch_schedule(ids[390_000], 5, 2))
+        out.zero_()
+        graph.replay()
+        assert np.array_equal(out.cpu().numpy(), oracle.epoch_schedule(ids[400_001], 5, 2))
+    ctx.close()
