@@ -119,18 +119,23 @@ __device__ __forceinline__ uint32_t rg_add_counts(uint32_t* gctl, int turn, unsi
     return (uint32_t)(before & mask);
 }
 
-// Four rows per thread (row i0 + k*256 + threadIdx.x, k = 0..3) so that each thread has four independent
-// loc[] lookups in flight; the miss pairs of a workgroup are appended in that visiting order (any order is valid).
-constexpr int kClassifyRows = 4;
+// R rows per thread (row i0 + k * T + threadIdx.x), so that each thread has as many independent loc[] lookups in flight; the miss pairs of
+// a workgroup of T threads are appended in that visiting order (any order is valid).  One batch: 4096 rows per workgroup, because
+// their additions to its counter queue up (1024 rows to a workgroup, 776 of them 21 us for 794 k rows of a mirrored cache, now 15; 3 M rows, a
+// tenth missing, 44 / 21).  Several batches, which have a counter each: eight rows per thread (8 batches of 400 k rows, four in workgroups of 256 and of
+// 1024 threads 69, eight of 256 55).
+template <bool ONE> constexpr int kClassifyThreads = ONE ? 1024 : 256;
+template <bool ONE> constexpr int kClassifyRows = ONE ? 4 : 8;
 
 // mirror_home != NULL: the cache is laid out as a mirror of the remote store, so a cached node's row is found at its
 // remote-store row (from its home word) instead of at its slot.
 // WIDE: batches of 2^23 rows or more, with separate counters that k_gather_reset has cleared.
-template <bool WIDE>
-__global__ void __launch_bounds__(256) k_classify(const ClassifyGroup C, const int32_t* __restrict__ loc,
+template <bool WIDE, bool ONE>
+__global__ void __launch_bounds__(kClassifyThreads<ONE>) k_classify(const ClassifyGroup C, const int32_t* __restrict__ loc,
                                                   const int32_t* __restrict__ mirror_home) {
-    __shared__ int smem[256 / RG_WAVE + 1];
-    __shared__ int cls[2][4];
+    constexpr int T = kClassifyThreads<ONE>, R = kClassifyRows<ONE>, NW = T / RG_WAVE;
+    __shared__ int smem[NW + 1];
+    __shared__ int cls[2][NW];
     __shared__ uint32_t miss_base;
     const int b = blockIdx.y;
     const int32_t* __restrict__ nodes = C.nodes[b];
@@ -139,7 +144,7 @@ __global__ void __launch_bounds__(256) k_classify(const ClassifyGroup C, const i
     uint32_t* __restrict__ gctl = C.gctl[b];
     unsigned long long* __restrict__ stats = C.stats[b];
     const int64_t n_act = rg_actual_n(C.n[b], C.n_dev[b]);
-    const int64_t i0 = (int64_t)blockIdx.x * (256 * kClassifyRows);
+    const int64_t i0 = (int64_t)blockIdx.x * (T * R);
     if (i0 >= n_act) {                                             // uniform per workgroup
         if (!WIDE && blockIdx.x == 0) {                            // an empty batch
             if (threadIdx.x < 3) stats[threadIdx.x] = 0ull;
@@ -147,25 +152,25 @@ __global__ void __launch_bounds__(256) k_classify(const ClassifyGroup C, const i
         }
         return;
     }
-    uint32_t w[kClassifyRows];
-    int32_t v[kClassifyRows];
+    uint32_t w[R];
+    int32_t v[R];
 #pragma unroll
-    for (int k = 0; k < kClassifyRows; ++k) {
-        const int64_t i = i0 + k * 256 + threadIdx.x;
+    for (int k = 0; k < R; ++k) {
+        const int64_t i = i0 + k * T + threadIdx.x;
         v[k] = i < n_act ? nodes[i] : -1;
     }
 #pragma unroll
-    for (int k = 0; k < kClassifyRows; ++k) w[k] = v[k] >= 0 ? (uint32_t)loc[v[k]] : 0xFFFFFFFFu;   // tag 3 = no row
+    for (int k = 0; k < R; ++k) w[k] = v[k] >= 0 ? (uint32_t)loc[v[k]] : 0xFFFFFFFFu;   // tag 3 = no row
     if (mirror_home) {
 #pragma unroll
-        for (int k = 0; k < kClassifyRows; ++k)
+        for (int k = 0; k < R; ++k)
             if ((w[k] >> RG_TAG_SHIFT) == RG_TAG_CACHE)
                 w[k] = (RG_TAG_CACHE << RG_TAG_SHIFT) | ((uint32_t)mirror_home[v[k]] & RG_ROW_MASK);
     }
     int c_local = 0, c_hit = 0, n_miss = 0;
 #pragma unroll
-    for (int k = 0; k < kClassifyRows; ++k) {
-        const int64_t i = i0 + k * 256 + threadIdx.x;
+    for (int k = 0; k < R; ++k) {
+        const int64_t i = i0 + k * T + threadIdx.x;
         const uint32_t tag = w[k] >> RG_TAG_SHIFT;
         if (i < n_act) src[i] = w[k];
         c_local += tag == RG_TAG_LOCAL;
@@ -177,11 +182,12 @@ __global__ void __launch_bounds__(256) k_classify(const ClassifyGroup C, const i
     c_hit = rg_wave_sum(c_hit);
     if (rg_lane() == 0) { cls[0][wave] = c_local; cls[1][wave] = c_hit; }
     int total_miss;
-    int excl = rg_block_excl_scan<256 / RG_WAVE>(n_miss, smem, &total_miss);          // barriers inside publish cls[]
+    int excl = rg_block_excl_scan<NW>(n_miss, smem, &total_miss);          // barriers inside publish cls[]
     if (threadIdx.x == 0) {
-        const int hits = cls[1][0] + cls[1][1] + cls[1][2] + cls[1][3];
+        int locals = 0, hits = 0;
+#pragma unroll
+        for (int w = 0; w < NW; ++w) { locals += WIDE ? cls[0][w] : 0; hits += cls[1][w]; }
         if (WIDE) {
-            const int locals = cls[0][0] + cls[0][1] + cls[0][2] + cls[0][3];
             if (locals) atomicAdd(&stats[0], (unsigned long long)locals);
             if (hits) atomicAdd(&stats[1], (unsigned long long)hits);
             if (total_miss) {
@@ -189,17 +195,17 @@ __global__ void __launch_bounds__(256) k_classify(const ClassifyGroup C, const i
                 miss_base = atomicAdd(&gctl[0], (uint32_t)total_miss);
             }
         } else {
-            miss_base = rg_add_counts(gctl, C.turn[b], stats, total_miss, hits, n_act, (unsigned)((n_act + 256 * kClassifyRows - 1) / (256 * kClassifyRows)));
+            miss_base = rg_add_counts(gctl, C.turn[b], stats, total_miss, hits, n_act, (unsigned)((n_act + T * R - 1) / (T * R)));
         }
     }
     if (total_miss == 0) return;                                   // uniform
     __syncthreads();
 #pragma unroll
-    for (int k = 0; k < kClassifyRows; ++k)
+    for (int k = 0; k < R; ++k)
         if ((w[k] >> RG_TAG_SHIFT) == RG_TAG_REMOTE) {   // (output row, remote row) pairs: the miss kernel needs no further lookup
             const int64_t j = (int64_t)miss_base + excl++;
             if (j >= n_act) continue;
-            miss_list[2 * j] = (int32_t)(i0 + k * 256 + threadIdx.x);
+            miss_list[2 * j] = (int32_t)(i0 + k * T + threadIdx.x);
             miss_list[2 * j + 1] = (int32_t)(w[k] & RG_ROW_MASK);
         }
 }
@@ -419,10 +425,14 @@ rg_status launch_classify(rg_ctx* ctx, int count, const int32_t* const* input_no
         k_clear_counters<<<count, 64, 0, s>>>(C);
         RG_LAUNCH_CHECK(ctx, "k_clear_counters");
     }
-    const dim3 grid((unsigned)rg_max64(1, rg_div_up(n_max, 256 * kClassifyRows)), (unsigned)count);
     const int32_t* home = cache->mirror_rows > 0 ? cache->home : nullptr;
-    if (wide) k_classify<true><<<grid, 256, 0, s>>>(C, cache->loc, home);
-    else k_classify<false><<<grid, 256, 0, s>>>(C, cache->loc, home);
+#define RG_CLASSIFY(WIDE, ONE)                                                                                        \
+    k_classify<WIDE, ONE><<<dim3((unsigned)rg_max64(1, rg_div_up(n_max, kClassifyThreads<ONE> * kClassifyRows<ONE>)), (unsigned)count), \
+                            kClassifyThreads<ONE>, 0, s>>>(C, cache->loc, home)
+    if (count == 1) { if (wide) RG_CLASSIFY(true, true); else RG_CLASSIFY(false, true); }
+    else if (wide) RG_CLASSIFY(true, false);
+    else RG_CLASSIFY(false, false);
+#undef RG_CLASSIFY
     RG_LAUNCH_CHECK(ctx, "k_classify");
     return RG_OK;
 }

@@ -1003,3 +1003,32 @@ def test_schedule_recorded_for_many_ids_survives_few(B):
         graph.replay()
         assert np.array_equal(out.cpu().numpy(), oracle.epoch_schedule(ids[400_001], 5, 2))
     ctx.close()
+
+
+# Lookups: workgroups of 4096 rows for one batch, of 2048 for several; last ones of one row, of all.
+@pytest.mark.parametrize("rows", [[1], [4096], [4097], [200_001], [1, 0], [2048, 2049, 4095, 0, 6144]])
+@pytest.mark.parametrize("mirror", [False, True])
+def test_lookups_of_one_and_of_several_batches(B, ctx, rows, mirror):
+    log(f"[lookups] rows={rows} mirror={mirror}")
+    n, dim, rng = 300_000, 4, np.random.default_rng(sum(rows))
+    X = torch.arange(n, device=DEV, dtype=torch.float32).reshape(-1, 1).expand(-1, dim).contiguous()
+    kind = rng.integers(0, 3, n)                        # local, cached, missing
+    is_local, is_cached = _i32(kind == 0).bool(), _i32(kind == 1).bool()
+    place = lambda m: torch.cumsum(m, 0) - 1  # noqa: E731
+    word = lambda tag, row: row + (tag << 30) - ((tag >= 2) << 32)  # noqa: E731
+    home = torch.where(is_local, word(0, place(is_local)), word(2, place(~is_local))).int()
+    loc = torch.where(is_cached, word(1, place(is_cached)), home.long()).int()
+    cache = B.FeatureCache(n, int((~is_local).sum()), dim, DEV, mirror_rows=int((~is_local).sum()) if mirror else 0, home=home if mirror else None)
+    cache.loc.copy_(loc)
+    at = (home.long() & (1 << 30) - 1)[is_cached] if mirror else place(is_cached)[is_cached]
+    cache.cache_rows[at] = X[is_cached]
+    remote = X[~is_local].cpu().pin_memory()
+    ids = [_i32(rng.permutation(n)[:k]) if k else torch.zeros(1, dtype=torch.int32, device=DEV) for k in rows]
+    stats = [torch.full((3,), -7, dtype=torch.int64, device=DEV) for _ in rows]
+    for _ in range(5):                                  # every one of the running counts, and the first again
+        ctx.gather_prepare(0, ids, rows, cache, stats)
+    for j, k in enumerate(rows):
+        out = torch.full((max(k, 1), dim), -7.0, device=DEV)
+        ctx.gather_run(j, k, cache, X[is_local].contiguous(), remote, dim, out)
+        assert torch.equal(out[:k], X[ids[j][:k].long()])
+        assert stats[j].cpu().tolist() == np.bincount(kind[ids[j][:k].cpu().numpy()], minlength=3).tolist()
