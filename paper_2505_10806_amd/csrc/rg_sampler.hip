@@ -1849,10 +1849,15 @@ __global__ void __launch_bounds__(256) k_relabel(const SampleScratch S, int firs
 // whose nodes have fewer neighbours than are drawn; where nearly all have more, and the bound's edges come, calls just below them lose.
 // The frontiers' nodes count like edges: there may be more of them where a fan-out is 0 or the graph has few edges (500 k seeds 1320-1370 /
 // 73-124 us).  Larger fan-outs take longer above 65,536 nodes: (25,10) on 100 k nodes 12 k 29 / 38 / 49 against 45, 20 k 34 / 53 / 72 against 46.
+// On graphs of 70 neighbours per node or more, whose batches bring nearly the bound's edges, and where the lists don't fit LDS, the launches of the
+// byte tiers are faster from 10,500 edges (two hops) on: eight batches of 18.5 k edges on 77 k nodes of 377 neighbours 62 / 34 us, two of 16.9 k on 86 k
+// 54 / 36, one of 13.7 k on 125 k 46 / 37, of 10.1 k on 67 k 40 / 35, of 8 k on 88 k 27 / 35; three hops 17.7 k 59 / 49, 12.4 k 48 / 46, 9.4 k 38 / 46.
 constexpr int64_t kSmallNodes = 512 * 1024;     // two bitmaps of 64 KB
-inline bool rg_is_small(int64_t num_nodes, int64_t edges_bound, int64_t frontiers_bound) {
+constexpr int64_t kSmallDense = 70;
+inline bool rg_is_small(int64_t num_nodes, int64_t num_edges, int hops, bool in_lds, int64_t edges_bound, int64_t frontiers_bound) {
+    const bool few = !in_lds && num_edges >= kSmallDense * num_nodes;
     return num_nodes > 0 && num_nodes <= kSmallNodes &&
-           rg_max64(edges_bound, frontiers_bound) <= (num_nodes <= 128 * 1024 ? 20 * 1024 : 8 * 1024);
+           rg_max64(edges_bound, frontiers_bound) <= (num_nodes > 128 * 1024 ? 8 * 1024 : few ? 8500 + 1000 * hops : 20 * 1024);
 }
 
 struct Fanouts {
@@ -2536,7 +2541,7 @@ rg_status rg_sample_blocks_group(rg_ctx* ctx, const rg_csr* csr, int32_t group, 
     for (int h = 0; h < num_hops; ++h) hop_edges = rg_max64(hop_edges, eub_max[h]);
     const bool in_lds = rg_small_lists_fit(N, fub_max[num_hops - 1], hop_edges);
     const bool small = !first_seen && max_fanout <= 32 && csr->num_edges < (1ll << 32) &&
-                       (rg_is_small(N, edges_bound, frontiers_bound) ||
+                       (rg_is_small(N, csr->num_edges, num_hops, in_lds, edges_bound, frontiers_bound) ||
                         (in_lds && max_fanout <= 16 && rg_max64(edges_bound, frontiers_bound) <= kSmallEdgesPerHop * num_hops));
     // Slices whose scratch is not there and cannot be allocated (a captured call, no memory): the atomic kernels, same results.
     if (!small && (mode == kTierSliced || mode == kTierRankedSeen || mode == kTierBytes)) {

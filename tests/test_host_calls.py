@@ -349,3 +349,16 @@ assert sample(c, {n}, {edges}, {seeds}, {fanouts}) == OK, lib.rg_last_error(c)
 names = list(dict.fromkeys(k.split("<")[0] for k in kernels() if "tier" in k or "bytes" in k or "slice" in k))
 assert names == {[t.split("<")[0] for t in tier]}, names
 """)
+
+
+# One launch for batches of up to 20,480 edges, but for 10,500 (a thousand more per hop) where lists don't fit LDS on graphs of 70 neighbours per node.
+@pytest.mark.parametrize("n,edges,seeds,fanouts,small", [
+    (100_000, 7_000_000, [161], (10, 5), True), (100_000, 7_000_000, [162], (10, 5), False), (100_000, 6_999_999, [162], (10, 5), True),
+    (100_000, 7_000_000, [15], (10, 5, 10), True), (100_000, 7_000_000, [16], (10, 5, 10), False), (50_000, 7_000_000, [162], (10, 5), True),
+    (64_000, 7_000_000, [36], (25, 10), True), (64_000, 7_000_000, [40], (25, 10), False)])
+def test_batches_of_dense_graphs_that_one_launch_takes(n, edges, seeds, fanouts, small):
+    host_calls.run(f"""
+c = context()
+assert sample(c, {n}, {edges}, {seeds}, {fanouts}) == OK, lib.rg_last_error(c)
+assert (len(kernels()) == 1) == {small}
+""")
