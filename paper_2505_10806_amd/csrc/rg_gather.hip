@@ -120,20 +120,19 @@ __device__ __forceinline__ uint32_t rg_add_counts(uint32_t* gctl, int turn, unsi
 }
 
 // R rows per thread (row i0 + k * T + threadIdx.x), so that each thread has as many independent loc[] lookups in flight; the miss pairs of
-// a workgroup of T threads are appended in that visiting order (any order is valid).  One batch: 4096 rows per workgroup, because
-// their additions to its counter queue up (1024 rows to a workgroup, 776 of them 21 us for 794 k rows of a mirrored cache, now 15; 3 M rows, a
-// tenth missing, 44 / 21).  Several batches, which have a counter each: eight rows per thread (8 batches of 400 k rows, four in workgroups of 256 and of
-// 1024 threads 69, eight of 256 55).
-template <bool ONE> constexpr int kClassifyThreads = ONE ? 1024 : 256;
-template <bool ONE> constexpr int kClassifyRows = ONE ? 4 : 8;
+// a workgroup of T threads are appended in that visiting order (any order is valid).  1024 rows to a workgroup where that is what fills the
+// device (70 k rows of one batch of a mirrored cache 6 us against 10 with 4096, 200 k 9 / 11.5).  Above, one batch in workgroups of 4096, because
+// their additions to its counter queue up (776 workgroups of 1024 rows 21 us for 794 k rows of a mirrored cache, now 15; 500 k rows without a
+// mirror 9.9 / 6.4); several batches, which have a counter each, with eight rows per thread (8 batches of 500 k rows 39 / 31).
+constexpr int64_t kClassifyFew = 220000;
 
 // mirror_home != NULL: the cache is laid out as a mirror of the remote store, so a cached node's row is found at its
 // remote-store row (from its home word) instead of at its slot.
 // WIDE: batches of 2^23 rows or more, with separate counters that k_gather_reset has cleared.
-template <bool WIDE, bool ONE>
-__global__ void __launch_bounds__(kClassifyThreads<ONE>) k_classify(const ClassifyGroup C, const int32_t* __restrict__ loc,
+template <bool WIDE, int T, int R>
+__global__ void __launch_bounds__(T) k_classify(const ClassifyGroup C, const int32_t* __restrict__ loc,
                                                   const int32_t* __restrict__ mirror_home) {
-    constexpr int T = kClassifyThreads<ONE>, R = kClassifyRows<ONE>, NW = T / RG_WAVE;
+    constexpr int NW = T / RG_WAVE;
     __shared__ int smem[NW + 1];
     __shared__ int cls[2][NW];
     __shared__ uint32_t miss_base;
@@ -426,12 +425,12 @@ rg_status launch_classify(rg_ctx* ctx, int count, const int32_t* const* input_no
         RG_LAUNCH_CHECK(ctx, "k_clear_counters");
     }
     const int32_t* home = cache->mirror_rows > 0 ? cache->home : nullptr;
-#define RG_CLASSIFY(WIDE, ONE)                                                                                        \
-    k_classify<WIDE, ONE><<<dim3((unsigned)rg_max64(1, rg_div_up(n_max, kClassifyThreads<ONE> * kClassifyRows<ONE>)), (unsigned)count), \
-                            kClassifyThreads<ONE>, 0, s>>>(C, cache->loc, home)
-    if (count == 1) { if (wide) RG_CLASSIFY(true, true); else RG_CLASSIFY(false, true); }
-    else if (wide) RG_CLASSIFY(true, false);
-    else RG_CLASSIFY(false, false);
+#define RG_CLASSIFY(WIDE, T, R)                                                                                       \
+    k_classify<WIDE, T, R><<<dim3((unsigned)rg_max64(1, rg_div_up(n_max, T * R)), (unsigned)count), T, 0, s>>>(C, cache->loc, home)
+    if (wide) RG_CLASSIFY(true, 1024, 4);
+    else if (n_max <= kClassifyFew) RG_CLASSIFY(false, 256, 4);
+    else if (count > 1) RG_CLASSIFY(false, 256, 8);
+    else RG_CLASSIFY(false, 1024, 4);
 #undef RG_CLASSIFY
     RG_LAUNCH_CHECK(ctx, "k_classify");
     return RG_OK;

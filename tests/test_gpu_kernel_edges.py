@@ -1005,8 +1005,8 @@ def test_schedule_recorded_for_many_ids_survives_few(B):
     ctx.close()
 
 
-# Lookups: workgroups of 4096 rows for one batch, of 2048 for several; last ones of one row, of all.
-@pytest.mark.parametrize("rows", [[1], [4096], [4097], [200_001], [1, 0], [2048, 2049, 4095, 0, 6144]])
+# Lookups: workgroups of 1024 rows up to 220,000, above of 4096 for one batch, of 2048 for several; last ones of one row, of all.
+@pytest.mark.parametrize("rows", [[1], [1024], [1025], [220_000], [220_001], [225_280], [225_281], [1, 0], [1025, 1023, 0, 4096], [220_001, 2048, 2049, 0, 225_281]])
 @pytest.mark.parametrize("mirror", [False, True])
 def test_lookups_of_one_and_of_several_batches(B, ctx, rows, mirror):
     log(f"[lookups] rows={rows} mirror={mirror}")
