@@ -34,10 +34,13 @@ constexpr int kChunk = 1024;         // frontier nodes per workgroup in the coun
 // static bound, which for RG_FANOUT_ALL is every edge of the graph: one batch of 16 seeds, all neighbours of one / two / three hops,
 // N = 10 M with 20 edges per node 39 / 67 / 116 us by the atomic way, 50 / 106 / 172 by slices.
 // by_threads: every hop is drawn by threads or lanes.  Such calls of less than N / 16 edges take the atomic way from 512 Ki nodes on, where they
-// don't take bytes: eight batches of 19 k edges on 1.2 M nodes 50 / 58 us, on 2 M 52 / 61, of 9 k in three hops on 1.2 M 61 / 78, four of 38 k on
-// 1.5 M 50 / 60; up to N / 4 edges it would be 0.84 (one batch of 224 k on 3.4 M) to 1.9 times (eight of 264 k on 1.5 M).
-inline bool rg_use_slices(int slices, int64_t num_nodes, int64_t edges, bool by_threads) {
-    return slices > 0 && (num_nodes <= (by_threads ? 512ll << 10 : 4ll << 20) || edges >= num_nodes / 16);
+// don't take bytes and name 256 Ki edges at most in all: eight batches of 19 k edges on 1.2 M nodes 50 / 58 us, on 2 M 52 / 61, of 9 k in three hops on
+// 1.2 M 61 / 78, one of 144 k on 4.1 M 55 / 67.  Of more edges the hubs' words queue up: eight of 33 k on 0.7 M nodes of 105 neighbours 67 / 58, three
+// of 170 k on 3 M 104 / 98, eight of 157 k on 3.7 M 144 / 97.
+inline bool rg_use_slices(int slices, int64_t num_nodes, int64_t edges, int group, bool by_threads) {
+    if (slices <= 0) return false;
+    const bool few = by_threads && edges * group <= 256ll << 10;
+    return num_nodes <= (few ? 512ll << 10 : 4ll << 20) || edges >= num_nodes / 16;
 }
 // Edges per hop of a batch of `seeds` nodes whose degrees are the graph's average, eub[] at most; returns their sum.
 inline int64_t rg_expected_edges(int64_t num_nodes, int64_t num_edges, int64_t seeds, const int32_t* fanouts, int num_hops,
@@ -67,7 +70,7 @@ enum TierMode { kTierSliced = 0, kTierAtomic = 1, kTierFirstSeen = 2, kTierRanke
 // bound it above: 2 batches, N = 10 M, 8 M edges each 0.80-0.82, 16 M 0.85-1.12; N = 40 M 0.87 and 0.94-1.10.
 constexpr int64_t kRankedSeenMin = 2200 * 1000;
 inline bool rg_use_ranked_seen(int slices, int64_t num_nodes, int64_t edges, int group) {
-    return rg_use_slices(slices, num_nodes, edges, false) && group >= 2 && num_nodes * group * group >= 9000 * 1000 &&
+    return rg_use_slices(slices, num_nodes, edges, group, false) && group >= 2 && num_nodes * group * group >= 9000 * 1000 &&
            edges * group >= kRankedSeenMin && edges <= 2 * group * num_nodes;
 }
 constexpr int64_t kRankedSeenEdges = 8ll << 20;      // per hop and batch at most
@@ -2531,7 +2534,7 @@ rg_status rg_sample_blocks_group(rg_ctx* ctx, const rg_csr* csr, int32_t group, 
     for (int g = 0; g < group && ranked_seen; ++g)
         for (int h = 0; h < num_hops; ++h)
             ranked_seen = ranked_seen && eub_max[h] <= kRankedSeenEdges && out[g].nbr_local && out[g].nbr_local[h] && out[g].nbr_local[h] != out[g].nbr[h];
-    TierMode mode = ranked_seen ? kTierRankedSeen : first_seen ? kTierFirstSeen : (rg_use_slices(S.slices, N, edges, by_threads) ? kTierSliced : kTierAtomic);
+    TierMode mode = ranked_seen ? kTierRankedSeen : first_seen ? kTierFirstSeen : (rg_use_slices(S.slices, N, edges, group, by_threads) ? kTierSliced : kTierAtomic);
     if (!first_seen && by_threads && rg_use_bytes(N, words, edges, group)) mode = kTierBytes;
     rg_status st = rg_sampler_reserve(ctx, N, fub_max[num_hops], group, max_edges, first_seen);
     if (st != RG_OK) return st;

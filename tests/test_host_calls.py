@@ -330,13 +330,13 @@ for n, grid in ((1, 1), (4097, 2), (8 << 20, 256), ((8 << 20) + 1, 512)):
 
 
 # Tiers from bytes by edges times nodes of all batches, up to 4 Mi nodes and two byte maps of 41 MB; counted by the emit up to 160,000 nodes.
-# Beyond that the atomic marking for less than a 16th of the nodes' number of edges.
+# Beyond that the atomic marking for less than a 16th of the nodes' number of edges and 256 Ki in all.
 @pytest.mark.parametrize("n,edges,seeds,fanouts,tier", [
     (232_965, 114_000_000, [1024], (25, 10), ["k_bytes_count", "k_tier_emit_small"]), (160_000, 9_000_000, [1024], (25, 10), ["k_bytes_emit_small"]),
     (160_001, 9_000_000, [1024], (25, 10), ["k_bytes_count", "k_tier_emit_small"]), (1_600_000, 9_000_000, [10] * 16, (10, 5), ["k_bytes_count", "k_tier_emit"]),
     (60_000, 9_000_000, [200] * 16, (25, 10), ["k_bytes_emit_small"]), (24_577, 9_000_000, [1536] * 16, (25, 10), ["k_bytes_emit_small"]),
     (4_194_304, 90_000_000, [100], (10, 5), ["k_bytes_count", "k_tier_emit_small"]), (4_194_305, 90_000_000, [100], (10, 5), ["k_tier_count", "k_tier_emit"]),
-    (2_000_000, 90_000_000, [300] * 8, (25, 10), ["k_tier_count", "k_tier_emit"]), (2_000_000, 90_000_000, [500] * 8, (25, 10), ["k_slice_mark", "k_slice_count", "k_slice_emit"]),
+    (2_000_000, 90_000_000, [114] * 8, (25, 10), ["k_tier_count", "k_tier_emit"]), (2_000_000, 90_000_000, [115] * 8, (25, 10), ["k_slice_mark", "k_slice_count", "k_slice_emit"]),
     (1_000_000, 90_000_000, [3600], (10, 100), ["k_slice_mark", "k_slice_count<192, 1>", "k_slice_emit_small<false>"]),
     (1_900_000, 90_000_000, [10_000], (20, 9), ["k_bytes_count", "k_tier_emit_small"]),
     (1_900_000, 90_000_000, [10_100], (20, 9), ["k_slice_mark", "k_slice_count<192, 1>", "k_slice_emit_small<false>"]),
