@@ -7,6 +7,8 @@
 // kernels read the actual counts.
 #include <string.h>
 
+#include <type_traits>
+
 #include "rg_internal.h"
 
 namespace {
@@ -1123,12 +1125,31 @@ __global__ void __launch_bounds__(T) k_slice_count(const SampleScratch S) {
     }
 }
 
+// Where a workgroup keeps its new ids until consecutive lanes store them: as distances from its first id where its LDS decides how many workgroups
+// a compute unit takes (three words to a thread: 33 KB, four workgroups; 17 KB, eight: the emits of three hops of 8 stress batches 24 + 48 + 25 us,
+// now 21.5 + 46 + 23), else as they are (a distance more to add: 1 % of calls of 50 us).
+template <int W> using EmitId = typename std::conditional<W == 1, int32_t, uint16_t>::type;
+
+// The ids of the bits of word `w` of a workgroup's words, from place j on, which moves on behind them: into LDS, or to nodes[].
+template <class Id>
+__device__ __forceinline__ void rg_put_ids(uint32_t bits, int w, bool in_lds, Id* ids, int32_t* __restrict__ nodes, int32_t first_id, int& j) {
+    if constexpr (sizeof(Id) == 4) {
+        int32_t* dst = in_lds ? ids : nodes;
+        for (uint32_t b = bits; b; b &= b - 1u) dst[j++] = first_id + (w << 5) + __ffs(b) - 1;
+    } else if (in_lds) {
+        for (uint32_t b = bits; b; b &= b - 1u) ids[j++] = (Id)((w << 5) + __ffs(b) - 1);
+    } else {
+        for (uint32_t b = bits; b; b &= b - 1u) nodes[j++] = first_id + (w << 5) + __ffs(b) - 1;
+    }
+}
+
 // What k_hop_count does for the next hop, by the kernels that emit a tier of ascending ids: the rows of its `total` nodes from position
 // `out` on, and their edges per chunk; the edges of the nodes in front of them, a chunk to a workgroup.
-// in_lds: the new ids are in LDS and go to nodes[] here; else they are there already.  POS: their positions go to pos[] too.
-template <int T, bool POS>
+// in_lds: the new ids are in LDS (EmitId) and go to nodes[] here; else they are there already.  POS: their positions go to pos[] too.
+template <int T, bool POS, class Id>
 __device__ __forceinline__ void rg_new_rows(const RowPtr& row_ptr, const SampleScratch& S, int g, int hop, int out, int total,
-                                            int32_t* __restrict__ nodes, const int32_t* ids, bool in_lds, int* edges, int num_chunks, int next_fanout) {
+                                            int32_t* __restrict__ nodes, const Id* ids, int32_t first_id, bool in_lds, int* edges, int num_chunks,
+                                            int next_fanout) {
     constexpr int U = 4;                                 // rows in flight per thread
     int32_t* __restrict__ pos = S.pos + g * S.num_nodes;
     int64_t* __restrict__ row_start = S.row_start + g * S.frontier_stride + out;
@@ -1139,7 +1160,10 @@ __device__ __forceinline__ void rg_new_rows(const RowPtr& row_ptr, const SampleS
 #pragma unroll
         for (int q = 0; q < U; ++q) {
             v[q] = -1;
-            if (i0 + T * q < total) v[q] = in_lds ? ids[i0 + T * q] : nodes[i0 + T * q];
+            if (i0 + T * q >= total) continue;
+            if constexpr (sizeof(Id) == 4) v[q] = in_lds ? ids[i0 + T * q] : nodes[i0 + T * q];
+            else if (in_lds) v[q] = first_id + ids[i0 + T * q];
+            else v[q] = nodes[i0 + T * q];
         }
         if (in_lds) {
 #pragma unroll
@@ -1189,13 +1213,13 @@ __device__ __forceinline__ void rg_old_edges(const SampleScratch& S, int g, int 
 
 // Emits the new tier behind the current frontier, ascending, with its rank blocks, and makes its ids frontier members.  The
 // ids go through LDS so that they are stored by consecutive lanes (thread by thread: 135 us at hop 2 of 8 batches, 7.5 M ids;
-// now 25); a workgroup with more new ids than fit there (over a third of its range) stores them directly.
+// now 23); a workgroup with more new ids than fit there (over a third of its range) stores them directly.
 // A thread takes W words: three, which are two rank blocks, or one where few workgroups leave the serial walk over the bits of a
 // word as what takes time; the words then meet in LDS.
 // RANKED_SEEN: the positions are ascending ones only, the nodes come later.
 // next_fanout >= 0: also what k_hop_count does for the next hop, the new nodes' rows here, where their ids are at hand and ascending, and
 // their edges per chunk; those of the nodes in front of them by the workgroups behind the tier_blocks.  (Hop 1 of the same batches,
-// 3.3 M rows: 49 us with the next hop's sizes, 20 + 44 apart; on XCDs of their own, without sharing lines of row_ptr, 65.)
+// 3.3 M rows: 46 us with the next hop's sizes, 20 + 44 apart; on XCDs of their own, without sharing lines of row_ptr, 65.)
 template <bool RANKED_SEEN, int T, int W, int WORDS = T * W>
 __device__ __forceinline__ void rg_slice_emit(const RowPtr& row_ptr, const SampleScratch& S, int hop,
                                               unsigned tier_blocks, int next_fanout, int run) {
@@ -1204,7 +1228,8 @@ __device__ __forceinline__ void rg_slice_emit(const RowPtr& row_ptr, const Sampl
     constexpr unsigned per_base = kBaseIds / (32 * WORDS);               // workgroups to a base
     __shared__ int smem[NW + 1];
     __shared__ int part[NW], part_above[NW];
-    __shared__ int32_t ids[RANKED_SEEN ? 1 : kEmitIds];
+    __shared__ EmitId<W> ids[RANKED_SEEN ? 1 : kEmitIds];
+    static_assert(WORDS * 32 <= 1 << 16, "ids are kept as 16-bit distances");
     __shared__ uint32_t word_bits[W == 1 ? TW : 1];
     __shared__ int word_rank[W == 1 ? TW : 1];
     __shared__ int edges[WORDS * 32 / kChunk + 2];
@@ -1247,7 +1272,8 @@ __device__ __forceinline__ void rg_slice_emit(const RowPtr& row_ptr, const Sampl
     for (int q = 0; q < NW; ++q) base -= part_above[q];
     if (threadIdx.x == 0 && blk == base_blk) rg_rank_bases(S, g, hop)[blk / per_base] = base;
     int32_t* __restrict__ nodes = rg_nodes(S, g) + out;
-    int32_t* dst = total <= kEmitIds ? ids : nodes;
+    const bool in_lds = total <= kEmitIds;
+    const int32_t first_id = (int32_t)((int64_t)blk * WORDS * 32);
     const RankBlocks rank = rg_rank_blocks(S, g, hop);
     const auto store_rank = [&](int64_t r, uint32_t b0, uint32_t b1, uint32_t b2, uint32_t above) {      // three words: two rank blocks
         rank.at[2 * r * rank.stride] = make_uint2(b0, (b1 & 0xFFFFu) | above << 16);
@@ -1265,8 +1291,7 @@ __device__ __forceinline__ void rg_slice_emit(const RowPtr& row_ptr, const Sampl
 #pragma unroll
     for (int q = 0; q < W; ++q) {
         if (bits[q]) visited[w + q] = members[q] | bits[q];
-        if (!RANKED_SEEN)
-            for (uint32_t b = bits[q]; b; b &= b - 1u) dst[j++] = (int32_t)((w + q) << 5) + __ffs(b) - 1;
+        if (!RANKED_SEEN) rg_put_ids<EmitId<W>>(bits[q], (int)threadIdx.x * W + q, in_lds, ids, nodes, first_id, j);
     }
     if (RANKED_SEEN && W == 3) return;
     __syncthreads();                                     // ids, nodes, words and edges are there
@@ -1276,7 +1301,7 @@ __device__ __forceinline__ void rg_slice_emit(const RowPtr& row_ptr, const Sampl
         if (3 * r < S.words) store_rank(r, word_bits[q], word_bits[q + 1], word_bits[q + 2], (uint32_t)word_rank[q]);
     }
     if (RANKED_SEEN) return;
-    rg_new_rows<T, false>(row_ptr, S, g, hop, out, total, nodes, ids, total <= kEmitIds, edges, (int)(sizeof(edges) / sizeof(int)), next_fanout);
+    rg_new_rows<T, false, EmitId<W>>(row_ptr, S, g, hop, out, total, nodes, ids, first_id, in_lds, edges, (int)(sizeof(edges) / sizeof(int)), next_fanout);
 }
 
 template <bool RANKED_SEEN>
@@ -1349,7 +1374,8 @@ __device__ __forceinline__ void rg_tier_emit(const RowPtr& row_ptr, const Sample
     constexpr int NW = T / RG_WAVE, W = WORDS > T ? WORDS / T : 1, TW = WORDS / W, kEmitIds = W == 1 ? WORDS * 32 : WORDS * 32 / 3;
     __shared__ int smem[NW + 1];
     __shared__ int part[NW];
-    __shared__ int32_t ids[kEmitIds];
+    __shared__ EmitId<W> ids[kEmitIds];
+    static_assert(WORDS * 32 <= 1 << 16, "ids are kept as 16-bit distances");
     __shared__ int edges[WORDS * 32 / kChunk + 2];
     int g;
     unsigned blk;
@@ -1411,12 +1437,12 @@ __device__ __forceinline__ void rg_tier_emit(const RowPtr& row_ptr, const Sample
     if (threadIdx.x == 0 && blk + 1 == tier_blocks) rg_tier_off(S, g)[hop + 2] = out + total;
     if (total == 0) return;                              // uniform
     int32_t* __restrict__ nodes = rg_nodes(S, g) + out;
-    int32_t* dst = total <= kEmitIds ? ids : nodes;
+    const bool in_lds = total <= kEmitIds;
+    const int32_t first_id = (int32_t)((int64_t)blk * WORDS * 32);
 #pragma unroll
-    for (int q = 0; q < W; ++q)
-        for (uint32_t b = bits[q]; b; b &= b - 1u) dst[j++] = (int32_t)((w + q) << 5) + __ffs(b) - 1;
+    for (int q = 0; q < W; ++q) rg_put_ids<EmitId<W>>(bits[q], (int)threadIdx.x * W + q, in_lds, ids, nodes, first_id, j);
     __syncthreads();                                     // ids, nodes and edges are there
-    rg_new_rows<T, true>(row_ptr, S, g, hop, out, total, nodes, ids, total <= kEmitIds, edges, num_chunks, next_fanout);
+    rg_new_rows<T, true, EmitId<W>>(row_ptr, S, g, hop, out, total, nodes, ids, first_id, in_lds, edges, num_chunks, next_fanout);
 }
 
 __global__ void __launch_bounds__(kTierWords / 3) k_tier_emit(const RowPtr row_ptr, const SampleScratch S, int hop, unsigned tier_blocks,
