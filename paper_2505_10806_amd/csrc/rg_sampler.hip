@@ -1535,9 +1535,9 @@ __global__ void __launch_bounds__(256) k_first_seen_emit(const RowPtr row_ptr, c
         if (!scanned) {
             for (int64_t b = added + threadIdx.x; b < chunk; b += 256) c += chunk_sum[b];
             added = chunk;
-        } else if (threadIdx.x == 0) {
-            c = chunk_sum[chunk];
-            before = n_h;
+        } else {
+            if (threadIdx.x == 0) c = chunk_sum[chunk];
+            before = n_h;                                          // (by every thread: the rounds before have added theirs)
         }
         c = rg_wave_sum(c);
         __syncthreads();                                           // part[] and edges[] of the chunk before have been read

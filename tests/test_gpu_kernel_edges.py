@@ -1032,3 +1032,22 @@ def test_lookups_of_one_and_of_several_batches(B, ctx, rows, mirror):
         ctx.gather_run(j, k, cache, X[is_local].contiguous(), remote, dim, out)
         assert torch.equal(out[:k], X[ids[j][:k].long()])
         assert stats[j].cpu().tolist() == np.bincount(kind[ids[j][:k].cpu().numpy()], minlength=3).tolist()
+
+
+# First-seen order by first edges where workgroups take several chunks of the edge list behind a scan: active nodes of far more neighbours than the
+# average, and a bound of more than 4096 chunks.
+def test_first_seen_chunks_behind_a_scan(B, ctx):
+    log("[first seen] several chunks to a workgroup behind a scan")
+    n, fanouts, rng = 9_000_000, (1, 33), np.random.default_rng(4)
+    deg = np.zeros(n, dtype=np.int64)
+    ids = rng.permutation(n)[:300_000]
+    deg[ids] = rng.choice([0, 1, 20, 34], ids.size)
+    rp = np.concatenate([[0], np.cumsum(deg)])
+    ci = rng.integers(0, n, rp[-1]).astype(np.int32)
+    ci[::2] = rng.choice(ids, ci[::2].size)
+    csr = B.CsrGraph(torch.as_tensor(rp, device=DEV).to(torch.int32), _i32(ci))
+    seeds = rng.permutation(ids)[:200_000].astype(np.int32)
+    out = B.BlockBuffers(n, ci.size, seeds.size, fanouts, DEV)
+    ctx.sample_blocks_group(csr, [_i32(seeds)], fanouts, 77, 1, [out], node_order=B.RG_ORDER_FIRST_SEEN)
+    orc = oracle.sample_blocks(rp, ci, seeds, fanouts, 77, 1, oracle.ORDER_FIRST_SEEN)
+    assert_batch_equal(HipBatch(out, len(fanouts)), orc, len(fanouts), "batch")
