@@ -764,8 +764,8 @@ __device__ __forceinline__ void rg_clear_next_sum(const SampleScratch& S, int g,
     for (int64_t c = thread; c <= S.frontier_stride / kChunk; c += threads) next_sum[c] = 0;
 }
 
-// General sampler: one wavefront (= one 64-thread workgroup) per frontier node, any fan-out up to
-// RG_MAX_FANOUT.  The Floyd set lives in LDS; step i tests membership of t with all lanes.
+// General sampler (fan-outs above 64, all neighbours, more than kWideNodes): one wavefront (= one 64-thread workgroup) per frontier node, any
+// fan-out up to RG_MAX_FANOUT.  The Floyd set lives in LDS; step i tests membership of t with all lanes.
 template <int MODE>
 __global__ void __launch_bounds__(RG_WAVE) k_hop_sample_wave(const int32_t* __restrict__ col_idx, const SampleScratch S, int fanout, uint32_t hop, uint32_t k0,
                                                             uint32_t k1, uint32_t epoch) {
@@ -942,8 +942,12 @@ __global__ void __launch_bounds__(256) k_hop_sample_thread(const int32_t* __rest
 // Draws (lanes) of a hop for which k_hop_sample_lanes is faster: 1024 nodes of 25 neighbours 11.2 -> 7.2 us, three batches' 78 k nodes of 10
 // (1.25 M lanes) make the call 66 us against 63.  With fan-outs up to 16 a thread per node takes less (10: 5.4 against 7.4 us, 5: 4.7 / 6.6).
 constexpr int64_t kLaneDraws = 1 << 18;
+// Frontier nodes up to which it draws for fan-outs of 33 to 64, where the other way is a wavefront per node with its set in LDS behind two launches for
+// the offsets: 64 of 0.5 M nodes 680 us a call against 1014, 40 of 2.4 M 1436 / 1773, 64 of eight batches of 91 nodes 33 / 60.  (Beyond, every
+// workgroup of four nodes adding up the chunks in front of it would be what takes time.)
+constexpr int64_t kWideNodes = 1 << 22, kWideNodesAll = 1 << 24;
 
-// The same for few frontier nodes of large fan-outs: KMAX lanes per node, one draw each, no staging.  Floyd's set by itself: draw s is taken already if an
+// The same for few frontier nodes of large fan-outs, and all of 33 to 64: KMAX lanes per node, one draw each, no staging.  Floyd's set by itself: draw s is taken already if an
 // earlier draw has its value, or if its value is the last position j_l of an earlier step l that found its own draw taken.
 template <int KMAX, int MODE>
 __global__ void __launch_bounds__(256) k_hop_sample_lanes(const int32_t* __restrict__ col_idx, const SampleScratch S, int fanout, uint32_t hop, uint32_t k0,
@@ -986,7 +990,10 @@ __global__ void __launch_bounds__(256) k_hop_sample_lanes(const int32_t* __restr
         const uint32_t j0 = (uint32_t)(deg - k), j = j0 + (uint32_t)lane;      // Floyd: j = d-k+s, t uniform in [0, j]
         const uint32_t t = __umulhi(word, j + 1u);
         bool taken = false;
-        for (int l = 0; l + 1 < k; ++l) taken |= (uint32_t)__shfl((int)t, l, KMAX) == t && l < lane;
+        for (int l = 0; l + 1 < k; ++l) {
+            if constexpr (KMAX == RG_WAVE) taken |= (uint32_t)__builtin_amdgcn_readlane((int)t, l) == t && l < lane;
+            else taken |= (uint32_t)__shfl((int)t, l, KMAX) == t && l < lane;
+        }
         const int node0 = rg_lane() & ~(KMAX - 1);
         const int l = (int)(t - j0);                     // the step whose last position t is
         const bool late = deg > k && t >= j0 && l < lane;
@@ -2553,8 +2560,12 @@ rg_status rg_sample_blocks_group(rg_ctx* ctx, const rg_csr* csr, int32_t group, 
     for (int h = 0; h < num_hops; ++h) { edges_bound += eub_max[h]; frontiers_bound += fub_max[h]; }
     int64_t expected[RG_MAX_HOPS];
     const int64_t edges = rg_expected_edges(N, csr->num_edges, seeds_max, fanouts, num_hops, eub_max, expected);
-    bool by_threads = csr->num_edges < (1ll << 32);
-    for (int h = 0; h < num_hops; ++h) by_threads = by_threads && fanouts[h] >= 1 && fanouts[h] <= 32;
+    // Hops that a thread or a few lanes per node draw for; these need no offsets per node.
+    const auto drawn_by_threads = [&](int h) {
+        return fanouts[h] >= 1 && (fanouts[h] <= 32 || (fanouts[h] <= RG_WAVE && fub_max[h] <= kWideNodes && fub_max[h] * group <= kWideNodesAll)) && csr->num_edges < (1ll << 32);
+    };
+    bool by_threads = true;
+    for (int h = 0; h < num_hops; ++h) by_threads = by_threads && drawn_by_threads(h);
     // in first-seen order the edges' ascending positions are kept where their final ones go
     bool ranked_seen = first_seen && rg_use_ranked_seen(S.slices, N, edges, group);
     for (int g = 0; g < group && ranked_seen; ++g)
@@ -2662,8 +2673,6 @@ rg_status rg_sample_blocks_group(rg_ctx* ctx, const rg_csr* csr, int32_t group, 
         ctx->sampler_dirty = true;       // cleared again when every launch of this call has been queued
     }
     const RowPtr row_ptr = {csr->row_ptr, rp64};
-    // Hops that a thread or a few lanes per node draw for; these need no offsets per node.
-    const auto drawn_by_threads = [&](int h) { return fanouts[h] >= 1 && fanouts[h] <= 32 && csr->num_edges < (1ll << 32); };
     int counted = -1;                                  // the hop whose sizes are there already
     // Small workgroups for the tiers while large ones would leave compute units without work: one batch on 233 k nodes 69 us a call with large, 56 with
     // small ones, on 380 k 150 / 117; 369 large ones (3 batches, 3 M nodes) 147 / 158, 648 (8 batches, 2 M) 120 / 140.
@@ -2770,7 +2779,7 @@ rg_status rg_sample_blocks_group(rg_ctx* ctx, const rg_csr* csr, int32_t group, 
     k_hop_sample_lanes<KM, MODE><<<(unsigned)grid_for(fub_max[h], 256 / KM, 1ll << 30) * ug, 256, 0, s>>>(csr->col_idx, S, F, (uint32_t)h, k0, k1, epoch)
 #define RG_LAUNCH_DRAW_K(NP, MODE)                                                                                    \
     do { if (F <= 8) RG_LAUNCH_DRAW(8, NP, MODE); else if (F <= 16) RG_LAUNCH_DRAW(16, NP, MODE); else RG_LAUNCH_DRAW(32, NP, MODE); } while (0)
-#define RG_LAUNCH_DRAW_N(MODE) do { if (lanes) RG_LAUNCH_LANES(32, MODE); else if (few) RG_LAUNCH_DRAW_K(64, MODE); else RG_LAUNCH_DRAW_K(256, MODE); } while (0)
+#define RG_LAUNCH_DRAW_N(MODE) do { if (F > 32) RG_LAUNCH_LANES(64, MODE); else if (lanes) RG_LAUNCH_LANES(32, MODE); else if (few) RG_LAUNCH_DRAW_K(64, MODE); else RG_LAUNCH_DRAW_K(256, MODE); } while (0)
             if (mode == kTierSliced || mode == kTierRankedSeen) RG_LAUNCH_DRAW_N(kTierSliced);
             else if (mode == kTierAtomic) RG_LAUNCH_DRAW_N(kTierAtomic);
             else if (mode == kTierBytes) RG_LAUNCH_DRAW_N(kTierBytes);

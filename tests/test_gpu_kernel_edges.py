@@ -1051,3 +1051,26 @@ def test_first_seen_chunks_behind_a_scan(B, ctx):
     ctx.sample_blocks_group(csr, [_i32(seeds)], fanouts, 77, 1, [out], node_order=B.RG_ORDER_FIRST_SEEN)
     orc = oracle.sample_blocks(rp, ci, seeds, fanouts, 77, 1, oracle.ORDER_FIRST_SEEN)
     assert_batch_equal(HipBatch(out, len(fanouts)), orc, len(fanouts), "batch")
+
+
+# A lane per draw for fan-outs of 33 to 64 (four nodes to a workgroup), a wavefront per node above; rows of about as many neighbours as
+# are drawn, where most draws find theirs taken.
+@pytest.mark.parametrize("n,fanouts,seeds", [(3001, (33, 2), [5, 0, 4]), (3001, (64, 3), [1, 130]), (70_001, (63, 2), [257]), (70_001, (65, 2), [257]),
+                                             (70_001, (5, 64), [600] * 2), (600_001, (2, 64, 33), [700, 0, 699]), (9_000_000, (64, 3), [120, 1]),
+                                             (9_000_000, (1, 33), [262_144])])
+@pytest.mark.parametrize("first_seen", [False, True])
+def test_draws_of_33_to_64(B, ctx, n, fanouts, seeds, first_seen):
+    log(f"[wide draws] N={n} fanouts={fanouts} seeds={seeds} first_seen={first_seen}")
+    rng, k = np.random.default_rng(n + len(fanouts)), max(fanouts)
+    deg = np.zeros(n, dtype=np.int64)
+    ids = rng.permutation(n)[:min(n, 300_000)]
+    deg[ids] = rng.choice([0, 1, k - 1, k, k + 1, k + 2, 2 * k], ids.size) if sum(seeds) < 100_000 else rng.choice([0, 1, 33, 34], ids.size)
+    rp = np.concatenate([[0], np.cumsum(deg)])
+    ci = rng.choice(ids, rp[-1]).astype(np.int32)
+    csr = B.CsrGraph(torch.as_tensor(rp, device=DEV).to(torch.int32), _i32(ci))
+    lists = [rng.permutation(ids)[:s].astype(np.int32) for s in seeds]
+    outs = [B.BlockBuffers(n, ci.size, max(s, 1), fanouts, DEV) for s in seeds]
+    ctx.sample_blocks_group(csr, [_i32(x) for x in lists], fanouts, 77, 1, outs, node_order=B.RG_ORDER_FIRST_SEEN if first_seen else B.RG_ORDER_ASCENDING)
+    for j, o in enumerate(outs):
+        orc = oracle.sample_blocks(rp, ci, lists[j], fanouts, 77, 1, oracle.ORDER_FIRST_SEEN if first_seen else oracle.ORDER_ASCENDING)
+        assert_batch_equal(HipBatch(o, len(fanouts)), orc, len(fanouts), f"batch {j}")
