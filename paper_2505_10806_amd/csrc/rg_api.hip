@@ -80,10 +80,10 @@ rg_status rg_gather_reserve(rg_ctx* ctx, int64_t rows) {
 // A value that `earlier` writes and `later` waits for costs the host 5 us, an event that is recorded and waited for 8 to 14 (by machine).  Two-stream
 // gathers, which order the streams twice: 4 k rows of 64 floats 41 -> 21 us, 7.5 k of 100 in HBM 44 -> 21, 40 k of 100 45 -> 37, 10 k misses of 602
 // 202 -> 199.  Every signal has one write on its way at most, its values only grow, and a wait is queued behind its write, so that every wait
-// ends.  While the signal that is next has not been written yet (the device is 128 orders behind: with 32 of them 2736 rows of 256, a third missing,
+// ends.  On the device a write and a wait take longer than the events' (by_value says whether the host's time is what counts).  While the signal that is next has not been written yet (the device is 128 orders behind: with 32 of them 2736 rows of 256, a third missing,
 // 39 us instead of 35), and for streams that record a graph, there are the events.
-rg_status rg_stream_after(rg_ctx* ctx, hipStream_t later, hipStream_t earlier, hipEvent_t event) {
-    if (ctx->stream_values && !rg_capturing(later) && !rg_capturing(earlier)) {
+rg_status rg_stream_after(rg_ctx* ctx, hipStream_t later, hipStream_t earlier, hipEvent_t event, bool by_value) {
+    if (by_value && ctx->stream_values && !rg_capturing(later) && !rg_capturing(earlier)) {
         RgSignal& s = ctx->signals[ctx->signal_value % (sizeof(ctx->signals) / sizeof(ctx->signals[0]))];
         if (!s.at) {
             if (hipExtMallocWithFlags((void**)&s.at, sizeof(uint64_t), hipMallocSignalMemory) == hipSuccess) {

@@ -443,6 +443,11 @@ int gather_vec(int32_t dim, const rg_cache* cache, const float* local_store, int
     return rg_pick_vec(dim, ptrs, 4, strides, 4);
 }
 
+// Bytes of a batch up to which two streams are ordered by values, with which the host's calls are no longer what takes time; on the device they take
+// longer than events, which are used above (values / events, buffers in turn): one launch of 13 MB 31 / 40 us, of 16 MB 43 / 40, of 15 MB with a fifth of the rows
+// missing 69 / 69, of 22 MB 78 / 76, of 24 MB 45 / 41; three launches of 45 MB 38 / 52, of 63 MB 49 / 52, of 129 MB 72 / 69, of 139 MB 78 / 75.
+constexpr int64_t kValueBytes = 64ll << 20, kValueBytesFused = 14ll << 20;
+
 // Copies the rows of one classified batch: HBM rows on sh, miss rows on sm (joined back into sh when they differ).
 // Every argument has been validated by the caller; `timed` brackets the kernels for rg_profile_read.
 rg_status launch_copies(rg_ctx* ctx, const GatherScratch& scr, int64_t n, const int32_t* n_dev, const rg_cache* cache,
@@ -451,8 +456,9 @@ rg_status launch_copies(rg_ctx* ctx, const GatherScratch& scr, int64_t n, const 
                         int parts = RG_GATHER_PART_HBM | RG_GATHER_PART_MISS) {
     const bool do_hbm = parts & RG_GATHER_PART_HBM, do_miss = parts & RG_GATHER_PART_MISS;
     const bool two_streams = sm != sh && do_hbm && do_miss;      // one part alone: no fork, no join, the caller orders the streams
+    const bool by_value = n * (int64_t)dim * 4 <= kValueBytes;
     if (two_streams) {
-        const rg_status st = rg_stream_after(ctx, sm, sh, ctx->ev_classified);
+        const rg_status st = rg_stream_after(ctx, sm, sh, ctx->ev_classified, by_value);
         if (st != RG_OK) return st;
     }
     const int vec = gather_vec(dim, cache, local_store, local_stride, remote_store, remote_stride, out, out_stride);
@@ -502,7 +508,7 @@ rg_status launch_copies(rg_ctx* ctx, const GatherScratch& scr, int64_t n, const 
         RG_LAUNCH_CHECK(ctx, "k_gather_miss");
     }
     if (two_streams) {
-        const rg_status st = rg_stream_after(ctx, sh, sm, ctx->ev_miss_done);
+        const rg_status st = rg_stream_after(ctx, sh, sm, ctx->ev_miss_done, by_value);
         if (st != RG_OK) return st;
     }
     return RG_OK;
@@ -522,8 +528,9 @@ bool rg_fits_fused(int64_t n, int32_t dim, int vec, hipStream_t sh, hipStream_t 
 rg_status launch_fused(rg_ctx* ctx, const GatherScratch& scr, const int32_t* nodes, int64_t n, const int32_t* n_dev, const rg_cache* cache,
                        const float* local_store, int64_t local_stride, const float* remote_store, int64_t remote_stride, int32_t dim,
                        float* out, int64_t out_stride, rg_gather_stats* stats, hipStream_t sh, hipStream_t sm, bool captured) {
+    const bool by_value = n * (int64_t)dim * 4 <= kValueBytesFused;
     if (sm != sh) {
-        const rg_status st = rg_stream_after(ctx, sh, sm, ctx->ev_classified);
+        const rg_status st = rg_stream_after(ctx, sh, sm, ctx->ev_classified, by_value);
         if (st != RG_OK) return st;
     }
     const int vec = gather_vec(dim, cache, local_store, local_stride, remote_store, remote_stride, out, out_stride);
@@ -547,7 +554,7 @@ rg_status launch_fused(rg_ctx* ctx, const GatherScratch& scr, const int32_t* nod
 #undef RG_LAUNCH_FUSED
     RG_LAUNCH_CHECK(ctx, "k_gather_fused");
     if (sm != sh) {
-        const rg_status st = rg_stream_after(ctx, sm, sh, ctx->ev_miss_done);
+        const rg_status st = rg_stream_after(ctx, sm, sh, ctx->ev_miss_done, by_value);
         if (st != RG_OK) return st;
     }
     return RG_OK;

@@ -115,7 +115,7 @@ static inline bool rg_capturing(hipStream_t s) {
     return status == hipStreamCaptureStatusActive;
 }
 // What `later` is given from now on waits for what `earlier` has been given.  `event` is for calls that the streams' values cannot serve.
-rg_status rg_stream_after(rg_ctx* ctx, hipStream_t later, hipStream_t earlier, hipEvent_t event);
+rg_status rg_stream_after(rg_ctx* ctx, hipStream_t later, hipStream_t earlier, hipEvent_t event, bool by_value);
 // Scratch with which no epoch histogram on num_nodes nodes allocates anything; the same.
 rg_status rg_histogram_reserve(rg_ctx* ctx, int64_t num_nodes);
 // Makes every gather ticket hold at least `rows` rows (a reallocation invalidates prepared tickets).
