@@ -81,25 +81,15 @@ rg_status rg_gather_reserve(rg_ctx* ctx, int64_t rows) {
 // gathers, which order the streams twice: 4 k rows of 64 floats 41 -> 21 us, 7.5 k of 100 in HBM 44 -> 21, 40 k of 100 45 -> 37, 10 k misses of 602
 // 202 -> 199.  Every signal has one write on its way at most, its values only grow, and a wait is queued behind its write, so that every wait
 // ends.  On the device a write and a wait take longer than the events' (by_value says whether the host's time is what counts).  While the signal that is next has not been written yet (the device is 128 orders behind: with 32 of them 2736 rows of 256, a third missing,
-// 39 us instead of 35), and for streams that record a graph, there are the events.
+// 39 us instead of 35), for streams that record a graph, and once the runtime has refused a write or a wait, there are the events.
 rg_status rg_stream_after(rg_ctx* ctx, hipStream_t later, hipStream_t earlier, hipEvent_t event, bool by_value) {
     if (by_value && ctx->stream_values && !rg_capturing(later) && !rg_capturing(earlier)) {
         RgSignal& s = ctx->signals[ctx->signal_value % (sizeof(ctx->signals) / sizeof(ctx->signals[0]))];
-        if (!s.at) {
-            if (hipExtMallocWithFlags((void**)&s.at, sizeof(uint64_t), hipMallocSignalMemory) == hipSuccess) {
-                __atomic_store_n(s.at, 0ull, __ATOMIC_RELEASE);
-            } else {
-                (void)hipGetLastError();
-                s.at = nullptr;
-                ctx->stream_values = false;
-            }
-        }
-        if (s.at && __atomic_load_n(s.at, __ATOMIC_ACQUIRE) == s.value) {
+        if (__atomic_load_n(s.at, __ATOMIC_ACQUIRE) == s.value) {
             const uint64_t value = ctx->signal_value + 1;
             if (hipStreamWriteValue64(earlier, s.at, value, 0) == hipSuccess) {
                 s.value = ctx->signal_value = value;
-                RG_HIP(ctx, hipStreamWaitValue64(later, s.at, value, hipStreamWaitValueGte, ~0ull));
-                return RG_OK;
+                if (hipStreamWaitValue64(later, s.at, value, hipStreamWaitValueGte, ~0ull) == hipSuccess) return RG_OK;
             }
             (void)hipGetLastError();
             ctx->stream_values = false;
@@ -108,6 +98,28 @@ rg_status rg_stream_after(rg_ctx* ctx, hipStream_t later, hipStream_t earlier, h
     RG_HIP(ctx, hipEventRecord(event, earlier));
     RG_HIP(ctx, hipStreamWaitEvent(later, event, 0));
     return RG_OK;
+}
+
+// The signals of rg_stream_after, which calls that must not allocate make use of.  A stream of this thread may be recording a graph
+// meanwhile, which an allocation is no part of.
+static bool make_signals(rg_ctx* ctx) {
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+    const bool relaxed = hipThreadExchangeStreamCaptureMode(&mode) == hipSuccess;
+    bool made = true;
+    for (RgSignal& s : ctx->signals) {
+        if (hipExtMallocWithFlags((void**)&s.at, sizeof(uint64_t), hipMallocSignalMemory) != hipSuccess) {
+            (void)hipGetLastError();
+            s.at = nullptr;
+            made = false;
+            break;
+        }
+        __atomic_store_n(s.at, 0ull, __ATOMIC_RELEASE);
+    }
+    if (!made)
+        for (RgSignal& s : ctx->signals)
+            if (s.at) { (void)hipFree(s.at); s.at = nullptr; }
+    if (relaxed) (void)hipThreadExchangeStreamCaptureMode(&mode);
+    return made;
 }
 
 static int env_int(const char* name, int dflt) {
@@ -148,6 +160,7 @@ rg_status rg_create(int device, rg_ctx** out) {
     int can_wait = 0;
     ctx->stream_values = hipDeviceGetAttribute(&can_wait, hipDeviceAttributeCanUseStreamWaitValue, device) == hipSuccess && can_wait;
     if (!ctx->stream_values) (void)hipGetLastError();
+    ctx->stream_values = ctx->stream_values && make_signals(ctx);
     rg_status st = rg_gather_static_init(ctx);
     if (st == RG_OK) st = rg_sampler_init(ctx);
     if (st != RG_OK) {

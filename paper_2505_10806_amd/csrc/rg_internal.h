@@ -88,9 +88,9 @@ struct rg_ctx {
     int64_t gather_cap = 0;                                  // rows per ticket the buffers hold
     int64_t gather_rows[RG_GATHER_TICKETS] = {-1, -1, -1, -1, -1, -1, -1, -1};   // rows a ticket was prepared for (-1: none)
     hipEvent_t ev_classified = nullptr, ev_miss_done = nullptr;
-    RgSignal signals[128];             // of rg_stream_after, used in turn
+    RgSignal signals[128];            // of rg_stream_after, used in turn; rg_create makes them
     uint64_t signal_value = 0;        // the last value that one of them was to be given
-    bool stream_values = false;       // the device waits for values in memory
+    bool stream_values = false;       // the device waits for values in memory, and the signals are there
     void* static_scratch = nullptr;   // device address of the library's file-scope gather scratch on ctx->device
     std::vector<hipStream_t> streams;   // streams made by rg_stream_create and not yet destroyed (rg_destroy takes the rest)
 

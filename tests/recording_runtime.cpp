@@ -12,7 +12,8 @@
 #include <string>
 
 struct Dim3 { uint32_t x, y, z; };
-static const int kOk = 0, kOutOfMemory = 2, kCaptureUnsupported = 900, kCaptureIsolation = 905;
+static const int kOk = 0, kInvalid = 1, kOutOfMemory = 2, kNotSupported = 801, kCaptureUnsupported = 900, kCaptureIsolation = 905;
+static const int kCanWaitForValues = 10013, kSignalMemory = 2, kRelaxed = 2;
 
 static std::string log_text;
 static std::map<uint64_t, size_t> blocks;                 // address -> bytes
@@ -23,6 +24,11 @@ static std::set<void*> capturing, joined_back;            // streams that record
 static void* origin;
 static std::map<void*, std::pair<void*, bool>> events;    // event -> stream it was recorded on, in a graph or not
 static struct { Dim3 grid, block; size_t shmem; void* stream; } pushed;
+static int capture_mode, refused;                         // of this thread; kinds of value calls that fail (refuse_values)
+static bool landing = true;                               // values are written as soon as they are asked for
+static std::map<uint64_t*, std::pair<uint64_t, uint64_t>> signals;        // eight bytes that streams write -> values asked for, and there
+static size_t in_use() { return held + 8 * signals.size(); }
+static bool forbidden() { return !capturing.empty() && capture_mode != kRelaxed; }       // nothing may be allocated: a graph is recorded
 
 template <typename... A> static void note(const char* fmt, A... a) {
     char buf[512];
@@ -37,7 +43,13 @@ extern "C" {
 const char* recorded() { return log_text.c_str(); }
 void forget() { log_text.clear(); }
 void limit_memory(size_t bytes) { limit = bytes; }
-size_t memory_held() { return held; }
+size_t memory_held() { return in_use(); }
+void refuse_values(int kinds) { refused = kinds; }        // 1: the device says it cannot, 2: no memory for them, 4: no write, 8: no wait
+void land_values(int on) {                                // off: writes that are asked for from now on are on their way until it is on again
+    landing = on != 0;
+    if (landing)
+        for (auto& s : signals) *s.first = s.second.second = s.second.first;
+}
 void begin_capture(void* s) { capturing = {s}; joined_back = {s}; origin = s; }
 int end_capture() {                                       // streams that were drawn into the graph and not joined back
     int open = 0;
@@ -58,8 +70,8 @@ int hipGetSymbolAddress(void** p, const void*) { *p = (void*)0x10000000ull; retu
 int hipPointerGetAttributes(int* type, const void*) { *type = 2; return kOk; }       // device memory
 
 int hipMalloc(void** p, size_t bytes) {
-    if (!capturing.empty()) { note("malloc in a graph"); return kCaptureUnsupported; }
-    if (bytes > limit || held > limit - bytes) { note("no memory %zu", bytes); return kOutOfMemory; }
+    if (forbidden()) { note("malloc in a graph"); return kCaptureUnsupported; }
+    if (bytes > limit || in_use() > limit - bytes) { note("no memory %zu", bytes); return kOutOfMemory; }
     *p = (void*)next_address;
     note("malloc %llx %zu", (unsigned long long)next_address, bytes);
     blocks[next_address] = bytes;
@@ -67,7 +79,23 @@ int hipMalloc(void** p, size_t bytes) {
     next_address += (bytes + 0xFFFFF) & ~0xFFFFFull;
     return kOk;
 }
+int hipExtMallocWithFlags(void** p, size_t bytes, unsigned flags) {
+    if (forbidden()) { note("malloc in a graph"); return kCaptureUnsupported; }
+    if (flags != kSignalMemory || bytes != 8) return kInvalid;
+    note("malloc signal");
+    if ((refused & 2) || bytes > limit || in_use() > limit - bytes) return kOutOfMemory;
+    uint64_t* at = new uint64_t(~0ull);
+    signals[at] = {0, 0};                                  // (what the library is to store there)
+    *p = at;
+    return kOk;
+}
 int hipFree(void* p) {
+    if (signals.count((uint64_t*)p)) {
+        signals.erase((uint64_t*)p);
+        delete (uint64_t*)p;
+        note("free signal");
+        return kOk;
+    }
     note("free %llx", (unsigned long long)(uintptr_t)p);
     held -= blocks[(uint64_t)(uintptr_t)p];
     blocks.erase((uint64_t)(uintptr_t)p);
@@ -75,6 +103,26 @@ int hipFree(void* p) {
 }
 int hipMemset(void*, int, size_t) { return kOk; }
 
+int hipDeviceGetAttribute(int* value, int attribute, int) {
+    *value = attribute == kCanWaitForValues && !(refused & 1);
+    return attribute == kCanWaitForValues ? kOk : kInvalid;
+}
+int hipThreadExchangeStreamCaptureMode(int* mode) { const int was = capture_mode; capture_mode = *mode; *mode = was; return kOk; }
+int hipStreamWriteValue64(void* s, void* p, uint64_t value, unsigned) {
+    note("write %p %p %llu", s, p, (unsigned long long)value);
+    if ((refused & 4) || capturing.count(s)) return kNotSupported;
+    const auto at = signals.find((uint64_t*)p);
+    if (at == signals.end() || *at->first != at->second.first) return kInvalid;          // one write on its way at most
+    at->second.first = value;
+    if (landing) *at->first = at->second.second = value;
+    return kOk;
+}
+int hipStreamWaitValue64(void* s, void* p, uint64_t value, unsigned flags, uint64_t mask) {
+    note("await %p %p %llu", s, p, (unsigned long long)value);
+    if ((refused & 8) || capturing.count(s)) return kNotSupported;
+    const auto at = signals.find((uint64_t*)p);                                          // (flags 0: until it is as large)
+    return at == signals.end() || at->second.first < value || flags != 0 || mask != ~0ull ? kInvalid : kOk;
+}
 int hipStreamIsCapturing(void* s, int* status) { *status = capturing.count(s) ? 1 : 0; return kOk; }
 int hipStreamSynchronize(void*) { return kOk; }
 int hipStreamDestroy(void*) { return kOk; }

@@ -362,3 +362,100 @@ c = context()
 assert sample(c, {n}, {edges}, {seeds}, {fanouts}) == OK, lib.rg_last_error(c)
 assert (len(kernels()) == 1) == {small}
 """)
+
+
+def test_no_gather_allocates_after_reserve():
+    """Neither the calls of rg_gather_features_static nor any gather behind rg_reserve: more of them on two streams than there are signals,
+    with writes that land at once and with none that does; nor while another stream of the thread records a graph."""
+    host_calls.run("""
+c = context()
+assert lib.rg_reserve(c, i64(1000), i64(1000), i64(60_000), i32(1)) == OK
+held = rt.memory_held()
+log()
+for landing in (1, 0):
+    rt.land_values(landing)
+    for k in range(200):
+        for rows, dim, static in ((1500, 64, True), (60_000, 256, True), (1500, 64, False), (60_000, 256, False)):
+            assert gather(c, rows, dim, hit=0x51, miss=0x52, static=static) == OK, lib.rg_last_error(c)
+    lines = log()
+    assert not [x for x in lines if x.startswith(("malloc", "free", "no memory"))], lines[:20]
+rt.land_values(1)
+d = context()
+log()
+rt.begin_capture(0x77)
+for k in range(70):
+    assert gather(d, 1500, 64, hit=0x51, miss=0x52, static=True) == OK
+rt.end_capture()
+lines = log()
+assert not [x for x in lines if "malloc" in x] and [x for x in lines if x.startswith("write")], lines[:20]
+lib.rg_destroy(c), lib.rg_destroy(d)
+assert rt.memory_held() == 0
+rt.begin_capture(0x77)                                    # a context made while a graph is recorded on another stream
+e = context()
+assert not [x for x in log() if x == "malloc in a graph"]
+rt.end_capture()
+lib.rg_destroy(e)
+""")
+
+
+# One launch up to 14 MB by values, above by events; three launches (from 32 MiB or 98,305 rows on) up to 64 MB by values, above by events.
+@pytest.mark.parametrize("rows,dim,launches,by_value", [
+    (1500, 64, 1, True), (14_336, 256, 1, True), (14_337, 256, 1, False), (30_000, 256, 1, False), (32_768, 256, 1, False), (32_769, 256, 3, True),
+    (98_305, 16, 3, True), (65_536, 256, 3, True), (65_537, 256, 3, False)])
+def test_streams_are_ordered_by_values_or_by_events(rows, dim, launches, by_value):
+    """Each order is a write on the earlier stream and behind it a wait of the later one for the same value, or a record and a wait."""
+    host_calls.run(f"""
+c = context()
+log()
+for static in (False, True):
+    assert gather(c, {rows}, {dim}, hit=0x51, miss=0x52, static=static) == OK, lib.rg_last_error(c)
+    lines = log()
+    assert sum(x.startswith("launch") for x in lines) == {launches}, lines
+    orders = [x.split() for x in lines if x.split()[0] in ("write", "await", "record", "wait")]
+    assert [x[0] for x in orders] == (["write", "await"] if {by_value} else ["record", "wait"]) * 2, orders
+    for first, then in (orders[:2], orders[2:]):
+        if {by_value}:                                        # stream, address, value
+            assert first[2:] == then[2:] and {{first[1], then[1]}} == {{"0x51", "0x52"}}, orders
+        else:                                                 # event, stream; stream, event
+            assert first[1] == then[2] and {{first[2], then[1]}} == {{"0x51", "0x52"}}, orders
+    # one launch runs on the hit stream: behind the miss stream, and in front of it; three begin and end there
+    streams = [orders[0][1 if {by_value} else 2], orders[2][1 if {by_value} else 2]]
+    assert streams == (["0x52", "0x51"] if {launches} == 1 else ["0x51", "0x52"]), orders
+""")
+
+
+def test_streams_are_ordered_by_events_where_values_cannot():
+    """A signal whose last write has not landed is left alone; a device, an allocation, a write or a wait that is refused; recorded streams."""
+    host_calls.run("""
+def orders(c, n=1):
+    log()
+    for _ in range(n):
+        assert gather(c, 1500, 64, hit=0x51, miss=0x52) == OK, lib.rg_last_error(c)
+    return [x.split()[0] for x in log() if x.split()[0] in ("write", "await", "record", "wait")]
+VALUES, EVENTS = ["write", "await"], ["record", "wait"]
+c = context()
+assert orders(c, 3) == VALUES * 6
+rt.land_values(0)
+got = orders(c, 100)
+n = got.count("write")
+assert 32 <= n < 200 and got == VALUES * n + EVENTS * (200 - n)
+rt.land_values(1)
+assert orders(c, 100) == VALUES * 200
+for kinds in (1, 2):
+    rt.refuse_values(kinds)
+    d = context()
+    assert orders(d, 2) == EVENTS * 4 and "malloc signal" not in log()
+    lib.rg_destroy(d)
+rt.refuse_values(4)
+d = context()
+assert orders(d, 2) == ["write"] + EVENTS * 4             # one try
+rt.refuse_values(8)
+e = context()
+assert orders(e, 2) == ["write", "await"] + EVENTS * 4
+rt.refuse_values(0)
+for recorded in (0x51, 0x52):
+    rt.begin_capture(recorded)
+    gather(c, 1500, 64, hit=0x51, miss=0x52)
+    rt.end_capture()
+    assert not [x for x in log() if x.startswith(("write", "await"))]
+""")
