@@ -945,12 +945,12 @@ def test_tiers_from_bytes(B, ctx, n, seeds, fanouts, captured):
             assert_batch_equal(HipBatch(o, len(fanouts)), orc, len(fanouts), f"batch {j}")
 
 
-# One launch, and lookup and copies apart; more calls on their way than there are signals for the streams' order.
-@pytest.mark.parametrize("rows", [2000, 30_000])
+# One launch, ordered by values and by events; lookup and copies apart, by values and by events; more calls on their way than there are signals.
+@pytest.mark.parametrize("rows", [2000, 30_000, 38_000, 70_000])
 def test_two_stream_gathers_keep_their_place_in_both_streams(B, ctx, rows):
     """The miss rows of a call come behind what the miss stream was given before it and in front of what either stream is given next."""
     log(f"[order] rows={rows}")
-    dim, n, calls, side = 256, 40_000, 100, torch.cuda.Stream()
+    dim, n, calls, side = 256, max(40_000, rows), 100, torch.cuda.Stream()
     ids = torch.randperm(n, device=DEV, dtype=torch.int32)[:rows].contiguous()
     cache = B.FeatureCache(n, 1, dim, DEV)
     cache.loc.copy_(torch.where(torch.arange(n, device=DEV) % 4 == 0, torch.arange(n, device=DEV) // 4 - 2 ** 31, torch.arange(n, device=DEV)).int())
