@@ -141,9 +141,10 @@ __device__ __forceinline__ void rg_row_extent(const RowPtr& row_ptr, int v, int6
 // their keys do, wait in a list.  Nothing is counted beforehand: the keys are worked out once, and a call is two launches.
 // Bound by launches, the Philox blocks (3.3 us for 1 M ids on the whole device) and the scattered 8-byte writes.
 // Few ids get small buckets, whose sort is a shorter chain of LDS passes (100 k ids 9.5 us, in buckets of 2048 12.0; 10 k 7.2 / 9.3; 400 k 14.8 / 15.9),
-// many get large ones, to whose counters the workgroups add less often (700 k 24.7 / 19.3).  Up to 3072 ids one workgroup does it all (1000 5.0 us, in
-// buckets 7.1; 3072 7.2 either way), of 1024 threads (4096 ids 9.6 us, with 512 threads 12.3).
-constexpr int kSchedLds = 3072;          // pairs one workgroup sorts in LDS
+// many get large ones, to whose counters the workgroups add less often (700 k 24.7 / 19.3).  Up to 4096 ids one workgroup does it all (1000 5.0 us, in
+// buckets 7.1; 3072 7.5 either way), of 1024 threads (4096 ids 9.4 us, with 512 threads 12.4; in buckets 8.4, but so a call needs no scratch, which
+// a graph that records a context's first call cannot allocate), with room for 3072 where that does (1000 ids 5.1 us, with room for 4096 5.6).
+constexpr int kSchedLds[2] = {3072, 4096};         // pairs one workgroup sorts in LDS
 constexpr int kSchedAvg[2] = {512, 2048};          // pairs per bucket on average, at most
 constexpr int kSchedRoom[2] = {1024, 2560};        // eleven standard deviations more and above
 constexpr int64_t kSchedFew = 400 * 1000;          // ids that get the small ones
@@ -2430,8 +2431,10 @@ rg_status rg_epoch_schedule(rg_ctx* ctx, const int32_t* train_ids, int64_t n, ui
     RG_HIP(ctx, hipSetDevice(ctx->device));
     hipStream_t s = (hipStream_t)stream;
     const uint32_t k0 = (uint32_t)(seed & 0xffffffffu), k1 = (uint32_t)(seed >> 32);
-    if (n <= kSchedLds) {
-        k_sched_sort<kSchedLds, true, 1024><<<1, 1024, 0, s>>>(train_ids, n, 0, k0, k1, epoch, nullptr, nullptr, nullptr, nullptr, order_out, nullptr, 0);
+    if (n <= kSchedLds[1]) {
+#define RG_SORT(MORE) k_sched_sort<kSchedLds[MORE], true, 1024><<<1, 1024, 0, s>>>(train_ids, n, 0, k0, k1, epoch, nullptr, nullptr, nullptr, nullptr, order_out, nullptr, 0)
+        if (n <= kSchedLds[0]) RG_SORT(0); else RG_SORT(1);
+#undef RG_SORT
         RG_LAUNCH_CHECK(ctx, "k_sched_sort");
         return RG_OK;
     }

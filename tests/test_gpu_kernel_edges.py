@@ -973,8 +973,8 @@ def test_two_stream_gathers_keep_their_place_in_both_streams(B, ctx, rows):
     assert stats.cpu().tolist() == [rows - missing.numel(), 0, missing.numel()]
 
 
-# One workgroup up to 3072 ids, buckets of 512 on average up to 400,000, of 2048 above; a bucket of 256 to 512 with room for 1024.
-@pytest.mark.parametrize("n", [1025, 3071, 3072, 3073, 16_384, 16_385, 262_144, 400_000, 400_001])
+# One workgroup up to 4096 ids, with room for 3072 where that does, buckets of 512 on average up to 400,000, of 2048 above; a bucket of 256 to 512 with room for 1024.
+@pytest.mark.parametrize("n", [1025, 3071, 3072, 3073, 4096, 4097, 16_384, 16_385, 262_144, 400_000, 400_001])
 def test_schedule_bucket_sizes(ctx, n):
     log(f"[schedule sizes] n={n}")
     ids = np.random.default_rng(n).permutation(2 * n)[:n].astype(np.int32)

@@ -459,3 +459,22 @@ for recorded in (0x51, 0x52):
     rt.end_capture()
     assert not [x for x in log() if x.startswith(("write", "await"))]
 """)
+
+
+@pytest.mark.parametrize("n", [1, 3072, 3073, 4096])
+def test_schedule_of_up_to_4096_ids_needs_no_scratch(n):
+    """One launch, also as a context's first call while a graph is recorded, and without memory."""
+    host_calls.run(f"""
+def schedule(c, n, stream=0):
+    return lib.rg_epoch_schedule(c, p(address()), i64(n), u64(7), u32(1), p(address()), p(stream))
+c = context()
+log()
+rt.begin_capture(0x51)
+assert schedule(c, {n}, 0x51) == OK, lib.rg_last_error(c)
+rt.end_capture()
+rt.limit_memory(rt.memory_held())
+assert schedule(c, {n}) == OK, lib.rg_last_error(c)
+lines = log()
+assert [x.split("<")[0] for x in lines if x.startswith("launch")] == ["launch k_sched_sort"] * 2 and not [x for x in lines if "malloc" in x], lines
+assert schedule(c, 4097) == OOM
+""")
