@@ -146,7 +146,8 @@ __device__ __forceinline__ void rg_row_extent(const RowPtr& row_ptr, int v, int6
 // a graph that records a context's first call cannot allocate), with room for 3072 where that does (1000 ids 5.1 us, with room for 4096 5.6).
 constexpr int kSchedLds[2] = {3072, 4096};         // pairs one workgroup sorts in LDS
 constexpr int kSchedAvg[2] = {512, 2048};          // pairs per bucket on average, at most
-constexpr int kSchedRoom[2] = {1024, 2560};        // eleven standard deviations more and above
+constexpr int kSchedRoom = 2560;                   // eleven standard deviations more than the large ones' average; in small ones for ids picked for their
+                                                   // keys (20 k ids, 1500 in one bucket: 10.0 us, with room for 1024 36)
 constexpr int64_t kSchedFew = 400 * 1000;          // ids that get the small ones
 constexpr int64_t kSchedFewBuckets = 1024;         // of the most of these
 static_assert(kSchedFew <= kSchedFewBuckets * kSchedAvg[0], "buckets for them");
@@ -181,7 +182,7 @@ __global__ void __launch_bounds__(1024) k_sched_scan(const int32_t* __restrict__
 
 // Pairs go to their bucket; the order inside is left to k_sched_sort.  count[b] = pairs of bucket b, those without room among them;
 // count[buckets] = ids in the list `late`.  PER ids per thread.
-template <bool LDS, int PER, int ROOM>
+template <bool LDS, int PER>
 __global__ void __launch_bounds__(1024) k_sched_scatter(const int32_t* __restrict__ train_ids, int64_t n, int log2_buckets, uint32_t k0,
                                                         uint32_t k1, uint32_t epoch, int32_t* __restrict__ count,
                                                         uint2* __restrict__ pairs, int32_t* __restrict__ late) {
@@ -216,23 +217,24 @@ __global__ void __launch_bounds__(1024) k_sched_scatter(const int32_t* __restric
         if (i0 + j * 1024 + threadIdx.x >= n) continue;
         const int64_t b = (int64_t)(key[j] >> (64 - log2_buckets));
         const int32_t at = (LDS ? h[b] : 0) + rank[j];
-        if (at < ROOM) pairs[b * ROOM + at] = make_uint2((uint32_t)(key[j] >> (32 - log2_buckets)), (uint32_t)v[j]);
+        if (at < kSchedRoom) pairs[b * kSchedRoom + at] = make_uint2((uint32_t)(key[j] >> (32 - log2_buckets)), (uint32_t)v[j]);
         else late[atomicAdd(&count[buckets], 1)] = v[j];
     }
 }
 
-// One workgroup per bucket: its pairs in order, the ids to their final places.  CAP: pairs it has room for in LDS.
+// One workgroup per bucket: its pairs in order, the ids to their final places.  CAP: pairs it has room for in LDS; up to FEW of them take fewer
+// rounds (100 k ids 10.0 us, with those for 2560 10.1 to 10.5).
 // SINGLE: one bucket, the n train ids themselves.  start == NULL: the workgroup adds up the counts in front of its own.
 // `clear` (or NULL): n_clear counters that the next call will use.
-template <int CAP, bool SINGLE, int T>
+template <int CAP, bool SINGLE, int T, int FEW = CAP>
 __global__ void __launch_bounds__(T) k_sched_sort(const int32_t* __restrict__ train_ids, int64_t n, int log2_buckets, uint32_t k0,
                                                     uint32_t k1, uint32_t epoch, const int32_t* __restrict__ count,
                                                     const int32_t* __restrict__ start, const uint2* __restrict__ pairs,
                                                     const int32_t* __restrict__ late, int32_t* order_out,
                                                     int32_t* __restrict__ clear, int n_clear) {
     constexpr int kTile = SINGLE ? 0 : 2048;            // of an overfull bucket
-    constexpr int PER = CAP / T, kSubBits = CAP > 1024 ? 11 : 10, SUB = 1 << kSubBits;
-    static_assert(CAP % T == 0 && SUB % T == 0, "whole rounds");
+    constexpr int kSubBits = FEW > 1024 ? 11 : 10, SUB = 1 << kSubBits;
+    static_assert(CAP % T == 0 && FEW % T == 0 && SUB % T == 0, "whole rounds");
     __shared__ uint32_t sk[CAP > kTile ? CAP : kTile];
     __shared__ int32_t si[CAP > kTile ? CAP : kTile];
     __shared__ int32_t sub[SUB + 1];
@@ -258,8 +260,8 @@ __global__ void __launch_bounds__(T) k_sched_sort(const int32_t* __restrict__ tr
         // Only ids picked for their keys get here: the bucket's and those of the list that belong to it, sorted where they will be,
         // by a network whose every comparison is ascending, so that the places behind its end count as larger than everything and are
         // never touched.  Steps within kTile ids are made in LDS, tile by tile; of the others there are few, which work the keys out
-        // from the ids.  A call of 100,000 ids of which 5000 belong to one bucket 136 us, 50,000 of them 1.8 ms (with all steps in
-        // global memory 374 and 5.0 ms; 12 where every bucket has room), one of 1 M ids with 4000 in a bucket 94 (277; 24).
+        // from the ids.  A call of 100,000 ids of which 4000 belong to one bucket 89 us, 6000 of them 150, 12,000 334 (10 where every bucket
+        // has room), one of 1 M ids with 4000 in a bucket 103 (24).
         int32_t* fill = sub;
         if (threadIdx.x == 0) *fill = CAP;
         for (int i = threadIdx.x; i < CAP; i += T) out[i] = (int32_t)pairs[bucket * CAP + i].y;
@@ -319,65 +321,70 @@ __global__ void __launch_bounds__(T) k_sched_sort(const int32_t* __restrict__ tr
         }
         return;
     }
-    uint32_t key[PER];
-    int32_t id[PER], rank[PER];
-    for (int b = threadIdx.x; b <= SUB; b += T) sub[b] = 0;
+    const auto sort = [&](auto rounds) {                              // of T pairs
+        constexpr int PER = decltype(rounds)::value;
+        uint32_t key[PER];
+        int32_t id[PER], rank[PER];
+        for (int b = threadIdx.x; b <= SUB; b += T) sub[b] = 0;
 #pragma unroll
-    for (int j = 0; j < PER; ++j) {
-        const int i = j * T + threadIdx.x;
-        if (i < m) {
-            if (SINGLE) {
-                id[j] = train_ids[i];
-                key[j] = (uint32_t)(full_key(id[j]) >> 32);
-            } else {
-                const uint2 x = pairs[bucket * CAP + i];
-                key[j] = x.x;
-                id[j] = (int32_t)x.y;
-            }
-        }
-    }
-    __syncthreads();
-#pragma unroll
-    for (int j = 0; j < PER; ++j)
-        if (j * T + (int)threadIdx.x < m) rank[j] = atomicAdd(&sub[key[j] >> (32 - kSubBits)], 1);
-    __syncthreads();
-    int mine[SUB / T], sum = 0;                                          // counts -> starts, SUB / T consecutive ones per thread
-#pragma unroll
-    for (int q = 0; q < SUB / T; ++q) { mine[q] = sub[threadIdx.x * (SUB / T) + q]; sum += mine[q]; }
-    int total;
-    int at = rg_block_excl_scan<T / RG_WAVE>(sum, smem, &total);         // its barriers separate the reads from the writes
-#pragma unroll
-    for (int q = 0; q < SUB / T; ++q) { sub[threadIdx.x * (SUB / T) + q] = at; at += mine[q]; }
-    if (threadIdx.x == T - 1) sub[SUB] = at;
-    __syncthreads();
-#pragma unroll
-    for (int j = 0; j < PER; ++j)
-        if (j * T + (int)threadIdx.x < m) {
-            const int p = sub[key[j] >> (32 - kSubBits)] + rank[j];
-            sk[p] = key[j];
-            si[p] = id[j];
-        }
-    __syncthreads();
-#pragma unroll
-    for (int j = 0; j < PER; ++j)
-        if (j * T + (int)threadIdx.x < m) {
-            const int b = (int)(key[j] >> (32 - kSubBits));
-            const int lo = sub[b], hi = sub[b + 1], me = lo + rank[j];
-            int place = lo;
-            for (int q = lo; q < hi; ++q) {
-                if (sk[q] != key[j]) {
-                    place += sk[q] < key[j];
-                } else if (q != me) {
-                    if (si[q] == id[j]) {                                // (equal pairs, which distinct ids do not give, keep their places)
-                        place += q < me;
-                    } else {
-                        const uint64_t mine_ = full_key(id[j]), other = full_key(si[q]);
-                        place += other != mine_ ? other < mine_ : si[q] < id[j];
-                    }
+        for (int j = 0; j < PER; ++j) {
+            const int i = j * T + threadIdx.x;
+            if (i < m) {
+                if (SINGLE) {
+                    id[j] = train_ids[i];
+                    key[j] = (uint32_t)(full_key(id[j]) >> 32);
+                } else {
+                    const uint2 x = pairs[bucket * CAP + i];
+                    key[j] = x.x;
+                    id[j] = (int32_t)x.y;
                 }
             }
-            out[place] = id[j];
         }
+        __syncthreads();
+#pragma unroll
+        for (int j = 0; j < PER; ++j)
+            if (j * T + (int)threadIdx.x < m) rank[j] = atomicAdd(&sub[key[j] >> (32 - kSubBits)], 1);
+        __syncthreads();
+        int mine[SUB / T], sum = 0;                                          // counts -> starts, SUB / T consecutive ones per thread
+#pragma unroll
+        for (int q = 0; q < SUB / T; ++q) { mine[q] = sub[threadIdx.x * (SUB / T) + q]; sum += mine[q]; }
+        int total;
+        int at = rg_block_excl_scan<T / RG_WAVE>(sum, smem, &total);         // its barriers separate the reads from the writes
+#pragma unroll
+        for (int q = 0; q < SUB / T; ++q) { sub[threadIdx.x * (SUB / T) + q] = at; at += mine[q]; }
+        if (threadIdx.x == T - 1) sub[SUB] = at;
+        __syncthreads();
+#pragma unroll
+        for (int j = 0; j < PER; ++j)
+            if (j * T + (int)threadIdx.x < m) {
+                const int p = sub[key[j] >> (32 - kSubBits)] + rank[j];
+                sk[p] = key[j];
+                si[p] = id[j];
+            }
+        __syncthreads();
+#pragma unroll
+        for (int j = 0; j < PER; ++j)
+            if (j * T + (int)threadIdx.x < m) {
+                const int b = (int)(key[j] >> (32 - kSubBits));
+                const int lo = sub[b], hi = sub[b + 1], me = lo + rank[j];
+                int place = lo;
+                for (int q = lo; q < hi; ++q) {
+                    if (sk[q] != key[j]) {
+                        place += sk[q] < key[j];
+                    } else if (q != me) {
+                        if (si[q] == id[j]) {                                // (equal pairs, which distinct ids do not give, keep their places)
+                            place += q < me;
+                        } else {
+                            const uint64_t mine_ = full_key(id[j]), other = full_key(si[q]);
+                            place += other != mine_ ? other < mine_ : si[q] < id[j];
+                        }
+                    }
+                }
+                out[place] = id[j];
+            }
+    };
+    if (FEW < CAP && m <= FEW) sort(std::integral_constant<int, FEW / T>{});
+    else sort(std::integral_constant<int, CAP / T>{});
 }
 
 // ---------------------------------------------------------------------------- batches of a group
@@ -2444,9 +2451,9 @@ rg_status rg_epoch_schedule(rg_ctx* ctx, const int32_t* train_ids, int64_t n, ui
     const int64_t buckets = 1ll << lb;
     rg_status st;
     // sized for the largest n of as many buckets, so that a call of another such n, captured perhaps, allocates nothing, and where there are
-    // many ids for few as well, whose buckets take more
+    // many ids for few as well, who have more buckets
     const int64_t most_buckets = many ? rg_max64(buckets, kSchedFewBuckets) : buckets;
-    const int64_t most_pairs = rg_max64(kSchedRoom[many] * buckets, many ? kSchedRoom[0] * kSchedFewBuckets : 0);
+    const int64_t most_pairs = kSchedRoom * most_buckets;
     if ((st = rg_ensure(ctx, ctx->sched_pairs, (size_t)most_pairs * 8)) != RG_OK) return st;
     if ((st = rg_ensure(ctx, ctx->sched_late, (size_t)rg_max64(kSchedAvg[many] * buckets, many ? kSchedAvg[0] * kSchedFewBuckets : 0) * 4)) != RG_OK) return st;
     const void* counters = ctx->sched_buckets.p;
@@ -2471,10 +2478,10 @@ rg_status rg_epoch_schedule(rg_ctx* ctx, const int32_t* train_ids, int64_t n, ui
     // 1024 ids to a workgroup while that leaves compute units without one
     const bool few = n <= 1024ll * ctx->num_cus;
     const int g = (int)rg_div_up(n, few ? 1024 : 4096);
-#define RG_SCATTER(LDS, PER, MANY) k_sched_scatter<LDS, PER, kSchedRoom[MANY]><<<g, 1024, 0, s>>>(train_ids, n, lb, k0, k1, epoch, count, pairs, late)
-    if (!many) { if (few) RG_SCATTER(true, 1, 0); else RG_SCATTER(true, 4, 0); }
-    else if (lds) RG_SCATTER(true, 4, 1);
-    else RG_SCATTER(false, 4, 1);
+#define RG_SCATTER(LDS, PER) k_sched_scatter<LDS, PER><<<g, 1024, 0, s>>>(train_ids, n, lb, k0, k1, epoch, count, pairs, late)
+    if (few) RG_SCATTER(true, 1);
+    else if (lds) RG_SCATTER(true, 4);
+    else RG_SCATTER(false, 4);
 #undef RG_SCATTER
     RG_LAUNCH_CHECK(ctx, "k_sched_scatter");
     if (start) {
@@ -2483,7 +2490,7 @@ rg_status rg_epoch_schedule(rg_ctx* ctx, const int32_t* train_ids, int64_t n, ui
     }
     int32_t* clear = captured || !ctx->sched_dirty[other] ? nullptr : (int32_t*)ctx->sched_buckets.p + other * set;
 #define RG_SORT(MANY)                                                                                                 \
-    k_sched_sort<kSchedRoom[MANY], false, 512><<<(unsigned)buckets, 512, 0, s>>>(nullptr, n, lb, k0, k1, epoch, count, start, pairs, late, order_out, \
+    k_sched_sort<kSchedRoom, false, 512, MANY ? kSchedRoom : 1024><<<(unsigned)buckets, 512, 0, s>>>(nullptr, n, lb, k0, k1, epoch, count, start, pairs, late, order_out, \
                                                                                 clear, clear ? (int)ctx->sched_dirty[other] : 0)
     if (many) RG_SORT(1); else RG_SORT(0);
 #undef RG_SORT

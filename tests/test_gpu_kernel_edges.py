@@ -258,12 +258,12 @@ def test_schedule_bucket_edges(ctx, n):
 
 
 def test_schedule_of_ids_picked_for_one_bucket(ctx):
-    """Every id's key starts with the same two bits: one of the four buckets of 6000 ids holds them all, more than a workgroup
+    """Every id's key starts with the same four bits: one of the sixteen buckets of 6000 ids holds them all, more than a workgroup
     sorts in LDS; the others are empty."""
     seed, epoch = 2025, 4
-    cand = np.arange(26_000, dtype=np.uint32)
-    top = np.array([oracle.philox4x32_10(np.array([v, 0xFFFFFFFF, 0, epoch]), np.array([seed, 0]))[0] >> 30 for v in cand])
-    ids = cand[top == 1][:6000].astype(np.int32)
+    cand = np.arange(104_000, dtype=np.uint32)
+    top = np.array([oracle.philox4x32_10(np.array([v, 0xFFFFFFFF, 0, epoch]), np.array([seed, 0]))[0] >> 28 for v in cand])
+    ids = cand[top == 5][:6000].astype(np.int32)
     assert ids.size == 6000
     got = ctx.epoch_schedule(_i32(ids), seed, epoch)
     assert np.array_equal(got.cpu().numpy(), oracle.epoch_schedule(ids, seed, epoch))
@@ -272,16 +272,13 @@ def test_schedule_of_ids_picked_for_one_bucket(ctx):
 # A bucket has room for 2560 ids; an overfull one is sorted in tiles of 2048 that are merged.
 @pytest.mark.parametrize("in_bucket", [2560, 2561, 4096, 4097, 10_001, 16_500])
 def test_schedule_bucket_with_more_ids_than_room(ctx, in_bucket):
-    """17,000 ids in sixteen buckets, the third of which gets in_bucket of them."""
-    n, seed, epoch = 17_000, 2025, 4
-    ids = np.arange(400_000, dtype=np.int32)
-    order = oracle.epoch_schedule(ids, seed, epoch)     # ascending by key: 25,000 ids or so to each of the sixteen
-    key = lambda v: oracle.philox4x32_10(np.array([v, 0xFFFFFFFF, 0, epoch]), np.array([seed, 0]))[0] >> 28  # noqa: E731
-    lo, hi = np.searchsorted([key(v) for v in order[::16]], [3, 4]) * 16
-    third, rng = order[lo:hi - 16], np.random.default_rng(in_bucket)
-    rest = np.concatenate([order[:lo - 16], order[hi:]])
-    ids = rng.permutation(np.concatenate([rng.permutation(third)[:in_bucket], rng.permutation(rest)[:n - in_bucket]]))
-    assert (np.array([key(v) for v in ids]) == 3).sum() == in_bucket
+    """402,000 ids in 256 buckets, the first of which gets in_bucket of them."""
+    n, seed, epoch = 402_000, 2025, 4
+    order = oracle.epoch_schedule(np.arange(4_600_000, dtype=np.int32), seed, epoch)     # ascending by key: 18,000 ids or so to each of the 256
+    key = lambda v: oracle.philox4x32_10(np.array([v, 0xFFFFFFFF, 0, epoch]), np.array([seed, 0]))[0] >> 24  # noqa: E731
+    assert key(order[17_000]) == 0 and key(order[19_000]) == 1
+    rng = np.random.default_rng(in_bucket)
+    ids = rng.permutation(np.concatenate([rng.permutation(order[:17_000])[:in_bucket], rng.permutation(order[19_000:])[:n - in_bucket]]))
     got = ctx.epoch_schedule(_i32(ids), seed, epoch)
     assert np.array_equal(got.cpu().numpy(), oracle.epoch_schedule(ids, seed, epoch))
 
@@ -578,10 +575,10 @@ def test_selection_after_other_selections(B):
     ctx.close()
 
 
-@pytest.mark.parametrize("copies", [2560, 2561, 4000])
-def test_schedule_of_ids_given_many_times(ctx, copies):
-    """Seven ids a few thousand times each fill their buckets up to the last place and beyond; the others stay empty."""
-    ids = np.random.default_rng(copies).permutation(np.repeat(np.arange(7, dtype=np.int32) * 977, copies))
+@pytest.mark.parametrize("distinct,copies", [(7, 1024), (7, 1025), (7, 2560), (7, 2561), (7, 4000), (157, 2560), (157, 2561)])
+def test_schedule_of_ids_given_many_times(ctx, distinct, copies):
+    """Some ids a few thousand times each fill their buckets, small ones or large ones, up to the last place and beyond; the others stay empty."""
+    ids = np.random.default_rng(copies).permutation(np.repeat(np.arange(distinct, dtype=np.int32) * 977, copies))
     got = ctx.epoch_schedule(_i32(ids), 11, 3)
     assert np.array_equal(got.cpu().numpy(), oracle.epoch_schedule(ids, 11, 3))
 
@@ -973,7 +970,7 @@ def test_two_stream_gathers_keep_their_place_in_both_streams(B, ctx, rows):
     assert stats.cpu().tolist() == [rows - missing.numel(), 0, missing.numel()]
 
 
-# One workgroup up to 4096 ids, with room for 3072 where that does, buckets of 512 on average up to 400,000, of 2048 above; a bucket of 256 to 512 with room for 1024.
+# One workgroup up to 4096 ids, with room for 3072 where that does, buckets of 256 to 512 ids up to 400,000, of 1024 to 2048 above.
 @pytest.mark.parametrize("n", [1025, 3071, 3072, 3073, 4096, 4097, 16_384, 16_385, 262_144, 400_000, 400_001])
 def test_schedule_bucket_sizes(ctx, n):
     log(f"[schedule sizes] n={n}")
@@ -981,7 +978,8 @@ def test_schedule_bucket_sizes(ctx, n):
     assert np.array_equal(ctx.epoch_schedule(_i32(ids), 21, 4).cpu().numpy(), oracle.epoch_schedule(ids, 21, 4))
 
 
-@pytest.mark.parametrize("in_bucket", [1000, 1024, 1025, 2048, 2500, 5000])
+# A small bucket's workgroup takes two rounds up to 1024 ids, five up to the 2560 that there is room for.
+@pytest.mark.parametrize("in_bucket", [1000, 1024, 1025, 2048, 2559, 2560, 2561, 5000])
 def test_schedule_small_bucket_with_more_ids_than_room(ctx, in_bucket):
     log(f"[small bucket] {in_bucket}")
     order = oracle.epoch_schedule(np.arange(2_000_000, dtype=np.int32), 21, 4)         # ascending by key: 7800 ids or so to each of 256 buckets

@@ -478,3 +478,18 @@ lines = log()
 assert [x.split("<")[0] for x in lines if x.startswith("launch")] == ["launch k_sched_sort"] * 2 and not [x for x in lines if "malloc" in x], lines
 assert schedule(c, 4097) == OOM
 """)
+
+
+@pytest.mark.parametrize("n,scatter,sort", [
+    (3072, None, "3072,true,1024,3072"), (4096, None, "4096,true,1024,4096"), (4097, "true,1", "2560,false,512,1024"),
+    (262_144, "true,1", "2560,false,512,1024"), (262_145, "true,4", "2560,false,512,1024"), (400_000, "true,4", "2560,false,512,1024"),
+    (400_001, "true,4", "2560,false,512,2560"), (8 << 20, "true,4", "2560,false,512,2560"), ((8 << 20) + 1, "false,4", "2560,false,512,2560")])
+def test_schedule_kernels(n, scatter, sort):
+    """Buckets of either size have room for 2560 ids."""
+    host_calls.run(f"""
+c = context()
+log()
+assert lib.rg_epoch_schedule(c, p(address()), i64({n}), u64(7), u32(1), p(address()), None) == OK
+got = [x[len("launch "):x.index(">") + 1] for x in log("launch k_sched_s") if "<" in x]
+assert got == ["k_sched_scatter<{scatter}>"] * {int(scatter is not None)} + ["k_sched_sort<{sort}>"], got
+""")
