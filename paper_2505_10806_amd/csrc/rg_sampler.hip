@@ -99,7 +99,8 @@ constexpr unsigned kTierSelfScan = 4096;     // workgroups up to which k_tier_em
 constexpr double kBytesEdgesNodes[2] = {4e12, 1.1e12};
 constexpr int64_t kBytesFit = 2 * 1000 * 1000;
 constexpr int64_t kBytesNodes = 4 << 20;
-// Two byte maps for all batches fit where slices' bitmaps do (sliced_bytes).
+// A byte map for all batches fits where slices' bitmaps do (sliced_bytes: up to kSliceWords words in all there is room for 32 maps, above for
+// kSliceGroups * kSliceWords words); the second one that kBytesSelfWords takes, below.
 inline bool rg_use_bytes(int64_t num_nodes, int64_t words, int64_t edges, int group) {
     return num_nodes <= kBytesNodes &&
            (double)edges * group * ((double)num_nodes * group) <= kBytesEdgesNodes[num_nodes * group >= kBytesFit] &&
@@ -109,6 +110,8 @@ inline bool rg_use_bytes(int64_t num_nodes, int64_t words, int64_t edges, int gr
 // 133 k nodes 37.4 us a call, 38.3 with a launch that counts, 177 k 60.1 / 58.7, 254 k 63.5 / 60.7, 486 k 75 / 62; eight on 119 k 82 / 86; four on
 // 59 k 66 / 71.
 constexpr int64_t kBytesSelfWords = 5000, kBytesSelfRead = 12 * 1000 * 1000;
+static_assert(2 * 32 * RG_MAX_GROUP * kBytesSelfWords <= (int64_t)kSliceGroups * kSliceWords * 4 && 2 * 32 <= kSliceGroups * 4,
+              "two byte maps of so many words fit");
 constexpr int kRankIds = 48;         // ids to a rank block, two to three bitmap words (see rg_rank_blocks)
 constexpr int kBaseIds = kRankIds * 1024;      // ids to a base: the members among them are counted in 16 bits
 static_assert(kBaseIds % (32 * kTierWords) == 0 && kBaseIds % (32 * kTierWordsSmall) == 0 && kTierWords % 3 == 0 && kTierWordsSmall % 3 == 0,
