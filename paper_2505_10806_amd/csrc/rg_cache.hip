@@ -54,21 +54,27 @@ __global__ void __launch_bounds__(256) k_histogram_seeds(const int32_t* __restri
 }
 
 constexpr int kSeedsBeside = 256;      // seeds per batch from which on k_hist_bounds counts them
+// Few batches get workgroups for kSeedRounds rounds of 256 seeds each, as far as all of them make kSeedBlocks workgroups to a compute unit (with one row
+// of the grid to a batch, two or three workgroups, 16 k seeds of 8 batches on 1 M nodes took 38 us a call, now 18, in a launch of their own 21, 65 k
+// 111 / 51 / 54); of many batches one row is enough (192 of 16 k on 10 M nodes 308, with four rounds each 327).
+constexpr int kSeedRounds = 4, kSeedBlocks = 4;
 
 // bounds[r * (ranges + 1) + j] = first entry of run r with an id >= j * range, as an index into the batch's list.  Consecutive
 // threads search one run for consecutive keys.  Bound by the lines the probes touch: ids sampled at random lie within a few
 // sqrt(len) / 2 entries of their proportional place and a correction from there ends a few entries away, so about four lines
 // per bound instead of the ten or more a bisection reads (any other run of ids only takes more steps): 295 k bounds in runs
 // of up to 283 k entries 19 us, with a bisection of the 4 sqrt(len) entries around the proportional place 41.
-// seed_batches: the first workgroups count the seeds of so many batches meanwhile, whose atomics wait for memory where the searches wait for
-// their probes: 192 batches of 1024 seeds, 393 k atomics, beside the 295 k bounds 29.6 us, in launches of their own 17.5 + 19.
+// seed_batches: the first workgroups, seed_rows rows of them to a batch, count the seeds of so many batches meanwhile, whose atomics wait for
+// memory where the searches wait for their probes: 192 batches of 1024 seeds, 393 k atomics, beside the 295 k bounds 29.6 us, in launches of their own 17.5 + 19.
 __global__ void __launch_bounds__(256) k_hist_bounds(const int32_t* __restrict__ nodes, int64_t batch_stride,
                                                      const int32_t* __restrict__ tier_off, int num_hops, int64_t num_nodes, int range,
-                                                     int ranges, int32_t* __restrict__ bounds, int seed_batches,
+                                                     int ranges, int32_t* __restrict__ bounds, int seed_batches, int seed_rows,
                                                      uint32_t* __restrict__ counts, uint32_t* __restrict__ first_batch) {
-    const int r = (int)blockIdx.y - seed_batches;
+    const int r = (int)blockIdx.y - seed_batches * seed_rows;
     if (r < 0) {
-        rg_count_seeds(nodes, batch_stride, tier_off, num_hops, blockIdx.y, blockIdx.x, gridDim.x, counts, first_batch);
+        int b = blockIdx.y, row = 0;
+        for (; b >= seed_batches; b -= seed_batches) ++row;
+        rg_count_seeds(nodes, batch_stride, tier_off, num_hops, b, row * gridDim.x + blockIdx.x, seed_rows * gridDim.x, counts, first_batch);
         return;
     }
     const int j = blockIdx.x * 256 + threadIdx.x;
@@ -1250,8 +1256,11 @@ rg_status rg_access_histogram_epoch(rg_ctx* ctx, const int32_t* nodes, int64_t b
     const RunStep by = {16 / num_hops, 16 % num_hops, kHistRunTile / num_hops, kHistRunTile % num_hops};
     const bool ahead = run_len >= (int64_t)kHistAhead * ranges;
     const int tok = rg_prof_begin(ctx, RG_K_HISTOGRAM, s);
-    // Batches of a workgroup's seeds or more are counted beside the bounds.
-    const bool beside = bounds && max_seeds >= kSeedsBeside && num_batches <= fit;
+    // Batches of a workgroup's seeds or more are counted beside the bounds, by some 64 workgroups each at most.
+    const int bound_blocks = (int)rg_div_up(ranges + 1, 256);
+    const int64_t seed_blocks = rg_min64(rg_min64(rg_div_up(max_seeds, 256 * kSeedRounds), 64), rg_div_up((int64_t)kSeedBlocks * ctx->num_cus, num_batches));
+    const int seed_rows = (int)rg_max64(1, (seed_blocks + bound_blocks / 2) / bound_blocks);
+    const bool beside = bounds && max_seeds >= kSeedsBeside && num_batches <= fit && (int64_t)num_batches * (num_hops + seed_rows) <= 65535;
     if (max_seeds > 0 && !beside) {
         dim3 seed_grid((unsigned)rg_min64(rg_div_up(max_seeds, 256), 64), (unsigned)num_batches);
         k_histogram_seeds<<<seed_grid, 256, 0, s>>>(nodes, batch_stride, tier_off, num_hops, counts, first_batch);
@@ -1261,8 +1270,8 @@ rg_status rg_access_histogram_epoch(rg_ctx* ctx, const int32_t* nodes, int64_t b
         const int32_t* list = nodes + (int64_t)b0 * batch_stride;
         const int32_t* tiers = tier_off + (int64_t)b0 * (num_hops + 2);
         if (bounds)
-            k_hist_bounds<<<dim3((unsigned)rg_div_up(ranges + 1, 256), (unsigned)(nb * num_hops + (beside ? nb : 0))), 256, 0, s>>>(
-                list, batch_stride, tiers, num_hops, num_nodes, range, ranges, bounds, beside ? nb : 0, counts, first_batch);
+            k_hist_bounds<<<dim3((unsigned)bound_blocks, (unsigned)(nb * (num_hops + (beside ? seed_rows : 0)))), 256, 0, s>>>(
+                list, batch_stride, tiers, num_hops, num_nodes, range, ranges, bounds, beside ? nb : 0, seed_rows, counts, first_batch);
 #define RG_LAUNCH_RUNS(FIRST, AHEAD)                                                                                      \
     k_histogram_runs<FIRST, AHEAD><<<ranges, 1024, 0, s>>>(list, batch_stride, tiers, bounds, nb, num_hops, b0, counts, first_batch, num_nodes, range, by)
         if (first_batch) { if (ahead) RG_LAUNCH_RUNS(true, true); else RG_LAUNCH_RUNS(true, false); }

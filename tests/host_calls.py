@@ -65,8 +65,8 @@ def gather(c, rows, dim, hit=0, miss=None, static=False):
     return call(c, p(address()), i64(rows), None, byref(cache), p(address()), i64(dim), p(address()), i64(dim), i32(dim), p(address()),
                 i64(dim), p(address()), p(hit), p(miss))
 
-def histogram(c, n, batches, hops, first=True, stream=0, stride=1 << 24):
-    return lib.rg_access_histogram_epoch(c, p(address()), i64(stride), p(address()), i32(batches), i32(hops), i32(100), p(address()),
+def histogram(c, n, batches, hops, first=True, stream=0, stride=1 << 24, seeds=100):
+    return lib.rg_access_histogram_epoch(c, p(address()), i64(stride), p(address()), i32(batches), i32(hops), i32(seeds), p(address()),
                                          p(address()) if first else None, i64(n), p(stream))
 '''
 

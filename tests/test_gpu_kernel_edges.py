@@ -352,6 +352,30 @@ def test_epoch_histogram_range_edges(B, ctx, n, batches, hops, skew):
     assert np.array_equal(counts.cpu().numpy().view(np.uint32), 2 * want)
 
 
+# Seeds beside the bounds: 256 to 1024 of them to a workgroup, more of many batches and above 65,536; workgroups of one row of the grid and of
+# several; batches of fewer seeds than the most.
+@pytest.mark.parametrize("n,batches,most", [(90_000, 300, 256), (90_000, 300, 1025), (300_000, 300, 3073), (90_000, 200, 65_537), (300_000, 100, 9000), (3_000_000, 20, 70_000)])
+def test_epoch_histogram_of_many_seeds(B, ctx, n, batches, most):
+    log(f"[histogram seeds] N={n} batches={batches} most={most}")
+    rng, tail = np.random.default_rng(most), 2000 if batches >= 100 else 50_000
+    arena = np.zeros((batches, most + 2 * tail), dtype=np.int32)
+    tier_offs = np.zeros((batches, 4), dtype=np.int32)
+    want, first = np.zeros(n, dtype=np.int64), np.full(n, 0xFFFFFFFF, dtype=np.uint32)
+    for b in range(batches):
+        seeds = most if b in (0, batches - 1) else int(rng.integers(0, most + 1)) * (b % 4 > 0)
+        parts = [rng.integers(0, n, seeds), np.sort(rng.choice(n, tail, replace=False)), np.sort(rng.choice(n, tail, replace=False))]
+        tier_offs[b, 1:] = np.cumsum([p.size for p in parts])
+        ids = np.concatenate(parts)
+        arena[b, :ids.size] = ids
+        want += np.bincount(ids, minlength=n)
+        first[ids] = np.minimum(first[ids], b)
+    counts = torch.zeros(n, dtype=torch.int32, device=DEV)
+    got_first = torch.full((n,), -1, dtype=torch.int32, device=DEV)
+    ctx.access_histogram_epoch(_i32(arena), _i32(tier_offs), batches, 2, most, counts, first_batch=got_first)
+    assert np.array_equal(counts.cpu().numpy(), want)
+    assert np.array_equal(got_first.cpu().numpy().view(np.uint32), first)
+
+
 # Segments of one wavefront's lanes, one more, one round of loads and one more, with and without bounds found first.
 @pytest.mark.parametrize("batches", [1, 10_000])
 def test_epoch_histogram_segment_lengths(B, ctx, batches):

@@ -493,3 +493,23 @@ assert lib.rg_epoch_schedule(c, p(address()), i64({n}), u64(7), u32(1), p(addres
 got = [x[len("launch "):x.index(">") + 1] for x in log("launch k_sched_s") if "<" in x]
 assert got == ["k_sched_scatter<{scatter}>"] * {int(scatter is not None)} + ["k_sched_sort<{sort}>"], got
 """)
+
+
+# Beside the bounds from 256 seeds on, 1024 to a workgroup of few batches, 64 workgroups to a batch at most, 1024 in all.
+@pytest.mark.parametrize("n,batches,seeds,stride,beside", [
+    (1_000_000, 8, 255, 150_000, False), (1_000_000, 8, 256, 150_000, True), (1_000_000, 8, 16_384, 150_000, True), (10_000_000, 8, 65_536, 600_000, True), (10_000_000, 8, 8192, 74_000, True),
+    (100_000, 64, 200_000, 600_000, True), (2_449_029, 192, 1024, 600_000, True), (2_449_029, 192, 20_000, 600_000, True), (300_000, 2000, 80_000, 30_000, True)])
+def test_seeds_beside_the_bounds(n, batches, seeds, stride, beside):
+    host_calls.run(f"""
+c = context()
+log()
+assert histogram(c, {n}, {batches}, 2, seeds={seeds}, stride={stride}) == OK
+lines = [x.split()[1:4] for x in log("launch")]
+own = [x for x in lines if x[0] == "k_histogram_seeds"]
+(_, gx, gy), = [x for x in lines if x[0] == "k_hist_bounds"]
+gx, rows = int(gx), int(gy) - {batches} * 2
+assert len(own) == {int(not beside)} and (rows > 0) == {beside}, lines
+if {beside}:
+    blocks = min(-(-{seeds} // 1024), 64, -(-1024 // {batches}))                 # whole rows of them
+    assert rows == {batches} * max(1, (blocks + gx // 2) // gx), lines
+""")
