@@ -1096,3 +1096,46 @@ def test_draws_of_33_to_64(B, ctx, n, fanouts, seeds, first_seen):
     for j, o in enumerate(outs):
         orc = oracle.sample_blocks(rp, ci, lists[j], fanouts, 77, 1, oracle.ORDER_FIRST_SEEN if first_seen else oracle.ORDER_ASCENDING)
         assert_batch_equal(HipBatch(o, len(fanouts)), orc, len(fanouts), f"batch {j}")
+
+
+# Plans from the sampler's bitmaps: 4096 workgroups of 256 words add up the counts in front of their own, more of them have these scanned.
+@pytest.mark.parametrize("n", [33_554_432, 33_554_433, 41_943_041])
+def test_plan_segments_behind_a_scan(B, ctx, n):
+    log(f"[plan scan] N={n}")
+    rng, fanouts, group = np.random.default_rng(n), (6, 4), 3
+    block = 256 * 32
+    active = np.unique(np.concatenate([np.arange(40), n // 2 + np.arange(-20, 20), 2 * block + np.arange(-3, 3), n - 1 - np.arange(40),
+                                       n // block * block - 1 - np.arange(40), rng.integers(0, n, 3000)]))
+    deg = np.zeros(n, dtype=np.int64)
+    deg[active] = rng.integers(0, 9, active.size)
+    rp = np.concatenate([[0], np.cumsum(deg)])
+    ci = rng.choice(active, rp[-1]).astype(np.int32)
+    csr = B.CsrGraph(torch.as_tensor(rp, device=DEV).to(torch.int32), _i32(ci))
+    remote = np.arange(n) % 3 > 0
+    remote[[0, n - 1]] = True
+    home = np.where(remote, np.cumsum(remote) - 1 - (1 << 31), np.cumsum(~remote) - 1).astype(np.int32)
+    n_remote = int(remote.sum())
+    cache = B.FeatureCache(n, n_remote, 1, DEV, mirror_rows=n_remote, home=_i32(home))
+    plan = B.PrefetchPlan(n_remote, 3, DEV)
+    plan.set_num_batches(3)
+    claimed = torch.zeros((n + 31) // 32, dtype=torch.int32, device=DEV)
+    seen, start = np.zeros(0, dtype=np.int64), 0
+    for seg in range(3):
+        seeds = [rng.permutation(active)[:300].astype(np.int32) if seg != 1 else np.array([0, n - 1], dtype=np.int32) for _ in range(group)]
+        outs = [B.BlockBuffers(n, ci.size, x.size, fanouts, DEV) for x in seeds]
+        ctx.sample_blocks_group(csr, [_i32(x) for x in seeds], fanouts, 11, seg, outs)
+        ctx.plan_sampled(group, cache, claimed, plan, seg)
+        named = np.unique(np.concatenate([oracle.sample_blocks(rp, ci, x, fanouts, 11, seg).input_nodes for x in seeds]))
+        new = np.setdiff1d(named, seen)
+        seen = np.union1d(seen, named)
+        rows = home[new[remote[new]]] & 0x3FFFFFFF
+        offs = plan.offsets.cpu().numpy()
+        assert offs[seg] == start and offs[seg + 1] == start + rows.size, (seg, offs[:4], rows.size)
+        pairs = plan.list[2 * start:2 * (start + rows.size)].cpu().numpy().reshape(-1, 2)
+        assert np.array_equal(pairs[:, 0], rows) and np.array_equal(pairs[:, 1], rows)
+        words = claimed.cpu().numpy().view(np.uint32)
+        want = np.zeros(words.size, dtype=np.uint32)
+        np.bitwise_or.at(want, seen >> 5, np.uint32(1) << (seen & 31).astype(np.uint32))
+        assert np.array_equal(words, want)
+        start += rows.size
+    assert start > 1000

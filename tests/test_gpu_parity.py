@@ -494,7 +494,7 @@ def test_plan_segments_from_sampler_bitmaps(B, ctx):
 @pytest.mark.parametrize("first_seen", [False, True])
 @pytest.mark.parametrize("n_nodes,group", [(33, 1), (33, 5), (700, 16), (70_001, 3), (70_001, 8)])
 def test_plan_segments_ragged_sizes(B, ctx, n_nodes, group, first_seen):
-    """rg_plan_sampled where the bitmaps end inside a word, span one or several 1024-word blocks and a ragged last one,
+    """rg_plan_sampled where the bitmaps end inside a word, span one or several 256-word blocks and a ragged last one,
     for groups of 1 to 16 batches (one of them empty) in either node order; home words drawn at random.  Two calls:
     the second segment holds only what the first has not claimed."""
     log(f"[plan ragged] N={n_nodes} group={group} first_seen={first_seen}")
