@@ -973,12 +973,11 @@ __global__ void __launch_bounds__(kPlanChunk) k_plan_block_scatter(const int32_t
             }
         } else {
             mine = total[threadIdx.x];
-            earlier = hist[(int64_t)threadIdx.x * nblocks + blockIdx.x];
         }
     }
     const int before = rg_block_excl_scan<NW>(mine, smem, &sum);      // its barriers also end the clearing of cnt
     if ((int)threadIdx.x < n_seg) {
-        key_base[threadIdx.x] = before + earlier;
+        key_base[threadIdx.x] = before + (by_chunk ? earlier : hist[(int64_t)threadIdx.x * nblocks + blockIdx.x]);
         if (blockIdx.x == 0) offsets[threadIdx.x] = before;
     }
     if (blockIdx.x == 0 && threadIdx.x == 0) offsets[n_seg] = sum;
