@@ -1008,27 +1008,30 @@ __global__ void __launch_bounds__(kPlanChunk) k_plan_block_scatter(const int32_t
 // group is the first to name are the new bits of their union against `claimed` (all nodes any earlier group named)
 // whose home is the remote store: two streaming passes over N/32 words and one home[] lookup per new node, instead of
 // one lookup and one probe per input node of every batch.  The pairs come out ascending by node id, i.e. by remote row.
-// A workgroup takes kClaimWords words; a wavefront asks for the home words of two of them at a time, a lane per id, kClaimPairs steps
-// together.  (With a thread per word, which asked for one id after the other, a call that names most nodes waited 32 times in a row: eight
-// batches of 4096 seeds (15,10,5) on 1 M nodes 75 us, now 16; on 10 M 92 / 35.)
-constexpr int kClaimWords = 256, kClaimPairs = 8;
+// A workgroup takes kClaimWords words, a lane one of them, whose ids' home words it asks for kClaimIds at a time: few instructions where there are few
+// ids to a word, and every lane has lines on their way.  Calls with nothing claimed before, (15,10), clearing `claimed` included; four words to a lane and
+// one id at a time / a lane per id, 64 of them together / now: 8 batches of 4096 seeds on 1 M nodes 56 / 20 / 15 us, on 10 M 53 / 39 / 25, 2 of them on
+// 10 M 28 / 33 / 15, one of 1024 on 4 M 17.6 / 18.6 / 12.0; with 8 ids at a time the same or 3 % more.
+constexpr int kClaimWords = 256, kClaimIds = 4;
+static_assert(kClaimWords == 256, "a lane per word");
 constexpr int kClaimSelfScan = 4096;        // workgroups up to which the emit adds up the counts in front of its own itself
-static_assert(kClaimWords == 256 && kClaimWords / 2 % (4 * kClaimPairs) == 0, "a thread per word, whole steps of the four wavefronts");
 
-// f(pair, lane's id, lane's bit, its home word) for the pairs of words of the workgroup that this wavefront takes.
+// f(number, id, its home word) for the ids of a lane's word.
 template <typename F>
-__device__ __forceinline__ void rg_claim_pairs(const uint32_t* bits, int64_t w0, const int32_t* __restrict__ home, F f) {
-    const int lane = rg_lane();
-    for (int p0 = (threadIdx.x >> 6) * (kClaimWords / 8); p0 < ((int)(threadIdx.x >> 6) + 1) * (kClaimWords / 8); p0 += kClaimPairs) {
-        uint32_t hw[kClaimPairs];
-        bool set[kClaimPairs];
+__device__ __forceinline__ void rg_claim_ids(uint32_t bits, int64_t word, const int32_t* __restrict__ home, F f) {
+    for (int k = 0; bits != 0u; k += kClaimIds) {
+        int id[kClaimIds];
+        uint32_t hw[kClaimIds];
 #pragma unroll
-        for (int q = 0; q < kClaimPairs; ++q) {
-            set[q] = (bits[2 * (p0 + q) + (lane >> 5)] >> (lane & 31)) & 1u;
-            hw[q] = set[q] ? (uint32_t)home[((w0 + 2 * (p0 + q)) << 5) + lane] : 0u;
+        for (int q = 0; q < kClaimIds; ++q) {
+            id[q] = __ffs(bits) - 1;
+            bits &= bits - 1u;
         }
 #pragma unroll
-        for (int q = 0; q < kClaimPairs; ++q) f(p0 + q, lane, set[q], hw[q]);
+        for (int q = 0; q < kClaimIds; ++q) hw[q] = id[q] >= 0 ? (uint32_t)home[(word << 5) + id[q]] : 0u;
+#pragma unroll
+        for (int q = 0; q < kClaimIds; ++q)
+            if (id[q] >= 0) f(k + q, id[q], hw[q]);
     }
 }
 
@@ -1036,9 +1039,8 @@ __device__ __forceinline__ void rg_claim_pairs(const uint32_t* bits, int64_t w0,
 __global__ void __launch_bounds__(256) k_claim_count(const uint32_t* __restrict__ visited, int64_t words, int group,
                                                      uint32_t* __restrict__ claimed, uint32_t* __restrict__ newbits,
                                                      const int32_t* __restrict__ home, int32_t* __restrict__ blk_count) {
-    __shared__ uint32_t bits[kClaimWords];
     __shared__ int part[4];
-    const int64_t w0 = (int64_t)blockIdx.x * kClaimWords, w = w0 + threadIdx.x;
+    const int64_t w = (int64_t)blockIdx.x * kClaimWords + threadIdx.x;
     uint32_t nw = 0u;
     if (w < words) {
         uint32_t u = 0u;
@@ -1047,17 +1049,12 @@ __global__ void __launch_bounds__(256) k_claim_count(const uint32_t* __restrict_
         nw = u & ~old;
         if (nw) claimed[w] = old | nw;
     }
-    bits[threadIdx.x] = nw;
-    __syncthreads();
-    int c = 0;
-    rg_claim_pairs(bits, w0, home, [&](int pair, int lane, bool set, uint32_t hw) {
-        const unsigned long long m = __ballot(set && (hw >> RG_TAG_SHIFT) == RG_TAG_REMOTE);
-        if (lane < 2) bits[2 * pair + lane] = (uint32_t)(m >> (32 * lane));            // (this wavefront's own words)
-        c += __popcll(m);
-    });
+    uint32_t remote = 0u;
+    rg_claim_ids(nw, w, home, [&](int, int id, uint32_t hw) { remote |= (uint32_t)((hw >> RG_TAG_SHIFT) == RG_TAG_REMOTE) << id; });
+    if (w < words) newbits[w] = remote;
+    const int c = rg_wave_sum(__popc(remote));
     if (rg_lane() == 0) part[threadIdx.x >> 6] = c;
     __syncthreads();
-    if (w < words) newbits[w] = bits[threadIdx.x];
     if (threadIdx.x == 0) blk_count[blockIdx.x] = part[0] + part[1] + part[2] + part[3];
 }
 
@@ -1085,8 +1082,6 @@ __global__ void __launch_bounds__(1024) k_claim_scan(int32_t* __restrict__ blk_c
 __global__ void __launch_bounds__(256) k_claim_emit(const uint32_t* __restrict__ newbits, int64_t words, const int32_t* __restrict__ home,
                                                     const int32_t* __restrict__ blk_count, int scanned, int32_t* __restrict__ seg_off,
                                                     int64_t list_capacity, int32_t* __restrict__ list) {
-    __shared__ uint32_t bits[kClaimWords];
-    __shared__ int first[kClaimWords];                                // new ids in front of the word
     __shared__ int smem[256 / RG_WAVE + 1];
     __shared__ int part[2][4];
     int before = 0, all = 0;
@@ -1102,11 +1097,10 @@ __global__ void __launch_bounds__(256) k_claim_emit(const uint32_t* __restrict__
     before = rg_wave_sum(before);
     all = rg_wave_sum(all);
     if (rg_lane() == 0) { part[0][threadIdx.x >> 6] = before; part[1][threadIdx.x >> 6] = all; }
-    const int64_t w0 = (int64_t)blockIdx.x * kClaimWords, w = w0 + threadIdx.x;
+    const int64_t w = (int64_t)blockIdx.x * kClaimWords + threadIdx.x;
     const uint32_t nw = w < words ? newbits[w] : 0u;
-    bits[threadIdx.x] = nw;
     int total;
-    first[threadIdx.x] = rg_block_excl_scan<256 / RG_WAVE>(__popc(nw), smem, &total);       // its barriers publish part[]
+    const int first = rg_block_excl_scan<256 / RG_WAVE>(__popc(nw), smem, &total);          // its barriers publish part[]
     all = part[1][0] + part[1][1] + part[1][2] + part[1][3];
     // a list that cannot take the segment (it holds one pair per remote row, so this means a caller error) gets an
     // empty segment instead of an overrun
@@ -1114,13 +1108,9 @@ __global__ void __launch_bounds__(256) k_claim_emit(const uint32_t* __restrict__
     const bool fits = begin + all <= list_capacity;
     if (blockIdx.x == 0 && threadIdx.x == 0) seg_off[1] = (int32_t)(fits ? begin + all : begin);
     if (!fits || total == 0) return;                                  // uniform
-    __syncthreads();
-    list += 2 * (begin + part[0][0] + part[0][1] + part[0][2] + part[0][3]);
-    rg_claim_pairs(bits, w0, home, [&](int pair, int lane, bool set, uint32_t hw) {
-        if (!set) return;
-        const int word = 2 * pair + (lane >> 5);
-        const int64_t j = first[word] + __popc(bits[word] & ((1u << (lane & 31)) - 1u));
-        list[2 * j] = list[2 * j + 1] = (int32_t)(hw & RG_ROW_MASK);  // mirrored cache: the row's place is its remote-store row
+    list += 2 * (begin + part[0][0] + part[0][1] + part[0][2] + part[0][3] + first);
+    rg_claim_ids(nw, w, home, [&](int k, int, uint32_t hw) {
+        list[2 * k] = list[2 * k + 1] = (int32_t)(hw & RG_ROW_MASK);  // mirrored cache: the row's place is its remote-store row
     });
 }
 
