@@ -87,13 +87,16 @@ constexpr int kEmitThreadsSmall = 384;       // of up to 6144 new ids wait to be
 constexpr unsigned kTierSelfScan = 4096;     // workgroups up to which k_tier_emit adds up the counts in front of its own itself
 // kTierBytes saves launches (two hops 6 instead of 10, or 8 where the tiers are counted by launches of their own), which are what bounds calls
 // of few edges, on the host as on the device; its stores cost 9 ps each, more where the bytes of all batches, which every hop clears and reads,
-// outgrow an XCD's L2 (two maps of 2 MB).  So the line is by the product of the batches' edges and nodes, and lower from 2 M nodes in all on;
-// whole call, bytes against slices:
+// outgrow an XCD's L2 (two maps of 2 MB).  So the line is by the product of the batches' edges and nodes, and lower from 2 M nodes in all on, below
+// the calls that lose; whole call, bytes against slices:
 //   below it   one batch of 356 k edges on 186 k nodes 59 / 77 us, 459 k on 40 k 58 / 83, 299 k on 254 k 61 / 78, 1.4 M on 673 k 88 / 110, 30 k on
 //              865 k 43 / 55, 80 k on 2 M 48 / 61; two of 527 k on 236 k 73 / 88, of 486 k on 972 k 86 / 96; four of 285 k on 59 k 66 / 85;
 //              eight of 61 k on 209 k 50 / 56, of 246 k on 119 k 81 / 90, of 25 k on 583 k 48 / 55
-//   above it   two of 190 k on 2.3 M 61 / 72, of 286 k on 3.1 M 69 / 72, four of 75 k on 1.9 M 60 / 65, two of 670 k on 1.8 M 87 / 82, of 1 M on
-//              1.1 M 121 / 126, one of 3.1 M on 2.8 M 165 / 148, two of 1 M on 3.1 M 150 / 133, four of 419 k on 1.6 M 103 / 89, eight of 178 k on 2.2 M 103 / 89
+//   above it   two of 670 k on 1.8 M 87 / 82, one of 3.1 M on 2.8 M 165 / 148, two of 1 M on 3.1 M 150 / 133, four of 419 k on 1.6 M 103 / 89, eight of
+//              178 k on 2.2 M 103 / 89, two of 1 M on 1.1 M 121 / 126
+//   from 2 M nodes in all on, between 1.1e12 and 4e12, either: one of 390 k on 4.1 M 62 / 74, of 397 k on 2.8 M 82 / 100, of 344 k on 3.8 M 85 / 101, two of
+//              127 k on 3.3 M 60 / 68, four of 118 k on 1.0 M 62 / 72, eight of 78 k on 263 k 53 / 59; two of 623 k on 1.4 M 103 / 100, and where few edges
+//              would take the atomic way (rg_use_slices) four of 25 k on 2.7 M 55 / 49, of 21 k on 3.8 M 80 / 68, three of 58 k on 4.0 M 81 / 77
 // An atomic on a bitmap in place of the byte makes words that many edges name queue up (dense-social batch 95 / 57); above 4 Mi nodes, where few
 // edges take it, it reads an eighth (one batch on 5-11 M nodes 46-52 us, with bytes 52-61).
 constexpr double kBytesEdgesNodes[2] = {4e12, 1.1e12};
