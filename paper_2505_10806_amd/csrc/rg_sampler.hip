@@ -228,6 +228,73 @@ __global__ void __launch_bounds__(1024) k_sched_scatter(const int32_t* __restric
     }
 }
 
+// The m ids of a bucket (SINGLE: of the call) to their places, in PER rounds of T.
+template <int PER, bool SINGLE, int T, int SUB_BITS>
+__device__ __forceinline__ void rg_sched_finish(const int32_t* __restrict__ train_ids, const uint2* __restrict__ pairs, int64_t m, uint32_t epoch, uint32_t k0,
+                                                uint32_t k1, uint32_t* sk, int32_t* si, int32_t* sub, int* smem, int32_t* out) {
+    constexpr int SUB = 1 << SUB_BITS;
+    const auto full_key = [&](int32_t v) { return rg_sched_key(v, epoch, k0, k1); };
+    uint32_t key[PER];
+    int32_t id[PER], rank[PER];
+    for (int b = threadIdx.x; b <= SUB; b += T) sub[b] = 0;
+#pragma unroll
+    for (int j = 0; j < PER; ++j) {
+        const int i = j * T + threadIdx.x;
+        if (i < m) {
+            if (SINGLE) {
+                id[j] = train_ids[i];
+                key[j] = (uint32_t)(full_key(id[j]) >> 32);
+            } else {
+                const uint2 x = pairs[i];
+                key[j] = x.x;
+                id[j] = (int32_t)x.y;
+            }
+        }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < PER; ++j)
+        if (j * T + (int)threadIdx.x < m) rank[j] = atomicAdd(&sub[key[j] >> (32 - SUB_BITS)], 1);
+    __syncthreads();
+    int mine[SUB / T], sum = 0;                                          // counts -> starts, SUB / T consecutive ones per thread
+#pragma unroll
+    for (int q = 0; q < SUB / T; ++q) { mine[q] = sub[threadIdx.x * (SUB / T) + q]; sum += mine[q]; }
+    int total;
+    int at = rg_block_excl_scan<T / RG_WAVE>(sum, smem, &total);         // its barriers separate the reads from the writes
+#pragma unroll
+    for (int q = 0; q < SUB / T; ++q) { sub[threadIdx.x * (SUB / T) + q] = at; at += mine[q]; }
+    if (threadIdx.x == T - 1) sub[SUB] = at;
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < PER; ++j)
+        if (j * T + (int)threadIdx.x < m) {
+            const int p = sub[key[j] >> (32 - SUB_BITS)] + rank[j];
+            sk[p] = key[j];
+            si[p] = id[j];
+        }
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < PER; ++j)
+        if (j * T + (int)threadIdx.x < m) {
+            const int b = (int)(key[j] >> (32 - SUB_BITS));
+            const int lo = sub[b], hi = sub[b + 1], me = lo + rank[j];
+            int place = lo;
+            for (int q = lo; q < hi; ++q) {
+                if (sk[q] != key[j]) {
+                    place += sk[q] < key[j];
+                } else if (q != me) {
+                    if (si[q] == id[j]) {                                // (equal pairs, which distinct ids do not give, keep their places)
+                        place += q < me;
+                    } else {
+                        const uint64_t mine_ = full_key(id[j]), other = full_key(si[q]);
+                        place += other != mine_ ? other < mine_ : si[q] < id[j];
+                    }
+                }
+            }
+            out[place] = id[j];
+        }
+}
+
 // One workgroup per bucket: its pairs in order, the ids to their final places.  CAP: pairs it has room for in LDS; up to FEW of them take fewer
 // rounds (100 k ids 10.0 us, with those for 2560 10.1 to 10.5).
 // SINGLE: one bucket, the n train ids themselves.  start == NULL: the workgroup adds up the counts in front of its own.
@@ -327,70 +394,8 @@ __global__ void __launch_bounds__(T) k_sched_sort(const int32_t* __restrict__ tr
         }
         return;
     }
-    const auto sort = [&](auto rounds) {                              // of T pairs
-        constexpr int PER = decltype(rounds)::value;
-        uint32_t key[PER];
-        int32_t id[PER], rank[PER];
-        for (int b = threadIdx.x; b <= SUB; b += T) sub[b] = 0;
-#pragma unroll
-        for (int j = 0; j < PER; ++j) {
-            const int i = j * T + threadIdx.x;
-            if (i < m) {
-                if (SINGLE) {
-                    id[j] = train_ids[i];
-                    key[j] = (uint32_t)(full_key(id[j]) >> 32);
-                } else {
-                    const uint2 x = pairs[bucket * CAP + i];
-                    key[j] = x.x;
-                    id[j] = (int32_t)x.y;
-                }
-            }
-        }
-        __syncthreads();
-#pragma unroll
-        for (int j = 0; j < PER; ++j)
-            if (j * T + (int)threadIdx.x < m) rank[j] = atomicAdd(&sub[key[j] >> (32 - kSubBits)], 1);
-        __syncthreads();
-        int mine[SUB / T], sum = 0;                                          // counts -> starts, SUB / T consecutive ones per thread
-#pragma unroll
-        for (int q = 0; q < SUB / T; ++q) { mine[q] = sub[threadIdx.x * (SUB / T) + q]; sum += mine[q]; }
-        int total;
-        int at = rg_block_excl_scan<T / RG_WAVE>(sum, smem, &total);         // its barriers separate the reads from the writes
-#pragma unroll
-        for (int q = 0; q < SUB / T; ++q) { sub[threadIdx.x * (SUB / T) + q] = at; at += mine[q]; }
-        if (threadIdx.x == T - 1) sub[SUB] = at;
-        __syncthreads();
-#pragma unroll
-        for (int j = 0; j < PER; ++j)
-            if (j * T + (int)threadIdx.x < m) {
-                const int p = sub[key[j] >> (32 - kSubBits)] + rank[j];
-                sk[p] = key[j];
-                si[p] = id[j];
-            }
-        __syncthreads();
-#pragma unroll
-        for (int j = 0; j < PER; ++j)
-            if (j * T + (int)threadIdx.x < m) {
-                const int b = (int)(key[j] >> (32 - kSubBits));
-                const int lo = sub[b], hi = sub[b + 1], me = lo + rank[j];
-                int place = lo;
-                for (int q = lo; q < hi; ++q) {
-                    if (sk[q] != key[j]) {
-                        place += sk[q] < key[j];
-                    } else if (q != me) {
-                        if (si[q] == id[j]) {                                // (equal pairs, which distinct ids do not give, keep their places)
-                            place += q < me;
-                        } else {
-                            const uint64_t mine_ = full_key(id[j]), other = full_key(si[q]);
-                            place += other != mine_ ? other < mine_ : si[q] < id[j];
-                        }
-                    }
-                }
-                out[place] = id[j];
-            }
-    };
-    if (FEW < CAP && m <= FEW) sort(std::integral_constant<int, FEW / T>{});
-    else sort(std::integral_constant<int, CAP / T>{});
+    if (FEW < CAP && m <= FEW) rg_sched_finish<FEW / T, SINGLE, T, kSubBits>(train_ids, pairs + bucket * CAP, m, epoch, k0, k1, sk, si, sub, smem, out);
+    else rg_sched_finish<CAP / T, SINGLE, T, kSubBits>(train_ids, pairs + bucket * CAP, m, epoch, k0, k1, sk, si, sub, smem, out);
 }
 
 // ---------------------------------------------------------------------------- batches of a group
